@@ -133,8 +133,10 @@ void fill_head_order(sta::HeadOrder *o, const int *window_tiles, int head_base, 
 {
     double cost[sta::kMaxHeadsPerLaunch];
     for (int h = 0; h < heads; ++h) {
+        const int *w = window_tiles + 3 * (head_base + h);
         o->h[h] = (uint16_t)h;
-        cost[h] = kept_pairs_of_head(n, window_tiles + 3 * (head_base + h));
+        // heads that share a window are usually neighbours
+        cost[h] = h > 0 && w[0] == w[-3] && w[1] == w[-2] && w[2] == w[-1] ? cost[h - 1] : kept_pairs_of_head(n, w);
     }
     for (int i = 1; i < heads; ++i) {          // insertion sort: at most 256 entries
         const uint16_t hi = o->h[i];

@@ -1,4 +1,4 @@
-// Sliding Tile Attention forward kernel for gfx950 (MI355X).
+// Sliding Tile Attention forward kernels for gfx950 (MI355X).
 //
 // What is computed: Eq. 1 of the paper (S = QK^T/sqrt(d), A = softmax(S + M),
 // O = AV) where M keeps, for each query tile, exactly the key tiles inside the
@@ -16,7 +16,7 @@
 // index is only a summation index, so the keys are fed in the order the
 // accumulator layout holds them and V^T is stored in LDS in that same order.
 //
-// MFMA: v_mfma_f32_32x32x16_bf16.  Operand layout (lane l, lo = l%32, hb = l/32):
+// MFMA of the general kernel: v_mfma_f32_32x32x16_bf16.  Operand layout (lane l, lo = l%32, hb = l/32):
 //   A (32 x 16): row lo,  k = 8*hb .. 8*hb+7
 //   B (16 x 32): col lo,  k = 8*hb .. 8*hb+7
 //   C (32 x 32): col lo,  row = 8*g + 4*hb + t for register r = 4*g + t.
@@ -26,6 +26,7 @@
 #include "sta_device_util.h"
 #include "sta_geometry.h"
 #include "sta_internal.h"
+#include "sta_staged.h"
 
 namespace {
 
@@ -392,440 +393,391 @@ __device__ __forceinline__ FwdItem fwd_item_of(uint32_t id, const sta::FwdParams
 template <int D>
 __host__ __device__ __forceinline__ size_t split_part_floats(int QB) { return (size_t)QB * (D + 2); }
 
-// ---------------------------------------------------------------------------
-// Fast path: head dim 128 or 64.  NW waves x 32 queries per workgroup (one query block per wave; at least two waves
-// per SIMD on a CU, so one wave's softmax overlaps another's MFMAs), K/V sub-blocks of KB keys DMA'd
-// HBM/L2 -> LDS with global_load_lds (no staging registers), STAGES-deep, one barrier per sub-block.  LDS holds
-// K and V row-major, 2*D bytes per key, with the 16-byte chunks of each row XOR-swizzled so that both the b128
-// K-operand reads and the transposing ds_read_b64_tr_b16 V-operand reads are bank-conflict free:
-//   D = 128 (a row spans all 64 banks):  K: chunk c of row r sits at position c ^ (r & 15)
-//                                        V: chunk c of row r sits at position c ^ ((r & 3) << 2)
-//   D = 64 (two rows span the banks):    K: c ^ ((r >> 1) & 7)      V: c ^ (((r >> 1) & 1) << 2)
-// (16 lanes of a b128 read take rows r..r+15 at one logical chunk: they must land on 16 different 16-byte bank
-// groups; 32 lanes of a transposing read take 4 rows x 4 consecutive chunks: likewise.)
-// Instances in use (<D, NW, KB, STAGES, MINB>), chosen in launch_forward: D = 128: <128, 12, 32, 2, 1> for 384-token
-// tiles (one 12-wave workgroup per query tile and per CU) and <128, 4, 32, 2, 3> for other multiples of 128 (three
-// 4-wave workgroups per CU; 32-key sub-blocks measured 3-5 % faster than 64-key ones in this shape); D = 64:
-// <64, 12, 64, 2, 1>, <64, 4, 64, 2, 3> and, for other multiples of 64 tokens, <64, 2, 32, 2, 3>.
-// ---------------------------------------------------------------------------
-template <int D>
-__device__ __forceinline__ constexpr int k_swizzle(int row) { return D == 128 ? (row & 15) : ((row >> 1) & 7); }
-template <int D>
-__device__ __forceinline__ constexpr int v_swizzle(int row) { return D == 128 ? ((row & 3) << 2) : (((row >> 1) & 1) << 2); }
-
-template <int D, int NW, int KB, int STAGES, int MINB>
-__global__ __launch_bounds__(NW * 64, MINB) void sta_fwd_fast_kernel(const bf16_raw *__restrict__ q,
-                                                                 const bf16_raw *__restrict__ k,
-                                                                 const bf16_raw *__restrict__ v,
-                                                                 bf16_raw *__restrict__ o, sta::FwdParams p,
-                                                                 sta::WindowTable win, sta::HeadOrder order,
-                                                                 uint32_t n_bh)
+// The same for the key-group kernel, with every division by a launch constant prepared by the host (found by division in the
+// kernel, the item, its box and the start of the walk took 7500 cycles of a workgroup that has 24,000 cycles of work to do,
+// a 64-token image tile at window 3x3; now 2000, most of it waiting for the kernel arguments) and two differences.  The
+// launch's items, taken head after head in scheduling order, are dealt to the XCDs in chunks of about an eighth of a head:
+// where a head has only a few items, whole eighths of every head would leave XCDs without work (nine items: one XCD gets
+// two, the others one).  And the tile's coordinates come out directly.
+struct GroupItem {
+    bool valid;
+    size_t bh;
+    uint32_t qblock;
+    StaBox box;
+};
+__device__ __forceinline__ uint32_t fast_div(uint32_t n, const sta::FastDiv &f)
 {
-    static_assert(D == 128 || D == 64, "head dimension");
-    constexpr int QB = NW * 32;                    // queries per workgroup: one 32-query block per wave
-    constexpr int MB = KB / 32;
-    constexpr int KS = D / 16;
-    constexpr int DB = D / 32;
-    constexpr int ROWB = D * 2;                    // bytes per key row in LDS
-    constexpr int TILE_BYTES = KB * ROWB;          // one K (or V) sub-block
-    constexpr int STAGE_BYTES = 2 * TILE_BYTES;    // K then V
-    constexpr int INSTR = TILE_BYTES / 1024;       // 1 KB DMA instructions per operand per sub-block
-    constexpr int WANT_LOADERS = NW < 4 ? NW : (NW < 8 ? 4 : 8);
-    constexpr int LOADERS = WANT_LOADERS < INSTR ? WANT_LOADERS : INSTR;     // waves 0 .. LOADERS-1 issue the DMA
-    constexpr int LOADS = INSTR / LOADERS;         // ... this many instructions per operand each
-    constexpr int RPI = 1024 / ROWB;               // key rows per DMA instruction (4 or 8)
-    constexpr int IPB = 16 / RPI;                  // DMA instructions per block of 16 rows
-    constexpr int LPR = ROWB / 16;                 // lanes (16-byte chunks) per row
-    static_assert(KB % 32 == 0 && INSTR % LOADERS == 0 && LOADS >= 1 && LOADERS <= NW && LOADERS % IPB == 0,
-                  "sub-block shape");
-    static_assert(STAGES >= 2 && STAGES <= 4, "LDS stages");
+    const uint32_t q = __umulhi(n, f.magic);
+    return (((n - q) >> f.pre) + q) >> f.post;
+}
+__device__ __forceinline__ GroupItem group_item_of(uint32_t id, const sta::FwdParams &p, const sta::FwdPlan &plan)
+{
+    GroupItem it;
+    const uint32_t xcd = id & 7, slot = id >> 3;
+    const uint32_t chunk = fast_div(slot, plan.chunk);
+    const uint32_t linear = (chunk * 8 + xcd) * plan.chunk.d + (slot - chunk * plan.chunk.d);
+    it.valid = linear < plan.total;
+    if (!it.valid) return it;
+    const uint32_t rank = fast_div(linear, plan.per_head), pos = linear - rank * plan.per_head.d;
+    const uint32_t head_rank = fast_div(rank, plan.batch);                  // batch entries of one head are adjacent
+    const sta::FwdPlan::Head head = plan.head[head_rank];
+    const uint32_t sched = fast_div(pos, plan.per_tile), sub = pos - sched * plan.per_tile.d;
+    const uint32_t hp = fast_div(sched, plan.pair_items), rem = sched - hp * plan.pair_items.d;
+    const uint32_t col = fast_div(rem, plan.n_t), t = rem - col * plan.n_t.d;
+    const bool two_rows = 2 * hp + 1 < p.n_h;
+    const uint32_t w = two_rows ? col >> 1 : col, h = 2 * hp + (two_rows ? col & 1 : 0);
+    it.qblock = ((t * p.n_h + h) * p.n_w + w) * plan.per_tile.d + sub;
+    it.bh = (size_t)(rank - head_rank * plan.batch.d) * p.H + p.head_base + head.h;
+    it.box.t = sta_axis_range(p.n_t, head.w[0], t);
+    it.box.h = sta_axis_range(p.n_h, head.w[1], h);
+    it.box.w = sta_axis_range(p.n_w, head.w[2], w);
+    return it;
+}
 
-    // the K/V stages; at the end every wave passes its 32 output rows (32 * ROWB bytes) through the same memory
-    constexpr int OUT_BYTES = QB * ROWB;
-    __shared__ __attribute__((aligned(1024))) char smem[STAGES * STAGE_BYTES > OUT_BYTES ? STAGES * STAGE_BYTES : OUT_BYTES];
+// ---------------------------------------------------------------------------
+// The key-group kernel: head dimension 64 at every tile size, head dimension 128 where the tile is not a multiple of 128
+// tokens.  A workgroup is QW waves of 32 queries (one query block) times KG key groups: the groups share the queries and
+// take one KG-th of the walk each, with LDS stages of their own, and their partial results are merged through LDS at the
+// end.  KG = 1 where the launch fills the chip; KG = 2 or 4 makes more waves of few queries, for launches that would leave
+// it idle.
+//
+// v_mfma_f32_16x16x32_bf16.  A lane holds column c16 = lane & 15 of a 16x16 result (a query) and its rows 4*g4 .. 4*g4+3
+// (g4 = lane >> 4); a wave's 32 queries are two blocks of 16 and every K and V fragment read from LDS feeds both.  The
+// score accumulators start at minus the exponent offset (Sinit).  Row sums are a matrix product too, with an operand of
+// ones: v_dot2_f32_bf16 runs on the matrix pipe as well and eight of them take longer than the two matrix instructions.
+// The LDS layouts (Staged for V, StagedRows for K) leave five operand addresses per wave, to which the stage is added.
+//
+// What bounds it.  Head dimension 64: a unit (32 keys) is 18 matrix instructions (288 cycles of the matrix pipe) next to 49
+// vector instructions, 16 of them exponentials; measured 350 cycles per wave and unit on 64-token image tiles with four
+// waves per SIMD.  30x48x80 grid, 24 heads, 384-token tiles, window 3x3x3: 7.00-7.15 ms with the 12-wave kernel on
+// v_mfma_f32_32x32x16_bf16 that was here before, 6.69-6.83 ms with QW = 4 (1090 TFLOP/s; QW = 12: 7.5 ms, QW = 2: 7.3 ms,
+// 64 keys per barrier: 6.9-7.0 ms; row sums by v_dot2: 7.2 ms).  128 heads of a 64x64 image in 8x8 tiles, window 3x3:
+// 105-109 us before, 98-100 us.  Head dimension 128, 96-token tiles (10x30x56, 10 slices, windows 3x3x3 and 2x4x3): 2390 us
+// with the register-staged kernel that served it before, 254-262 us (1100 TFLOP/s).
+// A third LDS stage (DMA two units ahead, waited for by count behind a bare s_barrier, which __syncthreads() does not
+// allow: it waits for every outstanding DMA) changes nothing at four waves per SIMD and costs occupancy on small tiles:
+// 6.77 against 6.73 ms, 108 against 98 us.
+// ---------------------------------------------------------------------------
+template <int D, int QW, int KG, int WPE>
+__global__ __attribute__((amdgpu_flat_work_group_size(QW * KG * 64, QW * KG * 64), amdgpu_waves_per_eu(WPE)))
+void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
+                                                                         const bf16_raw *__restrict__ k,
+                                                                         const bf16_raw *__restrict__ v,
+                                                                         bf16_raw *__restrict__ o, sta::FwdParams p,
+                                                                         sta::FwdPlan plan)
+{
+    using L = Staged<D>;                                    // V; K is read by rows only
+    using R = StagedRows<D>;
+    constexpr int KS = L::KS, CB = L::CB;
+    constexpr int NQ = 2;                                   // 16-query blocks per wave
+    constexpr int WQ = 16 * NQ;                             // queries per wave
+    constexpr int QB = QW * WQ;                             // queries per workgroup
+    constexpr int UNIT_B = R::Tile + L::Tile;               // 32 keys: K, then V
+    constexpr int GROUP_B = 2 * UNIT_B;                     // LDS of one key group: two stages
+    constexpr int OPS = 2 * L::Groups;                      // DMA instructions per unit
+    constexpr int WAVE_OPS = (OPS + QW - 1) / QW;           // at most this many per wave
+    constexpr int WAVE_OUT = WQ * L::RowB;                  // a wave's output rows
+    constexpr int WAVE_PART = (CB * NQ + 1) * 1024;         // a wave's accumulators, offsets and row sums in fp32
+    constexpr int MERGE_B = (KG / 2) * QW * WAVE_PART;
+    constexpr int LPR = L::RowB / 16;                       // 16-byte chunks per row
+    constexpr int SMEM = KG * GROUP_B > QW * WAVE_OUT ? (KG * GROUP_B > MERGE_B ? KG * GROUP_B : MERGE_B)
+                                                      : (QW * WAVE_OUT > MERGE_B ? QW * WAVE_OUT : MERGE_B);
+    __shared__ __attribute__((aligned(1024))) char smem[SMEM];
 
-    // ---- work item (see fwd_item_of), possibly one part of a split item
-    uint32_t item_id = blockIdx.x, part = 0;
-    const bool is_part = blockIdx.x >= p.split_first;
-    if (is_part) {
-        const uint32_t idx = blockIdx.x - p.split_first;
-        item_id = p.split_first + idx / p.split_parts;
-        part = idx - (item_id - p.split_first) * p.split_parts;
-    }
-    const FwdItem item = fwd_item_of<QB>(item_id, p, order, n_bh);
+    const GroupItem item = group_item_of(blockIdx.x, p, plan);
     if (!item.valid) return;
-    const uint32_t qblock = item.qblock, h_local = item.h_local;
+    const uint32_t qblock = item.qblock;
     const size_t bh = item.bh;
-    const uint32_t q_tile = (qblock * QB) / p.P;
-    const StaBox box = sta_key_tile_box_of(p.n_t, p.n_h, p.n_w, win.w[h_local][0], win.w[h_local][1],
-                                           win.w[h_local][2], q_tile);
-
+    const StaBox box = item.box;
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int lane = tid & 63;
-    const int lo = lane & 31;
-    const int hb = lane >> 5;
+    const int kg = wave / QW, qw = wave % QW;               // key group, and which queries of the workgroup
+    const int lane = tid & 63, c16 = lane & 15, g4 = lane >> 4;
 
-    const bf16_raw *qh = q + (bh * p.N + (size_t)qblock * QB + (size_t)wave * 32) * D;
+    const size_t my_row = bh * p.N + (size_t)qblock * QB + (size_t)qw * WQ;
     const char *kh = reinterpret_cast<const char *>(k + bh * p.N * D);
     const char *vh = reinterpret_cast<const char *>(v + bh * p.N * D);
 
-    // ---- DMA loads.  Each wave-wide 16 B/lane instruction fills 1 KB of LDS = RPI consecutive key rows (a
-    // lane's LDS slot is fixed by the hardware: base + 16*lane), so the swizzle is applied on the global side: the
-    // lane fetches the logical chunk that belongs at its slot.  The KB keys of a sub-block are taken as blocks of
-    // 16 rows; loading wave w fetches rows RPI*(w%IPB) .. +RPI-1 of the blocks LOADS*(w/IPB) .. +LOADS-1, one
-    // instruction per block.  Both swizzles depend on the row only through row & 15, so a lane's offset inside
-    // its block is the same for all its instructions and the rest of the address is wave-uniform: one 32-bit
-    // lane offset per operand on top of a scalar base, and no vector arithmetic per load.
-    uint32_t k_lane_off, v_lane_off;
-    {
-        const int lrow = RPI * (wave % IPB) + lane / LPR;   // row & 15 of every row this lane fetches
-        const int slot = lane % LPR;
-        k_lane_off = (uint32_t)(lrow * ROWB + ((slot ^ k_swizzle<D>(lrow)) << 4));
-        v_lane_off = (uint32_t)(lrow * ROWB + ((slot ^ v_swizzle<D>(lrow)) << 4));
-    }
-    auto issue_loads = [&](int stage, size_t key_byte_base) {
-        char *sdst = smem + stage * STAGE_BYTES;                           // only waves < LOADERS get here
+    // ---- this group's share of the walk, in units of 32 keys
+    BoxWalk walk;
+    walk.start(box, p.n_h, p.n_w, p.P);
+    const int n_all = box.count() * walk.sub_per_tile;
+    const int u_lo = KG == 1 ? 0 : n_all * kg / KG;
+    const int n_units = KG == 1 ? n_all : n_all * (kg + 1) / KG - u_lo;
+    const int n_steps = (n_all + KG - 1) / KG;              // the largest share of any group
+    auto to_share = [&]() __attribute__((always_inline)) {
+        if constexpr (KG > 1) {
+            const uint32_t tiles = fast_div((uint32_t)u_lo, plan.sub_per_tile);
+            walk.skip(tiles, (uint32_t)u_lo - tiles * plan.sub_per_tile.d);
+        }
+    };
+    to_share();
+
+    // ---- DMA: instruction j of a unit brings 1 KB of K or V; wave qw of the group issues j = qw, qw + QW, ..
+    const uint32_t k_lane_off = R::dma_lane_offset(lane), v_lane_off = L::dma_lane_offset(lane);
+    int issued = 0;                                         // units requested so far
+    auto issue_next = [&]() __attribute__((always_inline)) {
+        if (issued >= n_units) return;
         uint32_t koff = k_lane_off, voff = v_lane_off;
-        asm volatile("" : "+v"(koff), "+v"(voff));      // keep the lane offsets 32-bit next to a scalar base
+        asm volatile("" : "+v"(koff), "+v"(voff));          // keep the lane offsets 32-bit next to a scalar base
+        const uint32_t row = walk.next_row;
+        walk.advance();
+        char *stage = smem + kg * GROUP_B + (issued & 1) * UNIT_B;
 #pragma unroll
-        for (int i = 0; i < LOADS; ++i) {
-            const int block16 = LOADS * (wave / IPB) + i;
-            const size_t gbase = key_byte_base + (size_t)block16 * (16 * ROWB);
-            char *kdst = sdst + (16 * block16 + RPI * (wave % IPB)) * ROWB;
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(kh + gbase + koff),
-                                             STA_LDS_PTR(kdst), 16, 0, 0);
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(vh + gbase + voff),
-                                             STA_LDS_PTR(kdst + TILE_BYTES), 16, 0, 0);
-        }
-    };
-
-    // ---- per-lane constants of the operand reads
-    // K (A operand of S^T = K Q^T): row 32*mb + lo, logical chunk 2*ks + hb
-    const uint32_t smem_addr = (uint32_t)(uintptr_t)smem;
-    uint32_t k_addr[KS];
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) k_addr[ks] = smem_addr + (uint32_t)(lo * ROWB + (((2 * ks + hb) ^ k_swizzle<D>(lo)) << 4));
-    // V (A operand of O^T += V^T P^T) through the transposing read: within each block of 16 lanes, lane
-    // r = 4*j4 + s supplies 4 channels (4*s..4*s+3 of the block's 16) of key row j4; lane i then receives
-    // channel i of rows 0..3.
-    const int j4 = (lane & 15) >> 2, s4 = lane & 3, blk = (lane >> 4) & 1;
-    uint32_t v_addr[DB];
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-        v_addr[db] = smem_addr + (uint32_t)((4 * hb + j4) * ROWB +
-                                            (((4 * db + 2 * blk + (s4 >> 1)) ^ v_swizzle<D>(4 * hb + j4)) << 4) + 8 * (s4 & 1));
-
-    // ---- Q fragments (B operand of S^T), resident in registers
-    bf16x8 Qr[KS];
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-        Qr[ks] = *reinterpret_cast<const bf16x8 *>(qh + (size_t)lo * D + ks * 16 + hb * 8);
-
-    floatx16 Oacc[DB];
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) Oacc[db][r] = 0.f;
-    float m_run = -INFINITY;      // running row max (raw scores) used as the exponent offset
-    float l_run = 0.f;            // this lane's share of the row sum
-
-    const int sub_per_tile = p.P / KB;
-    const int n_all = box.count() * sub_per_tile;           // sub-blocks of the whole item
-    const int iter_lo = is_part ? (int)((long long)n_all * part / p.split_parts) : 0;
-    const int n_iter = (is_part ? (int)((long long)n_all * (part + 1) / p.split_parts) : n_all) - iter_lo;
-    // Order in which the key tiles of the box are visited.  Along each axis the box [lo, hi] holds e = hi-lo+1
-    // consecutive tiles, hence exactly one tile of every residue class mod e; the walk takes them in the order
-    // of that residue (k mod e = 0, 1, ..), i.e. it starts inside the box and wraps from hi to lo.  Query tiles
-    // that are neighbours along an axis have boxes shifted by one tile: with this order they reach each key
-    // tile they share at the SAME step of their walks, so workgroups resident on an XCD at one time read the
-    // same K/V tiles at about the same time and find them in that XCD's L2.  (Walking every box from its own lo
-    // makes neighbours read a shared tile at different steps; the L2 is far too small to keep it that long.)
-    const int e_t = box.t.hi - box.t.lo + 1, e_h = box.h.hi - box.h.lo + 1, e_w = box.w.hi - box.w.lo + 1;
-    const int start_t = box.t.lo + (e_t - box.t.lo % e_t) % e_t;
-    const int start_h = box.h.lo + (e_h - box.h.lo % e_h) % e_h;
-    const int start_w = box.w.lo + (e_w - box.w.lo % e_w) % e_w;
-    int it_t, it_h, it_w, it_s;
-    int left_h, left_w;                     // tiles still to visit in the current h-cycle / w-cycle
-    auto row_start = [&]() -> size_t {      // byte offset of key tile (it_t, it_h, it_w) inside the head
-        const size_t kt = ((size_t)it_t * p.n_h + it_h) * p.n_w + it_w;
-        return kt * p.P * ROWB;
-    };
-    size_t next_base;
-    auto start_walk = [&]() __attribute__((always_inline)) {
-        it_t = start_t; it_h = start_h; it_w = start_w;
-        left_h = e_h; left_w = e_w;
-        // a part starts iter_lo sub-blocks into the walk: whole tiles first, then sub-blocks inside the tile
-        for (int skip = iter_lo / sub_per_tile; skip > 0; --skip) {
-            if (++it_w > box.w.hi) it_w = box.w.lo;
-            if (--left_w == 0) {
-                left_w = e_w;
-                it_w = start_w;
-                if (++it_h > box.h.hi) it_h = box.h.lo;
-                if (--left_h == 0) {
-                    left_h = e_h;
-                    it_h = start_h;
-                    if (++it_t > box.t.hi) it_t = box.t.lo;
-                }
+        for (int i = 0; i < WAVE_OPS; ++i) {
+            const int j = qw + i * QW;
+            if (OPS % QW == 0 || j < OPS) {
+                const bool is_v = j >= L::Groups;
+                const int group = j % L::Groups;
+                const char *src = (is_v ? vh : kh) + (size_t)(row + L::GroupRows * group) * L::RowB;
+                char *dst = stage + (is_v ? R::Tile + group * L::Group : group * R::Group);
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + (is_v ? voff : koff)),
+                                                 STA_LDS_PTR(dst), 16, 0, 0);
             }
         }
-        it_s = iter_lo % sub_per_tile;
-        next_base = row_start() + (size_t)it_s * KB * ROWB;
+        ++issued;
     };
-    auto advance = [&]() __attribute__((always_inline)) {
-        next_base += (size_t)KB * ROWB;
-        if (++it_s == sub_per_tile) {
-            it_s = 0;
-            if (++it_w > box.w.hi) it_w = box.w.lo;
-            if (--left_w == 0) {
-                left_w = e_w;
-                it_w = start_w;
-                if (++it_h > box.h.hi) it_h = box.h.lo;
-                if (--left_h == 0) {
-                    left_h = e_h;
-                    it_h = start_h;
-                    if (++it_t > box.t.hi) it_t = box.t.lo;
-                }
-            }
-            next_base = row_start();
+    issue_next();
+
+    // ---- operand read addresses (stage 0 of the group) and resident Q fragments
+    const uint32_t group_addr = (uint32_t)(uintptr_t)smem + (uint32_t)(kg * GROUP_B);
+    const uint32_t row_addr = R::address(group_addr, lane);
+    uint32_t tr_addr[4];
+    L::transposed_addresses(group_addr + R::Tile, lane, tr_addr);
+    bf16x8 Qr[NQ][KS];
+#pragma unroll
+    for (int qb = 0; qb < NQ; ++qb)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+            Qr[qb][ks] = *reinterpret_cast<const bf16x8 *>(q + (my_row + 16 * qb + c16) * D + ks * 32 + g4 * 8);
+
+    floatx4 Oacc[CB][NQ];                                   // channel 16*cb + 4*g4 + i of query 16*qb + c16
+    floatx4 Sinit[NQ];                                      // minus the exponent offset of the lane's queries
+    float m_run[NQ];
+    floatx4 l_acc[NQ];                                      // row sums (a product with ones: all registers hold the same)
+    auto reset = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int qb = 0; qb < NQ; ++qb) {
+            Sinit[qb] = floatx4{0.f, 0.f, 0.f, 0.f};
+            l_acc[qb] = floatx4{0.f, 0.f, 0.f, 0.f};
+            m_run[qb] = 0.f;
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) Oacc[cb][qb] = floatx4{0.f, 0.f, 0.f, 0.f};
         }
     };
-
+    reset();
     const float c = p.scale_log2e;
-    // The SIMD's arbiter prefers its oldest wave, and a wave whose next instruction is an MFMA waiting for the
-    // matrix pipe holds the vector issue port meanwhile: the softmax arithmetic of the younger waves of a SIMD
-    // then waits behind the older waves' matrix phases.  Static priorities against the age order (waves w, w+4,
-    // w+8 share a SIMD) even this out.  Measured in one call: 12.41 -> 12.22 ms, and 9.50 -> 9.24 ms on constant
-    // inputs, where the clock does not move.
-    if constexpr (NW == 12) {
+    if constexpr (QW * KG == 12) {                          // static priorities against the age order, as in the kernel below
         if (wave >= 8) __builtin_amdgcn_s_setprio(2);
         else if (wave >= 4) __builtin_amdgcn_s_setprio(1);
     }
 
-    // ---- pipeline: up to STAGES-1 sub-blocks are in flight.  (it_t, it_h, it_w, it_s) always names the next
-    // sub-block to request; `issued` counts the requests made so far.
-    int issued;
-    auto issue_next = [&]() __attribute__((always_inline)) {
-        if (issued < n_iter) {
-            if (wave < LOADERS) issue_loads(issued % STAGES, next_base);
-            advance();
-            ++issued;
-        }
-    };
-    auto start_pipeline = [&]() __attribute__((always_inline)) {
-        start_walk();
-        issued = 0;
+    constexpr int kPlain = 0, kFollow = 1, kFirst = 2;
+    // One unit of 32 keys whose K begins at LDS offset off (relative to the group's first stage).
+    auto unit_at = [&](auto track_c, uint32_t off, float grow_above) __attribute__((always_inline)) {
+        constexpr int TRACK = decltype(track_c)::value;     // kFirst: set the offsets; kFollow: move them with the scores
+        uint32_t tr_at[4];
 #pragma unroll
-        for (int s = 0; s < STAGES - 1; ++s) issue_next();
-    };
-    start_pipeline();
-
-    // One sub-block.  The LDS stage is a compile-time constant here (the loop below is unrolled over the
-    // stages), so every operand read carries its stage as an immediate offset and needs no address arithmetic.
-    // TRACK: follow the growth of the scores in this sub-block (see the loops below).
-    auto sub_block = [&](auto track_c, auto stage_c, int iter) __attribute__((always_inline)) {
-        constexpr bool TRACK = decltype(track_c)::value;
-        constexpr int stage = decltype(stage_c)::value;
-        constexpr int KOFF = stage * STAGE_BYTES;
-        constexpr int VOFF = KOFF + TILE_BYTES;
-        // This wave's DMA for sub-block `iter` must have landed; the requests for later sub-blocks (2*LOADS
-        // instructions each, returned in order) may stay outstanding.
-        const int pend = issued - 1 - iter;
-        if (STAGES <= 2 || pend == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        else if (STAGES <= 3 || pend == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * LOADS) : "memory");
-        else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * LOADS) : "memory");
-        __syncthreads();   // ... and everyone's; the stage read in the previous iteration is free again
-        issue_next();      // refills stage (iter - 1) % STAGES
-
-        // ---- S^T = K Q^T ------------------------------------------------------------
-        // K-operand reads are issued by hand, one group of four k-steps ahead of the MFMAs.
-        floatx16 S[MB];
+        for (int m = 0; m < 4; ++m) tr_at[m] = tr_addr[m] + off;
+        floatx4 S[2][NQ];                                   // [key block][query block]
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
+        for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) S[mb][r] = 0.f;
-        bf16x8 ka[2][4];
-        constexpr int GPM = KS / 4;                 // groups of four k-steps per 32-key block
-        k_issue<0, ROWB, KOFF, GPM>(ka[0], k_addr);
-        static_for<0, MB * GPM>([&](auto gi) {
-            constexpr int g = decltype(gi)::value;
-            constexpr int mb = g / GPM, ks0 = 4 * (g % GPM);
-            if constexpr (g + 1 < MB * GPM) {
-                k_issue<g + 1, ROWB, KOFF, GPM>(ka[(g + 1) & 1], k_addr);
-                k_wait<4>(ka[g & 1]);
+            for (int qb = 0; qb < NQ; ++qb) S[kb][qb] = Sinit[qb];
+        rows_times_resident<D, 0>(row_addr + off, Qr, S);   // K Q^T minus the offset
+        if constexpr (TRACK != kPlain) {
+            float mq[NQ];
+#pragma unroll
+            for (int qb = 0; qb < NQ; ++qb) {
+                mq[qb] = max3(S[0][qb][0], S[0][qb][1], S[0][qb][2]);
+                mq[qb] = max3(mq[qb], S[0][qb][3], S[1][qb][0]);
+                mq[qb] = max3(mq[qb], S[1][qb][1], S[1][qb][2]);
+                mq[qb] = fmaxf(mq[qb], S[1][qb][3]);
+            }
+            if constexpr (TRACK == kFirst) {
+#pragma unroll
+                for (int qb = 0; qb < NQ; ++qb) {
+                    m_run[qb] = quad_lane_max(mq[qb]);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) Sinit[qb][r] = -m_run[qb];
+#pragma unroll
+                    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) S[kb][qb][r] -= m_run[qb];
+                }
             } else {
-                k_wait<0>(ka[g & 1]);
-            }
+                float mx = mq[0];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) S[mb] = mfma_32x32x16(ka[g & 1][i], Qr[ks0 + i], S[mb]);
-            __builtin_amdgcn_sched_barrier(0);   // keep each MFMA group ahead of the next group's wait
-        });
-        // first group of V-operand reads goes out now so that its latency hides behind the softmax
-        shortx4 va[2][DB][2];
-        pv_issue<VOFF, DB, ROWB>(va[0], v_addr);
-
-        // ---- online softmax: one query column per lane ------------------------------
-        if constexpr (TRACK) {
-            float mx = max3(S[0][0], S[0][1], S[0][2]);
-    #pragma unroll
-            for (int mb = 0; mb < MB; ++mb) {
-    #pragma unroll
-                for (int r = (mb == 0 ? 3 : 1); r + 1 < 16; r += 2) mx = max3(mx, S[mb][r], S[mb][r + 1]);
-                mx = max3(mx, S[mb][15], mb == 0 ? S[mb][15] : S[mb][0]);
-            }
-            mx = half_swap_max(mx);
-            // Lazy rescale: the exponent offset only moves when the max grew by more than 2^8 in the
-            // exponent, so probabilities stay below 256 and the accumulators are rarely touched.
-            const bool grow = (mx - m_run) * c > 8.0f;
-            if (__builtin_amdgcn_ballot_w64(grow)) {
-                const float m_new = grow ? mx : m_run;
-                const float alpha = exp2f((m_run - m_new) * c);
-                m_run = m_new;
-                l_run *= alpha;
-    #pragma unroll
-                for (int db = 0; db < DB; ++db)
-    #pragma unroll
-                    for (int r = 0; r < 16; ++r) Oacc[db][r] *= alpha;
+                for (int qb = 1; qb < NQ; ++qb) mx = fmaxf(mx, mq[qb]);
+                if (__builtin_expect(__builtin_amdgcn_ballot_w64(mx > grow_above) != 0, 0)) {
+#pragma unroll
+                    for (int qb = 0; qb < NQ; ++qb) {
+                        const float row_max = quad_lane_max(mq[qb]);
+                        const float shift = row_max > grow_above ? row_max : 0.f;     // the same in the four lanes of a query
+                        const float alpha = __builtin_amdgcn_exp2f(-shift * c);
+                        m_run[qb] += shift;
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) Sinit[qb][r] = -m_run[qb];
+#pragma unroll
+                        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) S[kb][qb][r] -= shift;
+                        l_acc[qb] *= alpha;
+                        const float alpha_settled = settled_after_transcendental(alpha);
+#pragma unroll
+                        for (int cb = 0; cb < CB; ++cb) scale_in_place(Oacc[cb][qb], alpha_settled);
+                    }
+                }
             }
         }
-        const float mneg = -m_run * c;
-        bf16x8 Pb[MB][2];
+        StagedTransposedProduct<D, 0> v_t;
+        v_t.prefetch(tr_at);
+        __builtin_amdgcn_sched_barrier(0);                  // the exponentials stay behind these reads
+        // probabilities, rounded to bf16, packed as the B operand of the PV product of their query block
+        bf16x8 Pb[NQ];
+        typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
+        for (int qb = 0; qb < NQ; ++qb)
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
+            for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-                for (int e = 0; e < 8; e += 2) {
-                    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-                    const float p0 = __builtin_amdgcn_exp2f(fmaf(S[mb][8 * j + e], c, mneg));
-                    const float p1 = __builtin_amdgcn_exp2f(fmaf(S[mb][8 * j + e + 1], c, mneg));
+                for (int e = 0; e < 4; e += 2) {
+                    const float p0 = __builtin_amdgcn_exp2f(S[kb][qb][e] * c);
+                    const float p1 = __builtin_amdgcn_exp2f(S[kb][qb][e + 1] * c);
                     bf16x2 pp;
                     pp[0] = static_cast<__bf16>(p0);
                     pp[1] = static_cast<__bf16>(p1);
-                    Pb[mb][j][e] = pp[0];
-                    Pb[mb][j][e + 1] = pp[1];
-                    bf16x2 ones;
-                    ones[0] = static_cast<__bf16>(1.0f);
-                    ones[1] = static_cast<__bf16>(1.0f);
-                    l_run = __builtin_amdgcn_fdot2_f32_bf16(pp, ones, l_run, false);   // sums the rounded values
+                    Pb[qb][4 * kb + e] = pp[0];
+                    Pb[qb][4 * kb + e + 1] = pp[1];
                 }
-
-        // ---- O^T += V^T P^T --------------------------------------------------------
-        // The transposing reads are issued by hand (the compiler would otherwise wait for the
-        // in-flight DMA of the next sub-block before each of them) and software-pipelined one
-        // 16-key group ahead of the MFMAs that consume them.
-        static_for<0, MB * 2>([&](auto gi) {
-            constexpr int g = decltype(gi)::value;
-            constexpr int mb = g / 2, j = g % 2;
-            if constexpr (g + 1 < MB * 2) {
-                pv_issue<VOFF + (g + 1) * 16 * ROWB, DB, ROWB>(va[(g + 1) & 1], v_addr);
-                pv_wait<DB * 2>(va[g & 1]);
-            } else {
-                pv_wait<0>(va[g & 1]);
-            }
+        bf16x8 ones;
 #pragma unroll
-            for (int db = 0; db < DB; ++db) {
-                typedef short shortx8 __attribute__((ext_vector_type(8)));
-                const shortx8 v01 = __builtin_shufflevector(va[g & 1][db][0], va[g & 1][db][1], 0, 1, 2, 3, 4, 5, 6, 7);
-                Oacc[db] = mfma_32x32x16(__builtin_bit_cast(bf16x8, v01), Pb[mb][j], Oacc[db]);
-            }
-        });
+        for (int e = 0; e < 8; ++e) ones[e] = static_cast<__bf16>(1.0f);
+#pragma unroll
+        for (int qb = 0; qb < NQ; ++qb) l_acc[qb] = mfma_16x16x32(ones, Pb[qb], l_acc[qb]);       // sums the rounded values
+        v_t.run(tr_at, Pb, Oacc);                           // O^T += V^T P^T
     };
 
-    // The first sub-block of an item sets the exponent offset (the row maxima of its keys).  The rest runs without
-    // following the maximum: probabilities, row sums and accumulators have 8 exponent bits, so an offset that
-    // turns out too low costs no precision until the sums near the end of that range.  The row sums are looked at
-    // once at the end; if one is beyond 2^96 or not a number, the workgroup does the whole item again with the
-    // careful loop, which moves the offset whenever a score exceeds it by more than 2^8 in the exponent.
-    // (2^96 leaves 66 in the exponent of e between the first keys' maximum and the largest score before the second
-    // pass is needed, and room for |V| up to 2^32 in the accumulators; those are checked as well.)
-    sub_block(std::true_type{}, std::integral_constant<int, 0>{}, 0);
-    for (int iter = 1; iter < n_iter; iter += STAGES) {
-        static_for<0, STAGES>([&](auto st) {
-            constexpr int stage = (1 + decltype(st)::value) % STAGES;       // sub-block i sits in stage i % STAGES
-            if (iter + decltype(st)::value < n_iter)
-                sub_block(std::false_type{}, std::integral_constant<int, stage>{}, iter + decltype(st)::value);
-        });
-    }
-    float l_tot = half_swap_sum(l_run);
-    constexpr float kRedoAbove = 79228162514264337593543950336.f;      // 2^96
-    // The accumulators too: with |V| beyond 2^32 they can leave the range before the row sums reach the bound.  The
-    // test is on the bit patterns (largest exponent field), so that it sees a NaN (infinity minus infinity) as well.
-    uint32_t o_max = 0;
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) o_max = max(o_max, __float_as_uint(Oacc[db][r]) & 0x7fffffffu);
-    // (With finite inputs a row sum is never a NaN: a probability that overflows is +infinity, and so is the sum.
-    // The barrier inside also ends every wave's reads of the stages.)
-    if (__builtin_expect(__syncthreads_or(!(l_tot < kRedoAbove) || o_max >= 0x7f800000u), 0)) {
-        m_run = -INFINITY;
-        l_run = 0.f;
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) Oacc[db][r] = 0.f;
-        start_pipeline();
-        for (int iter = 0; iter < n_iter; iter += STAGES) {
-            static_for<0, STAGES>([&](auto st) {
-                if (iter + decltype(st)::value < n_iter) sub_block(std::true_type{}, st, iter + decltype(st)::value);
-            });
+    // One pass over the group's units; the first has been requested.  CAREFUL: follow the maximum in every unit.
+    auto run_pass = [&](auto careful_c) __attribute__((always_inline)) {
+        constexpr int TRACK = decltype(careful_c)::value ? kFollow : kPlain;
+        const float bound = TRACK == kFollow ? __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(8.0f / c))) : 0.f;
+        auto next_unit = [&]() __attribute__((always_inline)) {
+            // this wave's DMA for the unit must have landed, and everyone's; the other stage is free again
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            issue_next();
+        };
+        next_unit();
+        if (KG == 1 || n_units > 0) unit_at(std::integral_constant<int, kFirst>{}, 0u, 0.f);
+#pragma unroll 1
+        for (int u = 1; u < n_steps; ++u) {
+            next_unit();
+            if (KG == 1 || u < n_units) unit_at(std::integral_constant<int, TRACK>{}, (uint32_t)((u & 1) * UNIT_B), bound);
         }
-        l_tot = half_swap_sum(l_run);
+    };
+    float l_tot[NQ];
+    auto row_sums = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int qb = 0; qb < NQ; ++qb) l_tot[qb] = l_acc[qb][0];
+    };
+    run_pass(std::false_type{});
+    row_sums();
+    constexpr float kRedoAbove = 79228162514264337593543950336.f;      // 2^96
+    uint32_t o_max = 0;
+    bool redo = false;
+#pragma unroll
+    for (int qb = 0; qb < NQ; ++qb) {
+        redo = redo || !(l_tot[qb] < kRedoAbove);
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) o_max = max(o_max, __float_as_uint(Oacc[cb][qb][r]) & 0x7fffffffu);
+    }
+    // (the barrier inside also ends every wave's reads of the stages)
+    if (__builtin_expect(__syncthreads_or(redo || o_max >= 0x7f800000u), 0)) {
+        reset();
+        walk.start(box, p.n_h, p.n_w, p.P);
+        to_share();
+        issued = 0;
+        issue_next();
+        run_pass(std::true_type{});
+        row_sums();
+        __syncthreads();
     }
 
-    // ---- finalize -------------------------------------------------------------------
-    if (is_part) {
-        // unnormalised accumulator, offset and row sum of this part; the combine kernel does the rest
-        float *ws = p.split_ws + (size_t)(blockIdx.x - p.split_first) * split_part_floats<D>(QB);
-        float *wo = ws + (size_t)(wave * 32 + lo) * D;
+    // ---- merge of the key groups: the upper half of the remaining groups hands its accumulators, offsets and row sums
+    // to the lower half through LDS until one is left, always in the same order
+    // (a group without units: an offset below every other, finite so that two such groups can be merged)
+    float m2[NQ];                                           // offsets in base-2 units
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
+    for (int qb = 0; qb < NQ; ++qb) m2[qb] = (KG > 1 && n_units == 0) ? -3.0e38f : m_run[qb] * c;
+    if constexpr (KG > 1) {
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                floatx4 ov;
+        for (int n = KG; n > 1; n = (n + 1) / 2) {
+            const int half = (n + 1) / 2;                   // groups half .. n-1 give, groups 0 .. n-1-half take
+            if (n != KG) __syncthreads();                   // the previous round has been read
+            if (kg >= half && kg < n) {
+                char *to = smem + ((kg - half) * QW + qw) * WAVE_PART + lane * 16;
 #pragma unroll
-                for (int t = 0; t < 4; ++t) ov[t] = Oacc[db][4 * g + t];
-                *reinterpret_cast<floatx4 *>(wo + db * 32 + g * 8 + hb * 4) = ov;
+                for (int qb = 0; qb < NQ; ++qb)
+#pragma unroll
+                    for (int cb = 0; cb < CB; ++cb) *reinterpret_cast<floatx4 *>(to + (qb * CB + cb) * 1024) = Oacc[cb][qb];
+                *reinterpret_cast<floatx4 *>(to + NQ * CB * 1024) = floatx4{m2[0], m2[1], l_tot[0], l_tot[1]};
             }
-        if (hb == 0) {
-            ws[(size_t)QB * D + wave * 32 + lo] = m_run * c;      // the merge takes base-2 units
-            ws[(size_t)QB * D + QB + wave * 32 + lo] = l_tot;
+            __syncthreads();
+            if (kg + half < n) {
+                const char *from = smem + (kg * QW + qw) * WAVE_PART + lane * 16;
+                const floatx4 ml = *reinterpret_cast<const floatx4 *>(from + NQ * CB * 1024);
+#pragma unroll
+                for (int qb = 0; qb < NQ; ++qb) {
+                    const float m_new = fmaxf(m2[qb], ml[qb]);
+                    const float wa = __builtin_amdgcn_exp2f(m2[qb] - m_new), wb = __builtin_amdgcn_exp2f(ml[qb] - m_new);
+                    m2[qb] = m_new;
+                    l_tot[qb] = l_tot[qb] * wa + ml[NQ + qb] * wb;
+#pragma unroll
+                    for (int cb = 0; cb < CB; ++cb) {
+                        const floatx4 x = *reinterpret_cast<const floatx4 *>(from + (qb * CB + cb) * 1024);
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) Oacc[cb][qb][r] = Oacc[cb][qb][r] * wa + x[r] * wb;
+                    }
+                }
+            }
         }
-        return;
+        __syncthreads();
+        if (kg != 0) return;
     }
-    bf16_raw *oh = o + (bh * p.N + (size_t)qblock * QB + (size_t)wave * 32) * D;
-    const float inv = 1.f / l_tot;
-    // sum_j exp(s_j * scale) = 2^(m * scale_log2e) * l  =>  ln = m * scale_log2e * ln 2 + ln l
-    if (p.lse != nullptr && hb == 0)
-        p.lse[bh * p.N + (size_t)qblock * QB + (size_t)wave * 32 + lo] = m_run * c * 0.6931471805599453f + __logf(l_tot);
-    // A lane holds 4 consecutive channels of one query row at a time: stored directly, every store instruction
-    // would touch 32 rows with 16 bytes each.  The rows go through LDS instead (each wave its own 32 rows; 16-byte
-    // chunk c of row r at position c ^ (r mod chunks per row)) and leave as whole rows, 1 KB contiguous per store
-    // instruction, with streaming stores.  Measured at window 1x1x1, where the launch is bound by HBM: the 8-byte
-    // stores cost 0.16 of 0.86 ms.
-    __syncthreads();                                   // every wave has finished reading the K/V stages
-    char *rows = smem + wave * (32 * ROWB);
+
+    // ---- finalize (the first group): rows through LDS, whole rows to memory with streaming stores
+    if (p.lse != nullptr && g4 == 0) {
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
+        for (int qb = 0; qb < NQ; ++qb) p.lse[my_row + 16 * qb + c16] = m2[qb] * 0.6931471805599453f + __logf(l_tot[qb]);
+    }
+    char *rows = smem + qw * WAVE_OUT;
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
+    for (int qb = 0; qb < NQ; ++qb) {
+        const float inv = 1.f / l_tot[qb];
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) {
             bf16x4 ov;
 #pragma unroll
-            for (int t = 0; t < 4; ++t) ov[t] = static_cast<__bf16>(Oacc[db][4 * g + t] * inv);
-            const int chunk = db * 4 + g;
-            *reinterpret_cast<bf16x4 *>(rows + lo * ROWB + ((chunk ^ (lo & (LPR - 1))) << 4) + 8 * hb) = ov;
+            for (int t = 0; t < 4; ++t) ov[t] = static_cast<__bf16>(Oacc[cb][qb][t] * inv);
+            const int chunk = 2 * cb + (g4 >> 1);
+            *reinterpret_cast<bf16x4 *>(rows + (16 * qb + c16) * L::RowB + ((chunk ^ (c16 & (LPR - 1))) << 4) + 8 * (g4 & 1)) = ov;
         }
+    }
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    char *out = reinterpret_cast<char *>(o + my_row * D);
 #pragma unroll
-    for (int i = 0; i < 32 / RPI; ++i) {
-        const int r = RPI * i + lane / LPR, cpos = lane % LPR;
-        const u32x4 x = *reinterpret_cast<const u32x4 *>(rows + r * ROWB + ((cpos ^ (r & (LPR - 1))) << 4));
-        __builtin_nontemporal_store(x, reinterpret_cast<u32x4 *>(reinterpret_cast<char *>(oh) + (size_t)r * ROWB + (cpos << 4)));
+    for (int i = 0; i < WAVE_OUT / 1024; ++i) {
+        const int r = L::GroupRows * i + lane / LPR, cpos = lane % LPR;
+        const u32x4 x = *reinterpret_cast<const u32x4 *>(rows + r * L::RowB + ((cpos ^ (r & (LPR - 1))) << 4));
+        __builtin_nontemporal_store(x, reinterpret_cast<u32x4 *>(out + (size_t)r * L::RowB + (cpos << 4)));
     }
 }
 
-// The same kernel built on v_mfma_f32_16x16x32_bf16 (head dimension 128, 32-key sub-blocks).  On this chip the run
+// Head dimension 128, tiles of 128 tokens' multiples: one kernel without key groups, 32-key sub-blocks.  On this chip the run
 // time on real data follows the energy of the instruction stream (the package sits at its power limit and lowers
 // the clock), and the 16x16x32 shape is the cheaper one per flop: it reads and writes 4 accumulator registers per
 // 16 Kflop where 32x32x16 moves 16 per 32 Kflop.  Measured with nothing but matrix instructions on N(0,1) operands:
@@ -1384,12 +1336,12 @@ inline uint32_t resident_workgroups(int minb)
     return (uint32_t)cus * (uint32_t)minb;
 }
 
-template <int D, int NW, int KB, int STAGES, int MINB, bool X32 = false, bool PRESCALE = false>
-hipError_t launch_fast(const void *q, const void *k, const void *v, void *o, int B, const sta::FwdParams &p_in,
+template <int NW, int KB, int STAGES, int MINB>
+hipError_t launch_x32(const void *q, const void *k, const void *v, void *o, int B, const sta::FwdParams &p_in,
                             const sta::WindowTable &win, const sta::HeadOrder &order, float *split_ws,
                             size_t split_ws_floats, hipStream_t stream)
 {
-    constexpr int QB = NW * 32;
+    constexpr int D = 128, QB = NW * 32;
     sta::FwdParams p = p_in;
     const uint32_t qblocks_per_head = p.N / QB;
     const uint32_t max_seg = (qblocks_per_head + 7) / 8;          // longest of the 8 per-XCD ranges
@@ -1399,7 +1351,7 @@ hipError_t launch_fast(const void *q, const void *k, const void *v, void *o, int
     p.split_parts = 1;
     p.split_ws = nullptr;
     uint32_t split_items = 0;
-    if (D == 128 && split_ws != nullptr) {
+    if (split_ws != nullptr) {
         // Items beyond the last full round of workgroups are split so that their parts fill the chip once.
         auto names_item = [&](uint32_t id) {
             const uint32_t xcd = id & 7, slot = id >> 3;
@@ -1440,24 +1392,81 @@ hipError_t launch_fast(const void *q, const void *k, const void *v, void *o, int
         }
     }
     dim3 grid(p.split_first + split_items * p.split_parts), block(NW * 64);
-    if constexpr (X32) {
-        static_assert(D == 128, "the 16x16x32 kernel exists for head dimension 128 only");
-        sta_fwd_x32_kernel<NW, KB, STAGES, MINB, PRESCALE><<<grid, block, 0, stream>>>(
-            static_cast<const bf16_raw *>(q), static_cast<const bf16_raw *>(k), static_cast<const bf16_raw *>(v),
-            static_cast<bf16_raw *>(o), p, win, order, n_bh);
-    } else {
-        sta_fwd_fast_kernel<D, NW, KB, STAGES, MINB><<<grid, block, 0, stream>>>(
-            static_cast<const bf16_raw *>(q), static_cast<const bf16_raw *>(k), static_cast<const bf16_raw *>(v),
-            static_cast<bf16_raw *>(o), p, win, order, n_bh);
-    }
+    sta_fwd_x32_kernel<NW, KB, STAGES, MINB, false><<<grid, block, 0, stream>>>(
+        static_cast<const bf16_raw *>(q), static_cast<const bf16_raw *>(k), static_cast<const bf16_raw *>(v),
+        static_cast<bf16_raw *>(o), p, win, order, n_bh);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || split_items == 0) return e;
-    if constexpr (D == 128) {
-        sta_fwd_combine_kernel<D, QB><<<dim3(QB / 4, split_items), dim3(256), 0, stream>>>(static_cast<bf16_raw *>(o), p, order, n_bh);
-        return hipGetLastError();
-    } else {
-        return hipErrorInvalidValue;      // head dimension 64 is never split (the caller passes no workspace)
+    sta_fwd_combine_kernel<D, QB><<<dim3(QB / 4, split_items), dim3(256), 0, stream>>>(static_cast<bf16_raw *>(o), p, order, n_bh);
+    return hipGetLastError();
+}
+
+template <int D, int QW, int KG, int WPE>
+hipError_t launch_group(const void *q, const void *k, const void *v, void *o, int B, const sta::FwdParams &p,
+                        const sta::WindowTable &win, const sta::HeadOrder &order, hipStream_t stream)
+{
+    sta::FwdPlan plan;
+    const uint32_t per_head = p.N / (QW * 32), n_bh = (uint32_t)B * p.heads;
+    plan.total = per_head * n_bh;
+    // as many rounds of chunks as eighths of a head would take, of equal length
+    const uint32_t eighth = (per_head + 7) / 8, rounds = (plan.total + 8 * eighth - 1) / (8 * eighth);
+    const uint32_t chunk = (plan.total + 8 * rounds - 1) / (8 * rounds);
+    plan.chunk = sta::fast_div_of(chunk);
+    plan.per_head = sta::fast_div_of(per_head);
+    plan.per_tile = sta::fast_div_of(p.P / (QW * 32));
+    plan.pair_items = sta::fast_div_of(2 * p.n_w * p.n_t);
+    plan.n_t = sta::fast_div_of(p.n_t);
+    plan.batch = sta::fast_div_of((uint32_t)B);
+    plan.sub_per_tile = sta::fast_div_of(p.P / kSub);
+    for (uint32_t h = 0; h < p.heads; ++h) {
+        plan.head[h].h = order.h[h];
+        for (int a = 0; a < 3; ++a) plan.head[h].w[a] = win.w[order.h[h]][a];
     }
+    const uint32_t ids = 8 * chunk * ((plan.total + 8 * chunk - 1) / (8 * chunk));
+    sta_fwd_group_kernel<D, QW, KG, WPE><<<dim3(ids), dim3(QW * KG * 64), 0, stream>>>(
+        static_cast<const bf16_raw *>(q), static_cast<const bf16_raw *>(k), static_cast<const bf16_raw *>(v),
+        static_cast<bf16_raw *>(o), p, plan);
+    return hipGetLastError();
+}
+
+// Shape of the key-group kernel for a launch.
+// Waves of queries: as many as the tile allows up to four (three for 96-token multiples), because a K/V unit brought into LDS
+// serves them all; five waves leave the four SIMDs uneven (tiles of 320 tokens: 585 us with five waves, 431 with two).
+// Key groups: the most, of 1, 2 and 4, with which the launch still fits the chip at once (16 waves per CU at head dimension
+// 64, 8 at 128) and a group has at least eight units to walk.  Measured around the line (us; 1, 2, 4 groups), head dimension
+// 64, 384-token tiles, 108 units: 324 waves of queries 45, 28, 24; 972 waves 62, 40, 38; 1944 waves 69, 66, 71; 2592 waves
+// 89, 94, 101.  64-token tiles, 18 units: 1024 waves 15.1, 12.6, 14.1; 2048 waves 17.3, 17.4, 22.9; 4096 waves 27.5, 30.1, 42.4.
+// Head dimension 128, 96-token tiles, about 75 units: 525 waves 50, 39, 34; 1050 waves 68, 78, 69.
+template <int D>
+hipError_t launch_groups(const void *q, const void *k, const void *v, void *o, int B, const sta::FwdParams &p,
+                         const sta::WindowTable &win, const sta::HeadOrder &order, hipStream_t stream)
+{
+    const uint64_t waves = (uint64_t)B * p.heads * (p.N / 32);
+    const uint32_t first = order.h[0];                      // the head with the most key tiles
+    uint32_t units = p.P / kSub;
+    const uint32_t n[3] = {p.n_t, p.n_h, p.n_w};
+    for (int a = 0; a < 3; ++a) {
+        const uint32_t kept = 2 * (win.w[first][a] / 2u) + 1;
+        units *= kept < n[a] ? kept : n[a];
+    }
+    const uint64_t fits = (uint64_t)resident_workgroups(1) * (D == 64 ? 16 : 8);
+    const int groups = 4 * waves <= fits && units >= 32 ? 4 : 2 * waves <= fits && units >= 16 ? 2 : 1;
+    if (p.P % 96 == 0 && p.P % 128 != 0) {
+        if (groups == 4) return launch_group<D, 3, 4, 3>(q, k, v, o, B, p, win, order, stream);
+        if (groups == 2) return launch_group<D, 3, 2, 3>(q, k, v, o, B, p, win, order, stream);
+        return launch_group<D, 3, 1, 3>(q, k, v, o, B, p, win, order, stream);
+    }
+    if (p.P % 64 == 0) {
+        constexpr int WPE = D == 64 ? 4 : 2;                // what registers and LDS allow
+        if (groups == 4) return launch_group<D, 2, 4, WPE>(q, k, v, o, B, p, win, order, stream);
+        if (groups == 2) return launch_group<D, 2, 2, WPE>(q, k, v, o, B, p, win, order, stream);
+        if (D == 64 && p.P % 128 == 0) return launch_group<64, 4, 1, 4>(q, k, v, o, B, p, win, order, stream);
+        return launch_group<D, 2, 1, WPE>(q, k, v, o, B, p, win, order, stream);
+    }
+    // other multiples of 32 tokens: one wave of queries, whose LDS stages then limit a CU to four such workgroups at head
+    // dimension 128, with or without key groups (525 waves: 59 us, two groups 74)
+    if (D == 64 && groups > 1) return launch_group<64, 1, 2, 2>(q, k, v, o, B, p, win, order, stream);
+    return launch_group<D, 1, 1, D == 64 ? 3 : 1>(q, k, v, o, B, p, win, order, stream);
 }
 
 // Test hook: the key-tile list of every (head, query tile) from the same box function.
@@ -1524,26 +1533,13 @@ hipError_t launch_forward(const void *q, const void *k, const void *v, void *o, 
                           hipStream_t stream)
 {
     if (!forward_supported((int)p.P, D)) return hipErrorInvalidValue;
-    if (D == 64) {
-        // Head dimension 64: the same kernel with 128-byte rows.  Measured (24 heads, 30x48x80, window 3x3x3):
-        // 12 waves with 64-key sub-blocks 1003 TFLOP/s, with 32-key sub-blocks 909; the register-staged general
-        // kernel 459.  64-token tiles (2D images) get 2-wave workgroups: 575 TFLOP/s on 128 heads of a 64x64 image
-        // (32-key sub-blocks, 2 stages; 64-key sub-blocks 501, 3 stages 537; general kernel 237).  That shape moves
-        // 147 KB of K and V from L2 per 9.4 MFLOP work item, about 9 TB/s at this rate: it is bound by L2, not MFMA.
-        if (p.P % 384 == 0) return launch_fast<64, 12, 64, 2, 1>(q, k, v, o, B, p, win, order, nullptr, 0, stream);
-        if (p.P % 128 == 0) return launch_fast<64, 4, 64, 2, 3>(q, k, v, o, B, p, win, order, nullptr, 0, stream);
-        if (p.P % 64 == 0) return launch_fast<64, 2, 32, 2, 3>(q, k, v, o, B, p, win, order, nullptr, 0, stream);
-        return launch_d<64>(q, k, v, o, B, p, win, stream);
-    }
+    if (D == 64) return launch_groups<64>(q, k, v, o, B, p, win, order, stream);
     // A tile of 384 tokens (the paper's 6x8x8) gets one 12-wave workgroup per query tile: every K/V sub-block
     // fetched from L2 then serves 384 queries instead of 128.  Measured at the 115,200-token layer, window
-    // 3x3x3: 12.8-13.1 ms against 13.6-13.7 ms for the 4-wave shape in the same session; 2 LDS stages were
-    // faster than 3 (13.15 ms) or 4 (13.3 ms).
-    if (p.P % 384 == 0)
-        return launch_fast<128, 12, 32, 2, 1, true>(q, k, v, o, B, p, win, order, split_ws, split_ws_floats, stream);
-    if (p.P % 128 == 0)
-        return launch_fast<128, 4, 32, 2, 3, true>(q, k, v, o, B, p, win, order, split_ws, split_ws_floats, stream);
-    return launch_d<128>(q, k, v, o, B, p, win, stream);
+    // 3x3x3: 12.8-13.1 ms against 13.6-13.7 ms for the 4-wave shape in the same session.
+    if (p.P % 384 == 0) return launch_x32<12, 32, 2, 1>(q, k, v, o, B, p, win, order, split_ws, split_ws_floats, stream);
+    if (p.P % 128 == 0) return launch_x32<4, 32, 2, 3>(q, k, v, o, B, p, win, order, split_ws, split_ws_floats, stream);
+    return launch_groups<128>(q, k, v, o, B, p, win, order, stream);
 }
 
 hipError_t launch_forward_general(const void *q, const void *k, const void *v, void *o, int B, int D, const FwdParams &p,

@@ -99,17 +99,6 @@ __device__ __forceinline__ shortx4 ds_read_tr16(uint32_t addr)
     return r;
 }
 
-// Issue the 2*DB transposing reads of one 16-key group (A operands of DB PV MFMAs).
-template <int BASE, int DB, int ROWB>
-__device__ __forceinline__ void pv_issue(shortx4 (&va)[DB][2], const uint32_t (&v_addr)[DB])
-{
-    static_for<0, DB>([&](auto dbi) {
-        constexpr int db = decltype(dbi)::value;
-        va[db][0] = ds_read_tr16<BASE>(v_addr[db]);
-        va[db][1] = ds_read_tr16<BASE + 8 * ROWB>(v_addr[db]);
-    });
-}
-
 // One 16-byte LDS read with a compile-time byte offset.
 template <int OFF>
 __device__ __forceinline__ bf16x8 ds_read_b128_at(uint32_t addr)
@@ -117,26 +106,6 @@ __device__ __forceinline__ bf16x8 ds_read_b128_at(uint32_t addr)
     bf16x8 r;
     asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(r) : "v"(addr), "n"(OFF));
     return r;
-}
-
-// Issue the K-operand reads of one group of 4 MFMA k-steps (A operands of S^T = K Q^T).
-// k_addr[ks] is the lane's LDS address of its chunk for k-step ks in stage 0, row block 0; BASE (a compile-time
-// byte offset, e.g. the stage) goes into the instruction's immediate.  GPM: groups per 32-row block (k-steps / 4).
-template <int G, int ROWB, int BASE, int GPM = 2, int KS>
-__device__ __forceinline__ void k_issue(bf16x8 (&ka)[4], const uint32_t (&k_addr)[KS])
-{
-    static_assert(KS == 4 * GPM, "k-steps per row block");
-    constexpr int mb = G / GPM, ks0 = 4 * (G % GPM);
-    static_for<0, 4>([&](auto i) {
-        constexpr int ks = ks0 + decltype(i)::value;
-        ka[decltype(i)::value] = ds_read_b128_at<BASE + mb * 32 * ROWB>(k_addr[ks]);
-    });
-}
-
-template <int PENDING>
-__device__ __forceinline__ void k_wait(bf16x8 (&ka)[4])
-{
-    asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(ka[0]), "+v"(ka[1]), "+v"(ka[2]), "+v"(ka[3]) : "n"(PENDING));
 }
 
 template <int PENDING>

@@ -55,6 +55,38 @@ struct FwdParams {
     float *split_ws = nullptr;
 };
 
+// Division of any 32-bit number by a launch constant with one multiplication: n / d = (((n - q) >> pre) + q) >> post
+// with q = the upper half of n * magic.
+struct FastDiv {
+    uint32_t d, magic;
+    uint32_t pre, post;
+};
+inline FastDiv fast_div_of(uint32_t d)
+{
+    const uint32_t s = d <= 1 ? 0 : 32 - __builtin_clz(d - 1);      // ceil(log2 d)
+    FastDiv f;
+    f.d = d;
+    f.magic = (uint32_t)(((((uint64_t)1 << s) - d) << 32) / d) + 1;
+    f.pre = s < 1 ? s : 1;
+    f.post = s < 1 ? 0 : s - 1;
+    return f;
+}
+
+// How the work items of one forward launch are dealt to the workgroups, with everything a workgroup would otherwise have
+// to find by division (see fwd_item_of).
+struct FwdPlan {
+    uint32_t total;            // work items
+    FastDiv chunk;             // consecutive items of one XCD
+    FastDiv per_head;          // items of one (batch, head)
+    FastDiv per_tile;          // items of one query tile
+    FastDiv pair_items;        // query tiles of two tile rows
+    FastDiv n_t, batch;
+    FastDiv sub_per_tile;      // 32-key units of a key tile
+    struct Head {
+        uint16_t h, w[3];      // head inside the launch, its window in tiles; most expensive head first
+    } head[kMaxHeadsPerLaunch];
+};
+
 // Returns hipErrorInvalidValue if no kernel instance exists for (P, D).
 // split_ws: optional device scratch for work splitting (null: every item is run by one workgroup).
 hipError_t launch_forward(const void *q, const void *k, const void *v, void *o, int B, int D,

@@ -1,0 +1,54 @@
+"""GPU parity of the key-group forward kernel at the edges of its shapes: one, two and four key groups, shares of the walk
+that do not divide evenly, every number of waves of queries, and the log-denominators merged over the groups."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2502_04507_amd as sta
+import synth_inputs as syn
+from oracle import sta_oracle as orc
+from tests import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+# The launches are small enough to fit the chip, so the number of 32-key units of the widest head decides: four groups from
+# 32 on, two from 16 on.  (grid, tile, per-head windows; units of each head)
+SHAPES = [
+    ("p32", (1, 16, 48), (1, 4, 8), [(1, 3, 5), (1, 1, 1)]),            # 15 and 1 units: one group
+    ("p32-two", (1, 16, 48), (1, 4, 8), [(1, 3, 6), (1, 3, 5)]),        # 18 and 15: two groups, an odd share
+    ("p96", (4, 18, 40), (2, 6, 8), [(1, 1, 5), (1, 1, 1)]),            # 15 and 3: one group
+    ("p96-two", (4, 18, 40), (2, 6, 8), [(1, 3, 3), (1, 1, 1)]),        # 27 and 3: two groups
+    ("p96-four", (4, 18, 40), (2, 6, 8), [(2, 3, 5), (1, 1, 1)]),       # 90 and 3: four groups, one of them without a unit
+    ("p64", (1, 40, 56), (1, 8, 8), [(1, 1, 7), (1, 1, 1)]),            # 14 and 2: one group
+    ("p64-two", (1, 40, 56), (1, 8, 8), [(1, 3, 3), (1, 2, 3)]),        # 18: two groups
+    ("p64-four", (1, 40, 56), (1, 8, 8), [(1, 5, 7), (1, 1, 1)]),       # 70 and 2: four groups, two of them without a unit
+    ("p128", (4, 24, 24), (2, 8, 8), [(1, 1, 3), (1, 1, 1)]),           # 12 and 4: one group
+    ("p128-two", (4, 24, 24), (2, 8, 8), [(2, 1, 3), (1, 3, 1)]),       # 24 and 12: two groups
+    ("p160", (5, 8, 12), (5, 8, 4), [(1, 1, 3), (1, 1, 1)]),            # 15 and 5: one group
+    ("p384", (6, 16, 16), (6, 8, 8), [(1, 1, 1), (1, 1, 1)]),           # 12: one group
+    ("p384-four", (6, 16, 24), (6, 8, 8), [(1, 2, 2), (1, 1, 1)]),      # 72 and 12: four groups
+]
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("name,grid,tile,windows", SHAPES, ids=[s[0] for s in SHAPES])
+def test_key_groups_match_the_oracle(name, grid, tile, windows, D):
+    w = syn.custom(name, 1, len(windows), D, grid, tile, windows, "bf16", seed=5150)
+    q, k, v = syn.make_qkv(w)
+    order = torch.from_numpy(orc.tile_order(w.grid, w.tile))
+    qt, kt, vt = (x[:, :, order].contiguous().to(DEV) for x in (q, k, v))
+    o = torch.full_like(qt, float("nan"))
+    lse = torch.full(qt.shape[:3], float("nan"), dtype=torch.float32, device=DEV)
+    sta.sta_forward_lse(qt, kt, vt, o, lse, w.grid, w.tile, w.window_tiles)
+    again = torch.full_like(qt, float("nan"))
+    sta.sta_forward(qt, kt, vt, again, w.grid, w.tile, w.window_tiles)
+    torch.cuda.synchronize()
+    assert torch.equal(again.view(torch.int16), o.view(torch.int16))
+    order = order.numpy()
+    for h in range(w.H):
+        ref_o, ref_lse = orc.attention(q[0, h].float().numpy(), k[0, h].float().numpy(), v[0, h].float().numpy(), w.grid,
+                                       w.tile, orc.window_tiles_to_tokens(w.window_tiles[h], w.tile), return_lse=True)
+        gu.assert_parity(o[0, h].float().cpu().numpy(), ref_o[order], "%s D%d h%d" % (name, D, h))
+        # bf16-rounded probabilities are summed: 2^-9 relative each, independent, so below 2^-9 = 2e-3 in the log
+        assert np.abs(lse[0, h].cpu().numpy() - ref_lse[order]).max() <= 2e-3
