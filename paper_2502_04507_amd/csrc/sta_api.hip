@@ -484,9 +484,11 @@ int sta_backward(const void *q_tiled, const void *k_tiled, const void *v_tiled, 
         fill_window_table(&win, window_tiles, hb, heads, s.n);
         p.head_base = hb;
         p.heads = heads;
+        sta::HeadOrder order;
+        fill_head_order(&order, window_tiles, hb, heads, s.n);
         hipError_t e = sta::launch_backward(q_tiled, k_tiled, v_tiled, o_tiled, d_o_tiled, lse_tiled,
-                                            static_cast<float *>(workspace), hb == 0, d_q_tiled, d_k_tiled, d_v_tiled, B,
-                                            D, p, win, static_cast<hipStream_t>(hip_stream));
+                                            static_cast<float *>(workspace), (size_t)B * H * s.N, d_q_tiled, d_k_tiled, d_v_tiled,
+                                            B, D, p, win, order, static_cast<hipStream_t>(hip_stream));
         if (e != hipSuccess) return STA_ERR_HIP;
     }
     return STA_OK;

@@ -405,11 +405,6 @@ struct GroupItem {
     uint32_t qblock;
     StaBox box;
 };
-__device__ __forceinline__ uint32_t fast_div(uint32_t n, const sta::FastDiv &f)
-{
-    const uint32_t q = __umulhi(n, f.magic);
-    return (((n - q) >> f.pre) + q) >> f.post;
-}
 __device__ __forceinline__ GroupItem group_item_of(uint32_t id, const sta::FwdParams &p, const sta::FwdPlan &plan)
 {
     GroupItem it;
@@ -1323,18 +1318,7 @@ __global__ __launch_bounds__(256) void sta_fwd_combine_kernel(bf16_raw *__restri
 }
 
 // Host side of the work splitting: how many workgroups the chip holds at once.
-inline uint32_t resident_workgroups(int minb)
-{
-    static int cus = 0;
-    if (cus == 0) {
-        int dev = 0, n = 0;
-        if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0)
-            cus = n;
-        else
-            cus = 256;
-    }
-    return (uint32_t)cus * (uint32_t)minb;
-}
+inline uint32_t resident_workgroups(int minb) { return sta::compute_units() * (uint32_t)minb; }
 
 template <int NW, int KB, int STAGES, int MINB>
 hipError_t launch_x32(const void *q, const void *k, const void *v, void *o, int B, const sta::FwdParams &p_in,
@@ -1516,6 +1500,16 @@ hipError_t launch_d(const void *q, const void *k, const void *v, void *o, int B,
 
 namespace sta {
 
+uint32_t compute_units()
+{
+    static const int cus = []() {
+        int dev = 0, n = 0;
+        return hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0
+                   ? n
+                   : 256;
+    }();
+    return (uint32_t)cus;
+}
 
 bool forward_supported(int P, int D) { return (D == 64 || D == 128) && P > 0 && P % 32 == 0; }
 

@@ -8,10 +8,10 @@
 //   dS_ij = P_ij (dP_ij - delta_i)     delta_i = dO_i . O_i
 //   dQ_i  = scale * sum_j dS_ij K_j    dK_j = scale * sum_i dS_ij Q_i
 //
-// Three kernels, no atomics, results repeatable:
-//   sta_bwd_delta_kernel  -delta_i and -lse_i / scale for every query row (HBM-bound, reads O and dO once);
+// Two kernels, no atomics, results repeatable:
 //   sta_bwd_dq_kernel     one workgroup per query block, walks the key tiles of its window (as the forward
-//                         kernel does): 3 MFMA products per block (K Q^T, V dO^T, K^T dS^T);
+//                         kernel does): 3 MFMA products per block (K Q^T, V dO^T, K^T dS^T); it also forms
+//                         -delta_i and -lse_i / scale of its queries and leaves them for the second kernel;
 //   sta_bwd_dkv_kernel    one workgroup per key block, walks the QUERY tiles that keep its key tile (the
 //                         transposed box): 4 MFMA products per block (Q K^T, dO V^T, dO^T P, Q^T dS), split
 //                         over pairs of waves.
@@ -24,8 +24,8 @@
 // global_load_lds; an operand may be read both by rows (A rows = tokens, 16-byte reads) and transposed (A rows =
 // channels, ds_read_b64_tr_b16), and one LDS layout serves both without bank conflicts (described where the two
 // products are defined).
-// These kernels: head dimension 64 or 128, tokens per tile a multiple of 128.  Other shapes (tiles that are other
-// multiples of 32 tokens) go through the simple kernels further down.
+// Both kernels: head dimension 64 or 128, any tile of a multiple of 32 tokens.  A workgroup's columns are the largest of
+// a few sizes that divides the tile; launches too small for the chip are cut into walk groups (see WalkShare).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -36,57 +36,143 @@
 
 namespace {
 
-constexpr int kNW = 4;                 // waves per workgroup, 32 columns each
-constexpr int kCols = kNW * 32;        // queries (dQ kernel) or keys (dK/dV kernel) per workgroup
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
+// How the column blocks (queries or keys) of one launch are dealt to the workgroups, with every division prepared.
+struct BwdPlan {
+    uint32_t total;            // column blocks
+    sta::FastDiv chunk;        // consecutive blocks of one XCD
+    sta::FastDiv per_head;     // blocks of one (batch, head)
+    sta::FastDiv per_tile;     // blocks of one tile
+    sta::FastDiv n_w, n_h, batch;
+    sta::FastDiv sub_per_tile; // 32-token sub-blocks of a tile
+    float inv_scale;           // 1 / softmax scale
+    struct Head {
+        uint16_t h, w[3];      // head inside the launch, its window in tiles; most expensive head first
+    } head[sta::kMaxHeadsPerLaunch];
+};
+
 // Work item of a workgroup.  The hardware deals workgroup ids round-robin over the 8 XCDs (each with its own
-// L2).  The launch's column blocks, taken head after head, are cut into chunks of `chunk` consecutive blocks and
+// L2).  The launch's column blocks, taken head after head, are cut into chunks of consecutive blocks and
 // the chunks are dealt to the XCDs in turn: the blocks resident on one XCD at a time are then neighbours that
 // share most of their windows, while all XCDs together still work on one region of one head.
-// Returns false for the padding ids of the launch.
-__device__ __forceinline__ bool work_item(uint32_t chunk, uint32_t blocks_per_head, uint32_t n_bh, uint32_t *block,
-                                          uint32_t *bh_rank)
+// QUERY_COLS: the columns are queries and the box holds the key tiles of their tile; otherwise the columns are keys and
+// the box holds the query tiles that keep their tile.
+struct BwdItem {
+    bool valid;                // false for the padding ids of the launch
+    uint32_t block;            // column block inside the head
+    size_t bh;
+    StaBox box;
+};
+template <bool QUERY_COLS>
+__device__ __forceinline__ BwdItem bwd_item_of(uint32_t id, const sta::FwdParams &p, const BwdPlan &plan)
 {
-    const uint32_t xcd = blockIdx.x & 7, s = blockIdx.x >> 3;
-    const uint32_t linear = ((s / chunk) * 8 + xcd) * chunk + s % chunk;
-    if (linear >= blocks_per_head * n_bh) return false;
-    *bh_rank = linear / blocks_per_head;
-    *block = linear - *bh_rank * blocks_per_head;
-    return true;
+    BwdItem it;
+    const uint32_t xcd = id & 7, slot = id >> 3;
+    const uint32_t chunk = fast_div(slot, plan.chunk);
+    const uint32_t linear = (chunk * 8 + xcd) * plan.chunk.d + (slot - chunk * plan.chunk.d);
+    it.valid = linear < plan.total;
+    if (!it.valid) return it;
+    const uint32_t rank = fast_div(linear, plan.per_head);
+    it.block = linear - rank * plan.per_head.d;
+    const uint32_t head_rank = fast_div(rank, plan.batch);          // batch entries of one head are adjacent
+    const BwdPlan::Head head = plan.head[head_rank];
+    it.bh = (size_t)(rank - head_rank * plan.batch.d) * p.H + p.head_base + head.h;
+    const uint32_t tile = fast_div(it.block, plan.per_tile);
+    const uint32_t row = fast_div(tile, plan.n_w), w = tile - row * plan.n_w.d;
+    const uint32_t t = fast_div(row, plan.n_h), h = row - t * plan.n_h.d;
+    if constexpr (QUERY_COLS) {
+        it.box.t = sta_axis_range(p.n_t, head.w[0], t);
+        it.box.h = sta_axis_range(p.n_h, head.w[1], h);
+        it.box.w = sta_axis_range(p.n_w, head.w[2], w);
+    } else {
+        it.box.t = sta_axis_query_range(p.n_t, head.w[0], t);
+        it.box.h = sta_axis_query_range(p.n_h, head.w[1], h);
+        it.box.w = sta_axis_query_range(p.n_w, head.w[2], w);
+    }
+    return it;
 }
 
-// ---------------------------------------------------------------------------------------------------------
-// Row statistics in the form the two kernels below start their accumulators with: neg_delta_i = -(dO_i . O_i)
-// and neg_lse_i = -lse_i / scale, so that the matrix instructions deliver dP - delta and S - lse / scale and
-// neither a subtraction nor a fused multiply-add per element is left (P = 2^(scale * log2(e) * (S - lse / scale))).
-// One group of D / 8 lanes per row (each lane 16 bytes of it).
-// ---------------------------------------------------------------------------------------------------------
-template <int D>
-__global__ __launch_bounds__(256) void sta_bwd_delta_kernel(const uint4 *__restrict__ o, const uint4 *__restrict__ d_o,
-                                                            const float *__restrict__ lse, float inv_scale,
-                                                            float *__restrict__ neg_delta, float *__restrict__ neg_lse,
-                                                            size_t rows)
-{
-    constexpr int LPR = D / 8;                          // lanes per row
-    const size_t row = (size_t)blockIdx.x * (256 / LPR) + (threadIdx.x / LPR);
-    const int part = threadIdx.x % LPR;
-    float acc = 0.f;
-    if (row < rows) {
-        const uint4 a = o[row * LPR + part], b = d_o[row * LPR + part];
-        const uint32_t as[4] = {a.x, a.y, a.z, a.w}, bs[4] = {b.x, b.y, b.z, b.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            acc = fmaf(__uint_as_float(as[e] << 16), __uint_as_float(bs[e] << 16), acc);
-            acc = fmaf(__uint_as_float(as[e] & 0xffff0000u), __uint_as_float(bs[e] & 0xffff0000u), acc);
+// A walk group's share of an item's walk, in sub-blocks: group g of G takes [n * g / G, n * (g + 1) / G).  The groups of a
+// workgroup hold the same columns, have LDS stages of their own and are summed through LDS at the end.
+template <int G>
+struct WalkShare {
+    BoxWalk walk;
+    int n_units, n_steps;      // this group's sub-blocks; the largest share of any group (all groups pass the same barriers)
+    __device__ __forceinline__ void start(const StaBox &box, const sta::FwdParams &p, const BwdPlan &plan, int group)
+    {
+        walk.start(box, p.n_h, p.n_w, p.P);
+        const int n_all = box.count() * walk.sub_per_tile;
+        n_steps = (n_all + G - 1) / G;
+        n_units = n_all;
+        if constexpr (G > 1) {
+            const int lo = n_all * group / G;
+            n_units = n_all * (group + 1) / G - lo;
+            const uint32_t tiles = fast_div((uint32_t)lo, plan.sub_per_tile);
+            walk.skip(tiles, (uint32_t)lo - tiles * plan.sub_per_tile.d);
         }
     }
+};
+
+// Sums the accumulators of the walk groups into group 0, in a fixed order: the upper half of the remaining groups hands
+// its accumulators to the lower half through LDS until one is left.  WAVES: waves per group, wave: index inside it.
+// Every wave of the workgroup calls this; all LDS reads of the stages are over when it starts to write.
+template <int G, int WAVES, int CB>
+__device__ __forceinline__ void merge_groups(char *smem, int group, int wave, int lane, floatx4 (&acc)[CB][2])
+{
+    constexpr int PART = CB * 2 * 1024;
+    __syncthreads();
 #pragma unroll
-    for (int off = LPR / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off, LPR);
-    if (row < rows && part == 0) {
-        neg_delta[row] = -acc;
-        neg_lse[row] = -lse[row] * inv_scale;
+    for (int n = G; n > 1; n = (n + 1) / 2) {
+        const int half = (n + 1) / 2;                           // groups half .. n-1 give, groups 0 .. n-1-half take
+        if (n != G) __syncthreads();                            // the previous round has been read
+        if (group >= half && group < n) {
+            char *to = smem + ((group - half) * WAVES + wave) * PART + lane * 16;
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                for (int col = 0; col < 2; ++col) *reinterpret_cast<floatx4 *>(to + (cb * 2 + col) * 1024) = acc[cb][col];
+        }
+        __syncthreads();
+        if (group + half < n) {
+            const char *from = smem + (group * WAVES + wave) * PART + lane * 16;
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+                for (int col = 0; col < 2; ++col) acc[cb][col] += *reinterpret_cast<const floatx4 *>(from + (cb * 2 + col) * 1024);
+        }
+    }
+    __syncthreads();
+}
+
+// A wave's 32 result rows (columns of its accumulators), scaled, rounded to bf16 and written as whole rows, 1 KB contiguous
+// per store instruction, through a part of LDS that belongs to the wave (16 rows at a time).
+template <int D>
+__device__ __forceinline__ void store_columns(char *wave_lds, const floatx4 (&acc)[D / 16][2], float mul, bf16_raw *dst, int lane)
+{
+    using L = Staged<D>;
+    constexpr int LPR = L::RowB / 16;                           // 16-byte chunks per row
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    const int c16 = lane & 15, g4 = lane >> 4;
+#pragma unroll
+    for (int col = 0; col < 2; ++col) {
+        // acc[cb][col][i] = channel 16*cb + 4*g4 + i of row 16*col + c16
+#pragma unroll
+        for (int cb = 0; cb < L::CB; ++cb) {
+            bf16x4 ov;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) ov[t] = static_cast<__bf16>(acc[cb][col][t] * mul);
+            const int chunk = 2 * cb + (g4 >> 1);
+            *reinterpret_cast<bf16x4 *>(wave_lds + c16 * L::RowB + ((chunk ^ (c16 & (LPR - 1))) << 4) + 8 * (g4 & 1)) = ov;
+        }
+        char *out = reinterpret_cast<char *>(dst + (size_t)(16 * col) * D);
+#pragma unroll
+        for (int i = 0; i < 16 / L::GroupRows; ++i) {
+            const int r = L::GroupRows * i + lane / LPR, cpos = lane % LPR;
+            const u32x4 x = *reinterpret_cast<const u32x4 *>(wave_lds + r * L::RowB + ((cpos ^ (r & (LPR - 1))) << 4));
+            __builtin_nontemporal_store(x, reinterpret_cast<u32x4 *>(out + (size_t)r * L::RowB + (cpos << 4)));
+        }
     }
 }
 
@@ -95,68 +181,84 @@ __device__ __forceinline__ void lds_write_b128(uint32_t addr, bf16x8 v)
     asm volatile("ds_write_b128 %0, %1" ::"v"(addr), "v"(v) : "memory");
 }
 
+constexpr int max_of(int a, int b) { return a > b ? a : b; }
+
 // ---------------------------------------------------------------------------------------------------------
-// dQ.  One workgroup of 4 waves per 128 queries (two workgroups per CU at head dimension 128, 206 registers); a lane
-// holds query column c16 of its wave's two 16-query blocks.  LDS stage: K (read by rows and transposed) and V (read by
-// rows), in the layout described above.  Per wave and 32-key sub-block: S^T = K Q^T - lse / scale and
-// dP^T = V dO^T - delta (the statistics of the lane's query as the initial value), dS^T = 2^(c S^T) o dP^T,
-// dQ^T += K^T dS^T; 16 matrix instructions each at head dimension 128, 8 at 64.
+// dQ.  One workgroup of QW waves per 32 * QW queries (times G walk groups); a lane holds query column c16 of its wave's two
+// 16-query blocks.  At head dimension 128 206 registers, two waves per SIMD; at 64 three.  LDS stage: K (read by rows and
+// transposed) and V (read by rows), in the layout described above.  Per wave and 32-key sub-block: S^T = K Q^T - lse / scale
+// and dP^T = V dO^T - delta (the statistics of the lane's query as the initial value, so that neither a subtraction nor a
+// fused multiply-add per element is left), dS^T = 2^(c S^T) o dP^T, dQ^T += K^T dS^T; 16 matrix instructions each at head
+// dimension 128, 8 at 64.
+// The row statistics are formed here, from the dO fragments the wave holds anyway and the same fragments of O, and written
+// for the dK/dV kernel (a kernel of their own for them read dO once more: 6.8 us of a 345 us training step at 16,384 tokens
+// x 8 heads of dimension 64, 0.23 ms of 53 ms at 115,200 x 24 of 128).
 // ---------------------------------------------------------------------------------------------------------
-template <int D>
-__global__ __launch_bounds__(kNW * 64, 2) void sta_bwd_dq_kernel(const bf16_raw *__restrict__ q,
-                                                                 const bf16_raw *__restrict__ k,
-                                                                 const bf16_raw *__restrict__ v,
-                                                                 const bf16_raw *__restrict__ d_o,
-                                                                 const float *__restrict__ neg_lse,
-                                                                 const float *__restrict__ neg_delta,
-                                                                 bf16_raw *__restrict__ d_q, sta::FwdParams p,
-                                                                 sta::WindowTable win, uint32_t n_bh, uint32_t chunk)
+template <int D, int QW, int G>
+__global__ __attribute__((amdgpu_flat_work_group_size(QW * G * 64, QW * G * 64), amdgpu_waves_per_eu(D == 64 ? 3 : QW == 1 ? 1 : 2)))
+void sta_bwd_dq_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restrict__ k, const bf16_raw *__restrict__ v,
+                       const bf16_raw *__restrict__ o, const bf16_raw *__restrict__ d_o, const float *__restrict__ lse,
+                       float *__restrict__ neg_delta, float *__restrict__ neg_lse, bf16_raw *__restrict__ d_q,
+                       sta::FwdParams p, BwdPlan plan)
 {
     using L = Staged<D>;
     constexpr int KS = L::KS, CB = L::CB;
+    constexpr int COLS = QW * 32;                       // queries per workgroup
     constexpr int STAGE_B = 2 * L::Tile;
     constexpr int K_TILE = 0, V_TILE = L::Tile;
-    constexpr int LOADS = L::Groups / kNW;              // DMA instructions per operand and wave: 2 or 1
-    __shared__ __attribute__((aligned(1024))) char smem[2 * STAGE_B];
+    constexpr int GROUP_B = 2 * STAGE_B;                // LDS of one walk group: two stages
+    constexpr int OPS = 2 * L::Groups;                  // DMA instructions per sub-block
+    constexpr int WAVE_OPS = (OPS + QW - 1) / QW;       // at most this many per wave
+    constexpr int WAVE_OUT = 16 * L::RowB;
+    constexpr int SMEM = max_of(G * GROUP_B, max_of((G / 2) * QW * CB * 2 * 1024, QW * WAVE_OUT));
+    __shared__ __attribute__((aligned(1024))) char smem[SMEM];
 
-    uint32_t qblock, bh_rank;
-    if (!work_item(chunk, p.N / kCols, n_bh, &qblock, &bh_rank)) return;
-    const uint32_t heads = p.heads;
-    const uint32_t h_local = bh_rank % heads, b = bh_rank / heads;
-    const size_t bh = (size_t)b * p.H + p.head_base + h_local;
-    const uint32_t q_tile = (qblock * kCols) / p.P;
-    const StaBox box = sta_key_tile_box_of(p.n_t, p.n_h, p.n_w, win.w[h_local][0], win.w[h_local][1], win.w[h_local][2],
-                                           q_tile);
+    const BwdItem item = bwd_item_of<true>(blockIdx.x, p, plan);
+    if (!item.valid) return;
+    const size_t bh = item.bh;
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int group = wave / QW, qw = wave % QW;
     const int lane = tid & 63, c16 = lane & 15, g4 = lane >> 4;
 
-    const size_t my_row = bh * p.N + (size_t)qblock * kCols + (size_t)wave * 32;
+    const size_t my_row = bh * p.N + (size_t)item.block * COLS + (size_t)qw * 32;
     const char *kh = reinterpret_cast<const char *>(k + bh * p.N * D);
     const char *vh = reinterpret_cast<const char *>(v + bh * p.N * D);
 
-    // DMA: each operand is L::Groups instructions of 1 KB; wave w issues the groups LOADS * w .. of each.
+    WalkShare<G> share;
+    share.start(item.box, p, plan, group);
+
+    // DMA: each operand is L::Groups instructions of 1 KB; wave qw of the group issues the instructions qw, qw + QW, ..
     const uint32_t src_lane_off = L::dma_lane_offset(lane);
-    auto issue_loads = [&](int stage, uint32_t first_row) {
+    int issued = 0;
+    auto issue_next = [&]() __attribute__((always_inline)) {
+        if (issued >= share.n_units) return;
         uint32_t off = src_lane_off;
         asm volatile("" : "+v"(off));                   // keep the lane offset 32-bit next to a scalar base
+        const uint32_t first_row = share.walk.next_row;
+        share.walk.advance();
+        char *stage = smem + group * GROUP_B + (issued & 1) * STAGE_B;
 #pragma unroll
-        for (int i = 0; i < LOADS; ++i) {
-            const int group = LOADS * wave + i;
-            const size_t base = (size_t)(first_row + L::GroupRows * group) * L::RowB;
-            char *dst = smem + stage * STAGE_B + group * L::Group;
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(kh + base + off),
-                                             STA_LDS_PTR(dst + K_TILE), 16, 0, 0);
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(vh + base + off),
-                                             STA_LDS_PTR(dst + V_TILE), 16, 0, 0);
+        for (int i = 0; i < WAVE_OPS; ++i) {
+            const int j = qw + i * QW;
+            if (OPS % QW == 0 || j < OPS) {
+                const bool is_v = j >= L::Groups;
+                const int part = j % L::Groups;
+                const char *src = (is_v ? vh : kh) + (size_t)(first_row + L::GroupRows * part) * L::RowB;
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + off),
+                                                 STA_LDS_PTR(stage + (is_v ? V_TILE : K_TILE) + part * L::Group), 16, 0, 0);
+            }
         }
+        ++issued;
     };
+    issue_next();
 
     uint32_t row_addr[KS], tr_addr[4];
-    L::addresses((uint32_t)(uintptr_t)smem, lane, row_addr, tr_addr);
+    L::addresses((uint32_t)(uintptr_t)smem + (uint32_t)(group * GROUP_B), lane, row_addr, tr_addr);
 
     // resident B fragments: query 16*qb + c16, channels 32*ks + 8*g4 ..
     bf16x8 Qr[2][KS], Gr[2][KS];
+    float delta[2] = {0.f, 0.f};
 #pragma unroll
     for (int qb = 0; qb < 2; ++qb)
 #pragma unroll
@@ -164,15 +266,23 @@ __global__ __launch_bounds__(kNW * 64, 2) void sta_bwd_dq_kernel(const bf16_raw 
             const size_t at = (my_row + 16 * qb + c16) * D + ks * 32 + g4 * 8;
             Qr[qb][ks] = *reinterpret_cast<const bf16x8 *>(q + at);
             Gr[qb][ks] = *reinterpret_cast<const bf16x8 *>(d_o + at);
+            const bf16x8 out = *reinterpret_cast<const bf16x8 *>(o + at);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) delta[qb] = fmaf(static_cast<float>(out[e]), static_cast<float>(Gr[qb][ks][e]), delta[qb]);
         }
     const float c = p.scale_log2e;
     // a lane owns one query column per block: the four registers of an accumulator all start at that query's statistic
     floatx4 s_init[2], dp_init[2];
 #pragma unroll
     for (int qb = 0; qb < 2; ++qb) {
-        const float a = neg_lse[my_row + 16 * qb + c16], d = neg_delta[my_row + 16 * qb + c16];
+        const size_t row = my_row + 16 * qb + c16;
+        const float a = -lse[row] * plan.inv_scale, d = -quad_lane_sum(delta[qb]);
         s_init[qb] = floatx4{a, a, a, a};
         dp_init[qb] = floatx4{d, d, d, d};
+        if (group == 0 && g4 == 0) {
+            neg_lse[row] = a;
+            neg_delta[row] = d;
+        }
     }
 
     floatx4 dQ[CB][2];                                  // [channel block][query block]
@@ -181,24 +291,12 @@ __global__ __launch_bounds__(kNW * 64, 2) void sta_bwd_dq_kernel(const bf16_raw 
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb) dQ[cb][qb] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-    BoxWalk walk;
-    walk.start(box, p.n_h, p.n_w, p.P);
-    const int n_iter = box.count() * walk.sub_per_tile;
-    int issued = 0;
-    auto issue_next = [&]() {
-        if (issued < n_iter) {
-            issue_loads(issued & 1, walk.next_row);
-            walk.advance();
-            ++issued;
-        }
-    };
-    issue_next();
-
-    auto sub_block = [&](auto stage_c) {
+    auto sub_block = [&](auto stage_c, int unit) __attribute__((always_inline)) {
         constexpr int ST = decltype(stage_c)::value * STAGE_B;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         issue_next();
+        if (G > 1 && unit >= share.n_units) return;
         floatx4 S[2][2], dP[2][2];                      // [key block][query block]
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
@@ -224,109 +322,119 @@ __global__ __launch_bounds__(kNW * 64, 2) void sta_bwd_dq_kernel(const bf16_raw 
                     dSb[qb][4 * kb + e] = static_cast<__bf16>(__builtin_amdgcn_exp2f(S[kb][qb][e] * c) * dP[kb][qb][e]);
         k_t.run(tr_addr, dSb, dQ);                                       // dQ^T += K^T dS^T
     };
-    for (int iter = 0; iter < n_iter; iter += 2) {
-        sub_block(std::integral_constant<int, 0>{});
-        if (iter + 1 < n_iter) sub_block(std::integral_constant<int, 1>{});
+    for (int u = 0; u < share.n_steps; u += 2) {
+        sub_block(std::integral_constant<int, 0>{}, u);
+        if (u + 1 < share.n_steps) sub_block(std::integral_constant<int, 1>{}, u + 1);
     }
-    // dQ[cb][qb][i] = channel 16*cb + 4*g4 + i of query 16*qb + c16
-    const float mul = c * kLn2;
-#pragma unroll
-    for (int qb = 0; qb < 2; ++qb)
-#pragma unroll
-        for (int cb = 0; cb < CB; ++cb) {
-            bf16x4 ov;
-#pragma unroll
-            for (int t = 0; t < 4; ++t) ov[t] = static_cast<__bf16>(dQ[cb][qb][t] * mul);
-            *reinterpret_cast<bf16x4 *>(d_q + (my_row + 16 * qb + c16) * D + 16 * cb + 4 * g4) = ov;
-        }
+    if constexpr (G > 1) {
+        merge_groups<G, QW>(smem, group, qw, lane, dQ);
+        if (group != 0) return;
+    } else {
+        __syncthreads();                                // every wave has finished reading the stages
+    }
+    store_columns<D>(smem + qw * WAVE_OUT, dQ, c * kLn2, d_q + my_row * D, lane);
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// dK, dV.  One workgroup of 2 * NPAIR waves per 32 * NPAIR keys.  Each 32-key column block is served by a PAIR of
-// waves: the first holds K and accumulates dV (S = Q K^T, P, dV^T += dO^T P), the second holds V and accumulates dK
-// (dP = dO V^T, dS = P o (dP - delta), dK^T += Q^T dS).  P, rounded to bf16 and packed as the MFMA B operand, goes
-// from the first to the second through 2 KB of LDS.  Four matrix products per block, no duplicate work inside the
+// dK, dV.  One workgroup of 2 * NPAIR waves per 32 * NPAIR keys (times G walk groups).  Each 32-key column block is served
+// by a PAIR of waves: the first holds K and accumulates dV (S = Q K^T, P, dV^T += dO^T P), the second holds V and accumulates
+// dK (dP = dO V^T, dS = P o (dP - delta), dK^T += Q^T dS).  P goes from the first to the second through LDS: in fp32 in
+// workgroups of up to three pairs, rounded to bf16 and packed as the MFMA B operand (half the LDS traffic) in the larger
+// ones, which serve tiles of 128 tokens' multiples.  Four matrix products per block, no duplicate work inside the
 // kernel, and each wave keeps one accumulator set: at head dimension 128, per wave and 32-query sub-block 32 matrix
 // instructions, 40 vector instructions and 26 LDS reads in 158 registers, so that three waves per SIMD fit (six pairs:
-// 192 keys per workgroup); at head dimension 64 it is 106 registers and two workgroups of four pairs share a CU.
+// 192 keys per workgroup); at head dimension 64 it is 106 registers and four waves per SIMD.
 // LDS stage: Q and dO (each read by rows and transposed) and the row statistics of the 32 queries.
+// What bounds it: the matrix pipe is busy 55 % of the cycles at head dimension 128 (30x48x80 grid, 24 heads, window 3x3x3:
+// 23.6 ms, 1200 TFLOP/s), at 64 the LDS reads take as long as the matrix instructions.  Tiles that are no multiple of 128
+// tokens went through one wave per workgroup with register-staged operands before (both kernels, the statistics included, in
+// us): 32 heads of a 64x64 image in 64-token tiles, window 3x3, head dimension 64 255 -> 113, 128 1060 -> 202; 10x30x56 in
+// 96-token tiles, window 3x3x3, ten slices, 128 5510 -> 858, 64 1192 -> 529; 9x40x40 in 192-token tiles, four heads of 128
+// 4550 -> 843.
 // A lane holds key column c16 of its wave's two 16-key blocks and the query rows 4*g4 .. 4*g4+3 of a result.
 // ---------------------------------------------------------------------------------------------------------
-template <int D, int NPAIR>
-__global__ __launch_bounds__(NPAIR * 128, (D == 64 && NPAIR == 4) ? 2 : 1) void sta_bwd_dkv_kernel(const bf16_raw *__restrict__ q,
-                                                                     const bf16_raw *__restrict__ k,
-                                                                     const bf16_raw *__restrict__ v,
-                                                                     const bf16_raw *__restrict__ d_o,
-                                                                     const float *__restrict__ neg_lse,
-                                                                     const float *__restrict__ neg_delta,
-                                                                     bf16_raw *__restrict__ d_k,
-                                                                     bf16_raw *__restrict__ d_v, sta::FwdParams p,
-                                                                     sta::WindowTable win, uint32_t n_bh, uint32_t chunk)
+template <int D, int NPAIR, int G>
+__global__ __attribute__((amdgpu_flat_work_group_size(NPAIR * G * 128, NPAIR * G * 128), amdgpu_waves_per_eu(D == 64 ? 4 : NPAIR == 1 ? 2 : 3)))
+void sta_bwd_dkv_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restrict__ k, const bf16_raw *__restrict__ v,
+                        const bf16_raw *__restrict__ d_o, const float *__restrict__ neg_lse,
+                        const float *__restrict__ neg_delta, bf16_raw *__restrict__ d_k, bf16_raw *__restrict__ d_v,
+                        sta::FwdParams p, BwdPlan plan)
 {
     using L = Staged<D>;
     constexpr int KS = L::KS, CB = L::CB;
     constexpr int COLS = NPAIR * 32;                    // keys per workgroup
+    constexpr int WAVES = 2 * NPAIR;                    // per walk group
     constexpr int STAGE_B = 2 * L::Tile;
     constexpr int Q_TILE = 0, G_TILE = L::Tile;
-    constexpr int P_XCHG = 2 * STAGE_B;                 // per pair: 2 key blocks x 64 lanes x 16 B
-    constexpr int STATS = P_XCHG + NPAIR * 2048;        // per stage: -lse / scale then -delta of the 32 staged query rows
+    constexpr bool P_F32 = NPAIR <= 3;                  // P handed over in fp32
+    constexpr int P_XCHG = 2 * STAGE_B;                 // per pair: planes of 64 lanes x 16 B, one per key block (bf16)
+    constexpr int PAIR_B = P_F32 ? 4096 : 2048;         // or per key and query block (fp32)
+    constexpr int STATS = P_XCHG + NPAIR * PAIR_B;      // per stage: -lse / scale then -delta of the 32 staged query rows
     constexpr int STAT_B = 2 * kSub * 4;
-    constexpr int DMA_WAVES = 8;                        // waves that bring the operands in
-    constexpr int STAT_WAVE = 2 * NPAIR > DMA_WAVES ? DMA_WAVES : DMA_WAVES - 1;   // a wave of its own where there is one
-    static_assert(2 * NPAIR >= DMA_WAVES, "eight loading waves");
-    __shared__ __attribute__((aligned(1024))) char smem[STATS + 2 * STAT_B];
+    constexpr int GROUP_B = STATS + 2 * STAT_B;         // LDS of one walk group
+    constexpr int OPS = 2 * L::Groups + 1;              // DMA instructions per sub-block: Q, dO, the row statistics
+    constexpr int WAVE_OPS = (OPS + WAVES - 1) / WAVES; // at most this many per wave
+    constexpr int WAVE_OUT = 16 * L::RowB;
+    constexpr int SMEM = max_of(G * GROUP_B, max_of((G / 2) * WAVES * CB * 2 * 1024, WAVES * WAVE_OUT));
+    __shared__ __attribute__((aligned(1024))) char smem[SMEM];
 
-    uint32_t kblock, bh_rank;
-    if (!work_item(chunk, p.N / COLS, n_bh, &kblock, &bh_rank)) return;
-    const uint32_t heads = p.heads;
-    const uint32_t h_local = bh_rank % heads, b = bh_rank / heads;
-    const size_t bh = (size_t)b * p.H + p.head_base + h_local;
-    const uint32_t k_tile = (kblock * COLS) / p.P;
-    const StaBox box = sta_query_tile_box_of(p.n_t, p.n_h, p.n_w, win.w[h_local][0], win.w[h_local][1],
-                                             win.w[h_local][2], k_tile);
+    const BwdItem item = bwd_item_of<false>(blockIdx.x, p, plan);
+    if (!item.valid) return;
+    const size_t bh = item.bh;
     const int tid = threadIdx.x;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int group = wave_all / WAVES, wave = wave_all % WAVES;
     const int lane = tid & 63, c16 = lane & 15, g4 = lane >> 4;
     const bool probs_role = wave < NPAIR;               // S, P, dV; the other role: dP, dS, dK
     const int pair = probs_role ? wave : wave - NPAIR;
 
     const size_t head_row = bh * p.N;
-    const size_t my_row = head_row + (size_t)kblock * COLS + (size_t)pair * 32;
+    const size_t my_row = head_row + (size_t)item.block * COLS + (size_t)pair * 32;
     const char *qh = reinterpret_cast<const char *>(q + head_row * D);
     const char *gh = reinterpret_cast<const char *>(d_o + head_row * D);
 
-    // DMA: each operand is L::Groups instructions of 1 KB.  Head dimension 128 (8 per operand): wave w < 8 issues
-    // instruction w of each operand; head dimension 64 (4 per operand): waves 0..3 bring Q, waves 4..7 dO.  Wave 8
-    // brings the row statistics of the sub-block (32 + 32 floats) with one 4-byte-per-lane instruction (wave 7 where
-    // there are eight).
+    WalkShare<G> share;
+    share.start(item.box, p, plan, group);
+
+    // DMA: each operand is L::Groups instructions of 1 KB, and the row statistics of the sub-block (32 + 32 floats) one of
+    // 4 bytes per lane; wave w of the group issues the instructions w, w + WAVES, ..
     const uint32_t src_lane_off = L::dma_lane_offset(lane);
     const uint32_t stat_lane_off = (uint32_t)((lane & (kSub - 1)) * 4);
     const char *stat_base = reinterpret_cast<const char *>((lane < kSub ? neg_lse : neg_delta) + head_row);
-    auto issue_loads = [&](int stage, uint32_t first_row) {
+    char *group_lds = smem + group * GROUP_B;
+    int issued = 0;
+    auto issue_next = [&]() __attribute__((always_inline)) {
+        if (issued >= share.n_units) return;
         uint32_t off = src_lane_off, soff = stat_lane_off;
         asm volatile("" : "+v"(off), "+v"(soff));       // keep the lane offsets 32-bit next to a scalar base
-        if (wave < DMA_WAVES) {
-            const int group = D == 128 ? wave : (wave & 3);
-            const size_t base = (size_t)(first_row + L::GroupRows * group) * L::RowB;
-            char *dst = smem + stage * STAGE_B + group * L::Group;
-            if (D == 128 || wave < 4)
-                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(qh + base + off),
-                                                 STA_LDS_PTR(dst + Q_TILE), 16, 0, 0);
-            if (D == 128 || wave >= 4)
-                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(gh + base + off),
-                                                 STA_LDS_PTR(dst + G_TILE), 16, 0, 0);
+        const uint32_t first_row = share.walk.next_row;
+        share.walk.advance();
+        const int stage = issued & 1;
+#pragma unroll
+        for (int i = 0; i < WAVE_OPS; ++i) {
+            const int j = wave + i * WAVES;
+            if (j < OPS - 1) {
+                const bool is_g = j >= L::Groups;
+                const int part = j % L::Groups;
+                const char *src = (is_g ? gh : qh) + (size_t)(first_row + L::GroupRows * part) * L::RowB;
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + off),
+                                                 STA_LDS_PTR(group_lds + stage * STAGE_B + (is_g ? G_TILE : Q_TILE) + part * L::Group),
+                                                 16, 0, 0);
+            } else if (j == OPS - 1) {
+                __builtin_amdgcn_global_load_lds(
+                    (const __attribute__((address_space(1))) void *)(stat_base + (size_t)first_row * 4 + soff),
+                    STA_LDS_PTR(group_lds + STATS + stage * STAT_B), 4, 0, 0);
+            }
         }
-        if (wave == STAT_WAVE)
-            __builtin_amdgcn_global_load_lds(
-                (const __attribute__((address_space(1))) void *)(stat_base + (size_t)first_row * 4 + soff),
-                STA_LDS_PTR(smem + STATS + stage * STAT_B), 4, 0, 0);
+        ++issued;
     };
+    issue_next();
 
-    const uint32_t smem_addr = (uint32_t)(uintptr_t)smem;
+    const uint32_t group_addr = (uint32_t)(uintptr_t)smem + (uint32_t)(group * GROUP_B);
     uint32_t row_addr[KS], tr_addr[4];
-    L::addresses(smem_addr, lane, row_addr, tr_addr);
-    const uint32_t xchg_addr = smem_addr + P_XCHG + pair * 2048 + lane * 16;   // two planes of 1 KB per pair
-    const uint32_t stat_addr = smem_addr + STATS + (probs_role ? 0 : kSub * 4) + 16 * g4;
+    L::addresses(group_addr, lane, row_addr, tr_addr);
+    const uint32_t xchg_addr = group_addr + P_XCHG + pair * PAIR_B + lane * 16;
+    const uint32_t stat_addr = group_addr + STATS + (probs_role ? 0 : kSub * 4) + 16 * g4;
 
     // resident B fragments: K rows (first role) or V rows (second role) of key 16*kb + c16, channels 32*ks + 8*g4 ..
     bf16x8 resident[2][KS];
@@ -346,28 +454,19 @@ __global__ __launch_bounds__(NPAIR * 128, (D == 64 && NPAIR == 4) ? 2 : 1) void 
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb) acc[cb][kb] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-    BoxWalk walk;
-    walk.start(box, p.n_h, p.n_w, p.P);
-    const int n_iter = box.count() * walk.sub_per_tile;
-    int issued = 0;
-    auto issue_next = [&]() {
-        if (issued < n_iter) {
-            issue_loads(issued & 1, walk.next_row);
-            walk.advance();
-            ++issued;
-        }
-    };
-    issue_next();
-
     // One sub-block in one role.  (The role is a compile-time argument and each role has its own loop: with the
     // branch inside a common loop the register allocator serves both paths at once and spills.)
-    auto sub_block = [&](auto role_c, auto stage_c) {
+    auto sub_block = [&](auto role_c, auto stage_c, int unit) __attribute__((always_inline)) {
         constexpr bool PROBS = decltype(role_c)::value;
         constexpr int ST = decltype(stage_c)::value * STAGE_B;
         constexpr int ST_STATS = decltype(stage_c)::value * STAT_B;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();       // the stage is complete; the other stage and the exchange buffer are free
         issue_next();
+        if (G > 1 && unit >= share.n_units) {
+            __builtin_amdgcn_s_barrier();               // the one at the hand-over below
+            return;
+        }
         // the accumulators of the first product start at the statistics of their query rows 16*qb + 4*g4 ..
         floatx4 init[2];
         {
@@ -389,16 +488,28 @@ __global__ __launch_bounds__(NPAIR * 128, (D == 64 && NPAIR == 4) ? 2 : 1) void 
             StagedTransposedProduct<D, ST + G_TILE> g_t;
             g_t.prefetch(tr_addr);
             __builtin_amdgcn_sched_barrier(0);
+            floatx4 P[2][2];                            // [query block][key block]
             bf16x8 Pb[2];
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
                 for (int qb = 0; qb < 2; ++qb)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        Pb[kb][4 * qb + e] = static_cast<__bf16>(__builtin_amdgcn_exp2f(X[qb][kb][e] * c));
-            lds_write_b128(xchg_addr, Pb[0]);
-            lds_write_b128(xchg_addr + 1024, Pb[1]);
+                    for (int e = 0; e < 4; ++e) {
+                        P[qb][kb][e] = __builtin_amdgcn_exp2f(X[qb][kb][e] * c);
+                        Pb[kb][4 * qb + e] = static_cast<__bf16>(P[qb][kb][e]);
+                    }
+            if constexpr (P_F32) {
+                // plain stores: the compiler gives them the wait states that exponentials and matrix results need
+                floatx4 *out = reinterpret_cast<floatx4 *>(group_lds + P_XCHG + pair * PAIR_B + lane * 16);
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                    for (int qb = 0; qb < 2; ++qb) out[64 * (2 * kb + qb)] = P[qb][kb];
+            } else {
+                lds_write_b128(xchg_addr, Pb[0]);
+                lds_write_b128(xchg_addr + 1024, Pb[1]);
+            }
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             __builtin_amdgcn_s_barrier();
             g_t.run(tr_addr, Pb, acc);                                              // dV^T += dO^T P
@@ -407,311 +518,171 @@ __global__ __launch_bounds__(NPAIR * 128, (D == 64 && NPAIR == 4) ? 2 : 1) void 
             StagedTransposedProduct<D, ST + Q_TILE> q_t;
             q_t.prefetch(tr_addr);
             __builtin_amdgcn_s_barrier();
-            bf16x8 Pb[2];
-            Pb[0] = ds_read_b128_at<0>(xchg_addr);
-            Pb[1] = ds_read_b128_at<1024>(xchg_addr);
-            lds_wait2<0>(Pb[0], Pb[1]);
             bf16x8 dSb[2];
+            if constexpr (P_F32) {
+                bf16x8 raw[4];                          // key block 0: query blocks 0, 1; key block 1
+                raw[0] = ds_read_b128_at<0>(xchg_addr);
+                raw[1] = ds_read_b128_at<1024>(xchg_addr);
+                raw[2] = ds_read_b128_at<2048>(xchg_addr);
+                raw[3] = ds_read_b128_at<3072>(xchg_addr);
+                lds_wait2<2>(raw[0], raw[1]);
+                lds_wait2<0>(raw[2], raw[3]);
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
+                for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-                for (int qb = 0; qb < 2; ++qb)
+                    for (int qb = 0; qb < 2; ++qb) {
+                        const floatx4 P = __builtin_bit_cast(floatx4, raw[2 * kb + qb]);
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        dSb[kb][4 * qb + e] = static_cast<__bf16>(static_cast<float>(Pb[kb][4 * qb + e]) * X[qb][kb][e]);
+                        for (int e = 0; e < 4; ++e) dSb[kb][4 * qb + e] = static_cast<__bf16>(P[e] * X[qb][kb][e]);
+                    }
+            } else {
+                bf16x8 Pb[2];
+                Pb[0] = ds_read_b128_at<0>(xchg_addr);
+                Pb[1] = ds_read_b128_at<1024>(xchg_addr);
+                lds_wait2<0>(Pb[0], Pb[1]);
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                    for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            dSb[kb][4 * qb + e] = static_cast<__bf16>(static_cast<float>(Pb[kb][4 * qb + e]) * X[qb][kb][e]);
+            }
             q_t.run(tr_addr, dSb, acc);                                             // dK^T += Q^T dS
         }
     };
-    auto all_sub_blocks = [&](auto role_c) {
-        for (int iter = 0; iter < n_iter; iter += 2) {
-            sub_block(role_c, std::integral_constant<int, 0>{});
-            if (iter + 1 < n_iter) sub_block(role_c, std::integral_constant<int, 1>{});
+    auto all_sub_blocks = [&](auto role_c) __attribute__((always_inline)) {
+        for (int u = 0; u < share.n_steps; u += 2) {
+            sub_block(role_c, std::integral_constant<int, 0>{}, u);
+            if (u + 1 < share.n_steps) sub_block(role_c, std::integral_constant<int, 1>{}, u + 1);
         }
     };
     if (probs_role) all_sub_blocks(std::true_type{});
     else all_sub_blocks(std::false_type{});
-    // acc[cb][kb][i] = channel 16*cb + 4*g4 + i of key 16*kb + c16
-    bf16_raw *dst = (probs_role ? d_v : d_k) + my_row * D;
-    const float mul = probs_role ? 1.0f : c * kLn2;
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int cb = 0; cb < CB; ++cb) {
-            bf16x4 ov;
-#pragma unroll
-            for (int t = 0; t < 4; ++t) ov[t] = static_cast<__bf16>(acc[cb][kb][t] * mul);
-            *reinterpret_cast<bf16x4 *>(dst + (size_t)(16 * kb + c16) * D + 16 * cb + 4 * g4) = ov;
-        }
+    if constexpr (G > 1) {
+        merge_groups<G, WAVES>(smem, group, wave, lane, acc);
+        if (group != 0) return;
+    } else {
+        __syncthreads();                                // every wave has finished reading the stages
+    }
+    store_columns<D>(smem + wave * WAVE_OUT, acc, probs_role ? 1.0f : c * kLn2, (probs_role ? d_v : d_k) + my_row * D, lane);
 }
 
-
-// ---------------------------------------------------------------------------------------------------------
-// General shapes: head dimension 64 or 128, any tile size that is a multiple of 32 tokens.  Same mathematics and
-// the same MFMA formulation (one lane owns one column, P or dS goes from the accumulators into the B operand),
-// kept simple: one wave per workgroup and 32 columns, staged operands copied through registers into a
-// row-major LDS block without swizzle (the row reads take bank conflicts), one sub-block at a time.  The fast
-// kernels above take over where they apply.
-// ---------------------------------------------------------------------------------------------------------
-__device__ __forceinline__ void pack16(const float (&x)[16], bf16x8 (&out)[2])
-{
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) out[j][e] = static_cast<__bf16>(x[8 * j + e]);
-}
-
-template <int D>
-struct GenericOps {
-    static constexpr int RowB = 2 * D;             // bytes per token row
-    static constexpr int SubB = kSub * RowB;       // one staged operand
-    static constexpr int KS = D / 16;              // k-steps of a product over the channels
-    static constexpr int DB = D / 32;              // 32-channel blocks of an accumulator over the channels
-
-    // One wave copies a 32-row sub-block (contiguous in global memory) to LDS, 16 bytes per lane and step.
-    static __device__ __forceinline__ void copy_in(char *dst, const char *src, int lane)
-    {
-#pragma unroll
-        for (int i = 0; i < SubB / 1024; ++i)
-            *reinterpret_cast<uint4 *>(dst + i * 1024 + lane * 16) = *reinterpret_cast<const uint4 *>(src + i * 1024 + lane * 16);
-    }
-    // acc(32 x 32) = A B, A = staged sub-block read by rows (k = channels), B = resident fragments.
-    static __device__ __forceinline__ floatx16 rows_times(const char *sub, int lane, const bf16x8 (&resident)[KS])
-    {
-        const int lo = lane & 31, hb = lane >> 5;
-        floatx16 acc;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const bf16x8 a = *reinterpret_cast<const bf16x8 *>(sub + lo * RowB + (2 * ks + hb) * 16);
-            acc = mfma_32x32x16(a, resident[ks], acc);
-        }
-        return acc;
-    }
-    // acc[db](32 channels x 32 columns) += A B, A = staged sub-block read transposed (rows = channels, k = its 32
-    // tokens in accumulator order), B = the two packed halves of an accumulator.
-    static __device__ __forceinline__ void transposed_times(uint32_t sub_addr, int lane, const bf16x8 (&packed)[2],
-                                                            floatx16 (&acc)[DB])
-    {
-        typedef short shortx8 __attribute__((ext_vector_type(8)));
-        const int hb = lane >> 5, j4 = (lane & 15) >> 2, s4 = lane & 3, blk = (lane >> 4) & 1;
-        const uint32_t base = sub_addr + (uint32_t)((4 * hb + j4) * RowB + (16 * blk + 4 * s4) * 2);
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int db = 0; db < DB; ++db) {
-                shortx4 f0, f1;
-                const uint32_t a = base + (uint32_t)(16 * j * RowB + 64 * db);
-                asm volatile("ds_read_b64_tr_b16 %0, %2\n\tds_read_b64_tr_b16 %1, %2 offset:%3\n\ts_waitcnt lgkmcnt(0)"
-                             : "=&v"(f0), "=&v"(f1)
-                             : "v"(a), "n"(8 * RowB));
-                const shortx8 a01 = __builtin_shufflevector(f0, f1, 0, 1, 2, 3, 4, 5, 6, 7);
-                acc[db] = mfma_32x32x16(__builtin_bit_cast(bf16x8, a01), packed[j], acc[db]);
-            }
-    }
-    static __device__ __forceinline__ void load_resident(const bf16_raw *rows, int lane, bf16x8 (&frag)[KS])
-    {
-        const int lo = lane & 31, hb = lane >> 5;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) frag[ks] = *reinterpret_cast<const bf16x8 *>(rows + (size_t)lo * D + ks * 16 + hb * 8);
-    }
-    static __device__ __forceinline__ void store_columns(bf16_raw *dst, int lane, const floatx16 (&acc)[DB], float mul)
-    {
-        const int lo = lane & 31, hb = lane >> 5;
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                bf16x4 ov;
-#pragma unroll
-                for (int t = 0; t < 4; ++t) ov[t] = static_cast<__bf16>(acc[db][4 * g + t] * mul);
-                *reinterpret_cast<bf16x4 *>(dst + (size_t)lo * D + db * 32 + g * 8 + hb * 4) = ov;
-            }
-    }
+struct BwdArgs {
+    const bf16_raw *q, *k, *v, *o, *d_o;
+    const float *lse;
+    float *neg_delta, *neg_lse;
+    bf16_raw *d_q, *d_k, *d_v;
+    int B;
+    sta::FwdParams p;
+    const sta::WindowTable &win;
+    const sta::HeadOrder &order;
+    hipStream_t stream;
 };
 
-template <int D>
-__global__ __launch_bounds__(256) void sta_bwd_delta_generic_kernel(const uint4 *__restrict__ o,
-                                                                    const uint4 *__restrict__ d_o,
-                                                                    float *__restrict__ delta, size_t rows)
+// One chunk = the column blocks of one row of tiles along w.  Measured at the 30x48x80 grid (chunk sizes 1, 3,
+// 6, 30, 60, 120 in one session): dK/dV kernel 32.7, 31.5, 31.6, 31.0, 31.1, 34.0 ms; dQ kernel 18.9, 18.8, 18.7,
+// 18.5, 18.5, 19.3 ms.  Launches of fewer than eight such rows are cut evenly, so that every XCD gets its share.
+BwdPlan make_plan(const BwdArgs &a, uint32_t cols, uint32_t *ids)
 {
-    constexpr int LPR = D / 8;                     // lanes per row, 16 bytes each
-    const size_t row = (size_t)blockIdx.x * (256 / LPR) + threadIdx.x / LPR;
-    const int part = threadIdx.x % LPR;
-    float acc = 0.f;
-    if (row < rows) {
-        const uint4 a = o[row * LPR + part], b = d_o[row * LPR + part];
-        const uint32_t as[4] = {a.x, a.y, a.z, a.w}, bs[4] = {b.x, b.y, b.z, b.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            acc = fmaf(__uint_as_float(as[e] << 16), __uint_as_float(bs[e] << 16), acc);
-            acc = fmaf(__uint_as_float(as[e] & 0xffff0000u), __uint_as_float(bs[e] & 0xffff0000u), acc);
-        }
+    const sta::FwdParams &p = a.p;
+    BwdPlan plan;
+    const uint32_t per_head = p.N / cols, per_tile = p.P / cols;
+    plan.total = per_head * (uint32_t)a.B * p.heads;
+    uint32_t chunk = p.n_w * per_tile;
+    if (chunk > (plan.total + 7) / 8) chunk = (plan.total + 7) / 8;
+    plan.chunk = sta::fast_div_of(chunk);
+    plan.per_head = sta::fast_div_of(per_head);
+    plan.per_tile = sta::fast_div_of(per_tile);
+    plan.n_w = sta::fast_div_of(p.n_w);
+    plan.n_h = sta::fast_div_of(p.n_h);
+    plan.batch = sta::fast_div_of((uint32_t)a.B);
+    plan.sub_per_tile = sta::fast_div_of(p.P / kSub);
+    plan.inv_scale = kLog2e / p.scale_log2e;
+    for (uint32_t r = 0; r < p.heads; ++r) {
+        const uint16_t h = a.order.h[r];
+        plan.head[r].h = h;
+        for (int i = 0; i < 3; ++i) plan.head[r].w[i] = a.win.w[h][i];
     }
-#pragma unroll
-    for (int off = LPR / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off, LPR);
-    if (row < rows && part == 0) delta[row] = acc;
+    const uint32_t chunks = (plan.total + chunk - 1) / chunk;
+    *ids = 8 * chunk * ((chunks + 7) / 8);
+    return plan;
 }
 
-// dQ of 32 queries: grid (N / 32, batch x heads of the launch).
-template <int D>
-__global__ __launch_bounds__(64) void sta_bwd_dq_generic_kernel(const bf16_raw *__restrict__ q,
-                                                                const bf16_raw *__restrict__ k,
-                                                                const bf16_raw *__restrict__ v,
-                                                                const bf16_raw *__restrict__ d_o,
-                                                                const float *__restrict__ lse,
-                                                                const float *__restrict__ delta,
-                                                                bf16_raw *__restrict__ d_q, sta::FwdParams p,
-                                                                sta::WindowTable win)
+template <int D, int QW, int G>
+hipError_t launch_dq(const BwdArgs &a)
 {
-    using G = GenericOps<D>;
-    __shared__ __attribute__((aligned(1024))) char smem[2 * G::SubB];         // K, V
-    const uint32_t qblock = blockIdx.x, bh_rank = blockIdx.y;
-    const uint32_t h_local = bh_rank % p.heads, b = bh_rank / p.heads;
-    const size_t bh = (size_t)b * p.H + p.head_base + h_local;
-    const uint32_t q_tile = (qblock * kSub) / p.P;
-    const StaBox box = sta_key_tile_box_of(p.n_t, p.n_h, p.n_w, win.w[h_local][0], win.w[h_local][1], win.w[h_local][2],
-                                           q_tile);
-    const int lane = threadIdx.x, lo = lane & 31;
-    const size_t my_row = bh * p.N + (size_t)qblock * kSub;
-    const char *kh = reinterpret_cast<const char *>(k + bh * p.N * D);
-    const char *vh = reinterpret_cast<const char *>(v + bh * p.N * D);
-    const uint32_t smem_addr = (uint32_t)(uintptr_t)smem;
-
-    bf16x8 Qr[G::KS], Gr[G::KS];
-    G::load_resident(q + my_row * D, lane, Qr);
-    G::load_resident(d_o + my_row * D, lane, Gr);
-    const float c = p.scale_log2e;
-    const float lse2 = lse[my_row + lo] * kLog2e;
-    const float dl = delta[my_row + lo];
-    floatx16 dQ[G::DB];
-#pragma unroll
-    for (int db = 0; db < G::DB; ++db)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) dQ[db][r] = 0.f;
-
-    BoxWalk walk;
-    walk.start(box, p.n_h, p.n_w, p.P);
-    const int n_iter = box.count() * walk.sub_per_tile;
-    for (int iter = 0; iter < n_iter; ++iter) {
-        __syncthreads();                                   // the previous sub-block has been read
-        G::copy_in(smem, kh + (size_t)walk.next_row * G::RowB, lane);
-        G::copy_in(smem + G::SubB, vh + (size_t)walk.next_row * G::RowB, lane);
-        walk.advance();
-        __syncthreads();
-        const floatx16 S = G::rows_times(smem, lane, Qr);                      // S^T  = K Q^T (keys x queries)
-        const floatx16 dP = G::rows_times(smem + G::SubB, lane, Gr);           // dP^T = V dO^T
-        float ds[16];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) ds[r] = __builtin_amdgcn_exp2f(fmaf(S[r], c, -lse2)) * (dP[r] - dl);
-        bf16x8 dSb[2];
-        pack16(ds, dSb);
-        G::transposed_times(smem_addr, lane, dSb, dQ);                         // dQ^T += K^T dS^T
-    }
-    G::store_columns(d_q + my_row * D, lane, dQ, c * kLn2);
-}
-
-// dK and dV of 32 keys: grid (N / 32, batch x heads of the launch); walks the query tiles that keep the key tile.
-template <int D>
-__global__ __launch_bounds__(64) void sta_bwd_dkv_generic_kernel(const bf16_raw *__restrict__ q,
-                                                                 const bf16_raw *__restrict__ k,
-                                                                 const bf16_raw *__restrict__ v,
-                                                                 const bf16_raw *__restrict__ d_o,
-                                                                 const float *__restrict__ lse,
-                                                                 const float *__restrict__ delta,
-                                                                 bf16_raw *__restrict__ d_k,
-                                                                 bf16_raw *__restrict__ d_v, sta::FwdParams p,
-                                                                 sta::WindowTable win)
-{
-    using G = GenericOps<D>;
-    __shared__ __attribute__((aligned(1024))) char smem[2 * G::SubB];         // Q, dO
-    const uint32_t kblock = blockIdx.x, bh_rank = blockIdx.y;
-    const uint32_t h_local = bh_rank % p.heads, b = bh_rank / p.heads;
-    const size_t bh = (size_t)b * p.H + p.head_base + h_local;
-    const uint32_t k_tile = (kblock * kSub) / p.P;
-    const StaBox box = sta_query_tile_box_of(p.n_t, p.n_h, p.n_w, win.w[h_local][0], win.w[h_local][1],
-                                             win.w[h_local][2], k_tile);
-    const int lane = threadIdx.x, hb = lane >> 5;
-    const size_t head_row = bh * p.N;
-    const size_t my_row = head_row + (size_t)kblock * kSub;
-    const char *qh = reinterpret_cast<const char *>(q + head_row * D);
-    const char *gh = reinterpret_cast<const char *>(d_o + head_row * D);
-    const uint32_t smem_addr = (uint32_t)(uintptr_t)smem;
-
-    bf16x8 Kr[G::KS], Vr[G::KS];
-    G::load_resident(k + my_row * D, lane, Kr);
-    G::load_resident(v + my_row * D, lane, Vr);
-    const float c = p.scale_log2e;
-    floatx16 dK[G::DB], dV[G::DB];
-#pragma unroll
-    for (int db = 0; db < G::DB; ++db)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            dK[db][r] = 0.f;
-            dV[db][r] = 0.f;
-        }
-
-    BoxWalk walk;
-    walk.start(box, p.n_h, p.n_w, p.P);
-    const int n_iter = box.count() * walk.sub_per_tile;
-    for (int iter = 0; iter < n_iter; ++iter) {
-        __syncthreads();
-        const uint32_t first_row = walk.next_row;
-        G::copy_in(smem, qh + (size_t)first_row * G::RowB, lane);
-        G::copy_in(smem + G::SubB, gh + (size_t)first_row * G::RowB, lane);
-        walk.advance();
-        // statistics of the query rows this lane's accumulator registers belong to: rows 8*g + 4*hb + t
-        float ls[16], dl[16];
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const floatx4 a = *reinterpret_cast<const floatx4 *>(lse + head_row + first_row + 8 * g + 4 * hb);
-            const floatx4 d = *reinterpret_cast<const floatx4 *>(delta + head_row + first_row + 8 * g + 4 * hb);
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                ls[4 * g + t] = a[t] * kLog2e;
-                dl[4 * g + t] = d[t];
-            }
-        }
-        __syncthreads();
-        const floatx16 S = G::rows_times(smem, lane, Kr);                      // S  = Q K^T (queries x keys)
-        const floatx16 dP = G::rows_times(smem + G::SubB, lane, Vr);           // dP = dO V^T
-        float prob[16], ds[16];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            prob[r] = __builtin_amdgcn_exp2f(fmaf(S[r], c, -ls[r]));
-            ds[r] = prob[r] * (dP[r] - dl[r]);
-        }
-        bf16x8 Pb[2], dSb[2];
-        pack16(prob, Pb);
-        pack16(ds, dSb);
-        G::transposed_times(smem_addr + G::SubB, lane, Pb, dV);                // dV^T += dO^T P
-        G::transposed_times(smem_addr, lane, dSb, dK);                         // dK^T += Q^T dS
-    }
-    G::store_columns(d_v + my_row * D, lane, dV, 1.0f);
-    G::store_columns(d_k + my_row * D, lane, dK, c * kLn2);
-}
-
-template <int D>
-hipError_t launch_backward_generic(const bf16_raw *q, const bf16_raw *k, const bf16_raw *v, const void *o, const void *d_o,
-                                   const float *lse, float *delta, bool compute_delta, void *d_q, void *d_k, void *d_v,
-                                   int B, const sta::FwdParams &p, const sta::WindowTable &win, hipStream_t stream)
-{
-    if (compute_delta) {
-        const size_t rows = (size_t)B * p.H * p.N;   // all heads of the tensor at once
-        const unsigned per_block = 256 / (D / 8);
-        sta_bwd_delta_generic_kernel<D><<<dim3((unsigned)((rows + per_block - 1) / per_block)), dim3(256), 0, stream>>>(
-            static_cast<const uint4 *>(o), static_cast<const uint4 *>(d_o), delta, rows);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    const dim3 grid(p.N / kSub, (uint32_t)B * p.heads), block(64);
-    const bf16_raw *gg = static_cast<const bf16_raw *>(d_o);
-    sta_bwd_dq_generic_kernel<D><<<grid, block, 0, stream>>>(q, k, v, gg, lse, delta, static_cast<bf16_raw *>(d_q), p, win);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    sta_bwd_dkv_generic_kernel<D><<<grid, block, 0, stream>>>(q, k, v, gg, lse, delta, static_cast<bf16_raw *>(d_k),
-                                                              static_cast<bf16_raw *>(d_v), p, win);
+    uint32_t ids;
+    const BwdPlan plan = make_plan(a, QW * 32, &ids);
+    sta_bwd_dq_kernel<D, QW, G><<<dim3(ids), dim3(QW * G * 64), 0, a.stream>>>(a.q, a.k, a.v, a.o, a.d_o, a.lse, a.neg_delta, a.neg_lse,
+                                                                              a.d_q, a.p, plan);
     return hipGetLastError();
+}
+
+template <int D, int NPAIR, int G>
+hipError_t launch_dkv(const BwdArgs &a)
+{
+    uint32_t ids;
+    const BwdPlan plan = make_plan(a, NPAIR * 32, &ids);
+    sta_bwd_dkv_kernel<D, NPAIR, G><<<dim3(ids), dim3(NPAIR * G * 128), 0, a.stream>>>(a.q, a.k, a.v, a.d_o, a.neg_lse, a.neg_delta,
+                                                                                      a.d_k, a.d_v, a.p, plan);
+    return hipGetLastError();
+}
+
+// Sub-blocks of the longest ordinary walk of the launch (the head with the most key tiles comes first).
+uint32_t longest_walk(const BwdArgs &a)
+{
+    const sta::FwdParams &p = a.p;
+    uint32_t units = p.P / kSub;
+    const uint32_t n[3] = {p.n_t, p.n_h, p.n_w};
+    for (int i = 0; i < 3; ++i) {
+        const uint32_t kept = 2 * (a.win.w[a.order.h[0]][i] / 2u) + 1;
+        units *= kept < n[i] ? kept : n[i];
+    }
+    return units;
+}
+
+// Shapes of the two kernels.  Measured in us, kernel alone; "clip" is the 12x48x48 grid in 384-token tiles at window 1x3x3
+// (108 sub-blocks per walk), "image" the 64x64 grid in 64-token tiles at 3x3 (18), "full" 12x32x48 in 384-token tiles at the
+// whole grid (576), then the number of heads.
+//
+// dQ: waves of queries as many as the tile allows up to four, because a staged sub-block serves them all (four against two at
+// head dimension 128: clip x 12 695 against 772, full x 8 1613 against 1726).  Two walk groups where the launch then still fits
+// the chip (8 waves per CU at head dimension 128, 12 at 64); one against two at 128: clip x 1 (864 waves) 128, 121, full x 1
+// (576) 390, 308, image x 2 (256) 18.1, 15.0, image x 8 (1024) 24.5, 22.7, clip x 2 (1728) 141, 160; at 64: image x 8 (1024)
+// 16.8, 14.2, image x 16 (2048) 21.1, 23.4.  Four groups are never faster (clip x 1 138, image x 8 33).
+template <int D>
+hipError_t dispatch_dq(const BwdArgs &a)
+{
+    const uint64_t waves = (uint64_t)a.B * a.p.heads * (a.p.N / 32), fits = (uint64_t)sta::compute_units() * (D == 128 ? 8 : 12);
+    const uint32_t P = a.p.P;
+    const bool two = 2 * waves <= fits && longest_walk(a) >= 16;
+    if (P % 96 == 0 && P % 128 != 0) return two ? launch_dq<D, 3, 2>(a) : launch_dq<D, 3, 1>(a);
+    if (P % 64 != 0) return launch_dq<D, 1, 1>(a);
+    if (two) return launch_dq<D, 2, 2>(a);
+    return P % 128 == 0 ? launch_dq<D, 4, 1>(a) : launch_dq<D, 2, 1>(a);
+}
+
+// dK/dV: head dimension 128: six pairs (a CU's twelve waves in one workgroup) where the tile allows and the last round of
+// workgroups is not mostly empty, otherwise four or two pairs; two, four, six pairs: clip x 12 (6.75 rounds of six pairs) 1091,
+// 1120, 1039, full x 8 (3.0) 2269, 2455, 2121, clip x 6 (3.4) 571, 577, 570, clip x 4 (2.25) 430, 431, 448, full x 3 (1.1)
+// 1095, 1009, 1340, full x 1 (0.4) 580, 482, 651.  Three walk groups of two pairs where all of them fit the chip at once:
+// image x 2 (512 waves) 22 against 27; beyond that they lose (image x 8, 2048 waves, 44 against 36).
+// Head dimension 64: four pairs, two workgroups per CU (clip x 12 581, two pairs 610, six 676); two walk groups of two pairs
+// where they fit: image x 8 (2048 waves) 23.2 against 26.7, image x 16 (4096) 43 against 37.
+// 96-token tiles: two walk groups always.  A workgroup of three pairs is six waves, and the SIMDs they leave half full take no
+// second one (10x30x56, 10 slices, windows up to 5x5x3: 681 with one group, 540 with two; head dimension 64 386, 365).
+template <int D>
+hipError_t dispatch_dkv(const BwdArgs &a)
+{
+    const uint64_t cus = sta::compute_units(), slices = (uint64_t)a.B * a.p.heads, waves = 2 * slices * (a.p.N / 32);
+    const uint32_t P = a.p.P;
+    if (P % 64 != 0) return P % 96 == 0 ? launch_dkv<D, 3, 2>(a) : launch_dkv<D, 1, 1>(a);
+    constexpr int GROUPS = D == 128 ? 3 : 2;
+    if (GROUPS * waves <= cus * (D == 128 ? 12 : 16) && longest_walk(a) >= 16) return launch_dkv<D, 2, GROUPS>(a);
+    const uint64_t blocks = slices * (a.p.N / 192), rounds = (blocks + cus - 1) / cus;
+    if (D == 128 && P % 384 == 0 && 5 * blocks >= 4 * rounds * cus) return launch_dkv<128, 6, 1>(a);
+    return P % 128 == 0 ? launch_dkv<D, 4, 1>(a) : launch_dkv<D, 2, 1>(a);
 }
 
 }  // namespace
@@ -720,65 +691,18 @@ namespace sta {
 
 bool backward_supported(int P, int D) { return (D == 64 || D == 128) && P > 0 && P % kSub == 0; }
 
-// The three tuned kernels for head dimension D: tokens per tile a multiple of 128.
-template <int D>
-hipError_t launch_backward_staged(const bf16_raw *qq, const bf16_raw *kk, const bf16_raw *vv, const void *o, const bf16_raw *gg,
-                                  const float *lse, float *delta, bool compute_delta, void *d_q, void *d_k, void *d_v, int B,
-                                  const FwdParams &p, const WindowTable &win, hipStream_t stream)
-{
-    // the workspace holds two floats per row here: -delta, then -lse / scale
-    const size_t rows = (size_t)B * p.H * p.N;       // all heads of the tensor at once
-    float *neg_delta = delta, *neg_lse = delta + rows;
-    if (compute_delta) {
-        constexpr unsigned per_block = 256 / (D / 8);
-        sta_bwd_delta_kernel<D><<<dim3((unsigned)((rows + per_block - 1) / per_block)), dim3(256), 0, stream>>>(
-            static_cast<const uint4 *>(o), reinterpret_cast<const uint4 *>(gg), lse, kLog2e / p.scale_log2e, neg_delta,
-            neg_lse, rows);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    const uint32_t n_bh = (uint32_t)B * p.heads;
-    const uint32_t total = (p.N / kCols) * n_bh;
-    auto grid_for = [&](uint32_t chunk) { return dim3(8 * chunk * ((((total + chunk - 1) / chunk) + 7) / 8)); };
-    // One chunk = the column blocks of one row of tiles along w.  Measured at the 30x48x80 grid (chunk sizes 1, 3,
-    // 6, 30, 60, 120 in one session): dK/dV kernel 32.7, 31.5, 31.6, 31.0, 31.1, 34.0 ms; dQ kernel 18.9, 18.8, 18.7,
-    // 18.5, 18.5, 19.3 ms.
-    const uint32_t chunk = p.n_w * (p.P / kCols);
-    dim3 block(kNW * 64);
-    sta_bwd_dq_kernel<D><<<grid_for(chunk), block, 0, stream>>>(qq, kk, vv, gg, neg_lse, neg_delta, static_cast<bf16_raw *>(d_q), p,
-                                                               win, n_bh, chunk);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    // Head dimension 128: six pairs (192 keys per workgroup, three waves per SIMD) where the tile allows.  Head
-    // dimension 64 needs 106 registers, so two workgroups of four pairs share a CU (four waves per SIMD); measured on
-    // the 30x48x80 grid with 384-token tiles: 21.7 ms for the entry point against 24.9-25.1 ms with six pairs.
-    if (D == 128 && p.P % 192 == 0) {
-        // the chunk is again one row of tiles along w
-        const uint32_t total6 = (p.N / 192) * n_bh, chunk6 = p.n_w * (p.P / 192);
-        const dim3 grid6(8 * chunk6 * ((((total6 + chunk6 - 1) / chunk6) + 7) / 8));
-        sta_bwd_dkv_kernel<D, 6><<<grid6, dim3(768), 0, stream>>>(qq, kk, vv, gg, neg_lse, neg_delta, static_cast<bf16_raw *>(d_k),
-                                                                 static_cast<bf16_raw *>(d_v), p, win, n_bh, chunk6);
-    } else {
-        sta_bwd_dkv_kernel<D, 4><<<grid_for(chunk), dim3(512), 0, stream>>>(qq, kk, vv, gg, neg_lse, neg_delta,
-                                                                           static_cast<bf16_raw *>(d_k),
-                                                                           static_cast<bf16_raw *>(d_v), p, win, n_bh, chunk);
-    }
-    return hipGetLastError();
-}
-
 hipError_t launch_backward(const void *q, const void *k, const void *v, const void *o, const void *d_o, const float *lse,
-                           float *delta, bool compute_delta, void *d_q, void *d_k, void *d_v, int B, int D,
-                           const FwdParams &p, const WindowTable &win, hipStream_t stream)
+                           float *stats, size_t stat_rows, void *d_q, void *d_k, void *d_v, int B, int D, const FwdParams &p,
+                           const WindowTable &win, const HeadOrder &order, hipStream_t stream)
 {
     if (!backward_supported((int)p.P, D)) return hipErrorInvalidValue;
-    const bf16_raw *qq = static_cast<const bf16_raw *>(q), *kk = static_cast<const bf16_raw *>(k);
-    const bf16_raw *vv = static_cast<const bf16_raw *>(v), *gg = static_cast<const bf16_raw *>(d_o);
-    const bool staged = p.P % kCols == 0;
-    if (D == 64)
-        return staged ? launch_backward_staged<64>(qq, kk, vv, o, gg, lse, delta, compute_delta, d_q, d_k, d_v, B, p, win, stream)
-                      : launch_backward_generic<64>(qq, kk, vv, o, d_o, lse, delta, compute_delta, d_q, d_k, d_v, B, p, win, stream);
-    return staged ? launch_backward_staged<128>(qq, kk, vv, o, gg, lse, delta, compute_delta, d_q, d_k, d_v, B, p, win, stream)
-                  : launch_backward_generic<128>(qq, kk, vv, o, d_o, lse, delta, compute_delta, d_q, d_k, d_v, B, p, win, stream);
+    const BwdArgs a = {static_cast<const bf16_raw *>(q), static_cast<const bf16_raw *>(k), static_cast<const bf16_raw *>(v),
+                       static_cast<const bf16_raw *>(o), static_cast<const bf16_raw *>(d_o), lse, stats, stats + stat_rows,
+                       static_cast<bf16_raw *>(d_q), static_cast<bf16_raw *>(d_k), static_cast<bf16_raw *>(d_v), B, p, win, order,
+                       stream};
+    const hipError_t e = D == 64 ? dispatch_dq<64>(a) : dispatch_dq<128>(a);
+    if (e != hipSuccess) return e;
+    return D == 64 ? dispatch_dkv<64>(a) : dispatch_dkv<128>(a);
 }
 
 }  // namespace sta

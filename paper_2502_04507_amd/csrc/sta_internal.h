@@ -26,6 +26,8 @@ hipError_t launch_permute(const void *src, void *dst, bool src_f32, bool dst_f32
                           const PermuteParams &p, uint32_t blocks, hipStream_t stream);
 
 // ---- attention -------------------------------------------------------------
+uint32_t compute_units();           // of the device that is current at the first call
+
 constexpr int kMaxHeadsPerLaunch = 256;
 
 struct WindowTable {
@@ -101,10 +103,11 @@ constexpr uint32_t kMaxTokenWindowTile = 1024;         // tokens per tile the sl
 bool forward_supported(int P, int D);
 
 // ---- gradients ---------------------------------------------------------------
-// delta: float [B, H, N] scratch (dO_i . O_i per query row), filled by the call when compute_delta is set.
+// stats: float [2][stat_rows] scratch, stat_rows = B * H * N: minus dO_i . O_i and minus lse_i / scale of every query row
+// (filled by the call, for the heads of the launch).
 hipError_t launch_backward(const void *q, const void *k, const void *v, const void *o, const void *d_o, const float *lse,
-                           float *delta, bool compute_delta, void *d_q, void *d_k, void *d_v, int B, int D,
-                           const FwdParams &p, const WindowTable &win, hipStream_t stream);
+                           float *stats, size_t stat_rows, void *d_q, void *d_k, void *d_v, int B, int D, const FwdParams &p,
+                           const WindowTable &win, const HeadOrder &order, hipStream_t stream);
 bool backward_supported(int P, int D);
 
 // ---- reductions around the attention kernel ----------------------------------

@@ -6,8 +6,15 @@
 
 #include "sta_device_util.h"
 #include "sta_geometry.h"
+#include "sta_internal.h"
 
 namespace {
+
+__device__ __forceinline__ uint32_t fast_div(uint32_t n, const sta::FastDiv &f)
+{
+    const uint32_t q = __umulhi(n, f.magic);
+    return (((n - q) >> f.pre) + q) >> f.post;
+}
 
 constexpr int kSub = 32;               // tokens per staged sub-block
 

@@ -1,0 +1,38 @@
+"""GPU parity of the gradient kernels at the edges of their shapes: every number of waves per workgroup, one and more walk
+groups, shares of the walk that do not divide evenly or hold nothing."""
+import pytest
+
+import synth_inputs as syn
+from tests.test_gpu_backward import assert_grad_parity, gpu_backward, oracle_backward
+
+pytestmark = pytest.mark.gpu
+
+# (grid, tile, batch, heads, per-head windows repeated over the heads).  Walk groups need 16 sub-blocks of 32 tokens in the widest
+# head; the launches are small enough to fit the chip in groups except where many heads are asked for.
+SHAPES = [
+    ("p32", (1, 16, 48), (1, 4, 8), 1, 2, [(1, 3, 5), (1, 1, 1)]),
+    ("p64-one", (1, 40, 56), (1, 8, 8), 1, 2, [(1, 1, 7), (1, 1, 1)]),          # 14 and 2 sub-blocks: one group
+    ("p64-groups", (1, 40, 56), (1, 8, 8), 2, 2, [(1, 3, 3), (1, 2, 3)]),       # 18
+    ("p64-empty", (1, 40, 56), (1, 8, 8), 1, 2, [(1, 5, 7), (1, 1, 1)]),        # 70 and 2: a group without a sub-block
+    ("p96-one", (4, 18, 40), (2, 6, 8), 1, 2, [(1, 1, 5), (1, 1, 1)]),          # 15 and 3
+    ("p96-two", (4, 18, 40), (2, 6, 8), 1, 2, [(2, 3, 5), (1, 1, 1)]),          # 90 and 3
+    ("p128-one", (4, 24, 24), (2, 8, 8), 1, 2, [(1, 1, 3), (1, 1, 1)]),         # 12 and 4
+    ("p128-groups", (4, 24, 24), (2, 8, 8), 1, 2, [(2, 1, 3), (1, 3, 1)]),      # 24 and 12
+    ("p160", (5, 8, 12), (5, 8, 4), 1, 2, [(1, 1, 3), (1, 1, 1)]),
+    ("p192-six", (3, 8, 216), (3, 8, 8), 1, 8, [(1, 1, 1), (1, 1, 2)]),         # 216 blocks of 192 keys: six pairs
+    ("p384-groups", (6, 16, 24), (6, 8, 8), 1, 2, [(1, 2, 2), (1, 1, 1)]),      # 72 and 12
+]
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("name,grid,tile,B,H,windows", SHAPES, ids=[s[0] for s in SHAPES])
+def test_gradient_kernel_shapes_match_the_oracle(name, grid, tile, B, H, windows, D):
+    w = syn.custom("bwd-" + name, B, H, D, grid, tile, [windows[h % len(windows)] for h in range(H)], "bf16", seed=1212)
+    q, k, v = syn.make_qkv(w)
+    g = syn.make_dout(w)
+    (dq, dk, dv), _ = gpu_backward(w, q, k, v, g)
+    for b in range(B):
+        for h in range(min(H, 2)):
+            rq, rk, rv = oracle_backward(w, q, k, v, g, b, h)
+            for label, got, ref in (("dQ", dq, rq), ("dK", dk, rk), ("dV", dv, rv)):
+                assert_grad_parity(got[b, h].float().numpy(), ref, "%s D%d %s b%d h%d" % (name, D, label, b, h))
