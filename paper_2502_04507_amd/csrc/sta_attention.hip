@@ -448,12 +448,18 @@ __device__ __forceinline__ GroupItem group_item_of(uint32_t id, const sta::FwdPa
 // v_mfma_f32_32x32x16_bf16 that was here before, 6.69-6.83 ms with QW = 4 (1090 TFLOP/s; QW = 12: 7.5 ms, QW = 2: 7.3 ms,
 // 64 keys per barrier: 6.9-7.0 ms; row sums by v_dot2: 7.2 ms).  128 heads of a 64x64 image in 8x8 tiles, window 3x3:
 // 105-109 us before, 98-100 us.  Head dimension 128, 96-token tiles (10x30x56, 10 slices, windows 3x3x3 and 2x4x3): 2390 us
-// with the register-staged kernel that served it before, 254-262 us (1100 TFLOP/s).
+// with the register-staged kernel that served it before, 299 us.
+// FOLLOW: the offset is the running maximum in every unit.  Otherwise it is the maximum of an item's first unit, and the
+// largest probabilities of a row are rounded to bf16 like any other; at the running maximum the largest is exactly 1 and has
+// no rounding error.  Against 64 bits (2-norm of the outputs, 96-token tiles, window 3x3x3, N(0,1)): 2.32e-3 with the fixed
+// offset, 2.17e-3 following, 2.24e-3 with the register-staged kernel.  Following costs 15 %
+// (260 -> 299 us), so it is done on the tiles whose kernel has always done it: no multiple of 128 tokens at head dimension
+// 128, of 64 at 64.
 // A third LDS stage (DMA two units ahead, waited for by count behind a bare s_barrier, which __syncthreads() does not
 // allow: it waits for every outstanding DMA) changes nothing at four waves per SIMD and costs occupancy on small tiles:
 // 6.77 against 6.73 ms, 108 against 98 us.
 // ---------------------------------------------------------------------------
-template <int D, int QW, int KG, int WPE>
+template <int D, int QW, int KG, int WPE, bool FOLLOW>
 __global__ __attribute__((amdgpu_flat_work_group_size(QW * KG * 64, QW * KG * 64), amdgpu_waves_per_eu(WPE)))
 void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
                                                                          const bf16_raw *__restrict__ k,
@@ -601,27 +607,24 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
                         for (int r = 0; r < 4; ++r) S[kb][qb][r] -= m_run[qb];
                 }
             } else {
-                float mx = mq[0];
+                // a query block at a time: that halves the accumulators scaled where only one of them has grown
 #pragma unroll
-                for (int qb = 1; qb < NQ; ++qb) mx = fmaxf(mx, mq[qb]);
-                if (__builtin_expect(__builtin_amdgcn_ballot_w64(mx > grow_above) != 0, 0)) {
+                for (int qb = 0; qb < NQ; ++qb) {
+                    if (__builtin_amdgcn_ballot_w64(mq[qb] > grow_above) == 0) continue;
+                    const float row_max = quad_lane_max(mq[qb]);
+                    const float shift = row_max > grow_above ? row_max : 0.f;         // the same in the four lanes of a query
+                    const float alpha = __builtin_amdgcn_exp2f(-shift * c);
+                    m_run[qb] += shift;
 #pragma unroll
-                    for (int qb = 0; qb < NQ; ++qb) {
-                        const float row_max = quad_lane_max(mq[qb]);
-                        const float shift = row_max > grow_above ? row_max : 0.f;     // the same in the four lanes of a query
-                        const float alpha = __builtin_amdgcn_exp2f(-shift * c);
-                        m_run[qb] += shift;
+                    for (int r = 0; r < 4; ++r) Sinit[qb][r] = -m_run[qb];
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) Sinit[qb][r] = -m_run[qb];
+                    for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-                        for (int kb = 0; kb < 2; ++kb)
+                        for (int r = 0; r < 4; ++r) S[kb][qb][r] -= shift;
+                    l_acc[qb] *= alpha;
+                    const float alpha_settled = settled_after_transcendental(alpha);
 #pragma unroll
-                            for (int r = 0; r < 4; ++r) S[kb][qb][r] -= shift;
-                        l_acc[qb] *= alpha;
-                        const float alpha_settled = settled_after_transcendental(alpha);
-#pragma unroll
-                        for (int cb = 0; cb < CB; ++cb) scale_in_place(Oacc[cb][qb], alpha_settled);
-                    }
+                    for (int cb = 0; cb < CB; ++cb) scale_in_place(Oacc[cb][qb], alpha_settled);
                 }
             }
         }
@@ -656,7 +659,7 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
     // One pass over the group's units; the first has been requested.  CAREFUL: follow the maximum in every unit.
     auto run_pass = [&](auto careful_c) __attribute__((always_inline)) {
         constexpr int TRACK = decltype(careful_c)::value ? kFollow : kPlain;
-        const float bound = TRACK == kFollow ? __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(8.0f / c))) : 0.f;
+        const float bound = FOLLOW || TRACK != kFollow ? 0.f : __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(8.0f / c)));
         auto next_unit = [&]() __attribute__((always_inline)) {
             // this wave's DMA for the unit must have landed, and everyone's; the other stage is free again
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -677,7 +680,7 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
 #pragma unroll
         for (int qb = 0; qb < NQ; ++qb) l_tot[qb] = l_acc[qb][0];
     };
-    run_pass(std::false_type{});
+    run_pass(std::bool_constant<FOLLOW>{});
     row_sums();
     constexpr float kRedoAbove = 79228162514264337593543950336.f;      // 2^96
     uint32_t o_max = 0;
@@ -1385,7 +1388,7 @@ hipError_t launch_x32(const void *q, const void *k, const void *v, void *o, int 
     return hipGetLastError();
 }
 
-template <int D, int QW, int KG, int WPE>
+template <int D, int QW, int KG, int WPE, bool FOLLOW>
 hipError_t launch_group(const void *q, const void *k, const void *v, void *o, int B, const sta::FwdParams &p,
                         const sta::WindowTable &win, const sta::HeadOrder &order, hipStream_t stream)
 {
@@ -1407,10 +1410,19 @@ hipError_t launch_group(const void *q, const void *k, const void *v, void *o, in
         for (int a = 0; a < 3; ++a) plan.head[h].w[a] = win.w[order.h[h]][a];
     }
     const uint32_t ids = 8 * chunk * ((plan.total + 8 * chunk - 1) / (8 * chunk));
-    sta_fwd_group_kernel<D, QW, KG, WPE><<<dim3(ids), dim3(QW * KG * 64), 0, stream>>>(
+    sta_fwd_group_kernel<D, QW, KG, WPE, FOLLOW><<<dim3(ids), dim3(QW * KG * 64), 0, stream>>>(
         static_cast<const bf16_raw *>(q), static_cast<const bf16_raw *>(k), static_cast<const bf16_raw *>(v),
         static_cast<bf16_raw *>(o), p, plan);
     return hipGetLastError();
+}
+
+template <int D, int QW, int WPE, bool FOLLOW>
+hipError_t launch_group_count(int groups, const void *q, const void *k, const void *v, void *o, int B, const sta::FwdParams &p,
+                              const sta::WindowTable &win, const sta::HeadOrder &order, hipStream_t stream)
+{
+    if (groups == 4) return launch_group<D, QW, 4, WPE, FOLLOW>(q, k, v, o, B, p, win, order, stream);
+    if (groups == 2) return launch_group<D, QW, 2, WPE, FOLLOW>(q, k, v, o, B, p, win, order, stream);
+    return launch_group<D, QW, 1, WPE, FOLLOW>(q, k, v, o, B, p, win, order, stream);
 }
 
 // Shape of the key-group kernel for a launch.
@@ -1436,21 +1448,18 @@ hipError_t launch_groups(const void *q, const void *k, const void *v, void *o, i
     const uint64_t fits = (uint64_t)resident_workgroups(1) * (D == 64 ? 16 : 8);
     const int groups = 4 * waves <= fits && units >= 32 ? 4 : 2 * waves <= fits && units >= 16 ? 2 : 1;
     if (p.P % 96 == 0 && p.P % 128 != 0) {
-        if (groups == 4) return launch_group<D, 3, 4, 3>(q, k, v, o, B, p, win, order, stream);
-        if (groups == 2) return launch_group<D, 3, 2, 3>(q, k, v, o, B, p, win, order, stream);
-        return launch_group<D, 3, 1, 3>(q, k, v, o, B, p, win, order, stream);
+        if (D == 64 && p.P % 64 == 0) return launch_group_count<64, 3, 3, false>(groups, q, k, v, o, B, p, win, order, stream);
+        return launch_group_count<D, 3, 3, true>(groups, q, k, v, o, B, p, win, order, stream);
     }
     if (p.P % 64 == 0) {
-        constexpr int WPE = D == 64 ? 4 : 2;                // what registers and LDS allow
-        if (groups == 4) return launch_group<D, 2, 4, WPE>(q, k, v, o, B, p, win, order, stream);
-        if (groups == 2) return launch_group<D, 2, 2, WPE>(q, k, v, o, B, p, win, order, stream);
-        if (D == 64 && p.P % 128 == 0) return launch_group<64, 4, 1, 4>(q, k, v, o, B, p, win, order, stream);
-        return launch_group<D, 2, 1, WPE>(q, k, v, o, B, p, win, order, stream);
+        if (D == 128) return launch_group_count<128, 2, 2, true>(groups, q, k, v, o, B, p, win, order, stream);
+        if (groups == 1 && p.P % 128 == 0) return launch_group<64, 4, 1, 4, false>(q, k, v, o, B, p, win, order, stream);
+        return launch_group_count<64, 2, 4, false>(groups, q, k, v, o, B, p, win, order, stream);
     }
     // other multiples of 32 tokens: one wave of queries, whose LDS stages then limit a CU to four such workgroups at head
     // dimension 128, with or without key groups (525 waves: 59 us, two groups 74)
-    if (D == 64 && groups > 1) return launch_group<64, 1, 2, 2>(q, k, v, o, B, p, win, order, stream);
-    return launch_group<D, 1, 1, D == 64 ? 3 : 1>(q, k, v, o, B, p, win, order, stream);
+    if (D == 64 && groups > 1) return launch_group<64, 1, 2, 2, true>(q, k, v, o, B, p, win, order, stream);
+    return launch_group<D, 1, 1, D == 64 ? 3 : 1, true>(q, k, v, o, B, p, win, order, stream);
 }
 
 // Test hook: the key-tile list of every (head, query tile) from the same box function.
