@@ -1425,6 +1425,18 @@ hipError_t launch_group_count(int groups, const void *q, const void *k, const vo
     return launch_group<D, QW, 1, WPE, FOLLOW>(q, k, v, o, B, p, win, order, stream);
 }
 
+// Units (32 keys) of the longest walk of a launch: that of the head with the most key tiles.
+uint32_t longest_walk(const sta::FwdParams &p, const sta::WindowTable &win, const sta::HeadOrder &order)
+{
+    uint32_t units = p.P / kSub;
+    const uint32_t n[3] = {p.n_t, p.n_h, p.n_w};
+    for (int a = 0; a < 3; ++a) {
+        const uint32_t kept = 2 * (win.w[order.h[0]][a] / 2u) + 1;
+        units *= kept < n[a] ? kept : n[a];
+    }
+    return units;
+}
+
 // Shape of the key-group kernel for a launch.
 // Waves of queries: as many as the tile allows up to four (three for 96-token multiples), because a K/V unit brought into LDS
 // serves them all; five waves leave the four SIMDs uneven (tiles of 320 tokens: 585 us with five waves, 431 with two).
@@ -1438,13 +1450,7 @@ hipError_t launch_groups(const void *q, const void *k, const void *v, void *o, i
                          const sta::WindowTable &win, const sta::HeadOrder &order, hipStream_t stream)
 {
     const uint64_t waves = (uint64_t)B * p.heads * (p.N / 32);
-    const uint32_t first = order.h[0];                      // the head with the most key tiles
-    uint32_t units = p.P / kSub;
-    const uint32_t n[3] = {p.n_t, p.n_h, p.n_w};
-    for (int a = 0; a < 3; ++a) {
-        const uint32_t kept = 2 * (win.w[first][a] / 2u) + 1;
-        units *= kept < n[a] ? kept : n[a];
-    }
+    const uint32_t units = longest_walk(p, win, order);
     const uint64_t fits = (uint64_t)resident_workgroups(1) * (D == 64 ? 16 : 8);
     const int groups = 4 * waves <= fits && units >= 32 ? 4 : 2 * waves <= fits && units >= 16 ? 2 : 1;
     if (p.P % 96 == 0 && p.P % 128 != 0) {
@@ -1452,6 +1458,7 @@ hipError_t launch_groups(const void *q, const void *k, const void *v, void *o, i
         return launch_group_count<D, 3, 3, true>(groups, q, k, v, o, B, p, win, order, stream);
     }
     if (p.P % 64 == 0) {
+        if (D == 128 && p.P % 128 == 0) return launch_group_count<128, 2, 2, false>(groups, q, k, v, o, B, p, win, order, stream);
         if (D == 128) return launch_group_count<128, 2, 2, true>(groups, q, k, v, o, B, p, win, order, stream);
         if (groups == 1 && p.P % 128 == 0) return launch_group<64, 4, 1, 4, false>(q, k, v, o, B, p, win, order, stream);
         return launch_group_count<64, 2, 4, false>(groups, q, k, v, o, B, p, win, order, stream);
@@ -1537,12 +1544,27 @@ hipError_t launch_forward(const void *q, const void *k, const void *v, void *o, 
 {
     if (!forward_supported((int)p.P, D)) return hipErrorInvalidValue;
     if (D == 64) return launch_groups<64>(q, k, v, o, B, p, win, order, stream);
+    if (p.P % 128 != 0) return launch_groups<128>(q, k, v, o, B, p, win, order, stream);
+    // Tiles of 128 tokens' multiples.  Up to 1280 waves of 32 queries (the chip holds 2048 of the key-group kernel's at this
+    // head dimension) the key-group kernel: more and smaller workgroups, and key groups that need no workspace.  Where one is
+    // given, items cut into parts come close on long walks, and only launches of up to 256 waves or walks of up to 80 units
+    // change over.  Measured in us, 12-wave or 4-wave kernel without a workspace, with one, key groups; waves, units:
+    // 6x16x24 in 384-token tiles, one head (72, 72) 79, 37, 26; 12x48x48, one head (864, 108) 116, 68, 57; 2x40x40 in 128-token
+    // tiles, one head (100, 36) 27, 26, 17, twelve (1200, 36) 37, 54, 34; 16x8x40 in 128-token tiles, four heads (640, 120) 76,
+    // 64, 58, eight (1280, 120) 102, 104, 99; 12x32x40 in 256-token tiles, four heads (1920, 216) 255, 255, 280.
+    const uint64_t cus = compute_units(), slices = (uint64_t)B * p.heads, waves = slices * (p.N / 32);
+    if (waves <= 5 * cus && (split_ws == nullptr || waves <= cus || longest_walk(p, win, order) <= 80))
+        return launch_groups<128>(q, k, v, o, B, p, win, order, stream);
     // A tile of 384 tokens (the paper's 6x8x8) gets one 12-wave workgroup per query tile: every K/V sub-block
     // fetched from L2 then serves 384 queries instead of 128.  Measured at the 115,200-token layer, window
-    // 3x3x3: 12.8-13.1 ms against 13.6-13.7 ms for the 4-wave shape in the same session.
-    if (p.P % 384 == 0) return launch_x32<12, 32, 2, 1>(q, k, v, o, B, p, win, order, split_ws, split_ws_floats, stream);
-    if (p.P % 128 == 0) return launch_x32<4, 32, 2, 3>(q, k, v, o, B, p, win, order, split_ws, split_ws_floats, stream);
-    return launch_groups<128>(q, k, v, o, B, p, win, order, stream);
+    // 3x3x3: 12.8-13.1 ms against 13.6-13.7 ms for the 4-wave shape in the same session.  Not where the last round of such
+    // workgroups would be mostly empty and is not cut into parts (12x48x48, window 1x3x3, us, 12 waves against 4: two heads,
+    // 0.56 rounds, 117, 97; three, 0.84, 126, 141; four, 1.13, 244, 194 and with parts 180, 184; six, 1.69, 252, 276).
+    const uint64_t items = slices * (p.N / 384), rounds = (items + cus - 1) / cus;
+    const bool in_parts = split_ws != nullptr && 2 * (items % cus) <= cus;
+    if (p.P % 384 == 0 && (in_parts || 10 * items >= 7 * rounds * cus))
+        return launch_x32<12, 32, 2, 1>(q, k, v, o, B, p, win, order, split_ws, split_ws_floats, stream);
+    return launch_x32<4, 32, 2, 3>(q, k, v, o, B, p, win, order, split_ws, split_ws_floats, stream);
 }
 
 hipError_t launch_forward_general(const void *q, const void *k, const void *v, void *o, int B, int D, const FwdParams &p,

@@ -52,3 +52,28 @@ def test_key_groups_match_the_oracle(name, grid, tile, windows, D):
         gu.assert_parity(o[0, h].float().cpu().numpy(), ref_o[order], "%s D%d h%d" % (name, D, h))
         # bf16-rounded probabilities are summed: 2^-9 relative each, independent, so below 2^-9 = 2e-3 in the log
         assert np.abs(lse[0, h].cpu().numpy() - ref_lse[order]).max() <= 2e-3
+
+
+@pytest.mark.parametrize("grid,tile,heads", [((6, 16, 24), (6, 8, 8), 18), ((6, 16, 24), (6, 8, 8), 30), ((4, 16, 16), (2, 8, 8), 41)],
+                         ids=["p384-4-waves", "p384-12-waves", "p128-4-waves"])
+def test_launches_beyond_the_key_groups_redo_items_whose_scores_grow(grid, tile, heads):
+    """Head dimension 128 with more than 1280 waves of queries: 4- and 12-wave workgroups.  The scores grow along the walk by
+    far more than fp32 sums can take with the first offset, so items are done again.  Every other head holds the same data."""
+    w = syn.custom("outgrow-many", 1, 2, 128, grid, tile, [(1, 3, 3), (3, 3, 3)], "bf16", seed=84)
+    q, k, v = syn.make_qkv(w)
+    order = torch.from_numpy(orc.tile_order(w.grid, w.tile))
+    ramp = torch.empty(w.N)
+    ramp[order] = torch.linspace(0.02, 14.0, w.N)                       # along the tiled sequence
+    k = (k.float() * ramp[None, None, :, None]).to(torch.bfloat16)
+    q = (q.float() * 2.0).to(torch.bfloat16)
+    index = torch.arange(heads) % 2
+    qt, kt, vt = (x[:, index][:, :, order].contiguous().to(DEV) for x in (q, k, v))
+    o = torch.full_like(qt, float("nan"))
+    sta.sta_forward(qt, kt, vt, o, w.grid, w.tile, [w.window_tiles[h % 2] for h in range(heads)])
+    torch.cuda.synchronize()
+    for h in range(heads):
+        assert torch.equal(o[:, h].view(torch.int16), o[:, h % 2].view(torch.int16)), h
+    for h in range(2):
+        ref = orc.attention(q[0, h].float().numpy(), k[0, h].float().numpy(), v[0, h].float().numpy(), w.grid, w.tile,
+                            orc.window_tiles_to_tokens(w.window_tiles[h], w.tile))
+        gu.assert_parity(o[0, h].float().cpu().numpy(), ref[order.numpy()], "outgrow-many h%d" % h)
