@@ -43,9 +43,12 @@ constexpr float kLn2 = 0.6931471805599453f;
 struct BwdPlan {
     uint32_t total;            // column blocks
     sta::FastDiv chunk;        // consecutive blocks of one XCD
-    sta::FastDiv per_head;     // blocks of one (batch, head)
+    sta::FastDiv per_row;      // blocks of one row of tiles along w
+    sta::FastDiv rows;         // such rows of one (batch, head)
+    sta::FastDiv slices;       // (batch, head) pairs
     sta::FastDiv per_tile;     // blocks of one tile
-    sta::FastDiv n_w, n_h, batch;
+    sta::FastDiv n_h, batch;
+    uint32_t row_major;        // the same row of every (batch, head), then the next row; otherwise head after head
     sta::FastDiv sub_per_tile; // 32-token sub-blocks of a tile
     float inv_scale;           // 1 / softmax scale
     struct Head {
@@ -53,8 +56,18 @@ struct BwdPlan {
     } head[sta::kMaxHeadsPerLaunch];
 };
 
+// The i-th tile to visit along an axis of n tiles with window w.  At window 2 * half + 1 the tiles 2 * half and n - 1 - 2 * half
+// are kept by the most query tiles (3 * half + 1) and the border tiles by the fewest (half + 1): the order starts at the
+// former and ends with the border, so that the last items of a launch are short ones.
+__device__ __forceinline__ int visit_order(int n, int w, int i)
+{
+    const int first = 2 * (w >> 1);
+    if (first >= n - 1) return i;
+    return i + first < n ? i + first : n - 1 - i;
+}
+
 // Work item of a workgroup.  The hardware deals workgroup ids round-robin over the 8 XCDs (each with its own
-// L2).  The launch's column blocks, taken head after head, are cut into chunks of consecutive blocks and
+// L2).  The launch's column blocks, taken row of tiles after row of tiles, are cut into chunks of consecutive blocks and
 // the chunks are dealt to the XCDs in turn: the blocks resident on one XCD at a time are then neighbours that
 // share most of their windows, while all XCDs together still work on one region of one head.
 // QUERY_COLS: the columns are queries and the box holds the key tiles of their tile; otherwise the columns are keys and
@@ -65,6 +78,8 @@ struct BwdItem {
     size_t bh;
     StaBox box;
 };
+// (The order of the visits matters to the keys' boxes only, those of the queries are equally long; and it pays where rows of
+// all heads are visited together, head after head it costs locality: 12x48x48, twelve heads 1153 against 1058 us.)
 template <bool QUERY_COLS>
 __device__ __forceinline__ BwdItem bwd_item_of(uint32_t id, const sta::FwdParams &p, const BwdPlan &plan)
 {
@@ -74,23 +89,36 @@ __device__ __forceinline__ BwdItem bwd_item_of(uint32_t id, const sta::FwdParams
     const uint32_t linear = (chunk * 8 + xcd) * plan.chunk.d + (slot - chunk * plan.chunk.d);
     it.valid = linear < plan.total;
     if (!it.valid) return it;
-    const uint32_t rank = fast_div(linear, plan.per_head);
-    it.block = linear - rank * plan.per_head.d;
+    const uint32_t line = fast_div(linear, plan.per_row), pos = linear - line * plan.per_row.d;
+    uint32_t row, rank;
+    if (plan.row_major) {
+        row = fast_div(line, plan.slices);
+        rank = line - row * plan.slices.d;
+    } else {
+        rank = fast_div(line, plan.rows);
+        row = line - rank * plan.rows.d;
+    }
     const uint32_t head_rank = fast_div(rank, plan.batch);          // batch entries of one head are adjacent
     const BwdPlan::Head head = plan.head[head_rank];
     it.bh = (size_t)(rank - head_rank * plan.batch.d) * p.H + p.head_base + head.h;
-    const uint32_t tile = fast_div(it.block, plan.per_tile);
-    const uint32_t row = fast_div(tile, plan.n_w), w = tile - row * plan.n_w.d;
-    const uint32_t t = fast_div(row, plan.n_h), h = row - t * plan.n_h.d;
+    uint32_t w = fast_div(pos, plan.per_tile);
+    const uint32_t sub = pos - w * plan.per_tile.d;
+    uint32_t t = fast_div(row, plan.n_h), h = row - t * plan.n_h.d;
     if constexpr (QUERY_COLS) {
         it.box.t = sta_axis_range(p.n_t, head.w[0], t);
         it.box.h = sta_axis_range(p.n_h, head.w[1], h);
         it.box.w = sta_axis_range(p.n_w, head.w[2], w);
     } else {
+        if (plan.row_major) {
+            t = visit_order(p.n_t, head.w[0], t);
+            h = visit_order(p.n_h, head.w[1], h);
+            w = visit_order(p.n_w, head.w[2], w);
+        }
         it.box.t = sta_axis_query_range(p.n_t, head.w[0], t);
         it.box.h = sta_axis_query_range(p.n_h, head.w[1], h);
         it.box.w = sta_axis_query_range(p.n_w, head.w[2], w);
     }
+    it.block = ((t * p.n_h + h) * p.n_w + w) * plan.per_tile.d + sub;
     return it;
 }
 
@@ -580,21 +608,37 @@ struct BwdArgs {
     hipStream_t stream;
 };
 
+// Sub-blocks of the walk of a head away from the borders; heads by rank, the one with the most key tiles first.
+uint32_t walk_of_rank(const BwdArgs &a, uint32_t rank)
+{
+    const sta::FwdParams &p = a.p;
+    uint32_t units = p.P / kSub;
+    const uint32_t n[3] = {p.n_t, p.n_h, p.n_w};
+    for (int i = 0; i < 3; ++i) {
+        const uint32_t kept = 2 * (a.win.w[a.order.h[rank]][i] / 2u) + 1;
+        units *= kept < n[i] ? kept : n[i];
+    }
+    return units;
+}
+uint32_t longest_walk(const BwdArgs &a) { return walk_of_rank(a, 0); }
+
 // One chunk = the column blocks of one row of tiles along w.  Measured at the 30x48x80 grid (chunk sizes 1, 3,
 // 6, 30, 60, 120 in one session): dK/dV kernel 32.7, 31.5, 31.6, 31.0, 31.1, 34.0 ms; dQ kernel 18.9, 18.8, 18.7,
 // 18.5, 18.5, 19.3 ms.  Launches of fewer than eight such rows are cut evenly, so that every XCD gets its share.
-BwdPlan make_plan(const BwdArgs &a, uint32_t cols, uint32_t *ids)
+BwdPlan make_plan(const BwdArgs &a, uint32_t cols, bool row_major, uint32_t *ids)
 {
     const sta::FwdParams &p = a.p;
     BwdPlan plan;
-    const uint32_t per_head = p.N / cols, per_tile = p.P / cols;
-    plan.total = per_head * (uint32_t)a.B * p.heads;
+    const uint32_t per_tile = p.P / cols;
+    plan.total = (p.N / cols) * (uint32_t)a.B * p.heads;
     uint32_t chunk = p.n_w * per_tile;
+    plan.per_row = sta::fast_div_of(chunk);
+    plan.rows = sta::fast_div_of(p.n_t * p.n_h);
+    plan.slices = sta::fast_div_of((uint32_t)a.B * p.heads);
+    plan.row_major = row_major;
     if (chunk > (plan.total + 7) / 8) chunk = (plan.total + 7) / 8;
     plan.chunk = sta::fast_div_of(chunk);
-    plan.per_head = sta::fast_div_of(per_head);
     plan.per_tile = sta::fast_div_of(per_tile);
-    plan.n_w = sta::fast_div_of(p.n_w);
     plan.n_h = sta::fast_div_of(p.n_h);
     plan.batch = sta::fast_div_of((uint32_t)a.B);
     plan.sub_per_tile = sta::fast_div_of(p.P / kSub);
@@ -613,33 +657,27 @@ template <int D, int QW, int G>
 hipError_t launch_dq(const BwdArgs &a)
 {
     uint32_t ids;
-    const BwdPlan plan = make_plan(a, QW * 32, &ids);
+    const BwdPlan plan = make_plan(a, QW * 32, false, &ids);
     sta_bwd_dq_kernel<D, QW, G><<<dim3(ids), dim3(QW * G * 64), 0, a.stream>>>(a.q, a.k, a.v, a.o, a.d_o, a.lse, a.neg_delta, a.neg_lse,
                                                                               a.d_q, a.p, plan);
     return hipGetLastError();
 }
 
+// Row after row over all heads, unless their walks differ (a head of long walks must not have rows left at the end: 16x48x64
+// in 256-token tiles, 3x3x3 and 3x3x5 2046 us head after head, 2377 row after row; 30x48x80, windows from 1x3x3 to the whole
+// grid 17.5, 26.6 ms) or the workgroups are the six-pair
+// ones, which need the neighbouring rows in L2 (24 heads of the 30x48x80 grid 23.9, 24.8 ms).  Head after head against row after
+// row, us: four images, 64-token tiles, head dimension 64 79, 59, 128 139, 107; 10x30x56 in 96-token tiles 550, 472; 16x48x64 in
+// 256-token tiles, eight heads, 128 3059, 2598, 64 1609, 1241; 18x40x64 in 192-token tiles 3054, 2809.
 template <int D, int NPAIR, int G>
 hipError_t launch_dkv(const BwdArgs &a)
 {
     uint32_t ids;
-    const BwdPlan plan = make_plan(a, NPAIR * 32, &ids);
+    const bool row_major = NPAIR < 6 && walk_of_rank(a, 0) == walk_of_rank(a, a.p.heads - 1);
+    const BwdPlan plan = make_plan(a, NPAIR * 32, row_major, &ids);
     sta_bwd_dkv_kernel<D, NPAIR, G><<<dim3(ids), dim3(NPAIR * G * 128), 0, a.stream>>>(a.q, a.k, a.v, a.d_o, a.neg_lse, a.neg_delta,
                                                                                       a.d_k, a.d_v, a.p, plan);
     return hipGetLastError();
-}
-
-// Sub-blocks of the longest ordinary walk of the launch (the head with the most key tiles comes first).
-uint32_t longest_walk(const BwdArgs &a)
-{
-    const sta::FwdParams &p = a.p;
-    uint32_t units = p.P / kSub;
-    const uint32_t n[3] = {p.n_t, p.n_h, p.n_w};
-    for (int i = 0; i < 3; ++i) {
-        const uint32_t kept = 2 * (a.win.w[a.order.h[0]][i] / 2u) + 1;
-        units *= kept < n[i] ? kept : n[i];
-    }
-    return units;
 }
 
 // Shapes of the two kernels.  Measured in us, kernel alone; "clip" is the 12x48x48 grid in 384-token tiles at window 1x3x3

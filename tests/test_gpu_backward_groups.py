@@ -20,6 +20,10 @@ SHAPES = [
     ("p128-groups", (4, 24, 24), (2, 8, 8), 1, 2, [(2, 1, 3), (1, 3, 1)]),      # 24 and 12
     ("p160", (5, 8, 12), (5, 8, 4), 1, 2, [(1, 1, 3), (1, 1, 1)]),
     ("p192-six", (3, 8, 216), (3, 8, 8), 1, 8, [(1, 1, 1), (1, 1, 2)]),         # 216 blocks of 192 keys: six pairs
+    # equal windows: rows of tiles over all heads, the longest boxes first
+    ("rows-p64", (1, 72, 40), (1, 8, 8), 2, 3, [(1, 5, 3)]),
+    ("rows-p128", (10, 16, 40), (2, 8, 8), 1, 2, [(3, 1, 4)]),
+    ("rows-p96", (6, 30, 8), (2, 6, 8), 1, 2, [(1, 3, 1)]),
     ("p384-groups", (6, 16, 24), (6, 8, 8), 1, 2, [(1, 2, 2), (1, 1, 1)]),      # 72 and 12
 ]
 
