@@ -279,20 +279,20 @@ __device__ __forceinline__ void staged_rows_times_resident(const uint32_t (&row_
 
 // acc[cb][col] (16 channels x 16 resident columns) += A B: A = the staged operand at OFF read transposed (A rows =
 // channels, k = its 32 rows: index 8*g4 + i is row 4*g4 + i of the first 16 for i < 4, of the second 16 otherwise),
-// B = packed[col].  The reads of channel blocks 0..3 can go out before B exists.
-template <int D, int OFF>
+// B = packed[col].  The reads of the first group of channel blocks can go out before B exists.
+template <int D, int OFF, int AT_ONCE = 4>
 struct StagedTransposedProduct {
-    static constexpr int CB = D / 16;                   // channel blocks: read four at a time
-    static constexpr int NG = CB / 4;
-    shortx4 frag[NG][4][2];
+    static constexpr int CB = D / 16;                   // channel blocks: read AT_ONCE at a time
+    static constexpr int NG = CB / AT_ONCE;
+    shortx4 frag[NG][AT_ONCE][2];
     template <int G>
     __device__ __forceinline__ void issue(const uint32_t (&tr_addr)[4])
     {
-        static_for<0, 4>([&](auto i) {
-            constexpr int cb = 4 * G + decltype(i)::value;
+        static_for<0, AT_ONCE>([&](auto i) {
+            constexpr int cb = AT_ONCE * G + decltype(i)::value;
             constexpr int at = OFF + Staged<D>::tr_offset(cb);
-            frag[G][cb & 3][0] = ds_read_tr16<at>(tr_addr[Staged<D>::tr_index(cb)]);
-            frag[G][cb & 3][1] = ds_read_tr16<at + Staged<D>::Rows16>(tr_addr[Staged<D>::tr_index(cb)]);
+            frag[G][cb % AT_ONCE][0] = ds_read_tr16<at>(tr_addr[Staged<D>::tr_index(cb)]);
+            frag[G][cb % AT_ONCE][1] = ds_read_tr16<at + Staged<D>::Rows16>(tr_addr[Staged<D>::tr_index(cb)]);
         });
     }
     __device__ __forceinline__ void prefetch(const uint32_t (&tr_addr)[4]) { issue<0>(tr_addr); }
@@ -304,17 +304,17 @@ struct StagedTransposedProduct {
             constexpr int g = decltype(gi)::value;
             if constexpr (g + 1 < NG) {
                 issue<g + 1>(tr_addr);
-                pv_wait<8>(frag[g]);
+                pv_wait<2 * AT_ONCE>(frag[g]);
             } else {
                 pv_wait<0>(frag[g]);
             }
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
+            for (int i = 0; i < AT_ONCE; ++i) {
                 const shortx8 a = __builtin_shufflevector(frag[g][i][0], frag[g][i][1], 0, 1, 2, 3, 4, 5, 6, 7);
 #pragma unroll
                 for (int t = 0; t < NC; ++t) {
                     const int col = (i & 1) ? NC - 1 - t : t;
-                    acc[4 * g + i][col] = mfma_16x16x32(__builtin_bit_cast(bf16x8, a), packed[col], acc[4 * g + i][col]);
+                    acc[AT_ONCE * g + i][col] = mfma_16x16x32(__builtin_bit_cast(bf16x8, a), packed[col], acc[AT_ONCE * g + i][col]);
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
