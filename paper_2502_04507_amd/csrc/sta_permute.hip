@@ -26,21 +26,32 @@ __device__ __forceinline__ uint32_t pack2_bf16(float a, float b)
     return __builtin_bit_cast(uint32_t, v);
 }
 
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+
+// STREAM: a load that is not to stay in the caches.
+template <bool STREAM>
+__device__ __forceinline__ u32x4_t load16(const void *base, size_t chunk16)
+{
+    const u32x4_t *p = reinterpret_cast<const u32x4_t *>(base) + chunk16;
+    if constexpr (STREAM) return __builtin_nontemporal_load(p);
+    else return *p;
+}
+
 // Load 8 elements as raw bf16 bits (4 dwords) or as 8 floats.
-template <bool SRC_F32>
+template <bool SRC_F32, bool STREAM>
 __device__ __forceinline__ void load8(const void *base, size_t chunk, Chunk8bf16 &b, Chunk8f32 &f)
 {
     if constexpr (SRC_F32) {
-        f = reinterpret_cast<const Chunk8f32 *>(base)[chunk];
+        f.lo = __builtin_bit_cast(float4, load16<STREAM>(base, 2 * chunk));
+        f.hi = __builtin_bit_cast(float4, load16<STREAM>(base, 2 * chunk + 1));
     } else {
-        b = reinterpret_cast<const Chunk8bf16 *>(base)[chunk];
+        b = __builtin_bit_cast(Chunk8bf16, load16<STREAM>(base, chunk));
     }
 }
 
 // 16-byte store that does not leave a dirty line in L2.  The outputs are written once and read by a later kernel;
 // with ordinary stores the dirty lines are written back when the kernel ends, which at small sizes costs more than
 // the copy itself (measured: 4 MB tensor 17 -> 2.7 us per launch, 85 MB tensor 33 -> 25.6 us, 1.4 GB 261 -> 247 us).
-typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void store16_streaming(void *base, size_t chunk16, u32x4_t v)
 {
     __builtin_nontemporal_store(v, reinterpret_cast<u32x4_t *>(base) + chunk16);
@@ -87,7 +98,7 @@ constexpr int kUnroll = 4;
 static_assert(kPermuteThreads * kUnroll == (int)sta::kPermuteChunksPerBlock, "one pass per workgroup");
 
 // TO_TILED: src is raster, dst is tiled.  Otherwise the reverse.
-template <bool SRC_F32, bool DST_F32, bool TO_TILED>
+template <bool SRC_F32, bool DST_F32, bool TO_TILED, bool STREAM>
 __global__ __launch_bounds__(kPermuteThreads) void sta_permute_kernel(const void *__restrict__ src,
                                                                      void *__restrict__ dst,
                                                                      sta::PermuteParams p)
@@ -123,7 +134,7 @@ __global__ __launch_bounds__(kPermuteThreads) void sta_permute_kernel(const void
                 const uint32_t ih = seg - it * p.T_h;
                 const size_t raster = raster_tile + (size_t)it * row_stride_t + (size_t)ih * row_stride_h + off;
                 const size_t tiled = tiled_base + idx;
-                load8<SRC_F32>(src, TO_TILED ? raster : tiled, b[u], f[u]);
+                load8<SRC_F32, STREAM>(src, TO_TILED ? raster : tiled, b[u], f[u]);
                 dst_idx[u] = TO_TILED ? tiled : raster;
             }
         }
@@ -135,17 +146,22 @@ __global__ __launch_bounds__(kPermuteThreads) void sta_permute_kernel(const void
     }
 }
 
-template <bool TO_TILED>
+template <bool TO_TILED, bool STREAM>
 hipError_t launch(const void *src, void *dst, bool src_f32, bool dst_f32, const sta::PermuteParams &p,
                   uint32_t blocks, hipStream_t stream)
 {
     dim3 g(blocks), b(kPermuteThreads);
-    if (!src_f32 && !dst_f32) sta_permute_kernel<false, false, TO_TILED><<<g, b, 0, stream>>>(src, dst, p);
-    else if (src_f32 && !dst_f32) sta_permute_kernel<true, false, TO_TILED><<<g, b, 0, stream>>>(src, dst, p);
-    else if (!src_f32 && dst_f32) sta_permute_kernel<false, true, TO_TILED><<<g, b, 0, stream>>>(src, dst, p);
-    else sta_permute_kernel<true, true, TO_TILED><<<g, b, 0, stream>>>(src, dst, p);
+    if (!src_f32 && !dst_f32) sta_permute_kernel<false, false, TO_TILED, STREAM><<<g, b, 0, stream>>>(src, dst, p);
+    else if (src_f32 && !dst_f32) sta_permute_kernel<true, false, TO_TILED, STREAM><<<g, b, 0, stream>>>(src, dst, p);
+    else if (!src_f32 && dst_f32) sta_permute_kernel<false, true, TO_TILED, STREAM><<<g, b, 0, stream>>>(src, dst, p);
+    else sta_permute_kernel<true, true, TO_TILED, STREAM><<<g, b, 0, stream>>>(src, dst, p);
     return hipGetLastError();
 }
+
+// Sources larger than the 256 MB Infinity Cache are read with streaming loads: nothing of them can still be there, and what
+// they would displace is the other tensors.  us, ordinary against streaming: 708 MB 248, 231 (to tiles) and 251, 237 (from
+// tiles); 85 MB 30.1, 29.3; but 17 MB, which is found in the cache, 6.2, 7.6.
+constexpr size_t kStreamAbove = (size_t)256 << 20;
 
 }  // namespace
 
@@ -154,8 +170,12 @@ namespace sta {
 hipError_t launch_permute(const void *src, void *dst, bool src_f32, bool dst_f32, bool to_tiled,
                           const PermuteParams &p, uint32_t blocks, hipStream_t stream)
 {
-    return to_tiled ? launch<true>(src, dst, src_f32, dst_f32, p, blocks, stream)
-                    : launch<false>(src, dst, src_f32, dst_f32, p, blocks, stream);
+    const size_t bytes = (size_t)blocks / p.parts * p.chunks_per_tile * (src_f32 ? 32 : 16);
+    if (bytes > kStreamAbove)
+        return to_tiled ? launch<true, true>(src, dst, src_f32, dst_f32, p, blocks, stream)
+                        : launch<false, true>(src, dst, src_f32, dst_f32, p, blocks, stream);
+    return to_tiled ? launch<true, false>(src, dst, src_f32, dst_f32, p, blocks, stream)
+                    : launch<false, false>(src, dst, src_f32, dst_f32, p, blocks, stream);
 }
 
 }  // namespace sta
