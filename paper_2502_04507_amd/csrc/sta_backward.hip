@@ -407,8 +407,10 @@ void sta_bwd_dkv_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restri
     constexpr int STATS = P_XCHG + NPAIR * PAIR_B;      // per stage: -lse / scale then -delta of the 32 staged query rows
     constexpr int STAT_B = 2 * kSub * 4;
     constexpr int GROUP_B = STATS + 2 * STAT_B;         // LDS of one walk group
-    constexpr int OPS = 2 * L::Groups + 1;              // DMA instructions per sub-block: Q, dO, the row statistics
-    constexpr int WAVE_OPS = (OPS + WAVES - 1) / WAVES; // at most this many per wave
+    constexpr int OPS = 2 * L::Groups;                  // DMA instructions per sub-block: Q, dO
+    constexpr int LOADERS = WAVES > 8 ? 8 : WAVES;      // waves that issue them, at most WAVE_OPS each
+    constexpr int WAVE_OPS = (OPS + LOADERS - 1) / LOADERS;
+    constexpr int STAT_WAVE = WAVES > LOADERS ? LOADERS : WAVES - 1;       // brings the row statistics
     constexpr int WAVE_OUT = 16 * L::RowB;
     constexpr int SMEM = max_of(G * GROUP_B, max_of((G / 2) * WAVES * CB * 2 * 1024, WAVES * WAVE_OUT));
     __shared__ __attribute__((aligned(1024))) char smem[SMEM];
@@ -431,8 +433,9 @@ void sta_bwd_dkv_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restri
     WalkShare<G> share;
     share.start(item.box, p, plan, group);
 
-    // DMA: each operand is L::Groups instructions of 1 KB, and the row statistics of the sub-block (32 + 32 floats) one of
-    // 4 bytes per lane; wave w of the group issues the instructions w, w + WAVES, ..
+    // DMA: each operand is L::Groups instructions of 1 KB; wave w of the group issues the instructions w, w + LOADERS, ..
+    // The row statistics of the sub-block (32 + 32 floats) are one of 4 bytes per lane.  (Dealt to all twelve waves of six
+    // pairs, one or two each: 30x48x80, 24 heads, window 3x3x3 43.3 against 43.0 ms, 1x3x3 14.93, 14.82.)
     const uint32_t src_lane_off = L::dma_lane_offset(lane);
     const uint32_t stat_lane_off = (uint32_t)((lane & (kSub - 1)) * 4);
     const char *stat_base = reinterpret_cast<const char *>((lane < kSub ? neg_lse : neg_delta) + head_row);
@@ -447,20 +450,20 @@ void sta_bwd_dkv_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restri
         const int stage = issued & 1;
 #pragma unroll
         for (int i = 0; i < WAVE_OPS; ++i) {
-            const int j = wave + i * WAVES;
-            if (j < OPS - 1) {
+            const int j = wave + i * LOADERS;
+            if (wave < LOADERS && (OPS % LOADERS == 0 || j < OPS)) {
                 const bool is_g = j >= L::Groups;
                 const int part = j % L::Groups;
                 const char *src = (is_g ? gh : qh) + (size_t)(first_row + L::GroupRows * part) * L::RowB;
                 __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + off),
                                                  STA_LDS_PTR(group_lds + stage * STAGE_B + (is_g ? G_TILE : Q_TILE) + part * L::Group),
                                                  16, 0, 0);
-            } else if (j == OPS - 1) {
-                __builtin_amdgcn_global_load_lds(
-                    (const __attribute__((address_space(1))) void *)(stat_base + (size_t)first_row * 4 + soff),
-                    STA_LDS_PTR(group_lds + STATS + stage * STAT_B), 4, 0, 0);
             }
         }
+        if (wave == STAT_WAVE)
+            __builtin_amdgcn_global_load_lds(
+                (const __attribute__((address_space(1))) void *)(stat_base + (size_t)first_row * 4 + soff),
+                STA_LDS_PTR(group_lds + STATS + stage * STAT_B), 4, 0, 0);
         ++issued;
     };
     issue_next();
