@@ -383,8 +383,8 @@ void sta_bwd_dq_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restric
 // What bounds it: the matrix pipe is busy 55 % of the cycles at head dimension 128 (30x48x80 grid, 24 heads, window 3x3x3:
 // 23.6 ms, 1200 TFLOP/s), at 64 the LDS reads take as long as the matrix instructions.  Tiles that are no multiple of 128
 // tokens went through one wave per workgroup with register-staged operands before (both kernels, the statistics included, in
-// us): 32 heads of a 64x64 image in 64-token tiles, window 3x3, head dimension 64 255 -> 113, 128 1060 -> 202; 10x30x56 in
-// 96-token tiles, window 3x3x3, ten slices, 128 5510 -> 858, 64 1192 -> 529; 9x40x40 in 192-token tiles, four heads of 128
+// us): 32 heads of a 64x64 image in 64-token tiles, window 3x3, head dimension 64 255 -> 92, 128 1060 -> 163; 10x30x56 in
+// 96-token tiles, window 3x3x3, ten slices, 128 5500 -> 763, 64 1180 -> 473; 9x40x40 in 192-token tiles, four heads of 128
 // 4550 -> 843.
 // A lane holds key column c16 of its wave's two 16-key blocks and the query rows 4*g4 .. 4*g4+3 of a result.
 // ---------------------------------------------------------------------------------------------------------
