@@ -556,27 +556,29 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
     floatx4 Sinit[NQ];                                      // minus the exponent offset of the lane's queries
     float m_run[NQ];
     floatx4 l_acc[NQ];                                      // row sums (a product with ones: all registers hold the same)
-    auto reset = [&]() __attribute__((always_inline)) {
+    auto reset = [&](float m) __attribute__((always_inline)) {
 #pragma unroll
         for (int qb = 0; qb < NQ; ++qb) {
             Sinit[qb] = floatx4{0.f, 0.f, 0.f, 0.f};
             l_acc[qb] = floatx4{0.f, 0.f, 0.f, 0.f};
-            m_run[qb] = 0.f;
+            m_run[qb] = m;
 #pragma unroll
             for (int cb = 0; cb < CB; ++cb) Oacc[cb][qb] = floatx4{0.f, 0.f, 0.f, 0.f};
         }
     };
-    reset();
+    reset(0.f);
     const float c = p.scale_log2e;
     if constexpr (QW * KG == 12) {                          // static priorities against the age order, as in the kernel below
         if (wave >= 8) __builtin_amdgcn_s_setprio(2);
         else if (wave >= 4) __builtin_amdgcn_s_setprio(1);
     }
 
-    constexpr int kPlain = 0, kFollow = 1, kFirst = 2;
+    constexpr int kPlain = 0, kFollow = 1, kFirst = 2, kCareful = 3;
     // One unit of 32 keys whose K begins at LDS offset off (relative to the group's first stage).
     auto unit_at = [&](auto track_c, uint32_t off, float grow_above) __attribute__((always_inline)) {
-        constexpr int TRACK = decltype(track_c)::value;     // kFirst: set the offsets; kFollow: move them with the scores
+        // kFirst: set the offsets; kFollow: move them with the scores.  kCareful: the same on scores that do not start at
+        // minus the offset: they lose nothing to an old offset that was far below them (keys masked by a lowest value).
+        constexpr int TRACK = decltype(track_c)::value;
         uint32_t tr_at[4];
 #pragma unroll
         for (int m = 0; m < 4; ++m) tr_at[m] = tr_addr[m] + off;
@@ -584,7 +586,7 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-            for (int qb = 0; qb < NQ; ++qb) S[kb][qb] = Sinit[qb];
+            for (int qb = 0; qb < NQ; ++qb) S[kb][qb] = TRACK == kCareful ? floatx4{0.f, 0.f, 0.f, 0.f} : Sinit[qb];
         rows_times_resident<D, 0>(row_addr + off, Qr, S);   // K Q^T minus the offset
         if constexpr (TRACK != kPlain) {
             float mq[NQ];
@@ -598,13 +600,33 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
             if constexpr (TRACK == kFirst) {
 #pragma unroll
                 for (int qb = 0; qb < NQ; ++qb) {
-                    m_run[qb] = quad_lane_max(mq[qb]);
+                    const float row_max = quad_lane_max(mq[qb]);
+                    m_run[qb] = row_max == -INFINITY ? 0.f : row_max;
 #pragma unroll
                     for (int r = 0; r < 4; ++r) Sinit[qb][r] = -m_run[qb];
 #pragma unroll
                     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
                         for (int r = 0; r < 4; ++r) S[kb][qb][r] -= m_run[qb];
+                }
+            } else if constexpr (TRACK == kCareful) {
+#pragma unroll
+                for (int qb = 0; qb < NQ; ++qb) {
+                    const float row_max = quad_lane_max(mq[qb]);
+                    const bool grown = row_max > m_run[qb] + grow_above;
+                    if (__builtin_amdgcn_ballot_w64(grown) != 0) {
+                        const float alpha = grown ? __builtin_amdgcn_exp2f((m_run[qb] - row_max) * c) : 1.f;
+                        m_run[qb] = grown ? row_max : m_run[qb];
+                        l_acc[qb] *= alpha;
+                        const float alpha_settled = settled_after_transcendental(alpha);
+#pragma unroll
+                        for (int cb = 0; cb < CB; ++cb) scale_in_place(Oacc[cb][qb], alpha_settled);
+                    }
+                    const float offset = m_run[qb] == -INFINITY ? 0.f : m_run[qb];
+#pragma unroll
+                    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) S[kb][qb][r] -= offset;
                 }
             } else {
                 // a query block at a time: that halves the accumulators scaled where only one of them has grown
@@ -622,6 +644,9 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
 #pragma unroll
                         for (int r = 0; r < 4; ++r) S[kb][qb][r] -= shift;
                     l_acc[qb] *= alpha;
+                    // the old offset was so far below that the scores behind it are lost: an infinite row sum asks for the
+                    // careful pass (it stays infinite; row_sums reads register 0)
+                    l_acc[qb][0] = alpha == 0.f ? INFINITY : l_acc[qb][0];
                     const float alpha_settled = settled_after_transcendental(alpha);
 #pragma unroll
                     for (int cb = 0; cb < CB; ++cb) scale_in_place(Oacc[cb][qb], alpha_settled);
@@ -656,10 +681,12 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
         v_t.run(tr_at, Pb, Oacc);                           // O^T += V^T P^T
     };
 
-    // One pass over the group's units; the first has been requested.  CAREFUL: follow the maximum in every unit.
+    // One pass over the group's units; the first has been requested.  CAREFUL: every unit in the careful form, with the
+    // offset moved when a score exceeds it by more than 2^8 in the exponent (FOLLOW: by anything).
     auto run_pass = [&](auto careful_c) __attribute__((always_inline)) {
-        constexpr int TRACK = decltype(careful_c)::value ? kFollow : kPlain;
-        const float bound = FOLLOW || TRACK != kFollow ? 0.f : __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(8.0f / c)));
+        constexpr bool CAREFUL = decltype(careful_c)::value;
+        constexpr int REST = CAREFUL ? kCareful : FOLLOW ? kFollow : kPlain;
+        const float bound = FOLLOW || !CAREFUL ? 0.f : __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(8.0f / c)));
         auto next_unit = [&]() __attribute__((always_inline)) {
             // this wave's DMA for the unit must have landed, and everyone's; the other stage is free again
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -667,12 +694,14 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
             asm volatile("" ::: "memory");
             issue_next();
         };
-        next_unit();
-        if (KG == 1 || n_units > 0) unit_at(std::integral_constant<int, kFirst>{}, 0u, 0.f);
-#pragma unroll 1
-        for (int u = 1; u < n_steps; ++u) {
+        if constexpr (!CAREFUL) {
             next_unit();
-            if (KG == 1 || u < n_units) unit_at(std::integral_constant<int, TRACK>{}, (uint32_t)((u & 1) * UNIT_B), bound);
+            if (KG == 1 || n_units > 0) unit_at(std::integral_constant<int, kFirst>{}, 0u, 0.f);
+        }
+#pragma unroll 1
+        for (int u = CAREFUL ? 0 : 1; u < n_steps; ++u) {
+            next_unit();
+            if (KG == 1 || u < n_units) unit_at(std::integral_constant<int, REST>{}, (uint32_t)((u & 1) * UNIT_B), bound);
         }
     };
     float l_tot[NQ];
@@ -680,14 +709,16 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
 #pragma unroll
         for (int qb = 0; qb < NQ; ++qb) l_tot[qb] = l_acc[qb][0];
     };
-    run_pass(std::bool_constant<FOLLOW>{});
+    run_pass(std::false_type{});
     row_sums();
-    constexpr float kRedoAbove = 79228162514264337593543950336.f;      // 2^96
+    // Done again: row sums beyond 2^96 (infinite where an offset has jumped) and below 2^-64, which only a group has whose
+    // first keys all score minus infinity (its offset is 0 then).
+    constexpr float kRedoAbove = 79228162514264337593543950336.f, kRedoBelow = 5.42101086242752217e-20f;
     uint32_t o_max = 0;
     bool redo = false;
 #pragma unroll
     for (int qb = 0; qb < NQ; ++qb) {
-        redo = redo || !(l_tot[qb] < kRedoAbove);
+        redo = redo || !(l_tot[qb] < kRedoAbove) || ((KG == 1 || n_units > 0) && l_tot[qb] < kRedoBelow);
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
@@ -695,7 +726,7 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
     }
     // (the barrier inside also ends every wave's reads of the stages)
     if (__builtin_expect(__syncthreads_or(redo || o_max >= 0x7f800000u), 0)) {
-        reset();
+        reset(-INFINITY);
         walk.start(box, p.n_h, p.n_w, p.P);
         to_share();
         issued = 0;
@@ -707,10 +738,11 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
 
     // ---- merge of the key groups: the upper half of the remaining groups hands its accumulators, offsets and row sums
     // to the lower half through LDS until one is left, always in the same order
-    // (a group without units: an offset below every other, finite so that two such groups can be merged)
+    // (a group without units or with scores of minus infinity only: an offset below every other, finite so that two such
+    // groups can be merged)
     float m2[NQ];                                           // offsets in base-2 units
 #pragma unroll
-    for (int qb = 0; qb < NQ; ++qb) m2[qb] = (KG > 1 && n_units == 0) ? -3.0e38f : m_run[qb] * c;
+    for (int qb = 0; qb < NQ; ++qb) m2[qb] = (KG > 1 && n_units == 0) ? -3.0e38f : fmaxf(m_run[qb] * c, -3.0e38f);
     if constexpr (KG > 1) {
 #pragma unroll
         for (int n = KG; n > 1; n = (n + 1) / 2) {
