@@ -714,6 +714,8 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
     // Done again: row sums beyond 2^96 (infinite where an offset has jumped) and below 2^-64, which only a group has whose
     // first keys all score minus infinity (its offset is 0 then).
     constexpr float kRedoAbove = 79228162514264337593543950336.f, kRedoBelow = 5.42101086242752217e-20f;
+    // Accumulators that have left the range; those of key groups from 2^125 on, so that the sum of four stays in it.
+    constexpr uint32_t kRedoBits = KG == 1 ? 0x7f800000u : 0x7e000000u;
     uint32_t o_max = 0;
     bool redo = false;
 #pragma unroll
@@ -725,7 +727,7 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
             for (int r = 0; r < 4; ++r) o_max = max(o_max, __float_as_uint(Oacc[cb][qb][r]) & 0x7fffffffu);
     }
     // (the barrier inside also ends every wave's reads of the stages)
-    if (__builtin_expect(__syncthreads_or(redo || o_max >= 0x7f800000u), 0)) {
+    if (__builtin_expect(__syncthreads_or(redo || o_max >= kRedoBits), 0)) {
         reset(-INFINITY);
         walk.start(box, p.n_h, p.n_w, p.P);
         to_share();

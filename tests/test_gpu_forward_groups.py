@@ -77,3 +77,25 @@ def test_launches_beyond_the_key_groups_redo_items_whose_scores_grow(grid, tile,
         ref = orc.attention(q[0, h].float().numpy(), k[0, h].float().numpy(), v[0, h].float().numpy(), w.grid, w.tile,
                             orc.window_tiles_to_tokens(w.window_tiles[h], w.tile))
         gu.assert_parity(o[0, h].float().cpu().numpy(), ref[order.numpy()], "outgrow-many h%d" % h)
+
+
+@pytest.mark.parametrize("D,grid,tile,groups", [(64, (1, 32, 32), (1, 8, 8), 4), (64, (1, 16, 48), (1, 8, 8), 2),
+                                                (128, (2, 32, 32), (2, 8, 8), 4), (128, (2, 16, 24), (2, 8, 8), 2)])
+def test_merged_accumulators_of_key_groups_stay_in_range(D, grid, tile, groups):
+    """Every group's accumulators end just below 2^128 with the offset of its first keys, so their sum would not: the first 32
+    keys of every tile are zero and the others exceed them by 2^79 (row sums stay below 2^96), under V = 2^b everywhere."""
+    w = syn.custom("merge-range", 1, 1, D, grid, tile, [tuple(g // t for g, t in zip(grid, tile))], "bf16", seed=1)
+    unit_of_key = torch.arange(w.N) % w.P // 32
+    hot = (unit_of_key > 0).to(torch.float32) * (4.875 if D == 128 else 6.875)
+    # log2 of a score factor: raw score x 1/sqrt(D) x log2(e); keys that count per group; then b for a sum in [2^127, 2^128)
+    exponent = float(hot.max()) * D * D ** -0.5 * 1.4426950408889634 + np.log2((unit_of_key > 0).sum().item() / groups)
+    b = int(np.floor(127.97 - exponent))
+    assert 127 < exponent + b < 127.97
+    k = hot[None, None, :, None].expand(1, 1, w.N, D).to(torch.bfloat16).to(DEV)
+    q = torch.ones_like(k)
+    v = torch.full_like(k, 2.0 ** b)
+    o, lse = torch.empty_like(k), torch.empty((1, 1, w.N), dtype=torch.float32, device=DEV)
+    sta.sta_forward_lse(q, k.contiguous(), v, o, lse, w.grid, w.tile, w.window_tiles)
+    got = o.float().cpu() * 2.0 ** -b
+    assert torch.isfinite(got).all()
+    assert (got - 1).abs().max().item() <= 2.0 ** -7
