@@ -1577,6 +1577,9 @@ hipError_t launch_forward(const void *q, const void *k, const void *v, void *o, 
                           hipStream_t stream)
 {
     if (!forward_supported((int)p.P, D)) return hipErrorInvalidValue;
+    // K or V at an odd address: tiles that have not always been staged by DMA keep to plain loads, which take any address.
+    if (p.P % (D == 64 ? 64 : 128) != 0 && !(dma_aligned(k) && dma_aligned(v)))
+        return D == 64 ? launch_d<64>(q, k, v, o, B, p, win, stream) : launch_d<128>(q, k, v, o, B, p, win, stream);
     if (D == 64) return launch_groups<64>(q, k, v, o, B, p, win, order, stream);
     if (p.P % 128 != 0) return launch_groups<128>(q, k, v, o, B, p, win, order, stream);
     // Tiles of 128 tokens' multiples.  Up to 1280 waves of 32 queries (the chip holds 2048 of the key-group kernel's at this

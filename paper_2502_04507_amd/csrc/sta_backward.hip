@@ -225,7 +225,7 @@ constexpr int max_of(int a, int b) { return a > b ? a : b; }
 // for the dK/dV kernel (a kernel of their own for them read dO once more: 6.8 us of a 345 us training step at 16,384 tokens
 // x 8 heads of dimension 64, 0.23 ms of 53 ms at 115,200 x 24 of 128).
 // ---------------------------------------------------------------------------------------------------------
-template <int D, int QW, int G>
+template <int D, int QW, int G, bool DMA>
 __global__ __attribute__((amdgpu_flat_work_group_size(QW * G * 64, QW * G * 64), amdgpu_waves_per_eu(QW == 1 ? (D == 64 ? 2 : 1) : (D == 64 ? 4 : 2))))
 void sta_bwd_dq_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restrict__ k, const bf16_raw *__restrict__ v,
                        const bf16_raw *__restrict__ o, const bf16_raw *__restrict__ d_o, const float *__restrict__ lse,
@@ -276,8 +276,7 @@ void sta_bwd_dq_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restric
                 const bool is_v = j >= L::Groups;
                 const int part = j % L::Groups;
                 const char *src = (is_v ? vh : kh) + (size_t)(first_row + L::GroupRows * part) * L::RowB;
-                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + off),
-                                                 STA_LDS_PTR(stage + (is_v ? V_TILE : K_TILE) + part * L::Group), 16, 0, 0);
+                stage_group<DMA>(src + off, stage + (is_v ? V_TILE : K_TILE) + part * L::Group, lane);
             }
         }
         ++issued;
@@ -388,7 +387,7 @@ void sta_bwd_dq_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restric
 // 4550 -> 843.
 // A lane holds key column c16 of its wave's two 16-key blocks and the query rows 4*g4 .. 4*g4+3 of a result.
 // ---------------------------------------------------------------------------------------------------------
-template <int D, int NPAIR, int G>
+template <int D, int NPAIR, int G, bool DMA>
 __global__ __attribute__((amdgpu_flat_work_group_size(NPAIR * G * 128, NPAIR * G * 128), amdgpu_waves_per_eu(D == 64 ? 4 : NPAIR == 1 ? 2 : 3)))
 void sta_bwd_dkv_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restrict__ k, const bf16_raw *__restrict__ v,
                         const bf16_raw *__restrict__ d_o, const float *__restrict__ neg_lse,
@@ -455,9 +454,7 @@ void sta_bwd_dkv_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restri
                 const bool is_g = j >= L::Groups;
                 const int part = j % L::Groups;
                 const char *src = (is_g ? gh : qh) + (size_t)(first_row + L::GroupRows * part) * L::RowB;
-                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + off),
-                                                 STA_LDS_PTR(group_lds + stage * STAGE_B + (is_g ? G_TILE : Q_TILE) + part * L::Group),
-                                                 16, 0, 0);
+                stage_group<DMA>(src + off, group_lds + stage * STAGE_B + (is_g ? G_TILE : Q_TILE) + part * L::Group, lane);
             }
         }
         if (wave == STAT_WAVE)
@@ -663,12 +660,12 @@ BwdPlan make_plan(const BwdArgs &a, uint32_t cols, bool row_major, uint32_t *ids
     return plan;
 }
 
-template <int D, int QW, int G>
+template <int D, int QW, int G, bool DMA = true>
 hipError_t launch_dq(const BwdArgs &a)
 {
     uint32_t ids;
     const BwdPlan plan = make_plan(a, QW * 32, false, &ids);
-    sta_bwd_dq_kernel<D, QW, G><<<dim3(ids), dim3(QW * G * 64), 0, a.stream>>>(a.q, a.k, a.v, a.o, a.d_o, a.lse, a.neg_delta, a.neg_lse,
+    sta_bwd_dq_kernel<D, QW, G, DMA><<<dim3(ids), dim3(QW * G * 64), 0, a.stream>>>(a.q, a.k, a.v, a.o, a.d_o, a.lse, a.neg_delta, a.neg_lse,
                                                                               a.d_q, a.p, plan);
     return hipGetLastError();
 }
@@ -679,17 +676,19 @@ hipError_t launch_dq(const BwdArgs &a)
 // ones, which need the neighbouring rows in L2 (24 heads of the 30x48x80 grid 23.9, 24.8 ms).  Head after head against row after
 // row, us: four images, 64-token tiles, head dimension 64 79, 59, 128 139, 107; 10x30x56 in 96-token tiles 550, 472; 16x48x64 in
 // 256-token tiles, eight heads, 128 3059, 2598, 64 1609, 1241; 18x40x64 in 192-token tiles 3054, 2809.
-template <int D, int NPAIR, int G>
+template <int D, int NPAIR, int G, bool DMA = true>
 hipError_t launch_dkv(const BwdArgs &a)
 {
     uint32_t ids;
     const bool row_major = NPAIR < 6 && walk_of_rank(a, 0) == walk_of_rank(a, a.p.heads - 1);
     const BwdPlan plan = make_plan(a, NPAIR * 32, row_major, &ids);
-    sta_bwd_dkv_kernel<D, NPAIR, G><<<dim3(ids), dim3(NPAIR * G * 128), 0, a.stream>>>(a.q, a.k, a.v, a.d_o, a.neg_lse, a.neg_delta,
+    sta_bwd_dkv_kernel<D, NPAIR, G, DMA><<<dim3(ids), dim3(NPAIR * G * 128), 0, a.stream>>>(a.q, a.k, a.v, a.d_o, a.neg_lse, a.neg_delta,
                                                                                       a.d_k, a.d_v, a.p, plan);
     return hipGetLastError();
 }
 
+// Operands at an odd address: tiles that have not always been staged by DMA (no multiple of 128 tokens) take the smallest
+// shape of either kernel, with plain loads.
 // Shapes of the two kernels.  Measured in us, kernel alone; "clip" is the 12x48x48 grid in 384-token tiles at window 1x3x3
 // (108 sub-blocks per walk), "image" the 64x64 grid in 64-token tiles at 3x3 (18), "full" 12x32x48 in 384-token tiles at the
 // whole grid (576), then the number of heads.
@@ -705,6 +704,7 @@ hipError_t dispatch_dq(const BwdArgs &a)
     const uint64_t waves = (uint64_t)a.B * a.p.heads * (a.p.N / 32), fits = (uint64_t)sta::compute_units() * (D == 128 ? 8 : 12);
     const uint32_t P = a.p.P;
     const bool two = 2 * waves <= fits && longest_walk(a) >= 16;
+    if (P % 128 != 0 && !(sta::dma_aligned(a.k) && sta::dma_aligned(a.v))) return launch_dq<D, 1, 1, false>(a);
     if (P % 96 == 0 && P % 128 != 0) return two ? launch_dq<D, 3, 2>(a) : launch_dq<D, 3, 1>(a);
     if (P % 64 != 0) return launch_dq<D, 1, 1>(a);
     if (two) return launch_dq<D, 2, 2>(a);
@@ -725,6 +725,7 @@ hipError_t dispatch_dkv(const BwdArgs &a)
 {
     const uint64_t cus = sta::compute_units(), slices = (uint64_t)a.B * a.p.heads, waves = 2 * slices * (a.p.N / 32);
     const uint32_t P = a.p.P;
+    if (P % 128 != 0 && !(sta::dma_aligned(a.q) && sta::dma_aligned(a.d_o))) return launch_dkv<D, 1, 1, false>(a);
     if (P % 64 != 0) return P % 96 == 0 ? launch_dkv<D, 3, 2>(a) : launch_dkv<D, 1, 1>(a);
     constexpr int GROUPS = D == 128 ? 3 : 2;
     if (GROUPS * waves <= cus * (D == 128 ? 12 : 16) && longest_walk(a) >= 16) return launch_dkv<D, 2, GROUPS>(a);

@@ -57,6 +57,9 @@ struct FwdParams {
     float *split_ws = nullptr;
 };
 
+// The DMA into LDS fetches 16 bytes per lane; tensors are only asked to hold elements.
+inline bool dma_aligned(const void *p) { return ((uintptr_t)p & 15) == 0; }
+
 // Division of any 32-bit number by a launch constant with one multiplication: n / d = (((n - q) >> pre) + q) >> post
 // with q = the upper half of n * magic.
 struct FastDiv {

@@ -161,6 +161,20 @@ struct Staged {
     static constexpr int tr_offset(int cb) { return D == 128 ? (cb & 1) * 32 : 0; }
 };
 
+// Brings the 1 KB group of a staged operand whose chunk for this lane starts at src to LDS address dst: by DMA, or, for sources
+// that do not start at a multiple of 16 bytes, through a register (a barrier with a wait for LDS has to follow).
+template <bool DMA>
+__device__ __forceinline__ void stage_group(const char *src, char *dst, int lane)
+{
+    if constexpr (DMA) {
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src, STA_LDS_PTR(dst), 16, 0, 0);
+    } else {
+        typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+        typedef u32x4 u32x4_anywhere __attribute__((aligned(1)));
+        *reinterpret_cast<u32x4 *>(dst + 16 * lane) = *reinterpret_cast<const u32x4_anywhere *>(src);
+    }
+}
+
 // Layout of an operand that is read by rows only: groups (one DMA instruction) 1024 + 64 bytes apart, the chunk's two
 // low bits XORed with the row inside the group (256-byte rows) or with half of it (128-byte rows).
 //  - 256-byte rows: the four rows of a group land in four 16-byte positions of one 64-byte quarter, and consecutive
