@@ -608,7 +608,7 @@ struct BwdArgs {
     const float *lse;
     float *neg_delta, *neg_lse;
     bf16_raw *d_q, *d_k, *d_v;
-    int B;
+    int B, D;
     sta::FwdParams p;
     const sta::WindowTable &win;
     const sta::HeadOrder &order;
@@ -670,18 +670,41 @@ hipError_t launch_dq(const BwdArgs &a)
     return hipGetLastError();
 }
 
-// Row after row over all heads, unless their walks differ (a head of long walks must not have rows left at the end: 16x48x64
-// in 256-token tiles, 3x3x3 and 3x3x5 2046 us head after head, 2377 row after row; 30x48x80, windows from 1x3x3 to the whole
-// grid 17.5, 26.6 ms) or the workgroups are the six-pair
-// ones, which need the neighbouring rows in L2 (24 heads of the 30x48x80 grid 23.9, 24.8 ms).  Head after head against row after
-// row, us: four images, 64-token tiles, head dimension 64 79, 59, 128 139, 107; 10x30x56 in 96-token tiles 550, 472; 16x48x64 in
-// 256-token tiles, eight heads, 128 3059, 2598, 64 1609, 1241; 18x40x64 in 192-token tiles 3054, 2809.
+// Order of the dK/dV items where all heads' walks are equal (otherwise head after head: heads of long walks must not have rows
+// left at the end; 16x48x64 in 256-token tiles, 3x3x3 and 3x3x5 2046 us head after head, 2377 row after row; 30x48x80, windows
+// from 1x3x3 to the whole grid 17.5, 26.6 ms).  Entry point, head after head against row after row:
+// - Rows of tiles per head a multiple of eight: head after head an XCD gets the same rows of every head, and border rows have
+//   half the work of inner ones.  16x48x64 in 256-token tiles, 24 heads, head dimension 64 7469, 6586 us, 128 13,994, 12,486;
+//   24x64x64 in 384-token tiles 128 40.8, 35.2 ms; 20x64x64 in 64-token tiles 3986, 3258.  A single head is the exception, it
+//   has no other head's rows to take in turn: 16x48x64 425, 475.
+// - Otherwise the rows of all heads in turn, longest first, shorten the tail, which tells in launches of up to about sixteen
+//   rounds of workgroups (18x40x64 in 192-token tiles, 16 heads 3564, 3310 us; 10x30x56 in 96-token tiles 529, 472; 30x48x80
+//   in 384-token tiles, head dimension 64, three heads 3042, 2936, eight 7565, 7511).  Beyond that what counts is that the next row
+//   of a head finds operands of this one in the caches: its box of Q and dO rows either fits an XCD's L2 (20x48x64 in
+//   128-token tiles, 40 heads 7295, 7194) or the rows of a head should stay together (30x48x80, 24 heads 21.98, 22.17 ms,
+//   twelve 11.30, 11.66).  A single head: only where all its workgroups are resident at once (20x48x64 in 128-token tiles
+//   288, 267 us; 30x48x80 1144, 1171).
+// - Six pairs, one workgroup per CU, stay head after head except in the first case: 12x48x48, six heads 917, 940 us; 30x48x80,
+//   24 heads 40.3, 41.3 ms.
+bool rows_of_all_heads(const BwdArgs &a, uint32_t cols, uint64_t resident, bool six_pairs)
+{
+    const sta::FwdParams &p = a.p;
+    const uint64_t slices = (uint64_t)a.B * p.heads;
+    if (walk_of_rank(a, 0) != walk_of_rank(a, p.heads - 1)) return false;
+    if (p.n_t * p.n_h % 8 == 0) return slices > 1;
+    if (six_pairs) return false;
+    if (slices == 1) return p.N / cols <= resident;
+    const uint32_t kept_w = 2 * (a.win.w[a.order.h[0]][2] / 2u) + 1;
+    const uint64_t box_rows = (uint64_t)longest_walk(a) * kSub / (kept_w < p.n_w ? kept_w : p.n_w) * p.n_w;
+    return slices * (p.N / cols) <= 16 * resident || box_rows * a.D * 4 <= (4u << 20);
+}
+
 template <int D, int NPAIR, int G, bool DMA = true>
 hipError_t launch_dkv(const BwdArgs &a)
 {
     uint32_t ids;
-    const bool row_major = NPAIR < 6 && walk_of_rank(a, 0) == walk_of_rank(a, a.p.heads - 1);
-    const BwdPlan plan = make_plan(a, NPAIR * 32, row_major, &ids);
+    const uint64_t resident = (uint64_t)sta::compute_units() * (D == 64 ? 16 : 12) / (2 * NPAIR * G);     // workgroups
+    const BwdPlan plan = make_plan(a, NPAIR * 32, rows_of_all_heads(a, NPAIR * 32, resident, NPAIR == 6), &ids);
     sta_bwd_dkv_kernel<D, NPAIR, G, DMA><<<dim3(ids), dim3(NPAIR * G * 128), 0, a.stream>>>(a.q, a.k, a.v, a.d_o, a.neg_lse, a.neg_delta,
                                                                                       a.d_k, a.d_v, a.p, plan);
     return hipGetLastError();
@@ -747,7 +770,7 @@ hipError_t launch_backward(const void *q, const void *k, const void *v, const vo
     if (!backward_supported((int)p.P, D)) return hipErrorInvalidValue;
     const BwdArgs a = {static_cast<const bf16_raw *>(q), static_cast<const bf16_raw *>(k), static_cast<const bf16_raw *>(v),
                        static_cast<const bf16_raw *>(o), static_cast<const bf16_raw *>(d_o), lse, stats, stats + stat_rows,
-                       static_cast<bf16_raw *>(d_q), static_cast<bf16_raw *>(d_k), static_cast<bf16_raw *>(d_v), B, p, win, order,
+                       static_cast<bf16_raw *>(d_q), static_cast<bf16_raw *>(d_k), static_cast<bf16_raw *>(d_v), B, D, p, win, order,
                        stream};
     const hipError_t e = D == 64 ? dispatch_dq<64>(a) : dispatch_dq<128>(a);
     if (e != hipSuccess) return e;

@@ -40,3 +40,22 @@ def test_gradient_kernel_shapes_match_the_oracle(name, grid, tile, B, H, windows
             rq, rk, rv = oracle_backward(w, q, k, v, g, b, h)
             for label, got, ref in (("dQ", dq, rq), ("dK", dk, rk), ("dV", dv, rv)):
                 assert_grad_parity(got[b, h].float().numpy(), ref, "%s D%d %s b%d h%d" % (name, D, label, b, h))
+
+
+# Launches that fill the chip with six pairs (384-token tiles, at least 205 column blocks of 192 keys on 256 CUs), whole heads.
+SIX_PAIRS = [
+    # eight rows of tiles per head and equal windows: the rows of all heads in turn
+    ("six-rows", (12, 32, 32), 4, [(1, 3, 1)]),
+]
+
+
+@pytest.mark.parametrize("name,grid,H,windows", SIX_PAIRS, ids=[s[0] for s in SIX_PAIRS])
+def test_six_pair_gradients_match_the_oracle(name, grid, H, windows):
+    w = syn.custom("bwd-" + name, 1, H, 128, grid, (6, 8, 8), [windows[h % len(windows)] for h in range(H)], "bf16", seed=1313)
+    q, k, v = syn.make_qkv(w)
+    g = syn.make_dout(w)
+    (dq, dk, dv), _ = gpu_backward(w, q, k, v, g)
+    for h in (0, H - 1):
+        rq, rk, rv = oracle_backward(w, q, k, v, g, 0, h)
+        for label, got, ref in (("dQ", dq, rq), ("dK", dk, rk), ("dV", dv, rv)):
+            assert_grad_parity(got[0, h].float().numpy(), ref, "%s %s h%d" % (name, label, h))
