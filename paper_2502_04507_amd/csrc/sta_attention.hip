@@ -445,8 +445,8 @@ __device__ __forceinline__ GroupItem group_item_of(uint32_t id, const sta::FwdPa
 // What bounds it.  Head dimension 64: a unit (32 keys) is 18 matrix instructions (288 cycles of the matrix pipe) next to 49
 // vector instructions, 16 of them exponentials; measured 350 cycles per wave and unit on 64-token image tiles with four
 // waves per SIMD.  30x48x80 grid, 24 heads, 384-token tiles, window 3x3x3: 7.00-7.15 ms with the 12-wave kernel on
-// v_mfma_f32_32x32x16_bf16 that was here before, 6.69-6.83 ms with QW = 4 (1090 TFLOP/s; QW = 12: 7.5 ms, QW = 2: 7.3 ms,
-// 64 keys per barrier: 6.9-7.0 ms; row sums by v_dot2: 7.2 ms).  128 heads of a 64x64 image in 8x8 tiles, window 3x3:
+// v_mfma_f32_32x32x16_bf16 that was here before, 6.68-6.83 ms with QW = 4 (QW = 12: 7.5 ms, QW = 2: 7.3 ms; row sums by
+// v_dot2: 7.2 ms), 6.53 with two units per stage (UPS, 64 keys per barrier; 1120 TFLOP/s).  128 heads of a 64x64 image in 8x8 tiles, window 3x3:
 // 105-109 us before, 98-100 us.  Head dimension 128, 96-token tiles (10x30x56, 10 slices, windows 3x3x3 and 2x4x3): 2390 us
 // with the register-staged kernel that served it before, 299 us.
 // FOLLOW: the offset is the running maximum in every unit.  Otherwise it is the maximum of an item's first unit, and the
@@ -459,7 +459,7 @@ __device__ __forceinline__ GroupItem group_item_of(uint32_t id, const sta::FwdPa
 // allow: it waits for every outstanding DMA) changes nothing at four waves per SIMD and costs occupancy on small tiles:
 // 6.77 against 6.73 ms, 108 against 98 us.
 // ---------------------------------------------------------------------------
-template <int D, int QW, int KG, int WPE, bool FOLLOW>
+template <int D, int QW, int KG, int WPE, bool FOLLOW, int UPS>
 __global__ __attribute__((amdgpu_flat_work_group_size(QW * KG * 64, QW * KG * 64), amdgpu_waves_per_eu(WPE)))
 void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
                                                                          const bf16_raw *__restrict__ k,
@@ -474,7 +474,9 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
     constexpr int WQ = 16 * NQ;                             // queries per wave
     constexpr int QB = QW * WQ;                             // queries per workgroup
     constexpr int UNIT_B = R::Tile + L::Tile;               // 32 keys: K, then V
-    constexpr int GROUP_B = 2 * UNIT_B;                     // LDS of one key group: two stages
+    constexpr int STAGE_B = UPS * UNIT_B;                   // what a barrier makes available
+    constexpr int GROUP_B = 2 * STAGE_B;                    // LDS of one key group: two stages
+    static_assert(UPS == 1 || KG == 1, "shares of a walk are counted in single units");
     constexpr int OPS = 2 * L::Groups;                      // DMA instructions per unit
     constexpr int WAVE_OPS = (OPS + QW - 1) / QW;           // at most this many per wave
     constexpr int WAVE_OUT = WQ * L::RowB;                  // a wave's output rows
@@ -521,22 +523,25 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
         if (issued >= n_units) return;
         uint32_t koff = k_lane_off, voff = v_lane_off;
         asm volatile("" : "+v"(koff), "+v"(voff));          // keep the lane offsets 32-bit next to a scalar base
-        const uint32_t row = walk.next_row;
-        walk.advance();
-        char *stage = smem + kg * GROUP_B + (issued & 1) * UNIT_B;
+        char *stage = smem + kg * GROUP_B + (issued / UPS & 1) * STAGE_B;
 #pragma unroll
-        for (int i = 0; i < WAVE_OPS; ++i) {
-            const int j = qw + i * QW;
-            if (OPS % QW == 0 || j < OPS) {
-                const bool is_v = j >= L::Groups;
-                const int group = j % L::Groups;
-                const char *src = (is_v ? vh : kh) + (size_t)(row + L::GroupRows * group) * L::RowB;
-                char *dst = stage + (is_v ? R::Tile + group * L::Group : group * R::Group);
-                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + (is_v ? voff : koff)),
-                                                 STA_LDS_PTR(dst), 16, 0, 0);
+        for (int su = 0; su < UPS; ++su) {
+            const uint32_t row = walk.next_row;
+            walk.advance();
+#pragma unroll
+            for (int i = 0; i < WAVE_OPS; ++i) {
+                const int j = qw + i * QW;
+                if (OPS % QW == 0 || j < OPS) {
+                    const bool is_v = j >= L::Groups;
+                    const int group = j % L::Groups;
+                    const char *src = (is_v ? vh : kh) + (size_t)(row + L::GroupRows * group) * L::RowB;
+                    char *dst = stage + su * UNIT_B + (is_v ? R::Tile + group * L::Group : group * R::Group);
+                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + (is_v ? voff : koff)),
+                                                     STA_LDS_PTR(dst), 16, 0, 0);
+                }
             }
         }
-        ++issued;
+        issued += UPS;
     };
     issue_next();
 
@@ -687,21 +692,25 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
         constexpr bool CAREFUL = decltype(careful_c)::value;
         constexpr int REST = CAREFUL ? kCareful : FOLLOW ? kFollow : kPlain;
         const float bound = FOLLOW || !CAREFUL ? 0.f : __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(8.0f / c)));
-        auto next_unit = [&]() __attribute__((always_inline)) {
-            // this wave's DMA for the unit must have landed, and everyone's; the other stage is free again
+        auto next_stage = [&]() __attribute__((always_inline)) {
+            // this wave's DMA for the stage must have landed, and everyone's; the other stage is free again
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
             issue_next();
         };
+        auto rest_at = [&](uint32_t off) __attribute__((always_inline)) { unit_at(std::integral_constant<int, REST>{}, off, bound); };
         if constexpr (!CAREFUL) {
-            next_unit();
+            next_stage();
             if (KG == 1 || n_units > 0) unit_at(std::integral_constant<int, kFirst>{}, 0u, 0.f);
+            if constexpr (UPS == 2) rest_at(UNIT_B);
         }
 #pragma unroll 1
-        for (int u = CAREFUL ? 0 : 1; u < n_steps; ++u) {
-            next_unit();
-            if (KG == 1 || u < n_units) unit_at(std::integral_constant<int, REST>{}, (uint32_t)((u & 1) * UNIT_B), bound);
+        for (int u = CAREFUL ? 0 : UPS; u < n_steps; u += UPS) {
+            next_stage();
+            const uint32_t at = (uint32_t)((u / UPS & 1) * STAGE_B);
+            if (KG == 1 || u < n_units) rest_at(at);
+            if constexpr (UPS == 2) rest_at(at + UNIT_B);
         }
     };
     float l_tot[NQ];
@@ -1422,7 +1431,7 @@ hipError_t launch_x32(const void *q, const void *k, const void *v, void *o, int 
     return hipGetLastError();
 }
 
-template <int D, int QW, int KG, int WPE, bool FOLLOW>
+template <int D, int QW, int KG, int WPE, bool FOLLOW, int UPS = 1>
 hipError_t launch_group(const void *q, const void *k, const void *v, void *o, int B, const sta::FwdParams &p,
                         const sta::WindowTable &win, const sta::HeadOrder &order, hipStream_t stream)
 {
@@ -1444,7 +1453,7 @@ hipError_t launch_group(const void *q, const void *k, const void *v, void *o, in
         for (int a = 0; a < 3; ++a) plan.head[h].w[a] = win.w[order.h[h]][a];
     }
     const uint32_t ids = 8 * chunk * ((plan.total + 8 * chunk - 1) / (8 * chunk));
-    sta_fwd_group_kernel<D, QW, KG, WPE, FOLLOW><<<dim3(ids), dim3(QW * KG * 64), 0, stream>>>(
+    sta_fwd_group_kernel<D, QW, KG, WPE, FOLLOW, UPS><<<dim3(ids), dim3(QW * KG * 64), 0, stream>>>(
         static_cast<const bf16_raw *>(q), static_cast<const bf16_raw *>(k), static_cast<const bf16_raw *>(v),
         static_cast<bf16_raw *>(o), p, plan);
     return hipGetLastError();
@@ -1473,7 +1482,13 @@ uint32_t longest_walk(const sta::FwdParams &p, const sta::WindowTable &win, cons
 
 // Shape of the key-group kernel for a launch.
 // Waves of queries: as many as the tile allows up to four (three for 96-token multiples), because a K/V unit brought into LDS
-// serves them all; five waves leave the four SIMDs uneven (tiles of 320 tokens: 585 us with five waves, 431 with two).
+// serves them all; five waves leave the four SIMDs uneven (tiles of 320 tokens: 585 us with five waves, 431 with two).  Tiles of
+// 192 tokens at head dimension 64 take three, but two where the fullest CU gets fewer waves that way (with key groups: no more;
+// us, three and two waves, waves of the fullest CU in brackets: 9x40x40, window 3x3x3, two heads 79 (6), 54 (4); four 118 (9),
+// 92 (8); twelve, one group 263 (24), 257 (22); six, one group 133 (12), 157 (12); 6x24x40, 1x3x3, four heads 18.9 (3), 21.8 (4)).
+// Two units per stage where four waves of queries share it and there are no key groups: one barrier for 64 keys (12x48x48 in
+// 384-token tiles, us, one and two units: three heads 85, 83; six 162, 157; twelve 289, 283).  With two waves or with groups the
+// larger stages or the registers cost a wave per SIMD (twelve heads, two groups 305, 362).
 // Key groups: the most, of 1, 2 and 4, with which the launch still fits the chip at once (16 waves per CU at head dimension
 // 64, 8 at 128) and a group has at least eight units to walk.  Measured around the line (us; 1, 2, 4 groups), head dimension
 // 64, 384-token tiles, 108 units: 324 waves of queries 45, 28, 24; 972 waves 62, 40, 38; 1944 waves 69, 66, 71; 2592 waves
@@ -1487,14 +1502,17 @@ hipError_t launch_groups(const void *q, const void *k, const void *v, void *o, i
     const uint32_t units = longest_walk(p, win, order);
     const uint64_t fits = (uint64_t)resident_workgroups(1) * (D == 64 ? 16 : 8);
     const int groups = 4 * waves <= fits && units >= 32 ? 4 : 2 * waves <= fits && units >= 16 ? 2 : 1;
-    if (p.P % 96 == 0 && p.P % 128 != 0) {
+    const uint64_t cus = resident_workgroups(1);
+    auto fullest_cu = [&](uint64_t qw) { return (waves / qw + cus - 1) / cus * qw; };          // waves of queries
+    const bool two_for_192 = D == 64 && p.P % 64 == 0 && (groups > 1 ? fullest_cu(2) <= fullest_cu(3) : 20 * fullest_cu(2) < 19 * fullest_cu(3));
+    if (p.P % 96 == 0 && p.P % 128 != 0 && !two_for_192) {
         if (D == 64 && p.P % 64 == 0) return launch_group_count<64, 3, 3, false>(groups, q, k, v, o, B, p, win, order, stream);
         return launch_group_count<D, 3, 3, true>(groups, q, k, v, o, B, p, win, order, stream);
     }
     if (p.P % 64 == 0) {
         if (D == 128 && p.P % 128 == 0) return launch_group_count<128, 2, 2, false>(groups, q, k, v, o, B, p, win, order, stream);
         if (D == 128) return launch_group_count<128, 2, 2, true>(groups, q, k, v, o, B, p, win, order, stream);
-        if (groups == 1 && p.P % 128 == 0) return launch_group<64, 4, 1, 4, false>(q, k, v, o, B, p, win, order, stream);
+        if (groups == 1 && p.P % 128 == 0) return launch_group<64, 4, 1, 4, false, 2>(q, k, v, o, B, p, win, order, stream);
         return launch_group_count<64, 2, 4, false>(groups, q, k, v, o, B, p, win, order, stream);
     }
     // other multiples of 32 tokens: one wave of queries, whose LDS stages then limit a CU to four such workgroups at head

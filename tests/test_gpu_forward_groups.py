@@ -26,6 +26,8 @@ SHAPES = [
     ("p128", (4, 24, 24), (2, 8, 8), [(1, 1, 3), (1, 1, 1)]),           # 12 and 4: one group
     ("p128-two", (4, 24, 24), (2, 8, 8), [(2, 1, 3), (1, 3, 1)]),       # 24 and 12: two groups
     ("p160", (5, 8, 12), (5, 8, 4), [(1, 1, 3), (1, 1, 1)]),            # 15 and 5: one group
+    ("p192-two-waves", (3, 24, 40), (3, 8, 8), [(1, 3, 5), (1, 1, 1)]), # 90 and 6: four groups, of two waves at head dimension 64
+    ("p192-three-waves", (6, 24, 40), (3, 8, 8), [(1, 3, 3)] * 4),      # 54: four groups, of three waves
     ("p384", (6, 16, 16), (6, 8, 8), [(1, 1, 1), (1, 1, 1)]),           # 12: one group
     ("p384-four", (6, 16, 24), (6, 8, 8), [(1, 2, 2), (1, 1, 1)]),      # 72 and 12: four groups
 ]
@@ -99,3 +101,27 @@ def test_merged_accumulators_of_key_groups_stay_in_range(D, grid, tile, groups):
     got = o.float().cpu() * 2.0 ** -b
     assert torch.isfinite(got).all()
     assert (got - 1).abs().max().item() <= 2.0 ** -7
+
+
+@pytest.mark.parametrize("grid,tile,heads", [((6, 16, 24), (6, 8, 8), 30), ((4, 16, 16), (2, 8, 8), 66)], ids=["p384", "p128"])
+def test_two_units_per_stage_redo_items_whose_scores_grow(grid, tile, heads):
+    """Head dimension 64 with more than 2048 waves of queries and tiles of 128 tokens' multiples: no key groups, two units per
+    stage.  The scores grow along the walk so that items are done again.  Every other head holds the same data."""
+    w = syn.custom("outgrow-stages", 1, 2, 64, grid, tile, [(1, 3, 3), (3, 3, 3)], "bf16", seed=85)
+    q, k, v = syn.make_qkv(w)
+    order = torch.from_numpy(orc.tile_order(w.grid, w.tile))
+    ramp = torch.empty(w.N)
+    ramp[order] = torch.linspace(0.02, 14.0, w.N)                       # along the tiled sequence
+    k = (k.float() * ramp[None, None, :, None]).to(torch.bfloat16)
+    q = (q.float() * 2.0).to(torch.bfloat16)
+    index = torch.arange(heads) % 2
+    qt, kt, vt = (x[:, index][:, :, order].contiguous().to(DEV) for x in (q, k, v))
+    o = torch.full_like(qt, float("nan"))
+    sta.sta_forward(qt, kt, vt, o, w.grid, w.tile, [w.window_tiles[h % 2] for h in range(heads)])
+    torch.cuda.synchronize()
+    for h in range(heads):
+        assert torch.equal(o[:, h].view(torch.int16), o[:, h % 2].view(torch.int16)), h
+    for h in range(2):
+        ref = orc.attention(q[0, h].float().numpy(), k[0, h].float().numpy(), v[0, h].float().numpy(), w.grid, w.tile,
+                            orc.window_tiles_to_tokens(w.window_tiles[h], w.tile))
+        gu.assert_parity(o[0, h].float().cpu().numpy(), ref[order.numpy()], "outgrow-stages h%d" % h)
