@@ -968,8 +968,8 @@ __global__ __launch_bounds__(NW * 64, MINB) void sta_fwd_x32_kernel(const bf16_r
     // Offset m per query, in the units of the scores (raw dot products; base-2 exponents with PRESCALE).  The score
     // accumulators START at -m (Sinit, the value replicated over the four registers of an accumulator), so what the
     // matrix instructions deliver is s - m and the exponential needs one multiplication by scale * log2(e) per
-    // element instead of a fused multiply-add plus bookkeeping.  m is 0 for the first sub-block, which then always
-    // takes the re-basing path below, and never decreases afterwards.
+    // element instead of a fused multiply-add plus bookkeeping.  m is 0 while the first sub-block's scores are formed, which
+    // then set it, and never decreases afterwards.
     float m_run[2] = {0.f, 0.f};
     floatx4 Sinit[2] = {floatx4{0.f, 0.f, 0.f, 0.f}, floatx4{0.f, 0.f, 0.f, 0.f}};
     float l_run[2] = {0.f, 0.f};                  // this lane's share of the two row sums
@@ -1070,8 +1070,11 @@ __global__ __launch_bounds__(NW * 64, MINB) void sta_fwd_x32_kernel(const bf16_r
     // (lds_off: where the stage begins; it enters the operand base addresses at run time)
     // units of the accumulated scores: base-2 exponents if Q was scaled, raw dot products otherwise
     const float c = PRESCALE ? 1.f : p.scale_log2e;
+    constexpr int kPlain = 0, kFirst = 1, kCareful = 2;
     auto sub_block_at = [&](auto track_c, uint32_t lds_off, float grow_above) __attribute__((always_inline)) {
-        constexpr bool TRACK = decltype(track_c)::value;   // follow the growth of the scores in this sub-block
+        // kFirst: set the offsets.  kCareful: follow the growth of the scores, which start at zero here: those of keys behind
+        // masked ones (scores of the lowest numbers) are lost in accumulators that start at minus such an offset.
+        constexpr int TRACK = decltype(track_c)::value;
         const uint32_t kb_ = k_base + lds_off;
         uint32_t vb_[4];
 #pragma unroll
@@ -1082,7 +1085,7 @@ __global__ __launch_bounds__(NW * 64, MINB) void sta_fwd_x32_kernel(const bf16_r
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-            for (int qb = 0; qb < 2; ++qb) S[kb][qb] = Sinit[qb];
+            for (int qb = 0; qb < 2; ++qb) S[kb][qb] = TRACK == kCareful ? floatx4{0.f, 0.f, 0.f, 0.f} : Sinit[qb];
         auto k_read = [&](auto kbc, auto ksc) {
             return ds_read_b128_at<decltype(kbc)::value * 4 * kKGroup + decltype(ksc)::value * 64>(kb_);
         };
@@ -1121,44 +1124,44 @@ __global__ __launch_bounds__(NW * 64, MINB) void sta_fwd_x32_kernel(const bf16_r
         for (int qb = 1; qb >= 0; --qb) S[1][qb] = mfma_16x16x32(b3, Qr[qb][3], S[1][qb]);
         __builtin_amdgcn_sched_barrier(0);
         // ---- online softmax.  A lane holds, for each of its two queries, 8 of the 32 scores (keys 4*g4 + i of both
-        // key blocks); the other 24 sit in the lanes 16, 32 and 48 further on.  The offset only moves when a score
-        // exceeds it by more than 2^8 in the exponent (lazy re-basing), which after the first sub-blocks is rare: the
-        // common path takes one maximum over the lane's 16 values and one comparison, with no exchange between
-        // lanes; only when some lane reports growth is the row maximum formed over the four lanes of a query, so
-        // that all of them move to the same offset.  grow_above is that bound in the units of the scores, or -infinity
-        // in an item's first sub-block.
-        if constexpr (TRACK) {
+        // key blocks); the other 24 sit in the lanes 16, 32 and 48 further on.  In the careful loop the offset only moves
+        // when a score exceeds it by more than 2^8 in the exponent (grow_above, in the units of the scores).
+        if constexpr (TRACK != kPlain) {
             float mq[2];
-    #pragma unroll
+#pragma unroll
             for (int qb = 0; qb < 2; ++qb) {
                 mq[qb] = max3(S[0][qb][0], S[0][qb][1], S[0][qb][2]);
                 mq[qb] = max3(mq[qb], S[0][qb][3], S[1][qb][0]);
                 mq[qb] = max3(mq[qb], S[1][qb][1], S[1][qb][2]);
+                mq[qb] = quad_lane_max(fmaxf(mq[qb], S[1][qb][3]));
             }
-            const float mx = max3(max3(mq[0], S[1][0][3], mq[1]), S[1][1][3], S[1][1][3]);
-            if (__builtin_expect(__builtin_amdgcn_ballot_w64(mx > grow_above) != 0, 0)) {
-    #pragma unroll
-                for (int qb = 0; qb < 2; ++qb) {
-                    const float row_max = quad_lane_max(fmaxf(mq[qb], S[1][qb][3]));
-                    const float shift = row_max > grow_above ? row_max : 0.f;     // the same in the four lanes of a query
-                    // shift is negative only in a first sub-block, where the accumulators are still zero
-                    const float alpha = __builtin_amdgcn_exp2f(fminf(-shift, 0.f) * c);
-                    m_run[qb] += shift;
-    #pragma unroll
-                    for (int r = 0; r < 4; ++r) Sinit[qb][r] = -m_run[qb];
-    #pragma unroll
-                    for (int kb = 0; kb < 2; ++kb)
-    #pragma unroll
-                        for (int r = 0; r < 4; ++r) S[kb][qb][r] -= shift;
-                    l_run[qb] *= alpha;
-                    // in place: written as plain multiplications the register allocator gives the scaled accumulators
-                    // new registers and then copies all 64 on the path that does NOT rescale
-                    // (the compiler does not see into the assembly: the wait state that a vector instruction needs before
-                    // it reads the result of a transcendental one is given by hand)
-                    const float alpha_settled = settled_after_transcendental(alpha);
-    #pragma unroll
-                    for (int cb = 0; cb < CB; ++cb) scale_in_place(Oacc[cb][qb], alpha_settled);
+#pragma unroll
+            for (int qb = 0; qb < 2; ++qb) {
+                float offset;
+                if constexpr (TRACK == kFirst) {
+                    m_run[qb] = offset = mq[qb] == -INFINITY ? 0.f : mq[qb];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) Sinit[qb][r] = -offset;
+                } else {
+                    const bool grown = mq[qb] > m_run[qb] + grow_above;           // the same in the four lanes of a query
+                    if (__builtin_amdgcn_ballot_w64(grown) != 0) {
+                        const float alpha = grown ? __builtin_amdgcn_exp2f((m_run[qb] - mq[qb]) * c) : 1.f;
+                        m_run[qb] = grown ? mq[qb] : m_run[qb];
+                        l_run[qb] *= alpha;
+                        // in place: written as plain multiplications the register allocator gives the scaled accumulators
+                        // new registers and then copies all 64 on the path that does NOT rescale
+                        // (the compiler does not see into the assembly: the wait state that a vector instruction needs before
+                        // it reads the result of a transcendental one is given by hand)
+                        const float alpha_settled = settled_after_transcendental(alpha);
+#pragma unroll
+                        for (int cb = 0; cb < CB; ++cb) scale_in_place(Oacc[cb][qb], alpha_settled);
+                    }
+                    offset = m_run[qb] == -INFINITY ? 0.f : m_run[qb];
                 }
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) S[kb][qb][r] -= offset;
             }
         }
         // first group of V-operand reads (channel blocks 0..3) goes out once the offsets are settled (no
@@ -1236,19 +1239,21 @@ __global__ __launch_bounds__(NW * 64, MINB) void sta_fwd_x32_kernel(const bf16_r
     // maximum (ten vector instructions and a branch less per sub-block), and the row sums are looked at once at the
     // end: if one of them is beyond 2^96 or not a number, or an accumulator has left the range, the workgroup does the
     // whole item again with the careful loop, which re-bases whenever a score exceeds the offset by more than 2^8 in
-    // the exponent.  (2^96 leaves 66 in the exponent of e between the first keys' maximum and the largest score before
+    // the exponent.  (Its scores start at zero and the offset is subtracted behind the product; with the offset in the
+    // accumulators as well it cost 36 bytes of scratch: 24 heads of 30x48x80, window 1x1x1 755 -> 728 us.)  (2^96 leaves 66 in the exponent of e between the first keys' maximum and the largest score before
     // the second pass is needed, and room for |V| up to 2^32 in the accumulators.)
     next_sub_block();
-    sub_block_at(std::true_type{}, 0u, __uint_as_float(0xff800000u));
+    sub_block_at(std::integral_constant<int, kFirst>{}, 0u, 0.f);
 #pragma unroll 1
     for (int iter = 1; iter < n_iter; ++iter) {
         next_sub_block();
-        sub_block_at(std::false_type{}, (uint32_t)((iter & 1) * STAGE_BYTES), 0.f);
+        sub_block_at(std::integral_constant<int, kPlain>{}, (uint32_t)((iter & 1) * STAGE_BYTES), 0.f);
     }
     float l_tot[2];
 #pragma unroll
     for (int qb = 0; qb < 2; ++qb) l_tot[qb] = quad_lane_sum(l_run[qb]);
-    constexpr float kRedoAbove = 79228162514264337593543950336.f;      // 2^96
+    // 2^96; and 2^-64, below which only rows are whose first keys all score minus infinity (their offset is 0 then)
+    constexpr float kRedoAbove = 79228162514264337593543950336.f, kRedoBelow = 5.42101086242752217e-20f;
     // The accumulators too: with |V| beyond 2^32 they can leave the range before the row sums reach the bound.  The
     // test is on the bit patterns (largest exponent field), so that it sees a NaN (infinity minus infinity) as well.
     uint32_t o_max = 0;
@@ -1260,10 +1265,11 @@ __global__ __launch_bounds__(NW * 64, MINB) void sta_fwd_x32_kernel(const bf16_r
             for (int r = 0; r < 4; ++r) o_max = max(o_max, __float_as_uint(Oacc[cb][qb][r]) & 0x7fffffffu);
     // (With finite inputs a row sum is never a NaN: a probability that overflows is +infinity, and so is the sum.
     // The barrier inside also ends every wave's reads of the stages.)
-    if (__builtin_expect(__syncthreads_or(!(l_tot[0] < kRedoAbove && l_tot[1] < kRedoAbove) || o_max >= 0x7f800000u), 0)) {
+    if (__builtin_expect(__syncthreads_or(!(l_tot[0] < kRedoAbove && l_tot[1] < kRedoAbove) || l_tot[0] < kRedoBelow ||
+                                         l_tot[1] < kRedoBelow || o_max >= 0x7f800000u), 0)) {
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb) {
-            m_run[qb] = 0.f;
+            m_run[qb] = -INFINITY;
             l_run[qb] = 0.f;
             Sinit[qb] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -1273,8 +1279,8 @@ __global__ __launch_bounds__(NW * 64, MINB) void sta_fwd_x32_kernel(const bf16_r
 #pragma unroll 1
         for (int iter = 0; iter < n_iter; ++iter) {
             next_sub_block();
-            // growth threshold: 2^8 in the units of the scores, -infinity for the first keys of an item
-            sub_block_at(std::true_type{}, (uint32_t)((iter & 1) * STAGE_BYTES), __uint_as_float(iter == 0 ? 0xff800000u : bound_bits));
+            // growth threshold: 2^8 in the units of the scores
+            sub_block_at(std::integral_constant<int, kCareful>{}, (uint32_t)((iter & 1) * STAGE_BYTES), __uint_as_float(bound_bits));
         }
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb) l_tot[qb] = quad_lane_sum(l_run[qb]);
@@ -1290,7 +1296,7 @@ __global__ __launch_bounds__(NW * 64, MINB) void sta_fwd_x32_kernel(const bf16_r
 #pragma unroll
             for (int cb = 0; cb < CB; ++cb) *reinterpret_cast<floatx4 *>(wo + 16 * cb + 4 * g4) = Oacc[cb][qb];
             if (g4 == 0) {
-                ws[(size_t)QB * D + wave * 32 + 16 * qb + c16] = m_run[qb] * c;      // the merge takes base-2 units
+                ws[(size_t)QB * D + wave * 32 + 16 * qb + c16] = fmaxf(m_run[qb] * c, -3.0e38f);     // the merge takes base-2 units
                 ws[(size_t)QB * D + QB + wave * 32 + 16 * qb + c16] = l_tot[qb];
             }
         }
