@@ -91,8 +91,7 @@ def test_backward_parity_whole(name, B, H, grid, tile, windows, scale):
 
 
 @pytest.mark.parametrize("name,D,grid,tile,windows", [
-    # head dimension 64 with the paper's 384-token tile and with a 128-token tile (the staged kernels, six and four
-    # pairs of waves in the dK/dV kernel), and with a 64-token 2D tile (the general kernels)
+    # head dimension 64 with the paper's 384-token tile, with a 128-token tile and with a 64-token 2D tile
     ("bwd-d64-p384", 64, (6, 16, 24), (6, 8, 8), [(1, 3, 3), (1, 1, 2)]),
     ("bwd-d64-p128", 64, (4, 16, 24), (2, 8, 8), [(3, 1, 3), (1, 3, 1)]),
     ("bwd-d64-p64-2d", 64, (1, 32, 40), (1, 8, 8), [(1, 3, 3), (1, 5, 1)]),
@@ -101,7 +100,7 @@ def test_backward_parity_whole(name, B, H, grid, tile, windows, scale):
     ("bwd-d128-p96", 128, (4, 12, 16), (2, 6, 8), [(1, 3, 1), (3, 3, 3)]),
 ])
 def test_backward_parity_general_shapes(name, D, grid, tile, windows):
-    """Head dimension 64 on both sets of kernels, and tiles of 32*k tokens, which go through the general kernels."""
+    """Head dimension 64, and tiles that are no multiple of 128 tokens."""
     w = syn.custom(name, 1, len(windows), D, grid, tile, windows, "bf16", seed=1210)
     q, k, v = syn.make_qkv(w)
     g = syn.make_dout(w)

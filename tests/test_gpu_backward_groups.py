@@ -1,8 +1,11 @@
 """GPU parity of the gradient kernels at the edges of their shapes: every number of waves per workgroup, one and more walk
 groups, shares of the walk that do not divide evenly or hold nothing."""
+import numpy as np
 import pytest
+import torch
 
 import synth_inputs as syn
+from oracle import sta_oracle as orc
 from tests.test_gpu_backward import assert_grad_parity, gpu_backward, oracle_backward
 
 pytestmark = pytest.mark.gpu
@@ -19,7 +22,7 @@ SHAPES = [
     ("p128-one", (4, 24, 24), (2, 8, 8), 1, 2, [(1, 1, 3), (1, 1, 1)]),         # 12 and 4
     ("p128-groups", (4, 24, 24), (2, 8, 8), 1, 2, [(2, 1, 3), (1, 3, 1)]),      # 24 and 12
     ("p160", (5, 8, 12), (5, 8, 4), 1, 2, [(1, 1, 3), (1, 1, 1)]),
-    ("p192-six", (3, 8, 216), (3, 8, 8), 1, 8, [(1, 1, 1), (1, 1, 2)]),         # 216 blocks of 192 keys: six pairs
+    ("p192", (3, 8, 216), (3, 8, 8), 1, 8, [(1, 1, 1), (1, 1, 2)]),             # three waves in dQ, two pairs in dK/dV
     # equal windows: rows of tiles over all heads, the longest boxes first
     ("rows-p64", (1, 72, 40), (1, 8, 8), 2, 3, [(1, 5, 3)]),
     ("rows-p128", (10, 16, 40), (2, 8, 8), 1, 2, [(3, 1, 4)]),
@@ -46,6 +49,9 @@ def test_gradient_kernel_shapes_match_the_oracle(name, grid, tile, B, H, windows
 SIX_PAIRS = [
     # eight rows of tiles per head and equal windows: the rows of all heads in turn
     ("six-rows", (12, 32, 32), 4, [(1, 3, 1)]),
+    # head after head: unequal windows, and equal ones with one row of tiles
+    ("six-mixed", (6, 8, 216), 4, [(1, 1, 1), (1, 1, 2)]),
+    ("six-one-row", (6, 8, 216), 4, [(1, 1, 4)]),
 ]
 
 
@@ -59,3 +65,24 @@ def test_six_pair_gradients_match_the_oracle(name, grid, H, windows):
         rq, rk, rv = oracle_backward(w, q, k, v, g, 0, h)
         for label, got, ref in (("dQ", dq, rq), ("dK", dk, rk), ("dV", dv, rv)):
             assert_grad_parity(got[0, h].float().numpy(), ref, "%s %s h%d" % (name, label, h))
+
+
+def test_six_pair_kept_set_read_from_dv():
+    """The transposed key-tile sets of the six-pair kernel, every head with its own window: with Q = 0 a kept key has the
+    probability 1 / (kept keys), so with dO one-hot in the query's tile dV_j[c] is 1 / (kept tiles of c) where c keeps j, else 0."""
+    windows = [(1, 3, 2), (2, 1, 3), (1, 1, 1), (3, 3, 1), (2, 2, 4)]
+    w = syn.custom("bwd-six-kept", 1, len(windows), 128, (12, 24, 32), (6, 8, 8), windows, "bf16", seed=1)      # 240 blocks
+    z = torch.zeros((1, w.H, w.N, 128), dtype=torch.bfloat16)
+    g = torch.zeros_like(z)
+    order = orc.tile_order(w.grid, w.tile)
+    tile_of_raster = np.empty(w.N, dtype=np.int64)
+    tile_of_raster[order] = np.repeat(np.arange(w.n_tiles), w.P)
+    g[0, :, torch.arange(w.N), torch.from_numpy(tile_of_raster)] = 1.0
+    (_, _, dv), _ = gpu_backward(w, z, z.clone(), torch.ones_like(z), g)
+    for h, window in enumerate(windows):
+        counts, lists = orc.key_tiles(w.grid, w.tile, orc.window_tiles_to_tokens(window, w.tile))
+        got = dv[0, h].float().numpy()[order].reshape(w.n_tiles, w.P, 128)
+        for j in range(w.n_tiles):
+            want = np.array([1.0 / counts[c] if j in lists[c][:counts[c]] else 0.0 for c in range(w.n_tiles)])
+            assert np.allclose(got[j][:, :w.n_tiles], want[None, :], rtol=2.0 ** -7, atol=0), (h, j)
+        assert (got[:, :, w.n_tiles:] == 0).all()

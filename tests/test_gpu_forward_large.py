@@ -1,6 +1,7 @@
 """GPU parity of the kernels that serve the large launches at head dimension 128 (tiles of 128 tokens' multiples, more than 1280
 waves of queries): 12 and 4 waves per workgroup, whole items and, with a workspace, items cut into parts along the keys.  Every
 other head holds the same data, so that the launches are large and the oracle's work is small."""
+import numpy as np
 import pytest
 import torch
 
@@ -55,3 +56,83 @@ def test_masked_keys_at_the_start_of_a_walk(name, channel):
     w = syn.custom("large-masked", 1, 2, 128, grid, tile, [(1, 2, 2), (3, 3, 3)], "bf16", seed=911)
     q, k, v = masked_inputs(w, channel)
     check(w, q, k, v, run(w, q, k, v, heads, workspace), name)
+
+
+@pytest.mark.parametrize("name", LAUNCHES)
+def test_items_are_done_again_where_scores_outgrow_the_first_offset(name):
+    """Scores that grow along the walk from near zero by more than 2^100 in the exponent: the row sums leave the safe range.  In a
+    split launch the parts restart where their share of the walk begins."""
+    grid, tile, heads, workspace = LAUNCHES[name]
+    w = syn.custom("large-outgrow", 1, 2, 128, grid, tile, [(1, 3, 3), (3, 3, 3)], "bf16", seed=84)
+    q, k, v = syn.make_qkv(w)
+    ramp = torch.empty(w.N)
+    ramp[torch.from_numpy(orc.tile_order(w.grid, w.tile))] = torch.linspace(0.02, 14.0, w.N)
+    k = (k.float() * ramp[None, None, :, None]).to(torch.bfloat16)
+    q = (q.float() * 2.0).to(torch.bfloat16)
+    check(w, q, k, v, run(w, q, k, v, heads, workspace), name)
+
+
+@pytest.mark.parametrize("name", LAUNCHES)
+def test_items_are_done_again_where_accumulators_leave_the_range(name):
+    """One tile's keys exceed all others by 2^79 as a factor, V is scaled by 2^50: row sums stay below 2^96, accumulators pass
+    2^128.  The result is 2^50 times that of the unscaled V."""
+    grid, tile, heads, workspace = LAUNCHES[name]
+    w = syn.custom("large-vhuge", 1, 2, 128, grid, tile, [(3, 3, 3), (1, 3, 3)], "bf16", seed=85)
+    _, _, v = syn.make_qkv(w)
+    order = torch.from_numpy(orc.tile_order(w.grid, w.tile))
+    q = torch.ones((1, 2, w.N, 128), dtype=torch.bfloat16)
+    k = torch.zeros_like(q)
+    k[:, :, order[(w.n_tiles - 1) * w.P:], :] = 4.875
+    out = run(w, q, k, (v.float() * 2.0 ** 50).to(torch.bfloat16), heads, workspace)
+    check(w, q, k, v, out.float() * 2.0 ** -50, name)
+
+
+@pytest.mark.parametrize("name", LAUNCHES)
+def test_all_scores_far_below_zero(name):
+    """The first offset has to move down from zero."""
+    grid, tile, heads, workspace = LAUNCHES[name]
+    w = syn.custom("large-negative", 1, 2, 128, grid, tile, [(1, 1, 2), (1, 2, 2)], "bf16", seed=83)
+    q, k, v = syn.make_qkv(w)
+    q = (q.float().abs() * 3.0).to(torch.bfloat16)
+    k = (-(k.float().abs()) * 3.0).to(torch.bfloat16)
+    check(w, q, k, v, run(w, q, k, v, heads, workspace), name)
+
+
+@pytest.mark.parametrize("name", LAUNCHES)
+def test_outputs_repeat_bit_for_bit(name):
+    grid, tile, heads, workspace = LAUNCHES[name]
+    w = syn.custom("large-repro", 1, 2, 128, grid, tile, [(1, 2, 3), (3, 3, 3)], "bf16", seed=81)
+    q, k, v = syn.make_qkv(w)
+    first = run(w, q, k, v, heads, workspace)
+    check(w, q, k, v, first, name)
+    for _ in range(3):
+        assert torch.equal(run(w, q, k, v, heads, workspace).view(torch.int16), first.view(torch.int16))
+
+
+@pytest.mark.parametrize("grid,tile,heads,workspace", [
+    ((12, 24, 32), (6, 8, 8), 16, False),          # 12 waves
+    ((12, 24, 32), (6, 8, 8), 16, True),           # ... 384 items, the last 128 in two parts
+    ((4, 24, 32), (2, 8, 8), 14, False),           # 4 waves
+    ((4, 24, 32), (2, 8, 8), 14, True),            # ... 336 items in two parts each
+], ids=["12-waves", "12-waves-parts", "4-waves", "4-waves-parts"])
+def test_kept_set_read_from_the_output(grid, tile, heads, workspace):
+    """Q = 0 and V one-hot in the key's tile: O[i, tau] = [tau kept] / kept tiles, every head with its own window."""
+    choices = [(1, 3, 3), (2, 1, 4), (2, 3, 4), (1, 2, 4), (3, 9, 9)]
+    windows = [choices[h % len(choices)] for h in range(heads)]
+    w = syn.custom("large-onehot", 1, heads, 128, grid, tile, windows, "bf16", seed=11)
+    q = torch.zeros((1, heads, w.N, 128), dtype=torch.bfloat16, device=DEV)
+    k = torch.randn(q.shape, generator=torch.Generator(device=DEV).manual_seed(11), device=DEV).to(torch.bfloat16)
+    v = torch.zeros_like(q)
+    v[:, :, torch.arange(w.N, device=DEV), torch.arange(w.N, device=DEV) // w.P] = 1.0
+    o = torch.full_like(q, float("nan"))
+    ws = torch.zeros(sta.sta_workspace_bytes(1, heads, 128, grid, tile), dtype=torch.uint8, device=DEV) if workspace else None
+    sta.sta_forward(q, k, v, o, grid, tile, windows, workspace=ws)
+    if workspace:
+        assert ws.any().item(), "no item was cut into parts"
+    out = o[0].float().cpu().numpy().reshape(heads, w.n_tiles, w.P, 128)
+    for h in range(heads):
+        counts, lists = orc.key_tiles(grid, tile, orc.window_tiles_to_tokens(windows[h], tile))
+        for qt in range(w.n_tiles):
+            want = np.zeros(128)
+            want[lists[qt, :counts[qt]]] = 1.0 / counts[qt]
+            assert np.allclose(out[h, qt], want[None, :], rtol=2.0 ** -7, atol=0), (h, qt)

@@ -199,8 +199,8 @@ def test_attention_running_max_keeps_growing(tile, grid):
 def test_attention_scores_outgrow_the_first_offset(tile, grid, D, windows):
     """The first keys of every window give scores near zero, later ones scores of many tens: an exponent offset
     that is set by the first sub-block and then left alone lets the row sums leave the range of fp32 (2^100 and
-    beyond).  The kernel has to notice and do such items again with offsets that follow the scores.  Every
-    shape of the DMA-staged kernels (384-, 128- and 64-token tiles, head dimension 128 and 64)."""
+    beyond).  The kernel has to notice and do such items again with offsets that follow the scores.  Small launches of
+    384-, 128- and 64-token tiles: the key-group kernel at both head dimensions."""
     w = syn.custom("outgrow", 1, 2, D, grid, tile, windows, "bf16", seed=84)
     q, k, v = syn.make_qkv(w)
     order = torch.from_numpy(orc.tile_order(w.grid, w.tile))
@@ -210,7 +210,7 @@ def test_attention_scores_outgrow_the_first_offset(tile, grid, D, windows):
     k = (k.float() * ramp[None, None, :, None]).to(torch.bfloat16)
     q = (q.float() * 2.0).to(torch.bfloat16)
     refs = [gu.oracle_rows(w, q, k, v, 0, h, None) for h in range(2)]
-    for workspace in (False, True):       # whole items, and (head dimension 128) items cut into parts along the keys
+    for workspace in (False, True):       # (these launches are small; items cut into parts: test_gpu_forward_large.py)
         out = gu.gpu_chain(w, q, k, v, workspace=workspace).float().numpy()
         assert np.isfinite(out).all()
         for h in range(2):
@@ -255,7 +255,7 @@ def test_attention_large_scores_stay_finite():
 def test_attention_all_scores_far_below_zero(tile, grid, D):
     """Every score of a row is a large negative number (positive queries, negative keys, a few hundred before
     scaling): an exponent offset that starts at zero and is not moved DOWN by the first keys makes every
-    probability underflow and the row sum zero.  All three kernel shapes."""
+    probability underflow and the row sum zero.  The key-group kernel (small launches)."""
     w = syn.custom("negscores", 1, 2, D, grid, tile, [(1, 1, 2), (1, 2, 2)], "bf16", seed=83)
     q, k, v = syn.make_qkv(w)
     q = (q.float().abs() * 3.0).to(torch.bfloat16)
@@ -279,7 +279,7 @@ def test_forward_is_bit_reproducible(tile, grid):
     sta.sta_tile_permute(kd, kt, w.grid, w.tile)
     sta.sta_tile_permute(vd, vt, w.grid, w.tile)
     ws = gu.forward_workspace(w, DEV)
-    for workspace in (None, ws):          # without and with work splitting below one query tile
+    for workspace in (None, ws):          # (small launches: the workspace is not used)
         outs = []
         for _ in range(4):
             o = torch.full_like(qt, float("nan"))
@@ -290,23 +290,23 @@ def test_forward_is_bit_reproducible(tile, grid):
             assert torch.equal(o.view(torch.int16), outs[0].view(torch.int16))
 
 
-@pytest.mark.parametrize("tile,grid,windows", [
-    ((6, 8, 8), (12, 24, 32), [(1, 3, 3), (3, 1, 2), (2, 3, 4)]),      # 12-wave kernel, 24 items per head
-    ((2, 8, 8), (4, 24, 32), [(2, 3, 4), (3, 3, 3), (2, 2, 2)]),       # 4-wave kernel; >= 8 kept tiles per head
+@pytest.mark.parametrize("tile,grid,windows,heads", [
+    ((6, 8, 8), (12, 24, 32), [(1, 3, 3), (3, 1, 2), (2, 3, 4)], 16),  # 12 waves: 384 items on 256 CUs, the last 128 in two parts
+    ((2, 8, 8), (4, 24, 32), [(2, 3, 4), (3, 3, 3), (2, 2, 2)], 14),   # 4 waves: 336 items, each in two parts; >= 8 kept tiles
 ])
-def test_split_items_match_whole_items_and_the_oracle(tile, grid, windows):
-    """With a workspace the last (here: all) work items are cut along the keys into parts whose partial results
-    a second kernel merges; the result must agree with the one-workgroup-per-item run to rounding and with the
+def test_split_items_match_whole_items_and_the_oracle(tile, grid, windows, heads):
+    """With a workspace the last work items are cut along the keys into parts whose partial results a second kernel
+    merges; the result must agree with the one-workgroup-per-item run of the same kernel to rounding and with the
     oracle to the usual tolerance.  A workspace that is too small is an error, not a silent fallback."""
-    w = syn.custom("split", 1, len(windows), 128, grid, tile, windows, "bf16", seed=4242)
+    w = syn.custom("split", 1, heads, 128, grid, tile, [windows[h % len(windows)] for h in range(heads)], "bf16", seed=4242)
     assert sta.sta_workspace_bytes(w.B, w.H, w.D, w.grid, w.tile) > 0
     q, k, v = syn.make_qkv(w)
     whole = gu.gpu_chain(w, q, k, v, workspace=False).float().numpy()
     split = gu.gpu_chain(w, q, k, v, workspace=True).float().numpy()
     assert np.isfinite(split).all()
     assert np.abs(split - whole).max() <= 2.0 ** -7 * np.abs(whole).max()      # both round the same value to bf16
-    assert (split != whole).any(), "the split path was not taken"
-    for h in range(w.H):
+    assert (split != whole).any(), "the split path was not taken"      # (the whole items of both runs have the same bits)
+    for h in (*range(len(windows)), heads - 1):
         ref = gu.oracle_rows(w, q, k, v, 0, h, None)
         gu.assert_parity(split[0, h], ref, "split h%d" % h)
     qd = q.to(DEV)
@@ -336,14 +336,15 @@ def test_full_window_equals_dense_attention_on_gpu():
 
 
 @pytest.mark.parametrize("D,grid,tile,workspace", [
-    (64, (4, 16, 16), (2, 4, 4), False),           # general kernel (32-token tiles), ascending walk
-    (64, (12, 24, 32), (6, 8, 8), False),          # 12-wave kernel at head dimension 64
-    (64, (1, 40, 48), (1, 8, 8), False),           # 2-wave kernel (64-token tiles), 30 tiles
-    (128, (12, 24, 32), (6, 8, 8), False),         # 12-wave kernel: residue-order walk of the box
-    (128, (12, 24, 32), (6, 8, 8), True),          # ... with items split along the keys
-    (128, (4, 24, 32), (2, 8, 8), False),          # 4-wave kernel
-    (128, (4, 24, 32), (2, 8, 8), True),
-    (128, (6, 40, 48), (6, 8, 8), False),          # 1x5x6 = 30 tiles: boxes that wrap along two axes
+    # the key-group kernel except where noted; the large launches' kernel in all its forms: test_gpu_forward_large.py
+    (64, (4, 16, 16), (2, 4, 4), False),           # 32-token tiles
+    (64, (12, 24, 32), (6, 8, 8), False),          # 384-token tiles, two key groups
+    (64, (1, 40, 48), (1, 8, 8), False),           # 64-token tiles, 30 of them, four key groups
+    (128, (12, 24, 32), (6, 8, 8), False),         # large launch: 4 waves
+    (128, (12, 24, 32), (6, 8, 8), True),          # ... whose items a workspace does not split
+    (128, (4, 24, 32), (2, 8, 8), False),          # 128-token tiles
+    (128, (4, 24, 32), (2, 8, 8), True),           # with a workspace: 4 waves
+    (128, (6, 40, 48), (6, 8, 8), False),          # large launch: 12 waves; 1x5x6 = 30 tiles: boxes that wrap along two axes
 ])
 def test_kept_set_read_from_gpu_output(D, grid, tile, workspace):
     """Q = 0 and V = one-hot(tile id): O[i, tau] = [tau kept] / kept(q tile), which reads the
@@ -435,7 +436,7 @@ def test_attention_parity_c5_mixed_windows_sampled():
 
 
 def test_attention_parity_head_dimension_64_full_size_sampled():
-    """The headline grid, tile and window at head dimension 64 (the 12-wave instance of the other attention kernel)."""
+    """The headline grid, tile and window at head dimension 64 (four waves of queries, two units per stage)."""
     _sampled_full_size("D64-3D", n_random=8, heads_with_full_tile=set(), heads=[0, 9, 17, 23], rows_per_stratum=8)
 
 
