@@ -75,15 +75,18 @@ int sta_untile(const void *src, void *dst, int src_dt, int dst_dt,
  * scores, softmax statistics and output accumulator, probabilities rounded
  * to bf16 before the PV product, output rounded to bf16.
  * Supported: D in {64, 128}; P a multiple of 32.  Anything else returns
- * STA_ERR_UNSUPPORTED.
+ * STA_ERR_UNSUPPORTED.  The fast kernels fetch K and V 16 bytes at a time:
+ * where these do not start at a multiple of 16 bytes, tiles that are no
+ * multiple of 64 (D = 64) or 128 tokens (D = 128) take a slower kernel that
+ * reads them from any address.
  * workspace: optional device scratch, 16-byte aligned, of at least
- * sta_workspace_bytes(...) bytes.  With it, the work items that would make up
- * the ragged last round of workgroups (the number of query tiles is rarely a
- * multiple of what the chip holds at once) are cut along the keys into parts
- * that fill the chip, each part leaving an unnormalised accumulator, exponent
- * offset and row sum there, and a second kernel merges them in a fixed order
- * (results stay repeatable bit for bit; they differ from the unsplit run by
- * rounding only).  NULL: every query tile is computed by one workgroup.  A
+ * sta_workspace_bytes(...) bytes.  With it, large launches at D = 128 may cut
+ * the work items that would make up the ragged last round of workgroups (the
+ * number of query tiles is rarely a multiple of what the chip holds at once)
+ * along the keys into parts that fill the chip, each part leaving an
+ * unnormalised accumulator, exponent offset and row sum there, and a second
+ * kernel merges them in a fixed order (results stay repeatable bit for bit;
+ * they differ from the unsplit run by rounding only).  NULL: no such parts.  A
  * non-NULL workspace that is too small or misaligned is STA_ERR_WORKSPACE; one
  * that overlaps a tensor is STA_ERR_ALIAS.  Its contents are undefined after
  * the call.
@@ -119,8 +122,9 @@ int sta_forward_lse(const void *q_tiled, const void *k_tiled, const void *v_tile
  * workspace: device, 16-byte aligned, at least sta_backward_workspace_bytes(B, H, grid) bytes
  * (two floats per query row), else STA_ERR_WORKSPACE.  lse_tiled must be 16-byte aligned as well
  * (the kernels read it four rows at a time), else STA_ERR_SHAPE.
- * Supported: D in {64, 128}; P a multiple of 32 (D = 128 with P a multiple of 128 takes the fast
- * kernels, everything else simple one-wave kernels); anything else returns STA_ERR_UNSUPPORTED.
+ * Supported: D in {64, 128}; P a multiple of 32; anything else returns STA_ERR_UNSUPPORTED.  Where q, k,
+ * v or d_o do not start at a multiple of 16 bytes, tiles that are no multiple of 128 tokens take a slower
+ * shape of the kernels that reads them from any address.
  */
 size_t sta_backward_workspace_bytes(int B, int H, const int grid[3]);
 int sta_backward(const void *q_tiled, const void *k_tiled, const void *v_tiled,

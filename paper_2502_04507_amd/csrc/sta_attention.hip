@@ -444,11 +444,14 @@ __device__ __forceinline__ GroupItem group_item_of(uint32_t id, const sta::FwdPa
 //
 // What bounds it.  Head dimension 64: a unit (32 keys) is 18 matrix instructions (288 cycles of the matrix pipe) next to 49
 // vector instructions, 16 of them exponentials; measured 350 cycles per wave and unit on 64-token image tiles with four
-// waves per SIMD.  30x48x80 grid, 24 heads, 384-token tiles, window 3x3x3: 7.00-7.15 ms with the 12-wave kernel on
-// v_mfma_f32_32x32x16_bf16 that was here before, 6.68-6.83 ms with QW = 4 (QW = 12: 7.5 ms, QW = 2: 7.3 ms; row sums by
-// v_dot2: 7.2 ms), 6.53 with two units per stage (UPS, 64 keys per barrier; 1120 TFLOP/s).  128 heads of a 64x64 image in 8x8 tiles, window 3x3:
-// 105-109 us before, 98-100 us.  Head dimension 128, 96-token tiles (10x30x56, 10 slices, windows 3x3x3 and 2x4x3): 2390 us
-// with the register-staged kernel that served it before, 299 us.
+// waves per SIMD.  Matrix pipe busy 63 % of the cycles on the 30x48x80 grid (24 heads, 384-token tiles, window 3x3x3), 39 % on
+// 128 heads of a 64x64 image in 8x8 tiles (18 units per item: a third of the launch remains without DMA and arithmetic), 13 % on
+// one head of 18x24x24 (162 workgroups); LDS bank conflicts only where the results leave (32 per wave and launch).
+// The grid: 6.97-7.15 ms with the 12-wave kernel on v_mfma_f32_32x32x16_bf16 that was here before, 6.68-6.83 with QW = 4
+// (QW = 12: 7.5, QW = 2: 7.3; row sums by v_dot2: 7.2), 6.53-6.63 with two units per stage (UPS, 64 keys per barrier).  The
+// images: 105-109 us before, 98-100.  Head dimension 128, 96-token tiles (10x30x56, 10 slices, windows 3x3x3 and 2x4x3): 2390 us
+// with the register-staged kernel that served it before, 294-299 us; its three-wave shapes spill (16 to 20 bytes of scratch at
+// the 168 registers that three waves per SIMD allow; with fewer fragments in flight they do not and are no faster, 291 us).
 // FOLLOW: the offset is the running maximum in every unit.  Otherwise it is the maximum of an item's first unit, and the
 // largest probabilities of a row are rounded to bf16 like any other; at the running maximum the largest is exactly 1 and has
 // no rounding error.  Against 64 bits (2-norm of the outputs, 96-token tiles, window 3x3x3, N(0,1)): 2.32e-3 with the fixed

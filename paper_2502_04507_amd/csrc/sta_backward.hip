@@ -213,7 +213,8 @@ constexpr int max_of(int a, int b) { return a > b ? a : b; }
 
 // ---------------------------------------------------------------------------------------------------------
 // dQ.  One workgroup of QW waves per 32 * QW queries (times G walk groups); a lane holds query column c16 of its wave's two
-// 16-query blocks.  At head dimension 128 206 registers, two waves per SIMD; at 64 128 and four (the
+// 16-query blocks.  At head dimension 128 211-212 registers, two waves per SIMD; at 64 128 and four (8 bytes of scratch in the
+// shape of three waves and two walk groups; the
 // statistic enters the exponent by a fused multiply-add instead of occupying eight registers of initial values, and the
 // transposed fragments are read two channel blocks at a time; three waves per SIMD before: 32 heads of a 64x64 image 42.7 ->
 // 37.7 us, 128 heads 165 -> 147, 12x48x48 x 4 156 -> 148, 30x48x80 x 24 9.11 -> 8.89 ms).  LDS stage: K (read by rows and
@@ -376,11 +377,12 @@ void sta_bwd_dq_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restric
 // workgroups of up to three pairs, rounded to bf16 and packed as the MFMA B operand (half the LDS traffic) in the larger
 // ones, which serve tiles of 128 tokens' multiples.  Four matrix products per block, no duplicate work inside the
 // kernel, and each wave keeps one accumulator set: at head dimension 128, per wave and 32-query sub-block 32 matrix
-// instructions, 40 vector instructions and 26 LDS reads in 158 registers, so that three waves per SIMD fit (six pairs:
-// 192 keys per workgroup); at head dimension 64 it is 106 registers and four waves per SIMD.
+// instructions, 40 vector instructions and 26 LDS reads in 165-168 registers, so that three waves per SIMD fit (six pairs:
+// 192 keys per workgroup); at head dimension 64 it is 110-118 registers and four waves per SIMD.
 // LDS stage: Q and dO (each read by rows and transposed) and the row statistics of the 32 queries.
 // What bounds it: the matrix pipe is busy 55 % of the cycles at head dimension 128 (30x48x80 grid, 24 heads, window 3x3x3:
-// 23.6 ms, 1200 TFLOP/s), at 64 the LDS reads take as long as the matrix instructions.  Tiles that are no multiple of 128
+// 24.0 ms, 1220 TFLOP/s); at 64 50 % of them, LDS 41 % (the same grid, 13.8-14.1 ms), on 64-token image tiles 26 and 27 %
+// (18 sub-blocks per item: two barriers each, and the item's fixed cost).  Tiles that are no multiple of 128
 // tokens went through one wave per workgroup with register-staged operands before (both kernels, the statistics included, in
 // us): 32 heads of a 64x64 image in 64-token tiles, window 3x3, head dimension 64 255 -> 92, 128 1060 -> 163; 10x30x56 in
 // 96-token tiles, window 3x3x3, ten slices, 128 5500 -> 763, 64 1180 -> 473; 9x40x40 in 192-token tiles, four heads of 128

@@ -71,16 +71,3 @@ STA_HD StaBox sta_key_tile_box_of(int nt, int nh, int nw, int wt, int wh, int ww
     b.w = sta_axis_range(nw, ww, qw);
     return b;
 }
-
-// Query tiles that keep key tile k_tile (a box as well, not symmetric to the key-tile box at the borders).
-STA_HD StaBox sta_query_tile_box_of(int nt, int nh, int nw, int wt, int wh, int ww, int k_tile)
-{
-    const int kw = k_tile % nw;
-    const int kh = (k_tile / nw) % nh;
-    const int kt = k_tile / (nw * nh);
-    StaBox b;
-    b.t = sta_axis_query_range(nt, wt, kt);
-    b.h = sta_axis_query_range(nh, wh, kh);
-    b.w = sta_axis_query_range(nw, ww, kw);
-    return b;
-}

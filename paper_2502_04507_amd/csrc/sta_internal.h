@@ -61,7 +61,7 @@ struct FwdParams {
 inline bool dma_aligned(const void *p) { return ((uintptr_t)p & 15) == 0; }
 
 // Division of any 32-bit number by a launch constant with one multiplication: n / d = (((n - q) >> pre) + q) >> post
-// with q = the upper half of n * magic.
+// with q = the upper half of n * magic (Granlund and Montgomery, Division by Invariant Integers using Multiplication, 1994).
 struct FastDiv {
     uint32_t d, magic;
     uint32_t pre, post;
@@ -77,8 +77,8 @@ inline FastDiv fast_div_of(uint32_t d)
     return f;
 }
 
-// How the work items of one forward launch are dealt to the workgroups, with everything a workgroup would otherwise have
-// to find by division (see fwd_item_of).
+// How the work items of one launch of the key-group forward kernel are dealt to the workgroups, with everything a workgroup
+// would otherwise have to find by division (see group_item_of).
 struct FwdPlan {
     uint32_t total;            // work items
     FastDiv chunk;             // consecutive items of one XCD
@@ -124,8 +124,6 @@ hipError_t static_mse_scratch(double **out);
 hipError_t launch_first_min(const float *losses, int n_patterns, int H, int32_t *best, hipStream_t stream);
 hipError_t launch_recall(const float *lse_window, const float *lse_full, int BH, size_t N, float *recall,
                          double *partial, float *mean_bh, hipStream_t stream);
-
-// 16 MFMAs per wave per iteration, 4 waves per workgroup; operands: 16 KB of bf16; sink: workgroups*256 floats.
 
 hipError_t launch_dump_key_tiles(const FwdParams &p, const WindowTable &win, int32_t *counts,
                                  int32_t *lists, hipStream_t stream);

@@ -158,9 +158,10 @@ hipError_t launch(const void *src, void *dst, bool src_f32, bool dst_f32, const 
     return hipGetLastError();
 }
 
-// Sources larger than the 256 MB Infinity Cache are read with streaming loads: nothing of them can still be there, and what
-// they would displace is the other tensors.  us, ordinary against streaming: 708 MB 248, 231 (to tiles) and 251, 237 (from
-// tiles); 85 MB 30.1, 29.3; but 17 MB, which is found in the cache, 6.2, 7.6.
+// Sources larger than the 256 MB Infinity Cache are read with streaming loads.  us, ordinary against streaming, source written
+// by the kernel before and, in brackets, another tensor of its size: 294 MB (fp32) 97, 85 (109, 78); 354 MB (bf16) 148, 120 (161,
+// 118); 708 MB 277, 240 (300, 235).  So they are the faster ones also where most of the source is still in the cache; below that
+// size they lose on a source that is there: 177 MB (fp32) 41, 55 (59, 50), 17 MB 6.2, 7.6.
 constexpr size_t kStreamAbove = (size_t)256 << 20;
 
 }  // namespace

@@ -8,7 +8,8 @@ SAME host tensors produced here.
 The paper measures on HunyuanVideo activations (latent grid 30x48x80, 24
 heads, head dim 128, bf16 -- Sec. 4 and the kernel benchmark table); those
 need trained weights, so i.i.d. N(0,1) tensors of the same shapes stand in.
-The kernel has no data-dependent control flow, so timing is unaffected.
+Timing depends on the data through the chip's power limit, and through second
+passes that such scores never need.
 """
 from dataclasses import dataclass, field
 from typing import List, Tuple

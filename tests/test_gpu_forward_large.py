@@ -136,3 +136,23 @@ def test_kept_set_read_from_the_output(grid, tile, heads, workspace):
             want = np.zeros(128)
             want[lists[qt, :counts[qt]]] = 1.0 / counts[qt]
             assert np.allclose(out[h, qt], want[None, :], rtol=2.0 ** -7, atol=0), (h, qt)
+
+
+@pytest.mark.parametrize("name", [n for n, launch in LAUNCHES.items() if not launch[3]])
+def test_log_denominators(name):
+    grid, tile, heads, _ = LAUNCHES[name]
+    w = syn.custom("large-lse", 1, 2, 128, grid, tile, [(1, 2, 3), (3, 3, 3)], "bf16", seed=82)
+    q, k, v = syn.make_qkv(w)
+    order = orc.tile_order(w.grid, w.tile)
+    index = torch.arange(heads) % 2
+    qt, kt, vt = (x[:, index][:, :, torch.from_numpy(order)].contiguous().to(DEV) for x in (q, k, v))
+    o = torch.full_like(qt, float("nan"))
+    lse = torch.full(qt.shape[:3], float("nan"), dtype=torch.float32, device=DEV)
+    sta.sta_forward_lse(qt, kt, vt, o, lse, w.grid, w.tile, [w.window_tiles[h % 2] for h in range(heads)])
+    check(w, q, k, v, o, name)
+    for h in range(2):
+        _, ref = orc.attention(q[0, h].float().numpy(), k[0, h].float().numpy(), v[0, h].float().numpy(), w.grid, w.tile,
+                               orc.window_tiles_to_tokens(w.window_tiles[h], w.tile), return_lse=True)
+        # bf16-rounded probabilities are summed: 2^-9 relative each, so below 2^-9 = 2e-3 in the log
+        for head in (h, heads - heads % 2 - 2 + h):
+            assert np.abs(lse[0, head].cpu().numpy() - ref[order]).max() <= 2e-3
