@@ -446,7 +446,7 @@ __device__ __forceinline__ GroupItem group_item_of(uint32_t id, const sta::FwdPa
 // vector instructions, 16 of them exponentials; measured 350 cycles per wave and unit on 64-token image tiles with four
 // waves per SIMD.  Matrix pipe busy 63 % of the cycles on the 30x48x80 grid (24 heads, 384-token tiles, window 3x3x3), 39 % on
 // 128 heads of a 64x64 image in 8x8 tiles (18 units per item: a third of the launch remains without DMA and arithmetic), 13 % on
-// one head of 18x24x24 (162 workgroups); LDS bank conflicts only where the results leave (32 per wave and launch).
+// one head of 18x24x24 (162 workgroups); LDS bank conflicts only where the results leave (16 to 64 per wave).
 // The grid: 6.97-7.15 ms with the 12-wave kernel on v_mfma_f32_32x32x16_bf16 that was here before, 6.68-6.83 with QW = 4
 // (QW = 12: 7.5, QW = 2: 7.3; row sums by v_dot2: 7.2), 6.53-6.63 with two units per stage (UPS, 64 keys per barrier).  The
 // images: 105-109 us before, 98-100.  Head dimension 128, 96-token tiles (10x30x56, 10 slices, windows 3x3x3 and 2x4x3): 2390 us
