@@ -49,6 +49,7 @@ struct BwdPlan {
     sta::FastDiv per_tile;     // blocks of one tile
     sta::FastDiv n_h, batch;
     uint32_t row_major;        // the same row of every (batch, head), then the next row; otherwise head after head
+    uint32_t longest_first;    // ... in the order of visit_order along t and h
     sta::FastDiv sub_per_tile; // 32-token sub-blocks of a tile
     float inv_scale;           // 1 / softmax scale
     struct Head {
@@ -78,8 +79,6 @@ struct BwdItem {
     size_t bh;
     StaBox box;
 };
-// (The order of the visits matters to the keys' boxes only, those of the queries are equally long; and it pays where rows of
-// all heads are visited together, head after head it costs locality: 12x48x48, twelve heads 1153 against 1058 us.)
 template <bool QUERY_COLS>
 __device__ __forceinline__ BwdItem bwd_item_of(uint32_t id, const sta::FwdParams &p, const BwdPlan &plan)
 {
@@ -101,7 +100,7 @@ __device__ __forceinline__ BwdItem bwd_item_of(uint32_t id, const sta::FwdParams
     const uint32_t head_rank = fast_div(rank, plan.batch);          // batch entries of one head are adjacent
     const BwdPlan::Head head = plan.head[head_rank];
     it.bh = (size_t)(rank - head_rank * plan.batch.d) * p.H + p.head_base + head.h;
-    uint32_t w = fast_div(pos, plan.per_tile);
+    const uint32_t w = fast_div(pos, plan.per_tile);
     const uint32_t sub = pos - w * plan.per_tile.d;
     uint32_t t = fast_div(row, plan.n_h), h = row - t * plan.n_h.d;
     if constexpr (QUERY_COLS) {
@@ -109,10 +108,9 @@ __device__ __forceinline__ BwdItem bwd_item_of(uint32_t id, const sta::FwdParams
         it.box.h = sta_axis_range(p.n_h, head.w[1], h);
         it.box.w = sta_axis_range(p.n_w, head.w[2], w);
     } else {
-        if (plan.row_major) {
+        if (plan.longest_first) {
             t = visit_order(p.n_t, head.w[0], t);
             h = visit_order(p.n_h, head.w[1], h);
-            w = visit_order(p.n_w, head.w[2], w);
         }
         it.box.t = sta_axis_query_range(p.n_t, head.w[0], t);
         it.box.h = sta_axis_query_range(p.n_h, head.w[1], h);
@@ -634,7 +632,7 @@ uint32_t longest_walk(const BwdArgs &a) { return walk_of_rank(a, 0); }
 // One chunk = the column blocks of one row of tiles along w.  Measured at the 30x48x80 grid (chunk sizes 1, 3,
 // 6, 30, 60, 120 in one session): dK/dV kernel 32.7, 31.5, 31.6, 31.0, 31.1, 34.0 ms; dQ kernel 18.9, 18.8, 18.7,
 // 18.5, 18.5, 19.3 ms.  Launches of fewer than eight such rows are cut evenly, so that every XCD gets its share.
-BwdPlan make_plan(const BwdArgs &a, uint32_t cols, bool row_major, uint32_t *ids)
+BwdPlan make_plan(const BwdArgs &a, uint32_t cols, bool row_major, bool longest_first, uint32_t *ids)
 {
     const sta::FwdParams &p = a.p;
     BwdPlan plan;
@@ -645,6 +643,7 @@ BwdPlan make_plan(const BwdArgs &a, uint32_t cols, bool row_major, uint32_t *ids
     plan.rows = sta::fast_div_of(p.n_t * p.n_h);
     plan.slices = sta::fast_div_of((uint32_t)a.B * p.heads);
     plan.row_major = row_major;
+    plan.longest_first = longest_first;
     if (chunk > (plan.total + 7) / 8) chunk = (plan.total + 7) / 8;
     plan.chunk = sta::fast_div_of(chunk);
     plan.per_tile = sta::fast_div_of(per_tile);
@@ -666,7 +665,7 @@ template <int D, int QW, int G, bool DMA = true>
 hipError_t launch_dq(const BwdArgs &a)
 {
     uint32_t ids;
-    const BwdPlan plan = make_plan(a, QW * 32, false, &ids);
+    const BwdPlan plan = make_plan(a, QW * 32, false, false, &ids);
     sta_bwd_dq_kernel<D, QW, G, DMA><<<dim3(ids), dim3(QW * G * 64), 0, a.stream>>>(a.q, a.k, a.v, a.o, a.d_o, a.lse, a.neg_delta, a.neg_lse,
                                                                               a.d_q, a.p, plan);
     return hipGetLastError();
@@ -674,39 +673,41 @@ hipError_t launch_dq(const BwdArgs &a)
 
 // Order of the dK/dV items where all heads' walks are equal (otherwise head after head: heads of long walks must not have rows
 // left at the end; 16x48x64 in 256-token tiles, 3x3x3 and 3x3x5 2046 us head after head, 2377 row after row; 30x48x80, windows
-// from 1x3x3 to the whole grid 17.5, 26.6 ms).  Entry point, head after head against row after row:
+// from 1x3x3 to the whole grid 17.5, 26.6 ms).  Entry point, head after head against the rows of all heads in turn:
 // - Rows of tiles per head a multiple of eight: head after head an XCD gets the same rows of every head, and border rows have
-//   half the work of inner ones.  16x48x64 in 256-token tiles, 24 heads, head dimension 64 7469, 6586 us, 128 13,994, 12,486;
-//   24x64x64 in 384-token tiles 128 40.8, 35.2 ms; 20x64x64 in 64-token tiles 3986, 3258.  A single head is the exception, it
-//   has no other head's rows to take in turn: 16x48x64 425, 475.
-// - Otherwise the rows of all heads in turn, longest first, shorten the tail, which tells in launches of up to about sixteen
-//   rounds of workgroups (18x40x64 in 192-token tiles, 16 heads 3564, 3310 us; 10x30x56 in 96-token tiles 529, 472; 30x48x80
-//   in 384-token tiles, head dimension 64, three heads 3042, 2936, eight 7565, 7511).  Beyond that what counts is that the next row
-//   of a head finds operands of this one in the caches: its box of Q and dO rows either fits an XCD's L2 (20x48x64 in
-//   128-token tiles, 40 heads 7295, 7194) or the rows of a head should stay together (30x48x80, 24 heads 21.98, 22.17 ms,
-//   twelve 11.30, 11.66).  A single head: only where all its workgroups are resident at once (20x48x64 in 128-token tiles
-//   288, 267 us; 30x48x80 1144, 1171).
-// - Six pairs, one workgroup per CU, stay head after head except in the first case: 12x48x48, six heads 917, 940 us; 30x48x80,
-//   24 heads 40.3, 41.3 ms.
-bool rows_of_all_heads(const BwdArgs &a, uint32_t cols, uint64_t resident, bool six_pairs)
+//   half the work of inner ones.  16x48x64 in 256-token tiles, 24 heads, head dimension 64 7443, 6488 us, 128 -12 %; 24x64x64 in
+//   384-token tiles 128 (six pairs) -16 %; 20x64x64 in 64-token tiles -19 %, four images -20 %.
+// - Otherwise it shortens the tail, which tells in launches of up to about sixteen rounds of workgroups (18x40x64 in 192-token
+//   tiles, 16 heads -7 %; 10x30x56 in 96-token tiles -11 %; 30x48x80 in 384-token tiles, two heads -9 %, four -5 %; six pairs,
+//   12x48x48, six heads -5 %).  Beyond that what counts is that the next row of a head finds operands of this one in the
+//   caches: its box of Q and dO rows either fits an XCD's L2 (20x48x64 in 128-token tiles, head dimension 64, 40 heads -1 %;
+//   12x48x48, 48 heads of 128 -3 %) or the rows of a head should stay together (30x48x80, head dimension 64, 12 to 24 heads
+//   +0.4 to +1.5 %; 128 +1 %).
+// - Not where every workgroup has a CU of its own and no order can even anything out (24x32x32, two heads of 128 +3 to +4 %).
+bool rows_of_all_heads(const BwdArgs &a, uint32_t cols, uint64_t resident)
 {
     const sta::FwdParams &p = a.p;
     const uint64_t slices = (uint64_t)a.B * p.heads;
+    const uint64_t blocks = slices * (p.N / cols);
     if (walk_of_rank(a, 0) != walk_of_rank(a, p.heads - 1)) return false;
-    if (p.n_t * p.n_h % 8 == 0) return slices > 1;
-    if (six_pairs) return false;
-    if (slices == 1) return p.N / cols <= resident;
+    if (resident <= sta::compute_units() && blocks <= resident) return false;
     const uint32_t kept_w = 2 * (a.win.w[a.order.h[0]][2] / 2u) + 1;
     const uint64_t box_rows = (uint64_t)longest_walk(a) * kSub / (kept_w < p.n_w ? kept_w : p.n_w) * p.n_w;
-    return slices * (p.N / cols) <= 16 * resident || box_rows * a.D * 4 <= (4u << 20);
+    return p.n_t * p.n_h % 8 == 0 || blocks <= 16 * resident || box_rows * a.D * 4 <= (4u << 20);
 }
 
+// The longest rows first on tiles of 96 tokens' multiples (workgroups that a CU holds few of: 10x30x56, us, rows as they come
+// and longest first: three heads 371, 341, five 439, 421; 192-token tiles, eight heads of 128 3057, 2947).  Not elsewhere: few
+// heads are then dealt unevenly (16x48x64, four heads -15 % as they come, -12 %; 30x48x80, two -9, -3 %), and not along w: every
+// fourth item of an XCD goes to the same part of it, and a row of eight tiles at window 4 would put the long ones there (20x12x64
+// in 128-token tiles, five heads 761, 957 us).
 template <int D, int NPAIR, int G, bool DMA = true>
 hipError_t launch_dkv(const BwdArgs &a)
 {
     uint32_t ids;
     const uint64_t resident = (uint64_t)sta::compute_units() * (D == 64 ? 16 : 12) / (2 * NPAIR * G);     // workgroups
-    const BwdPlan plan = make_plan(a, NPAIR * 32, rows_of_all_heads(a, NPAIR * 32, resident, NPAIR == 6), &ids);
+    const bool row_major = rows_of_all_heads(a, NPAIR * 32, resident), longest_first = a.p.P % 96 == 0 && a.p.P % 128 != 0;
+    const BwdPlan plan = make_plan(a, NPAIR * 32, row_major, row_major && longest_first, &ids);
     sta_bwd_dkv_kernel<D, NPAIR, G, DMA><<<dim3(ids), dim3(NPAIR * G * 128), 0, a.stream>>>(a.q, a.k, a.v, a.d_o, a.neg_lse, a.neg_delta,
                                                                                       a.d_k, a.d_v, a.p, plan);
     return hipGetLastError();

@@ -23,7 +23,7 @@ SHAPES = [
     ("p128-groups", (4, 24, 24), (2, 8, 8), 1, 2, [(2, 1, 3), (1, 3, 1)]),      # 24 and 12
     ("p160", (5, 8, 12), (5, 8, 4), 1, 2, [(1, 1, 3), (1, 1, 1)]),
     ("p192", (3, 8, 216), (3, 8, 8), 1, 8, [(1, 1, 1), (1, 1, 2)]),             # three waves in dQ, two pairs in dK/dV
-    # equal windows: rows of tiles over all heads, the longest boxes first
+    # equal windows: rows of tiles over all heads, on the 96-token tiles the longest boxes first
     ("rows-p64", (1, 72, 40), (1, 8, 8), 2, 3, [(1, 5, 3)]),
     ("rows-p128", (10, 16, 40), (2, 8, 8), 1, 2, [(3, 1, 4)]),
     ("rows-p96", (6, 30, 8), (2, 6, 8), 1, 2, [(1, 3, 1)]),
@@ -47,11 +47,11 @@ def test_gradient_kernel_shapes_match_the_oracle(name, grid, tile, B, H, windows
 
 # Launches that fill the chip with six pairs (384-token tiles, at least 205 column blocks of 192 keys on 256 CUs), whole heads.
 SIX_PAIRS = [
-    # eight rows of tiles per head and equal windows: the rows of all heads in turn
-    ("six-rows", (12, 32, 32), 4, [(1, 3, 1)]),
-    # head after head: unequal windows, and equal ones with one row of tiles
+    # equal windows and two rounds: the rows of all heads in turn
+    ("six-rows", (12, 32, 32), 8, [(1, 3, 1)]),
+    # head after head: unequal windows, and equal ones in one round
     ("six-mixed", (6, 8, 216), 4, [(1, 1, 1), (1, 1, 2)]),
-    ("six-one-row", (6, 8, 216), 4, [(1, 1, 4)]),
+    ("six-one-round", (6, 8, 216), 4, [(1, 1, 4)]),
 ]
 
 
