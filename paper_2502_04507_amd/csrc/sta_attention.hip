@@ -1477,16 +1477,20 @@ hipError_t launch_group_count(int groups, const void *q, const void *k, const vo
     return launch_group<D, QW, 1, WPE, FOLLOW>(q, k, v, o, B, p, win, order, stream);
 }
 
-// Units (32 keys) of the longest walk of a launch: that of the head with the most key tiles.
-uint32_t longest_walk(const sta::FwdParams &p, const sta::WindowTable &win, const sta::HeadOrder &order)
+// Units (32 keys) of the walk of a head of the launch; heads by rank, the one with the most key tiles first.
+uint32_t walk_of_rank(const sta::FwdParams &p, const sta::WindowTable &win, const sta::HeadOrder &order, uint32_t rank)
 {
     uint32_t units = p.P / kSub;
     const uint32_t n[3] = {p.n_t, p.n_h, p.n_w};
     for (int a = 0; a < 3; ++a) {
-        const uint32_t kept = 2 * (win.w[order.h[0]][a] / 2u) + 1;
+        const uint32_t kept = 2 * (win.w[order.h[rank]][a] / 2u) + 1;
         units *= kept < n[a] ? kept : n[a];
     }
     return units;
+}
+uint32_t longest_walk(const sta::FwdParams &p, const sta::WindowTable &win, const sta::HeadOrder &order)
+{
+    return walk_of_rank(p, win, order, 0);
 }
 
 // Shape of the key-group kernel for a launch.
@@ -1499,7 +1503,10 @@ uint32_t longest_walk(const sta::FwdParams &p, const sta::WindowTable &win, cons
 // 384-token tiles, us, one and two units: three heads 85, 83; six 162, 157; twelve 289, 283).  With two waves or with groups the
 // larger stages or the registers cost a wave per SIMD (twelve heads, two groups 305, 362).
 // Key groups: the most, of 1, 2 and 4, with which the launch still fits the chip at once (16 waves per CU at head dimension
-// 64, 8 at 128) and a group has at least eight units to walk.  Measured around the line (us; 1, 2, 4 groups), head dimension
+// 64, 8 at 128) and a group has at least eight units to walk.  Where the longest walk is 64 units or more, heads count by their
+// walks, because it is the long ones that leave the chip idle (six heads of a 128x112 image, two of them over all of it, 242 us
+// counted by heads, 153 by walks; 9x40x40, 1x3x3, 3x5x5 and 1x1x3, six heads 245, 156; but 27 of a 32x48 image, 8 to 48 units,
+// 17.9, 20.8).  Measured around the line (us; 1, 2, 4 groups), head dimension
 // 64, 384-token tiles, 108 units: 324 waves of queries 45, 28, 24; 972 waves 62, 40, 38; 1944 waves 69, 66, 71; 2592 waves
 // 89, 94, 101.  64-token tiles, 18 units: 1024 waves 15.1, 12.6, 14.1; 2048 waves 17.3, 17.4, 22.9; 4096 waves 27.5, 30.1, 42.4.
 // Head dimension 128, 96-token tiles, about 75 units: 525 waves 50, 39, 34; 1050 waves 68, 78, 69.
@@ -1507,8 +1514,14 @@ template <int D>
 hipError_t launch_groups(const void *q, const void *k, const void *v, void *o, int B, const sta::FwdParams &p,
                          const sta::WindowTable &win, const sta::HeadOrder &order, hipStream_t stream)
 {
-    const uint64_t waves = (uint64_t)B * p.heads * (p.N / 32);
     const uint32_t units = longest_walk(p, win, order);
+    uint64_t heads = p.heads;
+    if (units >= 64) {
+        uint64_t all_units = 0;
+        for (uint32_t r = 0; r < p.heads; ++r) all_units += walk_of_rank(p, win, order, r);
+        heads = (all_units + units - 1) / units;
+    }
+    const uint64_t waves = (uint64_t)B * heads * (p.N / 32);
     const uint64_t fits = (uint64_t)resident_workgroups(1) * (D == 64 ? 16 : 8);
     const int groups = 4 * waves <= fits && units >= 32 ? 4 : 2 * waves <= fits && units >= 16 ? 2 : 1;
     const uint64_t cus = resident_workgroups(1);
