@@ -431,7 +431,7 @@ __device__ __forceinline__ GroupItem group_item_of(uint32_t id, const sta::FwdPa
 
 // ---------------------------------------------------------------------------
 // The key-group kernel: head dimension 64 at every tile size, head dimension 128 where the tile is not a multiple of 128
-// tokens.  A workgroup is QW waves of 32 queries (one query block) times KG key groups: the groups share the queries and
+// tokens and in small launches of those that are.  A workgroup is QW waves of 32 queries (one query block) times KG key groups: the groups share the queries and
 // take one KG-th of the walk each, with LDS stages of their own, and their partial results are merged through LDS at the
 // end.  KG = 1 where the launch fills the chip; KG = 2 or 4 makes more waves of few queries, for launches that would leave
 // it idle.
