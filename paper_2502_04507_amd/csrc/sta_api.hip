@@ -318,8 +318,12 @@ size_t sta_head_mse_workspace_bytes(int B, int H)
     return (size_t)B * (size_t)H * sta::kMseSlices * sizeof(double);
 }
 
-int sta_head_mse(const void *a, const void *b, int B, int H, int D, const int grid[3], void *workspace,
-                 size_t workspace_bytes, float *dev_mse, void *hip_stream)
+}  // extern "C"
+
+namespace {
+
+int head_mse_common(const void *a, const void *b, int B, int H, int D, const int grid[3], void *workspace,
+                    size_t workspace_bytes, float *dev_mse, int n_before, int32_t *dev_best, void *hip_stream)
 {
     if (!a || !b || !dev_mse) return STA_ERR_NULL;
     const int unit[3] = {1, 1, 1};
@@ -328,9 +332,19 @@ int sta_head_mse(const void *a, const void *b, int B, int H, int D, const int gr
     if (D % 8 != 0) return STA_ERR_UNSUPPORTED;
     if (!workspace || workspace_bytes < sta_head_mse_workspace_bytes(B, H)) return STA_ERR_WORKSPACE;
     if (((uintptr_t)workspace & 7) != 0) return STA_ERR_WORKSPACE;
-    hipError_t e = sta::launch_head_mse(a, b, B, H, (size_t)s.N * D, static_cast<double *>(workspace), dev_mse,
-                                        static_cast<hipStream_t>(hip_stream));
+    hipError_t e = sta::launch_head_mse(a, b, B, H, (size_t)s.N * D, static_cast<double *>(workspace), dev_mse, n_before,
+                                        dev_best, static_cast<hipStream_t>(hip_stream));
     return e == hipSuccess ? STA_OK : STA_ERR_HIP;
+}
+
+}  // namespace
+
+extern "C" {
+
+int sta_head_mse(const void *a, const void *b, int B, int H, int D, const int grid[3], void *workspace,
+                 size_t workspace_bytes, float *dev_mse, void *hip_stream)
+{
+    return head_mse_common(a, b, B, H, D, grid, workspace, workspace_bytes, dev_mse, 0, nullptr, hip_stream);
 }
 
 int sta_head_mse_static(const void *a, const void *b, int B, int H, int D, const int grid[3], float *dev_mse,
@@ -344,7 +358,7 @@ int sta_head_mse_static(const void *a, const void *b, int B, int H, int D, const
     if ((int64_t)B * H > sta::kStaticMseMaxSlabs) return STA_ERR_WORKSPACE;
     double *partial = nullptr;
     if (sta::static_mse_scratch(&partial) != hipSuccess) return STA_ERR_HIP;
-    hipError_t e = sta::launch_head_mse(a, b, B, H, (size_t)s.N * D, partial, dev_mse,
+    hipError_t e = sta::launch_head_mse(a, b, B, H, (size_t)s.N * D, partial, dev_mse, 0, nullptr,
                                         static_cast<hipStream_t>(hip_stream));
     return e == hipSuccess ? STA_OK : STA_ERR_HIP;
 }
@@ -394,12 +408,11 @@ int sta_mask_search(const void *q_tiled, const void *k_tiled, const void *v_tile
         if (int rc = forward_common(q_tiled, k_tiled, v_tiled, o_pattern, nullptr, B, H, D, grid, tile, win, scale,
                                     nullptr, 0, hip_stream))
             return rc;
-        if (int rc = sta_head_mse(o_full, o_pattern, B, H, D, grid, workspace, workspace_bytes,
-                                  dev_losses + (size_t)p * H, hip_stream))
+        if (int rc = head_mse_common(o_full, o_pattern, B, H, D, grid, workspace, workspace_bytes, dev_losses + (size_t)p * H,
+                                     p, p + 1 == n_patterns ? dev_best : nullptr, hip_stream))
             return rc;
     }
-    hipError_t e = sta::launch_first_min(dev_losses, n_patterns, H, dev_best, static_cast<hipStream_t>(hip_stream));
-    return e == hipSuccess ? STA_OK : STA_ERR_HIP;
+    return STA_OK;
 }
 
 int sta_key_tile_box(const int grid_tiles[3], const int window_tiles[3], const int q_tile[3], int lo[3], int hi[3])
