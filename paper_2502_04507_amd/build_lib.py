@@ -22,6 +22,10 @@ FLAGS = [
     # no NaN is ever produced inside the kernels (the only infinities are the initial running maxima, which meet
     # finite values only); saying so lets max chains compile to v_max3_f32 without per-operand canonicalisation
     "-fno-honor-nans",
+    # matrix instructions accumulate in vector registers everywhere.  Left to itself the compiler moves the accumulators of
+    # kernels whose LDS allows one wave per SIMD into accumulation registers and copies them to scale or test them (40 heads of
+    # 64x96 in 32-token tiles, head dimension 128: forward 118 -> 97 us, gradients 232 -> 221)
+    "-mllvm", "-amdgpu-mfma-vgpr-form=1",
 ]
 
 

@@ -698,7 +698,7 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
         auto next_stage = [&]() __attribute__((always_inline)) {
             // this wave's DMA for the stage must have landed, and everyone's; the other stage is free again
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            __builtin_amdgcn_s_barrier();
+            if constexpr (QW > 1) __builtin_amdgcn_s_barrier();          // the stages of a single wave are its own
             asm volatile("" ::: "memory");
             issue_next();
         };
