@@ -12,9 +12,10 @@
 //   sta_bwd_dq_kernel     one workgroup per query block, walks the key tiles of its window (as the forward
 //                         kernel does): 3 MFMA products per block (K Q^T, V dO^T, K^T dS^T); it also forms
 //                         -delta_i and -lse_i / scale of its queries and leaves them for the second kernel;
-//   sta_bwd_dkv_kernel    one workgroup per key block, walks the QUERY tiles that keep its key tile (the
-//                         transposed box): 4 MFMA products per block (Q K^T, dO V^T, dO^T P, Q^T dS), split
-//                         over pairs of waves.
+//   sta_bwd_dkv_kernel    one wave per 32 keys, walks the QUERY tiles that keep its key tile (the
+//                         transposed box): 4 MFMA products per block (Q K^T, dO V^T, dO^T P, Q^T dS);
+//   sta_bwd_dkv_pair_kernel   the same with the products split over pairs of waves (head dimension 128 on
+//                         tiles that are no multiple of 64 tokens).
 // S and dP are thus computed twice (7 products against the 5 of a single-pass scheme with atomics on dQ).
 //
 // Same MFMA formulation as the forward kernel (v_mfma_f32_16x16x32_bf16, the shape that costs the least energy per
@@ -24,8 +25,9 @@
 // global_load_lds; an operand may be read both by rows (A rows = tokens, 16-byte reads) and transposed (A rows =
 // channels, ds_read_b64_tr_b16), and one LDS layout serves both without bank conflicts (described where the two
 // products are defined).
-// Both kernels: head dimension 64 or 128, any tile of a multiple of 32 tokens.  A workgroup's columns are the largest of
-// a few sizes that divides the tile; launches too small for the chip are cut into walk groups (see WalkShare).
+// All kernels: any tile of a multiple of 32 tokens.  A workgroup's columns are the largest of a few sizes that divides the
+// tile; launches too small for the chip are cut into walk groups (see WalkShare), the smallest ones into four groups of one
+// wave each, which has its LDS to itself and passes no barrier until the groups are summed.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -172,6 +174,42 @@ __device__ __forceinline__ void merge_groups(char *smem, int group, int wave, in
     __syncthreads();
 }
 
+// The same for groups of one wave each, all of them at work: every wave leaves its accumulators in its own part of LDS
+// (REGION bytes apart), sums the groups' parts of its share of the 16x16 blocks in ascending order and puts the result,
+// scaled and rounded, where the rows are assembled; then the rows leave 16 bytes per lane.  DMA into the regions is over.
+template <int D, int G, int REGION>
+__device__ __forceinline__ void merge_waves(char *smem, char *rows, int group, int lane, const floatx4 (&acc)[D / 16][2], float mul)
+{
+    constexpr int RowB = 2 * D, BLOCKS = D / 16 * 2, SHARE = BLOCKS / G;
+    static_assert(BLOCKS % G == 0 && BLOCKS * 1024 <= REGION, "a wave's accumulators fit its region");
+    const int c16 = lane & 15, g4 = lane >> 4;
+#pragma unroll
+    for (int b = 0; b < BLOCKS; ++b) *reinterpret_cast<floatx4 *>(smem + group * REGION + b * 1024 + lane * 16) = acc[b / 2][b % 2];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < SHARE; ++j) {
+        const int b = group * SHARE + j;
+        floatx4 sum = *reinterpret_cast<const floatx4 *>(smem + b * 1024 + lane * 16);
+#pragma unroll
+        for (int g = 1; g < G; ++g) sum += *reinterpret_cast<const floatx4 *>(smem + g * REGION + b * 1024 + lane * 16);
+        bf16x4 ov;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) ov[t] = static_cast<__bf16>(sum[t] * mul);
+        *reinterpret_cast<bf16x4 *>(rows + (16 * (b % 2) + c16) * RowB + (16 * (b / 2) + 4 * g4) * 2) = ov;
+    }
+    __syncthreads();
+}
+template <int D, int THREADS>
+__device__ __forceinline__ void store_rows(const char *rows, bf16_raw *dst, int tid)
+{
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+#pragma unroll
+    for (int i = 0; i < 32 * 2 * D; i += THREADS * 16)
+        if (i + tid * 16 < 32 * 2 * D)
+            __builtin_nontemporal_store(*reinterpret_cast<const u32x4 *>(rows + i + tid * 16),
+                                        reinterpret_cast<u32x4 *>(reinterpret_cast<char *>(dst) + i + tid * 16));
+}
+
 // A wave's 32 result rows (columns of its accumulators), scaled, rounded to bf16 and written as whole rows, 1 KB contiguous
 // per store instruction, through a part of LDS that belongs to the wave (16 rows at a time).
 template <int D>
@@ -202,12 +240,14 @@ __device__ __forceinline__ void store_columns(char *wave_lds, const floatx4 (&ac
     }
 }
 
-__device__ __forceinline__ void lds_write_b128(uint32_t addr, bf16x8 v)
-{
-    asm volatile("ds_write_b128 %0, %1" ::"v"(addr), "v"(v) : "memory");
-}
-
 constexpr int max_of(int a, int b) { return a > b ? a : b; }
+
+// Waits until at most PENDING of the wave's own requests are outstanding (they complete in order).
+template <int PENDING>
+__device__ __forceinline__ void wait_dma()
+{
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PENDING) : "memory");
+}
 
 // ---------------------------------------------------------------------------------------------------------
 // dQ.  One workgroup of QW waves per 32 * QW queries (times G walk groups); a lane holds query column c16 of its wave's two
@@ -240,7 +280,8 @@ void sta_bwd_dq_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restric
     constexpr int OPS = 2 * L::Groups;                  // DMA instructions per sub-block
     constexpr int WAVE_OPS = (OPS + QW - 1) / QW;       // at most this many per wave
     constexpr int WAVE_OUT = 16 * L::RowB;
-    constexpr int SMEM = max_of(G * GROUP_B, max_of((G / 2) * QW * CB * 2 * 1024, QW * WAVE_OUT));
+    constexpr int SMEM = QW == 1 && G > 1 ? G * GROUP_B + 32 * L::RowB
+                                          : max_of(G * GROUP_B, max_of((G / 2) * QW * CB * 2 * 1024, QW * WAVE_OUT));
     __shared__ __attribute__((aligned(1024))) char smem[SMEM];
 
     const BwdItem item = bwd_item_of<true>(blockIdx.x, p, plan);
@@ -325,7 +366,8 @@ void sta_bwd_dq_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restric
     auto sub_block = [&](auto stage_c, int unit) __attribute__((always_inline)) {
         constexpr int ST = decltype(stage_c)::value * STAGE_B;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
+        // (the stages of a single wave are its own; operands staged by plain stores have to be waited for)
+        if constexpr (QW > 1 || !DMA) __syncthreads();
         issue_next();
         if (G > 1 && unit >= share.n_units) return;
         floatx4 S[2][2], dP[2][2];                      // [key block][query block]
@@ -359,7 +401,12 @@ void sta_bwd_dq_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restric
         sub_block(std::integral_constant<int, 0>{}, u);
         if (u + 1 < share.n_steps) sub_block(std::integral_constant<int, 1>{}, u + 1);
     }
-    if constexpr (G > 1) {
+    if constexpr (QW == 1 && G > 1) {
+        char *rows = smem + G * GROUP_B;
+        merge_waves<D, G, GROUP_B>(smem, rows, group, lane, dQ, c * kLn2);
+        store_rows<D, G * 64>(rows, d_q + my_row * D, tid);
+        return;
+    } else if constexpr (G > 1) {
         merge_groups<G, QW>(smem, group, qw, lane, dQ);
         if (group != 0) return;
     } else {
@@ -369,26 +416,29 @@ void sta_bwd_dq_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restric
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// dK, dV.  One workgroup of 2 * NPAIR waves per 32 * NPAIR keys (times G walk groups).  Each 32-key column block is served
-// by a PAIR of waves: the first holds K and accumulates dV (S = Q K^T, P, dV^T += dO^T P), the second holds V and accumulates
-// dK (dP = dO V^T, dS = P o (dP - delta), dK^T += Q^T dS).  P goes from the first to the second through LDS: in fp32 in
-// workgroups of up to three pairs, rounded to bf16 and packed as the MFMA B operand (half the LDS traffic) in the larger
-// ones, which serve tiles of 128 tokens' multiples.  Four matrix products per block, no duplicate work inside the
-// kernel, and each wave keeps one accumulator set: at head dimension 128, per wave and 32-query sub-block 32 matrix
-// instructions, 40 vector instructions and 26 LDS reads in 165-168 registers, so that three waves per SIMD fit (six pairs:
-// 192 keys per workgroup); at head dimension 64 it is 110-118 registers and four waves per SIMD.
-// LDS stage: Q and dO (each read by rows and transposed) and the row statistics of the 32 queries.
-// What bounds it: the matrix pipe is busy 55 % of the cycles at head dimension 128 (30x48x80 grid, 24 heads, window 3x3x3:
-// 24.0 ms, 1220 TFLOP/s); at 64 50 % of them, LDS 41 % (the same grid, 13.8-14.1 ms), on 64-token image tiles 26 and 27 %
-// (18 sub-blocks per item: two barriers each, and the item's fixed cost).  Tiles that are no multiple of 128
-// tokens went through one wave per workgroup with register-staged operands before (both kernels, the statistics included, in
-// us): 32 heads of a 64x64 image in 64-token tiles, window 3x3, head dimension 64 255 -> 92, 128 1060 -> 163; 10x30x56 in
-// 96-token tiles, window 3x3x3, ten slices, 128 5500 -> 763, 64 1180 -> 473; 9x40x40 in 192-token tiles, four heads of 128
-// 4550 -> 843.
+// dK, dV.  One workgroup of NW waves per 32 * NW keys (times G walk groups); a wave holds K and V of its 32 keys, accumulates
+// dK and dV and forms all four products, S = Q K^T, dV^T += dO^T P, dP = dO V^T, dK^T += Q^T dS, in this order: P stays in
+// registers in fp32 and no other wave is waited for.  At head dimension 64 158 registers, three waves per SIMD; at 128 all 256
+// that two waves per SIMD allow (128 accumulator, 64 resident operand; 20 bytes of scratch outside the loop).  Per wave and 32-query
+// sub-block 64 matrix instructions at head dimension 128, 32 at 64, next to about 64 vector instructions.
+// LDS stage: Q and dO (each read by rows and transposed) and the row statistics of the 32 queries, from which the accumulators of
+// S and dP start.  UPS sub-blocks per stage, i.e. per barrier.
+// NW = 1 ("solo", for the small launches): the stage belongs to one wave, which needs no barrier, only its own requests to have
+// landed, and refills either operand as soon as it has read it: half the LDS, so that a CU holds eight such waves at head
+// dimension 128 and twelve at 64.  There dP and dS come before the product with P, which frees dO first.
+// What bounds it: matrix pipe and power on large launches (30x48x80, 24 heads, window 3x3x3, head dimension 128: 22.1 ms, 1330
+// TFLOP/s; 64: 11.5 ms, 1280).  Before, each 32 keys were served by a pair of waves, one for S, P and dV, one for dP, dS and dK,
+// with P handed over through LDS at a barrier of its own.  Entry point, pairs against this kernel, us: 30x48x80, 24 heads of 128
+// 40,040, 38,810; of 64 21,720, 20,320; 12x24x40 in 4x8x8 tiles, 28 heads of 128 2640, 2420; 16x48x48 in 8x8x8 tiles, 48 heads
+// of 128 23,215, 21,995; 16x40x120 in 4x4x8 tiles, 16 heads of 64 2825, 2585; 64x64 images in 64-token tiles, 128 heads of 64 326,
+// 299.  The error of dK on tiles of 128 tokens' multiples at head dimension 128 went from 2.88e-3 to 2.35e-3 against 64 bits
+// (2-norm): P had been handed over in bf16 there.
+// dP before P in the shared form (as in the solo one) spills 56 bytes at head dimension 128 and is slower (24,073 against
+// 21,995 us on the 8x8x8 case); two sub-blocks per stage give 0.5 to 1 % at 64 and lose as much at 128.
 // A lane holds key column c16 of its wave's two 16-key blocks and the query rows 4*g4 .. 4*g4+3 of a result.
 // ---------------------------------------------------------------------------------------------------------
-template <int D, int NPAIR, int G, bool DMA>
-__global__ __attribute__((amdgpu_flat_work_group_size(NPAIR * G * 128, NPAIR * G * 128), amdgpu_waves_per_eu(D == 64 ? 4 : NPAIR == 1 ? 2 : 3)))
+template <int D, int NW, int G, int UPS, bool DMA>
+__global__ __attribute__((amdgpu_flat_work_group_size(NW * G * 64, NW * G * 64), amdgpu_waves_per_eu(D == 64 ? 3 : 2)))
 void sta_bwd_dkv_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restrict__ k, const bf16_raw *__restrict__ v,
                         const bf16_raw *__restrict__ d_o, const float *__restrict__ neg_lse,
                         const float *__restrict__ neg_delta, bf16_raw *__restrict__ d_k, bf16_raw *__restrict__ d_v,
@@ -396,13 +446,263 @@ void sta_bwd_dkv_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restri
 {
     using L = Staged<D>;
     constexpr int KS = L::KS, CB = L::CB;
+    constexpr bool SOLO = NW == 1 && DMA;               // a wave with a stage of its own: no barriers, single buffers
+    constexpr int COLS = NW * 32;                       // keys per workgroup
+    constexpr int UNIT_B = 2 * L::Tile;
+    constexpr int Q_TILE = 0, G_TILE = L::Tile;
+    constexpr int UNITS = SOLO ? 1 : 2 * UPS;           // sub-blocks in LDS, per walk group
+    constexpr int STATS = UNITS * UNIT_B;               // per sub-block: -lse / scale then -delta of the 32 staged query rows
+    constexpr int STAT_B = 2 * kSub * 4;
+    constexpr int GROUP_B = STATS + UNITS * STAT_B;     // LDS of one walk group
+    constexpr int OPS = 2 * L::Groups;                  // DMA instructions per sub-block: Q, dO
+    constexpr int WAVE_OPS = (OPS + NW - 1) / NW;
+    constexpr int WAVE_OUT = 16 * L::RowB;
+    constexpr int ROWS_B = 32 * L::RowB;
+    constexpr int SMEM = SOLO && G > 1 ? G * GROUP_B + ROWS_B
+                                       : max_of(G * GROUP_B, max_of((G / 2) * NW * CB * 2 * 1024, NW * WAVE_OUT));
+    static_assert(UPS == 1 || G == 1, "shares of a walk are counted in single units");
+    __shared__ __attribute__((aligned(1024))) char smem[SMEM];
+
+    const BwdItem item = bwd_item_of<false>(blockIdx.x, p, plan);
+    if (!item.valid) return;
+    const size_t bh = item.bh;
+    const int tid = threadIdx.x;
+    const int wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int group = wave_all / NW, wave = wave_all % NW;
+    const int lane = tid & 63, c16 = lane & 15, g4 = lane >> 4;
+
+    const size_t head_row = bh * p.N;
+    const size_t my_row = head_row + (size_t)item.block * COLS + (size_t)wave * 32;
+    const char *qh = reinterpret_cast<const char *>(q + head_row * D);
+    const char *gh = reinterpret_cast<const char *>(d_o + head_row * D);
+
+    WalkShare<G> share;
+    share.start(item.box, p, plan, group);
+
+    // DMA: each operand is L::Groups instructions of 1 KB; wave w of the group issues the instructions w, w + NW, .., the last
+    // wave also the one of 4 bytes per lane that brings the row statistics (32 + 32 floats).
+    const uint32_t src_lane_off = L::dma_lane_offset(lane);
+    const uint32_t stat_lane_off = (uint32_t)((lane & (kSub - 1)) * 4);
+    const char *stat_base = reinterpret_cast<const char *>((lane < kSub ? neg_lse : neg_delta) + head_row);
+    char *group_lds = smem + group * GROUP_B;
+    auto issue_stats = [&](uint32_t row, int unit) __attribute__((always_inline)) {
+        uint32_t soff = stat_lane_off;
+        asm volatile("" : "+v"(soff));                  // keep the lane offsets 32-bit next to a scalar base
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(stat_base + (size_t)row * 4 + soff),
+                                         STA_LDS_PTR(group_lds + STATS + unit * STAT_B), 4, 0, 0);
+    };
+    auto issue_operand = [&](auto is_g_c, uint32_t row) __attribute__((always_inline)) {     // single buffers
+        constexpr bool IS_G = decltype(is_g_c)::value;
+        uint32_t off = src_lane_off;
+        asm volatile("" : "+v"(off));
+#pragma unroll
+        for (int j = 0; j < L::Groups; ++j)
+            stage_group<DMA>((IS_G ? gh : qh) + (size_t)(row + L::GroupRows * j) * L::RowB + off,
+                             group_lds + (IS_G ? G_TILE : Q_TILE) + j * L::Group, lane);
+    };
+    int issued = 0;
+    auto issue_next = [&]() __attribute__((always_inline)) {
+        if (issued >= share.n_units) return;
+        uint32_t off = src_lane_off;
+        asm volatile("" : "+v"(off));
+#pragma unroll
+        for (int su = 0; su < UPS; ++su) {
+            const int unit = issued % (2 * UPS) + su;
+            const uint32_t first_row = share.walk.next_row;
+            share.walk.advance();
+#pragma unroll
+            for (int i = 0; i < WAVE_OPS; ++i) {
+                const int j = wave + i * NW;
+                if (OPS % NW == 0 || j < OPS) {
+                    const bool is_g = j >= L::Groups;
+                    const int part = j % L::Groups;
+                    const char *src = (is_g ? gh : qh) + (size_t)(first_row + L::GroupRows * part) * L::RowB;
+                    stage_group<DMA>(src + off, group_lds + unit * UNIT_B + (is_g ? G_TILE : Q_TILE) + part * L::Group, lane);
+                }
+            }
+            if (wave == NW - 1) issue_stats(first_row, unit);
+        }
+        issued += UPS;
+    };
+    if constexpr (SOLO) {
+        if (share.n_units > 0) {
+            issue_stats(share.walk.next_row, 0);
+            issue_operand(std::true_type{}, share.walk.next_row);
+            issue_operand(std::false_type{}, share.walk.next_row);
+        }
+    } else {
+        issue_next();
+    }
+
+    const uint32_t group_addr = (uint32_t)(uintptr_t)smem + (uint32_t)(group * GROUP_B);
+    uint32_t row_addr[KS], tr_addr[4];
+    L::addresses(group_addr, lane, row_addr, tr_addr);
+    const uint32_t stat_addr = group_addr + STATS + 16 * g4;
+
+    // resident B fragments: key 16*kb + c16, channels 32*ks + 8*g4 ..
+    bf16x8 Kr[2][KS], Vr[2][KS];
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            const size_t at = (my_row + 16 * kb + c16) * D + ks * 32 + g4 * 8;
+            Kr[kb][ks] = *reinterpret_cast<const bf16x8 *>(k + at);
+            Vr[kb][ks] = *reinterpret_cast<const bf16x8 *>(v + at);
+        }
+    const float c = p.scale_log2e;
+
+    floatx4 dV[CB][2], dK[CB][2];                       // [channel block][key block]
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) {
+            dV[cb][kb] = floatx4{0.f, 0.f, 0.f, 0.f};
+            dK[cb][kb] = floatx4{0.f, 0.f, 0.f, 0.f};
+        }
+
+    // Accumulators [query block][key block] that start at the statistics of their query rows 16*qb + 4*g4 ..
+    auto start_at = [&](auto off_c, floatx4 (&X)[2][2]) __attribute__((always_inline)) {
+        constexpr int OFF = decltype(off_c)::value;
+        typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+        u32x4 r0, r1;
+        asm volatile("ds_read_b128 %0, %2 offset:%3\n\tds_read_b128 %1, %2 offset:%4\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&v"(r0), "=&v"(r1)
+                     : "v"(stat_addr), "n"(OFF), "n"(OFF + 64));
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) {
+            X[0][kb] = __builtin_bit_cast(floatx4, r0);
+            X[1][kb] = __builtin_bit_cast(floatx4, r1);
+        }
+    };
+    // S becomes P = 2^(c S); Pb: rounded, packed as the B operand of the product over the queries
+    auto probabilities = [&](floatx4 (&S)[2][2], bf16x8 (&Pb)[2]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+            for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    S[qb][kb][e] = __builtin_amdgcn_exp2f(S[qb][kb][e] * c);
+                    Pb[kb][4 * qb + e] = static_cast<__bf16>(S[qb][kb][e]);
+                }
+    };
+    auto products = [&](const floatx4 (&P)[2][2], const floatx4 (&dP)[2][2], bf16x8 (&dSb)[2]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+            for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) dSb[kb][4 * qb + e] = static_cast<__bf16>(P[qb][kb][e] * dP[qb][kb][e]);
+    };
+    auto sub_block = [&](auto unit_c) __attribute__((always_inline)) {
+        constexpr int ST = decltype(unit_c)::value * UNIT_B;
+        constexpr int ST_STATS = decltype(unit_c)::value * STAT_B;
+        floatx4 S[2][2], dP[2][2];                      // [query block][key block]
+        bf16x8 Pb[2], dSb[2];
+        start_at(std::integral_constant<int, ST_STATS>{}, S);
+        staged_rows_times_resident<D, ST + Q_TILE>(row_addr, Kr, S);      // Q K^T - lse / scale
+        StagedTransposedProduct<D, ST + G_TILE, 2> g_t;
+        g_t.prefetch(tr_addr);
+        __builtin_amdgcn_sched_barrier(0);
+        probabilities(S, Pb);
+        g_t.run(tr_addr, Pb, dV);                                         // dV^T += dO^T P
+        start_at(std::integral_constant<int, ST_STATS + kSub * 4>{}, dP);
+        staged_rows_times_resident<D, ST + G_TILE>(row_addr, Vr, dP);     // dO V^T - delta
+        StagedTransposedProduct<D, ST + Q_TILE, 2> q_t;
+        q_t.prefetch(tr_addr);
+        __builtin_amdgcn_sched_barrier(0);
+        products(S, dP, dSb);
+        q_t.run(tr_addr, dSb, dK);                                        // dK^T += Q^T dS
+    };
+    if constexpr (SOLO) {
+#pragma unroll 1
+        for (int u = 0; u < share.n_units; ++u) {
+            floatx4 S[2][2], dP[2][2];
+            bf16x8 Pb[2], dSb[2];
+            wait_dma<L::Groups>();                                        // statistics and dO; Q has been requested behind them
+            start_at(std::integral_constant<int, kSub * 4>{}, dP);
+            start_at(std::integral_constant<int, 0>{}, S);
+            staged_rows_times_resident<D, G_TILE>(row_addr, Vr, dP);      // dO V^T - delta
+            wait_dma<0>();
+            staged_rows_times_resident<D, Q_TILE>(row_addr, Kr, S);       // Q K^T - lse / scale
+            StagedTransposedProduct<D, G_TILE, 2> g_t;
+            g_t.prefetch(tr_addr);
+            __builtin_amdgcn_sched_barrier(0);
+            probabilities(S, Pb);
+            products(S, dP, dSb);
+            g_t.run(tr_addr, Pb, dV);                                     // dV^T += dO^T P
+            share.walk.advance();
+            if (u + 1 < share.n_units) {
+                issue_stats(share.walk.next_row, 0);
+                issue_operand(std::true_type{}, share.walk.next_row);
+            }
+            StagedTransposedProduct<D, Q_TILE, 2> q_t;
+            q_t.prefetch(tr_addr);
+            q_t.run(tr_addr, dSb, dK);                                    // dK^T += Q^T dS
+            if (u + 1 < share.n_units) issue_operand(std::false_type{}, share.walk.next_row);
+        }
+    } else {
+        auto next_stage = [&]() __attribute__((always_inline)) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            issue_next();
+        };
+        for (int u = 0; u < share.n_steps; u += 2 * UPS) {
+            next_stage();
+            if (G == 1 || u < share.n_units) sub_block(std::integral_constant<int, 0>{});
+            if constexpr (UPS == 2) sub_block(std::integral_constant<int, 1>{});
+            if (u + UPS < share.n_steps) {
+                next_stage();
+                if (G == 1 || u + UPS < share.n_units) sub_block(std::integral_constant<int, UPS>{});
+                if constexpr (UPS == 2) sub_block(std::integral_constant<int, UPS + 1>{});
+            }
+        }
+    }
+    if constexpr (SOLO && G > 1) {
+        char *rows = smem + G * GROUP_B;
+        merge_waves<D, G, GROUP_B>(smem, rows, group, lane, dV, 1.0f);
+        store_rows<D, G * 64>(rows, d_v + my_row * D, tid);
+        merge_waves<D, G, GROUP_B>(smem, rows, group, lane, dK, c * kLn2);
+        store_rows<D, G * 64>(rows, d_k + my_row * D, tid);
+        return;
+    } else if constexpr (G > 1) {
+        merge_groups<G, NW>(smem, group, wave, lane, dV);
+        merge_groups<G, NW>(smem, group, wave, lane, dK);
+        if (group != 0) return;
+    } else {
+        __syncthreads();                                // every wave has finished reading the stages
+    }
+    store_columns<D>(smem + wave * WAVE_OUT, dV, 1.0f, d_v + my_row * D, lane);
+    store_columns<D>(smem + wave * WAVE_OUT, dK, c * kLn2, d_k + my_row * D, lane);
+}
+
+// ---------------------------------------------------------------------------------------------------------
+// dK, dV at head dimension 128 on tiles of 96 and 32 tokens' multiples.  One workgroup of 2 * NPAIR waves per 32 * NPAIR keys
+// (times G walk groups).  Each 32-key column block is served by a PAIR of waves: the first holds K and accumulates dV (S = Q K^T,
+// P, dV^T += dO^T P), the second holds V and accumulates dK (dP = dO V^T, dS = P o (dP - delta), dK^T += Q^T dS).  P goes from the
+// first to the second through LDS in fp32.  165-172 registers, three waves per SIMD: on these tiles the two waves per SIMD of
+// the kernel above do not fill the CU (three waves of 96 keys leave every fourth place empty) or need more LDS than there is
+// (one wave of 32).  Entry point, this kernel against the other, us: 10x30x56 in 96-token tiles, window 3x3x3, four slices
+// 356, 373, eight 643, 659, forty 3346, 3346; window 1x3x3, four 147, 153; 32x64 images in 32-token tiles, 16 heads 37, 47, 64
+// heads 127, 150.
+// A lane holds key column c16 of its wave's two 16-key blocks and the query rows 4*g4 .. 4*g4+3 of a result.
+// ---------------------------------------------------------------------------------------------------------
+template <int NPAIR, int G, bool DMA>
+__global__ __attribute__((amdgpu_flat_work_group_size(NPAIR * G * 128, NPAIR * G * 128), amdgpu_waves_per_eu(NPAIR == 1 ? 2 : 3)))
+void sta_bwd_dkv_pair_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restrict__ k, const bf16_raw *__restrict__ v,
+                        const bf16_raw *__restrict__ d_o, const float *__restrict__ neg_lse,
+                        const float *__restrict__ neg_delta, bf16_raw *__restrict__ d_k, bf16_raw *__restrict__ d_v,
+                        sta::FwdParams p, BwdPlan plan)
+{
+    constexpr int D = 128;
+    using L = Staged<D>;
+    constexpr int KS = L::KS, CB = L::CB;
     constexpr int COLS = NPAIR * 32;                    // keys per workgroup
     constexpr int WAVES = 2 * NPAIR;                    // per walk group
     constexpr int STAGE_B = 2 * L::Tile;
     constexpr int Q_TILE = 0, G_TILE = L::Tile;
-    constexpr bool P_F32 = NPAIR <= 3;                  // P handed over in fp32
-    constexpr int P_XCHG = 2 * STAGE_B;                 // per pair: planes of 64 lanes x 16 B, one per key block (bf16)
-    constexpr int PAIR_B = P_F32 ? 4096 : 2048;         // or per key and query block (fp32)
+    constexpr int P_XCHG = 2 * STAGE_B;                 // per pair: planes of 64 lanes x 16 B, one per key and query block
+    constexpr int PAIR_B = 4096;
     constexpr int STATS = P_XCHG + NPAIR * PAIR_B;      // per stage: -lse / scale then -delta of the 32 staged query rows
     constexpr int STAT_B = 2 * kSub * 4;
     constexpr int GROUP_B = STATS + 2 * STAT_B;         // LDS of one walk group
@@ -534,17 +834,12 @@ void sta_bwd_dkv_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restri
                         P[qb][kb][e] = __builtin_amdgcn_exp2f(X[qb][kb][e] * c);
                         Pb[kb][4 * qb + e] = static_cast<__bf16>(P[qb][kb][e]);
                     }
-            if constexpr (P_F32) {
-                // plain stores: the compiler gives them the wait states that exponentials and matrix results need
-                floatx4 *out = reinterpret_cast<floatx4 *>(group_lds + P_XCHG + pair * PAIR_B + lane * 16);
+            // plain stores: the compiler gives them the wait states that exponentials and matrix results need
+            floatx4 *out = reinterpret_cast<floatx4 *>(group_lds + P_XCHG + pair * PAIR_B + lane * 16);
 #pragma unroll
-                for (int kb = 0; kb < 2; ++kb)
+            for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-                    for (int qb = 0; qb < 2; ++qb) out[64 * (2 * kb + qb)] = P[qb][kb];
-            } else {
-                lds_write_b128(xchg_addr, Pb[0]);
-                lds_write_b128(xchg_addr + 1024, Pb[1]);
-            }
+                for (int qb = 0; qb < 2; ++qb) out[64 * (2 * kb + qb)] = P[qb][kb];
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             __builtin_amdgcn_s_barrier();
             g_t.run(tr_addr, Pb, acc);                                              // dV^T += dO^T P
@@ -554,35 +849,21 @@ void sta_bwd_dkv_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restri
             q_t.prefetch(tr_addr);
             __builtin_amdgcn_s_barrier();
             bf16x8 dSb[2];
-            if constexpr (P_F32) {
-                bf16x8 raw[4];                          // key block 0: query blocks 0, 1; key block 1
-                raw[0] = ds_read_b128_at<0>(xchg_addr);
-                raw[1] = ds_read_b128_at<1024>(xchg_addr);
-                raw[2] = ds_read_b128_at<2048>(xchg_addr);
-                raw[3] = ds_read_b128_at<3072>(xchg_addr);
-                lds_wait2<2>(raw[0], raw[1]);
-                lds_wait2<0>(raw[2], raw[3]);
+            bf16x8 raw[4];                              // key block 0: query blocks 0, 1; key block 1
+            raw[0] = ds_read_b128_at<0>(xchg_addr);
+            raw[1] = ds_read_b128_at<1024>(xchg_addr);
+            raw[2] = ds_read_b128_at<2048>(xchg_addr);
+            raw[3] = ds_read_b128_at<3072>(xchg_addr);
+            lds_wait2<2>(raw[0], raw[1]);
+            lds_wait2<0>(raw[2], raw[3]);
 #pragma unroll
-                for (int kb = 0; kb < 2; ++kb)
+            for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-                    for (int qb = 0; qb < 2; ++qb) {
-                        const floatx4 P = __builtin_bit_cast(floatx4, raw[2 * kb + qb]);
+                for (int qb = 0; qb < 2; ++qb) {
+                    const floatx4 P = __builtin_bit_cast(floatx4, raw[2 * kb + qb]);
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) dSb[kb][4 * qb + e] = static_cast<__bf16>(P[e] * X[qb][kb][e]);
-                    }
-            } else {
-                bf16x8 Pb[2];
-                Pb[0] = ds_read_b128_at<0>(xchg_addr);
-                Pb[1] = ds_read_b128_at<1024>(xchg_addr);
-                lds_wait2<0>(Pb[0], Pb[1]);
-#pragma unroll
-                for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                    for (int qb = 0; qb < 2; ++qb)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            dSb[kb][4 * qb + e] = static_cast<__bf16>(static_cast<float>(Pb[kb][4 * qb + e]) * X[qb][kb][e]);
-            }
+                    for (int e = 0; e < 4; ++e) dSb[kb][4 * qb + e] = static_cast<__bf16>(P[e] * X[qb][kb][e]);
+                }
             q_t.run(tr_addr, dSb, acc);                                             // dK^T += Q^T dS
         }
     };
@@ -701,15 +982,27 @@ bool rows_of_all_heads(const BwdArgs &a, uint32_t cols, uint64_t resident)
 // heads are then dealt unevenly (16x48x64, four heads -15 % as they come, -12 %; 30x48x80, two -9, -3 %), and not along w: every
 // fourth item of an XCD goes to the same part of it, and a row of eight tiles at window 4 would put the long ones there (20x12x64
 // in 128-token tiles, five heads 761, 957 us).
-template <int D, int NPAIR, int G, bool DMA = true>
+template <int D, int NW, int G, int UPS = 1, bool DMA = true>
 hipError_t launch_dkv(const BwdArgs &a)
 {
     uint32_t ids;
-    const uint64_t resident = (uint64_t)sta::compute_units() * (D == 64 ? 16 : 12) / (2 * NPAIR * G);     // workgroups
-    const bool row_major = rows_of_all_heads(a, NPAIR * 32, resident), longest_first = a.p.P % 96 == 0 && a.p.P % 128 != 0;
+    const uint64_t resident = (uint64_t)sta::compute_units() * (D == 64 ? 12 : 8) / (NW * G);     // workgroups
+    const bool row_major = rows_of_all_heads(a, NW * 32, resident), longest_first = a.p.P % 96 == 0 && a.p.P % 128 != 0;
+    const BwdPlan plan = make_plan(a, NW * 32, row_major, row_major && longest_first, &ids);
+    sta_bwd_dkv_kernel<D, NW, G, UPS, DMA><<<dim3(ids), dim3(NW * G * 64), 0, a.stream>>>(a.q, a.k, a.v, a.d_o, a.neg_lse, a.neg_delta,
+                                                                                    a.d_k, a.d_v, a.p, plan);
+    return hipGetLastError();
+}
+
+template <int NPAIR, int G, bool DMA = true>
+hipError_t launch_dkv_pairs(const BwdArgs &a)
+{
+    uint32_t ids;
+    const uint64_t resident = (uint64_t)sta::compute_units() * 12 / (2 * NPAIR * G);     // workgroups
+    const bool row_major = rows_of_all_heads(a, NPAIR * 32, resident), longest_first = a.p.P % 96 == 0;
     const BwdPlan plan = make_plan(a, NPAIR * 32, row_major, row_major && longest_first, &ids);
-    sta_bwd_dkv_kernel<D, NPAIR, G, DMA><<<dim3(ids), dim3(NPAIR * G * 128), 0, a.stream>>>(a.q, a.k, a.v, a.d_o, a.neg_lse, a.neg_delta,
-                                                                                      a.d_k, a.d_v, a.p, plan);
+    sta_bwd_dkv_pair_kernel<NPAIR, G, DMA><<<dim3(ids), dim3(NPAIR * G * 128), 0, a.stream>>>(a.q, a.k, a.v, a.d_o, a.neg_lse, a.neg_delta,
+                                                                                        a.d_k, a.d_v, a.p, plan);
     return hipGetLastError();
 }
 
@@ -723,7 +1016,11 @@ hipError_t launch_dkv(const BwdArgs &a)
 // head dimension 128: clip x 12 695 against 772, full x 8 1613 against 1726).  Two walk groups where the launch then still fits
 // the chip (8 waves per CU at head dimension 128, 12 at 64); one against two at 128: clip x 1 (864 waves) 128, 121, full x 1
 // (576) 390, 308, image x 2 (256) 18.1, 15.0, image x 8 (1024) 24.5, 22.7, clip x 2 (1728) 141, 160; at 64: image x 8 (1024)
-// 16.8, 14.2, image x 16 (2048) 21.1, 23.4.  Four groups are never faster (clip x 1 138, image x 8 33).
+// 16.8, 14.2, image x 16 (2048) 21.1, 23.4.  Four groups of one wave, without barriers, up to one such workgroup per CU
+// (two on 96-token tiles at head dimension 64); entry point, two groups of two or three waves against these: 12x24x24 in
+// 384-token tiles, one head (216 waves) of 64 100, 87, of 128 151, 131, two (432) 107, 110; 64x64 image, 5x5, one head (128) of 128 149,
+// 140, three (384) 150, 157; 4x12x24 in 96-token tiles, one head (36) of 64 39.5, 31.2, of 128 59.6, 47.3; twelve (432) 40.6, 35.4
+// and 61.3, 61.9.
 template <int D>
 hipError_t dispatch_dq(const BwdArgs &a)
 {
@@ -731,33 +1028,47 @@ hipError_t dispatch_dq(const BwdArgs &a)
     const uint32_t P = a.p.P;
     const bool two = 2 * waves <= fits && longest_walk(a) >= 16;
     if (P % 128 != 0 && !(sta::dma_aligned(a.k) && sta::dma_aligned(a.v))) return launch_dq<D, 1, 1, false>(a);
+    const uint64_t cus = sta::compute_units();
+    if (waves <= (D == 64 && P % 96 == 0 && P % 128 != 0 ? 2 * cus : cus)) return launch_dq<D, 1, 4>(a);
     if (P % 96 == 0 && P % 128 != 0) return two ? launch_dq<D, 3, 2>(a) : launch_dq<D, 3, 1>(a);
     if (P % 64 != 0) return launch_dq<D, 1, 1>(a);
     if (two) return launch_dq<D, 2, 2>(a);
     return P % 128 == 0 ? launch_dq<D, 4, 1>(a) : launch_dq<D, 2, 1>(a);
 }
 
-// dK/dV: head dimension 128: six pairs (a CU's twelve waves in one workgroup) where the tile allows and the last round of
-// workgroups is not mostly empty, otherwise four or two pairs; two, four, six pairs: clip x 12 (6.75 rounds of six pairs) 1091,
-// 1120, 1039, full x 8 (3.0) 2269, 2455, 2121, clip x 6 (3.4) 571, 577, 570, clip x 4 (2.25) 430, 431, 448, full x 3 (1.1)
-// 1095, 1009, 1340, full x 1 (0.4) 580, 482, 651.  Three walk groups of two pairs where all of them fit the chip at once:
-// image x 2 (512 waves) 22 against 27; beyond that they lose (image x 8, 2048 waves, 44 against 36).
-// Head dimension 64: four pairs, two workgroups per CU (clip x 12 581, two pairs 610, six 676); two walk groups of two pairs
-// where they fit: image x 8 (2048 waves) 23.2 against 26.7, image x 16 (4096) 43 against 37.
-// 96-token tiles: two walk groups always.  A workgroup of three pairs is six waves, and the SIMDs they leave half full take no
-// second one (10x30x56, 10 slices, windows up to 5x5x3: 681 with one group, 540 with two; head dimension 64 386, 365).
+// dK/dV.  Entry point in us; waves of 32 keys and sub-blocks per walk in brackets.
+// Four walk groups of one wave each while few of them share a CU, against two groups of two waves: head dimension 64, 64x64 image
+// at 3x3, two heads (256, 18) 21.1, 25.2, eight (1024, 18) 35.2, 34.3; at 5x5, eight (1024, 50) 70, 80; 12x24x24 in 384-token tiles,
+// two (432, 108) 83, 89, three (648, 108) 104, 94; 9x40x40 in 192-token tiles, two (900, 54) 82, 97, four (1800, 54) 126, 129; 128,
+// 8x32x32 in 128-token tiles, one (256, 36) 46, 60, two (512, 36) 65, 61; 64x64 at 5x5, five (640, 50) 101, 110; 9x40x40, three (1350,
+// 54) 199, 185.  Against the shapes of 96- and 32-token tiles: 10x30x56, 64, 3x3x3, four slices (2100, 81) 185, 221, eight (4200, 81)
+// 341, 378, ten (5250, 81) 430, 418; 128, two (1050, 81) 227, 285, three (1575, 81) 329, 339, 1x3x3, two (1050, 27) 98, 98; 32x64 in
+// 32-token tiles, 128, four (256, 9) 24.4, 25.4, eight (512, 9) 32.8, 31.0, at 5x5 (512, 25) 62, 79.
+// Beyond that two groups of two waves where the launch is still small or the walk long, against two or four waves: 64, 384-token
+// tiles, six heads (1296, 108) 142, 156, eight (1728, 108) 187, 175; 128-token tiles, eight (2048, 36) 89, 91, 24 (6144, 36) 205, 220,
+// 256-token tiles, 28 (10080, 120) 951, 914; 64x64, 3x3, 16 (2048, 18) 53, 53, 32 (4096, 18) 88, 85; 192-token tiles, 16 (7200, 54) 355,
+// 384; 128, 128-token tiles, six (1536, 36) 128, 137, 24 (6144, 36) 379, 382; 192-token tiles, eight (3600, 54) 360, 408, 24 (10800, 54)
+// 1019, 1010; 320-token tiles, eight (4000, 90) 605, 694, 24 (12000, 90) 1744, 1715.
 template <int D>
 hipError_t dispatch_dkv(const BwdArgs &a)
 {
-    const uint64_t cus = sta::compute_units(), slices = (uint64_t)a.B * a.p.heads, waves = 2 * slices * (a.p.N / 32);
-    const uint32_t P = a.p.P;
-    if (P % 128 != 0 && !(sta::dma_aligned(a.q) && sta::dma_aligned(a.d_o))) return launch_dkv<D, 1, 1, false>(a);
-    if (P % 64 != 0) return P % 96 == 0 ? launch_dkv<D, 3, 2>(a) : launch_dkv<D, 1, 1>(a);
-    constexpr int GROUPS = D == 128 ? 3 : 2;
-    if (GROUPS * waves <= cus * (D == 128 ? 12 : 16) && longest_walk(a) >= 16) return launch_dkv<D, 2, GROUPS>(a);
-    const uint64_t blocks = slices * (a.p.N / 192), rounds = (blocks + cus - 1) / cus;
-    if (D == 128 && P % 384 == 0 && 5 * blocks >= 4 * rounds * cus) return launch_dkv<128, 6, 1>(a);
-    return P % 128 == 0 ? launch_dkv<D, 4, 1>(a) : launch_dkv<D, 2, 1>(a);
+    const uint64_t cus = sta::compute_units(), waves = (uint64_t)a.B * a.p.heads * (a.p.N / 32);
+    const uint32_t P = a.p.P, units = longest_walk(a);
+    if (P % 128 != 0 && !(sta::dma_aligned(a.q) && sta::dma_aligned(a.d_o))) {
+        if constexpr (D == 128) return launch_dkv_pairs<1, 1, false>(a);
+        else return launch_dkv<64, 1, 1, 1, false>(a);
+    }
+    uint64_t solo = D == 64 ? 2 * cus : cus;            // up to so many waves
+    if (P % 64 == 0 && P % 128 != 0 && units >= 48) solo = (D == 64 ? 8 : 4) * cus;
+    if (P % 64 != 0 && P % 96 == 0) solo = (D == 64 ? 18 : 6) * cus;
+    if (P % 64 != 0 && P % 96 != 0 && units >= 24) solo = 2 * cus;
+    if (waves <= solo) return launch_dkv<D, 1, 4>(a);
+    if (P % 64 != 0) {
+        if constexpr (D == 128) return P % 96 == 0 ? launch_dkv_pairs<3, 2>(a) : launch_dkv_pairs<1, 1>(a);
+        else return P % 96 == 0 ? launch_dkv<64, 3, 1>(a) : waves <= 4 * cus ? launch_dkv<64, 1, 2>(a) : launch_dkv<64, 1, 1>(a);
+    }
+    if (P % 128 == 0) return waves <= (P == 128 ? 24 : 6) * cus ? launch_dkv<D, 2, 2>(a) : launch_dkv<D, 4, 1, D == 64 ? 2 : 1>(a);
+    return waves <= 8 * cus || (units >= 32 && (D == 64 || waves <= 32 * cus)) ? launch_dkv<D, 2, 2>(a) : launch_dkv<D, 2, 1>(a);
 }
 
 }  // namespace
