@@ -821,6 +821,288 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
     }
 }
 
+// ---------------------------------------------------------------------------
+// The small launches' kernel ("solo"): a workgroup is KG waves that share NQ blocks of 16 queries and take one KG-th of the walk
+// each, with LDS of their own.  No barrier until the end, so that the waves drift apart and one computes where another waits; and
+// a wave's requests need no second stage: K of the next unit is requested as soon as K of this one has been read, V likewise,
+// each waited for by count (requests complete in order).  At the end every wave leaves its accumulators, offsets and row sums in
+// its LDS, and all of them merge one share of the channels each, in a fixed order: two barriers, whatever KG is.
+//
+// What bounds it: the latencies of one wave's unit where there are few waves (1200 cycles a unit at one wave per SIMD in the kernel
+// above, which had all its waves in the same phase behind one barrier per unit), the 64 bytes per cycle that a CU takes from L2 where
+// there are many (8 KB a unit at head dimension 64, for 32 queries; hence NQ = 4, 64 queries, where the walk is long), and the fixed
+// part of a launch, about 6 us: arguments, Q and the first K from memory, the merge, the way out.  In us, the kernel above and this
+// one: 4x12x24 in 96-token tiles, one head, 64 16.6, 9.1, 128 23.6, 13.1; 12x24x24 in 384-token tiles, one head, 64 24.2, 14.4, 128
+// 35.0, 23.1; 18x24x24, one head of 64 24.4, 19.5; 10x30x56 in 96-token tiles, 64, three heads 84, 62.
+//
+// The scores start at 0 and the offset enters the exponent by a fused multiply-add (one instruction per score, as the
+// multiplication it replaces): six registers less than scores that start at minus the offset.
+// ---------------------------------------------------------------------------
+template <int D, int NQ, int KG, int WPE, bool FOLLOW>
+__global__ __attribute__((amdgpu_flat_work_group_size(KG * 64, KG * 64), amdgpu_waves_per_eu(WPE)))
+void sta_fwd_solo_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restrict__ k, const bf16_raw *__restrict__ v,
+                         bf16_raw *__restrict__ o, sta::FwdParams p, sta::FwdPlan plan)
+{
+    using L = Staged<D>;                                    // V; K is read by rows only
+    using R = StagedRows<D>;
+    constexpr int KS = L::KS, CB = L::CB;
+    constexpr int QB = 16 * NQ;                             // queries of the workgroup
+    constexpr int GROUPS = L::Groups;                       // DMA instructions per operand of a unit
+    constexpr int SLICES = CB * NQ;                         // 16x16 blocks of an accumulator, 1 KB each
+    constexpr int UNIT_B = R::Tile + L::Tile;
+    constexpr int REGION = UNIT_B > SLICES * 1024 ? UNIT_B : SLICES * 1024;    // LDS of a wave: K, then V; at the end its accumulators
+    constexpr int PER_WAVE = SLICES / KG;                   // of them that a wave merges
+    static_assert(SLICES % KG == 0 && PER_WAVE <= CB, "merge");
+    constexpr int STATS = KG * REGION;                      // offset and row sum of every group's queries
+    constexpr int FLAGS = STATS + KG * QB * 8;
+    constexpr int OUT = (FLAGS + KG * 4 + 15) / 16 * 16;
+    __shared__ __attribute__((aligned(1024))) char smem[OUT + QB * L::RowB];
+
+    const GroupItem item = group_item_of(blockIdx.x, p, plan);
+    if (!item.valid) return;
+    const size_t bh = item.bh;
+    const StaBox box = item.box;
+    const int tid = threadIdx.x;
+    const int kg = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = tid & 63, c16 = lane & 15, g4 = lane >> 4;
+    const size_t my_row = bh * p.N + (size_t)item.qblock * QB;
+    const char *kh = reinterpret_cast<const char *>(k + bh * p.N * D);
+    const char *vh = reinterpret_cast<const char *>(v + bh * p.N * D);
+
+    BoxWalk walk;
+    int n_units;
+    auto start_walk = [&]() __attribute__((always_inline)) {
+        walk.start(box, p.n_h, p.n_w, p.P);
+        const int n_all = box.count() * walk.sub_per_tile;
+        const int lo = n_all * kg / KG;
+        n_units = n_all * (kg + 1) / KG - lo;
+        const uint32_t tiles = fast_div((uint32_t)lo, plan.sub_per_tile);
+        walk.skip(tiles, (uint32_t)lo - tiles * plan.sub_per_tile.d);
+    };
+    start_walk();
+
+    char *region = smem + kg * REGION;
+    const uint32_t k_lane_off = R::dma_lane_offset(lane), v_lane_off = L::dma_lane_offset(lane);
+    auto issue_k = [&](uint32_t row) __attribute__((always_inline)) {
+        uint32_t off = k_lane_off;
+        asm volatile("" : "+v"(off));                       // keep the lane offset 32-bit next to a scalar base
+#pragma unroll
+        for (int i = 0; i < GROUPS; ++i)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(kh + (size_t)(row + L::GroupRows * i) * L::RowB + off),
+                                             STA_LDS_PTR(region + i * R::Group), 16, 0, 0);
+    };
+    auto issue_v = [&](uint32_t row) __attribute__((always_inline)) {
+        uint32_t off = v_lane_off;
+        asm volatile("" : "+v"(off));
+#pragma unroll
+        for (int i = 0; i < GROUPS; ++i)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(vh + (size_t)(row + L::GroupRows * i) * L::RowB + off),
+                                             STA_LDS_PTR(region + R::Tile + i * L::Group), 16, 0, 0);
+    };
+    if (n_units > 0) {
+        issue_k(walk.next_row);
+        issue_v(walk.next_row);
+    }
+
+    const uint32_t region_addr = (uint32_t)(uintptr_t)smem + (uint32_t)(kg * REGION);
+    const uint32_t row_addr = R::address(region_addr, lane);
+    uint32_t tr_addr[4];
+    L::transposed_addresses(region_addr + R::Tile, lane, tr_addr);
+    bf16x8 Qr[NQ][KS];
+#pragma unroll
+    for (int qb = 0; qb < NQ; ++qb)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+            Qr[qb][ks] = *reinterpret_cast<const bf16x8 *>(q + (my_row + 16 * qb + c16) * D + ks * 32 + g4 * 8);
+
+    floatx4 Oacc[CB][NQ];                                   // channel 16*cb + 4*g4 + i of query 16*qb + c16
+    float m_run[NQ], off[NQ];                               // largest score, in its own units and (rounded) in base 2
+    floatx4 l_acc[NQ];                                      // row sums
+    auto reset = [&](float m) __attribute__((always_inline)) {
+#pragma unroll
+        for (int qb = 0; qb < NQ; ++qb) {
+            l_acc[qb] = floatx4{0.f, 0.f, 0.f, 0.f};
+            m_run[qb] = m;
+            off[qb] = 0.f;
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) Oacc[cb][qb] = floatx4{0.f, 0.f, 0.f, 0.f};
+        }
+    };
+    reset(0.f);
+    const float c = p.scale_log2e;
+
+    auto run_pass = [&](auto careful_c) __attribute__((always_inline)) {
+        constexpr bool CAREFUL = decltype(careful_c)::value;
+        const float bound = FOLLOW || !CAREFUL ? 0.f : __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(8.0f / c)));
+#pragma unroll 1
+        for (int u = 0; u < n_units; ++u) {
+            const bool more = u + 1 < n_units;
+            wait_dma<GROUPS>();                             // K of this unit; its V has been requested behind it
+            floatx4 S[2][NQ];                               // [key block][query block]
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int qb = 0; qb < NQ; ++qb) S[kb][qb] = floatx4{0.f, 0.f, 0.f, 0.f};
+            rows_times_resident<D, 0>(row_addr, Qr, S);     // K Q^T
+            walk.advance();
+            if (more) issue_k(walk.next_row);
+            if (CAREFUL || FOLLOW || u == 0) {
+                float mq[NQ];
+#pragma unroll
+                for (int qb = 0; qb < NQ; ++qb) {
+                    mq[qb] = max3(S[0][qb][0], S[0][qb][1], S[0][qb][2]);
+                    mq[qb] = max3(mq[qb], S[0][qb][3], S[1][qb][0]);
+                    mq[qb] = max3(mq[qb], S[1][qb][1], S[1][qb][2]);
+                    mq[qb] = fmaxf(mq[qb], S[1][qb][3]);
+                }
+                if constexpr (CAREFUL) {
+#pragma unroll
+                    for (int qb = 0; qb < NQ; ++qb) {
+                        const float row_max = quad_lane_max(mq[qb]);
+                        const bool grown = row_max > m_run[qb] + bound;
+                        if (__builtin_amdgcn_ballot_w64(grown) != 0) {
+                            const float alpha = grown ? __builtin_amdgcn_exp2f((m_run[qb] - row_max) * c) : 1.f;
+                            m_run[qb] = grown ? row_max : m_run[qb];
+                            l_acc[qb] *= alpha;
+                            const float alpha_settled = settled_after_transcendental(alpha);
+#pragma unroll
+                            for (int cb = 0; cb < CB; ++cb) scale_in_place(Oacc[cb][qb], alpha_settled);
+                        }
+                        // subtracted, exactly 0 for the largest score: c times a lowest number and its rounding are far apart
+                        const float offset = m_run[qb] == -INFINITY ? 0.f : m_run[qb];
+#pragma unroll
+                        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) S[kb][qb][r] -= offset;
+                    }
+                } else if constexpr (!FOLLOW) {
+#pragma unroll
+                    for (int qb = 0; qb < NQ; ++qb) {
+                        const float row_max = quad_lane_max(mq[qb]);
+                        m_run[qb] = row_max == -INFINITY ? 0.f : row_max;
+                        off[qb] = m_run[qb] * c;
+                    }
+                } else {
+                    const bool first = u == 0;              // sets the offset, which is 0 until then
+#pragma unroll
+                    for (int qb = 0; qb < NQ; ++qb) {
+                        if (!first && __builtin_amdgcn_ballot_w64(mq[qb] > m_run[qb]) == 0) continue;
+                        const float row_max = quad_lane_max(mq[qb]);
+                        const float m_new = first ? (row_max == -INFINITY ? 0.f : row_max) : fmaxf(m_run[qb], row_max);
+                        float off_new = m_new * c;
+                        asm volatile("" : "+v"(off_new));   // one rounded number in all its uses
+                        const float alpha = first ? 1.f : __builtin_amdgcn_exp2f(off[qb] - off_new);
+                        m_run[qb] = m_new;
+                        off[qb] = off_new;
+                        l_acc[qb] *= alpha;
+                        // an offset that jumped so far that what lay behind it is lost: an infinite row sum asks for the careful pass
+                        l_acc[qb][0] = alpha == 0.f ? INFINITY : l_acc[qb][0];
+                        const float alpha_settled = settled_after_transcendental(alpha);
+#pragma unroll
+                        for (int cb = 0; cb < CB; ++cb) scale_in_place(Oacc[cb][qb], alpha_settled);
+                    }
+                }
+            }
+            bf16x8 Pb[NQ];
+#pragma unroll
+            for (int qb = 0; qb < NQ; ++qb)
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float x = CAREFUL ? S[kb][qb][e] * c : fmaf(S[kb][qb][e], c, -off[qb]);
+                        Pb[qb][4 * kb + e] = static_cast<__bf16>(__builtin_amdgcn_exp2f(x));
+                    }
+            bf16x8 ones;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) ones[e] = static_cast<__bf16>(1.0f);
+            if (more) wait_dma<GROUPS>();                   // V of this unit; the next unit's K has been requested behind it
+            else wait_dma<0>();
+            StagedTransposedProduct<D, 0> v_t;
+            v_t.prefetch(tr_addr);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int qb = 0; qb < NQ; ++qb) l_acc[qb] = mfma_16x16x32(ones, Pb[qb], l_acc[qb]);       // sums the rounded values
+            v_t.run(tr_addr, Pb, Oacc);                     // O^T += V^T P^T
+            if (more) issue_v(walk.next_row);
+        }
+    };
+
+    // (In the first pass c times the scores is exact inside the fused multiply-add and the offset rounded: what is between them is a
+    // factor common to a row's probabilities and its sum, which shows as an extreme row sum where it is extreme.)
+    // Row sums and accumulators of this wave to LDS; what asks for the careful pass is as in the kernel above.
+    constexpr float kRedoAbove = 79228162514264337593543950336.f, kRedoBelow = 5.42101086242752217e-20f;
+    constexpr uint32_t kRedoBits = KG > 4 ? 0x7d800000u : 0x7e000000u;      // 2^124, 2^125: the sum of all groups stays in range
+    auto leave_partial = [&](bool careful) __attribute__((always_inline)) {
+        uint32_t o_max = 0;
+        bool redo = false;
+#pragma unroll
+        for (int qb = 0; qb < NQ; ++qb) {
+            redo = redo || !(l_acc[qb][0] < kRedoAbove) || (n_units > 0 && l_acc[qb][0] < kRedoBelow);
+            const float m2 = n_units == 0 ? -3.0e38f : fmaxf(careful ? m_run[qb] * c : off[qb], -3.0e38f);
+            if (g4 == 0) *reinterpret_cast<float2 *>(smem + STATS + (kg * QB + 16 * qb + c16) * 8) = make_float2(m2, l_acc[qb][0]);
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) o_max = max(o_max, __float_as_uint(Oacc[cb][qb][r]) & 0x7fffffffu);
+                *reinterpret_cast<floatx4 *>(region + (qb * CB + cb) * 1024 + lane * 16) = Oacc[cb][qb];
+            }
+        }
+        const uint64_t any = __builtin_amdgcn_ballot_w64(redo || o_max >= kRedoBits);
+        if (lane == 0) *reinterpret_cast<uint32_t *>(smem + FLAGS + 4 * kg) = any != 0;
+    };
+    run_pass(std::false_type{});
+    leave_partial(false);
+    __syncthreads();
+    const uint32_t flag = lane < KG ? *reinterpret_cast<const uint32_t *>(smem + FLAGS + 4 * lane) : 0u;
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(flag != 0) != 0, 0)) {
+        __syncthreads();                                    // everyone has seen the flags and is about to start again
+        reset(-INFINITY);
+        start_walk();
+        if (n_units > 0) {
+            issue_k(walk.next_row);
+            issue_v(walk.next_row);
+        }
+        run_pass(std::true_type{});
+        leave_partial(true);
+        __syncthreads();
+    }
+
+    // ---- merge: every wave sums the groups' parts of its slices of the accumulators, in ascending order
+    const int first = kg * PER_WAVE, qb = first / CB;
+    const float2 *stats = reinterpret_cast<const float2 *>(smem + STATS) + 16 * qb + c16;
+    float m = -INFINITY, l = 0.f, weight[KG];
+#pragma unroll
+    for (int g = 0; g < KG; ++g) m = fmaxf(m, stats[g * QB].x);
+#pragma unroll
+    for (int g = 0; g < KG; ++g) {
+        weight[g] = __builtin_amdgcn_exp2f(stats[g * QB].x - m);
+        l += stats[g * QB].y * weight[g];
+    }
+    const float inv = 1.f / l;
+#pragma unroll
+    for (int j = 0; j < PER_WAVE; ++j) {
+        const int cb = first % CB + j;
+        floatx4 sum = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int g = 0; g < KG; ++g) {
+            const floatx4 x = *reinterpret_cast<const floatx4 *>(smem + g * REGION + (first + j) * 1024 + lane * 16);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) sum[r] = fmaf(x[r], weight[g], sum[r]);
+        }
+        bf16x4 ov;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) ov[r] = static_cast<__bf16>(sum[r] * inv);
+        *reinterpret_cast<bf16x4 *>(smem + OUT + (16 * qb + c16) * L::RowB + (16 * cb + 4 * g4) * 2) = ov;
+    }
+    if (p.lse != nullptr && first % CB == 0 && g4 == 0) p.lse[my_row + 16 * qb + c16] = m * 0.6931471805599453f + __logf(l);
+    __syncthreads();
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    char *out = reinterpret_cast<char *>(o + my_row * D);
+    for (int i = tid * 16; i < QB * L::RowB; i += KG * 64 * 16)
+        __builtin_nontemporal_store(*reinterpret_cast<const u32x4 *>(smem + OUT + i), reinterpret_cast<u32x4 *>(out + i));
+}
+
 // Head dimension 128, tiles of 128 tokens' multiples: one kernel without key groups, 32-key sub-blocks.  On this chip the run
 // time on real data follows the energy of the instruction stream (the package sits at its power limit and lowers
 // the clock), and the 16x16x32 shape is the cheaper one per flop: it reads and writes 4 accumulator registers per
@@ -1440,19 +1722,18 @@ hipError_t launch_x32(const void *q, const void *k, const void *v, void *o, int 
     return hipGetLastError();
 }
 
-template <int D, int QW, int KG, int WPE, bool FOLLOW, int UPS = 1>
-hipError_t launch_group(const void *q, const void *k, const void *v, void *o, int B, const sta::FwdParams &p,
-                        const sta::WindowTable &win, const sta::HeadOrder &order, hipStream_t stream)
+// The plan of a launch of query blocks of 32 * waves queries, and its workgroup ids.
+sta::FwdPlan make_plan(int waves, int B, const sta::FwdParams &p, const sta::WindowTable &win, const sta::HeadOrder &order, uint32_t *ids)
 {
     sta::FwdPlan plan;
-    const uint32_t per_head = p.N / (QW * 32), n_bh = (uint32_t)B * p.heads;
+    const uint32_t per_head = p.N / (waves * 32), n_bh = (uint32_t)B * p.heads;
     plan.total = per_head * n_bh;
     // as many rounds of chunks as eighths of a head would take, of equal length
     const uint32_t eighth = (per_head + 7) / 8, rounds = (plan.total + 8 * eighth - 1) / (8 * eighth);
     const uint32_t chunk = (plan.total + 8 * rounds - 1) / (8 * rounds);
     plan.chunk = sta::fast_div_of(chunk);
     plan.per_head = sta::fast_div_of(per_head);
-    plan.per_tile = sta::fast_div_of(p.P / (QW * 32));
+    plan.per_tile = sta::fast_div_of(p.P / (waves * 32));
     plan.pair_items = sta::fast_div_of(2 * p.n_w * p.n_t);
     plan.n_t = sta::fast_div_of(p.n_t);
     plan.batch = sta::fast_div_of((uint32_t)B);
@@ -1461,20 +1742,32 @@ hipError_t launch_group(const void *q, const void *k, const void *v, void *o, in
         plan.head[h].h = order.h[h];
         for (int a = 0; a < 3; ++a) plan.head[h].w[a] = win.w[order.h[h]][a];
     }
-    const uint32_t ids = 8 * chunk * ((plan.total + 8 * chunk - 1) / (8 * chunk));
+    *ids = 8 * chunk * ((plan.total + 8 * chunk - 1) / (8 * chunk));
+    return plan;
+}
+
+template <int D, int QW, int KG, int WPE, bool FOLLOW, int UPS = 1>
+hipError_t launch_group(const void *q, const void *k, const void *v, void *o, int B, const sta::FwdParams &p,
+                        const sta::WindowTable &win, const sta::HeadOrder &order, hipStream_t stream)
+{
+    uint32_t ids;
+    const sta::FwdPlan plan = make_plan(QW, B, p, win, order, &ids);
     sta_fwd_group_kernel<D, QW, KG, WPE, FOLLOW, UPS><<<dim3(ids), dim3(QW * KG * 64), 0, stream>>>(
         static_cast<const bf16_raw *>(q), static_cast<const bf16_raw *>(k), static_cast<const bf16_raw *>(v),
         static_cast<bf16_raw *>(o), p, plan);
     return hipGetLastError();
 }
 
-template <int D, int QW, int WPE, bool FOLLOW>
-hipError_t launch_group_count(int groups, const void *q, const void *k, const void *v, void *o, int B, const sta::FwdParams &p,
-                              const sta::WindowTable &win, const sta::HeadOrder &order, hipStream_t stream)
+template <int D, int NQ, int KG, bool FOLLOW>
+hipError_t launch_solo(const void *q, const void *k, const void *v, void *o, int B, const sta::FwdParams &p,
+                       const sta::WindowTable &win, const sta::HeadOrder &order, hipStream_t stream)
 {
-    if (groups == 4) return launch_group<D, QW, 4, WPE, FOLLOW>(q, k, v, o, B, p, win, order, stream);
-    if (groups == 2) return launch_group<D, QW, 2, WPE, FOLLOW>(q, k, v, o, B, p, win, order, stream);
-    return launch_group<D, QW, 1, WPE, FOLLOW>(q, k, v, o, B, p, win, order, stream);
+    uint32_t ids;
+    const sta::FwdPlan plan = make_plan(NQ / 2, B, p, win, order, &ids);
+    sta_fwd_solo_kernel<D, NQ, KG, D == 64 && NQ == 2 ? 4 : 2, FOLLOW><<<dim3(ids), dim3(KG * 64), 0, stream>>>(
+        static_cast<const bf16_raw *>(q), static_cast<const bf16_raw *>(k), static_cast<const bf16_raw *>(v),
+        static_cast<bf16_raw *>(o), p, plan);
+    return hipGetLastError();
 }
 
 // Units (32 keys) of the walk of a head of the launch; heads by rank, the one with the most key tiles first.
@@ -1493,53 +1786,99 @@ uint32_t longest_walk(const sta::FwdParams &p, const sta::WindowTable &win, cons
     return walk_of_rank(p, win, order, 0);
 }
 
-// Shape of the key-group kernel for a launch.
-// Waves of queries: as many as the tile allows up to four (three for 96-token multiples), because a K/V unit brought into LDS
-// serves them all; five waves leave the four SIMDs uneven (tiles of 320 tokens: 585 us with five waves, 431 with two).  Tiles of
-// 192 tokens at head dimension 64 take three, but two where the fullest CU gets fewer waves that way (with key groups: no more;
-// us, three and two waves, waves of the fullest CU in brackets: 9x40x40, window 3x3x3, two heads 79 (6), 54 (4); four 118 (9),
+// Shape of the kernel for a launch.
+// Small launches, solo: in waves of 32 queries (counted as for the key groups below) and units of the longest walk; us, key-group
+// kernel against KG = 8, 4, and where they exist 64 queries per wave with KG = 8, 4.
+// Head dimension 64, tiles of 64 tokens' multiples: 128 waves, 18 units 8.4, 8.0, 7.7, 9.5, 9.1; 128, 50 14.5, 9.3, 10.7, 13.0, 15.3;
+// 216, 108 24.2, 14.4, 17.9, 19.2, 25.7; 432, 108 24.4, 23.6, 22.3, 20.0, 25.6; 450, 54 15.1, 15.2, 13.9, 13.4, 15.9; 512, 36 11.6, 12.4,
+// 11.4, 11.7, 12.2; 648, 108 34.8, 34.0, 31.7, 37.9, 31.0; 768, 36 16.9, 17.4, 15.6, 21.5, 15.6; 1024, 18 10.8, 16.2, 13.2, 18.0, 12.2;
+// 1024, 50 22.4, 27.0, 24.4, 26.5, 21.1; 1296, 108 50, 64, 59, 62, 56.  96-token tiles: 144, 36 16.8, 9.6, 10.8; 525, 27 16.8, 16.4,
+// 14.0; 1575, 81 84, 68, 62; 2100, 81 82, 88, 79; 3150, 81 109, 126, 114.  32-token tiles: 256, 25 13.2, 8.7, 9.6; 768, 25 16.9, 16.7,
+// 14.6; 768, 9 9.5, 12.2, 9.6; 1024, 25 18.3, 20.8, 17.9.
+// Head dimension 128: 384-token tiles 216, 108 35.0, 23.1, 25.0; 432, 108 37, 45, 40; 128-token tiles 256, 36 16.6, 12.8, 12.2; 512, 36
+// 18, 25, 20; 64-token tiles 128, 50 24.3, 16.0, 18.5; 384, 50 24.9, 29.3, 23.2; 512, 18 14.0, 20.1, 13.8; 640, 50 38, 44, 39; 192-token
+// tiles 900, 54 72, 62, 49; 1350, 54 62, 91, 73; 96-token tiles 36, 36 23.6, 13.1, 14.4; 432, 36 24.8, 26.9, 21.4; 525, 27 22.8, 32, 25;
+// 32-token tiles 256, 25 25.9, 12.8, 13.1; 512, 25 26.7, 23.3, 17.3; 768, 25 27, 34, 27.
+// Key-group kernel.  Waves of queries: as many as the tile allows up to four (three for 96-token multiples), because a K/V unit
+// brought into LDS serves them all; five waves leave the four SIMDs uneven (tiles of 320 tokens: 585 us with five waves, 431 with
+// two).  Tiles of 192 tokens at head dimension 64 take three, but two where the fullest CU gets fewer waves that way (with key groups:
+// no more; us, three and two waves, waves of the fullest CU in brackets: 9x40x40, window 3x3x3, two heads 79 (6), 54 (4); four 118 (9),
 // 92 (8); twelve, one group 263 (24), 257 (22); six, one group 133 (12), 157 (12); 6x24x40, 1x3x3, four heads 18.9 (3), 21.8 (4)).
 // Two units per stage where four waves of queries share it and there are no key groups: one barrier for 64 keys (12x48x48 in
 // 384-token tiles, us, one and two units: three heads 85, 83; six 162, 157; twelve 289, 283).  With two waves or with groups the
 // larger stages or the registers cost a wave per SIMD (twelve heads, two groups 305, 362).
-// Key groups: the most, of 1, 2 and 4, with which the launch still fits the chip at once (16 waves per CU at head dimension
-// 64, 8 at 128) and a group has at least eight units to walk.  Where the longest walk is 64 units or more, heads count by their
-// walks, because it is the long ones that leave the chip idle (six heads of a 128x112 image, two of them over all of it, 242 us
-// counted by heads, 153 by walks; 9x40x40, 1x3x3, 3x5x5 and 1x1x3, six heads 245, 156; but 27 of a 32x48 image, 8 to 48 units,
-// 17.9, 20.8).  Measured around the line (us; 1, 2, 4 groups), head dimension
-// 64, 384-token tiles, 108 units: 324 waves of queries 45, 28, 24; 972 waves 62, 40, 38; 1944 waves 69, 66, 71; 2592 waves
-// 89, 94, 101.  64-token tiles, 18 units: 1024 waves 15.1, 12.6, 14.1; 2048 waves 17.3, 17.4, 22.9; 4096 waves 27.5, 30.1, 42.4.
-// Head dimension 128, 96-token tiles, about 75 units: 525 waves 50, 39, 34; 1050 waves 68, 78, 69.
+// Key groups: the most, of 1, 2 and (384-token tiles and the like at head dimension 128) 4, with which the launch still fits the chip
+// at once (16 waves per CU at head dimension 64, 8 at 128) and a group has at least eight units to walk.  Where the longest walk is 64
+// units or more, heads count by their walks, because it is the long ones that leave the chip idle (six heads of a 128x112 image, two
+// of them over all of it, 242 us counted by heads, 153 by walks; 9x40x40, 1x3x3, 3x5x5 and 1x1x3, six heads 245, 156; but 27 of a 32x48
+// image, 8 to 48 units, 17.9, 20.8).  Measured around the line (us; 1, 2, 4 groups), head dimension 64, 384-token tiles, 108 units: 972
+// waves 62, 40, 38; 1944 waves 69, 66, 71; 2592 waves 89, 94, 101.  64-token tiles, 18 units: 1024 waves 15.1, 12.6, 14.1; 2048 waves
+// 17.3, 17.4, 22.9; 4096 waves 27.5, 30.1, 42.4.  Head dimension 128, 96-token tiles, about 75 units: 525 waves 50, 39, 34; 1050 waves
+// 68, 78, 69.
 template <int D>
 hipError_t launch_groups(const void *q, const void *k, const void *v, void *o, int B, const sta::FwdParams &p,
                          const sta::WindowTable &win, const sta::HeadOrder &order, hipStream_t stream)
 {
-    const uint32_t units = longest_walk(p, win, order);
+    constexpr uint32_t kFixed = D == 64 ? 64 : 128;         // tiles of its multiples keep the offset of the first unit
+    const uint32_t units = longest_walk(p, win, order), P = p.P;
     uint64_t heads = p.heads;
     if (units >= 64) {
         uint64_t all_units = 0;
         for (uint32_t r = 0; r < p.heads; ++r) all_units += walk_of_rank(p, win, order, r);
         heads = (all_units + units - 1) / units;
     }
-    const uint64_t waves = (uint64_t)B * heads * (p.N / 32);
-    const uint64_t fits = (uint64_t)resident_workgroups(1) * (D == 64 ? 16 : 8);
-    const int groups = 4 * waves <= fits && units >= 32 ? 4 : 2 * waves <= fits && units >= 16 ? 2 : 1;
-    const uint64_t cus = resident_workgroups(1);
-    auto fullest_cu = [&](uint64_t qw) { return (waves / qw + cus - 1) / cus * qw; };          // waves of queries
-    const bool two_for_192 = D == 64 && p.P % 64 == 0 && (groups > 1 ? fullest_cu(2) <= fullest_cu(3) : 20 * fullest_cu(2) < 19 * fullest_cu(3));
-    if (p.P % 96 == 0 && p.P % 128 != 0 && !two_for_192) {
-        if (D == 64 && p.P % 64 == 0) return launch_group_count<64, 3, 3, false>(groups, q, k, v, o, B, p, win, order, stream);
-        return launch_group_count<D, 3, 3, true>(groups, q, k, v, o, B, p, win, order, stream);
+    const uint64_t cus = resident_workgroups(1), waves = (uint64_t)B * heads * (p.N / 32);
+
+    if (waves <= cus) {
+        const bool eight = units >= (D == 64 ? (P % 64 == 0 ? 24 : 16) : P % 64 == 0 ? (P % 128 == 0 ? 48 : 32) : 16);
+        if (P % kFixed == 0)
+            return eight ? launch_solo<D, 2, 8, false>(q, k, v, o, B, p, win, order, stream)
+                         : launch_solo<D, 2, 4, false>(q, k, v, o, B, p, win, order, stream);
+        return eight ? launch_solo<D, 2, 8, true>(q, k, v, o, B, p, win, order, stream)
+                     : launch_solo<D, 2, 4, true>(q, k, v, o, B, p, win, order, stream);
     }
-    if (p.P % 64 == 0) {
-        if (D == 128 && p.P % 128 == 0) return launch_group_count<128, 2, 2, false>(groups, q, k, v, o, B, p, win, order, stream);
-        if (D == 128) return launch_group_count<128, 2, 2, true>(groups, q, k, v, o, B, p, win, order, stream);
-        if (groups == 1 && p.P % 128 == 0) return launch_group<64, 4, 1, 4, false, 2>(q, k, v, o, B, p, win, order, stream);
-        return launch_group_count<64, 2, 4, false>(groups, q, k, v, o, B, p, win, order, stream);
+    if constexpr (D == 64) {
+        if (P % 64 == 0 && waves <= 2 * cus)
+            return units >= 48 ? launch_solo<64, 4, 8, false>(q, k, v, o, B, p, win, order, stream)
+                               : launch_solo<64, 2, 4, false>(q, k, v, o, B, p, win, order, stream);
+        if (P % 64 == 0 && waves <= 4 * cus && units >= 32) return launch_solo<64, 4, 4, false>(q, k, v, o, B, p, win, order, stream);
+        if (P % 64 != 0 && waves <= (P % 96 == 0 ? 8 : units >= 16 ? 3 : 2) * cus)
+            return launch_solo<64, 2, 4, true>(q, k, v, o, B, p, win, order, stream);
+    } else if (P % 128 != 0 && waves <= (P % 192 == 0 ? 4 : 2) * cus) {
+        return launch_solo<128, 2, 4, true>(q, k, v, o, B, p, win, order, stream);
+    }
+
+    const uint64_t fits = cus * (D == 64 ? 16 : 8);
+    const bool two = 2 * waves <= fits && units >= 16;
+    auto fullest_cu = [&](uint64_t qw) { return (waves / qw + cus - 1) / cus * qw; };          // waves of queries
+    const bool two_for_192 = D == 64 && P % 64 == 0 && (two ? fullest_cu(2) <= fullest_cu(3) : 20 * fullest_cu(2) < 19 * fullest_cu(3));
+    if (P % 96 == 0 && P % 128 != 0 && !two_for_192) {
+        if constexpr (D == 64) {
+            if (P % 64 != 0) return launch_group<64, 3, 1, 3, true>(q, k, v, o, B, p, win, order, stream);
+            return two ? launch_group<64, 3, 2, 3, false>(q, k, v, o, B, p, win, order, stream)
+                       : launch_group<64, 3, 1, 3, false>(q, k, v, o, B, p, win, order, stream);
+        } else {
+            return two ? launch_group<128, 3, 2, 3, true>(q, k, v, o, B, p, win, order, stream)
+                       : launch_group<128, 3, 1, 3, true>(q, k, v, o, B, p, win, order, stream);
+        }
+    }
+    if (P % 64 == 0) {
+        if constexpr (D == 128) {
+            if (P % 128 != 0)
+                return two ? launch_group<128, 2, 2, 2, true>(q, k, v, o, B, p, win, order, stream)
+                           : launch_group<128, 2, 1, 2, true>(q, k, v, o, B, p, win, order, stream);
+            if (4 * waves <= fits && units >= 32) return launch_group<128, 2, 4, 2, false>(q, k, v, o, B, p, win, order, stream);
+            return two ? launch_group<128, 2, 2, 2, false>(q, k, v, o, B, p, win, order, stream)
+                       : launch_group<128, 2, 1, 2, false>(q, k, v, o, B, p, win, order, stream);
+        } else {
+            if (two) return launch_group<64, 2, 2, 4, false>(q, k, v, o, B, p, win, order, stream);
+            return P % 128 == 0 ? launch_group<64, 4, 1, 4, false, 2>(q, k, v, o, B, p, win, order, stream)
+                                : launch_group<64, 2, 1, 4, false>(q, k, v, o, B, p, win, order, stream);
+        }
     }
     // other multiples of 32 tokens: one wave of queries, whose LDS stages then limit a CU to four such workgroups at head
     // dimension 128, with or without key groups (525 waves: 59 us, two groups 74)
-    if (D == 64 && groups > 1) return launch_group<64, 1, 2, 2, true>(q, k, v, o, B, p, win, order, stream);
+    if (D == 64 && two) return launch_group<64, 1, 2, 2, true>(q, k, v, o, B, p, win, order, stream);
     return launch_group<D, 1, 1, D == 64 ? 3 : 1, true>(q, k, v, o, B, p, win, order, stream);
 }
 

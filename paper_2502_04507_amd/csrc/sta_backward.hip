@@ -242,13 +242,6 @@ __device__ __forceinline__ void store_columns(char *wave_lds, const floatx4 (&ac
 
 constexpr int max_of(int a, int b) { return a > b ? a : b; }
 
-// Waits until at most PENDING of the wave's own requests are outstanding (they complete in order).
-template <int PENDING>
-__device__ __forceinline__ void wait_dma()
-{
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PENDING) : "memory");
-}
-
 // ---------------------------------------------------------------------------------------------------------
 // dQ.  One workgroup of QW waves per 32 * QW queries (times G walk groups); a lane holds query column c16 of its wave's two
 // 16-query blocks.  At head dimension 128 211-212 registers, two waves per SIMD; at 64 128 and four (8 bytes of scratch in the

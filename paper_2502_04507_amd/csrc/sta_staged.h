@@ -175,6 +175,13 @@ __device__ __forceinline__ void stage_group(const char *src, char *dst, int lane
     }
 }
 
+// Waits until at most PENDING of the wave's own requests are outstanding (they complete in order).
+template <int PENDING>
+__device__ __forceinline__ void wait_dma()
+{
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PENDING) : "memory");
+}
+
 // Layout of an operand that is read by rows only: groups (one DMA instruction) 1024 + 64 bytes apart, the chunk's two
 // low bits XORed with the row inside the group (256-byte rows) or with half of it (128-byte rows).
 //  - 256-byte rows: the four rows of a group land in four 16-byte positions of one 64-byte quarter, and consecutive
