@@ -1,15 +1,20 @@
-"""ctypes binding of libsta.so.  Same names as the C entry points.
+"""Binding of libsta.so.  Same names as the C entry points.
 
 Tensors are torch tensors used purely as device-memory handles (data_ptr);
 the stream is torch's current HIP stream unless one is given.
+
+The permutations, sta_forward, sta_forward_lse and sta_backward go through the extension sta_fastcall where their arguments are
+ordinary ones, everything else (and every error message) through ctypes.
 """
 import ctypes
+import importlib
 import os
 
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB = None
+_FAST = None
 
 STA_BF16, STA_F32 = 0, 1
 STA_MASK_STA, STA_MASK_NATTEN = 0, 1
@@ -35,7 +40,7 @@ def lib_path() -> str:
 
 def load_library():
     """Load libsta.so; raises if it has not been built (no fallback exists)."""
-    global _LIB
+    global _LIB, _FAST
     if _LIB is not None:
         return _LIB
     path = lib_path()
@@ -90,8 +95,25 @@ def load_library():
     lib.sta_strerror.restype = ctypes.c_char_p
     lib.sta_version.argtypes = []
     lib.sta_version.restype = ci
-    _LIB = lib
+    try:
+        fast = importlib.import_module(__package__ + ".sta_fastcall")
+    except ImportError as e:
+        raise ImportError("sta_fastcall.so is not built or does not load: run `python -m paper_2502_04507_amd.build_lib` "
+                          "(or __graft_entry__.build()) first") from e
+    if _raw_stream is not None and _current_device is not None:     # unbound, it leaves every call to ctypes
+        fast.bind(*[ctypes.cast(getattr(lib, name), vp).value for name in _FAST_ENTRIES], _current_device, _raw_stream)
+    _LIB, _FAST = lib, fast
     return lib
+
+
+_FAST_ENTRIES = ("sta_tile_permute", "sta_untile", "sta_forward", "sta_forward_lse", "sta_backward")
+
+
+def _fast():
+    """The extension: its functions return a status, or None for arguments that they leave to the general path."""
+    if _FAST is None:
+        load_library()
+    return _FAST
 
 
 def sta_strerror(status: int) -> str:
@@ -181,11 +203,21 @@ def _permute(fn_name, src, dst, grid, tile, stream):
 
 def sta_tile_permute(src, dst, grid, tile, stream=None):
     """Raster [B,H,N,D] -> tiled [B,H,N,D] (dst preallocated; dtype may differ: fused cast)."""
+    if stream is None:
+        status = _fast().tile_permute(src, dst, grid, tile)
+        if status is not None:
+            _check(status)
+            return dst
     return _permute("sta_tile_permute", src, dst, grid, tile, stream)
 
 
 def sta_untile(src, dst, grid, tile, stream=None):
     """Tiled -> raster."""
+    if stream is None:
+        status = _fast().untile(src, dst, grid, tile)
+        if status is not None:
+            _check(status)
+            return dst
     return _permute("sta_untile", src, dst, grid, tile, stream)
 
 
@@ -196,6 +228,11 @@ def sta_workspace_bytes(B, H, D, grid, tile) -> int:
 def sta_forward(q_tiled, k_tiled, v_tiled, o_tiled, grid, tile, window_tiles, scale=0.0, workspace=None,
                 stream=None):
     """STA forward on tiled bf16 [B,H,N,D] tensors; window_tiles: H entries of (t,h,w) in tiles."""
+    if stream is None:
+        status = _fast().forward(q_tiled, k_tiled, v_tiled, o_tiled, grid, tile, window_tiles, scale, workspace)
+        if status is not None:
+            _check(status)
+            return o_tiled
     lib = load_library()
     B, H, N, D = _check_bf16((q_tiled, k_tiled, v_tiled, o_tiled),
                              "expect four bf16 [B, H, N, D] tensors of equal shape")
@@ -226,6 +263,11 @@ def sta_forward_general(q_tiled, k_tiled, v_tiled, o_tiled, grid, tile, mask_kin
 
 def sta_forward_lse(q_tiled, k_tiled, v_tiled, o_tiled, lse_tiled, grid, tile, window_tiles, scale=0.0, stream=None):
     """sta_forward that also writes lse_tiled (float32 [B,H,N], tiled order): ln of each row's softmax denominator."""
+    if stream is None:
+        status = _fast().forward_lse(q_tiled, k_tiled, v_tiled, o_tiled, lse_tiled, grid, tile, window_tiles, scale)
+        if status is not None:
+            _check(status)
+            return o_tiled, lse_tiled
     lib = load_library()
     B, H, N, D = _check_bf16((q_tiled, k_tiled, v_tiled, o_tiled),
                              "expect four bf16 [B, H, N, D] tensors of equal shape")
@@ -247,6 +289,12 @@ def sta_backward(q_tiled, k_tiled, v_tiled, o_tiled, d_o_tiled, lse_tiled, d_q_t
                  window_tiles, workspace, scale=0.0, stream=None):
     """Gradients of sta_forward.  All tensors bf16 [B,H,N,D] in tiled order except lse_tiled (float32 [B,H,N]) and
     workspace (any dtype, at least sta_backward_workspace_bytes bytes)."""
+    if stream is None:
+        status = _fast().backward(q_tiled, k_tiled, v_tiled, o_tiled, d_o_tiled, lse_tiled, d_q_tiled, d_k_tiled, d_v_tiled, grid,
+                                  tile, window_tiles, workspace, scale)
+        if status is not None:
+            _check(status)
+            return d_q_tiled, d_k_tiled, d_v_tiled
     lib = load_library()
     B, H, N, D = _check_bf16((q_tiled, k_tiled, v_tiled, o_tiled, d_o_tiled, d_q_tiled, d_k_tiled, d_v_tiled),
                              "expect bf16 [B, H, N, D] tensors of equal shape")

@@ -1,8 +1,10 @@
 """Build libsta.so (the C-ABI HIP library) and libsta_mfma_probe.so (a matrix-instruction-only kernel that the
-benchmark alone loads) for gfx950 with hipcc, in-tree."""
+benchmark alone loads) for gfx950 with hipcc, and sta_fastcall.so (the CPython extension that calls the library's hot entry
+points) with the host compiler, in-tree."""
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -12,6 +14,9 @@ BUILD_DIR = os.path.join(HERE, "_build")
 SOURCES = ["sta_api.hip", "sta_permute.hip", "sta_attention.hip", "sta_reduce.hip", "sta_backward.hip"]
 PROBE_SOURCE = "bench_mfma_probe.hip"
 PROBE_OUT = os.path.join(HERE, "libsta_mfma_probe.so")
+
+FASTCALL_SOURCE = "sta_fastcall.cpp"
+FASTCALL_OUT = os.path.join(HERE, "sta_fastcall.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -42,10 +47,26 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _build_fastcall() -> None:
+    import torch
+    root = os.path.dirname(torch.__file__)
+    include, lib = os.path.join(root, "include"), os.path.join(root, "lib")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-isystem", include, "-isystem",
+           os.path.join(include, "torch", "csrc", "api", "include"), "-I", sysconfig.get_paths()["include"],
+           os.path.join(CSRC, FASTCALL_SOURCE), "-o", FASTCALL_OUT, "-L", lib, "-ltorch_python", "-ltorch_cpu", "-lc10",
+           "-Wl,-rpath," + lib]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("the host compiler failed for %s:\n%s\n%s" % (FASTCALL_SOURCE, r.stdout, r.stderr))
+
+
 def build(verbose: bool = False) -> str:
     os.makedirs(BUILD_DIR, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=len(SOURCES) + 1) as ex:
+    with ThreadPoolExecutor(max_workers=len(SOURCES) + 2) as ex:
+        fastcall = ex.submit(_build_fastcall)
         objs = list(ex.map(_compile, SOURCES + [PROBE_SOURCE]))
+        fastcall.result()
     for out, members in ((OUT, objs[:-1]), (PROBE_OUT, objs[-1:])):
         cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", out] + members
         r = subprocess.run(cmd, capture_output=True, text=True)
@@ -53,6 +74,8 @@ def build(verbose: bool = False) -> str:
             raise RuntimeError("link failed:\n%s\n%s" % (r.stdout, r.stderr))
         if verbose:
             print(out)
+    if verbose:
+        print(FASTCALL_OUT)
     return OUT
 
 
