@@ -333,57 +333,6 @@ __global__ __launch_bounds__(NW * 64) void sta_fwd_kernel(const bf16_raw *__rest
 }
 
 
-// Work items of the head-dim-128 kernels.  The hardware deals workgroup ids round-robin over the 8 XCDs (each with
-// its own L2) and, inside an XCD, starts them in increasing order.  Every (batch, head) slice is cut into 8
-// contiguous ranges of query blocks, one per XCD, so each XCD carries one eighth of every head whatever the
-// per-head windows are (load balance: with mixed per-head windows this halved the launch time), and its resident
-// workgroups are neighbouring query blocks of one head (shared K/V in L2).  Heads are visited in descending cost
-// order, so the tail of the launch is made of cheap items.  The price is that neighbouring ranges of a head fetch
-// the same border K/V tiles into two L2s: measured HBM-side reads rose by about 10 % against giving each XCD
-// whole heads.
-// Inside a head the query tiles are scheduled by pairs of tile rows (h), then w, then the row of the pair, then t
-// fastest, so that the ~32 tiles resident on an XCD at one time form a compact 3-D block, (all t) x (2 h) x
-// (about 3 w), and share key tiles along all three axes (measured: reads past L2 9.8 -> 6.4 GB per launch against
-// plain tile-id order, 12.81 -> 12.74 ms).
-struct FwdItem {
-    bool valid;
-    size_t bh;          // b * H + head
-    uint32_t qblock;    // index of the QB-query block inside the head
-    uint32_t h_local;   // head inside this launch
-};
-
-// id: position in the launch's list of work items (a workgroup id, or the item a split workgroup belongs to).
-template <int QB>
-__device__ __forceinline__ FwdItem fwd_item_of(uint32_t id, const sta::FwdParams &p, const sta::HeadOrder &order,
-                                               uint32_t n_bh)
-{
-    FwdItem it;
-    it.valid = false;
-    const uint32_t xcd = id & 7;
-    const uint32_t slot = id >> 3;
-    const uint32_t qblocks_per_head = p.N / QB;
-    const uint32_t seg_lo = (xcd * qblocks_per_head) >> 3;
-    const uint32_t seg_len = (((xcd + 1) * qblocks_per_head) >> 3) - seg_lo;
-    if (seg_len == 0) return it;
-    const uint32_t bh_rank = slot / seg_len;
-    if (bh_rank >= n_bh) return it;
-    const uint32_t pos = seg_lo + (slot - bh_rank * seg_len);
-    const uint32_t per_tile = p.P / QB;
-    const uint32_t sched = pos / per_tile, sub = pos - sched * per_tile;
-    const uint32_t pair_items = 2 * p.n_w * p.n_t;
-    const uint32_t hp = sched / pair_items;
-    uint32_t rem = sched - hp * pair_items;
-    const uint32_t rows = (p.n_h - 2 * hp) < 2 ? (p.n_h - 2 * hp) : 2;
-    const uint32_t w_ = rem / (rows * p.n_t);
-    rem -= w_ * rows * p.n_t;
-    const uint32_t hh = rem / p.n_t, t_ = rem - hh * p.n_t;
-    it.qblock = ((t_ * p.n_h + 2 * hp + hh) * p.n_w + w_) * per_tile + sub;
-    it.h_local = order.h[bh_rank / (n_bh / p.heads)];     // batch entries of one head are adjacent
-    it.bh = (size_t)(bh_rank % (n_bh / p.heads)) * p.H + p.head_base + it.h_local;
-    it.valid = true;
-    return it;
-}
-
 // Work splitting below one query block.  The last workgroups of a launch would run on a mostly idle chip (the
 // item count is rarely a multiple of the number of workgroups the chip holds).  The host therefore turns the
 // items from `split_first` on into `split_parts` workgroups each; part j walks the sub-blocks
@@ -393,12 +342,19 @@ __device__ __forceinline__ FwdItem fwd_item_of(uint32_t id, const sta::FwdParams
 template <int D>
 __host__ __device__ __forceinline__ size_t split_part_floats(int QB) { return (size_t)QB * (D + 2); }
 
-// The same for the key-group kernel, with every division by a launch constant prepared by the host (found by division in the
-// kernel, the item, its box and the start of the walk took 7500 cycles of a workgroup that has 24,000 cycles of work to do,
-// a 64-token image tile at window 3x3; now 2000, most of it waiting for the kernel arguments) and two differences.  The
-// launch's items, taken head after head in scheduling order, are dealt to the XCDs in chunks of about an eighth of a head:
-// where a head has only a few items, whole eighths of every head would leave XCDs without work (nine items: one XCD gets
-// two, the others one).  And the tile's coordinates come out directly.
+// Work items.  The hardware deals workgroup ids round-robin over the 8 XCDs (each with its own L2) and, inside an XCD, starts
+// them in increasing order.  The launch's items, taken head after head in scheduling order, are dealt to the XCDs in chunks of
+// about an eighth of a head: each XCD carries one eighth of every head whatever the per-head windows are (load balance: with
+// mixed per-head windows this halved the launch time), its resident workgroups are neighbouring query blocks of one head (shared
+// K/V in L2), and where a head has only a few items no XCD gets one more of every head than the others (eighteen 384-token items
+// a head, 28 heads, 1x2x3: 249 us with exact eighths of every head, which gave two XCDs three rounds of workgroups where two are
+// needed, 193 in chunks; fifteen of 25 items 281, 219).  Heads are visited in descending cost order, so the tail of the launch is made of cheap items.
+// Inside a head the query tiles are scheduled by pairs of tile rows (h), then w, then the row of the pair, then t fastest, so that
+// the ~32 tiles resident on an XCD at one time form a compact 3-D block, (all t) x (2 h) x (about 3 w), and share key tiles along
+// all three axes (measured: reads past L2 9.8 -> 6.4 GB per launch against plain tile-id order, 12.81 -> 12.74 ms).
+// Every division by a launch constant is prepared by the host: found by division in the kernel, the item, its box and the start
+// of the walk took 7500 cycles of a workgroup that has 24,000 cycles of work to do, a 64-token image tile at window 3x3; now 2000,
+// most of it waiting for the kernel arguments.
 struct GroupItem {
     bool valid;
     size_t bh;
@@ -1134,8 +1090,7 @@ __global__ __launch_bounds__(NW * 64, MINB) void sta_fwd_x32_kernel(const bf16_r
                                                                  const bf16_raw *__restrict__ k,
                                                                  const bf16_raw *__restrict__ v,
                                                                  bf16_raw *__restrict__ o, sta::FwdParams p,
-                                                                 sta::WindowTable win, sta::HeadOrder order,
-                                                                 uint32_t n_bh)
+                                                                 sta::FwdPlan plan)
 {
     constexpr int D = 128;
     static_assert(KB == 32, "keys per sub-block");
@@ -1161,7 +1116,7 @@ __global__ __launch_bounds__(NW * 64, MINB) void sta_fwd_x32_kernel(const bf16_r
     constexpr int OUT_BYTES = QB * ROWB;
     __shared__ __attribute__((aligned(1024))) char smem[STAGES * STAGE_BYTES > OUT_BYTES ? STAGES * STAGE_BYTES : OUT_BYTES];
 
-    // ---- work item (see fwd_item_of), possibly one part of a split item
+    // ---- work item (see group_item_of), possibly one part of a split item
     uint32_t item_id = blockIdx.x, part = 0;
     const bool is_part = blockIdx.x >= p.split_first;
     if (is_part) {
@@ -1169,13 +1124,11 @@ __global__ __launch_bounds__(NW * 64, MINB) void sta_fwd_x32_kernel(const bf16_r
         item_id = p.split_first + idx / p.split_parts;
         part = idx - (item_id - p.split_first) * p.split_parts;
     }
-    const FwdItem item = fwd_item_of<QB>(item_id, p, order, n_bh);
+    const GroupItem item = group_item_of(item_id, p, plan);
     if (!item.valid) return;
-    const uint32_t qblock = item.qblock, h_local = item.h_local;
+    const uint32_t qblock = item.qblock;
     const size_t bh = item.bh;
-    const uint32_t q_tile = (qblock * QB) / p.P;
-    const StaBox box = sta_key_tile_box_of(p.n_t, p.n_h, p.n_w, win.w[h_local][0], win.w[h_local][1],
-                                           win.w[h_local][2], q_tile);
+    const StaBox box = item.box;
 
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1620,42 +1573,82 @@ __global__ __launch_bounds__(NW * 64, MINB) void sta_fwd_x32_kernel(const bf16_r
     }
 }
 
-// Merges the parts of every split item: one wave per query row, two channels per lane.  With m the largest of
-// the parts' offsets (base-2 units):  O = sum_j 2^(m_j - m) O_j / sum_j 2^(m_j - m) l_j, parts in ascending order.
+// Merges the parts of every split item.  With m the largest of the parts' offsets (base-2 units):
+// O = sum_j 2^(m_j - m) O_j / sum_j 2^(m_j - m) l_j, parts in ascending order.  A wave takes eight query rows, half a wave a row,
+// four channels a lane, with four rows' loads in flight.  (One row per wave before: 18,432 workgroups for 48 items of 384 queries in
+// two parts, each of which finds its item first: 19 us, now 15, and 9 at best.)
 template <int D, int QB>
-__global__ __launch_bounds__(256) void sta_fwd_combine_kernel(bf16_raw *__restrict__ o, sta::FwdParams p,
-                                                              sta::HeadOrder order, uint32_t n_bh)
+__global__ __launch_bounds__(256) void sta_fwd_combine_kernel(bf16_raw *__restrict__ o, sta::FwdParams p, sta::FwdPlan plan)
 {
-    static_assert(D == 128, "two channels per lane");
+    static_assert(D == 128, "four channels per lane");
+    constexpr int ROWS = 4;                                    // per lane, two rows apart
     const uint32_t item_id = p.split_first + blockIdx.y;
-    const FwdItem item = fwd_item_of<QB>(item_id, p, order, n_bh);
+    const GroupItem item = group_item_of(item_id, p, plan);
     if (!item.valid) return;
-    const int row = blockIdx.x * 4 + (threadIdx.x >> 6);       // query inside the block
     const int lane = threadIdx.x & 63;
+    const int row0 = blockIdx.x * 32 + (threadIdx.x >> 6) * 8 + (lane >> 5), channel = 4 * (lane & 31);
     const float *ws = p.split_ws + (size_t)blockIdx.y * p.split_parts * split_part_floats<D>(QB);
-    float m = -INFINITY;
-    for (uint32_t j = 0; j < p.split_parts; ++j) m = fmaxf(m, ws[j * split_part_floats<D>(QB) + (size_t)QB * D + row]);
-    float l = 0.f, a0 = 0.f, a1 = 0.f;
+    float m[ROWS], l[ROWS];
+    floatx4 acc[ROWS];
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+        m[r] = -INFINITY;
+        l[r] = 0.f;
+        acc[r] = floatx4{0.f, 0.f, 0.f, 0.f};
+    }
+    for (uint32_t j = 0; j < p.split_parts; ++j)
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) m[r] = fmaxf(m[r], ws[j * split_part_floats<D>(QB) + (size_t)QB * D + row0 + 2 * r]);
     for (uint32_t j = 0; j < p.split_parts; ++j) {
         const float *part = ws + j * split_part_floats<D>(QB);
-        const float w = exp2f(part[(size_t)QB * D + row] - m);
-        l += w * part[(size_t)QB * D + QB + row];
-        const float2 x = *reinterpret_cast<const float2 *>(part + (size_t)row * D + 2 * lane);
-        a0 += w * x.x;
-        a1 += w * x.y;
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            const int row = row0 + 2 * r;
+            const floatx4 x = *reinterpret_cast<const floatx4 *>(part + (size_t)row * D + channel);
+            const float w = exp2f(part[(size_t)QB * D + row] - m[r]);
+            l[r] += w * part[(size_t)QB * D + QB + row];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) acc[r][c] += w * x[c];
+        }
     }
-    const float inv = 1.f / l;
-    const size_t out_row = item.bh * p.N + (size_t)item.qblock * QB + row;
-    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-    bf16x2 ov;
-    ov[0] = static_cast<__bf16>(a0 * inv);
-    ov[1] = static_cast<__bf16>(a1 * inv);
-    *reinterpret_cast<bf16x2 *>(o + out_row * D + 2 * lane) = ov;
-    if (p.lse != nullptr && lane == 0) p.lse[out_row] = m * 0.6931471805599453f + __logf(l);
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+        const float inv = 1.f / l[r];
+        const size_t out_row = item.bh * p.N + (size_t)item.qblock * QB + row0 + 2 * r;
+        bf16x4 ov;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) ov[c] = static_cast<__bf16>(acc[r][c] * inv);
+        __builtin_nontemporal_store(ov, reinterpret_cast<bf16x4 *>(o + out_row * D + channel));
+        if (p.lse != nullptr && (lane & 31) == 0) p.lse[out_row] = m[r] * 0.6931471805599453f + __logf(l[r]);
+    }
 }
 
 // Host side of the work splitting: how many workgroups the chip holds at once.
 inline uint32_t resident_workgroups(int minb) { return sta::compute_units() * (uint32_t)minb; }
+
+// The plan of a launch of query blocks of 32 * waves queries, and its workgroup ids.
+sta::FwdPlan make_plan(int waves, int B, const sta::FwdParams &p, const sta::WindowTable &win, const sta::HeadOrder &order, uint32_t *ids)
+{
+    sta::FwdPlan plan;
+    const uint32_t per_head = p.N / (waves * 32), n_bh = (uint32_t)B * p.heads;
+    plan.total = per_head * n_bh;
+    // as many rounds of chunks as eighths of a head would take, of equal length
+    const uint32_t eighth = (per_head + 7) / 8, rounds = (plan.total + 8 * eighth - 1) / (8 * eighth);
+    const uint32_t chunk = (plan.total + 8 * rounds - 1) / (8 * rounds);
+    plan.chunk = sta::fast_div_of(chunk);
+    plan.per_head = sta::fast_div_of(per_head);
+    plan.per_tile = sta::fast_div_of(p.P / (waves * 32));
+    plan.pair_items = sta::fast_div_of(2 * p.n_w * p.n_t);
+    plan.n_t = sta::fast_div_of(p.n_t);
+    plan.batch = sta::fast_div_of((uint32_t)B);
+    plan.sub_per_tile = sta::fast_div_of(p.P / kSub);
+    for (uint32_t h = 0; h < p.heads; ++h) {
+        plan.head[h].h = order.h[h];
+        for (int a = 0; a < 3; ++a) plan.head[h].w[a] = win.w[order.h[h]][a];
+    }
+    *ids = 8 * chunk * ((plan.total + 8 * chunk - 1) / (8 * chunk));
+    return plan;
+}
 
 template <int NW, int KB, int STAGES, int MINB>
 hipError_t launch_x32(const void *q, const void *k, const void *v, void *o, int B, const sta::FwdParams &p_in,
@@ -1664,10 +1657,8 @@ hipError_t launch_x32(const void *q, const void *k, const void *v, void *o, int 
 {
     constexpr int D = 128, QB = NW * 32;
     sta::FwdParams p = p_in;
-    const uint32_t qblocks_per_head = p.N / QB;
-    const uint32_t max_seg = (qblocks_per_head + 7) / 8;          // longest of the 8 per-XCD ranges
-    const uint32_t n_bh = (uint32_t)B * p.heads;
-    const uint32_t ids = 8 * max_seg * n_bh;                      // item ids; some of them name no item
+    uint32_t ids;                                                 // item ids; some of them name no item
+    const sta::FwdPlan plan = make_plan(NW, B, p, win, order, &ids);
     p.split_first = ids;
     p.split_parts = 1;
     p.split_ws = nullptr;
@@ -1675,14 +1666,11 @@ hipError_t launch_x32(const void *q, const void *k, const void *v, void *o, int 
     if (split_ws != nullptr) {
         // Items beyond the last full round of workgroups are split so that their parts fill the chip once.
         auto names_item = [&](uint32_t id) {
-            const uint32_t xcd = id & 7, slot = id >> 3;
-            const uint32_t seg_lo = (xcd * qblocks_per_head) >> 3;
-            const uint32_t seg_len = (((xcd + 1) * qblocks_per_head) >> 3) - seg_lo;
-            return seg_len != 0 && slot / seg_len < n_bh;
+            const uint32_t slot = id >> 3, chunk = slot / plan.chunk.d;
+            return (chunk * 8 + (id & 7)) * plan.chunk.d + (slot - chunk * plan.chunk.d) < plan.total;
         };
         const uint32_t capacity = resident_workgroups(MINB);
-        const uint64_t items = (uint64_t)qblocks_per_head * n_bh;
-        const uint32_t tail = (uint32_t)(items % capacity);
+        const uint32_t tail = plan.total % capacity;
         if (tail != 0 && 2 * tail <= capacity) {
             uint32_t parts = capacity / tail;
             // a part should keep at least four sub-blocks of the cheapest item of the launch
@@ -1715,35 +1703,11 @@ hipError_t launch_x32(const void *q, const void *k, const void *v, void *o, int 
     dim3 grid(p.split_first + split_items * p.split_parts), block(NW * 64);
     sta_fwd_x32_kernel<NW, KB, STAGES, MINB, false><<<grid, block, 0, stream>>>(
         static_cast<const bf16_raw *>(q), static_cast<const bf16_raw *>(k), static_cast<const bf16_raw *>(v),
-        static_cast<bf16_raw *>(o), p, win, order, n_bh);
+        static_cast<bf16_raw *>(o), p, plan);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || split_items == 0) return e;
-    sta_fwd_combine_kernel<D, QB><<<dim3(QB / 4, split_items), dim3(256), 0, stream>>>(static_cast<bf16_raw *>(o), p, order, n_bh);
+    sta_fwd_combine_kernel<D, QB><<<dim3(QB / 32, split_items), dim3(256), 0, stream>>>(static_cast<bf16_raw *>(o), p, plan);
     return hipGetLastError();
-}
-
-// The plan of a launch of query blocks of 32 * waves queries, and its workgroup ids.
-sta::FwdPlan make_plan(int waves, int B, const sta::FwdParams &p, const sta::WindowTable &win, const sta::HeadOrder &order, uint32_t *ids)
-{
-    sta::FwdPlan plan;
-    const uint32_t per_head = p.N / (waves * 32), n_bh = (uint32_t)B * p.heads;
-    plan.total = per_head * n_bh;
-    // as many rounds of chunks as eighths of a head would take, of equal length
-    const uint32_t eighth = (per_head + 7) / 8, rounds = (plan.total + 8 * eighth - 1) / (8 * eighth);
-    const uint32_t chunk = (plan.total + 8 * rounds - 1) / (8 * rounds);
-    plan.chunk = sta::fast_div_of(chunk);
-    plan.per_head = sta::fast_div_of(per_head);
-    plan.per_tile = sta::fast_div_of(p.P / (waves * 32));
-    plan.pair_items = sta::fast_div_of(2 * p.n_w * p.n_t);
-    plan.n_t = sta::fast_div_of(p.n_t);
-    plan.batch = sta::fast_div_of((uint32_t)B);
-    plan.sub_per_tile = sta::fast_div_of(p.P / kSub);
-    for (uint32_t h = 0; h < p.heads; ++h) {
-        plan.head[h].h = order.h[h];
-        for (int a = 0; a < 3; ++a) plan.head[h].w[a] = win.w[order.h[h]][a];
-    }
-    *ids = 8 * chunk * ((plan.total + 8 * chunk - 1) / (8 * chunk));
-    return plan;
 }
 
 template <int D, int QW, int KG, int WPE, bool FOLLOW, int UPS = 1>
