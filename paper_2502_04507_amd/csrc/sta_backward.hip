@@ -670,7 +670,7 @@ void sta_bwd_dkv_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restri
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// dK, dV at head dimension 128 on tiles of 96 and 32 tokens' multiples.  One workgroup of 2 * NPAIR waves per 32 * NPAIR keys
+// dK, dV at head dimension 128 on tiles of 96 and 32 tokens' multiples, and where the shapes above would half fill the chip.  One workgroup of 2 * NPAIR waves per 32 * NPAIR keys
 // (times G walk groups).  Each 32-key column block is served by a PAIR of waves: the first holds K and accumulates dV (S = Q K^T,
 // P, dV^T += dO^T P), the second holds V and accumulates dK (dP = dO V^T, dS = P o (dP - delta), dK^T += Q^T dS).  P goes from the
 // first to the second through LDS in fp32.  165-172 registers, three waves per SIMD: on these tiles the two waves per SIMD of
@@ -918,7 +918,8 @@ BwdPlan make_plan(const BwdArgs &a, uint32_t cols, bool row_major, bool longest_
     plan.slices = sta::fast_div_of((uint32_t)a.B * p.heads);
     plan.row_major = row_major;
     plan.longest_first = longest_first;
-    if (chunk > (plan.total + 7) / 8) chunk = (plan.total + 7) / 8;
+    const uint64_t rounds = (plan.total + 8 * (uint64_t)chunk - 1) / (8 * (uint64_t)chunk);       // of chunks over the XCDs
+    if (20 * 8 * rounds * chunk > 21 * (uint64_t)plan.total) chunk = (uint32_t)((plan.total + 8 * rounds - 1) / (8 * rounds));
     plan.chunk = sta::fast_div_of(chunk);
     plan.per_tile = sta::fast_div_of(per_tile);
     plan.n_h = sta::fast_div_of(p.n_h);
@@ -1059,6 +1060,12 @@ hipError_t dispatch_dkv(const BwdArgs &a)
     if (P % 64 != 0) {
         if constexpr (D == 128) return P % 96 == 0 ? launch_dkv_pairs<3, 2>(a) : launch_dkv_pairs<1, 1>(a);
         else return P % 96 == 0 ? launch_dkv<64, 3, 1>(a) : waves <= 4 * cus ? launch_dkv<64, 1, 2>(a) : launch_dkv<64, 1, 1>(a);
+    }
+    // One round of six pairs, at least four fifths full: half a wave's products per wave fill a CU where whole ones leave it half
+    // empty in the same time (30x24x32, two heads of 128 (1440, 720) 1495, 1589; 12x24x24, six (1296, 108) 259, 262).
+    if constexpr (D == 128) {
+        const uint64_t blocks = waves / 6;
+        if (P % 384 == 0 && blocks <= cus && 5 * blocks >= 4 * cus) return launch_dkv_pairs<6, 1>(a);
     }
     if (P % 128 == 0) return waves <= (P == 128 ? 24 : 6) * cus ? launch_dkv<D, 2, 2>(a) : launch_dkv<D, 4, 1, D == 64 ? 2 : 1>(a);
     return waves <= 8 * cus || (units >= 32 && (D == 64 || waves <= 32 * cus)) ? launch_dkv<D, 2, 2>(a) : launch_dkv<D, 2, 1>(a);
