@@ -90,6 +90,10 @@ int permute_common(const void *src, void *dst, int src_dt, int dst_dt, int B, in
     p.parts = (uint32_t)((cpt + p.span - 1) / p.span);
     if (tiles * p.parts >= ((uint64_t)1 << 31)) return STA_ERR_SHAPE;
     const uint32_t blocks = (uint32_t)(tiles * p.parts);
+    p.by_parts = sta::fast_div_of(p.parts);
+    p.by_tiles = sta::fast_div_of(p.n_tiles);
+    p.by_n_w = sta::fast_div_of(p.n_w);
+    p.by_n_h = sta::fast_div_of(p.n_h);
     hipError_t e = sta::launch_permute(src, dst, src_dt == STA_F32, dst_dt == STA_F32, to_tiled, p, blocks,
                                        static_cast<hipStream_t>(hip_stream));
     return e == hipSuccess ? STA_OK : STA_ERR_HIP;

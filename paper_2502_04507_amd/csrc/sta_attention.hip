@@ -445,6 +445,7 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
     constexpr int SMEM = KG * GROUP_B > QW * WAVE_OUT ? (KG * GROUP_B > MERGE_B ? KG * GROUP_B : MERGE_B)
                                                       : (QW * WAVE_OUT > MERGE_B ? QW * WAVE_OUT : MERGE_B);
     __shared__ __attribute__((aligned(1024))) char smem[SMEM];
+    __shared__ uint32_t redo_of[QW * KG];
 
     const GroupItem item = group_item_of(blockIdx.x, p, plan);
     if (!item.valid) return;
@@ -684,7 +685,9 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
     constexpr float kRedoAbove = 79228162514264337593543950336.f, kRedoBelow = 5.42101086242752217e-20f;
     // Accumulators that have left the range; those of key groups from 2^125 on, so that the sum of four stays in it.
     constexpr uint32_t kRedoBits = KG == 1 ? 0x7f800000u : 0x7e000000u;
-    uint32_t o_max = 0;
+    // The sum of their absolute values is at least their largest and not a number where one of them is not; it is tested on the
+    // bit pattern, which a NaN passes.  (That the sum leaves the range before any of them costs a second pass, no result.)
+    float o_sum[4] = {0.f, 0.f, 0.f, 0.f};
     bool redo = false;
 #pragma unroll
     for (int qb = 0; qb < NQ; ++qb) {
@@ -692,10 +695,16 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) o_max = max(o_max, __float_as_uint(Oacc[cb][qb][r]) & 0x7fffffffu);
+            for (int r = 0; r < 4; ++r) o_sum[r] += __builtin_fabsf(Oacc[cb][qb][r]);
     }
-    // (the barrier inside also ends every wave's reads of the stages)
-    if (__builtin_expect(__syncthreads_or(redo || o_max >= kRedoBits), 0)) {
+    const uint32_t o_bits = __float_as_uint((o_sum[0] + o_sum[1]) + (o_sum[2] + o_sum[3])) & 0x7fffffffu;
+    // Every wave leaves its answer in LDS and sees everyone's behind one barrier, which also ends all reads of the stages.
+    // (__syncthreads_or took 0.55 us of a 64-token item's 11, with the maximum over the bit patterns that was formed here.)
+    const bool wave_redo = __builtin_amdgcn_ballot_w64(redo || o_bits >= kRedoBits) != 0;
+    if (lane == 0) redo_of[wave] = wave_redo;
+    __syncthreads();
+    const uint32_t others = lane < QW * KG ? redo_of[lane] : 0u;
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(others != 0) != 0, 0)) {
         reset(-INFINITY);
         walk.start(box, p.n_h, p.n_w, p.P);
         to_share();
@@ -990,7 +999,7 @@ void sta_fwd_solo_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restr
     constexpr float kRedoAbove = 79228162514264337593543950336.f, kRedoBelow = 5.42101086242752217e-20f;
     constexpr uint32_t kRedoBits = KG > 4 ? 0x7d800000u : 0x7e000000u;      // 2^124, 2^125: the sum of all groups stays in range
     auto leave_partial = [&](bool careful) __attribute__((always_inline)) {
-        uint32_t o_max = 0;
+        float o_sum[4] = {0.f, 0.f, 0.f, 0.f};
         bool redo = false;
 #pragma unroll
         for (int qb = 0; qb < NQ; ++qb) {
@@ -1000,11 +1009,12 @@ void sta_fwd_solo_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restr
 #pragma unroll
             for (int cb = 0; cb < CB; ++cb) {
 #pragma unroll
-                for (int r = 0; r < 4; ++r) o_max = max(o_max, __float_as_uint(Oacc[cb][qb][r]) & 0x7fffffffu);
+                for (int r = 0; r < 4; ++r) o_sum[r] += __builtin_fabsf(Oacc[cb][qb][r]);
                 *reinterpret_cast<floatx4 *>(region + (qb * CB + cb) * 1024 + lane * 16) = Oacc[cb][qb];
             }
         }
-        const uint64_t any = __builtin_amdgcn_ballot_w64(redo || o_max >= kRedoBits);
+        const uint32_t o_bits = __float_as_uint((o_sum[0] + o_sum[1]) + (o_sum[2] + o_sum[3])) & 0x7fffffffu;
+        const uint64_t any = __builtin_amdgcn_ballot_w64(redo || o_bits >= kRedoBits);
         if (lane == 0) *reinterpret_cast<uint32_t *>(smem + FLAGS + 4 * kg) = any != 0;
     };
     run_pass(std::false_type{});

@@ -6,6 +6,8 @@
 
 #include <type_traits>
 
+#include "sta_internal.h"
+
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -79,6 +81,13 @@ __device__ __forceinline__ void scale_in_place(floatx4 &x, float a)
     asm volatile("v_mul_f32_e32 %0, %4, %0\n\tv_mul_f32_e32 %1, %4, %1\n\tv_mul_f32_e32 %2, %4, %2\n\tv_mul_f32_e32 %3, %4, %3"
                  : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3])
                  : "v"(a));
+}
+
+// n divided by the launch constant of f.
+__device__ __forceinline__ uint32_t fast_div(uint32_t n, const sta::FastDiv &f)
+{
+    const uint32_t q = __umulhi(n, f.magic);
+    return (((n - q) >> f.pre) + q) >> f.post;
 }
 
 template <int I, int N, typename F>

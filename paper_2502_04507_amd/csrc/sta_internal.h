@@ -5,6 +5,23 @@
 
 namespace sta {
 
+// Division of any 32-bit number by a launch constant with one multiplication: n / d = (((n - q) >> pre) + q) >> post
+// with q = the upper half of n * magic (Granlund and Montgomery, Division by Invariant Integers using Multiplication, 1994).
+struct FastDiv {
+    uint32_t d, magic;
+    uint32_t pre, post;
+};
+inline FastDiv fast_div_of(uint32_t d)
+{
+    const uint32_t s = d <= 1 ? 0 : 32 - __builtin_clz(d - 1);      // ceil(log2 d)
+    FastDiv f;
+    f.d = d;
+    f.magic = (uint32_t)(((((uint64_t)1 << s) - d) << 32) / d) + 1;
+    f.pre = s < 1 ? s : 1;
+    f.post = s < 1 ? 0 : s - 1;
+    return f;
+}
+
 // ---- permutation -----------------------------------------------------------
 struct PermuteParams {
     uint32_t N;                 // tokens per (b,h) slice
@@ -18,6 +35,7 @@ struct PermuteParams {
     uint32_t T_h_magic;         // ceil(2^32 / T_h)
     uint32_t parts;             // workgroups per tile
     uint32_t span;              // chunks per workgroup (the last one of a tile may get fewer)
+    FastDiv by_parts, by_tiles, by_n_w, by_n_h;     // divisions of a workgroup id, a tile number and its row
 };
 
 constexpr uint32_t kPermuteChunksPerBlock = 1024;   // 256 lanes x 4 chunks of 16 bytes
@@ -59,23 +77,6 @@ struct FwdParams {
 
 // The DMA into LDS fetches 16 bytes per lane; tensors are only asked to hold elements.
 inline bool dma_aligned(const void *p) { return ((uintptr_t)p & 15) == 0; }
-
-// Division of any 32-bit number by a launch constant with one multiplication: n / d = (((n - q) >> pre) + q) >> post
-// with q = the upper half of n * magic (Granlund and Montgomery, Division by Invariant Integers using Multiplication, 1994).
-struct FastDiv {
-    uint32_t d, magic;
-    uint32_t pre, post;
-};
-inline FastDiv fast_div_of(uint32_t d)
-{
-    const uint32_t s = d <= 1 ? 0 : 32 - __builtin_clz(d - 1);      // ceil(log2 d)
-    FastDiv f;
-    f.d = d;
-    f.magic = (uint32_t)(((((uint64_t)1 << s) - d) << 32) / d) + 1;
-    f.pre = s < 1 ? s : 1;
-    f.post = s < 1 ? 0 : s - 1;
-    return f;
-}
 
 // How the work items of one launch of the key-group forward kernel are dealt to the workgroups, with everything a workgroup
 // would otherwise have to find by division (see group_item_of).

@@ -10,6 +10,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "sta_device_util.h"
 #include "sta_internal.h"
 
 namespace {
@@ -87,7 +88,7 @@ __device__ __forceinline__ void store8(void *base, size_t chunk, const Chunk8bf1
     }
 }
 
-__device__ __forceinline__ uint32_t fast_div(uint32_t n, uint32_t d, uint32_t magic)
+__device__ __forceinline__ uint32_t small_div(uint32_t n, uint32_t d, uint32_t magic)
 {
     // magic = ceil(2^32 / d) for d > 1; exact while n * d < 2^32 (checked on the host).
     return d == 1 ? n : __umulhi(n, magic);
@@ -103,13 +104,11 @@ __global__ __launch_bounds__(kPermuteThreads) void sta_permute_kernel(const void
                                                                      void *__restrict__ dst,
                                                                      sta::PermuteParams p)
 {
-    const uint32_t part = blockIdx.x % p.parts;
-    const uint32_t tile_linear = blockIdx.x / p.parts;
-    const uint32_t tile_id = tile_linear % p.n_tiles;
-    const uint32_t outer = tile_linear / p.n_tiles;         // b*H + h
-    const uint32_t tw = tile_id % p.n_w;
-    const uint32_t th = (tile_id / p.n_w) % p.n_h;
-    const uint32_t tt = tile_id / (p.n_w * p.n_h);
+    // (divisions prepared by the host: found in the kernel, they took a tenth of the launch at 17 MB, 4.36 -> 3.93 us; 4 MB 2.88 -> 2.66)
+    const uint32_t tile_linear = fast_div(blockIdx.x, p.by_parts), part = blockIdx.x - tile_linear * p.parts;
+    const uint32_t outer = fast_div(tile_linear, p.by_tiles), tile_id = tile_linear - outer * p.n_tiles;         // b*H + h
+    const uint32_t row = fast_div(tile_id, p.by_n_w), tw = tile_id - row * p.n_w;
+    const uint32_t tt = fast_div(row, p.by_n_h), th = row - tt * p.n_h;
 
     const size_t slice = (size_t)outer * p.N * p.cpr;       // chunk offset of this (b,h) slice
     const size_t tiled_base = slice + (size_t)tile_id * p.chunks_per_tile;
@@ -128,9 +127,9 @@ __global__ __launch_bounds__(kPermuteThreads) void sta_permute_kernel(const void
         for (int u = 0; u < kUnroll; ++u) {
             const uint32_t idx = i0 + u * kPermuteThreads;
             if (idx < end) {
-                const uint32_t seg = fast_div(idx, p.seg, p.seg_magic);      // which (i_t, i_h) run
+                const uint32_t seg = small_div(idx, p.seg, p.seg_magic);      // which (i_t, i_h) run
                 const uint32_t off = idx - seg * p.seg;
-                const uint32_t it = fast_div(seg, p.T_h, p.T_h_magic);
+                const uint32_t it = small_div(seg, p.T_h, p.T_h_magic);
                 const uint32_t ih = seg - it * p.T_h;
                 const size_t raster = raster_tile + (size_t)it * row_stride_t + (size_t)ih * row_stride_h + off;
                 const size_t tiled = tiled_base + idx;

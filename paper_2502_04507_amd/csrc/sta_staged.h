@@ -10,12 +10,6 @@
 
 namespace {
 
-__device__ __forceinline__ uint32_t fast_div(uint32_t n, const sta::FastDiv &f)
-{
-    const uint32_t q = __umulhi(n, f.magic);
-    return (((n - q) >> f.pre) + q) >> f.post;
-}
-
 constexpr int kSub = 32;               // tokens per staged sub-block
 
 // Walks the sub-blocks of the tiles of a box; next_row is the first token row (tiled order, inside the head) of
