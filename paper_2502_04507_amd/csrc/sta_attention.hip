@@ -406,13 +406,13 @@ __device__ __forceinline__ GroupItem group_item_of(uint32_t id, const sta::FwdPa
 // The grid: 6.97-7.15 ms with the 12-wave kernel on v_mfma_f32_32x32x16_bf16 that was here before, 6.68-6.83 with QW = 4
 // (QW = 12: 7.5, QW = 2: 7.3; row sums by v_dot2: 7.2), 6.53-6.63 with two units per stage (UPS, 64 keys per barrier).  The
 // images: 105-109 us before, 98-100.  Head dimension 128, 96-token tiles (10x30x56, 10 slices, windows 3x3x3 and 2x4x3): 2390 us
-// with the register-staged kernel that served it before, 294-299 us; its three-wave shapes spill (16 to 20 bytes of scratch at
-// the 168 registers that three waves per SIMD allow; with fewer fragments in flight they do not and are no faster, 291 us).
+// with the register-staged kernel that served it before, 294-299 us, 290 since a move of the offset touches no score (below).
 // FOLLOW: the offset is the running maximum in every unit.  Otherwise it is the maximum of an item's first unit, and the
 // largest probabilities of a row are rounded to bf16 like any other; at the running maximum the largest is exactly 1 and has
 // no rounding error.  Against 64 bits (2-norm of the outputs, 96-token tiles, window 3x3x3, N(0,1)): 2.32e-3 with the fixed
 // offset, 2.17e-3 following, 2.24e-3 with the register-staged kernel.  Following costs 15 %
-// (260 -> 299 us), so it is done on the tiles whose kernel has always done it: no multiple of 128 tokens at head dimension
+// (260 -> 299 us; 290 with the offset in the exponent's fused multiply-add, which also ended the spills of the three-wave shapes at
+// head dimension 128, 12 to 32 bytes; 24 slices, 1x3x3 229 -> 222, 30 of head dimension 64 420 -> 411), so it is done on the tiles whose kernel has always done it: no multiple of 128 tokens at head dimension
 // 128, of 64 at 64.
 // A third LDS stage (DMA two units ahead, waited for by count behind a bare s_barrier, which __syncthreads() does not
 // allow: it waits for every outstanding DMA) changes nothing at four waves per SIMD and costs occupancy on small tiles:
@@ -518,13 +518,16 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
             Qr[qb][ks] = *reinterpret_cast<const bf16x8 *>(q + (my_row + 16 * qb + c16) * D + ks * 32 + g4 * 8);
 
     floatx4 Oacc[CB][NQ];                                   // channel 16*cb + 4*g4 + i of query 16*qb + c16
-    floatx4 Sinit[NQ];                                      // minus the exponent offset of the lane's queries
-    float m_run[NQ];
+    // Offset of the lane's queries.  Fixed: the scores start at minus the offset (Sinit).  Following: they start at 0 and the offset
+    // (off, rounded, in base 2) enters the exponent by a fused multiply-add, so that a move changes one register and no score.
+    floatx4 Sinit[FOLLOW ? 1 : NQ];
+    float m_run[NQ], off[NQ];
     floatx4 l_acc[NQ];                                      // row sums (a product with ones: all registers hold the same)
     auto reset = [&](float m) __attribute__((always_inline)) {
 #pragma unroll
         for (int qb = 0; qb < NQ; ++qb) {
-            Sinit[qb] = floatx4{0.f, 0.f, 0.f, 0.f};
+            if constexpr (!FOLLOW) Sinit[qb] = floatx4{0.f, 0.f, 0.f, 0.f};
+            off[qb] = 0.f;
             l_acc[qb] = floatx4{0.f, 0.f, 0.f, 0.f};
             m_run[qb] = m;
 #pragma unroll
@@ -539,20 +542,20 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
     }
 
     constexpr int kPlain = 0, kFollow = 1, kFirst = 2, kCareful = 3;
-    // One unit of 32 keys whose K begins at LDS offset off (relative to the group's first stage).
-    auto unit_at = [&](auto track_c, uint32_t off, float grow_above) __attribute__((always_inline)) {
+    // One unit of 32 keys whose K begins at LDS offset at (relative to the group's first stage).
+    auto unit_at = [&](auto track_c, uint32_t at, float grow_above) __attribute__((always_inline)) {
         // kFirst: set the offsets; kFollow: move them with the scores.  kCareful: the same on scores that do not start at
         // minus the offset: they lose nothing to an old offset that was far below them (keys masked by a lowest value).
         constexpr int TRACK = decltype(track_c)::value;
         uint32_t tr_at[4];
 #pragma unroll
-        for (int m = 0; m < 4; ++m) tr_at[m] = tr_addr[m] + off;
+        for (int m = 0; m < 4; ++m) tr_at[m] = tr_addr[m] + at;
         floatx4 S[2][NQ];                                   // [key block][query block]
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-            for (int qb = 0; qb < NQ; ++qb) S[kb][qb] = TRACK == kCareful ? floatx4{0.f, 0.f, 0.f, 0.f} : Sinit[qb];
-        rows_times_resident<D, 0>(row_addr + off, Qr, S);   // K Q^T minus the offset
+            for (int qb = 0; qb < NQ; ++qb) S[kb][qb] = FOLLOW || TRACK == kCareful ? floatx4{0.f, 0.f, 0.f, 0.f} : Sinit[FOLLOW ? 0 : qb];
+        rows_times_resident<D, 0>(row_addr + at, Qr, S);   // K Q^T minus the offset
         if constexpr (TRACK != kPlain) {
             float mq[NQ];
 #pragma unroll
@@ -567,12 +570,16 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
                 for (int qb = 0; qb < NQ; ++qb) {
                     const float row_max = quad_lane_max(mq[qb]);
                     m_run[qb] = row_max == -INFINITY ? 0.f : row_max;
+                    if constexpr (FOLLOW) {
+                        off[qb] = m_run[qb] * c;
+                    } else {
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) Sinit[qb][r] = -m_run[qb];
+                        for (int r = 0; r < 4; ++r) Sinit[qb][r] = -m_run[qb];
 #pragma unroll
-                    for (int kb = 0; kb < 2; ++kb)
+                        for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) S[kb][qb][r] -= m_run[qb];
+                            for (int r = 0; r < 4; ++r) S[kb][qb][r] -= m_run[qb];
+                    }
                 }
             } else if constexpr (TRACK == kCareful) {
 #pragma unroll
@@ -597,17 +604,13 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
                 // a query block at a time: that halves the accumulators scaled where only one of them has grown
 #pragma unroll
                 for (int qb = 0; qb < NQ; ++qb) {
-                    if (__builtin_amdgcn_ballot_w64(mq[qb] > grow_above) == 0) continue;
-                    const float row_max = quad_lane_max(mq[qb]);
-                    const float shift = row_max > grow_above ? row_max : 0.f;         // the same in the four lanes of a query
-                    const float alpha = __builtin_amdgcn_exp2f(-shift * c);
-                    m_run[qb] += shift;
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) Sinit[qb][r] = -m_run[qb];
-#pragma unroll
-                    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) S[kb][qb][r] -= shift;
+                    if (__builtin_amdgcn_ballot_w64(mq[qb] > m_run[qb]) == 0) continue;
+                    const float m_new = fmaxf(m_run[qb], quad_lane_max(mq[qb]));      // the same in the four lanes of a query
+                    float off_new = m_new * c;
+                    asm volatile("" : "+v"(off_new));       // one rounded number in all its uses
+                    const float alpha = __builtin_amdgcn_exp2f(off[qb] - off_new);
+                    m_run[qb] = m_new;
+                    off[qb] = off_new;
                     l_acc[qb] *= alpha;
                     // the old offset was so far below that the scores behind it are lost: an infinite row sum asks for the
                     // careful pass (it stays infinite; row_sums reads register 0)
@@ -630,8 +633,9 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
                 for (int e = 0; e < 4; e += 2) {
-                    const float p0 = __builtin_amdgcn_exp2f(S[kb][qb][e] * c);
-                    const float p1 = __builtin_amdgcn_exp2f(S[kb][qb][e + 1] * c);
+                    auto exponent = [&](float x) { return FOLLOW && TRACK != kCareful ? fmaf(x, c, -off[qb]) : x * c; };
+                    const float p0 = __builtin_amdgcn_exp2f(exponent(S[kb][qb][e]));
+                    const float p1 = __builtin_amdgcn_exp2f(exponent(S[kb][qb][e + 1]));
                     bf16x2 pp;
                     pp[0] = static_cast<__bf16>(p0);
                     pp[1] = static_cast<__bf16>(p1);
@@ -659,7 +663,7 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
             asm volatile("" ::: "memory");
             issue_next();
         };
-        auto rest_at = [&](uint32_t off) __attribute__((always_inline)) { unit_at(std::integral_constant<int, REST>{}, off, bound); };
+        auto rest_at = [&](uint32_t at) __attribute__((always_inline)) { unit_at(std::integral_constant<int, REST>{}, at, bound); };
         if constexpr (!CAREFUL) {
             next_stage();
             if (KG == 1 || n_units > 0) unit_at(std::integral_constant<int, kFirst>{}, 0u, 0.f);
@@ -712,6 +716,8 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
         issue_next();
         run_pass(std::true_type{});
         row_sums();
+#pragma unroll
+        for (int qb = 0; qb < NQ; ++qb) off[qb] = m_run[qb] * c;
         __syncthreads();
     }
 
@@ -721,7 +727,7 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
     // groups can be merged)
     float m2[NQ];                                           // offsets in base-2 units
 #pragma unroll
-    for (int qb = 0; qb < NQ; ++qb) m2[qb] = (KG > 1 && n_units == 0) ? -3.0e38f : fmaxf(m_run[qb] * c, -3.0e38f);
+    for (int qb = 0; qb < NQ; ++qb) m2[qb] = (KG > 1 && n_units == 0) ? -3.0e38f : fmaxf(FOLLOW ? off[qb] : m_run[qb] * c, -3.0e38f);
     if constexpr (KG > 1) {
 #pragma unroll
         for (int n = KG; n > 1; n = (n + 1) / 2) {
@@ -1838,8 +1844,12 @@ hipError_t launch_groups(const void *q, const void *k, const void *v, void *o, i
     }
     if (P % 64 == 0) {
         if constexpr (D == 128) {
+            // two groups also for one to one and a half rounds of long walks: half as many workgroups at once, each half as long
+            // (10x24x48 in 320-token tiles, 2x2x4, eight heads, 1.4 rounds, 300 units 566 -> 506 us; 10x40x40, eight, 1.95 rounds 214,
+            // 232; 64x64 at 5x5, 48, 6 rounds, 50 units 196, 210)
+            const uint64_t blocks = waves / 2, places = 4 * cus;
             if (P % 128 != 0)
-                return two ? launch_group<128, 2, 2, 2, true>(q, k, v, o, B, p, win, order, stream)
+                return two || (units >= 64 && blocks > places && 2 * blocks <= 3 * places) ? launch_group<128, 2, 2, 2, true>(q, k, v, o, B, p, win, order, stream)
                            : launch_group<128, 2, 1, 2, true>(q, k, v, o, B, p, win, order, stream);
             if (4 * waves <= fits && units >= 32) return launch_group<128, 2, 4, 2, false>(q, k, v, o, B, p, win, order, stream);
             return two ? launch_group<128, 2, 2, 2, false>(q, k, v, o, B, p, win, order, stream)
