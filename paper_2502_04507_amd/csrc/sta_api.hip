@@ -82,19 +82,12 @@ int permute_common(const void *src, void *dst, int src_dt, int dst_dt, int B, in
     p.chunks_per_tile = (uint32_t)cpt;
     p.seg_magic = magic_of(p.seg);
     p.T_h_magic = magic_of(p.T_h);
-    // One workgroup moves at most kPermuteChunksPerBlock chunks, one pass of four 16-byte loads and stores per lane:
-    // measured at the 115,200-token, 24-head tensor 5.0 TB/s with one workgroup per 384-token tile (six passes),
-    // 5.2 / 5.4 / 5.5 TB/s with 2 / 3 / 6 workgroups per tile.
     const uint64_t tiles = (uint64_t)B * H * s.n_tiles;
-    p.span = sta::kPermuteChunksPerBlock;
-    p.parts = (uint32_t)((cpt + p.span - 1) / p.span);
-    if (tiles * p.parts >= ((uint64_t)1 << 31)) return STA_ERR_SHAPE;
-    const uint32_t blocks = (uint32_t)(tiles * p.parts);
-    p.by_parts = sta::fast_div_of(p.parts);
+    if (tiles * ((cpt + 1023) / 1024) >= ((uint64_t)1 << 31)) return STA_ERR_SHAPE;
     p.by_tiles = sta::fast_div_of(p.n_tiles);
     p.by_n_w = sta::fast_div_of(p.n_w);
     p.by_n_h = sta::fast_div_of(p.n_h);
-    hipError_t e = sta::launch_permute(src, dst, src_dt == STA_F32, dst_dt == STA_F32, to_tiled, p, blocks,
+    hipError_t e = sta::launch_permute(src, dst, src_dt == STA_F32, dst_dt == STA_F32, to_tiled, p, tiles,
                                        static_cast<hipStream_t>(hip_stream));
     return e == hipSuccess ? STA_OK : STA_ERR_HIP;
 }

@@ -34,14 +34,15 @@ struct PermuteParams {
     uint32_t seg, seg_magic;    // T_w * cpr chunks per contiguous run, ceil(2^32/seg)
     uint32_t T_h_magic;         // ceil(2^32 / T_h)
     uint32_t parts;             // workgroups per tile
-    uint32_t span;              // chunks per workgroup (the last one of a tile may get fewer)
-    FastDiv by_parts, by_tiles, by_n_w, by_n_h;     // divisions of a workgroup id, a tile number and its row
+    uint32_t blocks;            // workgroups
+    uint32_t row_blocks;        // workgroups per row of tiles along w, which one XCD moves
+    uint32_t in_rounds;         // workgroups in full rounds of eight such rows
+    FastDiv by_round, by_parts, by_tiles, by_n_w, by_n_h;       // divisions of a workgroup id, a tile number and its row
 };
 
-constexpr uint32_t kPermuteChunksPerBlock = 1024;   // 256 lanes x 4 chunks of 16 bytes
-
+// Fills in what depends on the split of a tile over workgroups; tiles of all slices.
 hipError_t launch_permute(const void *src, void *dst, bool src_f32, bool dst_f32, bool to_tiled,
-                          const PermuteParams &p, uint32_t blocks, hipStream_t stream);
+                          PermuteParams p, uint64_t tiles, hipStream_t stream);
 
 // ---- attention -------------------------------------------------------------
 uint32_t compute_units();           // of the device that is current at the first call

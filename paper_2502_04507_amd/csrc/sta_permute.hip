@@ -4,9 +4,8 @@
 // run of the sequence (Sec. 3.1; appendix "Tiling in STA").  In
 // raster order a tile is T_t*T_h runs of T_w consecutive tokens, so both sides
 // of the copy are made of contiguous segments of T_w*D elements: a workgroup
-// moves one tile of one (batch, head) slice, or an even share of it when the
-// tensor has too few tiles to fill the chip, each lane moving 8 elements (16 B
-// of bf16) at a time with the tiled side fully linear.
+// moves 256 or 512 pieces of 8 elements (16 B of bf16) of one tile of one
+// (batch, head) slice, with the tiled side fully linear.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -95,17 +94,30 @@ __device__ __forceinline__ uint32_t small_div(uint32_t n, uint32_t d, uint32_t m
 }
 
 constexpr int kPermuteThreads = 256;
-constexpr int kUnroll = 4;
-static_assert(kPermuteThreads * kUnroll == (int)sta::kPermuteChunksPerBlock, "one pass per workgroup");
+constexpr int kGridShift = 23;                              // a grid holds fewer than 2^32 lanes along x
 
 // TO_TILED: src is raster, dst is tiled.  Otherwise the reverse.
-template <bool SRC_F32, bool DST_F32, bool TO_TILED, bool STREAM>
+// What bounds it: HBM, and how reads and writes mix there.  CHUNKS pieces of 8 elements per lane: one, so that a workgroup reads and
+// writes one run of 4 KB and is gone; two for fp32 sources that are rounded to bf16 and not streamed (26 MB 13.4 -> 12.3 us, 170 MB 50
+// -> 44).  us in whole layers, to tiles and back, four pieces (what was here before), two, one, one in the order below: 708 MB 231,
+// 236; 234, 241; 217, 224; 214, 216.  85 MB 30.0, 29.6; 29.8, 30.1; 28.6, 29.2; 28.6, 28.4.  96-token tiles, 43 MB 16.9, 17.3; 15.0,
+// 16.8; 14.6, 15.8; 14.9, 15.3.  64-token tiles of dimension 64, 67 MB 23.8, 23.8; 24.2, 24.0; 23.1, 23.3; 23.0, 22.8.  32-token tiles
+// of dimension 64, a piece per lane before as well, 157 MB 50.3, 49.6; ordered 50.0, 50.3.  One or two by 512 or 1024 lanes: no better.
+// Order: workgroup ids go round-robin over the 8 XCDs; every XCD takes whole rows of tiles along w, whose tokens are one piece of each
+// raster row, in turn with the others (full rounds of eight rows; what is left over in the order of the ids).
+template <bool SRC_F32, bool DST_F32, bool TO_TILED, bool STREAM, int CHUNKS>
 __global__ __launch_bounds__(kPermuteThreads) void sta_permute_kernel(const void *__restrict__ src,
                                                                      void *__restrict__ dst,
                                                                      sta::PermuteParams p)
 {
     // (divisions prepared by the host: found in the kernel, they took a tenth of the launch at 17 MB, 4.36 -> 3.93 us; 4 MB 2.88 -> 2.66)
-    const uint32_t tile_linear = fast_div(blockIdx.x, p.by_parts), part = blockIdx.x - tile_linear * p.parts;
+    uint32_t id = (blockIdx.y << kGridShift) + blockIdx.x;
+    if (id >= p.blocks) return;
+    if (id < p.in_rounds) {
+        const uint32_t in_round = id - fast_div(id, p.by_round) * p.by_round.d;
+        id += (in_round & 7) * p.row_blocks + (in_round >> 3) - in_round;
+    }
+    const uint32_t tile_linear = fast_div(id, p.by_parts), part = id - tile_linear * p.parts;
     const uint32_t outer = fast_div(tile_linear, p.by_tiles), tile_id = tile_linear - outer * p.n_tiles;         // b*H + h
     const uint32_t row = fast_div(tile_id, p.by_n_w), tw = tile_id - row * p.n_w;
     const uint32_t tt = fast_div(row, p.by_n_h), th = row - tt * p.n_h;
@@ -117,43 +129,39 @@ __global__ __launch_bounds__(kPermuteThreads) void sta_permute_kernel(const void
     const uint32_t row_stride_h = p.L_w * p.cpr;            // chunks per raster row of tokens (fixed t,h)
     const uint32_t row_stride_t = p.L_h * row_stride_h;
 
-    const uint32_t first = part * p.span;
-    const uint32_t end = first + p.span < p.chunks_per_tile ? first + p.span : p.chunks_per_tile;
-    for (uint32_t i0 = first + threadIdx.x; i0 < end; i0 += kPermuteThreads * kUnroll) {
-        Chunk8bf16 b[kUnroll];
-        Chunk8f32 f[kUnroll];
-        size_t dst_idx[kUnroll];
+    const uint32_t first = part * (kPermuteThreads * CHUNKS) + threadIdx.x;
+    Chunk8bf16 b[CHUNKS];
+    Chunk8f32 f[CHUNKS];
+    size_t dst_idx[CHUNKS];
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            const uint32_t idx = i0 + u * kPermuteThreads;
-            if (idx < end) {
-                const uint32_t seg = small_div(idx, p.seg, p.seg_magic);      // which (i_t, i_h) run
-                const uint32_t off = idx - seg * p.seg;
-                const uint32_t it = small_div(seg, p.T_h, p.T_h_magic);
-                const uint32_t ih = seg - it * p.T_h;
-                const size_t raster = raster_tile + (size_t)it * row_stride_t + (size_t)ih * row_stride_h + off;
-                const size_t tiled = tiled_base + idx;
-                load8<SRC_F32, STREAM>(src, TO_TILED ? raster : tiled, b[u], f[u]);
-                dst_idx[u] = TO_TILED ? tiled : raster;
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            const uint32_t idx = i0 + u * kPermuteThreads;
-            if (idx < end) store8<SRC_F32, DST_F32>(dst, dst_idx[u], b[u], f[u]);
+    for (int u = 0; u < CHUNKS; ++u) {
+        const uint32_t idx = first + u * kPermuteThreads;
+        if (idx < p.chunks_per_tile) {
+            const uint32_t seg = small_div(idx, p.seg, p.seg_magic);          // which (i_t, i_h) run
+            const uint32_t off = idx - seg * p.seg;
+            const uint32_t it = small_div(seg, p.T_h, p.T_h_magic);
+            const uint32_t ih = seg - it * p.T_h;
+            const size_t raster = raster_tile + (size_t)it * row_stride_t + (size_t)ih * row_stride_h + off;
+            const size_t tiled = tiled_base + idx;
+            load8<SRC_F32, STREAM>(src, TO_TILED ? raster : tiled, b[u], f[u]);
+            dst_idx[u] = TO_TILED ? tiled : raster;
         }
     }
+#pragma unroll
+    for (int u = 0; u < CHUNKS; ++u)
+        if (first + u * kPermuteThreads < p.chunks_per_tile) store8<SRC_F32, DST_F32>(dst, dst_idx[u], b[u], f[u]);
 }
 
 template <bool TO_TILED, bool STREAM>
 hipError_t launch(const void *src, void *dst, bool src_f32, bool dst_f32, const sta::PermuteParams &p,
-                  uint32_t blocks, hipStream_t stream)
+                  hipStream_t stream)
 {
-    dim3 g(blocks), b(kPermuteThreads);
-    if (!src_f32 && !dst_f32) sta_permute_kernel<false, false, TO_TILED, STREAM><<<g, b, 0, stream>>>(src, dst, p);
-    else if (src_f32 && !dst_f32) sta_permute_kernel<true, false, TO_TILED, STREAM><<<g, b, 0, stream>>>(src, dst, p);
-    else if (!src_f32 && dst_f32) sta_permute_kernel<false, true, TO_TILED, STREAM><<<g, b, 0, stream>>>(src, dst, p);
-    else sta_permute_kernel<true, true, TO_TILED, STREAM><<<g, b, 0, stream>>>(src, dst, p);
+    constexpr int kRounded = STREAM ? 1 : 2;                // fp32 to bf16
+    dim3 g(p.blocks >> kGridShift ? 1u << kGridShift : p.blocks, ((p.blocks - 1) >> kGridShift) + 1), b(kPermuteThreads);
+    if (!src_f32 && !dst_f32) sta_permute_kernel<false, false, TO_TILED, STREAM, 1><<<g, b, 0, stream>>>(src, dst, p);
+    else if (src_f32 && !dst_f32) sta_permute_kernel<true, false, TO_TILED, STREAM, kRounded><<<g, b, 0, stream>>>(src, dst, p);
+    else if (!src_f32 && dst_f32) sta_permute_kernel<false, true, TO_TILED, STREAM, 1><<<g, b, 0, stream>>>(src, dst, p);
+    else sta_permute_kernel<true, true, TO_TILED, STREAM, 1><<<g, b, 0, stream>>>(src, dst, p);
     return hipGetLastError();
 }
 
@@ -168,14 +176,23 @@ constexpr size_t kStreamAbove = (size_t)256 << 20;
 namespace sta {
 
 hipError_t launch_permute(const void *src, void *dst, bool src_f32, bool dst_f32, bool to_tiled,
-                          const PermuteParams &p, uint32_t blocks, hipStream_t stream)
+                          PermuteParams p, uint64_t tiles, hipStream_t stream)
 {
-    const size_t bytes = (size_t)blocks / p.parts * p.chunks_per_tile * (src_f32 ? 32 : 16);
-    if (bytes > kStreamAbove)
-        return to_tiled ? launch<true, true>(src, dst, src_f32, dst_f32, p, blocks, stream)
-                        : launch<false, true>(src, dst, src_f32, dst_f32, p, blocks, stream);
-    return to_tiled ? launch<true, false>(src, dst, src_f32, dst_f32, p, blocks, stream)
-                    : launch<false, false>(src, dst, src_f32, dst_f32, p, blocks, stream);
+    const bool streamed = tiles * p.chunks_per_tile * (src_f32 ? 32 : 16) > kStreamAbove;
+    const uint32_t per_block = kPermuteThreads * (src_f32 && !dst_f32 && !streamed ? 2 : 1);
+    p.parts = (p.chunks_per_tile + per_block - 1) / per_block;
+    if (tiles * p.parts >= ((uint64_t)1 << 31)) return hipErrorInvalidValue;         // terabytes
+    p.blocks = (uint32_t)(tiles * p.parts);
+    p.row_blocks = p.n_w * p.parts;
+    const uint32_t round = p.row_blocks <= p.blocks / 8 ? 8 * p.row_blocks : 0;
+    p.in_rounds = round ? p.blocks / round * round : 0;
+    p.by_parts = fast_div_of(p.parts);
+    p.by_round = fast_div_of(round ? round : 1);
+    if (streamed)
+        return to_tiled ? launch<true, true>(src, dst, src_f32, dst_f32, p, stream)
+                        : launch<false, true>(src, dst, src_f32, dst_f32, p, stream);
+    return to_tiled ? launch<true, false>(src, dst, src_f32, dst_f32, p, stream)
+                    : launch<false, false>(src, dst, src_f32, dst_f32, p, stream);
 }
 
 }  // namespace sta
