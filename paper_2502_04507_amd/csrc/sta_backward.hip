@@ -670,8 +670,8 @@ void sta_bwd_dkv_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restri
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// dK, dV at head dimension 128 on tiles of 96 and 32 tokens' multiples, and where the shapes above would half fill the chip.  One workgroup of 2 * NPAIR waves per 32 * NPAIR keys
-// (times G walk groups).  Each 32-key column block is served by a PAIR of waves: the first holds K and accumulates dV (S = Q K^T,
+// dK, dV at head dimension 128 on tiles of 96 and 32 tokens' multiples, and where the shapes above would half fill the chip.  One
+// workgroup of 2 * NPAIR waves per 32 * NPAIR keys (times G walk groups).  Each 32-key column block is served by a PAIR of waves: the first holds K and accumulates dV (S = Q K^T,
 // P, dV^T += dO^T P), the second holds V and accumulates dK (dP = dO V^T, dS = P o (dP - delta), dK^T += Q^T dS).  P goes from the
 // first to the second through LDS in fp32.  165-172 registers, three waves per SIMD: on these tiles the two waves per SIMD of
 // the kernel above do not fill the CU (three waves of 96 keys leave every fourth place empty) or need more LDS than there is
@@ -1035,7 +1035,7 @@ hipError_t dispatch_dq(const BwdArgs &a)
 // at 3x3, two heads (256, 18) 21.1, 25.2, eight (1024, 18) 35.2, 34.3; at 5x5, eight (1024, 50) 70, 80; 12x24x24 in 384-token tiles,
 // two (432, 108) 83, 89, three (648, 108) 104, 94; 9x40x40 in 192-token tiles, two (900, 54) 82, 97, four (1800, 54) 126, 129; 128,
 // 8x32x32 in 128-token tiles, one (256, 36) 46, 60, two (512, 36) 65, 61; 64x64 at 5x5, five (640, 50) 101, 110; 9x40x40, three (1350,
-// 54) 199, 185.  Against the shapes of 96- and 32-token tiles: 10x30x56, 64, 3x3x3, four slices (2100, 81) 185, 221, eight (4200, 81)
+// 54) 199, 185; training steps 64-token tiles (800, 90) 260, 259, 192 (960, 72) 261, 258, 320 (900, 180) 455, 413.  Against the shapes of 96- and 32-token tiles: 10x30x56, 64, 3x3x3, four slices (2100, 81) 185, 221, eight (4200, 81)
 // 341, 378, ten (5250, 81) 430, 418; 128, two (1050, 81) 227, 285, three (1575, 81) 329, 339, 1x3x3, two (1050, 27) 98, 98; 32x64 in
 // 32-token tiles, 128, four (256, 9) 24.4, 25.4, eight (512, 9) 32.8, 31.0, at 5x5 (512, 25) 62, 79.
 // Beyond that two groups of two waves where the launch is still small or the walk long, against two or four waves: 64, 384-token
@@ -1053,7 +1053,7 @@ hipError_t dispatch_dkv(const BwdArgs &a)
         else return launch_dkv<64, 1, 1, 1, false>(a);
     }
     uint64_t solo = D == 64 ? 2 * cus : cus;            // up to so many waves
-    if (P % 64 == 0 && P % 128 != 0 && units >= 48) solo = (D == 64 ? 8 : 4) * cus;
+    if (P % 64 == 0 && P % 128 != 0 && units >= 48) solo = (D == 64 ? 8 : 3) * cus;
     if (P % 64 != 0 && P % 96 == 0) solo = (D == 64 ? 18 : 6) * cus;
     if (P % 64 != 0 && P % 96 != 0 && units >= 24) solo = 2 * cus;
     if (waves <= solo) return launch_dkv<D, 1, 4>(a);
@@ -1062,10 +1062,16 @@ hipError_t dispatch_dkv(const BwdArgs &a)
         else return P % 96 == 0 ? launch_dkv<64, 3, 1>(a) : waves <= 4 * cus ? launch_dkv<64, 1, 2>(a) : launch_dkv<64, 1, 1>(a);
     }
     // One round of six pairs, at least four fifths full: half a wave's products per wave fill a CU where whole ones leave it half
-    // empty in the same time (30x24x32, two heads of 128 (1440, 720) 1495, 1589; 12x24x24, six (1296, 108) 259, 262).
+    // empty in the same time (30x24x32, two heads of 128 (1440, 720) 1495, 1589; 12x24x24, six (1296, 108) 259, 262; training steps,
+    // six pairs, two groups: (1344, 48) 211, 217, (1440, 72) 307, 313).  Not where the walks of the heads differ: the long ones are one
+    // round by themselves ((1296, 72) 253, 239; (1512, 108) 517, 408).
+    // 64-token tiles and the like, short walks: two pairs, of which a CU holds three workgroups, where the two workgroups it holds of the
+    // groups below begin a second round (training steps, groups, pairs: (1008, 18) 111, 112; (1200, 18) 131, 128; (1404, 36) 142, 132;
+    // (1512, 30) 192, 184; (1584, 12) 130, 126; (1632, 6) 112, 105; but (1440, 144) 431, 453).
     if constexpr (D == 128) {
         const uint64_t blocks = waves / 6;
-        if (P % 384 == 0 && blocks <= cus && 5 * blocks >= 4 * cus) return launch_dkv_pairs<6, 1>(a);
+        if (P % 384 == 0 && blocks <= cus && 5 * blocks >= 4 * cus && units == walk_of_rank(a, a.p.heads - 1)) return launch_dkv_pairs<6, 1>(a);
+        if (P % 128 != 0 && units < 48 && waves > 4 * cus && 2 * waves <= 13 * cus) return launch_dkv_pairs<2, 1>(a);
     }
     if (P % 128 == 0) return waves <= (P == 128 ? 24 : 6) * cus ? launch_dkv<D, 2, 2>(a) : launch_dkv<D, 4, 1, D == 64 ? 2 : 1>(a);
     return waves <= 8 * cus || (units >= 32 && (D == 64 || waves <= 32 * cus)) ? launch_dkv<D, 2, 2>(a) : launch_dkv<D, 2, 1>(a);

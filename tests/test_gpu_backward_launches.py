@@ -13,6 +13,9 @@ LAUNCHES = [
     ("p384-four-waves", (64, 128), (6, 16, 16), (6, 8, 8), 1, 36, [(1, 2, 1), (1, 1, 1)]),        # 1728
     ("p128-four-waves", (64, 128), (2, 8, 24), (2, 8, 8), 4, 132, [(1, 1, 3), (1, 1, 1)]),        # 6336
     ("p64-two-groups", (64, 128), (1, 16, 24), (1, 8, 8), 8, 8, [(1, 2, 3), (1, 1, 1)]),          # 768; 12 and 2 sub-blocks
+    ("p64-two-pairs", (128,), (1, 16, 24), (1, 8, 8), 10, 10, [(1, 2, 3), (1, 1, 1)]),            # 1200; 12 and 2 sub-blocks
+    ("p384-mixed", (128,), (6, 16, 16), (6, 8, 8), 1, 28, [(1, 2, 1), (1, 1, 1)]),                # 1344: no six pairs
+    ("p384-six-pairs", (128,), (6, 16, 16), (6, 8, 8), 1, 28, [(1, 2, 1)]),                       # 1344
     ("p64-two-waves", (64, 128), (1, 16, 24), (1, 8, 8), 12, 15, [(1, 2, 2)]),                    # 2160
     ("p192-two-groups", (64, 128), (3, 16, 24), (3, 8, 8), 8, 9, [(1, 3, 2)]),                    # 2592; 36 sub-blocks
     ("p96-many", (64, 128), (2, 12, 16), (2, 6, 8), 4, 100, [(1, 1, 2), (1, 2, 1)]),              # 4800
