@@ -1064,13 +1064,15 @@ hipError_t dispatch_dkv(const BwdArgs &a)
     // One round of six pairs, at least four fifths full: half a wave's products per wave fill a CU where whole ones leave it half
     // empty in the same time (30x24x32, two heads of 128 (1440, 720) 1495, 1589; 12x24x24, six (1296, 108) 259, 262; training steps,
     // six pairs, two groups: (1344, 48) 211, 217, (1440, 72) 307, 313).  Not where the walks of the heads differ: the long ones are one
-    // round by themselves ((1296, 72) 253, 239; (1512, 108) 517, 408).
+    // round by themselves ((1296, 72) 253, 239), nor where the rows of tiles are dealt so that an XCD gets more workgroups than it has CUs
+    // (14 heads of 6x24x24 (1512, 108): 42 rows of six workgroups, 36 on two of the XCDs, 517, 408).
     // 64-token tiles and the like, short walks: two pairs, of which a CU holds three workgroups, where the two workgroups it holds of the
     // groups below begin a second round (training steps, groups, pairs: (1008, 18) 111, 112; (1200, 18) 131, 128; (1404, 36) 142, 132;
     // (1512, 30) 192, 184; (1584, 12) 130, 126; (1632, 6) 112, 105; but (1440, 144) 431, 453).
     if constexpr (D == 128) {
         const uint64_t blocks = waves / 6;
-        if (P % 384 == 0 && blocks <= cus && 5 * blocks >= 4 * cus && units == walk_of_rank(a, a.p.heads - 1)) return launch_dkv_pairs<6, 1>(a);
+        const uint64_t rows = (uint64_t)a.B * a.p.heads * a.p.n_t * a.p.n_h, fullest_xcd = (rows + 7) / 8 * a.p.n_w * (P / 192);
+        if (P % 384 == 0 && 8 * fullest_xcd <= cus && 5 * blocks >= 4 * cus && units == walk_of_rank(a, a.p.heads - 1)) return launch_dkv_pairs<6, 1>(a);
         if (P % 128 != 0 && units < 48 && waves > 4 * cus && 2 * waves <= 13 * cus) return launch_dkv_pairs<2, 1>(a);
     }
     if (P % 128 == 0) return waves <= (P == 128 ? 24 : 6) * cus ? launch_dkv<D, 2, 2>(a) : launch_dkv<D, 4, 1, D == 64 ? 2 : 1>(a);
