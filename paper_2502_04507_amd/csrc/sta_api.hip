@@ -504,6 +504,41 @@ int sta_backward(const void *q_tiled, const void *k_tiled, const void *v_tiled, 
     return STA_OK;
 }
 
+// Not part of the interface: the kernels that sta_forward (with a workspace or without) or sta_backward would launch on aligned
+// tensors, one line each, so that tests can say which of them they run.  Launches nothing; without a device 256 compute units.
+int sta_describe_launches(int gradients, int B, int H, int D, const int grid[3], const int tile[3], const int *window_tiles,
+                          int with_workspace, char *text, size_t text_bytes)
+{
+    if (!text || text_bytes == 0) return STA_ERR_NULL;
+    text[0] = 0;
+    Shape s;
+    if (int rc = check_shape(B, H, D, grid, tile, &s)) return rc;
+    if (int rc = check_windows(H, window_tiles)) return rc;
+    if (!sta::forward_supported((int)s.P, D)) return STA_ERR_UNSUPPORTED;
+    sta::FwdParams p = make_fwd_params(s, H, 1.f);
+    const size_t ws_bytes = with_workspace ? sta::forward_split_workspace_bytes((int)s.P, D) : 0;
+    float *const ws = ws_bytes != 0 ? reinterpret_cast<float *>(16) : nullptr;      // never read
+    sta::LaunchNote note = {text, text_bytes};
+    const int max_heads = B <= 255 ? sta::kMaxHeadsPerLaunch : 65535 / B;
+    if (max_heads < 1) return STA_ERR_SHAPE;
+    for (int hb = 0; hb < H; hb += max_heads) {
+        const int heads = (H - hb) < max_heads ? (H - hb) : max_heads;
+        sta::WindowTable win;
+        fill_window_table(&win, window_tiles, hb, heads, s.n);
+        p.head_base = hb;
+        p.heads = heads;
+        sta::HeadOrder order;
+        fill_head_order(&order, window_tiles, hb, heads, s.n);
+        const hipError_t e =
+            gradients ? sta::launch_backward(nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0, nullptr, nullptr, nullptr,
+                                             B, D, p, win, order, nullptr, &note)
+                      : sta::launch_forward(nullptr, nullptr, nullptr, nullptr, B, D, p, win, order, ws, ws_bytes / sizeof(float), nullptr,
+                                            &note);
+        if (e != hipSuccess) return STA_ERR_SHAPE;
+    }
+    return STA_OK;
+}
+
 int sta_dump_key_tiles(int H, const int grid[3], const int tile[3], const int *window_tiles, int32_t *dev_counts,
                        int32_t *dev_lists, void *hip_stream)
 {

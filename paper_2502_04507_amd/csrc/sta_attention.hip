@@ -1642,11 +1642,26 @@ __global__ __launch_bounds__(256) void sta_fwd_combine_kernel(bf16_raw *__restri
 // Host side of the work splitting: how many workgroups the chip holds at once.
 inline uint32_t resident_workgroups(int minb) { return sta::compute_units() * (uint32_t)minb; }
 
+// What a launch function is called with.
+struct FwdArgs {
+    const void *q, *k, *v;
+    void *o;
+    int B;
+    const sta::FwdParams &p;
+    const sta::WindowTable &win;
+    const sta::HeadOrder &order;
+    float *split_ws;
+    size_t split_ws_floats;
+    hipStream_t stream;
+    sta::LaunchNote *note;      // not null: the shape is written there and nothing is launched
+};
+
 // The plan of a launch of query blocks of 32 * waves queries, and its workgroup ids.
-sta::FwdPlan make_plan(int waves, int B, const sta::FwdParams &p, const sta::WindowTable &win, const sta::HeadOrder &order, uint32_t *ids)
+sta::FwdPlan make_plan(int waves, const FwdArgs &a, uint32_t *ids)
 {
+    const sta::FwdParams &p = a.p;
     sta::FwdPlan plan;
-    const uint32_t per_head = p.N / (waves * 32), n_bh = (uint32_t)B * p.heads;
+    const uint32_t per_head = p.N / (waves * 32), n_bh = (uint32_t)a.B * p.heads;
     plan.total = per_head * n_bh;
     // as many rounds of chunks as eighths of a head would take, of equal length
     const uint32_t eighth = (per_head + 7) / 8, rounds = (plan.total + 8 * eighth - 1) / (8 * eighth);
@@ -1656,30 +1671,28 @@ sta::FwdPlan make_plan(int waves, int B, const sta::FwdParams &p, const sta::Win
     plan.per_tile = sta::fast_div_of(p.P / (waves * 32));
     plan.pair_items = sta::fast_div_of(2 * p.n_w * p.n_t);
     plan.n_t = sta::fast_div_of(p.n_t);
-    plan.batch = sta::fast_div_of((uint32_t)B);
+    plan.batch = sta::fast_div_of((uint32_t)a.B);
     plan.sub_per_tile = sta::fast_div_of(p.P / kSub);
     for (uint32_t h = 0; h < p.heads; ++h) {
-        plan.head[h].h = order.h[h];
-        for (int a = 0; a < 3; ++a) plan.head[h].w[a] = win.w[order.h[h]][a];
+        plan.head[h].h = a.order.h[h];
+        for (int i = 0; i < 3; ++i) plan.head[h].w[i] = a.win.w[a.order.h[h]][i];
     }
     *ids = 8 * chunk * ((plan.total + 8 * chunk - 1) / (8 * chunk));
     return plan;
 }
 
 template <int NW, int KB, int STAGES, int MINB>
-hipError_t launch_x32(const void *q, const void *k, const void *v, void *o, int B, const sta::FwdParams &p_in,
-                            const sta::WindowTable &win, const sta::HeadOrder &order, float *split_ws,
-                            size_t split_ws_floats, hipStream_t stream)
+hipError_t launch_x32(const FwdArgs &a)
 {
     constexpr int D = 128, QB = NW * 32;
-    sta::FwdParams p = p_in;
+    sta::FwdParams p = a.p;
     uint32_t ids;                                                 // item ids; some of them name no item
-    const sta::FwdPlan plan = make_plan(NW, B, p, win, order, &ids);
+    const sta::FwdPlan plan = make_plan(NW, a, &ids);
     p.split_first = ids;
     p.split_parts = 1;
     p.split_ws = nullptr;
     uint32_t split_items = 0;
-    if (split_ws != nullptr) {
+    if (a.split_ws != nullptr) {
         // Items beyond the last full round of workgroups are split so that their parts fill the chip once.
         auto names_item = [&](uint32_t id) {
             const uint32_t slot = id >> 3, chunk = slot / plan.chunk.d;
@@ -1694,9 +1707,9 @@ hipError_t launch_x32(const void *q, const void *k, const void *v, void *o, int 
             for (uint32_t h = 0; h < p.heads; ++h) {
                 uint32_t tiles = 1;
                 const uint32_t n[3] = {p.n_t, p.n_h, p.n_w};
-                for (int a = 0; a < 3; ++a) {
-                    const uint32_t kept = 2 * (win.w[h][a] / 2) + 1;
-                    tiles *= kept < n[a] ? kept : n[a];
+                for (int i = 0; i < 3; ++i) {
+                    const uint32_t kept = 2 * (a.win.w[h][i] / 2) + 1;
+                    tiles *= kept < n[i] ? kept : n[i];
                 }
                 min_tiles = tiles < min_tiles ? tiles : min_tiles;
             }
@@ -1708,63 +1721,62 @@ hipError_t launch_x32(const void *q, const void *k, const void *v, void *o, int 
                 if (names_item(first)) ++found;
             }
             const size_t need = (size_t)(ids - first) * parts * split_part_floats<D>(QB);
-            if (parts > 1 && found == tail && need <= split_ws_floats) {
+            if (parts > 1 && found == tail && need <= a.split_ws_floats) {
                 p.split_first = first;
                 p.split_parts = parts;
-                p.split_ws = split_ws;
+                p.split_ws = a.split_ws;
                 split_items = ids - first;
             }
         }
     }
     dim3 grid(p.split_first + split_items * p.split_parts), block(NW * 64);
-    sta_fwd_x32_kernel<NW, KB, STAGES, MINB, false><<<grid, block, 0, stream>>>(
-        static_cast<const bf16_raw *>(q), static_cast<const bf16_raw *>(k), static_cast<const bf16_raw *>(v),
-        static_cast<bf16_raw *>(o), p, plan);
+    if (a.note) return a.note->add("x32<%d> items %u workgroups %u parts %u of %u", NW, plan.total, grid.x, p.split_parts, split_items);
+    sta_fwd_x32_kernel<NW, KB, STAGES, MINB, false><<<grid, block, 0, a.stream>>>(
+        static_cast<const bf16_raw *>(a.q), static_cast<const bf16_raw *>(a.k), static_cast<const bf16_raw *>(a.v),
+        static_cast<bf16_raw *>(a.o), p, plan);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || split_items == 0) return e;
-    sta_fwd_combine_kernel<D, QB><<<dim3(QB / 32, split_items), dim3(256), 0, stream>>>(static_cast<bf16_raw *>(o), p, plan);
+    sta_fwd_combine_kernel<D, QB><<<dim3(QB / 32, split_items), dim3(256), 0, a.stream>>>(static_cast<bf16_raw *>(a.o), p, plan);
     return hipGetLastError();
 }
 
 template <int D, int QW, int KG, int WPE, bool FOLLOW, int UPS = 1>
-hipError_t launch_group(const void *q, const void *k, const void *v, void *o, int B, const sta::FwdParams &p,
-                        const sta::WindowTable &win, const sta::HeadOrder &order, hipStream_t stream)
+hipError_t launch_group(const FwdArgs &a)
 {
     uint32_t ids;
-    const sta::FwdPlan plan = make_plan(QW, B, p, win, order, &ids);
-    sta_fwd_group_kernel<D, QW, KG, WPE, FOLLOW, UPS><<<dim3(ids), dim3(QW * KG * 64), 0, stream>>>(
-        static_cast<const bf16_raw *>(q), static_cast<const bf16_raw *>(k), static_cast<const bf16_raw *>(v),
-        static_cast<bf16_raw *>(o), p, plan);
+    const sta::FwdPlan plan = make_plan(QW, a, &ids);
+    if (a.note) return a.note->add("group<%d,%d,%d,%d> items %u workgroups %u", D, QW, KG, UPS, plan.total, ids);
+    sta_fwd_group_kernel<D, QW, KG, WPE, FOLLOW, UPS><<<dim3(ids), dim3(QW * KG * 64), 0, a.stream>>>(
+        static_cast<const bf16_raw *>(a.q), static_cast<const bf16_raw *>(a.k), static_cast<const bf16_raw *>(a.v),
+        static_cast<bf16_raw *>(a.o), a.p, plan);
     return hipGetLastError();
 }
 
 template <int D, int NQ, int KG, bool FOLLOW>
-hipError_t launch_solo(const void *q, const void *k, const void *v, void *o, int B, const sta::FwdParams &p,
-                       const sta::WindowTable &win, const sta::HeadOrder &order, hipStream_t stream)
+hipError_t launch_solo(const FwdArgs &a)
 {
     uint32_t ids;
-    const sta::FwdPlan plan = make_plan(NQ / 2, B, p, win, order, &ids);
-    sta_fwd_solo_kernel<D, NQ, KG, D == 64 && NQ == 2 ? 4 : 2, FOLLOW><<<dim3(ids), dim3(KG * 64), 0, stream>>>(
-        static_cast<const bf16_raw *>(q), static_cast<const bf16_raw *>(k), static_cast<const bf16_raw *>(v),
-        static_cast<bf16_raw *>(o), p, plan);
+    const sta::FwdPlan plan = make_plan(NQ / 2, a, &ids);
+    if (a.note) return a.note->add("solo<%d,%d,%d> items %u workgroups %u", D, NQ, KG, plan.total, ids);
+    sta_fwd_solo_kernel<D, NQ, KG, D == 64 && NQ == 2 ? 4 : 2, FOLLOW><<<dim3(ids), dim3(KG * 64), 0, a.stream>>>(
+        static_cast<const bf16_raw *>(a.q), static_cast<const bf16_raw *>(a.k), static_cast<const bf16_raw *>(a.v),
+        static_cast<bf16_raw *>(a.o), a.p, plan);
     return hipGetLastError();
 }
 
 // Units (32 keys) of the walk of a head of the launch; heads by rank, the one with the most key tiles first.
-uint32_t walk_of_rank(const sta::FwdParams &p, const sta::WindowTable &win, const sta::HeadOrder &order, uint32_t rank)
+uint32_t walk_of_rank(const FwdArgs &a, uint32_t rank)
 {
+    const sta::FwdParams &p = a.p;
     uint32_t units = p.P / kSub;
     const uint32_t n[3] = {p.n_t, p.n_h, p.n_w};
-    for (int a = 0; a < 3; ++a) {
-        const uint32_t kept = 2 * (win.w[order.h[rank]][a] / 2u) + 1;
-        units *= kept < n[a] ? kept : n[a];
+    for (int i = 0; i < 3; ++i) {
+        const uint32_t kept = 2 * (a.win.w[a.order.h[rank]][i] / 2u) + 1;
+        units *= kept < n[i] ? kept : n[i];
     }
     return units;
 }
-uint32_t longest_walk(const sta::FwdParams &p, const sta::WindowTable &win, const sta::HeadOrder &order)
-{
-    return walk_of_rank(p, win, order, 0);
-}
+uint32_t longest_walk(const FwdArgs &a) { return walk_of_rank(a, 0); }
 
 // Shape of the kernel for a launch.
 // Small launches, solo: in waves of 32 queries (counted as for the key groups below) and units of the longest walk; us, key-group
@@ -1796,36 +1808,36 @@ uint32_t longest_walk(const sta::FwdParams &p, const sta::WindowTable &win, cons
 // 17.3, 17.4, 22.9; 4096 waves 27.5, 30.1, 42.4.  Head dimension 128, 96-token tiles, about 75 units: 525 waves 50, 39, 34; 1050 waves
 // 68, 78, 69.
 template <int D>
-hipError_t launch_groups(const void *q, const void *k, const void *v, void *o, int B, const sta::FwdParams &p,
-                         const sta::WindowTable &win, const sta::HeadOrder &order, hipStream_t stream)
+hipError_t launch_groups(const FwdArgs &a)
 {
     constexpr uint32_t kFixed = D == 64 ? 64 : 128;         // tiles of its multiples keep the offset of the first unit
-    const uint32_t units = longest_walk(p, win, order), P = p.P;
+    const sta::FwdParams &p = a.p;
+    const uint32_t units = longest_walk(a), P = p.P;
     uint64_t heads = p.heads;
     if (units >= 64) {
         uint64_t all_units = 0;
-        for (uint32_t r = 0; r < p.heads; ++r) all_units += walk_of_rank(p, win, order, r);
+        for (uint32_t r = 0; r < p.heads; ++r) all_units += walk_of_rank(a, r);
         heads = (all_units + units - 1) / units;
     }
-    const uint64_t cus = resident_workgroups(1), waves = (uint64_t)B * heads * (p.N / 32);
+    const uint64_t cus = resident_workgroups(1), waves = (uint64_t)a.B * heads * (p.N / 32);
 
     if (waves <= cus) {
         const bool eight = units >= (D == 64 ? (P % 64 == 0 ? 24 : 16) : P % 64 == 0 ? (P % 128 == 0 ? 48 : 32) : 16);
         if (P % kFixed == 0)
-            return eight ? launch_solo<D, 2, 8, false>(q, k, v, o, B, p, win, order, stream)
-                         : launch_solo<D, 2, 4, false>(q, k, v, o, B, p, win, order, stream);
-        return eight ? launch_solo<D, 2, 8, true>(q, k, v, o, B, p, win, order, stream)
-                     : launch_solo<D, 2, 4, true>(q, k, v, o, B, p, win, order, stream);
+            return eight ? launch_solo<D, 2, 8, false>(a)
+                         : launch_solo<D, 2, 4, false>(a);
+        return eight ? launch_solo<D, 2, 8, true>(a)
+                     : launch_solo<D, 2, 4, true>(a);
     }
     if constexpr (D == 64) {
         if (P % 64 == 0 && waves <= 2 * cus)
-            return units >= 48 ? launch_solo<64, 4, 8, false>(q, k, v, o, B, p, win, order, stream)
-                               : launch_solo<64, 2, 4, false>(q, k, v, o, B, p, win, order, stream);
-        if (P % 64 == 0 && waves <= 4 * cus && units >= 32) return launch_solo<64, 4, 4, false>(q, k, v, o, B, p, win, order, stream);
+            return units >= 48 ? launch_solo<64, 4, 8, false>(a)
+                               : launch_solo<64, 2, 4, false>(a);
+        if (P % 64 == 0 && waves <= 4 * cus && units >= 32) return launch_solo<64, 4, 4, false>(a);
         if (P % 64 != 0 && waves <= (P % 96 == 0 ? 8 : units >= 16 ? 3 : 2) * cus)
-            return launch_solo<64, 2, 4, true>(q, k, v, o, B, p, win, order, stream);
+            return launch_solo<64, 2, 4, true>(a);
     } else if (P % 128 != 0 && waves <= (P % 192 == 0 ? 4 : 2) * cus) {
-        return launch_solo<128, 2, 4, true>(q, k, v, o, B, p, win, order, stream);
+        return launch_solo<128, 2, 4, true>(a);
     }
 
     const uint64_t fits = cus * (D == 64 ? 16 : 8);
@@ -1834,12 +1846,12 @@ hipError_t launch_groups(const void *q, const void *k, const void *v, void *o, i
     const bool two_for_192 = D == 64 && P % 64 == 0 && (two ? fullest_cu(2) <= fullest_cu(3) : 20 * fullest_cu(2) < 19 * fullest_cu(3));
     if (P % 96 == 0 && P % 128 != 0 && !two_for_192) {
         if constexpr (D == 64) {
-            if (P % 64 != 0) return launch_group<64, 3, 1, 3, true>(q, k, v, o, B, p, win, order, stream);
-            return two ? launch_group<64, 3, 2, 3, false>(q, k, v, o, B, p, win, order, stream)
-                       : launch_group<64, 3, 1, 3, false>(q, k, v, o, B, p, win, order, stream);
+            if (P % 64 != 0) return launch_group<64, 3, 1, 3, true>(a);
+            return two ? launch_group<64, 3, 2, 3, false>(a)
+                       : launch_group<64, 3, 1, 3, false>(a);
         } else {
-            return two ? launch_group<128, 3, 2, 3, true>(q, k, v, o, B, p, win, order, stream)
-                       : launch_group<128, 3, 1, 3, true>(q, k, v, o, B, p, win, order, stream);
+            return two ? launch_group<128, 3, 2, 3, true>(a)
+                       : launch_group<128, 3, 1, 3, true>(a);
         }
     }
     if (P % 64 == 0) {
@@ -1849,21 +1861,21 @@ hipError_t launch_groups(const void *q, const void *k, const void *v, void *o, i
             // 232; 64x64 at 5x5, 48, 6 rounds, 50 units 196, 210)
             const uint64_t blocks = waves / 2, places = 4 * cus;
             if (P % 128 != 0)
-                return two || (units >= 64 && blocks > places && 2 * blocks <= 3 * places) ? launch_group<128, 2, 2, 2, true>(q, k, v, o, B, p, win, order, stream)
-                           : launch_group<128, 2, 1, 2, true>(q, k, v, o, B, p, win, order, stream);
-            if (4 * waves <= fits && units >= 32) return launch_group<128, 2, 4, 2, false>(q, k, v, o, B, p, win, order, stream);
-            return two ? launch_group<128, 2, 2, 2, false>(q, k, v, o, B, p, win, order, stream)
-                       : launch_group<128, 2, 1, 2, false>(q, k, v, o, B, p, win, order, stream);
+                return two || (units >= 64 && blocks > places && 2 * blocks <= 3 * places) ? launch_group<128, 2, 2, 2, true>(a)
+                           : launch_group<128, 2, 1, 2, true>(a);
+            if (4 * waves <= fits && units >= 32) return launch_group<128, 2, 4, 2, false>(a);
+            return two ? launch_group<128, 2, 2, 2, false>(a)
+                       : launch_group<128, 2, 1, 2, false>(a);
         } else {
-            if (two) return launch_group<64, 2, 2, 4, false>(q, k, v, o, B, p, win, order, stream);
-            return P % 128 == 0 ? launch_group<64, 4, 1, 4, false, 2>(q, k, v, o, B, p, win, order, stream)
-                                : launch_group<64, 2, 1, 4, false>(q, k, v, o, B, p, win, order, stream);
+            if (two) return launch_group<64, 2, 2, 4, false>(a);
+            return P % 128 == 0 ? launch_group<64, 4, 1, 4, false, 2>(a)
+                                : launch_group<64, 2, 1, 4, false>(a);
         }
     }
     // other multiples of 32 tokens: one wave of queries, whose LDS stages then limit a CU to four such workgroups at head
     // dimension 128, with or without key groups (525 waves: 59 us, two groups 74)
-    if (D == 64 && two) return launch_group<64, 1, 2, 2, true>(q, k, v, o, B, p, win, order, stream);
-    return launch_group<D, 1, 1, D == 64 ? 3 : 1, true>(q, k, v, o, B, p, win, order, stream);
+    if (D == 64 && two) return launch_group<64, 1, 2, 2, true>(a);
+    return launch_group<D, 1, 1, D == 64 ? 3 : 1, true>(a);
 }
 
 // Test hook: the key-tile list of every (head, query tile) from the same box function.
@@ -1886,26 +1898,25 @@ __global__ void sta_dump_key_tiles_kernel(sta::FwdParams p, sta::WindowTable win
 }
 
 template <int D, int NW, int NQ, int KB, bool TW = false>
-hipError_t launch_cfg(const void *q, const void *k, const void *v, void *o, int B, const sta::FwdParams &p,
-                      const sta::WindowTable &win, hipStream_t stream)
+hipError_t launch_cfg(const FwdArgs &a)
 {
     using C = FwdCfg<D, NW, NQ, KB>;
-    dim3 grid(p.N / C::kQB, (uint32_t)B * p.heads);
+    dim3 grid(a.p.N / C::kQB, (uint32_t)a.B * a.p.heads);
     dim3 block(C::kThreads);
-    sta_fwd_kernel<D, NW, NQ, KB, TW><<<grid, block, 0, stream>>>(
-        static_cast<const bf16_raw *>(q), static_cast<const bf16_raw *>(k), static_cast<const bf16_raw *>(v),
-        static_cast<bf16_raw *>(o), p, win);
+    if (a.note) return a.note->add("general<%d,%d,%d>", D, NW, KB);
+    sta_fwd_kernel<D, NW, NQ, KB, TW><<<grid, block, 0, a.stream>>>(
+        static_cast<const bf16_raw *>(a.q), static_cast<const bf16_raw *>(a.k), static_cast<const bf16_raw *>(a.v),
+        static_cast<bf16_raw *>(a.o), a.p, a.win);
     return hipGetLastError();
 }
 
 template <int D, bool TW = false>
-hipError_t launch_d(const void *q, const void *k, const void *v, void *o, int B, const sta::FwdParams &p,
-                    const sta::WindowTable &win, hipStream_t stream)
+hipError_t launch_d(const FwdArgs &a)
 {
-    const uint32_t P = p.P;
-    if (P % 128 == 0) return launch_cfg<D, 4, 1, 64, TW>(q, k, v, o, B, p, win, stream);
-    if (P % 64 == 0) return launch_cfg<D, 2, 1, 64, TW>(q, k, v, o, B, p, win, stream);
-    if (P % 32 == 0) return launch_cfg<D, 1, 1, 32, TW>(q, k, v, o, B, p, win, stream);
+    const uint32_t P = a.p.P;
+    if (P % 128 == 0) return launch_cfg<D, 4, 1, 64, TW>(a);
+    if (P % 64 == 0) return launch_cfg<D, 2, 1, 64, TW>(a);
+    if (P % 32 == 0) return launch_cfg<D, 1, 1, 32, TW>(a);
     return hipErrorInvalidValue;
 }
 
@@ -1937,14 +1948,15 @@ size_t forward_split_workspace_bytes(int P, int D)
 
 hipError_t launch_forward(const void *q, const void *k, const void *v, void *o, int B, int D, const FwdParams &p,
                           const WindowTable &win, const HeadOrder &order, float *split_ws, size_t split_ws_floats,
-                          hipStream_t stream)
+                          hipStream_t stream, LaunchNote *note)
 {
     if (!forward_supported((int)p.P, D)) return hipErrorInvalidValue;
+    const FwdArgs a = {q, k, v, o, B, p, win, order, split_ws, split_ws_floats, stream, note};
     // K or V at an odd address: tiles that have not always been staged by DMA keep to plain loads, which take any address.
     if (p.P % (D == 64 ? 64 : 128) != 0 && !(dma_aligned(k) && dma_aligned(v)))
-        return D == 64 ? launch_d<64>(q, k, v, o, B, p, win, stream) : launch_d<128>(q, k, v, o, B, p, win, stream);
-    if (D == 64) return launch_groups<64>(q, k, v, o, B, p, win, order, stream);
-    if (p.P % 128 != 0) return launch_groups<128>(q, k, v, o, B, p, win, order, stream);
+        return D == 64 ? launch_d<64>(a) : launch_d<128>(a);
+    if (D == 64) return launch_groups<64>(a);
+    if (p.P % 128 != 0) return launch_groups<128>(a);
     // Tiles of 128 tokens' multiples.  Up to 1280 waves of 32 queries (the chip holds 2048 of the key-group kernel's at this
     // head dimension) the key-group kernel: more and smaller workgroups, and key groups that need no workspace.  Where one is
     // given, items cut into parts come close on long walks, and only launches of up to 256 waves or walks of up to 80 units
@@ -1953,8 +1965,8 @@ hipError_t launch_forward(const void *q, const void *k, const void *v, void *o, 
     // tiles, one head (100, 36) 27, 26, 17, twelve (1200, 36) 37, 54, 34; 16x8x40 in 128-token tiles, four heads (640, 120) 76,
     // 64, 58, eight (1280, 120) 102, 104, 99; 12x32x40 in 256-token tiles, four heads (1920, 216) 255, 255, 280.
     const uint64_t cus = compute_units(), slices = (uint64_t)B * p.heads, waves = slices * (p.N / 32);
-    if (waves <= 5 * cus && (split_ws == nullptr || waves <= cus || longest_walk(p, win, order) <= 80))
-        return launch_groups<128>(q, k, v, o, B, p, win, order, stream);
+    if (waves <= 5 * cus && (split_ws == nullptr || waves <= cus || longest_walk(a) <= 80))
+        return launch_groups<128>(a);
     // A tile of 384 tokens (the paper's 6x8x8) gets one 12-wave workgroup per query tile: every K/V sub-block
     // fetched from L2 then serves 384 queries instead of 128.  Measured at the 115,200-token layer, window
     // 3x3x3: 12.8-13.1 ms against 13.6-13.7 ms for the 4-wave shape in the same session.  Not where the last round of such
@@ -1963,19 +1975,21 @@ hipError_t launch_forward(const void *q, const void *k, const void *v, void *o, 
     const uint64_t items = slices * (p.N / 384), rounds = (items + cus - 1) / cus;
     const bool in_parts = split_ws != nullptr && 2 * (items % cus) <= cus;
     if (p.P % 384 == 0 && (in_parts || 10 * items >= 7 * rounds * cus))
-        return launch_x32<12, 32, 2, 1>(q, k, v, o, B, p, win, order, split_ws, split_ws_floats, stream);
-    return launch_x32<4, 32, 2, 3>(q, k, v, o, B, p, win, order, split_ws, split_ws_floats, stream);
+        return launch_x32<12, 32, 2, 1>(a);
+    return launch_x32<4, 32, 2, 3>(a);
 }
 
 hipError_t launch_forward_general(const void *q, const void *k, const void *v, void *o, int B, int D, const FwdParams &p,
                                   const WindowTable &win, bool token_window, hipStream_t stream)
 {
     if (!forward_supported((int)p.P, D)) return hipErrorInvalidValue;
+    const HeadOrder order = {};                             // the general kernel takes the heads as they come
+    const FwdArgs a = {q, k, v, o, B, p, win, order, nullptr, 0, stream, nullptr};
     if (token_window) {
         if (p.P > kMaxTokenWindowTile || p.T_t > 1023 || p.T_h > 1023 || p.T_w > 1023) return hipErrorInvalidValue;
-        return D == 64 ? launch_d<64, true>(q, k, v, o, B, p, win, stream) : launch_d<128, true>(q, k, v, o, B, p, win, stream);
+        return D == 64 ? launch_d<64, true>(a) : launch_d<128, true>(a);
     }
-    return D == 64 ? launch_d<64>(q, k, v, o, B, p, win, stream) : launch_d<128>(q, k, v, o, B, p, win, stream);
+    return D == 64 ? launch_d<64>(a) : launch_d<128>(a);
 }
 
 hipError_t launch_dump_key_tiles(const FwdParams &p, const WindowTable &win, int32_t *counts, int32_t *lists,

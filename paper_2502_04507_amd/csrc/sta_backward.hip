@@ -887,6 +887,7 @@ struct BwdArgs {
     const sta::WindowTable &win;
     const sta::HeadOrder &order;
     hipStream_t stream;
+    sta::LaunchNote *note;      // not null: the shape is written there and nothing is launched
 };
 
 // Sub-blocks of the walk of a head away from the borders; heads by rank, the one with the most key tiles first.
@@ -941,6 +942,7 @@ hipError_t launch_dq(const BwdArgs &a)
 {
     uint32_t ids;
     const BwdPlan plan = make_plan(a, QW * 32, false, false, &ids);
+    if (a.note) return a.note->add("dq<%d,%d,%d,%d> items %u chunk %u", D, QW, G, (int)DMA, plan.total, plan.chunk.d);
     sta_bwd_dq_kernel<D, QW, G, DMA><<<dim3(ids), dim3(QW * G * 64), 0, a.stream>>>(a.q, a.k, a.v, a.o, a.d_o, a.lse, a.neg_delta, a.neg_lse,
                                                                               a.d_q, a.p, plan);
     return hipGetLastError();
@@ -983,6 +985,7 @@ hipError_t launch_dkv(const BwdArgs &a)
     const uint64_t resident = (uint64_t)sta::compute_units() * (D == 64 ? 12 : 8) / (NW * G);     // workgroups
     const bool row_major = rows_of_all_heads(a, NW * 32, resident), longest_first = a.p.P % 96 == 0 && a.p.P % 128 != 0;
     const BwdPlan plan = make_plan(a, NW * 32, row_major, row_major && longest_first, &ids);
+    if (a.note) return a.note->add("dkv<%d,%d,%d,%d,%d> items %u chunk %u", D, NW, G, UPS, (int)DMA, plan.total, plan.chunk.d);
     sta_bwd_dkv_kernel<D, NW, G, UPS, DMA><<<dim3(ids), dim3(NW * G * 64), 0, a.stream>>>(a.q, a.k, a.v, a.d_o, a.neg_lse, a.neg_delta,
                                                                                     a.d_k, a.d_v, a.p, plan);
     return hipGetLastError();
@@ -995,6 +998,7 @@ hipError_t launch_dkv_pairs(const BwdArgs &a)
     const uint64_t resident = (uint64_t)sta::compute_units() * 12 / (2 * NPAIR * G);     // workgroups
     const bool row_major = rows_of_all_heads(a, NPAIR * 32, resident), longest_first = a.p.P % 96 == 0;
     const BwdPlan plan = make_plan(a, NPAIR * 32, row_major, row_major && longest_first, &ids);
+    if (a.note) return a.note->add("dkv_pair<%d,%d,%d> items %u chunk %u", NPAIR, G, (int)DMA, plan.total, plan.chunk.d);
     sta_bwd_dkv_pair_kernel<NPAIR, G, DMA><<<dim3(ids), dim3(NPAIR * G * 128), 0, a.stream>>>(a.q, a.k, a.v, a.d_o, a.neg_lse, a.neg_delta,
                                                                                         a.d_k, a.d_v, a.p, plan);
     return hipGetLastError();
@@ -1087,13 +1091,13 @@ bool backward_supported(int P, int D) { return (D == 64 || D == 128) && P > 0 &&
 
 hipError_t launch_backward(const void *q, const void *k, const void *v, const void *o, const void *d_o, const float *lse,
                            float *stats, size_t stat_rows, void *d_q, void *d_k, void *d_v, int B, int D, const FwdParams &p,
-                           const WindowTable &win, const HeadOrder &order, hipStream_t stream)
+                           const WindowTable &win, const HeadOrder &order, hipStream_t stream, LaunchNote *note)
 {
     if (!backward_supported((int)p.P, D)) return hipErrorInvalidValue;
     const BwdArgs a = {static_cast<const bf16_raw *>(q), static_cast<const bf16_raw *>(k), static_cast<const bf16_raw *>(v),
                        static_cast<const bf16_raw *>(o), static_cast<const bf16_raw *>(d_o), lse, stats, stats + stat_rows,
                        static_cast<bf16_raw *>(d_q), static_cast<bf16_raw *>(d_k), static_cast<bf16_raw *>(d_v), B, D, p, win, order,
-                       stream};
+                       stream, note};
     const hipError_t e = D == 64 ? dispatch_dq<64>(a) : dispatch_dq<128>(a);
     if (e != hipSuccess) return e;
     return D == 64 ? dispatch_dkv<64>(a) : dispatch_dkv<128>(a);

@@ -1,7 +1,9 @@
 // Internal declarations shared by the translation units of libsta (GPU side only).
 #pragma once
 #include <hip/hip_runtime.h>
+#include <stdarg.h>
 #include <stdint.h>
+#include <stdio.h>
 
 namespace sta {
 
@@ -45,6 +47,24 @@ hipError_t launch_permute(const void *src, void *dst, bool src_f32, bool dst_f32
                           PermuteParams p, uint64_t tiles, hipStream_t stream);
 
 // ---- attention -------------------------------------------------------------
+// What a launch would run, as text, one line per kernel: for tests of the rules that choose the shapes, without a GPU.
+struct LaunchNote {
+    char *text;
+    size_t size, used = 0;
+    __attribute__((format(printf, 2, 3))) hipError_t add(const char *format, ...)
+    {
+        va_list args;
+        va_start(args, format);
+        const int n = vsnprintf(text + used, size - used, format, args);
+        va_end(args);
+        if (n < 0 || (size_t)n + 1 >= size - used) return hipErrorInvalidValue;
+        used += (size_t)n + 1;
+        text[used - 1] = '\n';
+        text[used] = 0;
+        return hipSuccess;
+    }
+};
+
 uint32_t compute_units();           // of the device that is current at the first call
 
 constexpr int kMaxHeadsPerLaunch = 256;
@@ -98,7 +118,7 @@ struct FwdPlan {
 // split_ws: optional device scratch for work splitting (null: every item is run by one workgroup).
 hipError_t launch_forward(const void *q, const void *k, const void *v, void *o, int B, int D,
                           const FwdParams &p, const WindowTable &win, const HeadOrder &order, float *split_ws,
-                          size_t split_ws_floats, hipStream_t stream);
+                          size_t split_ws_floats, hipStream_t stream, LaunchNote *note = nullptr);
 size_t forward_split_workspace_bytes(int P, int D);    // upper bound of what the splitting ever uses
 // The general (register-staged) kernel for any supported shape.  token_window = false: the STA mask, win in tiles
 // (same results as launch_forward).  token_window = true: the token-granular sliding window, win in tokens.
@@ -112,7 +132,7 @@ bool forward_supported(int P, int D);
 // (filled by the call, for the heads of the launch).
 hipError_t launch_backward(const void *q, const void *k, const void *v, const void *o, const void *d_o, const float *lse,
                            float *stats, size_t stat_rows, void *d_q, void *d_k, void *d_v, int B, int D, const FwdParams &p,
-                           const WindowTable &win, const HeadOrder &order, hipStream_t stream);
+                           const WindowTable &win, const HeadOrder &order, hipStream_t stream, LaunchNote *note = nullptr);
 bool backward_supported(int P, int D);
 
 // ---- reductions around the attention kernel ----------------------------------
