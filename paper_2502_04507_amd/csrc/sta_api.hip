@@ -539,6 +539,13 @@ int sta_describe_launches(int gradients, int B, int H, int D, const int grid[3],
     return STA_OK;
 }
 
+// Nor this: the items of a forward launch of so many per slice, in the order of the workgroup ids that run them.
+void sta_dealt_items(uint32_t per_head, uint32_t slices, uint32_t *items)
+{
+    const sta::Deal d = sta::deal_of(per_head, slices);
+    for (uint32_t id = 0; id < d.total; ++id) items[id] = sta::dealt_item(id, d);
+}
+
 int sta_dump_key_tiles(int H, const int grid[3], const int tile[3], const int *window_tiles, int32_t *dev_counts,
                        int32_t *dev_lists, void *hip_stream)
 {

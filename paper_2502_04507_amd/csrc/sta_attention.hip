@@ -348,7 +348,11 @@ __host__ __device__ __forceinline__ size_t split_part_floats(int QB) { return (s
 // mixed per-head windows this halved the launch time), its resident workgroups are neighbouring query blocks of one head (shared
 // K/V in L2), and where a head has only a few items no XCD gets one more of every head than the others (eighteen 384-token items
 // a head, 28 heads, 1x2x3: 249 us with exact eighths of every head, which gave two XCDs three rounds of workgroups where two are
-// needed, 193 in chunks; fifteen of 25 items 281, 219).  Heads are visited in descending cost order, so the tail of the launch is made of cheap items.
+// needed, 193 in chunks; fifteen of 25 items 281, 219).  The last round of chunks divides what is left evenly (see Deal): whole
+// layers, us, with a last round of whole chunks, which some XCDs get and others do not, and evenly: seven heads of 6x16x24 in
+// 384-token tiles, head dimension 64, 1x2x3 (252 items: 35 on the fullest XCD's 32 CUs, 32) 43.0, 32.0; 15 of 6x40x40 in 128-token
+// tiles, 3x3x3 297, 284; 24 of 30x48x80, 3x3x3 12.29, 11.92 ms.  Heads are visited in descending cost order, so the tail of the
+// launch is made of cheap items.
 // Inside a head the query tiles are scheduled by pairs of tile rows (h), then w, then the row of the pair, then t fastest, so that
 // the ~32 tiles resident on an XCD at one time form a compact 3-D block, (all t) x (2 h) x (about 3 w), and share key tiles along
 // all three axes (measured: reads past L2 9.8 -> 6.4 GB per launch against plain tile-id order, 12.81 -> 12.74 ms).
@@ -356,7 +360,6 @@ __host__ __device__ __forceinline__ size_t split_part_floats(int QB) { return (s
 // of the walk took 7500 cycles of a workgroup that has 24,000 cycles of work to do, a 64-token image tile at window 3x3; now 2000,
 // most of it waiting for the kernel arguments.
 struct GroupItem {
-    bool valid;
     size_t bh;
     uint32_t qblock;
     StaBox box;
@@ -364,11 +367,7 @@ struct GroupItem {
 __device__ __forceinline__ GroupItem group_item_of(uint32_t id, const sta::FwdParams &p, const sta::FwdPlan &plan)
 {
     GroupItem it;
-    const uint32_t xcd = id & 7, slot = id >> 3;
-    const uint32_t chunk = fast_div(slot, plan.chunk);
-    const uint32_t linear = (chunk * 8 + xcd) * plan.chunk.d + (slot - chunk * plan.chunk.d);
-    it.valid = linear < plan.total;
-    if (!it.valid) return it;
+    const uint32_t linear = sta::dealt_item(id, plan.deal);
     const uint32_t rank = fast_div(linear, plan.per_head), pos = linear - rank * plan.per_head.d;
     const uint32_t head_rank = fast_div(rank, plan.batch);                  // batch entries of one head are adjacent
     const sta::FwdPlan::Head head = plan.head[head_rank];
@@ -448,7 +447,6 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
     __shared__ uint32_t redo_of[QW * KG];
 
     const GroupItem item = group_item_of(blockIdx.x, p, plan);
-    if (!item.valid) return;
     const uint32_t qblock = item.qblock;
     const size_t bh = item.bh;
     const StaBox box = item.box;
@@ -830,7 +828,6 @@ void sta_fwd_solo_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restr
     __shared__ __attribute__((aligned(1024))) char smem[OUT + QB * L::RowB];
 
     const GroupItem item = group_item_of(blockIdx.x, p, plan);
-    if (!item.valid) return;
     const size_t bh = item.bh;
     const StaBox box = item.box;
     const int tid = threadIdx.x;
@@ -1141,7 +1138,6 @@ __global__ __launch_bounds__(NW * 64, MINB) void sta_fwd_x32_kernel(const bf16_r
         part = idx - (item_id - p.split_first) * p.split_parts;
     }
     const GroupItem item = group_item_of(item_id, p, plan);
-    if (!item.valid) return;
     const uint32_t qblock = item.qblock;
     const size_t bh = item.bh;
     const StaBox box = item.box;
@@ -1600,7 +1596,6 @@ __global__ __launch_bounds__(256) void sta_fwd_combine_kernel(bf16_raw *__restri
     constexpr int ROWS = 4;                                    // per lane, two rows apart
     const uint32_t item_id = p.split_first + blockIdx.y;
     const GroupItem item = group_item_of(item_id, p, plan);
-    if (!item.valid) return;
     const int lane = threadIdx.x & 63;
     const int row0 = blockIdx.x * 32 + (threadIdx.x >> 6) * 8 + (lane >> 5), channel = 4 * (lane & 31);
     const float *ws = p.split_ws + (size_t)blockIdx.y * p.split_parts * split_part_floats<D>(QB);
@@ -1656,17 +1651,13 @@ struct FwdArgs {
     sta::LaunchNote *note;      // not null: the shape is written there and nothing is launched
 };
 
-// The plan of a launch of query blocks of 32 * waves queries, and its workgroup ids.
-sta::FwdPlan make_plan(int waves, const FwdArgs &a, uint32_t *ids)
+// The plan of a launch of query blocks of 32 * waves queries.
+sta::FwdPlan make_plan(int waves, const FwdArgs &a)
 {
     const sta::FwdParams &p = a.p;
     sta::FwdPlan plan;
-    const uint32_t per_head = p.N / (waves * 32), n_bh = (uint32_t)a.B * p.heads;
-    plan.total = per_head * n_bh;
-    // as many rounds of chunks as eighths of a head would take, of equal length
-    const uint32_t eighth = (per_head + 7) / 8, rounds = (plan.total + 8 * eighth - 1) / (8 * eighth);
-    const uint32_t chunk = (plan.total + 8 * rounds - 1) / (8 * rounds);
-    plan.chunk = sta::fast_div_of(chunk);
+    const uint32_t per_head = p.N / (waves * 32);
+    plan.deal = sta::deal_of(per_head, (uint32_t)a.B * p.heads);
     plan.per_head = sta::fast_div_of(per_head);
     plan.per_tile = sta::fast_div_of(p.P / (waves * 32));
     plan.pair_items = sta::fast_div_of(2 * p.n_w * p.n_t);
@@ -1677,8 +1668,35 @@ sta::FwdPlan make_plan(int waves, const FwdArgs &a, uint32_t *ids)
         plan.head[h].h = a.order.h[h];
         for (int i = 0; i < 3; ++i) plan.head[h].w[i] = a.win.w[a.order.h[h]][i];
     }
-    *ids = 8 * chunk * ((plan.total + 8 * chunk - 1) / (8 * chunk));
     return plan;
+}
+
+// Items of qb queries beyond the last full round of workgroups are cut into parts that fill the chip once: how many parts
+// each of them gets, 1 where they are left whole (no workspace, more than half a round, walks too short).  They are the last ids,
+// all of which name an item, so that the parts never need more than one resident set of the workspace.  (While ids without an
+// item stood among them and took slots, launches with few items in a round of chunks were left whole: whole layers, us, whole and
+// in parts, nine heads of 12x24x40 in 384-token tiles, 1x3x3 279, 219, 1x3x5 428, 301; 13 of 6x48x80, 1x3x3 604, 546; 19 of
+// 18x24x24, 3x3x3 1124, 938.)
+uint32_t parts_of_tail(const FwdArgs &a, uint32_t items, uint32_t capacity, int qb)
+{
+    const sta::FwdParams &p = a.p;
+    const uint32_t tail = items % capacity;
+    if (a.split_ws == nullptr || tail == 0 || 2 * tail > capacity) return 1;
+    uint32_t parts = capacity / tail;
+    // a part should keep at least four sub-blocks of the cheapest item of the launch
+    uint32_t min_tiles = 0xffffffffu;
+    for (uint32_t h = 0; h < p.heads; ++h) {
+        uint32_t tiles = 1;
+        const uint32_t n[3] = {p.n_t, p.n_h, p.n_w};
+        for (int i = 0; i < 3; ++i) {
+            const uint32_t kept = 2 * (a.win.w[h][i] / 2) + 1;
+            tiles *= kept < n[i] ? kept : n[i];
+        }
+        min_tiles = tiles < min_tiles ? tiles : min_tiles;
+    }
+    const uint32_t min_iters = min_tiles * (p.P / kSub);
+    while (parts > 1 && min_iters / parts < 4) --parts;
+    return (size_t)tail * parts * split_part_floats<128>(qb) <= a.split_ws_floats ? parts : 1;
 }
 
 template <int NW, int KB, int STAGES, int MINB>
@@ -1686,51 +1704,14 @@ hipError_t launch_x32(const FwdArgs &a)
 {
     constexpr int D = 128, QB = NW * 32;
     sta::FwdParams p = a.p;
-    uint32_t ids;                                                 // item ids; some of them name no item
-    const sta::FwdPlan plan = make_plan(NW, a, &ids);
-    p.split_first = ids;
-    p.split_parts = 1;
-    p.split_ws = nullptr;
-    uint32_t split_items = 0;
-    if (a.split_ws != nullptr) {
-        // Items beyond the last full round of workgroups are split so that their parts fill the chip once.
-        auto names_item = [&](uint32_t id) {
-            const uint32_t slot = id >> 3, chunk = slot / plan.chunk.d;
-            return (chunk * 8 + (id & 7)) * plan.chunk.d + (slot - chunk * plan.chunk.d) < plan.total;
-        };
-        const uint32_t capacity = resident_workgroups(MINB);
-        const uint32_t tail = plan.total % capacity;
-        if (tail != 0 && 2 * tail <= capacity) {
-            uint32_t parts = capacity / tail;
-            // a part should keep at least four sub-blocks of the cheapest item of the launch
-            uint32_t min_tiles = 0xffffffffu;
-            for (uint32_t h = 0; h < p.heads; ++h) {
-                uint32_t tiles = 1;
-                const uint32_t n[3] = {p.n_t, p.n_h, p.n_w};
-                for (int i = 0; i < 3; ++i) {
-                    const uint32_t kept = 2 * (a.win.w[h][i] / 2) + 1;
-                    tiles *= kept < n[i] ? kept : n[i];
-                }
-                min_tiles = tiles < min_tiles ? tiles : min_tiles;
-            }
-            const uint32_t min_iters = min_tiles * (p.P / KB);
-            while (parts > 1 && min_iters / parts < 4) --parts;
-            uint32_t first = ids, found = 0;
-            while (first > 0 && found < tail) {
-                --first;
-                if (names_item(first)) ++found;
-            }
-            const size_t need = (size_t)(ids - first) * parts * split_part_floats<D>(QB);
-            if (parts > 1 && found == tail && need <= a.split_ws_floats) {
-                p.split_first = first;
-                p.split_parts = parts;
-                p.split_ws = a.split_ws;
-                split_items = ids - first;
-            }
-        }
-    }
+    const sta::FwdPlan plan = make_plan(NW, a);
+    const uint32_t items = plan.deal.total, capacity = resident_workgroups(MINB);
+    p.split_parts = parts_of_tail(a, items, capacity, QB);
+    const uint32_t split_items = p.split_parts > 1 ? items % capacity : 0;
+    p.split_first = items - split_items;
+    p.split_ws = split_items ? a.split_ws : nullptr;
     dim3 grid(p.split_first + split_items * p.split_parts), block(NW * 64);
-    if (a.note) return a.note->add("x32<%d> items %u workgroups %u parts %u of %u", NW, plan.total, grid.x, p.split_parts, split_items);
+    if (a.note) return a.note->add("x32<%d> items %u workgroups %u parts %u of %u", NW, items, grid.x, p.split_parts, split_items);
     sta_fwd_x32_kernel<NW, KB, STAGES, MINB, false><<<grid, block, 0, a.stream>>>(
         static_cast<const bf16_raw *>(a.q), static_cast<const bf16_raw *>(a.k), static_cast<const bf16_raw *>(a.v),
         static_cast<bf16_raw *>(a.o), p, plan);
@@ -1743,10 +1724,9 @@ hipError_t launch_x32(const FwdArgs &a)
 template <int D, int QW, int KG, int WPE, bool FOLLOW, int UPS = 1>
 hipError_t launch_group(const FwdArgs &a)
 {
-    uint32_t ids;
-    const sta::FwdPlan plan = make_plan(QW, a, &ids);
-    if (a.note) return a.note->add("group<%d,%d,%d,%d> items %u workgroups %u", D, QW, KG, UPS, plan.total, ids);
-    sta_fwd_group_kernel<D, QW, KG, WPE, FOLLOW, UPS><<<dim3(ids), dim3(QW * KG * 64), 0, a.stream>>>(
+    const sta::FwdPlan plan = make_plan(QW, a);
+    if (a.note) return a.note->add("group<%d,%d,%d,%d> items %u workgroups %u", D, QW, KG, UPS, plan.deal.total, plan.deal.total);
+    sta_fwd_group_kernel<D, QW, KG, WPE, FOLLOW, UPS><<<dim3(plan.deal.total), dim3(QW * KG * 64), 0, a.stream>>>(
         static_cast<const bf16_raw *>(a.q), static_cast<const bf16_raw *>(a.k), static_cast<const bf16_raw *>(a.v),
         static_cast<bf16_raw *>(a.o), a.p, plan);
     return hipGetLastError();
@@ -1755,10 +1735,9 @@ hipError_t launch_group(const FwdArgs &a)
 template <int D, int NQ, int KG, bool FOLLOW>
 hipError_t launch_solo(const FwdArgs &a)
 {
-    uint32_t ids;
-    const sta::FwdPlan plan = make_plan(NQ / 2, a, &ids);
-    if (a.note) return a.note->add("solo<%d,%d,%d> items %u workgroups %u", D, NQ, KG, plan.total, ids);
-    sta_fwd_solo_kernel<D, NQ, KG, D == 64 && NQ == 2 ? 4 : 2, FOLLOW><<<dim3(ids), dim3(KG * 64), 0, a.stream>>>(
+    const sta::FwdPlan plan = make_plan(NQ / 2, a);
+    if (a.note) return a.note->add("solo<%d,%d,%d> items %u workgroups %u", D, NQ, KG, plan.deal.total, plan.deal.total);
+    sta_fwd_solo_kernel<D, NQ, KG, D == 64 && NQ == 2 ? 4 : 2, FOLLOW><<<dim3(plan.deal.total), dim3(KG * 64), 0, a.stream>>>(
         static_cast<const bf16_raw *>(a.q), static_cast<const bf16_raw *>(a.k), static_cast<const bf16_raw *>(a.v),
         static_cast<bf16_raw *>(a.o), a.p, plan);
     return hipGetLastError();
@@ -1940,8 +1919,8 @@ bool forward_supported(int P, int D) { return (D == 64 || D == 128) && P > 0 && 
 size_t forward_split_workspace_bytes(int P, int D)
 {
     if (D != 128 || P % 128 != 0) return 0;
-    // About one resident set of workgroups leaves partial results, QB queries x (128 + 2) floats each; twice
-    // that, because ids that name no item (ranges of unequal length) also take a slot.
+    // At most one resident set of workgroups leaves partial results, QB queries x (128 + 2) floats each.  (Twice that, as it has
+    // always been: a caller's workspace has to have this size.)
     if (P % 384 == 0) return (size_t)2 * resident_workgroups(1) * 384 * 130 * sizeof(float);
     return (size_t)2 * resident_workgroups(3) * 128 * 130 * sizeof(float);
 }
@@ -1973,8 +1952,7 @@ hipError_t launch_forward(const void *q, const void *k, const void *v, void *o, 
     // workgroups would be mostly empty and is not cut into parts (12x48x48, window 1x3x3, us, 12 waves against 4: two heads,
     // 0.56 rounds, 117, 97; three, 0.84, 126, 141; four, 1.13, 244, 194 and with parts 180, 184; six, 1.69, 252, 276).
     const uint64_t items = slices * (p.N / 384), rounds = (items + cus - 1) / cus;
-    const bool in_parts = split_ws != nullptr && 2 * (items % cus) <= cus;
-    if (p.P % 384 == 0 && (in_parts || 10 * items >= 7 * rounds * cus))
+    if (p.P % 384 == 0 && (parts_of_tail(a, (uint32_t)items, (uint32_t)cus, 384) > 1 || 10 * items >= 7 * rounds * cus))
         return launch_x32<12, 32, 2, 1>(a);
     return launch_x32<4, 32, 2, 3>(a);
 }

@@ -83,12 +83,7 @@ __device__ __forceinline__ void scale_in_place(floatx4 &x, float a)
                  : "v"(a));
 }
 
-// n divided by the launch constant of f.
-__device__ __forceinline__ uint32_t fast_div(uint32_t n, const sta::FastDiv &f)
-{
-    const uint32_t q = __umulhi(n, f.magic);
-    return (((n - q) >> f.pre) + q) >> f.post;
-}
+using sta::fast_div;
 
 template <int I, int N, typename F>
 __device__ __forceinline__ void static_for(F &&f)

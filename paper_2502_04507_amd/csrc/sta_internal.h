@@ -99,15 +99,55 @@ struct FwdParams {
 // The DMA into LDS fetches 16 bytes per lane; tensors are only asked to hold elements.
 inline bool dma_aligned(const void *p) { return ((uintptr_t)p & 15) == 0; }
 
-// How the work items of one launch of the key-group forward kernel are dealt to the workgroups, with everything a workgroup
-// would otherwise have to find by division (see group_item_of).
-struct FwdPlan {
-    uint32_t total;            // work items
+// n divided by the launch constant of f.
+__host__ __device__ __forceinline__ uint32_t fast_div(uint32_t n, const FastDiv &f)
+{
+    const uint32_t q = (uint32_t)(((uint64_t)n * f.magic) >> 32);
+    return (((n - q) >> f.pre) + q) >> f.post;
+}
+
+// How the items of a forward launch are dealt to the workgroup ids, which the hardware gives to the 8 XCDs in turn: rounds of
+// eight chunks of consecutive items, one per XCD, and a last round that divides what is left evenly (the first last_more XCDs
+// get one item more).  Every id below total names an item, and no XCD gets more than one item more than another.
+struct Deal {
+    uint32_t total;            // items
     FastDiv chunk;             // consecutive items of one XCD
+    uint32_t last_slot;        // slots (ids of one XCD) in full rounds
+    uint32_t last_len, last_more;
+};
+// per_head items of each of n_bh (batch, head) slices: as many rounds of chunks as eighths of a head would take.
+inline Deal deal_of(uint32_t per_head, uint32_t n_bh)
+{
+    Deal d;
+    d.total = per_head * n_bh;
+    const uint32_t eighth = (per_head + 7) / 8, rounds = (d.total + 8 * eighth - 1) / (8 * eighth);
+    const uint32_t chunk = (d.total + 8 * rounds - 1) / (8 * rounds);
+    d.chunk = fast_div_of(chunk);
+    d.last_slot = d.total / (8 * chunk) * chunk;
+    const uint32_t left = d.total - 8 * d.last_slot;
+    d.last_len = left / 8;
+    d.last_more = left % 8;
+    return d;
+}
+__host__ __device__ __forceinline__ uint32_t dealt_item(uint32_t id, const Deal &d)
+{
+    // without a branch: a workgroup waits for this before anything else
+    const uint32_t xcd = id & 7, slot = id >> 3, first_slot = fast_div(slot, d.chunk) * d.chunk.d;       // of the round
+    const bool last = slot >= d.last_slot;
+    const uint32_t more = xcd < d.last_more ? xcd : d.last_more;
+    return slot + 7 * first_slot + xcd * (last ? d.last_len : d.chunk.d) + (last ? more : 0);
+}
+
+// The work items of one launch of a forward kernel, with everything a workgroup would otherwise have to find by division
+// (see group_item_of).
+struct FwdPlan {
+    // what leads to the head stands first: one scalar load brings it, and the rest is on its way with the head's window
+    Deal deal;
     FastDiv per_head;          // items of one (batch, head)
+    FastDiv batch;
     FastDiv per_tile;          // items of one query tile
     FastDiv pair_items;        // query tiles of two tile rows
-    FastDiv n_t, batch;
+    FastDiv n_t;
     FastDiv sub_per_tile;      // 32-key units of a key tile
     struct Head {
         uint16_t h, w[3];      // head inside the launch, its window in tiles; most expensive head first

@@ -1,0 +1,49 @@
+"""Host-side rules of the forward and gradient launches: which item a workgroup id runs, where the last round of workgroups is
+cut into parts.  No GPU: without one the rules count 256 compute units."""
+import ctypes
+import re
+
+import numpy as np
+import pytest
+
+import paper_2502_04507_amd as sta
+from tests.launch_shapes import launches
+
+CUS = 256
+
+
+@pytest.mark.parametrize("per_head", [1, 2, 3, 7, 8, 9, 25, 36, 41, 108, 300, 1201])
+def test_every_workgroup_id_names_an_item_and_the_xcds_get_equal_shares(per_head):
+    for slices in (1, 2, 3, 7, 8, 9, 24, 48, 333):
+        total = per_head * slices
+        items = np.full(total + 1, 0xffffffff, dtype=np.uint32)
+        sta.load_library().sta_dealt_items(per_head, slices, ctypes.c_void_p(items.ctypes.data))
+        assert items[total] == 0xffffffff
+        items = items[:total]
+        assert np.array_equal(np.sort(items), np.arange(total)), (per_head, slices)
+        # ids go to the XCDs in turn, so their shares are equal as they are; each takes runs of about an eighth of a head
+        share = items[::8]
+        runs = 1 + np.count_nonzero(np.diff(share.astype(np.int64)) != 1)
+        assert runs <= -(-total // (8 * -(-per_head // 8))) + 1, (per_head, slices, runs)
+
+
+@pytest.mark.parametrize("grid,window", [((12, 24, 40), (1, 3, 3)), ((6, 48, 80), (1, 3, 3)), ((18, 48, 48), (3, 3, 3)),
+                                         ((6, 40, 40), (1, 3, 3)), ((30, 48, 80), (3, 3, 3)), ((18, 24, 24), (1, 1, 1))])
+def test_a_last_round_of_at_most_half_is_cut_into_parts(grid, window):
+    """384-token tiles, head dimension 128, with a workspace: one workgroup of 12 waves per tile and CU."""
+    per_head = grid[0] * grid[1] * grid[2] // 384
+    cut = 0
+    for heads in range(1, 97):
+        items = per_head * heads
+        tail = items % CUS
+        if items < CUS or tail == 0 or 2 * tail > CUS:
+            continue
+        (line,) = launches(1, heads, 128, grid, (6, 8, 8), [window], workspace=True)
+        match = re.fullmatch(r"x32<12> items %d workgroups (\d+) parts (\d+) of (\d+)" % items, line)
+        assert match, line
+        workgroups, parts, of = map(int, match.groups())
+        units = 12 * np.prod([min(2 * (w // 2) + 1, g // t) for w, g, t in zip(window, grid, (6, 8, 8))])
+        want = min(CUS // tail, max(p for p in range(1, units + 1) if units // p >= 4))
+        assert (parts, of, workgroups) == (want, tail, items - tail + tail * want), line
+        cut += 1
+    assert cut > 10
