@@ -43,8 +43,7 @@ constexpr float kLn2 = 0.6931471805599453f;
 
 // How the column blocks (queries or keys) of one launch are dealt to the workgroups, with every division prepared.
 struct BwdPlan {
-    uint32_t total;            // column blocks
-    sta::FastDiv chunk;        // consecutive blocks of one XCD
+    sta::Deal deal;            // of the column blocks
     sta::FastDiv per_row;      // blocks of one row of tiles along w
     sta::FastDiv rows;         // such rows of one (batch, head)
     sta::FastDiv slices;       // (batch, head) pairs
@@ -70,13 +69,12 @@ __device__ __forceinline__ int visit_order(int n, int w, int i)
 }
 
 // Work item of a workgroup.  The hardware deals workgroup ids round-robin over the 8 XCDs (each with its own
-// L2).  The launch's column blocks, taken row of tiles after row of tiles, are cut into chunks of consecutive blocks and
-// the chunks are dealt to the XCDs in turn: the blocks resident on one XCD at a time are then neighbours that
+// L2).  The launch's column blocks, taken row of tiles after row of tiles, are dealt to the XCDs by whole rows in
+// turn, the rows left over evenly (see Deal and deal_blocks): the blocks resident on one XCD at a time are then neighbours that
 // share most of their windows, while all XCDs together still work on one region of one head.
 // QUERY_COLS: the columns are queries and the box holds the key tiles of their tile; otherwise the columns are keys and
 // the box holds the query tiles that keep their tile.
 struct BwdItem {
-    bool valid;                // false for the padding ids of the launch
     uint32_t block;            // column block inside the head
     size_t bh;
     StaBox box;
@@ -85,11 +83,7 @@ template <bool QUERY_COLS>
 __device__ __forceinline__ BwdItem bwd_item_of(uint32_t id, const sta::FwdParams &p, const BwdPlan &plan)
 {
     BwdItem it;
-    const uint32_t xcd = id & 7, slot = id >> 3;
-    const uint32_t chunk = fast_div(slot, plan.chunk);
-    const uint32_t linear = (chunk * 8 + xcd) * plan.chunk.d + (slot - chunk * plan.chunk.d);
-    it.valid = linear < plan.total;
-    if (!it.valid) return it;
+    const uint32_t linear = sta::dealt_item(id, plan.deal);
     const uint32_t line = fast_div(linear, plan.per_row), pos = linear - line * plan.per_row.d;
     uint32_t row, rank;
     if (plan.row_major) {
@@ -278,7 +272,6 @@ void sta_bwd_dq_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restric
     __shared__ __attribute__((aligned(1024))) char smem[SMEM];
 
     const BwdItem item = bwd_item_of<true>(blockIdx.x, p, plan);
-    if (!item.valid) return;
     const size_t bh = item.bh;
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -457,7 +450,6 @@ void sta_bwd_dkv_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restri
     __shared__ __attribute__((aligned(1024))) char smem[SMEM];
 
     const BwdItem item = bwd_item_of<false>(blockIdx.x, p, plan);
-    if (!item.valid) return;
     const size_t bh = item.bh;
     const int tid = threadIdx.x;
     const int wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -708,7 +700,6 @@ void sta_bwd_dkv_pair_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__r
     __shared__ __attribute__((aligned(1024))) char smem[SMEM];
 
     const BwdItem item = bwd_item_of<false>(blockIdx.x, p, plan);
-    if (!item.valid) return;
     const size_t bh = item.bh;
     const int tid = threadIdx.x;
     const int wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -904,24 +895,56 @@ uint32_t walk_of_rank(const BwdArgs &a, uint32_t rank)
 }
 uint32_t longest_walk(const BwdArgs &a) { return walk_of_rank(a, 0); }
 
-// One chunk = the column blocks of one row of tiles along w.  Measured at the 30x48x80 grid (chunk sizes 1, 3,
+// Sub-blocks that the XCD with the most of them walks, of a launch that is dealt head after head; per_rank blocks per head.
+uint64_t fullest_xcd(const BwdArgs &a, const sta::Deal &deal, uint64_t per_rank)
+{
+    uint64_t before[sta::kMaxHeadsPerLaunch + 1] = {}, load[8] = {}, most = 0;
+    for (uint32_t r = 0; r < a.p.heads; ++r) before[r + 1] = before[r] + per_rank * walk_of_rank(a, r);
+    auto up_to = [&](uint64_t block) {
+        const uint64_t r = block / per_rank;
+        return before[r] + (r < a.p.heads ? (block - r * per_rank) * walk_of_rank(a, (uint32_t)r) : 0);
+    };
+    uint64_t at = 0;
+    for (uint32_t c = 0; c < 8 * (deal.last_slot / deal.chunk.d + 1); ++c) {
+        const uint32_t xcd = c & 7;
+        const uint64_t to = at + (at < 8 * (uint64_t)deal.last_slot ? deal.chunk.d : deal.last_len + (xcd < deal.last_more));
+        load[xcd] += up_to(to) - up_to(at);
+        at = to;
+    }
+    for (uint64_t l : load) most = l > most ? l : most;
+    return most;
+}
+
+// How the blocks are dealt.  One chunk = the column blocks of one row of tiles along w.  Measured at the 30x48x80 grid (chunk sizes 1, 3,
 // 6, 30, 60, 120 in one session): dK/dV kernel 32.7, 31.5, 31.6, 31.0, 31.1, 34.0 ms; dQ kernel 18.9, 18.8, 18.7,
-// 18.5, 18.5, 19.3 ms.  Launches of fewer than eight such rows are cut evenly, so that every XCD gets its share.
-BwdPlan make_plan(const BwdArgs &a, uint32_t cols, bool row_major, bool longest_first, uint32_t *ids)
+// 18.5, 18.5, 19.3 ms.  Where the walks of the heads differ, a round of eight rows can hold rows of two heads, and an XCD gets the long
+// ones: launches of fewer than twenty rounds are then cut into as many rounds of equal chunks, but only where that makes the walks of the
+// fullest XCD shorter by more than a twentieth (three heads of 12x24x40 in 384-token tiles, 1x3x3 and 2x1x1, by 17 %; not ten of
+// 6x24x24, eight of them with walks of 108 sub-blocks and two of 36, whose 24 long rows are three for every XCD: chosen by the number
+// of blocks alone, equal chunks gave two XCDs 68 long ones for 64 places, 115 -> 150 us dK/dV, training step 281 -> 325).
+sta::Deal deal_blocks(const BwdArgs &a, uint32_t cols)
+{
+    const sta::FwdParams &p = a.p;
+    const uint64_t per_rank = (uint64_t)(p.N / cols) * a.B;
+    const uint32_t total = (uint32_t)(per_rank * p.heads), row = p.n_w * (p.P / cols);
+    const sta::Deal rows = sta::deal_in_chunks(total, row);
+    const uint32_t rounds = (uint32_t)((total + 8 * (uint64_t)row - 1) / (8 * (uint64_t)row));
+    if (rounds > 20 || walk_of_rank(a, 0) == walk_of_rank(a, p.heads - 1)) return rows;
+    const sta::Deal equal = sta::deal_in_chunks(total, (total + 8 * rounds - 1) / (8 * rounds));
+    return 20 * fullest_xcd(a, rows, per_rank) > 21 * fullest_xcd(a, equal, per_rank) ? equal : rows;
+}
+
+BwdPlan make_plan(const BwdArgs &a, uint32_t cols, bool row_major, bool longest_first)
 {
     const sta::FwdParams &p = a.p;
     BwdPlan plan;
     const uint32_t per_tile = p.P / cols;
-    plan.total = (p.N / cols) * (uint32_t)a.B * p.heads;
-    uint32_t chunk = p.n_w * per_tile;
-    plan.per_row = sta::fast_div_of(chunk);
+    plan.deal = deal_blocks(a, cols);
+    plan.per_row = sta::fast_div_of(p.n_w * per_tile);
     plan.rows = sta::fast_div_of(p.n_t * p.n_h);
     plan.slices = sta::fast_div_of((uint32_t)a.B * p.heads);
     plan.row_major = row_major;
     plan.longest_first = longest_first;
-    const uint64_t rounds = (plan.total + 8 * (uint64_t)chunk - 1) / (8 * (uint64_t)chunk);       // of chunks over the XCDs
-    if (20 * 8 * rounds * chunk > 21 * (uint64_t)plan.total) chunk = (uint32_t)((plan.total + 8 * rounds - 1) / (8 * rounds));
-    plan.chunk = sta::fast_div_of(chunk);
     plan.per_tile = sta::fast_div_of(per_tile);
     plan.n_h = sta::fast_div_of(p.n_h);
     plan.batch = sta::fast_div_of((uint32_t)a.B);
@@ -932,18 +955,35 @@ BwdPlan make_plan(const BwdArgs &a, uint32_t cols, bool row_major, bool longest_
         plan.head[r].h = h;
         for (int i = 0; i < 3; ++i) plan.head[r].w[i] = a.win.w[h][i];
     }
-    const uint32_t chunks = (plan.total + chunk - 1) / chunk;
-    *ids = 8 * chunk * ((chunks + 7) / 8);
     return plan;
+}
+
+// The shape of a launch as text, with the sub-blocks that the XCD with the most of them walks and those of all.
+hipError_t note_launch(const BwdArgs &a, const BwdPlan &plan, const char *shape)
+{
+    uint64_t load[8] = {}, all = 0, most = 0;
+    for (uint32_t id = 0; id < plan.deal.total; ++id) {
+        const uint32_t line = sta::dealt_item(id, plan.deal) / plan.per_row.d;
+        const uint32_t rank = plan.row_major ? line % plan.slices.d : line / plan.rows.d;
+        load[id & 7] += walk_of_rank(a, rank / plan.batch.d);
+    }
+    for (uint64_t l : load) {
+        all += l;
+        most = l > most ? l : most;
+    }
+    return a.note->add("%s items %u, fullest XCD %llu of %llu sub-blocks", shape, plan.deal.total, (unsigned long long)most, (unsigned long long)all);
 }
 
 template <int D, int QW, int G, bool DMA = true>
 hipError_t launch_dq(const BwdArgs &a)
 {
-    uint32_t ids;
-    const BwdPlan plan = make_plan(a, QW * 32, false, false, &ids);
-    if (a.note) return a.note->add("dq<%d,%d,%d,%d> items %u chunk %u", D, QW, G, (int)DMA, plan.total, plan.chunk.d);
-    sta_bwd_dq_kernel<D, QW, G, DMA><<<dim3(ids), dim3(QW * G * 64), 0, a.stream>>>(a.q, a.k, a.v, a.o, a.d_o, a.lse, a.neg_delta, a.neg_lse,
+    const BwdPlan plan = make_plan(a, QW * 32, false, false);
+    if (a.note) {
+        char shape[64];
+        snprintf(shape, sizeof shape, "dq<%d,%d,%d,%d>", D, QW, G, (int)DMA);
+        return note_launch(a, plan, shape);
+    }
+    sta_bwd_dq_kernel<D, QW, G, DMA><<<dim3(plan.deal.total), dim3(QW * G * 64), 0, a.stream>>>(a.q, a.k, a.v, a.o, a.d_o, a.lse, a.neg_delta, a.neg_lse,
                                                                               a.d_q, a.p, plan);
     return hipGetLastError();
 }
@@ -981,12 +1021,15 @@ bool rows_of_all_heads(const BwdArgs &a, uint32_t cols, uint64_t resident)
 template <int D, int NW, int G, int UPS = 1, bool DMA = true>
 hipError_t launch_dkv(const BwdArgs &a)
 {
-    uint32_t ids;
     const uint64_t resident = (uint64_t)sta::compute_units() * (D == 64 ? 12 : 8) / (NW * G);     // workgroups
     const bool row_major = rows_of_all_heads(a, NW * 32, resident), longest_first = a.p.P % 96 == 0 && a.p.P % 128 != 0;
-    const BwdPlan plan = make_plan(a, NW * 32, row_major, row_major && longest_first, &ids);
-    if (a.note) return a.note->add("dkv<%d,%d,%d,%d,%d> items %u chunk %u", D, NW, G, UPS, (int)DMA, plan.total, plan.chunk.d);
-    sta_bwd_dkv_kernel<D, NW, G, UPS, DMA><<<dim3(ids), dim3(NW * G * 64), 0, a.stream>>>(a.q, a.k, a.v, a.d_o, a.neg_lse, a.neg_delta,
+    const BwdPlan plan = make_plan(a, NW * 32, row_major, row_major && longest_first);
+    if (a.note) {
+        char shape[64];
+        snprintf(shape, sizeof shape, "dkv<%d,%d,%d,%d,%d>", D, NW, G, UPS, (int)DMA);
+        return note_launch(a, plan, shape);
+    }
+    sta_bwd_dkv_kernel<D, NW, G, UPS, DMA><<<dim3(plan.deal.total), dim3(NW * G * 64), 0, a.stream>>>(a.q, a.k, a.v, a.d_o, a.neg_lse, a.neg_delta,
                                                                                     a.d_k, a.d_v, a.p, plan);
     return hipGetLastError();
 }
@@ -994,12 +1037,15 @@ hipError_t launch_dkv(const BwdArgs &a)
 template <int NPAIR, int G, bool DMA = true>
 hipError_t launch_dkv_pairs(const BwdArgs &a)
 {
-    uint32_t ids;
     const uint64_t resident = (uint64_t)sta::compute_units() * 12 / (2 * NPAIR * G);     // workgroups
     const bool row_major = rows_of_all_heads(a, NPAIR * 32, resident), longest_first = a.p.P % 96 == 0;
-    const BwdPlan plan = make_plan(a, NPAIR * 32, row_major, row_major && longest_first, &ids);
-    if (a.note) return a.note->add("dkv_pair<%d,%d,%d> items %u chunk %u", NPAIR, G, (int)DMA, plan.total, plan.chunk.d);
-    sta_bwd_dkv_pair_kernel<NPAIR, G, DMA><<<dim3(ids), dim3(NPAIR * G * 128), 0, a.stream>>>(a.q, a.k, a.v, a.d_o, a.neg_lse, a.neg_delta,
+    const BwdPlan plan = make_plan(a, NPAIR * 32, row_major, row_major && longest_first);
+    if (a.note) {
+        char shape[64];
+        snprintf(shape, sizeof shape, "dkv_pair<%d,%d,%d>", NPAIR, G, (int)DMA);
+        return note_launch(a, plan, shape);
+    }
+    sta_bwd_dkv_pair_kernel<NPAIR, G, DMA><<<dim3(plan.deal.total), dim3(NPAIR * G * 128), 0, a.stream>>>(a.q, a.k, a.v, a.d_o, a.neg_lse, a.neg_delta,
                                                                                         a.d_k, a.d_v, a.p, plan);
     return hipGetLastError();
 }

@@ -106,7 +106,7 @@ __host__ __device__ __forceinline__ uint32_t fast_div(uint32_t n, const FastDiv 
     return (((n - q) >> f.pre) + q) >> f.post;
 }
 
-// How the items of a forward launch are dealt to the workgroup ids, which the hardware gives to the 8 XCDs in turn: rounds of
+// How the items of a launch are dealt to the workgroup ids, which the hardware gives to the 8 XCDs in turn: rounds of
 // eight chunks of consecutive items, one per XCD, and a last round that divides what is left evenly (the first last_more XCDs
 // get one item more).  Every id below total names an item, and no XCD gets more than one item more than another.
 struct Deal {
@@ -115,19 +115,23 @@ struct Deal {
     uint32_t last_slot;        // slots (ids of one XCD) in full rounds
     uint32_t last_len, last_more;
 };
-// per_head items of each of n_bh (batch, head) slices: as many rounds of chunks as eighths of a head would take.
-inline Deal deal_of(uint32_t per_head, uint32_t n_bh)
+inline Deal deal_in_chunks(uint32_t total, uint32_t chunk)
 {
     Deal d;
-    d.total = per_head * n_bh;
-    const uint32_t eighth = (per_head + 7) / 8, rounds = (d.total + 8 * eighth - 1) / (8 * eighth);
-    const uint32_t chunk = (d.total + 8 * rounds - 1) / (8 * rounds);
+    d.total = total;
     d.chunk = fast_div_of(chunk);
-    d.last_slot = d.total / (8 * chunk) * chunk;
-    const uint32_t left = d.total - 8 * d.last_slot;
+    d.last_slot = (uint32_t)(total / (8 * (uint64_t)chunk)) * chunk;
+    const uint32_t left = total - 8 * d.last_slot;
     d.last_len = left / 8;
     d.last_more = left % 8;
     return d;
+}
+// per_head items of each of n_bh (batch, head) slices: as many rounds of chunks as eighths of a head would take.
+inline Deal deal_of(uint32_t per_head, uint32_t n_bh)
+{
+    const uint32_t total = per_head * n_bh;
+    const uint32_t eighth = (per_head + 7) / 8, rounds = (total + 8 * eighth - 1) / (8 * eighth);
+    return deal_in_chunks(total, (total + 8 * rounds - 1) / (8 * rounds));
 }
 __host__ __device__ __forceinline__ uint32_t dealt_item(uint32_t id, const Deal &d)
 {

@@ -47,3 +47,16 @@ def test_a_last_round_of_at_most_half_is_cut_into_parts(grid, window):
         assert (parts, of, workgroups) == (want, tail, items - tail + tail * want), line
         cut += 1
     assert cut > 10
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("grid,heads,windows", [
+    ((6, 24, 24), 10, [(1, 2, 3), (1, 3, 2), (1, 1, 2), (1, 2, 3), (1, 3, 3)]),      # 24 rows of long walks, six of short ones
+    ((6, 8, 48), 9, [(1, 1, 5)]),                                                    # nine rows
+    ((6, 24, 24), 14, [(1, 3, 3)]), ((12, 24, 40), 3, [(1, 3, 3), (2, 1, 1)]),
+])
+def test_the_xcds_of_a_gradient_launch_walk_equally_far(grid, heads, windows, D):
+    """Counted in sub-blocks of 32 tokens, over the walks that the windows give their heads."""
+    for line in launches(1, heads, D, grid, (6, 8, 8), windows, gradients=True):
+        most, total = map(int, re.search(r"fullest XCD (\d+) of (\d+)", line).groups())
+        assert most <= 1.06 * total / 8, line         # chunks may leave a twentieth
