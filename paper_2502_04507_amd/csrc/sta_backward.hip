@@ -894,6 +894,23 @@ uint32_t walk_of_rank(const BwdArgs &a, uint32_t rank)
     return units;
 }
 uint32_t longest_walk(const BwdArgs &a) { return walk_of_rank(a, 0); }
+// Sub-blocks of the longest walk over the queries of a key tile: a window of 2 * half + 1 tiles keeps the tiles 2 * half from a border
+// for 3 * half + 1 query tiles, or for all where both borders see them.
+uint32_t longest_key_walk(const BwdArgs &a)
+{
+    const sta::FwdParams &p = a.p;
+    const uint32_t n[3] = {p.n_t, p.n_h, p.n_w};
+    uint32_t most = 0;
+    for (uint32_t h = 0; h < p.heads; ++h) {
+        uint32_t units = p.P / kSub;
+        for (int i = 0; i < 3; ++i) {
+            const uint32_t half = a.win.w[h][i] / 2u;
+            units *= n[i] - 1 <= 4 * half ? n[i] : 3 * half + 1;
+        }
+        most = units > most ? units : most;
+    }
+    return most;
+}
 
 // Sub-blocks that the XCD with the most of them walks, of a launch that is dealt head after head; per_rank blocks per head.
 uint64_t fullest_xcd(const BwdArgs &a, const sta::Deal &deal, uint64_t per_rank)
@@ -1111,6 +1128,12 @@ hipError_t dispatch_dkv(const BwdArgs &a)
         if constexpr (D == 128) return P % 96 == 0 ? launch_dkv_pairs<3, 2>(a) : launch_dkv_pairs<1, 1>(a);
         else return P % 96 == 0 ? launch_dkv<64, 3, 1>(a) : waves <= 4 * cus ? launch_dkv<64, 1, 2>(a) : launch_dkv<64, 1, 1>(a);
     }
+    uint64_t by_walk = waves;                           // waves, those of a head with half the longest walk counted half
+    if constexpr (D == 128) {
+        uint64_t all_units = 0;
+        for (uint32_t r = 0; r < a.p.heads; ++r) all_units += walk_of_rank(a, r);
+        by_walk = (uint64_t)a.B * (a.p.N / 32) * all_units / units;
+    }
     // One round of six pairs, at least four fifths full: half a wave's products per wave fill a CU where whole ones leave it half
     // empty in the same time (30x24x32, two heads of 128 (1440, 720) 1495, 1589; 12x24x24, six (1296, 108) 259, 262; training steps,
     // six pairs, two groups: (1344, 48) 211, 217, (1440, 72) 307, 313).  Not where the walks of the heads differ: the long ones are one
@@ -1118,15 +1141,20 @@ hipError_t dispatch_dkv(const BwdArgs &a)
     // (14 heads of 6x24x24 (1512, 108): 42 rows of six workgroups, 36 on two of the XCDs, 517, 408).
     // 64-token tiles and the like, short walks: two pairs, of which a CU holds three workgroups, where the two workgroups it holds of the
     // groups below begin a second round (training steps, groups, pairs: (1008, 18) 111, 112; (1200, 18) 131, 128; (1404, 36) 142, 132;
-    // (1512, 30) 192, 184; (1584, 12) 130, 126; (1632, 6) 112, 105; but (1440, 144) 431, 453).
+    // (1512, 30) 192, 184; (1584, 12) 130, 126; (1632, 6) 112, 105; but (1440, 144) 431, 453).  Waves count by the walks of their
+    // heads, as the long ones fill the chip (140 slices of 16x24, 4 and 12 sub-blocks, 1680 waves that count 1288: 130, 122; 70 of
+    // 32x24, 6 to 24: 151, 144; by their number the groups had them).  Not where the longest walk, which two groups halve, is more than
+    // 2.2 times a place's even share of all (32x48, 25 heads, 6 to 24, up to 32 of a key tile 127, 131; 40x40, 20 heads 120, 126).
     if constexpr (D == 128) {
         const uint64_t blocks = waves / 6;
         const uint64_t rows = (uint64_t)a.B * a.p.heads * a.p.n_t * a.p.n_h, fullest_xcd = (rows + 7) / 8 * a.p.n_w * (P / 192);
         if (P % 384 == 0 && 8 * fullest_xcd <= cus && 5 * blocks >= 4 * cus && units == walk_of_rank(a, a.p.heads - 1)) return launch_dkv_pairs<6, 1>(a);
-        if (P % 128 != 0 && units < 48 && waves > 4 * cus && 2 * waves <= 13 * cus) return launch_dkv_pairs<2, 1>(a);
+        const uint64_t longest = longest_key_walk(a), all = by_walk * units;                // sub-blocks; of all items, doubled
+        const bool small = units < 32 ? by_walk <= 8 * cus : units < 48 && 2 * waves <= 13 * cus;
+        if (P % 128 != 0 && waves > 4 * cus && small && (longest < 32 || 30 * cus * longest <= 11 * all)) return launch_dkv_pairs<2, 1>(a);
     }
     if (P % 128 == 0) return waves <= (P == 128 ? 24 : 6) * cus ? launch_dkv<D, 2, 2>(a) : launch_dkv<D, 4, 1, D == 64 ? 2 : 1>(a);
-    return waves <= 8 * cus || (units >= 32 && (D == 64 || waves <= 32 * cus)) ? launch_dkv<D, 2, 2>(a) : launch_dkv<D, 2, 1>(a);
+    return by_walk <= 8 * cus || (units >= 32 && (D == 64 || waves <= 32 * cus)) ? launch_dkv<D, 2, 2>(a) : launch_dkv<D, 2, 1>(a);
 }
 
 }  // namespace

@@ -60,3 +60,15 @@ def test_the_xcds_of_a_gradient_launch_walk_equally_far(grid, heads, windows, D)
     for line in launches(1, heads, D, grid, (6, 8, 8), windows, gradients=True):
         most, total = map(int, re.search(r"fullest XCD (\d+) of (\d+)", line).groups())
         assert most <= 1.06 * total / 8, line         # chunks may leave a twentieth
+
+
+@pytest.mark.parametrize("B,H,grid,windows,want", [
+    (7, 20, (1, 16, 24), [(1, 2, 1), (1, 2, 3), (1, 2, 3)], "dkv_pair<2,1,1>"),       # 1680 waves, by their walks 1288
+    (4, 20, (1, 16, 48), [(1, 2, 1), (1, 1, 2)], "dkv_pair<2,1,1>"),                  # 1920, 1600
+    (7, 8, (1, 48, 32), [(1, 3, 1), (1, 1, 1), (1, 1, 1), (1, 5, 3)], "dkv<128,2,2,1,1>"),     # 2688, 896; one long walk
+    (1, 25, (1, 32, 48), [(1, 3, 1), (1, 4, 2), (1, 3, 2)], "dkv<128,2,2,1,1>"),      # 1200, 780; walks of up to 32 of 12 on average
+    (1, 25, (1, 32, 48), [(1, 3, 1)], "dkv_pair<2,1,1>"),                             # 1200, equal
+    (4, 25, (1, 32, 48), [(1, 3, 1)], "dkv<128,2,1,1,1>"),                            # 4800
+])
+def test_short_walks_on_64_token_tiles_count_by_their_length(B, H, grid, windows, want):
+    assert launches(B, H, 128, grid, (1, 8, 8), windows, gradients=True)[1].startswith(want + " ")
