@@ -4,11 +4,12 @@ Tensors are torch tensors used purely as device-memory handles (data_ptr);
 the stream is torch's current HIP stream unless one is given.
 
 The permutations, sta_forward, sta_forward_lse and sta_backward go through the extension sta_fastcall where their arguments are
-ordinary ones, everything else (and every error message) through ctypes.
+ordinary ones, everything else (and every error message) through ctypes; without the extension, with a warning, everything.
 """
 import ctypes
 import importlib
 import os
+import warnings
 
 import torch
 
@@ -40,7 +41,7 @@ def lib_path() -> str:
 
 def load_library():
     """Load libsta.so; raises if it has not been built (no fallback exists)."""
-    global _LIB, _FAST
+    global _LIB
     if _LIB is not None:
         return _LIB
     path = lib_path()
@@ -95,24 +96,36 @@ def load_library():
     lib.sta_strerror.restype = ctypes.c_char_p
     lib.sta_version.argtypes = []
     lib.sta_version.restype = ci
-    try:
-        fast = importlib.import_module(__package__ + ".sta_fastcall")
-    except ImportError as e:
-        raise ImportError("sta_fastcall.so is not built or does not load: run `python -m paper_2502_04507_amd.build_lib` "
-                          "(or __graft_entry__.build()) first") from e
-    if _raw_stream is not None and _current_device is not None:     # unbound, it leaves every call to ctypes
-        fast.bind(*[ctypes.cast(getattr(lib, name), vp).value for name in _FAST_ENTRIES], _current_device, _raw_stream)
-    _LIB, _FAST = lib, fast
+    _LIB = lib
     return lib
 
 
 _FAST_ENTRIES = ("sta_tile_permute", "sta_untile", "sta_forward", "sta_forward_lse", "sta_backward")
 
 
+class _GeneralPath:
+    """Stands for the extension where it cannot be loaded: leaves every call to the general path."""
+    tile_permute = untile = forward = forward_lse = backward = staticmethod(lambda *args: None)
+
+
+def _load_fast():
+    lib = load_library()
+    try:
+        fast = importlib.import_module(__package__ + ".sta_fastcall")
+    except ImportError as e:
+        warnings.warn("sta_fastcall.so is not built or does not load here (%s): the same kernels are launched through ctypes, at 2 "
+                      "to 7 us more host time a call; `python -m paper_2502_04507_amd.build_lib` builds it" % e, RuntimeWarning, 2)
+        return _GeneralPath
+    if _raw_stream is not None and _current_device is not None:     # unbound, it leaves every call to the general path
+        fast.bind(*[ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in _FAST_ENTRIES], _current_device, _raw_stream)
+    return fast
+
+
 def _fast():
     """The extension: its functions return a status, or None for arguments that they leave to the general path."""
+    global _FAST
     if _FAST is None:
-        load_library()
+        _FAST = _load_fast()
     return _FAST
 
 

@@ -1,5 +1,11 @@
 """The extension that calls the hot entry points: what it takes it computes as the general path does, and it leaves everything
 else to that path, with its results and its errors."""
+import os
+import shutil
+import subprocess
+import sys
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -29,6 +35,63 @@ def test_leaves_what_it_does_not_know_to_the_general_path():
     for call in (lambda: sta.sta_tile_permute(a, b, GRID, TILE), lambda: sta.sta_forward(a, b, c, d, GRID, TILE, WINDOWS)):
         with pytest.raises(ValueError, match="must live in device memory"):
             call()
+
+
+def test_the_library_alone_suffices(tmp_path):
+    """A copy of the package without the extension: host-side helpers work silently, a hot entry point warns once and behaves."""
+    home = os.path.dirname(sta.__file__)
+    copy = tmp_path / os.path.basename(home)
+    copy.mkdir()
+    for name in os.listdir(home):
+        if name.endswith(".py") or name == "libsta.so":
+            shutil.copy(os.path.join(home, name), copy / name)
+    program = '''
+import warnings
+with warnings.catch_warnings():
+    warnings.simplefilter("error")
+    import paper_2502_04507_amd as sta
+    assert sta.sta_version() >= 100 and sta.sta_strerror(0)
+    assert sta.sta_kept_flops(1, 2, 64, (1, 16, 16), (1, 8, 8), [(1, 1, 1)] * 2) > 0
+import torch
+a, b = torch.zeros(1, 2, 256, 64, dtype=torch.bfloat16), torch.zeros(1, 2, 256, 64, dtype=torch.bfloat16)
+with warnings.catch_warnings(record=True) as seen:
+    warnings.simplefilter("always")
+    for _ in range(2):
+        try:
+            sta.sta_tile_permute(a, b, (1, 16, 16), (1, 8, 8))
+        except ValueError as e:
+            assert "must live in device memory" in str(e)
+        else:
+            raise AssertionError
+assert [w.category for w in seen] == [RuntimeWarning], seen
+print("ok")
+'''
+    r = subprocess.run([sys.executable, "-c", program], cwd=tmp_path, capture_output=True, text=True,
+                       env=dict(os.environ, PYTHONPATH=str(tmp_path)))
+    assert r.stdout.strip().endswith("ok"), r.stdout + r.stderr
+
+
+def test_a_build_without_a_host_compiler_says_so(monkeypatch, tmp_path):
+    from paper_2502_04507_amd import build_lib
+    stale = tmp_path / "sta_fastcall.so"
+    stale.write_bytes(b"old")
+    monkeypatch.setattr(build_lib, "FASTCALL_OUT", str(stale))
+    monkeypatch.setenv("CXX", str(tmp_path / "no-such-compiler"))
+    assert "no-such-compiler" in build_lib._build_fastcall()
+    assert not stale.exists()
+
+
+def test_first_use_by_several_threads(monkeypatch):
+    monkeypatch.setattr(binding, "_FAST", None)
+    monkeypatch.setattr(binding, "_LIB", None)
+    a = tensors(2, "cpu")
+    got = []
+    threads = [threading.Thread(target=lambda: got.append(binding._fast().tile_permute(*a, GRID, TILE))) for _ in range(16)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert got == [None] * 16
 
 
 def general(monkeypatch, call):
