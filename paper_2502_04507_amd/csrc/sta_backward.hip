@@ -1135,10 +1135,11 @@ hipError_t dispatch_dkv(const BwdArgs &a)
         by_walk = (uint64_t)a.B * (a.p.N / 32) * all_units / units;
     }
     // One round of six pairs, at least four fifths full: half a wave's products per wave fill a CU where whole ones leave it half
-    // empty in the same time (30x24x32, two heads of 128 (1440, 720) 1495, 1589; 12x24x24, six (1296, 108) 259, 262; training steps,
-    // six pairs, two groups: (1344, 48) 211, 217, (1440, 72) 307, 313).  Not where the walks of the heads differ: the long ones are one
-    // round by themselves ((1296, 72) 253, 239), nor where the rows of tiles are dealt so that an XCD gets more workgroups than it has CUs
-    // (14 heads of 6x24x24 (1512, 108): 42 rows of six workgroups, 36 on two of the XCDs, 517, 408).
+    // empty in the same time (training steps, two groups, six pairs: 30x24x32, two heads of 128, whole grid (1440, 720) 1589, 1495;
+    // 6x16x16, 31 heads (1488, 48) 219, 212; 6x24x24, 14 heads (1512, 108) 402, 393; 12x24x24, seven (1512, 216) 728, 713).  Not where the
+    // walks of the heads differ: the long ones are one round by themselves ((1296, 72) 239, 253), nor where those of the key tiles do by
+    // more than 4 : 3, for the same reason (6x32x32, seven heads at 1x3x3, walks up to 1.8 times the 108 of a query tile 427, 477; 30x24x32,
+    // two at 3x3x3, up to 2.2 times 324 1179, 1464; at 4 : 3, 1x3x3, 427, 422).
     // 64-token tiles and the like, short walks: two pairs, of which a CU holds three workgroups, where the two workgroups it holds of the
     // groups below begin a second round (training steps, groups, pairs: (1008, 18) 111, 112; (1200, 18) 131, 128; (1404, 36) 142, 132;
     // (1512, 30) 192, 184; (1584, 12) 130, 126; (1632, 6) 112, 105; but (1440, 144) 431, 453).  Waves count by the walks of their
@@ -1146,10 +1147,13 @@ hipError_t dispatch_dkv(const BwdArgs &a)
     // 32x24, 6 to 24: 151, 144; by their number the groups had them).  Not where the longest walk, which two groups halve, is more than
     // 2.2 times a place's even share of all (32x48, 25 heads, 6 to 24, up to 32 of a key tile 127, 131; 40x40, 20 heads 120, 126).
     if constexpr (D == 128) {
-        const uint64_t blocks = waves / 6;
-        const uint64_t rows = (uint64_t)a.B * a.p.heads * a.p.n_t * a.p.n_h, fullest_xcd = (rows + 7) / 8 * a.p.n_w * (P / 192);
-        if (P % 384 == 0 && 8 * fullest_xcd <= cus && 5 * blocks >= 4 * cus && units == walk_of_rank(a, a.p.heads - 1)) return launch_dkv_pairs<6, 1>(a);
         const uint64_t longest = longest_key_walk(a), all = by_walk * units;                // sub-blocks; of all items, doubled
+        const bool equal = units == walk_of_rank(a, a.p.heads - 1);
+        if (P % 384 == 0 && waves <= 6 * cus && 5 * waves >= 24 * cus && equal && 3 * longest <= 4 * units) return launch_dkv_pairs<6, 1>(a);
+        // groups also for one round or so of four waves whose longest walk is 1.8 times a place's share of all or more: they halve it
+        // (four waves, two groups: 12x32x40, four heads at 1x3x3 (1920, 108) 599, 523; 6x48x40, seven (2520, 108) 684, 651; 4x40x40 in
+        // 256-token tiles, nine of 40 and 120 sub-blocks (1800) 472, 427; but 18x24x48, three, 1.4 times (1944, 324) 1298, 1332)
+        if (P % 128 == 0 && waves <= 10 * cus && 40 * cus * longest > 9 * all) return launch_dkv<128, 2, 2>(a);
         const bool small = units < 32 ? by_walk <= 8 * cus : units < 48 && 2 * waves <= 13 * cus;
         if (P % 128 != 0 && waves > 4 * cus && small && (longest < 32 || 30 * cus * longest <= 11 * all)) return launch_dkv_pairs<2, 1>(a);
     }

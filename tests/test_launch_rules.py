@@ -72,3 +72,13 @@ def test_the_xcds_of_a_gradient_launch_walk_equally_far(grid, heads, windows, D)
 ])
 def test_short_walks_on_64_token_tiles_count_by_their_length(B, H, grid, windows, want):
     assert launches(B, H, 128, grid, (1, 8, 8), windows, gradients=True)[1].startswith(want + " ")
+
+
+@pytest.mark.parametrize("H,grid,window,want", [
+    (31, (6, 16, 16), (1, 2, 2), "dkv_pair<6,1,1>"), (14, (6, 24, 24), (1, 3, 3), "dkv_pair<6,1,1>"),      # one round, equal walks
+    (2, (30, 24, 32), (3, 3, 3), "dkv<128,2,2,1,1>"), (7, (6, 32, 32), (1, 3, 3), "dkv<128,2,2,1,1>"),     # key tiles of 2.2 and 1.8 times the walk
+    (16, (6, 24, 24), (1, 3, 3), "dkv<128,4,1,1,1>"), (3, (18, 24, 48), (3, 3, 3), "dkv<128,4,1,1,1>"),    # beyond a round of pairs
+    (4, (12, 32, 40), (1, 3, 3), "dkv<128,2,2,1,1>"), (7, (6, 48, 40), (1, 3, 3), "dkv<128,2,2,1,1>"),     # one walk of 2.4 and 1.8 shares
+])
+def test_launches_of_a_round_or_so_go_by_the_longest_walk_of_a_key_tile(H, grid, window, want):
+    assert launches(1, H, 128, grid, (6, 8, 8), [window], gradients=True)[1].startswith(want + " ")
