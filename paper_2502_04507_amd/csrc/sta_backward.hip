@@ -936,7 +936,7 @@ uint64_t fullest_xcd(const BwdArgs &a, const sta::Deal &deal, uint64_t per_rank)
 // 6, 30, 60, 120 in one session): dK/dV kernel 32.7, 31.5, 31.6, 31.0, 31.1, 34.0 ms; dQ kernel 18.9, 18.8, 18.7,
 // 18.5, 18.5, 19.3 ms.  Where the walks of the heads differ, a round of eight rows can hold rows of two heads, and an XCD gets the long
 // ones: launches of fewer than twenty rounds are then cut into as many rounds of equal chunks, but only where that makes the walks of the
-// fullest XCD shorter by more than a twentieth (three heads of 12x24x40 in 384-token tiles, 1x3x3 and 2x1x1, by 17 %; not ten of
+// fullest XCD shorter by more than 1 % (22 heads of 12x8x40 in 384-token tiles, 2x1x4 and 2x1x2, by 1.8 %: step 662 -> 638 us; not ten of
 // 6x24x24, eight of them with walks of 108 sub-blocks and two of 36, whose 24 long rows are three for every XCD: chosen by the number
 // of blocks alone, equal chunks gave two XCDs 68 long ones for 64 places, 115 -> 150 us dK/dV, training step 281 -> 325).
 sta::Deal deal_blocks(const BwdArgs &a, uint32_t cols)
@@ -948,7 +948,7 @@ sta::Deal deal_blocks(const BwdArgs &a, uint32_t cols)
     const uint32_t rounds = (uint32_t)((total + 8 * (uint64_t)row - 1) / (8 * (uint64_t)row));
     if (rounds > 20 || walk_of_rank(a, 0) == walk_of_rank(a, p.heads - 1)) return rows;
     const sta::Deal equal = sta::deal_in_chunks(total, (total + 8 * rounds - 1) / (8 * rounds));
-    return 20 * fullest_xcd(a, rows, per_rank) > 21 * fullest_xcd(a, equal, per_rank) ? equal : rows;
+    return 100 * fullest_xcd(a, rows, per_rank) > 101 * fullest_xcd(a, equal, per_rank) ? equal : rows;
 }
 
 BwdPlan make_plan(const BwdArgs &a, uint32_t cols, bool row_major, bool longest_first)
