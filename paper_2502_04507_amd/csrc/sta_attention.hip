@@ -1725,7 +1725,7 @@ template <int D, int QW, int KG, int WPE, bool FOLLOW, int UPS = 1>
 hipError_t launch_group(const FwdArgs &a)
 {
     const sta::FwdPlan plan = make_plan(QW, a);
-    if (a.note) return a.note->add("group<%d,%d,%d,%d> items %u workgroups %u", D, QW, KG, UPS, plan.deal.total, plan.deal.total);
+    if (a.note) return a.note->add("group<%d,%d,%d,%d,%d> items %u", D, QW, KG, (int)FOLLOW, UPS, plan.deal.total);
     sta_fwd_group_kernel<D, QW, KG, WPE, FOLLOW, UPS><<<dim3(plan.deal.total), dim3(QW * KG * 64), 0, a.stream>>>(
         static_cast<const bf16_raw *>(a.q), static_cast<const bf16_raw *>(a.k), static_cast<const bf16_raw *>(a.v),
         static_cast<bf16_raw *>(a.o), a.p, plan);
@@ -1736,7 +1736,7 @@ template <int D, int NQ, int KG, bool FOLLOW>
 hipError_t launch_solo(const FwdArgs &a)
 {
     const sta::FwdPlan plan = make_plan(NQ / 2, a);
-    if (a.note) return a.note->add("solo<%d,%d,%d> items %u workgroups %u", D, NQ, KG, plan.deal.total, plan.deal.total);
+    if (a.note) return a.note->add("solo<%d,%d,%d,%d> items %u", D, NQ, KG, (int)FOLLOW, plan.deal.total);
     sta_fwd_solo_kernel<D, NQ, KG, D == 64 && NQ == 2 ? 4 : 2, FOLLOW><<<dim3(plan.deal.total), dim3(KG * 64), 0, a.stream>>>(
         static_cast<const bf16_raw *>(a.q), static_cast<const bf16_raw *>(a.k), static_cast<const bf16_raw *>(a.v),
         static_cast<bf16_raw *>(a.o), a.p, plan);

@@ -6,6 +6,7 @@ import torch
 
 import synth_inputs as syn
 from oracle import sta_oracle as orc
+from tests.launch_shapes import launches
 from tests.test_gpu_backward import assert_grad_parity, gpu_backward, oracle_backward
 
 pytestmark = pytest.mark.gpu
@@ -45,13 +46,16 @@ def test_gradient_kernel_shapes_match_the_oracle(name, grid, tile, B, H, windows
                 assert_grad_parity(got[b, h].float().numpy(), ref, "%s D%d %s b%d h%d" % (name, D, label, b, h))
 
 
-# Launches that fill the chip with six pairs (384-token tiles, at least 205 column blocks of 192 keys on 256 CUs), whole heads.
+# Launches of 384-token tiles with at least 205 column blocks of 192 keys, whole heads: beyond what six pairs take in one round on
+# 256 CUs (four waves, two groups of two), and in one round of them.
 SIX_PAIRS = [
     # equal windows and two rounds: the rows of all heads in turn
     ("six-rows", (12, 32, 32), 8, [(1, 3, 1)]),
-    # head after head: unequal windows, and equal ones in one round
+    # head after head: unequal windows, and equal ones in one round whose walks over the queries differ
     ("six-mixed", (6, 8, 216), 4, [(1, 1, 1), (1, 1, 2)]),
     ("six-one-round", (6, 8, 216), 4, [(1, 1, 4)]),
+    # six pairs: one round, equal walks
+    ("six-full", (6, 24, 24), 14, [(1, 1, 3), (1, 3, 1)]),
 ]
 
 
@@ -68,10 +72,31 @@ def test_six_pair_gradients_match_the_oracle(name, grid, H, windows):
 
 
 def test_six_pair_kept_set_read_from_dv():
-    """The transposed key-tile sets of the six-pair kernel, every head with its own window: with Q = 0 a kept key has the
+    """The transposed key-tile sets where every head has its own window (which no six pairs take): with Q = 0 a kept key has the
     probability 1 / (kept keys), so with dO one-hot in the query's tile dV_j[c] is 1 / (kept tiles of c) where c keeps j, else 0."""
     windows = [(1, 3, 2), (2, 1, 3), (1, 1, 1), (3, 3, 1), (2, 2, 4)]
     w = syn.custom("bwd-six-kept", 1, len(windows), 128, (12, 24, 32), (6, 8, 8), windows, "bf16", seed=1)      # 240 blocks
+    z = torch.zeros((1, w.H, w.N, 128), dtype=torch.bfloat16)
+    g = torch.zeros_like(z)
+    order = orc.tile_order(w.grid, w.tile)
+    tile_of_raster = np.empty(w.N, dtype=np.int64)
+    tile_of_raster[order] = np.repeat(np.arange(w.n_tiles), w.P)
+    g[0, :, torch.arange(w.N), torch.from_numpy(tile_of_raster)] = 1.0
+    (_, _, dv), _ = gpu_backward(w, z, z.clone(), torch.ones_like(z), g)
+    for h, window in enumerate(windows):
+        counts, lists = orc.key_tiles(w.grid, w.tile, orc.window_tiles_to_tokens(window, w.tile))
+        got = dv[0, h].float().numpy()[order].reshape(w.n_tiles, w.P, 128)
+        for j in range(w.n_tiles):
+            want = np.array([1.0 / counts[c] if j in lists[c][:counts[c]] else 0.0 for c in range(w.n_tiles)])
+            assert np.allclose(got[j][:, :w.n_tiles], want[None, :], rtol=2.0 ** -7, atol=0), (h, j)
+        assert (got[:, :, w.n_tiles:] == 0).all()
+
+
+def test_kept_set_of_six_pairs_read_from_dv():
+    """The same in a launch that six pairs take: one round, every head a window of three tiles along one of two axes."""
+    windows = [(1, 1, 3), (1, 3, 1)] * 6
+    assert launches(1, 12, 128, (6, 24, 24), (6, 8, 8), windows, gradients=True)[1].startswith("dkv_pair<6,1,1> items 216,")
+    w = syn.custom("bwd-six-kept-round", 1, 12, 128, (6, 24, 24), (6, 8, 8), windows, "bf16", seed=1)
     z = torch.zeros((1, w.H, w.N, 128), dtype=torch.bfloat16)
     g = torch.zeros_like(z)
     order = orc.tile_order(w.grid, w.tile)

@@ -1,5 +1,6 @@
 """GPU parity of the dK/dV kernel shapes that launches take once the smallest shapes (a wave per walk group) no longer serve them;
-counts of waves are on 256 CUs.  Every slice runs, the oracle looks at three of them."""
+counts of waves are on 256 CUs.  Every slice runs, the oracle looks at three of them.  (test_launch_rules.py says which kernels each
+of them runs.)"""
 import pytest
 
 import synth_inputs as syn
@@ -20,6 +21,7 @@ LAUNCHES = [
     ("p192-two-groups", (64, 128), (3, 16, 24), (3, 8, 8), 8, 9, [(1, 3, 2)]),                    # 2592; 36 sub-blocks
     ("p96-many", (64, 128), (2, 12, 16), (2, 6, 8), 4, 100, [(1, 1, 2), (1, 2, 1)]),              # 4800
     ("p96-some", (64, 128), (2, 12, 16), (2, 6, 8), 4, 33, [(1, 2, 2), (1, 1, 1)]),               # 1584
+    ("p96-few", (128,), (4, 18, 40), (2, 6, 8), 1, 4, [(1, 3, 3), (1, 1, 1)]),                    # 360; 27 sub-blocks and 3
     ("p32-some", (64, 128), (1, 8, 24), (1, 4, 8), 10, 10, [(1, 2, 3), (1, 1, 1)]),               # 600; 6 sub-blocks and 1
     ("p32-many", (64, 128), (1, 8, 24), (1, 4, 8), 20, 10, [(1, 1, 3)]),                          # 1200
 ]

@@ -1,7 +1,7 @@
 """GPU parity of every shape of the forward kernels that small and middle-sized launches take, on ordinary inputs, on keys masked
 at the start of a walk and on scores that grow along it (both of which make items run again): waves on their own (a key share each,
 32 or 64 queries per wave) and key groups that share LDS stages.  Counts of waves are on 256 CUs; every other head holds the same
-data, so that the oracle looks at two."""
+data, so that the oracle looks at two.  (test_launch_rules.py says which kernel each of them runs.)"""
 import numpy as np
 import pytest
 import torch
@@ -34,6 +34,8 @@ LAUNCHES = [
     ("shared-p64-two", 64, (1, 40, 56), (1, 8, 8), 16, (1, 3, 3)),            # 1120, 18
     ("shared-p64-one", 64, (1, 40, 56), (1, 8, 8), 30, (1, 3, 3)),            # 2100
     ("shared-p192-two", 64, (3, 24, 40), (3, 8, 8), 16, (1, 3, 3)),           # 1440, 54
+    ("shared-p192-three-two", 64, (3, 24, 40), (3, 8, 8), 7, (1, 1, 3)),      # 630, 18
+    ("shared-p192-three-one", 64, (3, 24, 40), (3, 8, 8), 24, (1, 3, 3)),     # 2160, 54
     ("shared-p96", 64, (4, 18, 40), (2, 6, 8), 24, (1, 3, 3)),                # 2160, 27
     ("shared-p32-two", 64, (1, 16, 48), (1, 4, 8), 34, (1, 3, 6)),            # 816, 18
     ("shared-p32-one", 64, (1, 16, 48), (1, 4, 8), 34, (1, 3, 3)),            # 816, 9

@@ -13,8 +13,8 @@ from tests.test_gpu_backward import assert_grad_parity, gpu_backward, oracle_bac
 
 pytestmark = pytest.mark.gpu
 
-# Key tiles with an even coordinate along the last axis are masked.  Every window holds tiles of both kinds; one, two and four
-# key groups.  (name, grid, tile, per-head windows)
+# Key tiles with an even coordinate along the last axis are masked.  Every window holds tiles of both kinds; small launches, whose
+# walks are shared by four or eight waves.  (name, grid, tile, per-head windows)
 SHAPES = [
     ("p32", (1, 16, 48), (1, 4, 8), [(1, 3, 5), (1, 1, 2)]),
     ("p64", (1, 40, 56), (1, 8, 8), [(1, 1, 7), (1, 1, 3)]),

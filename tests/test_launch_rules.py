@@ -7,6 +7,8 @@ import numpy as np
 import pytest
 
 import paper_2502_04507_amd as sta
+from tests import test_gpu_backward_groups, test_gpu_backward_launches, test_gpu_forward_groups, test_gpu_forward_large
+from tests import test_gpu_forward_launches
 from tests.launch_shapes import launches
 
 CUS = 256
@@ -82,3 +84,81 @@ def test_short_walks_on_64_token_tiles_count_by_their_length(B, H, grid, windows
 ])
 def test_launches_of_a_round_or_so_go_by_the_longest_walk_of_a_key_tile(H, grid, window, want):
     assert launches(1, H, 128, grid, (6, 8, 8), [window], gradients=True)[1].startswith(want + " ")
+
+
+# The kernels that the cases of tests/test_gpu_forward_launches.py and test_gpu_backward_launches.py run: a rule that sends one of
+# them elsewhere leaves its kernel without those tests.
+FORWARD = {
+    "own-p64-32q-8": "solo<64,2,8,0>", "own-p64-32q-4": "solo<64,2,4,0>", "own-p64-64q-8": "solo<64,4,8,0>",
+    "own-p64-64q-4": "solo<64,4,4,0>", "own-p192-64q-4": "solo<64,4,4,0>", "own-p384-64q-8": "solo<64,4,8,0>",
+    "own-p96-4": "solo<64,2,4,1>", "own-p32-4": "solo<64,2,4,1>", "own-p160-8": "solo<64,2,4,1>",
+    "own-p384-d128-8": "solo<128,2,8,0>", "own-p128-d128-4": "solo<128,2,4,0>", "own-p64-d128-4": "solo<128,2,4,1>",
+    "own-p192-d128-4": "solo<128,2,4,1>", "own-p32-d128-4": "solo<128,2,4,1>",
+    "shared-p64-two": "group<64,2,2,0,1>", "shared-p64-one": "group<64,2,1,0,1>", "shared-p192-two": "group<64,2,2,0,1>",
+    "shared-p192-three-two": "group<64,3,2,0,1>", "shared-p192-three-one": "group<64,3,1,0,1>", "shared-p96": "group<64,3,1,1,1>",
+    "shared-p32-two": "group<64,1,2,1,1>", "shared-p32-one": "group<64,1,1,1,1>", "shared-p384-d128-four": "group<128,2,4,0,1>",
+    "shared-p384-d128-two": "group<128,2,2,0,1>", "shared-p384-d128-one": "group<128,2,1,0,1>",
+    "shared-p64-d128-two": "group<128,2,2,1,1>", "shared-p64-d128-one": "group<128,2,1,1,1>",
+    "shared-p96-d128-two": "group<128,3,2,1,1>", "shared-p96-d128-one": "group<128,3,1,1,1>", "shared-p32-d128": "group<128,1,1,1,1>",
+}
+BACKWARD = {
+    ("p128-two-groups", 64): "dq<64,2,2,1> dkv<64,2,2,1,1>", ("p128-two-groups", 128): "dq<128,2,2,1> dkv<128,2,2,1,1>",
+    ("p384-four-waves", 64): "dq<64,4,1,1> dkv<64,4,1,2,1>", ("p384-four-waves", 128): "dq<128,4,1,1> dkv<128,4,1,1,1>",
+    ("p128-four-waves", 64): "dq<64,4,1,1> dkv<64,4,1,2,1>", ("p128-four-waves", 128): "dq<128,4,1,1> dkv<128,4,1,1,1>",
+    ("p64-two-groups", 64): "dq<64,2,1,1> dkv<64,2,2,1,1>", ("p64-two-groups", 128): "dq<128,2,1,1> dkv<128,2,2,1,1>",
+    ("p64-two-pairs", 128): "dq<128,2,1,1> dkv_pair<2,1,1>", ("p384-mixed", 128): "dq<128,4,1,1> dkv<128,2,2,1,1>",
+    ("p384-six-pairs", 128): "dq<128,4,1,1> dkv_pair<6,1,1>", ("p64-two-waves", 64): "dq<64,2,1,1> dkv<64,2,1,1,1>",
+    ("p64-two-waves", 128): "dq<128,2,1,1> dkv<128,2,1,1,1>", ("p192-two-groups", 64): "dq<64,3,1,1> dkv<64,2,2,1,1>",
+    ("p192-two-groups", 128): "dq<128,3,1,1> dkv<128,2,2,1,1>", ("p96-many", 64): "dq<64,3,1,1> dkv<64,3,1,1,1>",
+    ("p96-many", 128): "dq<128,3,1,1> dkv_pair<3,2,1>", ("p96-some", 64): "dq<64,3,1,1> dkv<64,1,4,1,1>",
+    ("p96-some", 128): "dq<128,3,1,1> dkv_pair<3,2,1>", ("p96-few", 128): "dq<128,3,2,1> dkv<128,1,4,1,1>",
+    ("p32-some", 64): "dq<64,1,1,1> dkv<64,1,2,1,1>", ("p32-some", 128): "dq<128,1,1,1> dkv_pair<1,1,1>",
+    ("p32-many", 64): "dq<64,1,1,1> dkv<64,1,1,1,1>", ("p32-many", 128): "dq<128,1,1,1> dkv_pair<1,1,1>",
+}
+# ... and the shapes that other GPU tests run: test_gpu_forward_groups.py (two units per stage), test_gpu_forward_large.py,
+# test_gpu_backward_groups.py (small launches, three waves in two groups)
+ELSEWHERE = {"group<64,4,1,0,2>", "x32<4>", "x32<12>", "solo<64,2,8,1>", "solo<128,2,8,1>", "dq<64,1,4,1>", "dq<128,1,4,1>", "dq<64,3,2,1>"}
+
+
+def kernels(lines):
+    return [line.split(" ")[0] for line in lines]
+
+
+def test_the_gpu_tests_run_the_kernels_that_they_are_for():
+    for name, D, grid, tile, heads, window in test_gpu_forward_launches.LAUNCHES:
+        assert kernels(launches(1, heads, D, grid, tile, [window])) == [FORWARD[name]], name
+    for name, D, grid, tile, B, H, windows in test_gpu_backward_launches.CASES:
+        assert kernels(launches(B, H, D, grid, tile, windows, gradients=True)) == BACKWARD[name, D].split(" "), (name, D)
+    seen = set()
+    for _, grid, tile, windows in test_gpu_forward_groups.SHAPES:
+        for D in (64, 128):
+            seen.update(kernels(launches(1, len(windows), D, grid, tile, windows)))
+    for heads, grid, tile in ((30, (6, 16, 24), (6, 8, 8)), (66, (4, 16, 16), (2, 8, 8))):
+        seen.update(kernels(launches(1, heads, 64, grid, tile, [(1, 3, 3), (3, 3, 3)])))
+    for name, (grid, tile, heads, workspace) in test_gpu_forward_large.LAUNCHES.items():
+        (line,) = launches(1, heads, 128, grid, tile, [(1, 3, 3), (3, 3, 3)], workspace=workspace)
+        assert ("parts 1 " not in line) == workspace, (name, line)
+        seen.update(kernels([line]))
+    for _, grid, tile, B, H, windows in test_gpu_backward_groups.SHAPES:
+        for D in (64, 128):
+            seen.update(kernels(launches(B, H, D, grid, tile, windows, gradients=True)))
+    assert ELSEWHERE <= seen, ELSEWHERE - seen
+    assert {"dkv_pair<6,1,1>", "dkv<128,4,1,1,1>", "dkv<128,2,2,1,1>"} == {
+        kernels(launches(1, H, 128, grid, (6, 8, 8), windows, gradients=True))[1] for _, grid, H, windows in test_gpu_backward_groups.SIX_PAIRS}
+
+
+def test_no_shape_is_without_a_gpu_test():
+    """Launches drawn over the whole range take no shape that the tables above do not name."""
+    named = set(FORWARD.values()) | {k for v in BACKWARD.values() for k in v.split(" ")} | ELSEWHERE
+    rng = np.random.default_rng(7)
+    tiles = [(6, 8, 8), (1, 8, 8), (2, 8, 8), (3, 8, 8), (4, 8, 8), (2, 6, 8), (4, 4, 6), (4, 4, 8), (5, 8, 8), (1, 4, 8), (6, 8, 16), (7, 4, 8)]
+    seen = set()
+    for _ in range(3000):
+        tile = tiles[rng.integers(len(tiles))]
+        n = [int(rng.integers(1, 4)) if tile[0] > 1 else 1, int(rng.integers(1, 7)), int(rng.integers(1, 9))]
+        windows = [tuple(int(rng.integers(1, m + 1)) for m in n) for _ in range(rng.integers(1, 4))]
+        B, H, D = int(rng.integers(1, 5)), int(np.exp(rng.uniform(0, 4))), int(rng.choice([64, 128]))
+        args = (B, H, D, tuple(a * b for a, b in zip(n, tile)), tile, windows)
+        seen.update(kernels(launches(*args, workspace=bool(rng.integers(2)))) + kernels(launches(*args, gradients=True)))
+    assert seen <= named, seen - named
+    assert named <= seen, named - seen
