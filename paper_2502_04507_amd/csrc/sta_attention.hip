@@ -1098,7 +1098,7 @@ void sta_fwd_solo_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restr
 // thirteen, and on this chip every vector instruction saved is energy, hence time.
 constexpr int kKGroup = 1024 + 64, kVGroup = 1024 + 32;
 
-template <int NW, int KB, int STAGES, int MINB, bool PRESCALE>
+template <int NW, int KB, int STAGES, int MINB>
 __global__ __launch_bounds__(NW * 64, MINB) void sta_fwd_x32_kernel(const bf16_raw *__restrict__ q,
                                                                  const bf16_raw *__restrict__ k,
                                                                  const bf16_raw *__restrict__ v,
@@ -1192,22 +1192,17 @@ __global__ __launch_bounds__(NW * 64, MINB) void sta_fwd_x32_kernel(const bf16_r
         v_addr[m] = smem_addr + (uint32_t)(K_BYTES + g4 * kVGroup + j4 * ROWB + ((((m ^ j4) << 2) | (s4 >> 1)) << 4) + 8 * (s4 & 1));
 
     // ---- Q fragments (B operand of S^T: query 16*qb + c16, channels 32*ks + 8*g4 ..), resident in registers.
-    // With PRESCALE they are multiplied by scale * log2(e) here, once, and rounded to bf16 again, so that the matrix
-    // product delivers base-2 exponents and the 16 multiplications per lane and sub-block disappear.  Measured
-    // 4.5 % faster (11.43 against 11.95 ms at 115,200 tokens, window 3x3x3), but the second rounding of Q puts a
-    // relative error of up to 2^-9 on every term of a score: with scores of a few tens the probabilities are off by
-    // a percent and the output error leaves the 2e-2 bound (0.07 on the growing-maximum test).  The entry points
-    // therefore use the exact form; the flag is kept for measurements.
+    // Multiplied by scale * log2(e) here, once, and rounded to bf16 again, they would make the matrix product deliver
+    // base-2 exponents and save the 16 multiplications per lane and sub-block.  That was 4.5 % faster (11.43 against
+    // 11.95 ms at 115,200 tokens, window 3x3x3), but the second rounding of Q puts a relative error of up to 2^-9 on every
+    // term of a score: with scores of a few tens the probabilities are off by a percent and the output error leaves the
+    // 2e-2 bound (0.07 on the growing-maximum test).
     bf16x8 Qr[2][KS];
 #pragma unroll
     for (int qb = 0; qb < 2; ++qb)
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const bf16x8 raw = *reinterpret_cast<const bf16x8 *>(qh + (size_t)(16 * qb + c16) * D + ks * 32 + g4 * 8);
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                Qr[qb][ks][e] = PRESCALE ? static_cast<__bf16>(static_cast<float>(raw[e]) * p.scale_log2e) : raw[e];
-        }
+        for (int ks = 0; ks < KS; ++ks)
+            Qr[qb][ks] = *reinterpret_cast<const bf16x8 *>(qh + (size_t)(16 * qb + c16) * D + ks * 32 + g4 * 8);
 
     // O^T accumulators: Oacc[cb][qb][i] = channel 16*cb + 4*g4 + i of query 16*qb + c16
     floatx4 Oacc[CB][2];
@@ -1215,7 +1210,7 @@ __global__ __launch_bounds__(NW * 64, MINB) void sta_fwd_x32_kernel(const bf16_r
     for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb) Oacc[cb][qb] = floatx4{0.f, 0.f, 0.f, 0.f};
-    // Offset m per query, in the units of the scores (raw dot products; base-2 exponents with PRESCALE).  The score
+    // Offset m per query, in the units of the scores (raw dot products).  The score
     // accumulators START at -m (Sinit, the value replicated over the four registers of an accumulator), so what the
     // matrix instructions deliver is s - m and the exponential needs one multiplication by scale * log2(e) per
     // element instead of a fused multiply-add plus bookkeeping.  m is 0 while the first sub-block's scores are formed, which
@@ -1319,7 +1314,7 @@ __global__ __launch_bounds__(NW * 64, MINB) void sta_fwd_x32_kernel(const bf16_r
     // enters the five operand base addresses with one addition each.
     // (lds_off: where the stage begins; it enters the operand base addresses at run time)
     // units of the accumulated scores: base-2 exponents if Q was scaled, raw dot products otherwise
-    const float c = PRESCALE ? 1.f : p.scale_log2e;
+    const float c = p.scale_log2e;
     constexpr int kPlain = 0, kFirst = 1, kCareful = 2;
     auto sub_block_at = [&](auto track_c, uint32_t lds_off, float grow_above) __attribute__((always_inline)) {
         // kFirst: set the offsets.  kCareful: follow the growth of the scores, which start at zero here: those of keys behind
@@ -1433,8 +1428,8 @@ __global__ __launch_bounds__(NW * 64, MINB) void sta_fwd_x32_kernel(const bf16_r
 #pragma unroll
                 for (int e = 0; e < 4; e += 2) {
                     typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-                    const float p0 = __builtin_amdgcn_exp2f(PRESCALE ? S[kb][qb][e] : S[kb][qb][e] * c);
-                    const float p1 = __builtin_amdgcn_exp2f(PRESCALE ? S[kb][qb][e + 1] : S[kb][qb][e + 1] * c);
+                    const float p0 = __builtin_amdgcn_exp2f(S[kb][qb][e] * c);
+                    const float p1 = __builtin_amdgcn_exp2f(S[kb][qb][e + 1] * c);
                     bf16x2 pp;
                     pp[0] = static_cast<__bf16>(p0);
                     pp[1] = static_cast<__bf16>(p1);
@@ -1712,7 +1707,7 @@ hipError_t launch_x32(const FwdArgs &a)
     p.split_ws = split_items ? a.split_ws : nullptr;
     dim3 grid(p.split_first + split_items * p.split_parts), block(NW * 64);
     if (a.note) return a.note->add("x32<%d> items %u workgroups %u parts %u of %u", NW, items, grid.x, p.split_parts, split_items);
-    sta_fwd_x32_kernel<NW, KB, STAGES, MINB, false><<<grid, block, 0, a.stream>>>(
+    sta_fwd_x32_kernel<NW, KB, STAGES, MINB><<<grid, block, 0, a.stream>>>(
         static_cast<const bf16_raw *>(a.q), static_cast<const bf16_raw *>(a.k), static_cast<const bf16_raw *>(a.v),
         static_cast<bf16_raw *>(a.o), p, plan);
     hipError_t e = hipGetLastError();

@@ -14,8 +14,8 @@
 //                         -delta_i and -lse_i / scale of its queries and leaves them for the second kernel;
 //   sta_bwd_dkv_kernel    one wave per 32 keys, walks the QUERY tiles that keep its key tile (the
 //                         transposed box): 4 MFMA products per block (Q K^T, dO V^T, dO^T P, Q^T dS);
-//   sta_bwd_dkv_pair_kernel   the same with the products split over pairs of waves (head dimension 128 on
-//                         tiles that are no multiple of 64 tokens).
+//   sta_bwd_dkv_pair_kernel   the same with the products split over pairs of waves (head dimension 128: tiles of 96 and 32 tokens'
+//                         multiples, short walks on other multiples of 64, one full round of equal walks on multiples of 384).
 // S and dP are thus computed twice (7 products against the 5 of a single-pass scheme with atomics on dQ).
 //
 // Same MFMA formulation as the forward kernel (v_mfma_f32_16x16x32_bf16, the shape that costs the least energy per
@@ -1009,15 +1009,15 @@ hipError_t launch_dq(const BwdArgs &a)
 // left at the end; 16x48x64 in 256-token tiles, 3x3x3 and 3x3x5 2046 us head after head, 2377 row after row; 30x48x80, windows
 // from 1x3x3 to the whole grid 17.5, 26.6 ms).  Entry point, head after head against the rows of all heads in turn:
 // - Rows of tiles per head a multiple of eight: head after head an XCD gets the same rows of every head, and border rows have
-//   half the work of inner ones.  16x48x64 in 256-token tiles, 24 heads, head dimension 64 7443, 6488 us, 128 -12 %; 24x64x64 in
-//   384-token tiles 128 (six pairs) -16 %; 20x64x64 in 64-token tiles -19 %, four images -20 %.
+//   half the work of inner ones.  16x48x64 in 256-token tiles, 24 heads, head dimension 64 7443, 6488 us, 128 -12 %;
+//   20x64x64 in 64-token tiles -19 %, four images -20 %.
 // - Otherwise it shortens the tail, which tells in launches of up to about sixteen rounds of workgroups (18x40x64 in 192-token
-//   tiles, 16 heads -7 %; 10x30x56 in 96-token tiles -11 %; 30x48x80 in 384-token tiles, two heads -9 %, four -5 %; six pairs,
-//   12x48x48, six heads -5 %).  Beyond that what counts is that the next row of a head finds operands of this one in the
-//   caches: its box of Q and dO rows either fits an XCD's L2 (20x48x64 in 128-token tiles, head dimension 64, 40 heads -1 %;
+//   tiles, 16 heads -7 %; 10x30x56 in 96-token tiles -11 %; 30x48x80 in 384-token tiles, two heads -9 %, four -5 %).  Beyond that
+//   what counts is that the next row of a head finds operands of this one in the caches: its box of Q and dO rows either fits an XCD's L2 (20x48x64 in 128-token tiles, head dimension 64, 40 heads -1 %;
 //   12x48x48, 48 heads of 128 -3 %) or the rows of a head should stay together (30x48x80, head dimension 64, 12 to 24 heads
 //   +0.4 to +1.5 %; 128 +1 %).
-// - Not where every workgroup has a CU of its own and no order can even anything out (24x32x32, two heads of 128 +3 to +4 %).
+// - Not where every workgroup has a CU of its own and no order can even anything out (24x32x32, two heads of 128 +3 to +4 %), as in
+//   every launch of six pairs.
 bool rows_of_all_heads(const BwdArgs &a, uint32_t cols, uint64_t resident)
 {
     const sta::FwdParams &p = a.p;

@@ -103,6 +103,8 @@ constexpr int kGridShift = 23;                              // a grid holds fewe
 // 236; 234, 241; 217, 224; 214, 216.  85 MB 30.0, 29.6; 29.8, 30.1; 28.6, 29.2; 28.6, 28.4.  96-token tiles, 43 MB 16.9, 17.3; 15.0,
 // 16.8; 14.6, 15.8; 14.9, 15.3.  64-token tiles of dimension 64, 67 MB 23.8, 23.8; 24.2, 24.0; 23.1, 23.3; 23.0, 22.8.  32-token tiles
 // of dimension 64, a piece per lane before as well, 157 MB 50.3, 49.6; ordered 50.0, 50.3.  One or two by 512 or 1024 lanes: no better.
+// From a graph, tensors in turn, four pieces and one: 0.4 MB 2.2, 1.9; 2 MB 2.45, 2.15; 4 MB 3.3, 3.1; but 8 MB 3.95, 4.2; 16 MB 6.2, 6.5
+// (two pieces 4.1 and 6.3); 22 MB 8.4, 8.4; 37 MB 14.8, 13.9.
 // Order: workgroup ids go round-robin over the 8 XCDs; every XCD takes whole rows of tiles along w, whose tokens are one piece of each
 // raster row, in turn with the others (full rounds of eight rows; what is left over in the order of the ids).
 template <bool SRC_F32, bool DST_F32, bool TO_TILED, bool STREAM, int CHUNKS>
