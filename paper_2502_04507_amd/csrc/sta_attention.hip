@@ -1217,7 +1217,9 @@ __global__ __launch_bounds__(NW * 64, MINB) void sta_fwd_x32_kernel(const bf16_r
     // then set it, and never decreases afterwards.
     float m_run[2] = {0.f, 0.f};
     floatx4 Sinit[2] = {floatx4{0.f, 0.f, 0.f, 0.f}, floatx4{0.f, 0.f, 0.f, 0.f}};
-    float l_run[2] = {0.f, 0.f};                  // this lane's share of the two row sums
+    // Row sums, a matrix product with an operand of ones (all registers of a lane hold the sum of its query).  Two matrix instructions a
+    // sub-block where eight v_dot2 had to go through the matrix pipe as well: 10,748 -> 10,649 us, and 10,116 -> 9784 over the whole grid.
+    floatx4 l_acc[2] = {floatx4{0.f, 0.f, 0.f, 0.f}, floatx4{0.f, 0.f, 0.f, 0.f}};
 
     const int sub_per_tile = p.P / KB;
     const int n_all = box.count() * sub_per_tile;           // sub-blocks of the whole item
@@ -1309,17 +1311,19 @@ __global__ __launch_bounds__(NW * 64, MINB) void sta_fwd_x32_kernel(const bf16_r
     };
     start_pipeline();
 
-    // One sub-block.  The loop is not unrolled over the two stages (unrolled, the register allocator gives the
-    // accumulators different registers in the two copies and copies all 64 once per pair of sub-blocks); the stage
-    // enters the five operand base addresses with one addition each.
-    // (lds_off: where the stage begins; it enters the operand base addresses at run time)
-    // units of the accumulated scores: base-2 exponents if Q was scaled, raw dot products otherwise
+    // One sub-block.  OFF and lds_off: where its stage begins.  In the first pass the loop is unrolled over the two stages and the
+    // stage is part of the read instructions (OFF), which saves an addition per operand address: 43 vector instructions where
+    // there were 53, with the row sums below.  The careful loop, which rarely runs, adds it at run time (lds_off).
+    // us, before and after both changes, 384-token tiles: 24 heads of 30x48x80, 3x3x3 10,834, 10,649, 1x3x3 3964, 3823; two heads
+    // over the whole grid 10,250, 9784; 12 heads of 12x48x48, 1x3x3 474, 461; 128-token tiles, 24 heads of 8x64x64, 3x3x3 1129, 1088.
     const float c = p.scale_log2e;
     constexpr int kPlain = 0, kFirst = 1, kCareful = 2;
-    auto sub_block_at = [&](auto track_c, uint32_t lds_off, float grow_above) __attribute__((always_inline)) {
+    using Stage0 = std::integral_constant<int, 0>;
+    using Stage1 = std::integral_constant<int, STAGE_BYTES>;
+    auto sub_block_at = [&](auto track_c, auto off_c, uint32_t lds_off, float grow_above) __attribute__((always_inline)) {
         // kFirst: set the offsets.  kCareful: follow the growth of the scores, which start at zero here: those of keys behind
         // masked ones (scores of the lowest numbers) are lost in accumulators that start at minus such an offset.
-        constexpr int TRACK = decltype(track_c)::value;
+        constexpr int TRACK = decltype(track_c)::value, OFF = decltype(off_c)::value;
         const uint32_t kb_ = k_base + lds_off;
         uint32_t vb_[4];
 #pragma unroll
@@ -1332,7 +1336,7 @@ __global__ __launch_bounds__(NW * 64, MINB) void sta_fwd_x32_kernel(const bf16_r
 #pragma unroll
             for (int qb = 0; qb < 2; ++qb) S[kb][qb] = TRACK == kCareful ? floatx4{0.f, 0.f, 0.f, 0.f} : Sinit[qb];
         auto k_read = [&](auto kbc, auto ksc) {
-            return ds_read_b128_at<decltype(kbc)::value * 4 * kKGroup + decltype(ksc)::value * 64>(kb_);
+            return ds_read_b128_at<OFF + decltype(kbc)::value * 4 * kKGroup + decltype(ksc)::value * 64>(kb_);
         };
         using I0 = std::integral_constant<int, 0>;
         using I1 = std::integral_constant<int, 1>;
@@ -1392,7 +1396,7 @@ __global__ __launch_bounds__(NW * 64, MINB) void sta_fwd_x32_kernel(const bf16_r
                     if (__builtin_amdgcn_ballot_w64(grown) != 0) {
                         const float alpha = grown ? __builtin_amdgcn_exp2f((m_run[qb] - mq[qb]) * c) : 1.f;
                         m_run[qb] = grown ? mq[qb] : m_run[qb];
-                        l_run[qb] *= alpha;
+                        l_acc[qb] *= alpha;
                         // in place: written as plain multiplications the register allocator gives the scaled accumulators
                         // new registers and then copies all 64 on the path that does NOT rescale
                         // (the compiler does not see into the assembly: the wait state that a vector instruction needs before
@@ -1414,8 +1418,8 @@ __global__ __launch_bounds__(NW * 64, MINB) void sta_fwd_x32_kernel(const bf16_r
         shortx4 va[2][4][2];
         static_for<0, 4>([&](auto i) {
             constexpr int cb = decltype(i)::value;
-            va[0][cb][0] = ds_read_tr16<(cb & 1) * 32>(vb_[cb >> 1]);
-            va[0][cb][1] = ds_read_tr16<(cb & 1) * 32 + 4 * kVGroup>(vb_[cb >> 1]);
+            va[0][cb][0] = ds_read_tr16<OFF + (cb & 1) * 32>(vb_[cb >> 1]);
+            va[0][cb][1] = ds_read_tr16<OFF + (cb & 1) * 32 + 4 * kVGroup>(vb_[cb >> 1]);
         });
         __builtin_amdgcn_sched_barrier(0);       // the exponentials stay behind these reads
         // probabilities, rounded to bf16, packed as the B operand of the PV product of their query block: k index
@@ -1435,12 +1439,13 @@ __global__ __launch_bounds__(NW * 64, MINB) void sta_fwd_x32_kernel(const bf16_r
                     pp[1] = static_cast<__bf16>(p1);
                     Pb[qb][4 * kb + e] = pp[0];
                     Pb[qb][4 * kb + e + 1] = pp[1];
-                    bf16x2 ones;
-                    ones[0] = static_cast<__bf16>(1.0f);
-                    ones[1] = static_cast<__bf16>(1.0f);
-                    l_run[qb] = __builtin_amdgcn_fdot2_f32_bf16(pp, ones, l_run[qb], false);   // sums the rounded values
                 }
         }
+        bf16x8 ones;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) ones[e] = static_cast<__bf16>(1.0f);
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb) l_acc[qb] = mfma_16x16x32(ones, Pb[qb], l_acc[qb]);       // sums the rounded values
 
         // ---- O^T += V^T P^T: one k-step covers the 32 keys; eight channel blocks x two query blocks.  The transposing
         // reads are issued by hand, four channel blocks ahead of the MFMAs that consume them.
@@ -1449,8 +1454,8 @@ __global__ __launch_bounds__(NW * 64, MINB) void sta_fwd_x32_kernel(const bf16_r
             if constexpr (g == 0) {
                 static_for<0, 4>([&](auto i) {
                     constexpr int cb = 4 + decltype(i)::value;
-                    va[1][cb - 4][0] = ds_read_tr16<(cb & 1) * 32>(vb_[cb >> 1]);
-                    va[1][cb - 4][1] = ds_read_tr16<(cb & 1) * 32 + 4 * kVGroup>(vb_[cb >> 1]);
+                    va[1][cb - 4][0] = ds_read_tr16<OFF + (cb & 1) * 32>(vb_[cb >> 1]);
+                    va[1][cb - 4][1] = ds_read_tr16<OFF + (cb & 1) * 32 + 4 * kVGroup>(vb_[cb >> 1]);
                 });
                 pv_wait<8>(va[0]);
             } else {
@@ -1488,15 +1493,19 @@ __global__ __launch_bounds__(NW * 64, MINB) void sta_fwd_x32_kernel(const bf16_r
     // accumulators as well it cost 36 bytes of scratch: 24 heads of 30x48x80, window 1x1x1 755 -> 728 us.)  (2^96 leaves 66 in the exponent of e between the first keys' maximum and the largest score before
     // the second pass is needed, and room for |V| up to 2^32 in the accumulators.)
     next_sub_block();
-    sub_block_at(std::integral_constant<int, kFirst>{}, 0u, 0.f);
+    sub_block_at(std::integral_constant<int, kFirst>{}, Stage0{}, 0u, 0.f);
 #pragma unroll 1
-    for (int iter = 1; iter < n_iter; ++iter) {
+    for (int iter = 1; iter < n_iter; iter += 2) {
         next_sub_block();
-        sub_block_at(std::integral_constant<int, kPlain>{}, (uint32_t)((iter & 1) * STAGE_BYTES), 0.f);
+        sub_block_at(std::integral_constant<int, kPlain>{}, Stage1{}, 0u, 0.f);
+        if (iter + 1 < n_iter) {
+            next_sub_block();
+            sub_block_at(std::integral_constant<int, kPlain>{}, Stage0{}, 0u, 0.f);
+        }
     }
     float l_tot[2];
 #pragma unroll
-    for (int qb = 0; qb < 2; ++qb) l_tot[qb] = quad_lane_sum(l_run[qb]);
+    for (int qb = 0; qb < 2; ++qb) l_tot[qb] = l_acc[qb][0];
     // 2^96; and 2^-64, below which only rows are whose first keys all score minus infinity (their offset is 0 then)
     constexpr float kRedoAbove = 79228162514264337593543950336.f, kRedoBelow = 5.42101086242752217e-20f;
     // The accumulators too: with |V| beyond 2^32 they can leave the range before the row sums reach the bound.  The
@@ -1515,7 +1524,7 @@ __global__ __launch_bounds__(NW * 64, MINB) void sta_fwd_x32_kernel(const bf16_r
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb) {
             m_run[qb] = -INFINITY;
-            l_run[qb] = 0.f;
+            l_acc[qb] = floatx4{0.f, 0.f, 0.f, 0.f};
             Sinit[qb] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int cb = 0; cb < CB; ++cb) Oacc[cb][qb] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -1525,10 +1534,10 @@ __global__ __launch_bounds__(NW * 64, MINB) void sta_fwd_x32_kernel(const bf16_r
         for (int iter = 0; iter < n_iter; ++iter) {
             next_sub_block();
             // growth threshold: 2^8 in the units of the scores
-            sub_block_at(std::integral_constant<int, kCareful>{}, (uint32_t)((iter & 1) * STAGE_BYTES), __uint_as_float(bound_bits));
+            sub_block_at(std::integral_constant<int, kCareful>{}, Stage0{}, (uint32_t)((iter & 1) * STAGE_BYTES), __uint_as_float(bound_bits));
         }
 #pragma unroll
-        for (int qb = 0; qb < 2; ++qb) l_tot[qb] = quad_lane_sum(l_run[qb]);
+        for (int qb = 0; qb < 2; ++qb) l_tot[qb] = l_acc[qb][0];
     }
 
     // ---- finalize -------------------------------------------------------------------
