@@ -534,17 +534,21 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
     };
     reset(0.f);
     const float c = p.scale_log2e;
+    bf16x8 ones;                                            // operand of the row sums
+#pragma unroll
+    for (int e = 0; e < 8; ++e) ones[e] = static_cast<__bf16>(1.0f);
+    if constexpr (!FOLLOW && UPS == 1) asm volatile("" : "+v"(ones));   // kept in registers, where there are enough, not made anew in every unit
     if constexpr (QW * KG == 12) {                          // static priorities against the age order, as in the kernel below
         if (wave >= 8) __builtin_amdgcn_s_setprio(2);
         else if (wave >= 4) __builtin_amdgcn_s_setprio(1);
     }
 
     constexpr int kPlain = 0, kFollow = 1, kFirst = 2, kCareful = 3;
-    // One unit of 32 keys whose K begins at LDS offset at (relative to the group's first stage).
-    auto unit_at = [&](auto track_c, uint32_t at, float grow_above) __attribute__((always_inline)) {
+    // One unit of 32 keys whose K begins at LDS offset OFF + at (relative to the group's first stage).
+    auto unit_at = [&](auto track_c, auto off_c, uint32_t at, float grow_above) __attribute__((always_inline)) {
         // kFirst: set the offsets; kFollow: move them with the scores.  kCareful: the same on scores that do not start at
         // minus the offset: they lose nothing to an old offset that was far below them (keys masked by a lowest value).
-        constexpr int TRACK = decltype(track_c)::value;
+        constexpr int TRACK = decltype(track_c)::value, OFF = decltype(off_c)::value;
         uint32_t tr_at[4];
 #pragma unroll
         for (int m = 0; m < 4; ++m) tr_at[m] = tr_addr[m] + at;
@@ -553,7 +557,7 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
         for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
             for (int qb = 0; qb < NQ; ++qb) S[kb][qb] = FOLLOW || TRACK == kCareful ? floatx4{0.f, 0.f, 0.f, 0.f} : Sinit[FOLLOW ? 0 : qb];
-        rows_times_resident<D, 0>(row_addr + at, Qr, S);   // K Q^T minus the offset
+        rows_times_resident<D, OFF>(row_addr + at, Qr, S);   // K Q^T minus the offset
         if constexpr (TRACK != kPlain) {
             float mq[NQ];
 #pragma unroll
@@ -619,7 +623,7 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
                 }
             }
         }
-        StagedTransposedProduct<D, 0> v_t;
+        StagedTransposedProduct<D, OFF> v_t;
         v_t.prefetch(tr_at);
         __builtin_amdgcn_sched_barrier(0);                  // the exponentials stay behind these reads
         // probabilities, rounded to bf16, packed as the B operand of the PV product of their query block
@@ -640,9 +644,6 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
                     Pb[qb][4 * kb + e] = pp[0];
                     Pb[qb][4 * kb + e + 1] = pp[1];
                 }
-        bf16x8 ones;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) ones[e] = static_cast<__bf16>(1.0f);
 #pragma unroll
         for (int qb = 0; qb < NQ; ++qb) l_acc[qb] = mfma_16x16x32(ones, Pb[qb], l_acc[qb]);       // sums the rounded values
         v_t.run(tr_at, Pb, Oacc);                           // O^T += V^T P^T
@@ -661,18 +662,26 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
             asm volatile("" ::: "memory");
             issue_next();
         };
-        auto rest_at = [&](uint32_t at) __attribute__((always_inline)) { unit_at(std::integral_constant<int, REST>{}, at, bound); };
-        if constexpr (!CAREFUL) {
+        using Rest = std::integral_constant<int, REST>;
+        using Stage0 = std::integral_constant<int, 0>;
+        using Stage1 = std::integral_constant<int, STAGE_B>;
+        auto stage_at = [&](auto first_c, auto stage_c, uint32_t at, int u) __attribute__((always_inline)) {
             next_stage();
-            if (KG == 1 || n_units > 0) unit_at(std::integral_constant<int, kFirst>{}, 0u, 0.f);
-            if constexpr (UPS == 2) rest_at(UNIT_B);
-        }
+            if (KG == 1 || u < n_units) unit_at(first_c, stage_c, at, bound);
+            if constexpr (UPS == 2) unit_at(Rest{}, std::integral_constant<int, decltype(stage_c)::value + UNIT_B>{}, at, bound);
+        };
+        if constexpr (!CAREFUL) stage_at(std::integral_constant<int, kFirst>{}, Stage0{}, 0u, 0);
+        // The stage is part of the read instructions, not an addition to each of five addresses.  (Added in the careful pass, and where
+        // the offset follows: there the unrolled loop copies the accumulators from one half to the other, 29 registers of scratch.)
+        if constexpr (!CAREFUL && !FOLLOW) {
 #pragma unroll 1
-        for (int u = CAREFUL ? 0 : UPS; u < n_steps; u += UPS) {
-            next_stage();
-            const uint32_t at = (uint32_t)((u / UPS & 1) * STAGE_B);
-            if (KG == 1 || u < n_units) rest_at(at);
-            if constexpr (UPS == 2) rest_at(at + UNIT_B);
+            for (int u = UPS; u < n_steps; u += 2 * UPS) {
+                stage_at(Rest{}, Stage1{}, 0u, u);
+                if (u + UPS < n_steps) stage_at(Rest{}, Stage0{}, 0u, u + UPS);
+            }
+        } else {
+#pragma unroll 1
+            for (int u = CAREFUL ? 0 : UPS; u < n_steps; u += UPS) stage_at(Rest{}, Stage0{}, (uint32_t)((u / UPS & 1) * STAGE_B), u);
         }
     };
     float l_tot[NQ];
