@@ -417,7 +417,7 @@ __device__ __forceinline__ GroupItem group_item_of(uint32_t id, const sta::FwdPa
 // allow: it waits for every outstanding DMA) changes nothing at four waves per SIMD and costs occupancy on small tiles:
 // 6.77 against 6.73 ms, 108 against 98 us.
 // ---------------------------------------------------------------------------
-template <int D, int QW, int KG, int WPE, bool FOLLOW, int UPS>
+template <int D, int QW, int KG, int WPE, bool FOLLOW, int UPS, bool ONEV>
 __global__ __attribute__((amdgpu_flat_work_group_size(QW * KG * 64, QW * KG * 64), amdgpu_waves_per_eu(WPE)))
 void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
                                                                          const bf16_raw *__restrict__ k,
@@ -433,7 +433,11 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
     constexpr int QB = QW * WQ;                             // queries per workgroup
     constexpr int UNIT_B = R::Tile + L::Tile;               // 32 keys: K, then V
     constexpr int STAGE_B = UPS * UNIT_B;                   // what a barrier makes available
-    constexpr int GROUP_B = 2 * STAGE_B;                    // LDS of one key group: two stages
+    // LDS of one key group: two stages, or (ONEV) two stages of K and one of V
+    constexpr int GROUP_B = ONEV ? 2 * R::Tile + L::Tile : 2 * STAGE_B;
+    constexpr int K_STAGE_B = ONEV ? R::Tile : STAGE_B;     // from K of a stage to K of the other
+    constexpr int V_AT = ONEV ? 2 * R::Tile : R::Tile;      // V of the first stage
+    static_assert(!ONEV || (FOLLOW && UPS == 1 && L::Groups % QW == 0));
     static_assert(UPS == 1 || KG == 1, "shares of a walk are counted in single units");
     constexpr int OPS = 2 * L::Groups;                      // DMA instructions per unit
     constexpr int WAVE_OPS = (OPS + QW - 1) / QW;           // at most this many per wave
@@ -476,9 +480,28 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
 
     // ---- DMA: instruction j of a unit brings 1 KB of K or V; wave qw of the group issues j = qw, qw + QW, ..
     const uint32_t k_lane_off = R::dma_lane_offset(lane), v_lane_off = L::dma_lane_offset(lane);
-    int issued = 0;                                         // units requested so far
+    // operand: K or V of the 32 keys from row, all of it (ONEV)
+    auto issue_operand = [&](const char *head, uint32_t lane_off, uint32_t row, char *dst, int group_bytes) __attribute__((always_inline)) {
+        asm volatile("" : "+v"(lane_off));
+#pragma unroll
+        for (int i = 0; i < L::Groups / QW; ++i) {
+            const int j = qw + i * QW;
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(head + (size_t)(row + L::GroupRows * j) * L::RowB + lane_off),
+                                             STA_LDS_PTR(dst + j * group_bytes), 16, 0, 0);
+        }
+    };
+    int issued = 0;                                         // units requested so far (ONEV: their K)
+    uint32_t v_row = 0;                                     // ONEV: the unit whose K was requested last
+    bool more = false;                                      // ONEV: a unit's K has been requested behind the V that is waited for
     auto issue_next = [&]() __attribute__((always_inline)) {
         if (issued >= n_units) return;
+        if constexpr (ONEV) {
+            v_row = walk.next_row;
+            issue_operand(kh, k_lane_off, v_row, smem + kg * GROUP_B + (issued & 1) * K_STAGE_B, R::Group);
+            walk.advance();
+            ++issued;
+            return;
+        }
         uint32_t koff = k_lane_off, voff = v_lane_off;
         asm volatile("" : "+v"(koff), "+v"(voff));          // keep the lane offsets 32-bit next to a scalar base
         char *stage = smem + kg * GROUP_B + (issued / UPS & 1) * STAGE_B;
@@ -507,7 +530,7 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
     const uint32_t group_addr = (uint32_t)(uintptr_t)smem + (uint32_t)(kg * GROUP_B);
     const uint32_t row_addr = R::address(group_addr, lane);
     uint32_t tr_addr[4];
-    L::transposed_addresses(group_addr + R::Tile, lane, tr_addr);
+    L::transposed_addresses(group_addr + V_AT, lane, tr_addr);
     bf16x8 Qr[NQ][KS];
 #pragma unroll
     for (int qb = 0; qb < NQ; ++qb)
@@ -543,6 +566,13 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
         else if (wave >= 4) __builtin_amdgcn_s_setprio(1);
     }
 
+    // ONEV: V of the unit has landed for everyone.  Every wave of the workgroup passes here once a step.
+    auto v_landed = [&]() __attribute__((always_inline)) {
+        if (more) wait_dma<L::Groups / QW>();               // the next unit's K may be on its way
+        else wait_dma<0>();
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
     constexpr int kPlain = 0, kFollow = 1, kFirst = 2, kCareful = 3;
     // One unit of 32 keys whose K begins at LDS offset OFF + at (relative to the group's first stage).
     auto unit_at = [&](auto track_c, auto off_c, uint32_t at, float grow_above) __attribute__((always_inline)) {
@@ -551,7 +581,7 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
         constexpr int TRACK = decltype(track_c)::value, OFF = decltype(off_c)::value;
         uint32_t tr_at[4];
 #pragma unroll
-        for (int m = 0; m < 4; ++m) tr_at[m] = tr_addr[m] + at;
+        for (int m = 0; m < 4; ++m) tr_at[m] = tr_addr[m] + (ONEV ? 0u : at);
         floatx4 S[2][NQ];                                   // [key block][query block]
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
@@ -624,8 +654,10 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
             }
         }
         StagedTransposedProduct<D, OFF> v_t;
-        v_t.prefetch(tr_at);
-        __builtin_amdgcn_sched_barrier(0);                  // the exponentials stay behind these reads
+        if constexpr (!ONEV) {
+            v_t.prefetch(tr_at);
+            __builtin_amdgcn_sched_barrier(0);              // the exponentials stay behind these reads
+        }
         // probabilities, rounded to bf16, packed as the B operand of the PV product of their query block
         bf16x8 Pb[NQ];
         typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -644,6 +676,12 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
                     Pb[qb][4 * kb + e] = pp[0];
                     Pb[qb][4 * kb + e + 1] = pp[1];
                 }
+        if constexpr (ONEV) {
+            __builtin_amdgcn_sched_barrier(0);
+            v_landed();
+            v_t.prefetch(tr_at);
+            __builtin_amdgcn_sched_barrier(0);
+        }
 #pragma unroll
         for (int qb = 0; qb < NQ; ++qb) l_acc[qb] = mfma_16x16x32(ones, Pb[qb], l_acc[qb]);       // sums the rounded values
         v_t.run(tr_at, Pb, Oacc);                           // O^T += V^T P^T
@@ -655,19 +693,25 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
         constexpr bool CAREFUL = decltype(careful_c)::value;
         constexpr int REST = CAREFUL ? kCareful : FOLLOW ? kFollow : kPlain;
         const float bound = FOLLOW || !CAREFUL ? 0.f : __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(8.0f / c)));
-        auto next_stage = [&]() __attribute__((always_inline)) {
+        auto next_stage = [&](int u) __attribute__((always_inline)) {
             // this wave's DMA for the stage must have landed, and everyone's; the other stage is free again
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             if constexpr (QW > 1) __builtin_amdgcn_s_barrier();          // the stages of a single wave are its own
             asm volatile("" ::: "memory");
+            if constexpr (ONEV) {
+                // V of this unit, whose place everyone has read; then the next K
+                if (u < n_units) issue_operand(vh, v_lane_off, v_row, smem + kg * GROUP_B + V_AT, L::Group);
+                more = issued < n_units;
+            }
             issue_next();
         };
         using Rest = std::integral_constant<int, REST>;
         using Stage0 = std::integral_constant<int, 0>;
         using Stage1 = std::integral_constant<int, STAGE_B>;
         auto stage_at = [&](auto first_c, auto stage_c, uint32_t at, int u) __attribute__((always_inline)) {
-            next_stage();
+            next_stage(u);
             if (KG == 1 || u < n_units) unit_at(first_c, stage_c, at, bound);
+            else if constexpr (ONEV) v_landed();
             if constexpr (UPS == 2) unit_at(Rest{}, std::integral_constant<int, decltype(stage_c)::value + UNIT_B>{}, at, bound);
         };
         if constexpr (!CAREFUL) stage_at(std::integral_constant<int, kFirst>{}, Stage0{}, 0u, 0);
@@ -681,7 +725,7 @@ void sta_fwd_group_kernel(const bf16_raw *__restrict__ q,
             }
         } else {
 #pragma unroll 1
-            for (int u = CAREFUL ? 0 : UPS; u < n_steps; u += UPS) stage_at(Rest{}, Stage0{}, (uint32_t)((u / UPS & 1) * STAGE_B), u);
+            for (int u = CAREFUL ? 0 : UPS; u < n_steps; u += UPS) stage_at(Rest{}, Stage0{}, (uint32_t)((u / UPS & 1) * K_STAGE_B), u);
         }
     };
     float l_tot[NQ];
@@ -1734,12 +1778,12 @@ hipError_t launch_x32(const FwdArgs &a)
     return hipGetLastError();
 }
 
-template <int D, int QW, int KG, int WPE, bool FOLLOW, int UPS = 1>
+template <int D, int QW, int KG, int WPE, bool FOLLOW, int UPS = 1, bool ONEV = false>
 hipError_t launch_group(const FwdArgs &a)
 {
     const sta::FwdPlan plan = make_plan(QW, a);
-    if (a.note) return a.note->add("group<%d,%d,%d,%d,%d> items %u", D, QW, KG, (int)FOLLOW, UPS, plan.deal.total);
-    sta_fwd_group_kernel<D, QW, KG, WPE, FOLLOW, UPS><<<dim3(plan.deal.total), dim3(QW * KG * 64), 0, a.stream>>>(
+    if (a.note) return a.note->add("%s<%d,%d,%d,%d,%d> items %u", ONEV ? "group_one_v" : "group", D, QW, KG, (int)FOLLOW, UPS, plan.deal.total);
+    sta_fwd_group_kernel<D, QW, KG, WPE, FOLLOW, UPS, ONEV><<<dim3(plan.deal.total), dim3(QW * KG * 64), 0, a.stream>>>(
         static_cast<const bf16_raw *>(a.q), static_cast<const bf16_raw *>(a.k), static_cast<const bf16_raw *>(a.v),
         static_cast<bf16_raw *>(a.o), a.p, plan);
     return hipGetLastError();
@@ -1848,13 +1892,26 @@ hipError_t launch_groups(const FwdArgs &a)
     }
     if (P % 64 == 0) {
         if constexpr (D == 128) {
-            // two groups also for one to one and a half rounds of long walks: half as many workgroups at once, each half as long
-            // (10x24x48 in 320-token tiles, 2x2x4, eight heads, 1.4 rounds, 300 units 566 -> 506 us; 10x40x40, eight, 1.95 rounds 214,
-            // 232; 64x64 at 5x5, 48, 6 rounds, 50 units 196, 210)
+            // Two stages of V, four of these workgroups a CU, or one stage, six (three with two groups).  One stage costs a second barrier
+            // a unit and waits for V; it pays by its places: more than a round of four, and two groups for up to three workgroups a CU (measured
+            // from 576 workgroups of one group on: 25.7, two 23.7).
+            // Not where the second round of four is nearly full ((1664) 51, 52; (1750) 372, 394; (1920) 54, 58), and where the walks of the
+            // heads differ, two groups of two stages for one to one and a half rounds, as the long walks are alone at the end (96x96, 18 heads
+            // of 18, 50 and 288 units 365, one stage 401; nine (by walks 576) 256, in two groups of one stage 194).  us, two stages, one, one and two groups; workgroups
+            // of one group in brackets: 64x64, 3x3 (640) 25.9, 26.0, 23.9; (768) 26.4, 26.3, 25.4; (1024) 29.6, 29.6, 33.1; (1280) 42.4, 37.6,
+            // 38.7; (1536) 50, 41, 44; (2048) 62, 59, 57; (3072) 86, 80, 87; 128x128, 5x5 (768) 57, 59, 53; (1280) 97, 85, 85; (1536) 113, 92, 98;
+            // (2048) 131, 138, 132; (2560) 169, 159, 161; (4096) 249, 242, 257; 10x40x40 in 320-token tiles (750) 168, 177, 156; (1500) 314, 288,
+            // 302; (2000) 388, 437, 400; (2500) 529, 488, 498; (4000) 765, 745, 779.
             const uint64_t blocks = waves / 2, places = 4 * cus;
-            if (P % 128 != 0)
-                return two || (units >= 64 && blocks > places && 2 * blocks <= 3 * places) ? launch_group<128, 2, 2, 2, true>(a)
-                           : launch_group<128, 2, 1, 2, true>(a);
+            if (P % 128 != 0) {
+                if (two) return launch_group<128, 2, 2, 2, true>(a);
+                if (4 * blocks >= 9 * cus && blocks <= 3 * cus && units >= 16) return launch_group<128, 2, 2, 3, true, 1, true>(a);
+                if (units >= 64 && units != walk_of_rank(a, p.heads - 1) && blocks > places && 2 * blocks <= 3 * places)
+                    return launch_group<128, 2, 2, 2, true>(a);
+                return blocks <= places || (5 * blocks > 8 * places && blocks <= 2 * places)
+                           ? launch_group<128, 2, 1, 2, true>(a)
+                           : launch_group<128, 2, 1, 3, true, 1, true>(a);
+            }
             if (4 * waves <= fits && units >= 32) return launch_group<128, 2, 4, 2, false>(a);
             return two ? launch_group<128, 2, 2, 2, false>(a)
                        : launch_group<128, 2, 1, 2, false>(a);
@@ -1867,6 +1924,10 @@ hipError_t launch_groups(const FwdArgs &a)
     // other multiples of 32 tokens: one wave of queries, whose LDS stages then limit a CU to four such workgroups at head
     // dimension 128, with or without key groups (525 waves: 59 us, two groups 74)
     if (D == 64 && two) return launch_group<64, 1, 2, 2, true>(a);
+    if constexpr (D == 128) {
+        // one stage of V here too: six waves a CU instead of four
+        if (waves > 8 * cus || (waves > 4 * cus && waves <= 6 * cus)) return launch_group<128, 1, 1, 2, true, 1, true>(a);
+    }
     return launch_group<D, 1, 1, D == 64 ? 3 : 1, true>(a);
 }
 

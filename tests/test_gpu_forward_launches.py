@@ -47,6 +47,13 @@ LAUNCHES = [
     ("shared-p96-d128-two", 128, (4, 18, 40), (2, 6, 8), 8, (1, 3, 3)),       # 720, 27
     ("shared-p96-d128-one", 128, (4, 18, 40), (2, 6, 8), 14, (1, 3, 3)),      # 1260
     ("shared-p32-d128", 128, (1, 16, 48), (1, 4, 8), 30, (1, 3, 5)),          # 720, 15
+    # one LDS stage of V: with two groups, one, one wave of queries; tiles of many units; short walks
+    ("one-v-p64-d128-two", 128, (1, 40, 56), (1, 8, 8), 18, (1, 3, 3)),       # 1260, 18
+    ("one-v-p64-d128-one", 128, (1, 40, 56), (1, 8, 8), 34, (1, 3, 3)),       # 2380
+    ("one-v-p320-d128", 128, (5, 24, 40), (5, 8, 8), 16, (1, 2, 3)),          # 2400, 90
+    ("one-v-p64-d128-short", 128, (1, 40, 56), (1, 8, 8), 34, (1, 1, 3)),     # 2380, 6
+    ("one-v-p32-d128", 128, (1, 16, 48), (1, 4, 8), 46, (1, 3, 5)),           # 1104, 15
+    ("one-v-p32-d128-short", 128, (1, 16, 48), (1, 4, 8), 46, (1, 1, 3)),     # 1104, 3
 ]
 
 
@@ -80,6 +87,11 @@ def test_launches_match_the_oracle(name, D, grid, tile, heads, window, kind):
         # weight (growing scores); the offset and the scores are fp32 numbers of the size of the result: 2^-22 of it
         want = ref_lse[order.numpy()]
         assert (np.abs(lse[0, h].cpu().numpy() - want) <= 2.0 ** -8 + 2.0 ** -22 * np.abs(want)).all()
+
+
+@pytest.mark.parametrize("name,grid,tile,heads", [("one-v-p64-d128", (1, 40, 56), (1, 8, 8), 34), ("one-v-p32-d128", (1, 16, 48), (1, 4, 8), 46)])
+def test_walks_of_one_tile_in_one_stage_of_v(name, grid, tile, heads):
+    test_launches_match_the_oracle(name + "-one-tile", 128, grid, tile, heads, (1, 1, 1), "plain")
 
 
 @pytest.mark.parametrize("D,grid,tile,window,groups", [(64, (1, 32, 32), (1, 8, 8), (1, 4, 4), 8), (128, (2, 32, 32), (2, 8, 8), (1, 4, 4), 8),
