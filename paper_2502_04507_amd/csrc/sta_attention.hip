@@ -873,8 +873,8 @@ void sta_fwd_solo_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restr
     constexpr int SLICES = CB * NQ;                         // 16x16 blocks of an accumulator, 1 KB each
     constexpr int UNIT_B = R::Tile + L::Tile;
     constexpr int REGION = UNIT_B > SLICES * 1024 ? UNIT_B : SLICES * 1024;    // LDS of a wave: K, then V; at the end its accumulators
-    constexpr int PER_WAVE = SLICES / KG;                   // of them that a wave merges
-    static_assert(SLICES % KG == 0 && PER_WAVE <= CB, "merge");
+    constexpr int PER_WAVE = SLICES > KG ? SLICES / KG : 1; // of them that a wave merges
+    static_assert((SLICES % KG == 0 || PER_WAVE == 1) && CB % PER_WAVE == 0, "merge");
     constexpr int STATS = KG * REGION;                      // offset and row sum of every group's queries
     constexpr int FLAGS = STATS + KG * QB * 8;
     constexpr int OUT = (FLAGS + KG * 4 + 15) / 16 * 16;
@@ -1053,7 +1053,8 @@ void sta_fwd_solo_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restr
     // factor common to a row's probabilities and its sum, which shows as an extreme row sum where it is extreme.)
     // Row sums and accumulators of this wave to LDS; what asks for the careful pass is as in the kernel above.
     constexpr float kRedoAbove = 79228162514264337593543950336.f, kRedoBelow = 5.42101086242752217e-20f;
-    constexpr uint32_t kRedoBits = KG > 4 ? 0x7d800000u : 0x7e000000u;      // 2^124, 2^125: the sum of all groups stays in range
+    // 2^123, 2^124, 2^125: the sum of all groups stays in range
+    constexpr uint32_t kRedoBits = KG > 8 ? 0x7d000000u : KG > 4 ? 0x7d800000u : 0x7e000000u;
     auto leave_partial = [&](bool careful) __attribute__((always_inline)) {
         float o_sum[4] = {0.f, 0.f, 0.f, 0.f};
         bool redo = false;
@@ -1092,32 +1093,34 @@ void sta_fwd_solo_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restr
 
     // ---- merge: every wave sums the groups' parts of its slices of the accumulators, in ascending order
     const int first = kg * PER_WAVE, qb = first / CB;
-    const float2 *stats = reinterpret_cast<const float2 *>(smem + STATS) + 16 * qb + c16;
-    float m = -INFINITY, l = 0.f, weight[KG];
+    if (SLICES >= KG || first < SLICES) {
+        const float2 *stats = reinterpret_cast<const float2 *>(smem + STATS) + 16 * qb + c16;
+        float m = -INFINITY, l = 0.f, weight[KG];
 #pragma unroll
-    for (int g = 0; g < KG; ++g) m = fmaxf(m, stats[g * QB].x);
-#pragma unroll
-    for (int g = 0; g < KG; ++g) {
-        weight[g] = __builtin_amdgcn_exp2f(stats[g * QB].x - m);
-        l += stats[g * QB].y * weight[g];
-    }
-    const float inv = 1.f / l;
-#pragma unroll
-    for (int j = 0; j < PER_WAVE; ++j) {
-        const int cb = first % CB + j;
-        floatx4 sum = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int g = 0; g < KG; ++g) m = fmaxf(m, stats[g * QB].x);
 #pragma unroll
         for (int g = 0; g < KG; ++g) {
-            const floatx4 x = *reinterpret_cast<const floatx4 *>(smem + g * REGION + (first + j) * 1024 + lane * 16);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) sum[r] = fmaf(x[r], weight[g], sum[r]);
+            weight[g] = __builtin_amdgcn_exp2f(stats[g * QB].x - m);
+            l += stats[g * QB].y * weight[g];
         }
-        bf16x4 ov;
+        const float inv = 1.f / l;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) ov[r] = static_cast<__bf16>(sum[r] * inv);
-        *reinterpret_cast<bf16x4 *>(smem + OUT + (16 * qb + c16) * L::RowB + (16 * cb + 4 * g4) * 2) = ov;
+        for (int j = 0; j < PER_WAVE; ++j) {
+            const int cb = first % CB + j;
+            floatx4 sum = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int g = 0; g < KG; ++g) {
+                const floatx4 x = *reinterpret_cast<const floatx4 *>(smem + g * REGION + (first + j) * 1024 + lane * 16);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) sum[r] = fmaf(x[r], weight[g], sum[r]);
+            }
+            bf16x4 ov;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) ov[r] = static_cast<__bf16>(sum[r] * inv);
+            *reinterpret_cast<bf16x4 *>(smem + OUT + (16 * qb + c16) * L::RowB + (16 * cb + 4 * g4) * 2) = ov;
+        }
+        if (p.lse != nullptr && first % CB == 0 && g4 == 0) p.lse[my_row + 16 * qb + c16] = m * 0.6931471805599453f + __logf(l);
     }
-    if (p.lse != nullptr && first % CB == 0 && g4 == 0) p.lse[my_row + 16 * qb + c16] = m * 0.6931471805599453f + __logf(l);
     __syncthreads();
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     char *out = reinterpret_cast<char *>(o + my_row * D);
@@ -1708,15 +1711,15 @@ struct FwdArgs {
     sta::LaunchNote *note;      // not null: the shape is written there and nothing is launched
 };
 
-// The plan of a launch of query blocks of 32 * waves queries.
-sta::FwdPlan make_plan(int waves, const FwdArgs &a)
+// The plan of a launch of blocks of that many queries.
+sta::FwdPlan make_plan(uint32_t queries, const FwdArgs &a)
 {
     const sta::FwdParams &p = a.p;
     sta::FwdPlan plan;
-    const uint32_t per_head = p.N / (waves * 32);
+    const uint32_t per_head = p.N / queries;
     plan.deal = sta::deal_of(per_head, (uint32_t)a.B * p.heads);
     plan.per_head = sta::fast_div_of(per_head);
-    plan.per_tile = sta::fast_div_of(p.P / (waves * 32));
+    plan.per_tile = sta::fast_div_of(p.P / queries);
     plan.pair_items = sta::fast_div_of(2 * p.n_w * p.n_t);
     plan.n_t = sta::fast_div_of(p.n_t);
     plan.batch = sta::fast_div_of((uint32_t)a.B);
@@ -1761,7 +1764,7 @@ hipError_t launch_x32(const FwdArgs &a)
 {
     constexpr int D = 128, QB = NW * 32;
     sta::FwdParams p = a.p;
-    const sta::FwdPlan plan = make_plan(NW, a);
+    const sta::FwdPlan plan = make_plan(QB, a);
     const uint32_t items = plan.deal.total, capacity = resident_workgroups(MINB);
     p.split_parts = parts_of_tail(a, items, capacity, QB);
     const uint32_t split_items = p.split_parts > 1 ? items % capacity : 0;
@@ -1781,7 +1784,7 @@ hipError_t launch_x32(const FwdArgs &a)
 template <int D, int QW, int KG, int WPE, bool FOLLOW, int UPS = 1, bool ONEV = false>
 hipError_t launch_group(const FwdArgs &a)
 {
-    const sta::FwdPlan plan = make_plan(QW, a);
+    const sta::FwdPlan plan = make_plan(32 * QW, a);
     if (a.note) return a.note->add("%s<%d,%d,%d,%d,%d> items %u", ONEV ? "group_one_v" : "group", D, QW, KG, (int)FOLLOW, UPS, plan.deal.total);
     sta_fwd_group_kernel<D, QW, KG, WPE, FOLLOW, UPS, ONEV><<<dim3(plan.deal.total), dim3(QW * KG * 64), 0, a.stream>>>(
         static_cast<const bf16_raw *>(a.q), static_cast<const bf16_raw *>(a.k), static_cast<const bf16_raw *>(a.v),
@@ -1792,9 +1795,9 @@ hipError_t launch_group(const FwdArgs &a)
 template <int D, int NQ, int KG, bool FOLLOW>
 hipError_t launch_solo(const FwdArgs &a)
 {
-    const sta::FwdPlan plan = make_plan(NQ / 2, a);
+    const sta::FwdPlan plan = make_plan(16 * NQ, a);
     if (a.note) return a.note->add("solo<%d,%d,%d,%d> items %u", D, NQ, KG, (int)FOLLOW, plan.deal.total);
-    sta_fwd_solo_kernel<D, NQ, KG, D == 64 && NQ == 2 ? 4 : 2, FOLLOW><<<dim3(plan.deal.total), dim3(KG * 64), 0, a.stream>>>(
+    sta_fwd_solo_kernel<D, NQ, KG, D == 64 && NQ < 4 ? 6 - NQ : 2, FOLLOW><<<dim3(plan.deal.total), dim3(KG * 64), 0, a.stream>>>(
         static_cast<const bf16_raw *>(a.q), static_cast<const bf16_raw *>(a.k), static_cast<const bf16_raw *>(a.v),
         static_cast<bf16_raw *>(a.o), a.p, plan);
     return hipGetLastError();
@@ -1866,6 +1869,11 @@ hipError_t launch_groups(const FwdArgs &a)
                      : launch_solo<D, 2, 4, true>(a);
     }
     if constexpr (D == 64) {
+        // 48 queries for twelve waves where that gives no CU two workgroups and 64 would leave a third of the chip without one.  us, 64
+        // queries for eight waves against these, waves and units in brackets: (324, 108) 19.6, 17.5; (360, 108) 19.0, 16.6; (324, 324)
+        // 40.5, 36.2; (360, 360) 43.5, 40.5; 192-token tiles (300, 54) 13.1, 12.2; not measured below that.  (Sixteen waves for 32 queries up to 256 waves: 1.0
+        // to 1.5 us slower than eight, at 36 to 128 units.)
+        if (P % 192 == 0 && 8 * waves > 9 * cus && 2 * waves <= 3 * cus && units >= 48) return launch_solo<64, 3, 12, false>(a);
         if (P % 64 == 0 && waves <= 2 * cus)
             return units >= 48 ? launch_solo<64, 4, 8, false>(a)
                                : launch_solo<64, 2, 4, false>(a);

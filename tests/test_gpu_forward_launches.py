@@ -47,6 +47,9 @@ LAUNCHES = [
     ("shared-p96-d128-two", 128, (4, 18, 40), (2, 6, 8), 8, (1, 3, 3)),       # 720, 27
     ("shared-p96-d128-one", 128, (4, 18, 40), (2, 6, 8), 14, (1, 3, 3)),      # 1260
     ("shared-p32-d128", 128, (1, 16, 48), (1, 4, 8), 30, (1, 3, 5)),          # 720, 15
+    # 48 queries shared by twelve waves
+    ("own-p384-48q-12", 64, (6, 24, 24), (6, 8, 8), 3, (1, 3, 3)),            # 324, 108
+    ("own-p192-48q-12", 64, (3, 24, 40), (3, 8, 8), 4, (1, 3, 3)),            # 360, 54
     # one LDS stage of V: with two groups, one, one wave of queries; tiles of many units; short walks
     ("one-v-p64-d128-two", 128, (1, 40, 56), (1, 8, 8), 18, (1, 3, 3)),       # 1260, 18
     ("one-v-p64-d128-one", 128, (1, 40, 56), (1, 8, 8), 34, (1, 3, 3)),       # 2380
@@ -95,9 +98,9 @@ def test_walks_of_one_tile_in_one_stage_of_v(name, grid, tile, heads):
 
 
 @pytest.mark.parametrize("D,grid,tile,window,groups", [(64, (1, 32, 32), (1, 8, 8), (1, 4, 4), 8), (128, (2, 32, 32), (2, 8, 8), (1, 4, 4), 8),
-                                                       (64, (1, 16, 48), (1, 8, 8), (1, 2, 3), 4)])
+                                                       (64, (1, 16, 48), (1, 8, 8), (1, 2, 3), 4), (64, (6, 32, 48), (3, 8, 8), (2, 4, 6), 12)])
 def test_accumulators_that_only_their_merge_would_take_out_of_range(D, grid, tile, window, groups):
-    """Up to eight key shares, each a quarter of the range's end with the offset of its first keys: the first 32 keys of every
+    """Up to twelve key shares, each a quarter of the range's end with the offset of its first keys: the first 32 keys of every
     tile are zero, the others exceed them by 2^79 or so, under V = 2^b everywhere."""
     w = syn.custom("merge-range-8", 1, 1, D, grid, tile, [window], "bf16", seed=1)
     unit_of_key = torch.arange(w.N) % w.P // 32

@@ -100,6 +100,7 @@ FORWARD = {
     "shared-p384-d128-two": "group<128,2,2,0,1>", "shared-p384-d128-one": "group<128,2,1,0,1>",
     "shared-p64-d128-two": "group<128,2,2,1,1>", "shared-p64-d128-one": "group<128,2,1,1,1>",
     "shared-p96-d128-two": "group<128,3,2,1,1>", "shared-p96-d128-one": "group<128,3,1,1,1>", "shared-p32-d128": "group<128,1,1,1,1>",
+    "own-p384-48q-12": "solo<64,3,12,0>", "own-p192-48q-12": "solo<64,3,12,0>",
     "one-v-p64-d128-two": "group_one_v<128,2,2,1,1>", "one-v-p64-d128-one": "group_one_v<128,2,1,1,1>",
     "one-v-p320-d128": "group_one_v<128,2,1,1,1>", "one-v-p64-d128-short": "group_one_v<128,2,1,1,1>",
     "one-v-p32-d128": "group_one_v<128,1,1,1,1>", "one-v-p32-d128-short": "group_one_v<128,1,1,1,1>",
