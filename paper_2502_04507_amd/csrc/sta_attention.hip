@@ -395,16 +395,18 @@ __device__ __forceinline__ GroupItem group_item_of(uint32_t id, const sta::FwdPa
 // (g4 = lane >> 4); a wave's 32 queries are two blocks of 16 and every K and V fragment read from LDS feeds both.  The
 // score accumulators start at minus the exponent offset (Sinit).  Row sums are a matrix product too, with an operand of
 // ones: v_dot2_f32_bf16 runs on the matrix pipe as well and eight of them take longer than the two matrix instructions.
-// The LDS layouts (Staged for V, StagedRows for K) leave five operand addresses per wave, to which the stage is added.
+// The LDS layouts (Staged for V, StagedRows for K) leave five operand addresses per wave; the stage is part of the read instructions
+// where the loop is unrolled over the stages (the offset stays), an addition to each address otherwise.
 //
-// What bounds it.  Head dimension 64: a unit (32 keys) is 18 matrix instructions (288 cycles of the matrix pipe) next to 49
-// vector instructions, 16 of them exponentials; measured 350 cycles per wave and unit on 64-token image tiles with four
-// waves per SIMD.  Matrix pipe busy 63 % of the cycles on the 30x48x80 grid (24 heads, 384-token tiles, window 3x3x3), 39 % on
-// 128 heads of a 64x64 image in 8x8 tiles (18 units per item: a third of the launch remains without DMA and arithmetic), 13 % on
-// one head of 18x24x24 (162 workgroups); LDS bank conflicts only where the results leave (16 to 64 per wave).
+// What bounds it.  Head dimension 64: the vector issue port.  A unit (32 keys) is 18 matrix instructions (288 cycles of the matrix
+// pipe, 8 of the port each) next to 41 vector instructions, 16 of them exponentials (9 cycles; the others 4): 205 ns a SIMD and unit for the
+// instructions alone, at 1.8 to 2.1 GHz, measured 230 on the 30x48x80 grid (24 heads, 384-token tiles, window 3x3x3), where the matrix pipe is
+// busy 68 % of the cycles.  Seven vector instructions more (the stage in the addresses, the operand of ones made in every unit) made that
+// 239.  41 % on 128 heads of a 64x64 image in 8x8 tiles (18 units per item, 78 % of an item's cycles; 99 -> 96 us); LDS bank
+// conflicts only where the results leave (16 to 64 per wave).
 // The grid: 6.97-7.15 ms with the 12-wave kernel on v_mfma_f32_32x32x16_bf16 that was here before, 6.68-6.83 with QW = 4
 // (QW = 12: 7.5, QW = 2: 7.3; row sums by v_dot2: 7.2), 6.53-6.63 with two units per stage (UPS, 64 keys per barrier).  The
-// images: 105-109 us before, 98-100.  Head dimension 128, 96-token tiles (10x30x56, 10 slices, windows 3x3x3 and 2x4x3): 2390 us
+// images: 105-109 us before, 98-100.  (Figures from before the loop was unrolled: 6.94 -> 6.69 ms a layer since.)  Head dimension 128, 96-token tiles (10x30x56, 10 slices, windows 3x3x3 and 2x4x3): 2390 us
 // with the register-staged kernel that served it before, 294-299 us, 290 since a move of the offset touches no score (below).
 // FOLLOW: the offset is the running maximum in every unit.  Otherwise it is the maximum of an item's first unit, and the
 // largest probabilities of a row are rounded to bf16 like any other; at the running maximum the largest is exactly 1 and has
@@ -413,6 +415,10 @@ __device__ __forceinline__ GroupItem group_item_of(uint32_t id, const sta::FwdPa
 // (260 -> 299 us; 290 with the offset in the exponent's fused multiply-add, which also ended the spills of the three-wave shapes at
 // head dimension 128, 12 to 32 bytes; 24 slices, 1x3x3 229 -> 222, 30 of head dimension 64 420 -> 411), so it is done on the tiles whose kernel has always done it: no multiple of 128 tokens at head dimension
 // 128, of 64 at 64.
+// ONEV: two stages of K and one of V, for 26 KB of LDS a group at head dimension 128 instead of 34.  A step is: K of the unit has landed
+// (barrier); V of the unit is requested, and K of the next; scores and exponentials; V has landed (barrier); its product.  The first barrier
+// comes when everyone has read the V before, the second when everyone has read the K before.  Six workgroups of two waves a CU, three waves
+// a SIMD, where two stages allow four; the rule and both sides are at launch_groups.
 // A third LDS stage (DMA two units ahead, waited for by count behind a bare s_barrier, which __syncthreads() does not
 // allow: it waits for every outstanding DMA) changes nothing at four waves per SIMD and costs occupancy on small tiles:
 // 6.77 against 6.73 ms, 108 against 98 us.
