@@ -400,9 +400,9 @@ __device__ __forceinline__ GroupItem group_item_of(uint32_t id, const sta::FwdPa
 //
 // What bounds it.  Head dimension 64: the vector issue port.  A unit (32 keys) is 18 matrix instructions (288 cycles of the matrix
 // pipe, 8 of the port each) next to 41 vector instructions, 16 of them exponentials (9 cycles; the others 4): 205 ns a SIMD and unit for the
-// instructions alone, at 1.8 to 2.1 GHz, measured 230 on the 30x48x80 grid (24 heads, 384-token tiles, window 3x3x3), where the matrix pipe is
+// instructions alone, at 1.8 to 2.1 GHz, measured 233 on the 30x48x80 grid (24 heads, 384-token tiles, window 3x3x3), where the matrix pipe is
 // busy 68 % of the cycles.  Seven vector instructions more (the stage in the addresses, the operand of ones made in every unit) made that
-// 239.  41 % on 128 heads of a 64x64 image in 8x8 tiles (18 units per item, 78 % of an item's cycles; 99 -> 96 us); LDS bank
+// 243.  41 % on 128 heads of a 64x64 image in 8x8 tiles (18 units per item, 78 % of an item's cycles; 99 -> 96 us); LDS bank
 // conflicts only where the results leave (16 to 64 per wave).
 // The grid: 6.97-7.15 ms with the 12-wave kernel on v_mfma_f32_32x32x16_bf16 that was here before, 6.68-6.83 with QW = 4
 // (QW = 12: 7.5, QW = 2: 7.3; row sums by v_dot2: 7.2), 6.53-6.63 with two units per stage (UPS, 64 keys per barrier).  The
@@ -2026,13 +2026,19 @@ hipError_t launch_forward(const void *q, const void *k, const void *v, void *o, 
     if (p.P % 128 != 0) return launch_groups<128>(a);
     // Tiles of 128 tokens' multiples.  Up to 1280 waves of 32 queries (the chip holds 2048 of the key-group kernel's at this
     // head dimension) the key-group kernel: more and smaller workgroups, and key groups that need no workspace.  Where one is
-    // given, items cut into parts come close on long walks, and only launches of up to 256 waves or walks of up to 80 units
-    // change over.  Measured in us, 12-wave or 4-wave kernel without a workspace, with one, key groups; waves, units:
+    // given, items cut into parts are ahead on long walks: then up to 256 waves, up to 512 (four groups) at up to 240 units, up to 1024
+    // (two) at up to 128, and any number here at up to 80.  us, parts and key groups; waves, units: 384-token tiles (324, 108) 44.4, 34.4;
+    // (432, 108) 47.1, 35.4; (360, 180) 57.0, 51.9; (384, 192) 59.4, 55.2; (432, 216) 65.6, 62.7; (384, 384) 89, 103; (648, 108) 53.8, 52.6;
+    // (864, 108) 63.2, 58.7; (576, 192) 72, 85; (960, 192) 101, 105; (1080, 108) 76, 81; 256-token tiles (384, 128) 50.3, 39.6; (400, 200)
+    // 63.1, 57.9; (768, 128) 67, 65; (1024, 128) 82, 75; (648, 216) 91, 98; 128-token tiles (480, 108) 48.7, 36.4; (480, 180) 64.5, 55.9; (480,
+    // 480) 132, 137; (960, 108) 70.2, 62.4; (720, 144) 71, 72; (576, 200) 77, 91.
+    // Measured in us, 12-wave or 4-wave kernel without a workspace, with one, key groups; waves, units:
     // 6x16x24 in 384-token tiles, one head (72, 72) 79, 37, 26; 12x48x48, one head (864, 108) 116, 68, 57; 2x40x40 in 128-token
     // tiles, one head (100, 36) 27, 26, 17, twelve (1200, 36) 37, 54, 34; 16x8x40 in 128-token tiles, four heads (640, 120) 76,
     // 64, 58, eight (1280, 120) 102, 104, 99; 12x32x40 in 256-token tiles, four heads (1920, 216) 255, 255, 280.
     const uint64_t cus = compute_units(), slices = (uint64_t)B * p.heads, waves = slices * (p.N / 32);
-    if (waves <= 5 * cus && (split_ws == nullptr || waves <= cus || longest_walk(a) <= 80))
+    const uint32_t units = longest_walk(a);
+    if (waves <= 5 * cus && (split_ws == nullptr || units <= 80 || waves <= cus || (waves <= 2 * cus && units <= 240) || (waves <= 4 * cus && units <= 128)))
         return launch_groups<128>(a);
     // A tile of 384 tokens (the paper's 6x8x8) gets one 12-wave workgroup per query tile: every K/V sub-block
     // fetched from L2 then serves 384 queries instead of 128.  Measured at the 115,200-token layer, window
