@@ -1077,7 +1077,9 @@ hipError_t launch_dkv_pairs(const BwdArgs &a)
 // head dimension 128: clip x 12 695 against 772, full x 8 1613 against 1726).  Two walk groups where the launch then still fits
 // the chip (8 waves per CU at head dimension 128, 12 at 64); one against two at 128: clip x 1 (864 waves) 128, 121, full x 1
 // (576) 390, 308, image x 2 (256) 18.1, 15.0, image x 8 (1024) 24.5, 22.7, clip x 2 (1728) 141, 160; at 64: image x 8 (1024)
-// 16.8, 14.2, image x 16 (2048) 21.1, 23.4.  Four groups of one wave, without barriers, up to one such workgroup per CU
+// 16.8, 14.2, image x 16 (2048) 21.1, 23.4; but walks of 32 and more on tiles of odd multiples of 64, whose one group has two waves as well,
+// up to the 16 that a CU holds (entry point, waves and units: (1664, 50) 104, 98, (2048, 50) 117, 110, (2000, 90) 199, 184; the other tiles,
+// of four and three waves a group, -1 to +1 %).  Four groups of one wave, without barriers, up to one such workgroup per CU
 // (two on 96-token tiles at head dimension 64); entry point, two groups of two or three waves against these: 12x24x24 in
 // 384-token tiles, one head (216 waves) of 64 100, 87, of 128 151, 131, two (432) 107, 110; 64x64 image, 5x5, one head (128) of 128 149,
 // 140, three (384) 150, 157; 4x12x24 in 96-token tiles, one head (36) of 64 39.5, 31.2, of 128 59.6, 47.3; twelve (432) 40.6, 35.4
@@ -1087,7 +1089,9 @@ hipError_t dispatch_dq(const BwdArgs &a)
 {
     const uint64_t waves = (uint64_t)a.B * a.p.heads * (a.p.N / 32), fits = (uint64_t)sta::compute_units() * (D == 128 ? 8 : 12);
     const uint32_t P = a.p.P;
-    const bool two = 2 * waves <= fits && longest_walk(a) >= 16;
+    const uint32_t units = longest_walk(a);
+    const bool two_for_64 = D == 64 && P % 64 == 0 && P % 128 != 0 && P % 96 != 0 && units >= 32;
+    const bool two = 2 * waves <= (two_for_64 ? 16 * (uint64_t)sta::compute_units() : fits) && units >= 16;
     if (P % 128 != 0 && !(sta::dma_aligned(a.k) && sta::dma_aligned(a.v))) return launch_dq<D, 1, 1, false>(a);
     const uint64_t cus = sta::compute_units();
     if (waves <= (D == 64 && P % 96 == 0 && P % 128 != 0 ? 2 * cus : cus)) return launch_dq<D, 1, 4>(a);
