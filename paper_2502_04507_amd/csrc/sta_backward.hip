@@ -1090,10 +1090,24 @@ hipError_t dispatch_dq(const BwdArgs &a)
     const uint64_t waves = (uint64_t)a.B * a.p.heads * (a.p.N / 32), fits = (uint64_t)sta::compute_units() * (D == 128 ? 8 : 12);
     const uint32_t P = a.p.P;
     const uint32_t units = longest_walk(a);
-    const bool two_for_64 = D == 64 && P % 64 == 0 && P % 128 != 0 && P % 96 != 0 && units >= 32;
-    const bool two = 2 * waves <= (two_for_64 ? 16 * (uint64_t)sta::compute_units() : fits) && units >= 16;
-    if (P % 128 != 0 && !(sta::dma_aligned(a.k) && sta::dma_aligned(a.v))) return launch_dq<D, 1, 1, false>(a);
     const uint64_t cus = sta::compute_units();
+    const bool two_for_64 = D == 64 && P % 64 == 0 && P % 128 != 0 && P % 96 != 0 && units >= 32;
+    const uint64_t places = two_for_64 ? 16 * cus : fits;
+    bool two = 2 * waves <= places && units >= 16;
+    // Where the walks of the heads differ, the long ones are alone at the end, and two groups halve them: where the longest is 1.8 times a
+    // place's share of all walks or more (entry point, us, by the number of waves and so; head dimension 64: 96x96 in 64-token tiles, nine
+    // heads of 288, 18 and 6 sub-blocks 342, 270; 12x48x48 in 384-token tiles, four of 36, 108, 12 and 864 1270, 971 (with dK/dV below);
+    // 8x40x48 in 128-token tiles, six of 480, 36 and 12 487, 438; 128: the same nine 540, 442; the same six 780, 750; 12x32x32 in
+    // 256-token tiles, four of 384 and 72 594, 558).  A CU holds six waves of the shapes of three at head dimension 128 (9x40x40, six heads of 162, 18
+    // and 6, 2.0 times in eighths, 1.5 in sixths 467, 480).
+    if (units >= 64 && units != walk_of_rank(a, a.p.heads - 1)) {
+        uint64_t all = 0;
+        for (uint32_t r = 0; r < a.p.heads; ++r) all += walk_of_rank(a, r);
+        all *= (uint64_t)a.B * (a.p.N / 32);
+        const uint64_t held = D == 128 && P % 96 == 0 && P % 128 != 0 ? 6 * cus : places;
+        two = 18 * all <= 10 * held * units;
+    }
+    if (P % 128 != 0 && !(sta::dma_aligned(a.k) && sta::dma_aligned(a.v))) return launch_dq<D, 1, 1, false>(a);
     if (waves <= (D == 64 && P % 96 == 0 && P % 128 != 0 ? 2 * cus : cus)) return launch_dq<D, 1, 4>(a);
     if (P % 96 == 0 && P % 128 != 0) return two ? launch_dq<D, 3, 2>(a) : launch_dq<D, 3, 1>(a);
     if (P % 64 != 0) return launch_dq<D, 1, 1>(a);
@@ -1133,7 +1147,7 @@ hipError_t dispatch_dkv(const BwdArgs &a)
         else return P % 96 == 0 ? launch_dkv<64, 3, 1>(a) : waves <= 4 * cus ? launch_dkv<64, 1, 2>(a) : launch_dkv<64, 1, 1>(a);
     }
     uint64_t by_walk = waves;                           // waves, those of a head with half the longest walk counted half
-    if constexpr (D == 128) {
+    if (D == 128 || units >= 64) {
         uint64_t all_units = 0;
         for (uint32_t r = 0; r < a.p.heads; ++r) all_units += walk_of_rank(a, r);
         by_walk = (uint64_t)a.B * (a.p.N / 32) * all_units / units;
@@ -1161,7 +1175,9 @@ hipError_t dispatch_dkv(const BwdArgs &a)
         const bool small = units < 32 ? by_walk <= 8 * cus : units < 48 && 2 * waves <= 13 * cus;
         if (P % 128 != 0 && waves > 4 * cus && small && (longest < 32 || 30 * cus * longest <= 11 * all)) return launch_dkv_pairs<2, 1>(a);
     }
-    if (P % 128 == 0) return waves <= (P == 128 ? 24 : 6) * cus ? launch_dkv<D, 2, 2>(a) : launch_dkv<D, 4, 1, D == 64 ? 2 : 1>(a);
+    // (at head dimension 64 by their walks: 12x32x32 in 384-token tiles, six heads of 384, 108 and 36 411, 365; 12x48x48, four of 36, 108, 12
+    // and 864 1260, 1113)
+    if (P % 128 == 0) return (D == 64 ? by_walk : waves) <= (P == 128 ? 24 : 6) * cus ? launch_dkv<D, 2, 2>(a) : launch_dkv<D, 4, 1, D == 64 ? 2 : 1>(a);
     return by_walk <= 8 * cus || (units >= 32 && (D == 64 || waves <= 32 * cus)) ? launch_dkv<D, 2, 2>(a) : launch_dkv<D, 2, 1>(a);
 }
 

@@ -86,6 +86,19 @@ def test_launches_of_a_round_or_so_go_by_the_longest_walk_of_a_key_tile(H, grid,
     assert launches(1, H, 128, grid, (6, 8, 8), [window], gradients=True)[1].startswith(want + " ")
 
 
+@pytest.mark.parametrize("D,H,grid,tile,windows,want", [
+    (64, 9, (1, 96, 96), (1, 8, 8), [(1, 12, 12), (1, 3, 3), (1, 1, 3)], "dq<64,2,2,1> dkv<64,2,2,1,1>"),      # longest 3.4 times a place's share
+    (128, 9, (1, 96, 96), (1, 8, 8), [(1, 12, 12), (1, 3, 3), (1, 1, 3)], "dq<128,2,2,1> dkv<128,2,2,1,1>"),   # 2.2
+    (64, 4, (12, 48, 48), (6, 8, 8), [(1, 1, 3), (1, 3, 3), (1, 1, 1), (2, 6, 6)], "dq<64,2,2,1> dkv<64,2,2,1,1>"),    # 3.0; by walks 1020 waves
+    (64, 8, (12, 48, 48), (6, 8, 8), [(1, 1, 3), (1, 3, 3), (1, 1, 1), (2, 6, 6)], "dq<64,4,1,1> dkv<64,4,1,2,1>"),    # 1.5; 2040
+    (128, 6, (9, 40, 40), (3, 8, 8), [(3, 3, 3), (1, 1, 3), (1, 1, 1)], "dq<128,3,1,1> dkv<128,2,2,1,1>"),     # 1.5 of six waves a CU
+    (64, 16, (1, 64, 64), (1, 8, 8), [(1, 5, 5)], "dq<64,2,2,1> dkv<64,1,4,1,1>"),                             # 2048 equal walks of 50
+    (64, 16, (1, 64, 64), (1, 8, 8), [(1, 3, 3)], "dq<64,2,1,1> dkv<64,2,2,1,1>"),                             # of 18
+])
+def test_long_walks_among_short_ones_are_halved_in_the_gradients(D, H, grid, tile, windows, want):
+    assert kernels(launches(1, H, D, grid, tile, windows, gradients=True)) == want.split(" ")
+
+
 # The kernels that the cases of tests/test_gpu_forward_launches.py and test_gpu_backward_launches.py run: a rule that sends one of
 # them elsewhere leaves its kernel without those tests.
 FORWARD = {
