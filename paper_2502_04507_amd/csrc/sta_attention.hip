@@ -1737,6 +1737,29 @@ sta::FwdPlan make_plan(uint32_t queries, const FwdArgs &a)
     return plan;
 }
 
+// Units (32 keys) of the walk of a head of the launch; heads by rank, the one with the most key tiles first.
+uint32_t walk_of_rank(const FwdArgs &a, uint32_t rank)
+{
+    const sta::FwdParams &p = a.p;
+    uint32_t units = p.P / kSub;
+    const uint32_t n[3] = {p.n_t, p.n_h, p.n_w};
+    for (int i = 0; i < 3; ++i) {
+        const uint32_t kept = 2 * (a.win.w[a.order.h[rank]][i] / 2u) + 1;
+        units *= kept < n[i] ? kept : n[i];
+    }
+    return units;
+}
+uint32_t longest_walk(const FwdArgs &a) { return walk_of_rank(a, 0); }
+
+// Where the walks of the heads differ and the longest is more than 1.4 times an even share of all of the launch's items on so many places
+// (the cases at its uses are at 1.45, 1.5 and 3.0): the long ones are what the launch waits for, and its last items, the short ones, are not.
+bool waits_for_long_walks(const FwdArgs &a, uint64_t items, uint64_t places)
+{
+    uint64_t all = 0;
+    for (uint32_t r = 0; r < a.p.heads; ++r) all += walk_of_rank(a, r);
+    return all != (uint64_t)a.p.heads * longest_walk(a) && 5 * (uint64_t)longest_walk(a) * places * a.p.heads > 7 * all * items;
+}
+
 // Items of qb queries beyond the last full round of workgroups are cut into parts that fill the chip once: how many parts
 // each of them gets, 1 where they are left whole (no workspace, more than half a round, walks too short).  They are the last ids,
 // all of which name an item, so that the parts never need more than one resident set of the workspace.  (While ids without an
@@ -1748,6 +1771,8 @@ uint32_t parts_of_tail(const FwdArgs &a, uint32_t items, uint32_t capacity, int 
     const sta::FwdParams &p = a.p;
     const uint32_t tail = items % capacity;
     if (a.split_ws == nullptr || tail == 0 || 2 * tail > capacity) return 1;
+    // (12x32x32 in 384-token tiles, twelve heads of 108, 384 and 36 units, 394 us in parts, 367 whole)
+    if (items > capacity && waits_for_long_walks(a, items, capacity)) return 1;
     uint32_t parts = capacity / tail;
     // a part should keep at least four sub-blocks of the cheapest item of the launch
     uint32_t min_tiles = 0xffffffffu;
@@ -1808,20 +1833,6 @@ hipError_t launch_solo(const FwdArgs &a)
         static_cast<bf16_raw *>(a.o), a.p, plan);
     return hipGetLastError();
 }
-
-// Units (32 keys) of the walk of a head of the launch; heads by rank, the one with the most key tiles first.
-uint32_t walk_of_rank(const FwdArgs &a, uint32_t rank)
-{
-    const sta::FwdParams &p = a.p;
-    uint32_t units = p.P / kSub;
-    const uint32_t n[3] = {p.n_t, p.n_h, p.n_w};
-    for (int i = 0; i < 3; ++i) {
-        const uint32_t kept = 2 * (a.win.w[a.order.h[rank]][i] / 2u) + 1;
-        units *= kept < n[i] ? kept : n[i];
-    }
-    return units;
-}
-uint32_t longest_walk(const FwdArgs &a) { return walk_of_rank(a, 0); }
 
 // Shape of the kernel for a launch.
 // Small launches, solo: in waves of 32 queries (counted as for the key groups below) and units of the longest walk; us, key-group
@@ -2047,8 +2058,10 @@ hipError_t launch_forward(const void *q, const void *k, const void *v, void *o, 
     // 1x3x3, us, 12 waves against 4, rounds in brackets: two heads (0.56) 117, 97; three (0.84) 126, 141; four (1.13) 244, 194 and with
     // parts 180, 184; six (1.69) 237, 262; eight (2.25) 355, 315; eleven (3.09) 477, 436; twelve (3.38) 486, 487; thirteen (3.66) 500, 498;
     // 6x48x48, eleven (1.55) 233, 223; twelve (1.69) 235, 258; 18x48x48, 3x3x3, five (2.11) 1009, 885; six (2.53) 1013, 1011).
+    // Nor where the launch waits for long walks, which the smaller workgroups spread over three times as many CUs (12x48x48, heads of 36,
+    // 108, 12 and 864 units, four 803, 482; eight 830, 775).
     const uint64_t items = slices * (p.N / 384), rounds = (items + cus - 1) / cus;
-    if (p.P % 384 == 0 && (parts_of_tail(a, (uint32_t)items, (uint32_t)cus, 384) > 1 || 5 * items >= 4 * rounds * cus))
+    if (p.P % 384 == 0 && !waits_for_long_walks(a, items, cus) && (parts_of_tail(a, (uint32_t)items, (uint32_t)cus, 384) > 1 || 5 * items >= 4 * rounds * cus))
         return launch_x32<12, 32, 2, 1>(a);
     return launch_x32<4, 32, 2, 3>(a);
 }
