@@ -1886,11 +1886,14 @@ hipError_t launch_groups(const FwdArgs &a)
                      : launch_solo<D, 2, 4, true>(a);
     }
     if constexpr (D == 64) {
-        // 48 queries for twelve waves where that gives no CU two workgroups and 64 would leave a third of the chip without one.  us, 64
-        // queries for eight waves against these, waves and units in brackets: (324, 108) 19.6, 17.5; (360, 108) 19.0, 16.6; (324, 324)
-        // 40.5, 36.2; (360, 360) 43.5, 40.5; 192-token tiles (300, 54) 13.1, 12.2; not measured below that.  (Sixteen waves for 32 queries up to 256 waves: 1.0
-        // to 1.5 us slower than eight, at 36 to 128 units.)
-        if (P % 192 == 0 && 8 * waves > 9 * cus && 2 * waves <= 3 * cus && units >= 48) return launch_solo<64, 3, 12, false>(a);
+        // 48 queries for twelve waves where that gives no CU two workgroups (of the workgroups there are, whatever their walks: the LDS holds
+        // one at a time) and 64 would leave a third of the chip without one.  us, 64 queries for eight waves against these, waves and units
+        // in brackets: (324, 108) 19.6, 17.5; (360, 108) 19.0, 16.6; (324, 324) 40.5, 36.2; (360, 360) 43.5, 40.5; 192-token tiles (300, 54)
+        // 13.1, 12.2; not measured below that.  Heads of different walks, more waves than 384 that count fewer: (594, 66 and 18) 16.9, 20.0;
+        // (768, 120, 24 and 6) 19.5, 22.1; (576, 192 to 36) 28.4, 30.6.  (Sixteen waves for 32 queries up to 256 waves: 1.0 to 1.5 us slower
+        // than eight, at 36 to 128 units.)
+        const uint64_t all_waves = (uint64_t)a.B * p.heads * (p.N / 32);
+        if (P % 192 == 0 && 8 * waves > 9 * cus && 2 * all_waves <= 3 * cus && units >= 48) return launch_solo<64, 3, 12, false>(a);
         if (P % 64 == 0 && waves <= 2 * cus)
             return units >= 48 ? launch_solo<64, 4, 8, false>(a)
                                : launch_solo<64, 2, 4, false>(a);

@@ -99,6 +99,17 @@ def test_long_walks_among_short_ones_are_halved_in_the_gradients(D, H, grid, til
     assert kernels(launches(1, H, D, grid, tile, windows, gradients=True)) == want.split(" ")
 
 
+@pytest.mark.parametrize("H,grid,tile,windows,want", [
+    (1, (18, 24, 24), (6, 8, 8), [(1, 3, 3)], "solo<64,3,12,0> items 216"),
+    (6, (18, 8, 16), (6, 8, 8), [(3, 1, 2)] * 3 + [(3, 1, 1)] + [(1, 1, 2)] * 2, "solo<64,4,8,0> items 216"),      # 432, by their walks 360
+    (2, (3, 40, 48), (3, 8, 8), [(1, 5, 5), (1, 3, 3)], "solo<64,3,12,0> items 240"),              # 360 waves of 150 and 54 units
+    (3, (12, 16, 32), (6, 8, 8), [(2, 2, 4), (2, 2, 3), (1, 1, 3)], "solo<64,4,8,0> items 288"),   # 576, by their walks 384
+    (25, (3, 40, 48), (3, 8, 8), [(1, 5, 6)] + [(1, 1, 1)] * 24, "solo<64,4,8,0> items 2250"),     # 4500, by their walks 360
+])
+def test_twelve_waves_for_48_queries_where_no_cu_gets_two_workgroups(H, grid, tile, windows, want):
+    assert launches(1, H, 64, grid, tile, windows) == [want]
+
+
 # The kernels that the cases of tests/test_gpu_forward_launches.py and test_gpu_backward_launches.py run: a rule that sends one of
 # them elsewhere leaves its kernel without those tests.
 FORWARD = {
