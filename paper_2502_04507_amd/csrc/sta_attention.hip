@@ -2057,14 +2057,16 @@ hipError_t launch_forward(const void *q, const void *k, const void *v, void *o, 
     // A tile of 384 tokens (the paper's 6x8x8) gets one 12-wave workgroup per query tile: every K/V sub-block
     // fetched from L2 then serves 384 queries instead of 128.  Measured at the 115,200-token layer, window
     // 3x3x3: 12.8-13.1 ms against 13.6-13.7 ms for the 4-wave shape in the same session.  Not where the last round of such
-    // workgroups would be mostly empty and is not cut into parts: where the rounds are filled by less than four fifths (12x48x48, window
+    // workgroups would be mostly empty and is not cut into parts: where the rounds are filled by less than four fifths, the only round
+    // by less than seven tenths (12x48x48, window
     // 1x3x3, us, 12 waves against 4, rounds in brackets: two heads (0.56) 117, 97; three (0.84) 126, 141; four (1.13) 244, 194 and with
     // parts 180, 184; six (1.69) 237, 262; eight (2.25) 355, 315; eleven (3.09) 477, 436; twelve (3.38) 486, 487; thirteen (3.66) 500, 498;
-    // 6x48x48, eleven (1.55) 233, 223; twelve (1.69) 235, 258; 18x48x48, 3x3x3, five (2.11) 1009, 885; six (2.53) 1013, 1011).
+    // 6x48x48, eleven (1.55) 233, 223; twelve (1.69) 235, 258; 18x48x48, 3x3x3, five (2.11) 1009, 885; six (2.53) 1013, 1011.  From 0.70 to
+    // 0.78 of a round, 94 launches of 24 to 432 units a walk: 12 waves ahead by 7 %, 15 at most; 119, 130 at 0.70 and 108 units).
     // Nor where the launch waits for long walks, which the smaller workgroups spread over three times as many CUs (12x48x48, heads of 36,
     // 108, 12 and 864 units, four 803, 482; eight 830, 775).
     const uint64_t items = slices * (p.N / 384), rounds = (items + cus - 1) / cus;
-    if (p.P % 384 == 0 && !waits_for_long_walks(a, items, cus) && (parts_of_tail(a, (uint32_t)items, (uint32_t)cus, 384) > 1 || 5 * items >= 4 * rounds * cus))
+    if (p.P % 384 == 0 && !waits_for_long_walks(a, items, cus) && (parts_of_tail(a, (uint32_t)items, (uint32_t)cus, 384) > 1 || 10 * items >= (rounds == 1 ? 7 : 8) * rounds * cus))
         return launch_x32<12, 32, 2, 1>(a);
     return launch_x32<4, 32, 2, 3>(a);
 }

@@ -110,6 +110,23 @@ def test_twelve_waves_for_48_queries_where_no_cu_gets_two_workgroups(H, grid, ti
     assert launches(1, H, 64, grid, tile, windows) == [want]
 
 
+@pytest.mark.parametrize("B,H,grid,windows,want", [
+    (1, 2, (12, 48, 48), [(1, 3, 3)], "x32<4> items 432"),            # workgroups of twelve waves fill 0.56 of a round
+    (1, 3, (12, 24, 88), [(1, 3, 3)], "x32<12> items 198"),           # 0.77
+    (1, 4, (30, 8, 80), [(5, 1, 7)], "x32<12> items 200"),            # 0.78, long walks
+    (1, 3, (12, 48, 48), [(1, 3, 3)], "x32<12> items 216"),           # 0.84
+    (1, 4, (12, 48, 48), [(1, 3, 3)], "x32<4> items 864"),            # 1.13 rounds
+    (1, 8, (12, 32, 48), [(1, 3, 3)], "x32<4> items 1152"),           # 1.5
+    (1, 6, (12, 48, 48), [(1, 3, 3)], "x32<12> items 432"),           # 1.69
+    (1, 8, (12, 48, 48), [(1, 3, 3)], "x32<4> items 1728"),           # 2.25
+    (1, 12, (12, 48, 48), [(1, 3, 3)], "x32<12> items 864"),          # 3.38
+])
+def test_twelve_waves_a_workgroup_where_their_rounds_are_full_enough(B, H, grid, windows, want):
+    """384-token tiles, head dimension 128, no workspace."""
+    (line,) = launches(B, H, 128, grid, (6, 8, 8), windows)
+    assert line.startswith(want + " "), line
+
+
 # The kernels that the cases of tests/test_gpu_forward_launches.py and test_gpu_backward_launches.py run: a rule that sends one of
 # them elsewhere leaves its kernel without those tests.
 FORWARD = {
