@@ -127,6 +127,22 @@ def test_twelve_waves_a_workgroup_where_their_rounds_are_full_enough(B, H, grid,
     assert line.startswith(want + " "), line
 
 
+@pytest.mark.parametrize("H,grid,windows,workspace,want", [
+    (4, (12, 48, 48), [(1, 1, 3), (1, 3, 3), (1, 1, 1), (2, 6, 6)], False, "x32<4> items 864 workgroups 864 parts 1"),     # longest 3.0 shares
+    (8, (12, 48, 48), [(1, 1, 3), (1, 3, 3), (1, 1, 1), (2, 6, 6)], False, "x32<4> items 1728 workgroups 1728 parts 1"),   # 1.5
+    (12, (12, 48, 48), [(1, 1, 3), (1, 3, 3), (1, 1, 1), (2, 6, 6)], False, "x32<12> items 864 workgroups 864 parts 1"),   # 1.0
+    (3, (18, 40, 40), [(3, 3, 3), (3, 3, 3), (3, 3, 5)], False, "x32<4> items 675 workgroups 675 parts 1"),    # 0.88 rounds, 324 and 540 units
+    (5, (36, 48, 8), [(6, 3, 1), (5, 3, 1)], False, "x32<12> items 180 workgroups 180 parts 1"),               # 0.70, 216 and 180
+    (8, (24, 32, 8), [(4, 4, 1), (4, 4, 1), (2, 4, 1)], True, "x32<12> items 128 workgroups 256 parts 2"),     # 0.5, 192 and 144
+    (12, (12, 32, 32), [(1, 3, 3), (2, 4, 4), (1, 1, 3)], True, "x32<4> items 1152 workgroups 1152 parts 1"),  # 108, 384 and 36
+    (12, (12, 32, 32), [(1, 3, 3)], True, "x32<12> items 384 workgroups 512 parts 2"),                         # equal
+])
+def test_four_waves_a_workgroup_where_the_launch_waits_for_long_walks(H, grid, windows, workspace, want):
+    """384-token tiles, head dimension 128."""
+    (line,) = launches(1, H, 128, grid, (6, 8, 8), windows, workspace=workspace)
+    assert line.startswith(want + " of "), line
+
+
 # The kernels that the cases of tests/test_gpu_forward_launches.py and test_gpu_backward_launches.py run: a rule that sends one of
 # them elsewhere leaves its kernel without those tests.
 FORWARD = {
