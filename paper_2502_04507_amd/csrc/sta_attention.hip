@@ -1751,6 +1751,14 @@ uint32_t walk_of_rank(const FwdArgs &a, uint32_t rank)
 }
 uint32_t longest_walk(const FwdArgs &a) { return walk_of_rank(a, 0); }
 
+// Heads whose walk is more than so many quarters of the longest.
+uint32_t heads_of_long_walks(const FwdArgs &a, uint32_t quarters)
+{
+    uint32_t n = 1;
+    while (n < a.p.heads && 4 * (uint64_t)walk_of_rank(a, n) > (uint64_t)quarters * longest_walk(a)) ++n;
+    return n;
+}
+
 // Where the walks of the heads differ and the longest is more than 1.4 times an even share of all of the launch's items on so many places
 // (the cases at its uses are at 1.45, 1.5 and 3.0): the long ones are what the launch waits for, and its last items, the short ones, are not.
 // They differ where the mean is less than nine tenths of the longest.  us, 384-token tiles, twelve waves a workgroup and four, by mean over
@@ -2070,8 +2078,20 @@ hipError_t launch_forward(const void *q, const void *k, const void *v, void *o, 
     // 0.78 of a round, 94 launches of 24 to 432 units a walk: 12 waves ahead by 7 %, 15 at most; 119, 130 at 0.70 and 108 units).
     // Nor where the launch waits for long walks, which the smaller workgroups spread over three times as many CUs (12x48x48, heads of 36,
     // 108, 12 and 864 units, four 803, 482; eight 830, 775).
+    // Nor is the second round too empty where the long walks, one to a CU, outlast all others beside them (heads of two lengths, us, 12 waves
+    // against 4, rounds of all and of the long ones in brackets: 396 and 36 units (1.41, 0.70) 424, 480; 180, 36 (1.41, 0.70) 209, 225; 240, 36
+    // (1.56, 0.78) 298, 313; 336, 72 (1.5, 0.75) 386, 416; but 324, 60 and 36 (2.25, 0.70) 470, 433): where the longest is 1.05 times
+    // an even share of all or more, what counts is the round of those over three quarters of it.
     const uint64_t items = slices * (p.N / 384), rounds = (items + cus - 1) / cus;
-    if (p.P % 384 == 0 && !waits_for_long_walks(a, items, cus) && (parts_of_tail(a, (uint32_t)items, (uint32_t)cus, 384) > 1 || 10 * items >= (rounds == 1 ? 7 : 8) * rounds * cus))
+    auto full = [&](uint64_t n) { return 10 * n >= (n <= cus ? 7 : 8 * ((n + cus - 1) / cus)) * cus; };
+    auto full_of_long_walks = [&]() {
+        uint64_t all = 0;
+        for (uint32_t r = 0; r < p.heads; ++r) all += walk_of_rank(a, r);
+        const uint64_t n = items / p.heads * heads_of_long_walks(a, 3);
+        return rounds == 2 && 20 * (uint64_t)units * cus * p.heads >= 21 * all * items && n <= cus && full(n);
+    };
+    if (p.P % 384 == 0 && !waits_for_long_walks(a, items, cus) &&
+        (parts_of_tail(a, (uint32_t)items, (uint32_t)cus, 384) > 1 || full(items) || full_of_long_walks()))
         return launch_x32<12, 32, 2, 1>(a);
     return launch_x32<4, 32, 2, 3>(a);
 }

@@ -120,6 +120,11 @@ def test_twelve_waves_for_48_queries_where_no_cu_gets_two_workgroups(H, grid, ti
     (1, 6, (12, 48, 48), [(1, 3, 3)], "x32<12> items 432"),           # 1.69
     (1, 8, (12, 48, 48), [(1, 3, 3)], "x32<4> items 1728"),           # 2.25
     (1, 12, (12, 48, 48), [(1, 3, 3)], "x32<12> items 864"),          # 3.38
+    (1, 12, (6, 40, 48), [(1, 3, 1), (1, 3, 5)], "x32<12> items 360"),        # 1.41 and half of it 36 units of 180: long ones 0.70 of a round
+    (1, 20, (6, 40, 32), [(1, 5, 4), (1, 1, 3)], "x32<12> items 400"),        # 1.56, 36 of 240: 0.78
+    (1, 12, (6, 40, 48), [(1, 3, 1), (1, 3, 5), (1, 3, 3)], "x32<4> items 1080"),     # 1.41, 36, 180 and 108: 0.47
+    (1, 12, (6, 40, 48), [(1, 3, 3), (1, 3, 5)], "x32<4> items 1080"),        # 1.41, 108 of 180: 1.1 rounds of work
+    (1, 16, (6, 32, 72), [(1, 1, 5), (1, 3, 9), (1, 3, 1)], "x32<4> items 1728"),     # 2.25, 60, 324 and 36
 ])
 def test_twelve_waves_a_workgroup_where_their_rounds_are_full_enough(B, H, grid, windows, want):
     """384-token tiles, head dimension 128, no workspace."""
