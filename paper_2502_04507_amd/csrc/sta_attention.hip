@@ -1936,7 +1936,8 @@ hipError_t launch_groups(const FwdArgs &a)
             // Two stages of V, four of these workgroups a CU, or one stage, six (three with two groups).  One stage costs a second barrier
             // a unit and waits for V; it pays by its places: more than a round of four, and two groups for up to three workgroups a CU (measured
             // from 576 workgroups of one group on: 25.7, two 23.7).
-            // Not where the second round of four is nearly full ((1664) 51, 52; (1750) 372, 394; (1920) 54, 58), and where the walks of the
+            // Not from the first round of six to the second of four ((1540, 308 units) 606, 641; (1600, 150) 313, 333; 36 launches up to 1620 4 % on
+            // average; (1664) 51, 52; (1750) 372, 394; (1920) 54, 58), and where the walks of the
             // heads differ, two groups of two stages for one to one and a half rounds, as the long walks are alone at the end (96x96, 18 heads
             // of 18, 50 and 288 units 365, one stage 401; nine (by walks 576) 256, in two groups of one stage 194).  us, two stages, one, one and two groups; workgroups
             // of one group in brackets: 64x64, 3x3 (640) 25.9, 26.0, 23.9; (768) 26.4, 26.3, 25.4; (1024) 29.6, 29.6, 33.1; (1280) 42.4, 37.6,
@@ -1949,7 +1950,7 @@ hipError_t launch_groups(const FwdArgs &a)
                 if (4 * blocks >= 9 * cus && blocks <= 3 * cus && units >= 16) return launch_group<128, 2, 2, 3, true, 1, true>(a);
                 if (units >= 64 && units != walk_of_rank(a, p.heads - 1) && blocks > places && 2 * blocks <= 3 * places)
                     return launch_group<128, 2, 2, 2, true>(a);
-                return blocks <= places || (5 * blocks > 8 * places && blocks <= 2 * places)
+                return blocks <= places || (2 * blocks > 3 * places && blocks <= 2 * places)
                            ? launch_group<128, 2, 1, 2, true>(a)
                            : launch_group<128, 2, 1, 3, true, 1, true>(a);
             }

@@ -148,6 +148,23 @@ def test_four_waves_a_workgroup_where_the_launch_waits_for_long_walks(H, grid, w
     assert line.startswith(want + " of "), line
 
 
+@pytest.mark.parametrize("H,grid,tile,windows,want", [
+    (32, (1, 64, 64), (1, 8, 8), [(1, 3, 3)], "group<128,2,1,1,1> items 2048"),         # 2.0 rounds of four two-wave workgroups a CU
+    (24, (1, 64, 64), (1, 8, 8), [(1, 3, 3)], "group_one_v<128,2,1,1,1> items 1536"),   # 1.5
+    (25, (1, 64, 64), (1, 8, 8), [(1, 3, 3)], "group<128,2,1,1,1> items 1600"),         # 1.56
+    (16, (1, 80, 80), (1, 8, 8), [(1, 5, 5)], "group<128,2,1,1,1> items 1600"),
+    (20, (1, 64, 64), (1, 8, 8), [(1, 3, 3)], "group_one_v<128,2,1,1,1> items 1280"),   # 1.25
+    (16, (1, 64, 64), (1, 8, 8), [(1, 3, 3)], "group<128,2,1,1,1> items 1024"),         # 1.0
+    (10, (1, 64, 64), (1, 8, 8), [(1, 3, 3)], "group_one_v<128,2,2,1,1> items 640"),
+    (8, (1, 64, 64), (1, 8, 8), [(1, 3, 3)], "group<128,2,2,1,1> items 512"),
+    (40, (1, 64, 64), (1, 8, 8), [(1, 3, 3)], "group_one_v<128,2,1,1,1> items 2560"),   # 2.5
+    (18, (1, 96, 96), (1, 8, 8), [(1, 3, 3), (1, 5, 5), (1, 12, 12)], "group<128,2,2,1,1> items 2592"),       # by walks 1.2 rounds
+    (9, (1, 96, 96), (1, 8, 8), [(1, 3, 3), (1, 5, 5), (1, 12, 12)], "group_one_v<128,2,2,1,1> items 1296"),  # 0.6
+])
+def test_one_lds_stage_of_v_by_the_rounds_of_the_launch(H, grid, tile, windows, want):
+    assert launches(1, H, 128, grid, tile, windows) == [want]
+
+
 # The kernels that the cases of tests/test_gpu_forward_launches.py and test_gpu_backward_launches.py run: a rule that sends one of
 # them elsewhere leaves its kernel without those tests.
 FORWARD = {
