@@ -1931,6 +1931,22 @@ hipError_t launch_groups(const FwdArgs &a)
                        : launch_group<128, 3, 1, 3, true>(a);
         }
     }
+    // One LDS stage of V instead of two (head dimension 128): whether n workgroups of qw waves of queries, of which a CU then holds six
+    // instead of four, are through in fewer rounds.  Heads of different walks: not where those over half the longest, which run first, are
+    // less than a round of four and the longest is an even share of a place or more, as a wave that is alone at the end is slower with one
+    // stage, nor where those ones end beyond a round of six and within two of four, unless the longest is less than 0.45 shares.  (us, two
+    // stages, one; waves, units and heads: 64-token tiles (4320; 60 x 10, 20, 12 and 6 x 30) 78, 102, (3200; 400 x 4, 50 x 4) 417, 520; 32-token
+    // tiles (2464; 55 x 8, 9 and 3 x 24) 53, 67, (3840; 96 x 20, 3 x 20) 169, 211; 347 launches that this leaves on two stages: one 3 % slower
+    // in the mean, 30 % at most; 1168 on one: 12 % faster.)
+    const uint64_t long_waves = (uint64_t)a.B * heads_of_long_walks(a, 2) * (p.N / 32);
+    auto one_stage = [&](uint64_t n, uint64_t qw) {
+        const uint64_t places = 4 * cus, long_ones = long_waves / qw, longest = units * places;
+        auto beyond_six = [&](uint64_t m) { return 2 * m > 3 * places && m <= 2 * places; };
+        uint64_t all = 0;                                   // units of all workgroups
+        for (uint32_t r = 0; r < p.heads; ++r) all += walk_of_rank(a, r);
+        all *= (uint64_t)a.B * (p.N / 32) / qw;
+        return n > places && !beyond_six(n) && (long_ones > places || longest < all) && !(beyond_six(long_ones) && 20 * longest >= 9 * all);
+    };
     if (P % 64 == 0) {
         if constexpr (D == 128) {
             // Two stages of V, four of these workgroups a CU, or one stage, six (three with two groups).  One stage costs a second barrier
@@ -1947,12 +1963,11 @@ hipError_t launch_groups(const FwdArgs &a)
             const uint64_t blocks = waves / 2, places = 4 * cus;
             if (P % 128 != 0) {
                 if (two) return launch_group<128, 2, 2, 2, true>(a);
-                if (4 * blocks >= 9 * cus && blocks <= 3 * cus && units >= 16) return launch_group<128, 2, 2, 3, true, 1, true>(a);
+                if (4 * blocks >= 9 * cus && blocks <= 3 * cus && long_waves <= 6 * cus && units >= 16) return launch_group<128, 2, 2, 3, true, 1, true>(a);
                 if (units >= 64 && units != walk_of_rank(a, p.heads - 1) && blocks > places && 2 * blocks <= 3 * places)
                     return launch_group<128, 2, 2, 2, true>(a);
-                return blocks <= places || (2 * blocks > 3 * places && blocks <= 2 * places)
-                           ? launch_group<128, 2, 1, 2, true>(a)
-                           : launch_group<128, 2, 1, 3, true, 1, true>(a);
+                return one_stage(blocks, 2) ? launch_group<128, 2, 1, 3, true, 1, true>(a)
+                                            : launch_group<128, 2, 1, 2, true>(a);
             }
             if (4 * waves <= fits && units >= 32) return launch_group<128, 2, 4, 2, false>(a);
             return two ? launch_group<128, 2, 2, 2, false>(a)
@@ -1968,7 +1983,7 @@ hipError_t launch_groups(const FwdArgs &a)
     if (D == 64 && two) return launch_group<64, 1, 2, 2, true>(a);
     if constexpr (D == 128) {
         // one stage of V here too: six waves a CU instead of four
-        if (waves > 8 * cus || (waves > 4 * cus && waves <= 6 * cus)) return launch_group<128, 1, 1, 2, true, 1, true>(a);
+        if (one_stage(waves, 1)) return launch_group<128, 1, 1, 2, true, 1, true>(a);
     }
     return launch_group<D, 1, 1, D == 64 ? 3 : 1, true>(a);
 }

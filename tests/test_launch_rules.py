@@ -160,6 +160,22 @@ def test_four_waves_a_workgroup_where_the_launch_waits_for_long_walks(H, grid, w
     (40, (1, 64, 64), (1, 8, 8), [(1, 3, 3)], "group_one_v<128,2,1,1,1> items 2560"),   # 2.5
     (18, (1, 96, 96), (1, 8, 8), [(1, 3, 3), (1, 5, 5), (1, 12, 12)], "group<128,2,2,1,1> items 2592"),       # by walks 1.2 rounds
     (9, (1, 96, 96), (1, 8, 8), [(1, 3, 3), (1, 5, 5), (1, 12, 12)], "group_one_v<128,2,2,1,1> items 1296"),  # 0.6
+    # heads of different walks: rounds of those over half the longest, and the longest in even shares of a place
+    (36, (1, 64, 64), (1, 8, 8), [(1, 3, 3), (1, 1, 1), (1, 1, 1)], "group<128,2,1,1,1> items 2304"),         # 0.75, 1.1
+    (48, (1, 64, 64), (1, 8, 8), [(1, 3, 3), (1, 1, 1), (1, 1, 1)], "group_one_v<128,2,1,1,1> items 3072"),   # 1.0, 0.8
+    (40, (1, 64, 64), (1, 8, 8), [(1, 3, 3), (1, 1, 1)], "group_one_v<128,2,1,1,1> items 2560"),              # 1.25
+    (60, (1, 64, 64), (1, 8, 8), [(1, 3, 3), (1, 1, 1)], "group<128,2,1,1,1> items 3840"),                    # 1.9, 0.48
+    (64, (1, 64, 64), (1, 8, 8), [(1, 3, 3), (1, 1, 3)], "group_one_v<128,2,1,1,1> items 4096"),              # 2.0, 0.37
+    (70, (1, 64, 64), (1, 8, 8), [(1, 3, 3), (1, 1, 1)], "group_one_v<128,2,1,1,1> items 4480"),              # 2.2
+    (40, (1, 64, 64), (1, 8, 8), [(1, 3, 3), (1, 2, 3)], "group_one_v<128,2,1,1,1> items 2560"),              # all of them, 2.5
+    (10, (20, 16, 16), (5, 8, 8), [(3, 2, 2)] * 7 + [(4, 2, 1)] * 3, "group<128,2,1,1,1> items 800"),         # two groups: by walks 720, long 800
+    # tiles of 32 tokens
+    (80, (1, 16, 16), (1, 4, 8), [(1, 3, 1)], "group<128,1,1,1,1> items 640"),
+    (140, (1, 16, 16), (1, 4, 8), [(1, 3, 1)], "group_one_v<128,1,1,1,1> items 1120"),                        # 1.1
+    (140, (1, 16, 16), (1, 4, 8), [(1, 3, 1), (1, 1, 1)], "group<128,1,1,1,1> items 1120"),                   # 0.55, 1.4
+    (220, (1, 16, 16), (1, 4, 8), [(1, 3, 1)], "group<128,1,1,1,1> items 1760"),                              # 1.7
+    (220, (1, 16, 16), (1, 4, 8), [(1, 3, 2), (1, 1, 1), (1, 3, 2)], "group<128,1,1,1,1> items 1760"),        # 1.15, but 1.7 in all
+    (170, (1, 16, 16), (1, 4, 8), [(1, 3, 2), (1, 1, 1), (1, 3, 2), (1, 3, 2), (1, 3, 2)], "group_one_v<128,1,1,1,1> items 1360"),   # 1.06
 ])
 def test_one_lds_stage_of_v_by_the_rounds_of_the_launch(H, grid, tile, windows, want):
     assert launches(1, H, 128, grid, tile, windows) == [want]
