@@ -2075,13 +2075,19 @@ hipError_t launch_forward(const void *q, const void *k, const void *v, void *o, 
     // (864, 108) 63.2, 58.7; (576, 192) 72, 85; (960, 192) 101, 105; (1080, 108) 76, 81; 256-token tiles (384, 128) 50.3, 39.6; (400, 200)
     // 63.1, 57.9; (768, 128) 67, 65; (1024, 128) 82, 75; (648, 216) 91, 98; 128-token tiles (480, 108) 48.7, 36.4; (480, 180) 64.5, 55.9; (480,
     // 480) 132, 137; (960, 108) 70.2, 62.4; (720, 144) 71, 72; (576, 200) 77, 91.
+    // Beyond 128 units only where the mean walk is two thirds of the longest or more: the parts of the long ones are shorter than a quarter,
+    // and share a CU with fewer ((432, 216 and 24) 55, 60; (400, 200 and 40) 51, 56; (480, 160, 80 and 48) 44, 46; (480, 240 and 200) 72, 69).
     // Measured in us, 12-wave or 4-wave kernel without a workspace, with one, key groups; waves, units:
     // 6x16x24 in 384-token tiles, one head (72, 72) 79, 37, 26; 12x48x48, one head (864, 108) 116, 68, 57; 2x40x40 in 128-token
     // tiles, one head (100, 36) 27, 26, 17, twelve (1200, 36) 37, 54, 34; 16x8x40 in 128-token tiles, four heads (640, 120) 76,
     // 64, 58, eight (1280, 120) 102, 104, 99; 12x32x40 in 256-token tiles, four heads (1920, 216) 255, 255, 280.
     const uint64_t cus = compute_units(), slices = (uint64_t)B * p.heads, waves = slices * (p.N / 32);
     const uint32_t units = longest_walk(a);
-    if (waves <= 5 * cus && (split_ws == nullptr || units <= 80 || waves <= cus || (waves <= 2 * cus && units <= 240) || (waves <= 4 * cus && units <= 128)))
+    uint64_t all_units = 0;                                 // units of a walk of every head
+    for (uint32_t r = 0; r < p.heads; ++r) all_units += walk_of_rank(a, r);
+    const bool alike = 3 * all_units >= 2 * (uint64_t)p.heads * units;
+    if (waves <= 5 * cus && (split_ws == nullptr || units <= 80 || waves <= cus || (waves <= 4 * cus && units <= 128) ||
+                             (waves <= 2 * cus && units <= 240 && alike)))
         return launch_groups<128>(a);
     // A tile of 384 tokens (the paper's 6x8x8) gets one 12-wave workgroup per query tile: every K/V sub-block
     // fetched from L2 then serves 384 queries instead of 128.  Measured at the 115,200-token layer, window
@@ -2101,10 +2107,8 @@ hipError_t launch_forward(const void *q, const void *k, const void *v, void *o, 
     const uint64_t items = slices * (p.N / 384), rounds = (items + cus - 1) / cus;
     auto full = [&](uint64_t n) { return 10 * n >= (n <= cus ? 7 : 8 * ((n + cus - 1) / cus)) * cus; };
     auto full_of_long_walks = [&]() {
-        uint64_t all = 0;
-        for (uint32_t r = 0; r < p.heads; ++r) all += walk_of_rank(a, r);
         const uint64_t n = items / p.heads * heads_of_long_walks(a, 3);
-        return rounds == 2 && 20 * (uint64_t)units * cus * p.heads >= 21 * all * items && n <= cus && full(n);
+        return rounds == 2 && 20 * (uint64_t)units * cus * p.heads >= 21 * all_units * items && n <= cus && full(n);
     };
     if (p.P % 384 == 0 && !waits_for_long_walks(a, items, cus) &&
         (parts_of_tail(a, (uint32_t)items, (uint32_t)cus, 384) > 1 || full(items) || full_of_long_walks()))

@@ -181,6 +181,24 @@ def test_one_lds_stage_of_v_by_the_rounds_of_the_launch(H, grid, tile, windows, 
     assert launches(1, H, 128, grid, tile, windows) == [want]
 
 
+@pytest.mark.parametrize("H,grid,tile,windows,want", [                                  # waves, units
+    (1, (12, 24, 24), (6, 8, 8), [(2, 3, 3)], "solo<128,2,8,0> items 216"),             # 216, 216
+    (2, (12, 24, 24), (6, 8, 8), [(2, 3, 3)], "group<128,2,4,0,1> items 216"),          # 432, 216
+    (1, (18, 24, 24), (6, 8, 8), [(3, 3, 3)], "x32<12> items 27 "),                     # 324, 324
+    (1, (12, 48, 48), (6, 8, 8), [(1, 3, 3)], "group<128,2,2,0,1> items 432"),          # 864, 108
+    (3, (12, 24, 32), (6, 8, 8), [(2, 2, 4)], "x32<12> items 72 "),                     # 864, 288
+    (5, (12, 24, 24), (6, 8, 8), [(1, 3, 3)], "x32<12> items 90 "),                     # 1080, 108
+    (2, (2, 72, 48), (2, 8, 8), [(1, 9, 6)], "group<128,2,4,0,1> items 216"),           # 432, 216
+    (2, (2, 72, 48), (2, 8, 8), [(1, 9, 6), (1, 1, 6)], "x32<4> items 108 "),           # 432, 216 and 24
+    (2, (20, 8, 40), (4, 8, 8), [(5, 1, 5), (5, 1, 1)], "x32<4> items 100 "),           # 400, 200 and 40
+    (2, (4, 48, 40), (2, 8, 8), [(2, 6, 5), (2, 5, 5)], "group<128,2,4,0,1> items 240"),    # 480, 240 and 200
+    (2, (4, 72, 24), (4, 8, 8), [(1, 5, 3), (1, 1, 3)], "group<128,2,4,0,1> items 216"),    # 432, 120 and 24
+])
+def test_key_groups_where_a_workspace_is_given(H, grid, tile, windows, want):
+    (line,) = launches(1, H, 128, grid, tile, windows, workspace=True)
+    assert line.startswith(want), line
+
+
 # The kernels that the cases of tests/test_gpu_forward_launches.py and test_gpu_backward_launches.py run: a rule that sends one of
 # them elsewhere leaves its kernel without those tests.
 FORWARD = {
