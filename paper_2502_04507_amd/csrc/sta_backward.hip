@@ -1098,14 +1098,27 @@ hipError_t dispatch_dq(const BwdArgs &a)
     // place's share of all walks or more (entry point, us, by the number of waves and so; head dimension 64: 96x96 in 64-token tiles, nine
     // heads of 288, 18 and 6 sub-blocks 342, 270; 12x48x48 in 384-token tiles, four of 36, 108, 12 and 864 1270, 971 (with dK/dV below);
     // 8x40x48 in 128-token tiles, six of 480, 36 and 12 487, 438; 128: the same nine 540, 442; the same six 780, 750; 12x32x32 in
-    // 256-token tiles, four of 384 and 72 594, 558).  A CU holds six waves of the shapes of three at head dimension 128 (9x40x40, six heads of 162, 18
-    // and 6, 2.0 times in eighths, 1.5 in sixths 467, 480).
+    // 256-token tiles, four of 384 and 72 594, 558).  Shapes of three waves, and of four at head
+    // dimension 128, in launches that do not have two groups whatever their walks: from two times on, those of three only where the waves of
+    // the walks over half the longest are 0.4 of the places or less.  Short of that two groups are 0.8 % ahead in the mean of 222 launches, but
+    // up to 12 % behind (one against two: 192-token tiles, 64, 14 heads of 180, 150, 90 and 18, 2.03 times, 289, 301; 288-token tiles, 128, six
+    // of 162 and 27, 2.03 times, 358, 376; 384-token tiles, 128, twelve of 120, 36 and 24, 1.86 times, 326, 335).
+    // A CU holds six waves of the shapes of three at head dimension 128 (9x40x40,
+    // six heads of 162, 18 and 6, 2.0 times in eighths, 1.5 in sixths 467, 480; 151 launches of up to 1024 waves less than 1.8 times in sixths: one
+    // group 0 to 10 % ahead).
     if (units >= 64 && units != walk_of_rank(a, a.p.heads - 1)) {
         uint64_t all = 0;
         for (uint32_t r = 0; r < a.p.heads; ++r) all += walk_of_rank(a, r);
         all *= (uint64_t)a.B * (a.p.N / 32);
-        const uint64_t held = D == 128 && P % 96 == 0 && P % 128 != 0 ? 6 * cus : places;
-        two = 18 * all <= 10 * held * units;
+        const bool three = P % 96 == 0 && P % 128 != 0;
+        const uint64_t held = D == 128 && three ? 6 * cus : places;
+        if (two || !(three || (D == 128 && P % 128 == 0))) {
+            two = 18 * all <= 10 * held * units;
+        } else {
+            uint64_t long_heads = 0;
+            for (uint32_t r = 0; r < a.p.heads; ++r) long_heads += 2 * walk_of_rank(a, r) > units;
+            two = 2 * all <= held * units && (!three || 10 * long_heads * a.B * (a.p.N / 32) <= 4 * held);
+        }
     }
     if (P % 128 != 0 && !(sta::dma_aligned(a.k) && sta::dma_aligned(a.v))) return launch_dq<D, 1, 1, false>(a);
     if (waves <= (D == 64 && P % 96 == 0 && P % 128 != 0 ? 2 * cus : cus)) return launch_dq<D, 1, 4>(a);

@@ -92,6 +92,13 @@ def test_launches_of_a_round_or_so_go_by_the_longest_walk_of_a_key_tile(H, grid,
     (64, 4, (12, 48, 48), (6, 8, 8), [(1, 1, 3), (1, 3, 3), (1, 1, 1), (2, 6, 6)], "dq<64,2,2,1> dkv<64,2,2,1,1>"),    # 3.0; by walks 1020 waves
     (64, 8, (12, 48, 48), (6, 8, 8), [(1, 1, 3), (1, 3, 3), (1, 1, 1), (2, 6, 6)], "dq<64,4,1,1> dkv<64,4,1,2,1>"),    # 1.5; 2040
     (128, 6, (9, 40, 40), (3, 8, 8), [(3, 3, 3), (1, 1, 3), (1, 1, 1)], "dq<128,3,1,1> dkv<128,2,2,1,1>"),     # 1.5 of six waves a CU
+    (128, 2, (9, 40, 40), (3, 8, 8), [(3, 3, 3), (1, 5, 5)], "dq<128,3,1,1> dkv<128,2,2,1,1>"),                # 900 waves; 1.77 of six a CU
+    (128, 6, (18, 12, 32), (6, 6, 8), [(3, 2, 3), (3, 1, 1)], "dq<128,3,1,1> dkv<128,1,4,1,1>"),               # 2.03, the long ones 0.42 of the places
+    (128, 4, (3, 48, 40), (3, 8, 8), [(1, 6, 5), (1, 3, 5), (1, 6, 5), (1, 3, 3)], "dq<128,3,2,1> dkv<128,1,4,1,1>"),  # 720; 2.1 and more
+    (64, 14, (3, 48, 40), (3, 8, 8), [(1, 6, 5)] * 4 + [(1, 5, 5)] * 3 + [(1, 3, 5)] * 3 + [(1, 1, 3)] * 4, "dq<64,3,1,1> dkv<64,2,2,1,1>"),  # 2.03, 0.41
+    (64, 6, (3, 48, 80), (3, 8, 8), [(1, 6, 10), (1, 1, 3), (1, 1, 3)], "dq<64,3,2,1> dkv<64,2,2,1,1>"),       # 3.6
+    (128, 12, (6, 16, 72), (6, 8, 8), [(1, 2, 5), (1, 1, 3), (1, 2, 1), (1, 2, 1)], "dq<128,4,1,1> dkv<128,4,1,1,1>"),  # 1.86 of eight a CU
+    (64, 4, (16, 32, 40), (4, 8, 8), [(4, 4, 5), (1, 3, 3)], "dq<64,2,2,1> dkv<64,2,2,1,1>"),
     (64, 16, (1, 64, 64), (1, 8, 8), [(1, 5, 5)], "dq<64,2,2,1> dkv<64,1,4,1,1>"),                             # 2048 equal walks of 50
     (64, 16, (1, 64, 64), (1, 8, 8), [(1, 3, 3)], "dq<64,2,1,1> dkv<64,2,2,1,1>"),                             # of 18
 ])
