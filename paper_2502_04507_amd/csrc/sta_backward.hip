@@ -1189,8 +1189,10 @@ hipError_t dispatch_dkv(const BwdArgs &a)
         if (P % 128 != 0 && waves > 4 * cus && small && (longest < 32 || 30 * cus * longest <= 11 * all)) return launch_dkv_pairs<2, 1>(a);
     }
     // (at head dimension 64 by their walks: 12x32x32 in 384-token tiles, six heads of 384, 108 and 36 411, 365; 12x48x48, four of 36, 108, 12
-    // and 864 1260, 1113)
-    if (P % 128 == 0) return (D == 64 ? by_walk : waves) <= (P == 128 ? 24 : 6) * cus ? launch_dkv<D, 2, 2>(a) : launch_dkv<D, 4, 1, D == 64 ? 2 : 1>(a);
+    // and 864 1260, 1113; but not on 128-token tiles, whose line is at four rounds of the chip and more: by walks -15 to +10 %, 4x72x8, 160 heads
+    // of 72, 24 and 8 326, 358)
+    if (P == 128) return waves <= 24 * cus ? launch_dkv<D, 2, 2>(a) : launch_dkv<D, 4, 1, D == 64 ? 2 : 1>(a);
+    if (P % 128 == 0) return (D == 64 ? by_walk : waves) <= 6 * cus ? launch_dkv<D, 2, 2>(a) : launch_dkv<D, 4, 1, D == 64 ? 2 : 1>(a);
     return by_walk <= 8 * cus || (units >= 32 && (D == 64 || waves <= 32 * cus)) ? launch_dkv<D, 2, 2>(a) : launch_dkv<D, 2, 1>(a);
 }
 

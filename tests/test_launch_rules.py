@@ -99,6 +99,9 @@ def test_launches_of_a_round_or_so_go_by_the_longest_walk_of_a_key_tile(H, grid,
     (64, 6, (3, 48, 80), (3, 8, 8), [(1, 6, 10), (1, 1, 3), (1, 1, 3)], "dq<64,3,2,1> dkv<64,2,2,1,1>"),       # 3.6
     (128, 12, (6, 16, 72), (6, 8, 8), [(1, 2, 5), (1, 1, 3), (1, 2, 1), (1, 2, 1)], "dq<128,4,1,1> dkv<128,4,1,1,1>"),  # 1.86 of eight a CU
     (64, 4, (16, 32, 40), (4, 8, 8), [(4, 4, 5), (1, 3, 3)], "dq<64,2,2,1> dkv<64,2,2,1,1>"),
+    (64, 160, (4, 72, 8), (2, 8, 8), [(2, 9, 1), (2, 3, 1), (2, 3, 1), (2, 1, 1)], "dq<64,4,1,1> dkv<64,4,1,2,1>"),    # 11520 waves, by walks 5120
+    (64, 80, (4, 72, 8), (2, 8, 8), [(2, 9, 1), (2, 3, 1), (2, 3, 1), (2, 1, 1)], "dq<64,4,1,1> dkv<64,2,2,1,1>"),     # 5760
+    (64, 6, (12, 32, 32), (6, 8, 8), [(2, 4, 4), (1, 3, 3), (1, 1, 3)], "dq<64,2,2,1> dkv<64,2,2,1,1>"),       # 2304, by walks 1056
     (64, 16, (1, 64, 64), (1, 8, 8), [(1, 5, 5)], "dq<64,2,2,1> dkv<64,1,4,1,1>"),                             # 2048 equal walks of 50
     (64, 16, (1, 64, 64), (1, 8, 8), [(1, 3, 3)], "dq<64,2,1,1> dkv<64,2,2,1,1>"),                             # of 18
 ])
