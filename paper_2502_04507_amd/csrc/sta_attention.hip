@@ -879,8 +879,8 @@ void sta_fwd_solo_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restr
     constexpr int SLICES = CB * NQ;                         // 16x16 blocks of an accumulator, 1 KB each
     constexpr int UNIT_B = R::Tile + L::Tile;
     constexpr int REGION = UNIT_B > SLICES * 1024 ? UNIT_B : SLICES * 1024;    // LDS of a wave: K, then V; at the end its accumulators
-    constexpr int PER_WAVE = SLICES > KG ? SLICES / KG : 1; // of them that a wave merges
-    static_assert((SLICES % KG == 0 || PER_WAVE == 1) && CB % PER_WAVE == 0, "merge");
+    constexpr int PER_WAVE = SLICES / KG;                   // of them that a wave merges
+    static_assert(SLICES % KG == 0 && CB % PER_WAVE == 0, "merge");
     constexpr int STATS = KG * REGION;                      // offset and row sum of every group's queries
     constexpr int FLAGS = STATS + KG * QB * 8;
     constexpr int OUT = (FLAGS + KG * 4 + 15) / 16 * 16;
@@ -1099,34 +1099,32 @@ void sta_fwd_solo_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restr
 
     // ---- merge: every wave sums the groups' parts of its slices of the accumulators, in ascending order
     const int first = kg * PER_WAVE, qb = first / CB;
-    if (SLICES >= KG || first < SLICES) {
-        const float2 *stats = reinterpret_cast<const float2 *>(smem + STATS) + 16 * qb + c16;
-        float m = -INFINITY, l = 0.f, weight[KG];
+    const float2 *stats = reinterpret_cast<const float2 *>(smem + STATS) + 16 * qb + c16;
+    float m = -INFINITY, l = 0.f, weight[KG];
 #pragma unroll
-        for (int g = 0; g < KG; ++g) m = fmaxf(m, stats[g * QB].x);
+    for (int g = 0; g < KG; ++g) m = fmaxf(m, stats[g * QB].x);
+#pragma unroll
+    for (int g = 0; g < KG; ++g) {
+        weight[g] = __builtin_amdgcn_exp2f(stats[g * QB].x - m);
+        l += stats[g * QB].y * weight[g];
+    }
+    const float inv = 1.f / l;
+#pragma unroll
+    for (int j = 0; j < PER_WAVE; ++j) {
+        const int cb = first % CB + j;
+        floatx4 sum = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int g = 0; g < KG; ++g) {
-            weight[g] = __builtin_amdgcn_exp2f(stats[g * QB].x - m);
-            l += stats[g * QB].y * weight[g];
+            const floatx4 x = *reinterpret_cast<const floatx4 *>(smem + g * REGION + (first + j) * 1024 + lane * 16);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) sum[r] = fmaf(x[r], weight[g], sum[r]);
         }
-        const float inv = 1.f / l;
+        bf16x4 ov;
 #pragma unroll
-        for (int j = 0; j < PER_WAVE; ++j) {
-            const int cb = first % CB + j;
-            floatx4 sum = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int g = 0; g < KG; ++g) {
-                const floatx4 x = *reinterpret_cast<const floatx4 *>(smem + g * REGION + (first + j) * 1024 + lane * 16);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) sum[r] = fmaf(x[r], weight[g], sum[r]);
-            }
-            bf16x4 ov;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) ov[r] = static_cast<__bf16>(sum[r] * inv);
-            *reinterpret_cast<bf16x4 *>(smem + OUT + (16 * qb + c16) * L::RowB + (16 * cb + 4 * g4) * 2) = ov;
-        }
-        if (p.lse != nullptr && first % CB == 0 && g4 == 0) p.lse[my_row + 16 * qb + c16] = m * 0.6931471805599453f + __logf(l);
+        for (int r = 0; r < 4; ++r) ov[r] = static_cast<__bf16>(sum[r] * inv);
+        *reinterpret_cast<bf16x4 *>(smem + OUT + (16 * qb + c16) * L::RowB + (16 * cb + 4 * g4) * 2) = ov;
     }
+    if (p.lse != nullptr && first % CB == 0 && g4 == 0) p.lse[my_row + 16 * qb + c16] = m * 0.6931471805599453f + __logf(l);
     __syncthreads();
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     char *out = reinterpret_cast<char *>(o + my_row * D);
