@@ -1235,7 +1235,7 @@ __global__ __launch_bounds__(NW * 64, MINB) void sta_fwd_x32_kernel(const bf16_r
         }
     };
 
-    // ---- per-lane constants of the operand reads (stage 0; the stage is added where they are used)
+    // ---- per-lane constants of the operand reads (stage 0; the other is in the read instructions, added in the careful pass)
     // K (A operand of S^T = K Q^T, 16 keys x 32 channels): key row 16*kb + c16 = row c16 & 3 of group 4*kb + (c16 >> 2),
     // logical chunk 4*ks + g4.  The XOR reaches only the two low bits of the chunk, so kb and ks are immediates.
     const uint32_t smem_addr = (uint32_t)(uintptr_t)smem;
