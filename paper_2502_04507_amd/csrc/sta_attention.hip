@@ -2068,11 +2068,13 @@ hipError_t launch_forward(const void *q, const void *k, const void *v, void *o, 
     // Tiles of 128 tokens' multiples.  Up to 1280 waves of 32 queries (the chip holds 2048 of the key-group kernel's at this
     // head dimension) the key-group kernel: more and smaller workgroups, and key groups that need no workspace.  Where one is
     // given, items cut into parts are ahead on long walks: then up to 256 waves, up to 512 (four groups) at up to 240 units, up to 1024
-    // (two) at up to 128, and any number here at up to 80.  us, parts and key groups; waves, units: 384-token tiles (324, 108) 44.4, 34.4;
+    // (two) at up to 128, and any number here at up to 80; from 256 to 320 waves at up to 192 units, from 512 to 614 at up to 112, as fewer
+    // items are cut into more parts.  us, parts and key groups; waves, units: 384-token tiles (324, 108) 44.4, 34.4;
     // (432, 108) 47.1, 35.4; (360, 180) 57.0, 51.9; (384, 192) 59.4, 55.2; (432, 216) 65.6, 62.7; (384, 384) 89, 103; (648, 108) 53.8, 52.6;
     // (864, 108) 63.2, 58.7; (576, 192) 72, 85; (960, 192) 101, 105; (1080, 108) 76, 81; 256-token tiles (384, 128) 50.3, 39.6; (400, 200)
     // 63.1, 57.9; (768, 128) 67, 65; (1024, 128) 82, 75; (648, 216) 91, 98; 128-token tiles (480, 108) 48.7, 36.4; (480, 180) 64.5, 55.9; (480,
-    // 480) 132, 137; (960, 108) 70.2, 62.4; (720, 144) 71, 72; (576, 200) 77, 91.
+    // 480) 132, 137; (960, 108) 70.2, 62.4; (720, 144) 71, 72; (576, 200) 77, 91; any of them (288, 144) 49, 43; (288, 216) 56, 60; (300, 180) 53,
+    // 51; (528, 120) 51, 54; (576, 120) 54, 56; (576, 108) 49.9, 49.6; (640, 120) 60, 57.
     // Beyond 128 units only where the mean walk is two thirds of the longest or more: the parts of the long ones are shorter than a quarter,
     // and share a CU with fewer ((432, 216 and 24) 55, 60; (400, 200 and 40) 51, 56; (480, 160, 80 and 48) 44, 46; (480, 240 and 200) 72, 69).
     // Measured in us, 12-wave or 4-wave kernel without a workspace, with one, key groups; waves, units:
@@ -2084,8 +2086,9 @@ hipError_t launch_forward(const void *q, const void *k, const void *v, void *o, 
     uint64_t all_units = 0;                                 // units of a walk of every head
     for (uint32_t r = 0; r < p.heads; ++r) all_units += walk_of_rank(a, r);
     const bool alike = 3 * all_units >= 2 * (uint64_t)p.heads * units;
-    if (waves <= 5 * cus && (split_ws == nullptr || units <= 80 || waves <= cus || (waves <= 4 * cus && units <= 128) ||
-                             (waves <= 2 * cus && units <= 240 && alike)))
+    const bool short_walks = waves <= 4 * cus && units <= (waves <= 2 * cus || 5 * waves > 12 * cus ? 128 : 112);
+    const bool long_walks = waves <= 2 * cus && units <= (4 * waves > 5 * cus ? 240 : 192) && alike;
+    if (waves <= 5 * cus && (split_ws == nullptr || units <= 80 || waves <= cus || short_walks || long_walks))
         return launch_groups<128>(a);
     // A tile of 384 tokens (the paper's 6x8x8) gets one 12-wave workgroup per query tile: every K/V sub-block
     // fetched from L2 then serves 384 queries instead of 128.  Measured at the 115,200-token layer, window

@@ -199,6 +199,11 @@ def test_one_lds_stage_of_v_by_the_rounds_of_the_launch(H, grid, tile, windows, 
     (3, (12, 24, 32), (6, 8, 8), [(2, 2, 4)], "x32<12> items 72 "),                     # 864, 288
     (5, (12, 24, 24), (6, 8, 8), [(1, 3, 3)], "x32<12> items 90 "),                     # 1080, 108
     (2, (2, 72, 48), (2, 8, 8), [(1, 9, 6)], "group<128,2,4,0,1> items 216"),           # 432, 216
+    (1, (24, 24, 16), (6, 8, 8), [(3, 3, 2)], "x32<12> items 24 "),                     # 288, 216
+    (1, (24, 24, 16), (6, 8, 8), [(4, 3, 1)], "group<128,2,4,0,1> items 144"),          # 288, 144
+    (2, (12, 88, 8), (6, 8, 8), [(2, 5, 1)], "x32<12> items 44 "),                      # 528, 120
+    (3, (6, 80, 16), (6, 8, 8), [(1, 5, 2)], "group<128,2,2,0,1> items 360"),           # 720, 120
+    (2, (12, 24, 48), (6, 8, 8), [(1, 3, 3)], "group<128,2,2,0,1> items 432"),          # 864, 108
     (2, (2, 72, 48), (2, 8, 8), [(1, 9, 6), (1, 1, 6)], "x32<4> items 108 "),           # 432, 216 and 24
     (2, (20, 8, 40), (4, 8, 8), [(5, 1, 5), (5, 1, 1)], "x32<4> items 100 "),           # 400, 200 and 40
     (2, (4, 48, 40), (2, 8, 8), [(2, 6, 5), (2, 5, 5)], "group<128,2,4,0,1> items 240"),    # 480, 240 and 200
