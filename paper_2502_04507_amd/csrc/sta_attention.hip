@@ -1931,11 +1931,11 @@ hipError_t launch_groups(const FwdArgs &a)
     }
     // One LDS stage of V instead of two (head dimension 128): whether n workgroups of qw waves of queries, of which a CU then holds six
     // instead of four, are through in fewer rounds.  Heads of different walks: not where those over half the longest, which run first, are
-    // less than a round of four and the longest is an even share of a place or more, as a wave that is alone at the end is slower with one
+    // less than a round of four and the longest is 0.9 of a place's even share or more, as a wave that is alone at the end is slower with one
     // stage, nor where those ones end beyond a round of six and within two of four, unless the longest is less than 0.45 shares.  (us, two
     // stages, one; waves, units and heads: 64-token tiles (4320; 60 x 10, 20, 12 and 6 x 30) 78, 102, (3200; 400 x 4, 50 x 4) 417, 520; 32-token
-    // tiles (2464; 55 x 8, 9 and 3 x 24) 53, 67, (3840; 96 x 20, 3 x 20) 169, 211; 347 launches that this leaves on two stages: one 3 % slower
-    // in the mean, 30 % at most; 1168 on one: 12 % faster.)
+    // tiles (2464; 55 x 8, 9 and 3 x 24) 53, 67, (3840; 96 x 20, 3 x 20) 169, 211; 383 launches that this leaves on two stages: one 2 % slower
+    // in the mean, 27 % at most; 1717 on one: 12 % faster.)
     const uint64_t long_waves = (uint64_t)a.B * heads_of_long_walks(a, 2) * (p.N / 32);
     auto one_stage = [&](uint64_t n, uint64_t qw) {
         const uint64_t places = 4 * cus, long_ones = long_waves / qw, longest = units * places;
@@ -1943,7 +1943,7 @@ hipError_t launch_groups(const FwdArgs &a)
         uint64_t all = 0;                                   // units of all workgroups
         for (uint32_t r = 0; r < p.heads; ++r) all += walk_of_rank(a, r);
         all *= (uint64_t)a.B * (p.N / 32) / qw;
-        return n > places && !beyond_six(n) && (long_ones > places || longest < all) && !(beyond_six(long_ones) && 20 * longest >= 9 * all);
+        return n > places && !beyond_six(n) && (long_ones > places || 10 * longest < 9 * all) && !(beyond_six(long_ones) && 20 * longest >= 9 * all);
     };
     if (P % 64 == 0) {
         if constexpr (D == 128) {

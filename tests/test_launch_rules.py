@@ -174,6 +174,7 @@ def test_four_waves_a_workgroup_where_the_launch_waits_for_long_walks(H, grid, w
     (36, (1, 64, 64), (1, 8, 8), [(1, 3, 3), (1, 1, 1), (1, 1, 1)], "group<128,2,1,1,1> items 2304"),         # 0.75, 1.1
     (48, (1, 64, 64), (1, 8, 8), [(1, 3, 3), (1, 1, 1), (1, 1, 1)], "group_one_v<128,2,1,1,1> items 3072"),   # 1.0, 0.8
     (40, (1, 64, 64), (1, 8, 8), [(1, 3, 3), (1, 1, 1)], "group_one_v<128,2,1,1,1> items 2560"),              # 1.25
+    (84, (1, 48, 40), (1, 8, 8), [(1, 6, 5), (1, 2, 5), (1, 1, 3), (1, 1, 3)], "group<128,2,1,1,1> items 2520"),      # 0.6, 0.96
     (60, (1, 64, 64), (1, 8, 8), [(1, 3, 3), (1, 1, 1)], "group<128,2,1,1,1> items 3840"),                    # 1.9, 0.48
     (64, (1, 64, 64), (1, 8, 8), [(1, 3, 3), (1, 1, 3)], "group_one_v<128,2,1,1,1> items 4096"),              # 2.0, 0.37
     (70, (1, 64, 64), (1, 8, 8), [(1, 3, 3), (1, 1, 1)], "group_one_v<128,2,1,1,1> items 4480"),              # 2.2
