@@ -2103,13 +2103,14 @@ hipError_t launch_forward(const void *q, const void *k, const void *v, void *o, 
     // 108, 12 and 864 units, four 803, 482; eight 830, 775).
     // Nor is the second round too empty where the long walks, one to a CU, outlast all others beside them (heads of two lengths, us, 12 waves
     // against 4, rounds of all and of the long ones in brackets: 396 and 36 units (1.41, 0.70) 424, 480; 180, 36 (1.41, 0.70) 209, 225; 240, 36
-    // (1.56, 0.78) 298, 313; 336, 72 (1.5, 0.75) 386, 416; 264, 72 (1.5, 0.75) 314, 341; but 324, 60 and 36 (2.25, 0.70) 470, 433): where the longest is 1.04 times
-    // an even share of all or more, what counts is the round of those over three quarters of it.
+    // (1.56, 0.78) 298, 313; 336, 72 (1.5, 0.75) 386, 416; 264, 72 (1.5, 0.75) 314, 341; but 36,
+    // 12 (1.15, 0.82) 68, 53 and 324, 60, 36 (2.25, 0.70) 470, 433): where the longest is 1.04 times an even share of all or more, and the two
+    // rounds are seven tenths full, what counts is the round of those over three quarters of it.
     const uint64_t items = slices * (p.N / 384), rounds = (items + cus - 1) / cus;
     auto full = [&](uint64_t n) { return 10 * n >= (n <= cus ? 7 : 8 * ((n + cus - 1) / cus)) * cus; };
     auto full_of_long_walks = [&]() {
         const uint64_t n = items / p.heads * heads_of_long_walks(a, 3);
-        return rounds == 2 && 25 * (uint64_t)units * cus * p.heads >= 26 * all_units * items && n <= cus && full(n);
+        return rounds == 2 && 10 * items >= 14 * cus && 25 * (uint64_t)units * cus * p.heads >= 26 * all_units * items && n <= cus && full(n);
     };
     if (p.P % 384 == 0 && !waits_for_long_walks(a, items, cus) &&
         (parts_of_tail(a, (uint32_t)items, (uint32_t)cus, 384) > 1 || full(items) || full_of_long_walks()))

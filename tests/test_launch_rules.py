@@ -133,6 +133,7 @@ def test_twelve_waves_for_48_queries_where_no_cu_gets_two_workgroups(H, grid, ti
     (1, 12, (6, 40, 48), [(1, 3, 1), (1, 3, 5)], "x32<12> items 360"),        # 1.41 and half of it 36 units of 180: long ones 0.70 of a round
     (1, 20, (6, 40, 32), [(1, 5, 4), (1, 1, 3)], "x32<12> items 400"),        # 1.56, 36 of 240: 0.78
     (2, 8, (12, 96, 8), [(2, 11, 1), (2, 3, 1)], "x32<12> items 384"),        # 1.5, 72 of 264: 0.75; longest 1.048 shares
+    (1, 7, (6, 56, 48), [(1, 3, 1), (1, 3, 1), (1, 1, 1)], "x32<4> items 882"),       # 1.15, 12 of 36: 0.82
     (1, 12, (6, 40, 48), [(1, 3, 1), (1, 3, 5), (1, 3, 3)], "x32<4> items 1080"),     # 1.41, 36, 180 and 108: 0.47
     (1, 12, (6, 40, 48), [(1, 3, 3), (1, 3, 5)], "x32<4> items 1080"),        # 1.41, 108 of 180: 1.1 rounds of work
     (1, 16, (6, 32, 72), [(1, 1, 5), (1, 3, 9), (1, 3, 1)], "x32<4> items 1728"),     # 2.25, 60, 324 and 36
