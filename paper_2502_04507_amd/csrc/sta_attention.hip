@@ -1957,7 +1957,8 @@ hipError_t launch_groups(const FwdArgs &a)
             // of one group in brackets: 64x64, 3x3 (640) 25.9, 26.0, 23.9; (768) 26.4, 26.3, 25.4; (1024) 29.6, 29.6, 33.1; (1280) 42.4, 37.6,
             // 38.7; (1536) 50, 41, 44; (2048) 62, 59, 57; (3072) 86, 80, 87; 128x128, 5x5 (768) 57, 59, 53; (1280) 97, 85, 85; (1536) 113, 92, 98;
             // (2048) 131, 138, 132; (2560) 169, 159, 161; (4096) 249, 242, 257; 10x40x40 in 320-token tiles (750) 168, 177, 156; (1500) 314, 288,
-            // 302; (2000) 388, 437, 400; (2500) 529, 488, 498; (4000) 765, 745, 779.
+            // 302; (2000) 388, 437, 400; (2500) 529, 488, 498; (4000) 765, 745, 779; 10x24x48 in them, 2x2x4, eight
+            // heads (1440, 300 units), two groups of two stages 547, one of one stage 475.
             const uint64_t blocks = waves / 2, places = 4 * cus;
             if (P % 128 != 0) {
                 if (two) return launch_group<128, 2, 2, 2, true>(a);
@@ -1980,7 +1981,9 @@ hipError_t launch_groups(const FwdArgs &a)
     // dimension 128, with or without key groups (525 waves: 59 us, two groups 74)
     if (D == 64 && two) return launch_group<64, 1, 2, 2, true>(a);
     if constexpr (D == 128) {
-        // one stage of V here too: six waves a CU instead of four
+        // one stage of V here too: six waves a CU instead of four (us, two stages, one; waves, units: 32-token tiles (1536, 9) 25.7, 19.4;
+        // (2304, 9) 36.2, 30.6; (3072, 9) 39.1, 35.2; (4608, 9) 61.8, 50.0; (3072, 25) 79, 73; (7680, 25) 203, 176; 160-token tiles (1080, 45)
+        // 79.6, 56.9; (1440, 45) 80.4, 59.7)
         if (one_stage(waves, 1)) return launch_group<128, 1, 1, 2, true, 1, true>(a);
     }
     return launch_group<D, 1, 1, D == 64 ? 3 : 1, true>(a);
