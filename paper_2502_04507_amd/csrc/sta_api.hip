@@ -65,18 +65,11 @@ int permute_common(const void *src, void *dst, int src_dt, int dst_dt, int B, in
     if (ranges_overlap(src, elems * elem_size(src_dt), dst, elems * elem_size(dst_dt))) return STA_ERR_ALIAS;
 
     sta::PermuteParams p;
-    p.N = (uint32_t)s.N;
-    p.cpr = (uint32_t)(D / 8);
-    p.L_h = grid[1];
-    p.L_w = grid[2];
-    p.T_t = tile[0];
-    p.T_h = tile[1];
-    p.T_w = tile[2];
-    p.n_h = s.n[1];
+    const uint32_t cpr = (uint32_t)(D / 8);
     p.n_w = s.n[2];
-    p.n_tiles = (uint32_t)s.n_tiles;
-    const uint64_t cpt = (uint64_t)s.P * p.cpr;
-    p.seg = p.T_w * p.cpr;
+    const uint64_t cpt = (uint64_t)s.P * cpr;
+    p.seg = tile[2] * cpr;
+    p.T_h = tile[1];
     // exactness condition of the multiply-high division used by the kernel
     if (cpt * p.seg >= ((uint64_t)1 << 32) || cpt * p.T_h >= ((uint64_t)1 << 32)) return STA_ERR_SHAPE;
     p.chunks_per_tile = (uint32_t)cpt;
@@ -84,9 +77,11 @@ int permute_common(const void *src, void *dst, int src_dt, int dst_dt, int B, in
     p.T_h_magic = magic_of(p.T_h);
     const uint64_t tiles = (uint64_t)B * H * s.n_tiles;
     if (tiles * ((cpt + 1023) / 1024) >= ((uint64_t)1 << 31)) return STA_ERR_SHAPE;
-    p.by_tiles = sta::fast_div_of(p.n_tiles);
-    p.by_n_w = sta::fast_div_of(p.n_w);
-    p.by_n_h = sta::fast_div_of(p.n_h);
+    p.line = grid[2] * cpr;
+    p.plane = grid[1] * p.line;
+    p.tile_h = tile[1] * p.line;
+    p.tile_t = (uint64_t)tile[0] * p.plane;
+    p.by_n_h = sta::fast_div_of(s.n[1]);
     hipError_t e = sta::launch_permute(src, dst, src_dt == STA_F32, dst_dt == STA_F32, to_tiled, p, tiles,
                                        static_cast<hipStream_t>(hip_stream));
     return e == hipSuccess ? STA_OK : STA_ERR_HIP;

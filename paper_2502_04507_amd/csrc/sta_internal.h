@@ -26,20 +26,19 @@ inline FastDiv fast_div_of(uint32_t d)
 
 // ---- permutation -----------------------------------------------------------
 struct PermuteParams {
-    uint32_t N;                 // tokens per (b,h) slice
-    uint32_t cpr;               // 8-element chunks per token row (D / 8)
-    uint32_t L_h, L_w;          // grid
-    uint32_t T_t, T_h, T_w;     // tile
-    uint32_t n_h, n_w;          // tile grid (h, w)
-    uint32_t n_tiles;
-    uint32_t chunks_per_tile;   // P * cpr
-    uint32_t seg, seg_magic;    // T_w * cpr chunks per contiguous run, ceil(2^32/seg)
-    uint32_t T_h_magic;         // ceil(2^32 / T_h)
-    uint32_t parts;             // workgroups per tile
+    FastDiv by_row;             // workgroups per row of tiles along w
+    FastDiv by_parts;           // workgroups per tile
+    FastDiv by_n_h;             // rows of tiles per layer of tiles (tiles at one place along t)
     uint32_t blocks;            // workgroups
-    uint32_t row_blocks;        // workgroups per row of tiles along w, which one XCD moves
-    uint32_t in_rounds;         // workgroups in full rounds of eight such rows
-    FastDiv by_round, by_parts, by_tiles, by_n_w, by_n_h;       // divisions of a workgroup id, a tile number and its row
+    uint32_t in_rounds;         // workgroups in full rounds of eight rows of tiles, one row per XCD
+    uint32_t n_w;               // tiles per row
+    // in chunks of 8 elements
+    uint32_t chunks_per_tile;   // P * D / 8
+    uint32_t seg, seg_magic;    // contiguous run of a tile in raster order, ceil(2^32/seg)
+    uint32_t T_h, T_h_magic;    // runs of a tile in one raster plane, ceil(2^32 / T_h)
+    uint32_t line, plane;       // raster line and plane of tokens
+    uint32_t tile_h;            // from a tile to the next along h
+    uint64_t tile_t;            // and along t; slices follow each other at multiples of it
 };
 
 // Fills in what depends on the split of a tile over workgroups; tiles of all slices.

@@ -112,25 +112,25 @@ __global__ __launch_bounds__(kPermuteThreads) void sta_permute_kernel(const void
                                                                      void *__restrict__ dst,
                                                                      sta::PermuteParams p)
 {
-    // (divisions prepared by the host: found in the kernel, they took a tenth of the launch at 17 MB, 4.36 -> 3.93 us; 4 MB 2.88 -> 2.66)
-    uint32_t id = (blockIdx.y << kGridShift) + blockIdx.x;
-    if (id >= p.blocks) return;
-    if (id < p.in_rounds) {
-        const uint32_t in_round = id - fast_div(id, p.by_round) * p.by_round.d;
-        id += (in_round & 7) * p.row_blocks + (in_round >> 3) - in_round;
-    }
-    const uint32_t tile_linear = fast_div(id, p.by_parts), part = id - tile_linear * p.parts;
-    const uint32_t outer = fast_div(tile_linear, p.by_tiles), tile_id = tile_linear - outer * p.n_tiles;         // b*H + h
-    const uint32_t row = fast_div(tile_id, p.by_n_w), tw = tile_id - row * p.n_w;
-    const uint32_t tt = fast_div(row, p.by_n_h), th = row - tt * p.n_h;
+    // Every argument is asked for at once and waited for once.  Left to the compiler they come where they are first used, behind the
+    // bounds of the grid, of a round and of the tile: four waits one after the other, and three more divisions (the places of a tile along
+    // t and of its slice are one number, since slices follow each other like the layers of tiles of one).  us from tensors in turn that are
+    // not in the L2 caches, before and now, a plain copy of the size: 0.2 MB 2.38, 2.27; fp32 to 1.3 MB of bf16 2.64, 2.50; 4 MB 2.98, 2.73,
+    // 2.61; 17 MB 6.39, 6.01, 5.91; 43 MB 15.4, 15.2, 15.8; 67 MB 23.6, 23.2, 23.3; 85 MB 28.7, 28.4, 28.6; back 4 MB 2.94, 2.67; 67 MB 23.4, 22.9.
+    asm volatile("" ::"s"(src), "s"(dst), "s"(p.by_row.d), "s"(p.by_row.magic), "s"(p.by_row.pre), "s"(p.by_row.post), "s"(p.by_parts.d), "s"(p.by_parts.magic),
+                 "s"(p.by_parts.pre), "s"(p.by_parts.post), "s"(p.by_n_h.d), "s"(p.by_n_h.magic), "s"(p.by_n_h.pre), "s"(p.by_n_h.post));
+    asm volatile("" ::"s"(p.blocks), "s"(p.in_rounds), "s"(p.n_w), "s"(p.chunks_per_tile), "s"(p.seg), "s"(p.seg_magic), "s"(p.T_h),
+                 "s"(p.T_h_magic), "s"(p.line), "s"(p.plane), "s"(p.tile_h), "s"(p.tile_t));
+    const uint32_t id = (blockIdx.y << kGridShift) + blockIdx.x;
+    const bool left_over = id >= p.in_rounds;
+    const uint32_t turn = left_over ? id : id >> 3;
+    const uint32_t q = fast_div(turn, p.by_row), in_row = turn - q * p.by_row.d;
+    const uint32_t row = left_over ? q : 8 * q + (id & 7);                  // row of tiles along w, of all slices
+    const uint32_t tw = fast_div(in_row, p.by_parts), part = in_row - tw * p.by_parts.d;
+    const uint32_t layer = fast_div(row, p.by_n_h), th = row - layer * p.by_n_h.d;
 
-    const size_t slice = (size_t)outer * p.N * p.cpr;       // chunk offset of this (b,h) slice
-    const size_t tiled_base = slice + (size_t)tile_id * p.chunks_per_tile;
-    // raster chunk index of the tile's first token
-    const size_t raster_tile = slice + (((size_t)tt * p.T_t * p.L_h + (size_t)th * p.T_h) * p.L_w + (size_t)tw * p.T_w) * p.cpr;
-    const uint32_t row_stride_h = p.L_w * p.cpr;            // chunks per raster row of tokens (fixed t,h)
-    const uint32_t row_stride_t = p.L_h * row_stride_h;
-
+    const size_t tiled_tile = ((size_t)row * p.n_w + tw) * p.chunks_per_tile;
+    const size_t raster_tile = layer * p.tile_t + (size_t)th * p.tile_h + tw * p.seg;         // the tile's first token
     const uint32_t first = part * (kPermuteThreads * CHUNKS) + threadIdx.x;
     Chunk8bf16 b[CHUNKS];
     Chunk8f32 f[CHUNKS];
@@ -138,20 +138,18 @@ __global__ __launch_bounds__(kPermuteThreads) void sta_permute_kernel(const void
 #pragma unroll
     for (int u = 0; u < CHUNKS; ++u) {
         const uint32_t idx = first + u * kPermuteThreads;
-        if (idx < p.chunks_per_tile) {
-            const uint32_t seg = small_div(idx, p.seg, p.seg_magic);          // which (i_t, i_h) run
-            const uint32_t off = idx - seg * p.seg;
-            const uint32_t it = small_div(seg, p.T_h, p.T_h_magic);
-            const uint32_t ih = seg - it * p.T_h;
-            const size_t raster = raster_tile + (size_t)it * row_stride_t + (size_t)ih * row_stride_h + off;
-            const size_t tiled = tiled_base + idx;
-            load8<SRC_F32, STREAM>(src, TO_TILED ? raster : tiled, b[u], f[u]);
-            dst_idx[u] = TO_TILED ? tiled : raster;
-        }
+        const uint32_t seg = small_div(idx, p.seg, p.seg_magic);            // which (i_t, i_h) run
+        const uint32_t off = idx - seg * p.seg;
+        const uint32_t it = small_div(seg, p.T_h, p.T_h_magic);
+        const uint32_t ih = seg - it * p.T_h;
+        const size_t raster = raster_tile + (size_t)it * p.plane + (ih * p.line + off);
+        const size_t tiled = tiled_tile + idx;
+        dst_idx[u] = TO_TILED ? tiled : raster;
+        if (idx < p.chunks_per_tile && id < p.blocks) load8<SRC_F32, STREAM>(src, TO_TILED ? raster : tiled, b[u], f[u]);
     }
 #pragma unroll
     for (int u = 0; u < CHUNKS; ++u)
-        if (first + u * kPermuteThreads < p.chunks_per_tile) store8<SRC_F32, DST_F32>(dst, dst_idx[u], b[u], f[u]);
+        if (first + u * kPermuteThreads < p.chunks_per_tile && id < p.blocks) store8<SRC_F32, DST_F32>(dst, dst_idx[u], b[u], f[u]);
 }
 
 template <bool TO_TILED, bool STREAM>
@@ -182,14 +180,13 @@ hipError_t launch_permute(const void *src, void *dst, bool src_f32, bool dst_f32
 {
     const bool streamed = tiles * p.chunks_per_tile * (src_f32 ? 32 : 16) > kStreamAbove;
     const uint32_t per_block = kPermuteThreads * (src_f32 && !dst_f32 && !streamed ? 2 : 1);
-    p.parts = (p.chunks_per_tile + per_block - 1) / per_block;
-    if (tiles * p.parts >= ((uint64_t)1 << 31)) return hipErrorInvalidValue;         // terabytes
-    p.blocks = (uint32_t)(tiles * p.parts);
-    p.row_blocks = p.n_w * p.parts;
-    const uint32_t round = p.row_blocks <= p.blocks / 8 ? 8 * p.row_blocks : 0;
-    p.in_rounds = round ? p.blocks / round * round : 0;
-    p.by_parts = fast_div_of(p.parts);
-    p.by_round = fast_div_of(round ? round : 1);
+    const uint32_t parts = (p.chunks_per_tile + per_block - 1) / per_block;
+    if (tiles * parts >= ((uint64_t)1 << 31)) return hipErrorInvalidValue;           // terabytes
+    p.blocks = (uint32_t)(tiles * parts);
+    p.by_parts = fast_div_of(parts);
+    p.by_row = fast_div_of(p.n_w * parts);
+    const uint64_t round = (uint64_t)8 * p.by_row.d;
+    p.in_rounds = (uint32_t)(p.blocks / round * round);
     if (streamed)
         return to_tiled ? launch<true, true>(src, dst, src_f32, dst_f32, p, stream)
                         : launch<false, true>(src, dst, src_f32, dst_f32, p, stream);
