@@ -27,7 +27,7 @@
 // products are defined).
 // All kernels: any tile of a multiple of 32 tokens.  A workgroup's columns are the largest of a few sizes that divides the
 // tile; launches too small for the chip are cut into walk groups (see WalkShare), the smallest ones into four groups of one
-// wave each, which has its LDS to itself and passes no barrier until the groups are summed.
+// wave each, or eight, which has its LDS to itself and passes no barrier until the groups are summed.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -238,7 +238,7 @@ constexpr int max_of(int a, int b) { return a > b ? a : b; }
 
 // ---------------------------------------------------------------------------------------------------------
 // dQ.  One workgroup of QW waves per 32 * QW queries (times G walk groups); a lane holds query column c16 of its wave's two
-// 16-query blocks.  At head dimension 128 211-212 registers, two waves per SIMD; at 64 128 and four (8 bytes of scratch in the
+// 16-query blocks.  At head dimension 128 206-210 registers, two waves per SIMD; at 64 128 and four (8 bytes of scratch in the
 // shape of three waves and two walk groups; the
 // statistic enters the exponent by a fused multiply-add instead of occupying eight registers of initial values, and the
 // transposed fragments are read two channel blocks at a time; three waves per SIMD before: 32 heads of a 64x64 image 42.7 ->
@@ -247,12 +247,15 @@ constexpr int max_of(int a, int b) { return a > b ? a : b; }
 // and dP^T = V dO^T - delta (the statistics of the lane's query as the initial value, so that neither a subtraction nor a
 // fused multiply-add per element is left), dS^T = 2^(c S^T) o dP^T, dQ^T += K^T dS^T; 16 matrix instructions each at head
 // dimension 128, 8 at 64.
+// QW = 1 with walk groups ("solo", for the small launches): as in the dK/dV kernel the stage belongs to one wave, which refills V as
+// soon as dP is formed and K after its last product.  One buffer for each, as eight groups at head dimension 128 have to share the
+// 160 KB of a CU (143 KB; with two for each four groups took 135); walks of 50 at four groups are no slower for it.
 // The row statistics are formed here, from the dO fragments the wave holds anyway and the same fragments of O, and written
 // for the dK/dV kernel (a kernel of their own for them read dO once more: 6.8 us of a 345 us training step at 16,384 tokens
 // x 8 heads of dimension 64, 0.23 ms of 53 ms at 115,200 x 24 of 128).
 // ---------------------------------------------------------------------------------------------------------
 template <int D, int QW, int G, bool DMA>
-__global__ __attribute__((amdgpu_flat_work_group_size(QW * G * 64, QW * G * 64), amdgpu_waves_per_eu(QW == 1 ? (D == 64 ? 2 : 1) : (D == 64 ? 4 : 2))))
+__global__ __attribute__((amdgpu_flat_work_group_size(QW * G * 64, QW * G * 64), amdgpu_waves_per_eu(QW == 1 ? (D == 64 || G == 8 ? 2 : 1) : (D == 64 ? 4 : 2))))
 void sta_bwd_dq_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restrict__ k, const bf16_raw *__restrict__ v,
                        const bf16_raw *__restrict__ o, const bf16_raw *__restrict__ d_o, const float *__restrict__ lse,
                        float *__restrict__ neg_delta, float *__restrict__ neg_lse, bf16_raw *__restrict__ d_q,
@@ -263,11 +266,13 @@ void sta_bwd_dq_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restric
     constexpr int COLS = QW * 32;                       // queries per workgroup
     constexpr int STAGE_B = 2 * L::Tile;
     constexpr int K_TILE = 0, V_TILE = L::Tile;
-    constexpr int GROUP_B = 2 * STAGE_B;                // LDS of one walk group: two stages
+    constexpr bool SOLO = QW == 1 && G > 1;             // a wave with a stage of its own: no barriers, single buffers
+    static_assert(!SOLO || DMA, "waited for by count");
+    constexpr int GROUP_B = SOLO ? STAGE_B : 2 * STAGE_B;       // LDS of one walk group
     constexpr int OPS = 2 * L::Groups;                  // DMA instructions per sub-block
     constexpr int WAVE_OPS = (OPS + QW - 1) / QW;       // at most this many per wave
     constexpr int WAVE_OUT = 16 * L::RowB;
-    constexpr int SMEM = QW == 1 && G > 1 ? G * GROUP_B + 32 * L::RowB
+    constexpr int SMEM = SOLO ? G * GROUP_B + 32 * L::RowB
                                           : max_of(G * GROUP_B, max_of((G / 2) * QW * CB * 2 * 1024, QW * WAVE_OUT));
     __shared__ __attribute__((aligned(1024))) char smem[SMEM];
 
@@ -307,7 +312,23 @@ void sta_bwd_dq_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restric
         }
         ++issued;
     };
-    issue_next();
+    auto issue_operand = [&](auto is_v_c, uint32_t row) __attribute__((always_inline)) {     // single buffers
+        constexpr bool IS_V = decltype(is_v_c)::value;
+        uint32_t off = src_lane_off;
+        asm volatile("" : "+v"(off));
+#pragma unroll
+        for (int j = 0; j < L::Groups; ++j)
+            stage_group<DMA>((IS_V ? vh : kh) + (size_t)(row + L::GroupRows * j) * L::RowB + off,
+                             smem + group * GROUP_B + (IS_V ? V_TILE : K_TILE) + j * L::Group, lane);
+    };
+    if constexpr (SOLO) {
+        if (share.n_units > 0) {
+            issue_operand(std::true_type{}, share.walk.next_row);
+            issue_operand(std::false_type{}, share.walk.next_row);
+        }
+    } else {
+        issue_next();
+    }
 
     uint32_t row_addr[KS], tr_addr[4];
     L::addresses((uint32_t)(uintptr_t)smem + (uint32_t)(group * GROUP_B), lane, row_addr, tr_addr);
@@ -349,14 +370,7 @@ void sta_bwd_dq_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restric
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb) dQ[cb][qb] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-    auto sub_block = [&](auto stage_c, int unit) __attribute__((always_inline)) {
-        constexpr int ST = decltype(stage_c)::value * STAGE_B;
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        // (the stages of a single wave are its own; operands staged by plain stores have to be waited for)
-        if constexpr (QW > 1 || !DMA) __syncthreads();
-        issue_next();
-        if (G > 1 && unit >= share.n_units) return;
-        floatx4 S[2][2], dP[2][2];                      // [key block][query block]
+    auto start_at_statistics = [&](floatx4 (&S)[2][2], floatx4 (&dP)[2][2]) __attribute__((always_inline)) {
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -364,14 +378,10 @@ void sta_bwd_dq_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restric
                 S[kb][qb] = s_init[qb];
                 dP[kb][qb] = dp_init[qb];
             }
-        staged_rows_times_resident<D, ST + K_TILE>(row_addr, Qr, S);    // K Q^T - lse / scale (128), K Q^T (64)
-        staged_rows_times_resident<D, ST + V_TILE>(row_addr, Gr, dP);   // V dO^T - delta
-        StagedTransposedProduct<D, ST + K_TILE, D == 64 ? 2 : 4> k_t;
-        k_t.prefetch(tr_addr);
-        __builtin_amdgcn_sched_barrier(0);
-        // dS^T, rounded to bf16 and packed as the B operand of the last product: k index 8*g4 + i is key 4*g4 + i
-        // of the first key block (i < 4) or of the second
-        bf16x8 dSb[2];
+    };
+    // dS^T, rounded to bf16 and packed as the B operand of the last product: k index 8*g4 + i is key 4*g4 + i
+    // of the first key block (i < 4) or of the second
+    auto products = [&](const floatx4 (&S)[2][2], const floatx4 (&dP)[2][2], bf16x8 (&dSb)[2]) __attribute__((always_inline)) {
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb)
 #pragma unroll
@@ -381,13 +391,56 @@ void sta_bwd_dq_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restric
                     const float x = D == 64 ? fmaf(S[kb][qb][e], c, exp_init[qb]) : S[kb][qb][e] * c;
                     dSb[qb][4 * kb + e] = static_cast<__bf16>(__builtin_amdgcn_exp2f(x) * dP[kb][qb][e]);
                 }
+    };
+    auto sub_block = [&](auto stage_c, int unit) __attribute__((always_inline)) {
+        constexpr int ST = decltype(stage_c)::value * STAGE_B;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        // (the stages of a single wave are its own; operands staged by plain stores have to be waited for)
+        if constexpr (QW > 1 || !DMA) __syncthreads();
+        issue_next();
+        if (G > 1 && unit >= share.n_units) return;
+        floatx4 S[2][2], dP[2][2];                      // [key block][query block]
+        bf16x8 dSb[2];
+        start_at_statistics(S, dP);
+        staged_rows_times_resident<D, ST + K_TILE>(row_addr, Qr, S);    // K Q^T - lse / scale (128), K Q^T (64)
+        staged_rows_times_resident<D, ST + V_TILE>(row_addr, Gr, dP);   // V dO^T - delta
+        StagedTransposedProduct<D, ST + K_TILE, D == 64 ? 2 : 4> k_t;
+        k_t.prefetch(tr_addr);
+        __builtin_amdgcn_sched_barrier(0);
+        products(S, dP, dSb);
         k_t.run(tr_addr, dSb, dQ);                                       // dQ^T += K^T dS^T
     };
-    for (int u = 0; u < share.n_steps; u += 2) {
-        sub_block(std::integral_constant<int, 0>{}, u);
-        if (u + 1 < share.n_steps) sub_block(std::integral_constant<int, 1>{}, u + 1);
+    if constexpr (SOLO) {
+#pragma unroll 1
+        for (int u = 0; u < share.n_units; ++u) {
+            const bool more = u + 1 < share.n_units;
+            floatx4 S[2][2], dP[2][2];
+            bf16x8 dSb[2];
+            start_at_statistics(S, dP);
+            wait_dma<L::Groups>();                                        // V; K has been requested behind it
+            staged_rows_times_resident<D, V_TILE>(row_addr, Gr, dP);
+            share.walk.advance();
+            if (more) {
+                issue_operand(std::true_type{}, share.walk.next_row);
+                wait_dma<L::Groups>();                                    // K; the next V has been requested behind it
+            } else {
+                wait_dma<0>();
+            }
+            staged_rows_times_resident<D, K_TILE>(row_addr, Qr, S);
+            StagedTransposedProduct<D, K_TILE, D == 64 ? 2 : 4> k_t;
+            k_t.prefetch(tr_addr);
+            __builtin_amdgcn_sched_barrier(0);
+            products(S, dP, dSb);
+            k_t.run(tr_addr, dSb, dQ);
+            if (more) issue_operand(std::false_type{}, share.walk.next_row);
+        }
+    } else {
+        for (int u = 0; u < share.n_steps; u += 2) {
+            sub_block(std::integral_constant<int, 0>{}, u);
+            if (u + 1 < share.n_steps) sub_block(std::integral_constant<int, 1>{}, u + 1);
+        }
     }
-    if constexpr (QW == 1 && G > 1) {
+    if constexpr (SOLO) {
         char *rows = smem + G * GROUP_B;
         merge_waves<D, G, GROUP_B>(smem, rows, group, lane, dQ, c * kLn2);
         store_rows<D, G * 64>(rows, d_q + my_row * D, tid);
@@ -411,7 +464,8 @@ void sta_bwd_dq_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restric
 // S and dP start.  UPS sub-blocks per stage, i.e. per barrier.
 // NW = 1 ("solo", for the small launches): the stage belongs to one wave, which needs no barrier, only its own requests to have
 // landed, and refills either operand as soon as it has read it: half the LDS, so that a CU holds eight such waves at head
-// dimension 128 and twelve at 64.  There dP and dS come before the product with P, which frees dO first.
+// dimension 128 and twelve at 64 (of eight groups the eight of one workgroup; 168 registers and 12 bytes of scratch, at 128 52,
+// outside the loop).  There dP and dS come before the product with P, which frees dO first.
 // What bounds it: matrix pipe and power on large launches (30x48x80, 24 heads, window 3x3x3, head dimension 128: 22.1 ms, 1330
 // TFLOP/s; 64: 11.5 ms, 1280).  Before, each 32 keys were served by a pair of waves, one for S, P and dV, one for dP, dS and dK,
 // with P handed over through LDS at a barrier of its own.  Entry point, pairs against this kernel, us: 30x48x80, 24 heads of 128
@@ -997,7 +1051,7 @@ hipError_t launch_dq(const BwdArgs &a)
     const BwdPlan plan = make_plan(a, QW * 32, false, false);
     if (a.note) {
         char shape[64];
-        snprintf(shape, sizeof shape, "dq<%d,%d,%d,%d>", D, QW, G, (int)DMA);
+        snprintf(shape, sizeof shape, "dq<%d,%d,%d,%d>%s", D, QW, G == 8 ? 4 : G, (int)DMA, G == 8 ? " doubled" : "");
         return note_launch(a, plan, shape);
     }
     return sta::launch_kernel(sta_bwd_dq_kernel<D, QW, G, DMA>, dim3(plan.deal.total), dim3(QW * G * 64), a.stream, a.q, a.k, a.v, a.o, a.d_o, a.lse,
@@ -1042,7 +1096,7 @@ hipError_t launch_dkv(const BwdArgs &a)
     const BwdPlan plan = make_plan(a, NW * 32, row_major, row_major && longest_first);
     if (a.note) {
         char shape[64];
-        snprintf(shape, sizeof shape, "dkv<%d,%d,%d,%d,%d>", D, NW, G, UPS, (int)DMA);
+        snprintf(shape, sizeof shape, "dkv<%d,%d,%d,%d,%d>%s", D, NW, G == 8 ? 4 : G, UPS, (int)DMA, G == 8 ? " doubled" : "");
         return note_launch(a, plan, shape);
     }
     return sta::launch_kernel(sta_bwd_dkv_kernel<D, NW, G, UPS, DMA>, dim3(plan.deal.total), dim3(NW * G * 64), a.stream, a.q, a.k, a.v, a.d_o,
@@ -1081,6 +1135,18 @@ hipError_t launch_dkv_pairs(const BwdArgs &a)
 // 384-token tiles, one head (216 waves) of 64 100, 87, of 128 151, 131, two (432) 107, 110; 64x64 image, 5x5, one head (128) of 128 149,
 // 140, three (384) 150, 157; 4x12x24 in 96-token tiles, one head (36) of 64 39.5, 31.2, of 128 59.6, 47.3; twelve (432) 40.6, 35.4
 // and 61.3, 61.9.
+//
+// Eight groups of one wave in both kernels where no CU gets a second workgroup and the walk has 40 sub-blocks or more: two waves a
+// SIMD, of which one computes while the other waits, and half the steps.  Entry point (with the permutation), four against eight, dQ
+// alone, dK/dV alone and both; waves and units: head dimension 64 (216, 216) 125.1, -6.6, -13.4, -19.2 %; (108, 108) 79.3, -4.0,
+// -8.6, -12.6; (72, 48) 64.0, -2.7, -6.0, -8.9; (56, 40) 54.3, -0.6, -5.9, -6.3; (240, 45) 59.9, -1.3, -4.8, -6.3; (144, 36) 50.5,
+// +0.2, -2.1, -1.9; (256, 18) 48.4, +0.4, +0.5, +0.1; 128 (216, 216) 203.4, -6.2, -9.8, -15.2; (108, 108) 120.3, -4.3, -5.8, -10.0;
+// (72, 48) 92.6, -2.7, -4.4, -7.0; (56, 40) 75.7, 0.0, -3.3, -3.2; (240, 45) 83.7, -0.4, -2.6, -2.8; (144, 36) 69.0, +1.4, +0.4, +1.9;
+// (256, 18) 63.4, +3.1, -0.9, +2.3.  With a second workgroup on some CUs the sum of eight and the LDS that they hold cost more:
+// 64 (324, 108) 99.3, 0.0, +5.5, +5.5; (432, 54) 78.6, +2.0, +5.5, +7.5; 128 (288, 27) 85.7, 0.0, +8.9, +8.9 (and (384, 50), 64x64
+// images, -5.7 and -4.2 % in dK/dV, which the rule leaves out).
+bool eight_groups(uint64_t waves, uint32_t units) { return waves <= (uint64_t)sta::compute_units() && units >= 40; }
+
 template <int D>
 hipError_t dispatch_dq(const BwdArgs &a)
 {
@@ -1118,6 +1184,7 @@ hipError_t dispatch_dq(const BwdArgs &a)
         }
     }
     if (P % 128 != 0 && !(sta::dma_aligned(a.k) && sta::dma_aligned(a.v))) return launch_dq<D, 1, 1, false>(a);
+    if (eight_groups(waves, units)) return launch_dq<D, 1, 8>(a);
     if (waves <= (D == 64 && P % 96 == 0 && P % 128 != 0 ? 2 * cus : cus)) return launch_dq<D, 1, 4>(a);
     if (P % 96 == 0 && P % 128 != 0) return two ? launch_dq<D, 3, 2>(a) : launch_dq<D, 3, 1>(a);
     if (P % 64 != 0) return launch_dq<D, 1, 1>(a);
@@ -1151,6 +1218,7 @@ hipError_t dispatch_dkv(const BwdArgs &a)
     if (P % 64 == 0 && P % 128 != 0 && units >= 48) solo = (D == 64 ? 8 : 3) * cus;
     if (P % 64 != 0 && P % 96 == 0) solo = (D == 64 ? 18 : 6) * cus;
     if (P % 64 != 0 && P % 96 != 0 && units >= 24) solo = 2 * cus;
+    if (eight_groups(waves, units)) return launch_dkv<D, 1, 8>(a);
     if (waves <= solo) return launch_dkv<D, 1, 4>(a);
     if (P % 64 != 0) {
         if constexpr (D == 128) return P % 96 == 0 ? launch_dkv_pairs<3, 2>(a) : launch_dkv_pairs<1, 1>(a);
