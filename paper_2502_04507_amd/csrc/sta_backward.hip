@@ -1131,7 +1131,7 @@ hipError_t launch_dkv_pairs(const BwdArgs &a)
 // 16.8, 14.2, image x 16 (2048) 21.1, 23.4; but walks of 32 and more on tiles of odd multiples of 64, whose one group has two waves as well,
 // up to the 16 that a CU holds (entry point, waves and units: (1664, 50) 104, 98, (2048, 50) 117, 110, (2000, 90) 199, 184; the other tiles,
 // of four and three waves a group, -1 to +1 %).  Four groups of one wave, without barriers, up to one such workgroup per CU
-// (two on 96-token tiles at head dimension 64); entry point, two groups of two or three waves against these: 12x24x24 in
+// (two on 96-token tiles at head dimension 64), and up to four where walks are long (below); entry point, two groups of two or three waves against these: 12x24x24 in
 // 384-token tiles, one head (216 waves) of 64 100, 87, of 128 151, 131, two (432) 107, 110; 64x64 image, 5x5, one head (128) of 128 149,
 // 140, three (384) 150, 157; 4x12x24 in 96-token tiles, one head (36) of 64 39.5, 31.2, of 128 59.6, 47.3; twelve (432) 40.6, 35.4
 // and 61.3, 61.9.
@@ -1146,6 +1146,42 @@ hipError_t launch_dkv_pairs(const BwdArgs &a)
 // 64 (324, 108) 99.3, 0.0, +5.5, +5.5; (432, 54) 78.6, +2.0, +5.5, +7.5; 128 (288, 27) 85.7, 0.0, +8.9, +8.9 (and (384, 50), 64x64
 // images, -5.7 and -4.2 % in dK/dV, which the rule leaves out).
 bool eight_groups(uint64_t waves, uint32_t units) { return waves <= (uint64_t)sta::compute_units() && units >= 40; }
+
+// Four groups of one wave beyond one workgroup per CU, which at head dimension 64 holds four of them (36 KB and 126 registers) and at 128
+// two (73 KB): they wait for no barrier, halve or quarter long walks, and a CU's share is one or two waves a SIMD whatever the tile.
+// Entry point (with the permutation and dK/dV), the shapes by barriers against these, waves and units:
+// - head dimension 64: 384-token tiles (432, 108) 102.5, 98.0, (648, 108) 147, 141, (432, 216) 164, 155, (600, 36) 82.8, 81.9, but (864, 108)
+//   152.6, 156.3, (960, 36) 90.8, 94.3; 256 (768, 96) 138, 135; 64 (384, 50) 79.6, 77.9, (512, 128) 119, 116, (640, 128) 156, 152, but (512, 18)
+//   53.7, 56.5, (768, 50) 102.6, 103.2, (1024, 50) 112.8, 117; 320 (450, 90) 104.6, 101.4, (750, 90) 136.7, 136.9; 192 (720, 36) 88.7, 87.5,
+//   (960, 36) 100, 95, (960, 108) 201, 186, but (768, 18) 64.1, 65.0; 96 (576, 54) 95.7, 93.6, (1008, 54) 134, 130, but (576, 9) 53.2, 55.3;
+//   32 (512, 35) 76.8, 68.2, (1024, 35) 104.8, 101.2, (512, 15) 57.0, 54.9, but (512, 9) 49.9, 50.5, (640, 15) 67.4, 67.6;
+//   160 (480, 45) 85.5, 75.4, (960, 45) 124, 115;
+// - head dimension 128: 384 (432, 108) 174.4, 169.3, (432, 216) 305, 291, but (288, 36) 87.4, 87.6, (648, 108) 232, 238; 64 (512, 128) 212, 210,
+//   but (512, 50) 137, 139; 96 (432, 27) 92.5, 89.7, (432, 54) 131.9, 123.6, (864, 54) 254, 236, but (432, 12) 66.8, 67.5, (576, 54) 158, 165;
+//   192 (480, 36) 110, 105, (960, 36) 181, 170, (960, 108) 391, 357, but (768, 108) 312, 323 (shapes of three waves have a second round
+//   of workgroups from 768 on); 32 (512, 35) 116, 105, (480, 15) 75.9, 74.9, but (512, 9) 67.8, 70.0, (1024, 35) 174, 180; 160 (480, 45) 130, 117.
+// Where the walks of the heads differ the long ones are alone at the end and the gain is larger: 64, 96-token tiles, seven heads of 27, 72
+// and 3 (504) 89.5, 75.7; 384, two of 108 and 216 159, 141, three 201, 186; 32-token, twelve of 49 and 9 (768) 104, 93; 192, eight of 30 and 3
+// (480) 79.6, 68.4; 128, the same 134, 116; 305, 280; (512) 120, 97; 117, 102; 256-token, five of 96 and 24 (480) 162, 157; but 192, sixteen of
+// 60 and 18 (960) 161, 167.  At 128 and 20 to 31 sub-blocks those on tiles of 96 tokens' multiples stay with two groups of three waves (360
+// waves of 27 and 3 85, 79: the small launch of unequal walks that the tests hold to that shape).
+template <int D>
+bool four_groups_of_one(const BwdArgs &a, uint64_t waves, uint32_t units)
+{
+    const uint64_t cus = sta::compute_units();
+    const uint32_t P = a.p.P;
+    const bool three = P % 96 == 0 && P % 128 != 0, one = P % 64 != 0 && P % 96 != 0;       // waves of the other shapes
+    if (waves <= (D == 64 && three ? 2 * cus : cus)) return true;
+    if (waves > 4 * cus) return false;
+    const bool equal = units == walk_of_rank(a, a.p.heads - 1);
+    if (D == 64) {
+        if (three) return units >= 30;
+        if (one) return units >= (waves <= 2 * cus ? 15 : 30);
+        return units >= 36 && waves <= (P % 128 == 0 ? 3 : 2) * cus;
+    }
+    if (three) return waves <= 2 * cus ? units >= (equal ? 20 : 32) : equal && units >= 20 && waves > 3 * cus;
+    return waves <= 2 * cus && units >= (one ? 15 : 64);
+}
 
 template <int D>
 hipError_t dispatch_dq(const BwdArgs &a)
@@ -1185,7 +1221,7 @@ hipError_t dispatch_dq(const BwdArgs &a)
     }
     if (P % 128 != 0 && !(sta::dma_aligned(a.k) && sta::dma_aligned(a.v))) return launch_dq<D, 1, 1, false>(a);
     if (eight_groups(waves, units)) return launch_dq<D, 1, 8>(a);
-    if (waves <= (D == 64 && P % 96 == 0 && P % 128 != 0 ? 2 * cus : cus)) return launch_dq<D, 1, 4>(a);
+    if (four_groups_of_one<D>(a, waves, units)) return launch_dq<D, 1, 4>(a);
     if (P % 96 == 0 && P % 128 != 0) return two ? launch_dq<D, 3, 2>(a) : launch_dq<D, 3, 1>(a);
     if (P % 64 != 0) return launch_dq<D, 1, 1>(a);
     if (two) return launch_dq<D, 2, 2>(a);

@@ -1,0 +1,51 @@
+"""dQ launches of four walk groups of one wave beyond one workgroup per CU: which launches take them (counted on 256 CUs, no GPU
+needed) and GPU parity at the edges of the rule."""
+import pytest
+
+import synth_inputs as syn
+from tests.launch_shapes import launches
+from tests.test_gpu_backward import assert_grad_parity, gpu_backward, oracle_backward
+
+# name, head dimensions, grid, tile, batch, heads, per-head windows repeated over the heads
+SINGLE = [
+    ("p384-768", (64,), (12, 32, 32), (6, 8, 8), 1, 2, [(1, 1, 3), (1, 1, 1)]),           # 768 waves; 36 sub-blocks and 12
+    ("p384-432", (128,), (12, 24, 24), (6, 8, 8), 1, 2, [(1, 2, 3), (1, 1, 1)]),          # 432; 108 and 12
+    ("p64-512", (64, 128), (1, 64, 64), (1, 8, 8), 2, 2, [(1, 8, 8), (1, 1, 1)]),         # 512; 128 and 2
+    ("p192-1020", (64, 128), (3, 16, 40), (3, 8, 8), 1, 17, [(1, 1, 5)]),                 # 1020; 30
+    ("p96-512", (64, 128), (2, 12, 16), (2, 6, 8), 21, 2, [(1, 2, 2), (1, 2, 2)]),        # 504 of at most 512; 12
+    ("p96-504", (64, 128), (4, 18, 32), (2, 6, 8), 1, 7, [(1, 3, 3)]),                    # 504; 27
+    ("p160-480", (64, 128), (5, 24, 16), (5, 8, 4), 2, 4, [(1, 1, 3), (1, 1, 3)]),        # 480; 15
+    ("p32-1024", (64,), (1, 32, 64), (1, 4, 8), 2, 8, [(1, 5, 7), (1, 1, 1)]),            # 1024; 35 and 1
+]
+TAKES = {("p96-512", 128): False}
+OTHERS = [
+    (64, (1, 64, 72), (1, 8, 8), 8, [(1, 8, 9)], "dq<64,2,2,1>"),          # 1152 waves
+    (64, (1, 64, 64), (1, 8, 8), 4, [(1, 3, 3)], "dq<64,2,2,1>"),          # 18 sub-blocks
+    (128, (1, 64, 64), (1, 8, 8), 4, [(1, 5, 5)], "dq<128,2,2,1>"),        # 50
+    (128, (3, 16, 40), (3, 8, 8), 12, [(1, 1, 5)], "dq<128,3,2,1>"),       # 720 waves
+    (128, (3, 16, 40), (3, 8, 8), 16, [(1, 1, 5), (1, 1, 1)], "dq<128,3,2,1>"),
+    (64, (1, 32, 64), (1, 4, 8), 10, [(1, 3, 5)], "dq<64,1,1,1>"),         # 640 waves of 15
+]
+
+
+def test_single_waves_where_walks_are_long():
+    for name, dims, grid, tile, B, H, windows in SINGLE:
+        for D in dims:
+            line = launches(B, H, D, grid, tile, windows, gradients=True)[0]
+            assert line.startswith("dq<%d,1,4,1> items" % D) == TAKES.get((name, D), True), (name, line)
+    for D, grid, tile, H, windows, want in OTHERS:
+        assert launches(1, H, D, grid, tile, windows, gradients=True)[0].startswith(want + " "), (D, grid, H, windows)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name,D,grid,tile,B,H,windows", [(n, D, *rest) for n, dims, *rest in SINGLE for D in dims],
+                         ids=["%s-d%d" % (s[0], D) for s in SINGLE for D in s[1]])
+def test_gradients_of_single_waves_match_the_oracle(name, D, grid, tile, B, H, windows):
+    w = syn.custom("bwd-single-" + name, B, H, D, grid, tile, [windows[h % len(windows)] for h in range(H)], "bf16", seed=2020)
+    q, k, v = syn.make_qkv(w)
+    g = syn.make_dout(w)
+    (dq, dk, dv), _ = gpu_backward(w, q, k, v, g)
+    for b, h in {(0, 0), (B - 1, H - 1)}:
+        rq, rk, rv = oracle_backward(w, q, k, v, g, b, h)
+        for label, got, ref in (("dQ", dq, rq), ("dK", dk, rk), ("dV", dv, rv)):
+            assert_grad_parity(got[b, h].float().numpy(), ref, "%s D%d %s b%d h%d" % (name, D, label, b, h))
