@@ -1231,7 +1231,7 @@ hipError_t dispatch_dq(const BwdArgs &a)
 // dK/dV.  Entry point in us; waves of 32 keys and sub-blocks per walk in brackets.
 // Four walk groups of one wave each while few of them share a CU, against two groups of two waves: head dimension 64, 64x64 image
 // at 3x3, two heads (256, 18) 21.1, 25.2, eight (1024, 18) 35.2, 34.3; at 5x5, eight (1024, 50) 70, 80; 12x24x24 in 384-token tiles,
-// two (432, 108) 83, 89, three (648, 108) 104, 94; 9x40x40 in 192-token tiles, two (900, 54) 82, 97, four (1800, 54) 126, 129; 128,
+// two (432, 108) 83, 89; 9x40x40 in 192-token tiles, two (900, 54) 82, 97, four (1800, 54) 126, 129; 128,
 // 8x32x32 in 128-token tiles, one (256, 36) 46, 60, two (512, 36) 65, 61; 64x64 at 5x5, five (640, 50) 101, 110; 9x40x40, three (1350,
 // 54) 199, 185; training steps 64-token tiles (800, 90) 260, 259, 192 (960, 72) 261, 258, 320 (900, 180) 455, 413.  Against the shapes of 96- and 32-token tiles: 10x30x56, 64, 3x3x3, four slices (2100, 81) 185, 221, eight (4200, 81)
 // 341, 378, ten (5250, 81) 430, 418; 128, two (1050, 81) 227, 285, three (1575, 81) 329, 339, 1x3x3, two (1050, 27) 98, 98; 32x64 in
@@ -1241,6 +1241,33 @@ hipError_t dispatch_dq(const BwdArgs &a)
 // 256-token tiles, 28 (10080, 120) 951, 914; 64x64, 3x3, 16 (2048, 18) 53, 53, 32 (4096, 18) 88, 85; 192-token tiles, 16 (7200, 54) 355,
 // 384; 128, 128-token tiles, six (1536, 36) 128, 137, 24 (6144, 36) 379, 382; 192-token tiles, eight (3600, 54) 360, 408, 24 (10800, 54)
 // 1019, 1010; 320-token tiles, eight (4000, 90) 605, 694, 24 (12000, 90) 1744, 1715.
+// Long walks: how many waves of columns go to four groups of one wave, which cut them in four, where `solo` do whatever the walk.  A key
+// tile's walk over the queries varies inside a head (a window of five along eight tiles keeps the inner ones for up to eight), the longest
+// ends a launch of a round or two, and the groups by two leave it twice as long.  Training steps, before and with this rule, us;
+// waves, longest walk of a query tile:
+// - multiples of 128 tokens, head dimension 64, up to three workgroups a CU: (648, 108) 141, 135, (768, 96) 135, 132, (576, 72) 107, 102,
+//   (720, 108), walks up to 1.8 times the mean, 186, 155, (672, 60) 108, 101; not short ones ((768, 32) 75.7, 76.0);
+// - the same at 128, up to two, where the longest is 1.3 times the mean of all query walks or more: (448, 140) 1.6 times 253, 232,
+//   (336, 180) 321, 276, (360, 60) 147, 133, two heads of 108 and 216 304, 253; below that (480, 240) 336, 343, (432, 72) 131, 135, and with
+//   a third workgroup (576, 120) 1.6 times 281, 294;
+// - multiples of 32 alone (32, 160, 224), up to three: 64 (768, 35) 89.7, 81.0, (672, 147) 216, 195, (588, 63) 110, 100; 128 (588, 147)
+//   450, 402, (768, 35) 158, 147, but (640, 40) 147, 151; up to four from 1.5 times on: 64 (840, 75) of several windows 139, 121, (900, 150)
+//   201, 188; 128 (784, 126) 449, 406; not (64, (800, 100) of equal walks 164, 174; 128 (1008, 42) 180, 189, (840, 45) 194, 197).
+// The other tiles: see solo's own lines.
+uint64_t single_waves_by_walk(const BwdArgs &a, int D, uint64_t waves, uint32_t units, uint64_t solo)
+{
+    const uint64_t cus = sta::compute_units();
+    const uint32_t P = a.p.P;
+    const bool whole = P % 128 == 0, one = P % 64 != 0 && P % 96 != 0;
+    if (one && waves <= 3 * cus) return units >= (D == 64 ? 32 : 48) ? 3 * cus : solo;
+    if (whole && D == 64) return units >= 48 ? 3 * cus : solo;
+    if (!(one ? units >= (D == 64 ? 40 : 60) : whole && waves <= 2 * cus && units >= 48)) return solo;
+    uint64_t all = 0;
+    for (uint32_t r = 0; r < a.p.heads; ++r) all += walk_of_rank(a, r);
+    if (10 * (uint64_t)longest_key_walk(a) * a.p.heads < (one ? 15 : 13) * all) return solo;
+    return (one ? 4 : 2) * cus;
+}
+
 template <int D>
 hipError_t dispatch_dkv(const BwdArgs &a)
 {
@@ -1255,6 +1282,7 @@ hipError_t dispatch_dkv(const BwdArgs &a)
     if (P % 64 != 0 && P % 96 == 0) solo = (D == 64 ? 18 : 6) * cus;
     if (P % 64 != 0 && P % 96 != 0 && units >= 24) solo = 2 * cus;
     if (eight_groups(waves, units)) return launch_dkv<D, 1, 8>(a);
+    if (waves > solo && waves <= 4 * cus) solo = single_waves_by_walk(a, D, waves, units, solo);
     if (waves <= solo) return launch_dkv<D, 1, 4>(a);
     if (P % 64 != 0) {
         if constexpr (D == 128) return P % 96 == 0 ? launch_dkv_pairs<3, 2>(a) : launch_dkv_pairs<1, 1>(a);

@@ -1,5 +1,5 @@
-"""dQ launches of four walk groups of one wave beyond one workgroup per CU: which launches take them (counted on 256 CUs, no GPU
-needed) and GPU parity at the edges of the rule."""
+"""Gradient launches of four walk groups of one wave beyond one workgroup per CU (dQ) or beyond short walks (dK/dV): which launches take
+them (counted on 256 CUs, no GPU needed) and GPU parity at the edges of the rules."""
 import pytest
 
 import synth_inputs as syn
@@ -26,6 +26,30 @@ OTHERS = [
     (128, (3, 16, 40), (3, 8, 8), 16, [(1, 1, 5), (1, 1, 1)], "dq<128,3,2,1>"),
     (64, (1, 32, 64), (1, 4, 8), 10, [(1, 3, 5)], "dq<64,1,1,1>"),         # 640 waves of 15
 ]
+# dK/dV: name, head dimension, grid, tile, heads, windows
+KEYS = [
+    ("dkv-p384-720", 64, (6, 32, 40), (6, 8, 8), 3, [(1, 3, 3), (1, 1, 1)]),             # 720 waves; 108 sub-blocks, up to 192 of a key tile
+    ("dkv-p256-768", 64, (8, 16, 24), (4, 8, 8), 8, [(1, 2, 3)]),                        # 768; 48
+    ("dkv-p128-448", 128, (2, 64, 56), (2, 8, 8), 2, [(1, 5, 7), (1, 1, 1)]),            # 448; 140, up to 224
+    ("dkv-p160-640", 64, (5, 32, 32), (5, 8, 4), 4, [(1, 1, 7)]),                        # 640; 35
+    ("dkv-p224-756", 128, (21, 32, 12), (7, 8, 4), 3, [(1, 2, 2)]),                      # 756; 63
+    ("dkv-p160-1000", 64, (5, 40, 32), (5, 8, 4), 5, [(1, 4, 1), (1, 2, 6)]),            # 1000; 105 and 25
+]
+OTHER_KEYS = [
+    (64, (6, 64, 16), (6, 8, 8), 3, [(1, 2, 1)], "dkv<64,2,2,1,1>"),                     # 576 waves of 36
+    (128, (6, 32, 40), (2, 8, 8), 2, [(3, 4, 4)], "dkv<128,2,2,1,1>"),                   # 480 of 240, all equal
+    (128, (8, 48, 48), (4, 8, 8), 1, [(1, 4, 3)], "dkv<128,2,2,1,1>"),                   # 576 of 120
+    (128, (5, 64, 8), (5, 8, 4), 8, [(1, 8, 1)], "dkv_pair<1,1,1>"),                     # 640 of 40
+    (64, (10, 16, 20), (5, 8, 4), 8, [(2, 2, 5)], "dkv<64,1,2,1,1>"),                    # 800 of 100, all equal
+]
+
+
+def test_dkv_single_waves_where_walks_are_long_or_uneven():
+    for name, D, grid, tile, H, windows in KEYS:
+        line = launches(1, H, D, grid, tile, windows, gradients=True)[1]
+        assert line.startswith("dkv<%d,1,4,1,1> items" % D), (name, line)
+    for D, grid, tile, H, windows, want in OTHER_KEYS:
+        assert launches(1, H, D, grid, tile, windows, gradients=True)[1].startswith(want + " "), (D, grid, H, windows)
 
 
 def test_single_waves_where_walks_are_long():
@@ -38,8 +62,9 @@ def test_single_waves_where_walks_are_long():
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("name,D,grid,tile,B,H,windows", [(n, D, *rest) for n, dims, *rest in SINGLE for D in dims],
-                         ids=["%s-d%d" % (s[0], D) for s in SINGLE for D in s[1]])
+@pytest.mark.parametrize("name,D,grid,tile,B,H,windows", [(n, D, *rest) for n, dims, *rest in SINGLE for D in dims]
+                         + [(n, D, grid, tile, 1, H, windows) for n, D, grid, tile, H, windows in KEYS],
+                         ids=["%s-d%d" % (s[0], D) for s in SINGLE for D in s[1]] + ["%s-d%d" % s[:2] for s in KEYS])
 def test_gradients_of_single_waves_match_the_oracle(name, D, grid, tile, B, H, windows):
     w = syn.custom("bwd-single-" + name, B, H, D, grid, tile, [windows[h % len(windows)] for h in range(H)], "bf16", seed=2020)
     q, k, v = syn.make_qkv(w)
