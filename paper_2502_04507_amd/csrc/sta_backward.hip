@@ -1131,7 +1131,8 @@ hipError_t launch_dkv_pairs(const BwdArgs &a)
 // 16.8, 14.2, image x 16 (2048) 21.1, 23.4; but walks of 32 and more on tiles of odd multiples of 64, whose one group has two waves as well,
 // up to the 16 that a CU holds (entry point, waves and units: (1664, 50) 104, 98, (2048, 50) 117, 110, (2000, 90) 199, 184; the other tiles,
 // of four and three waves a group, -1 to +1 %).  Four groups of one wave, without barriers, up to one such workgroup per CU
-// (two on 96-token tiles at head dimension 64), and up to four where walks are long (below); entry point, two groups of two or three waves against these: 12x24x24 in
+// (two on 96-token tiles at head dimension 64), and up to four where walks are long (below); entry point, two groups of two or three waves against these,
+// which then still had two buffers for each operand: 12x24x24 in
 // 384-token tiles, one head (216 waves) of 64 100, 87, of 128 151, 131, two (432) 107, 110; 64x64 image, 5x5, one head (128) of 128 149,
 // 140, three (384) 150, 157; 4x12x24 in 96-token tiles, one head (36) of 64 39.5, 31.2, of 128 59.6, 47.3; twelve (432) 40.6, 35.4
 // and 61.3, 61.9.

@@ -5,7 +5,7 @@
 // path, which accepts what it always accepted and raises what it always raised.  Nothing is launched before every argument has
 // been looked at.
 //
-// What bounds a small layer is the host: five launches of 2.6 us each and, through ctypes, as much again in Python.  us per call,
+// What bounds a small layer is the host: five launches of 2.4 us each and, through ctypes, as much again in Python.  us per call,
 // host alone, ctypes against this: sta_tile_permute 5.3, 3.05; sta_forward of 2 heads 7.5, 3.5, of 24 11.4, 3.9.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
