@@ -247,15 +247,17 @@ constexpr int max_of(int a, int b) { return a > b ? a : b; }
 // and dP^T = V dO^T - delta (the statistics of the lane's query as the initial value, so that neither a subtraction nor a
 // fused multiply-add per element is left), dS^T = 2^(c S^T) o dP^T, dQ^T += K^T dS^T; 16 matrix instructions each at head
 // dimension 128, 8 at 64.
-// QW = 1 with walk groups ("solo", for the small launches): as in the dK/dV kernel the stage belongs to one wave, which refills V as
+// SOLO (a single wave in each walk group, or alone beyond a round of them): as in the dK/dV kernel the stage belongs to one wave, which refills V as
 // soon as dP is formed and K after its last product.  One buffer for each, as eight groups at head dimension 128 have to share the
 // 160 KB of a CU (143 KB; with two for each four groups took 135); walks of 50 at four groups are no slower for it.
+// Without groups (tiles of 32 tokens' multiples) a CU holds eight such waves at head dimension 128 and sixteen at 64, with two buffers four and
+// twelve.
 // The row statistics are formed here, from the dO fragments the wave holds anyway and the same fragments of O, and written
 // for the dK/dV kernel (a kernel of their own for them read dO once more: 6.8 us of a 345 us training step at 16,384 tokens
 // x 8 heads of dimension 64, 0.23 ms of 53 ms at 115,200 x 24 of 128).
 // ---------------------------------------------------------------------------------------------------------
-template <int D, int QW, int G, bool DMA>
-__global__ __attribute__((amdgpu_flat_work_group_size(QW * G * 64, QW * G * 64), amdgpu_waves_per_eu(QW == 1 ? (D == 64 || G == 8 ? 2 : 1) : (D == 64 ? 4 : 2))))
+template <int D, int QW, int G, bool DMA, bool SOLO>
+__global__ __attribute__((amdgpu_flat_work_group_size(QW * G * 64, QW * G * 64), amdgpu_waves_per_eu(SOLO && G == 1 ? (D == 64 ? 4 : 2) : QW == 1 ? (D == 64 || G == 8 ? 2 : 1) : (D == 64 ? 4 : 2))))
 void sta_bwd_dq_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restrict__ k, const bf16_raw *__restrict__ v,
                        const bf16_raw *__restrict__ o, const bf16_raw *__restrict__ d_o, const float *__restrict__ lse,
                        float *__restrict__ neg_delta, float *__restrict__ neg_lse, bf16_raw *__restrict__ d_q,
@@ -266,13 +268,12 @@ void sta_bwd_dq_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restric
     constexpr int COLS = QW * 32;                       // queries per workgroup
     constexpr int STAGE_B = 2 * L::Tile;
     constexpr int K_TILE = 0, V_TILE = L::Tile;
-    constexpr bool SOLO = QW == 1 && G > 1;             // a wave with a stage of its own: no barriers, single buffers
-    static_assert(!SOLO || DMA, "waited for by count");
+    static_assert(!SOLO || (QW == 1 && DMA), "SOLO: a wave with a stage of its own, no barriers, single buffers");
     constexpr int GROUP_B = SOLO ? STAGE_B : 2 * STAGE_B;       // LDS of one walk group
     constexpr int OPS = 2 * L::Groups;                  // DMA instructions per sub-block
     constexpr int WAVE_OPS = (OPS + QW - 1) / QW;       // at most this many per wave
     constexpr int WAVE_OUT = 16 * L::RowB;
-    constexpr int SMEM = SOLO ? G * GROUP_B + 32 * L::RowB
+    constexpr int SMEM = SOLO && G > 1 ? G * GROUP_B + 32 * L::RowB
                                           : max_of(G * GROUP_B, max_of((G / 2) * QW * CB * 2 * 1024, QW * WAVE_OUT));
     __shared__ __attribute__((aligned(1024))) char smem[SMEM];
 
@@ -440,7 +441,7 @@ void sta_bwd_dq_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restric
             if (u + 1 < share.n_steps) sub_block(std::integral_constant<int, 1>{}, u + 1);
         }
     }
-    if constexpr (SOLO) {
+    if constexpr (SOLO && G > 1) {
         char *rows = smem + G * GROUP_B;
         merge_waves<D, G, GROUP_B>(smem, rows, group, lane, dQ, c * kLn2);
         store_rows<D, G * 64>(rows, d_q + my_row * D, tid);
@@ -1045,16 +1046,16 @@ hipError_t note_launch(const BwdArgs &a, const BwdPlan &plan, const char *shape)
     return a.note->add("%s items %u, fullest XCD %llu of %llu sub-blocks", shape, plan.deal.total, (unsigned long long)most, (unsigned long long)all);
 }
 
-template <int D, int QW, int G, bool DMA = true>
+template <int D, int QW, int G, bool DMA = true, bool SOLO = (QW == 1 && G > 1)>
 hipError_t launch_dq(const BwdArgs &a)
 {
     const BwdPlan plan = make_plan(a, QW * 32, false, false);
     if (a.note) {
         char shape[64];
-        snprintf(shape, sizeof shape, "dq<%d,%d,%d,%d>%s", D, QW, G == 8 ? 4 : G, (int)DMA, G == 8 ? " doubled" : "");
+        snprintf(shape, sizeof shape, "dq<%d,%d,%d,%d>%s", D, QW, G == 8 ? 4 : G, (int)DMA, G == 8 ? " doubled" : SOLO && G == 1 ? " refilled" : "");
         return note_launch(a, plan, shape);
     }
-    return sta::launch_kernel(sta_bwd_dq_kernel<D, QW, G, DMA>, dim3(plan.deal.total), dim3(QW * G * 64), a.stream, a.q, a.k, a.v, a.o, a.d_o, a.lse,
+    return sta::launch_kernel(sta_bwd_dq_kernel<D, QW, G, DMA, SOLO>, dim3(plan.deal.total), dim3(QW * G * 64), a.stream, a.q, a.k, a.v, a.o, a.d_o, a.lse,
                               a.neg_delta, a.neg_lse, a.d_q, a.p, plan);
 }
 
@@ -1224,7 +1225,11 @@ hipError_t dispatch_dq(const BwdArgs &a)
     if (eight_groups(waves, units)) return launch_dq<D, 1, 8>(a);
     if (four_groups_of_one<D>(a, waves, units)) return launch_dq<D, 1, 4>(a);
     if (P % 96 == 0 && P % 128 != 0) return two ? launch_dq<D, 3, 2>(a) : launch_dq<D, 3, 1>(a);
-    if (P % 64 != 0) return launch_dq<D, 1, 1>(a);
+    // One buffer from the first round that two leave short on: training steps, two buffers, one, waves and units: head dimension 64 (2048, 25) 167,
+    // 164, (2560, 45) 274, 254, (3200, 90) 841, 790, (8192, 9) 264, 256; below that the wave alone waits longer for a buffer it
+    // has just emptied, (1280, 25) 126, 128, (1280, 45) 161, 165; 128 (1280, 45) 265, 239, (1280, 25) 200, 183, (1536, 9) 127, 120, (6400, 90)
+    // 2769, 2670; but (800, 45) 193, 197, (640, 25) 136, 138, (1024, 9) 90.3, 90.6.
+    if (P % 64 != 0) return waves >= (D == 64 ? 8 * cus : 4 * cus + 1) ? launch_dq<D, 1, 1, true, true>(a) : launch_dq<D, 1, 1>(a);
     if (two) return launch_dq<D, 2, 2>(a);
     return P % 128 == 0 ? launch_dq<D, 4, 1>(a) : launch_dq<D, 2, 1>(a);
 }

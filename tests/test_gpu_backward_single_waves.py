@@ -61,10 +61,23 @@ def test_single_waves_where_walks_are_long():
         assert launches(1, H, D, grid, tile, windows, gradients=True)[0].startswith(want + " "), (D, grid, H, windows)
 
 
+# dQ, one wave alone, one buffer for each operand: beyond a round of those with two
+ALONE = [
+    ("p32-2048", 64, (1, 32, 64), (1, 4, 8), 2, 16, [(1, 3, 5), (1, 1, 1)]),             # 2048 waves; 15 sub-blocks and 1
+    ("p160-1120", 128, (5, 16, 28), (5, 8, 4), 4, 4, [(1, 1, 5), (1, 2, 1)]),            # 1120; 25 and 10
+]
+
+
+def test_one_buffer_where_a_wave_alone_fills_the_chip():
+    for name, D, grid, tile, B, H, windows in ALONE:
+        assert launches(B, H, D, grid, tile, windows, gradients=True)[0].startswith("dq<%d,1,1,1> refilled items" % D), name
+        assert "refilled" not in launches(B, H - 1, D, grid, tile, windows, gradients=True)[0], name
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("name,D,grid,tile,B,H,windows", [(n, D, *rest) for n, dims, *rest in SINGLE for D in dims]
-                         + [(n, D, grid, tile, 1, H, windows) for n, D, grid, tile, H, windows in KEYS],
-                         ids=["%s-d%d" % (s[0], D) for s in SINGLE for D in s[1]] + ["%s-d%d" % s[:2] for s in KEYS])
+                         + [(n, D, grid, tile, 1, H, windows) for n, D, grid, tile, H, windows in KEYS] + ALONE,
+                         ids=["%s-d%d" % (s[0], D) for s in SINGLE for D in s[1]] + ["%s-d%d" % s[:2] for s in KEYS + ALONE])
 def test_gradients_of_single_waves_match_the_oracle(name, D, grid, tile, B, H, windows):
     w = syn.custom("bwd-single-" + name, B, H, D, grid, tile, [windows[h % len(windows)] for h in range(H)], "bf16", seed=2020)
     q, k, v = syn.make_qkv(w)
