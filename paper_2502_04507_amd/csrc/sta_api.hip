@@ -53,6 +53,29 @@ bool ranges_overlap(const void *a, size_t abytes, const void *b, size_t bbytes)
 
 uint32_t magic_of(uint32_t d) { return d <= 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) + d - 1) / d); }
 
+// What the permutation kernel needs of a shape, but for the split over workgroups; tiles of all slices.
+int permute_params(const Shape &s, int B, int H, int D, const int grid[3], const int tile[3], sta::PermuteParams *p, uint64_t *tiles)
+{
+    const uint32_t cpr = (uint32_t)(D / 8);
+    p->n_w = s.n[2];
+    const uint64_t cpt = (uint64_t)s.P * cpr;
+    p->seg = tile[2] * cpr;
+    p->T_h = tile[1];
+    // exactness condition of the multiply-high division used by the kernel
+    if (cpt * p->seg >= ((uint64_t)1 << 32) || cpt * p->T_h >= ((uint64_t)1 << 32)) return STA_ERR_SHAPE;
+    p->chunks_per_tile = (uint32_t)cpt;
+    p->seg_magic = magic_of(p->seg);
+    p->T_h_magic = magic_of(p->T_h);
+    *tiles = (uint64_t)B * H * s.n_tiles;
+    if (*tiles * ((cpt + 1023) / 1024) >= ((uint64_t)1 << 31)) return STA_ERR_SHAPE;
+    p->line = grid[2] * cpr;
+    p->plane = (uint64_t)grid[1] * p->line;
+    p->tile_h = (uint64_t)tile[1] * p->line;
+    p->tile_t = tile[0] * p->plane;
+    p->by_n_h = sta::fast_div_of(s.n[1]);
+    return STA_OK;
+}
+
 int permute_common(const void *src, void *dst, int src_dt, int dst_dt, int B, int H, int D, const int grid[3],
                    const int tile[3], void *hip_stream, bool to_tiled)
 {
@@ -65,23 +88,8 @@ int permute_common(const void *src, void *dst, int src_dt, int dst_dt, int B, in
     if (ranges_overlap(src, elems * elem_size(src_dt), dst, elems * elem_size(dst_dt))) return STA_ERR_ALIAS;
 
     sta::PermuteParams p;
-    const uint32_t cpr = (uint32_t)(D / 8);
-    p.n_w = s.n[2];
-    const uint64_t cpt = (uint64_t)s.P * cpr;
-    p.seg = tile[2] * cpr;
-    p.T_h = tile[1];
-    // exactness condition of the multiply-high division used by the kernel
-    if (cpt * p.seg >= ((uint64_t)1 << 32) || cpt * p.T_h >= ((uint64_t)1 << 32)) return STA_ERR_SHAPE;
-    p.chunks_per_tile = (uint32_t)cpt;
-    p.seg_magic = magic_of(p.seg);
-    p.T_h_magic = magic_of(p.T_h);
-    const uint64_t tiles = (uint64_t)B * H * s.n_tiles;
-    if (tiles * ((cpt + 1023) / 1024) >= ((uint64_t)1 << 31)) return STA_ERR_SHAPE;
-    p.line = grid[2] * cpr;
-    p.plane = grid[1] * p.line;
-    p.tile_h = tile[1] * p.line;
-    p.tile_t = (uint64_t)tile[0] * p.plane;
-    p.by_n_h = sta::fast_div_of(s.n[1]);
+    uint64_t tiles;
+    if (int rc = permute_params(s, B, H, D, grid, tile, &p, &tiles)) return rc;
     hipError_t e = sta::launch_permute(src, dst, src_dt == STA_F32, dst_dt == STA_F32, to_tiled, p, tiles,
                                        static_cast<hipStream_t>(hip_stream));
     return e == hipSuccess ? STA_OK : STA_ERR_HIP;
@@ -539,6 +547,30 @@ void sta_dealt_items(uint32_t per_head, uint32_t slices, uint32_t *items)
 {
     const sta::Deal d = sta::deal_of(per_head, slices);
     for (uint32_t id = 0; id < d.total; ++id) items[id] = sta::dealt_item(id, d);
+}
+
+// Nor this: the chunks of 8 elements, in raster and in tiled order, that a permutation's workgroup moves by its piece of that number;
+// both all ones where it has none.  Needs no memory of the tensor's size.
+int sta_permuted_piece(int src_dtype, int dst_dtype, int B, int H, int D, const int grid[3], const int tile[3], uint32_t workgroup,
+                       uint32_t piece, uint64_t *raster, uint64_t *tiled)
+{
+    Shape s;
+    if (int rc = check_shape(B, H, D, grid, tile, &s)) return rc;
+    if (D % 8 != 0) return STA_ERR_UNSUPPORTED;
+    sta::PermuteParams p;
+    uint64_t tiles;
+    uint32_t per_block;
+    bool streamed;
+    if (int rc = permute_params(s, B, H, D, grid, tile, &p, &tiles)) return rc;
+    if (!sta::permute_split(&p, src_dtype == STA_F32, dst_dtype == STA_F32, tiles, &per_block, &streamed)) return STA_ERR_SHAPE;
+    *raster = *tiled = ~(uint64_t)0;
+    if (workgroup >= p.blocks || piece >= per_block) return STA_OK;
+    const sta::PermuteTile t = sta::permute_tile(workgroup, p);
+    const uint64_t idx = (uint64_t)t.part * per_block + piece;
+    if (idx >= p.chunks_per_tile) return STA_OK;
+    *raster = t.raster + sta::permute_piece((uint32_t)idx, p);
+    *tiled = t.tiled + idx;
+    return STA_OK;
 }
 
 int sta_dump_key_tiles(int H, const int grid[3], const int tile[3], const int *window_tiles, int32_t *dev_counts,

@@ -49,12 +49,49 @@ struct PermuteParams {
     uint32_t chunks_per_tile;   // P * D / 8
     uint32_t seg, seg_magic;    // contiguous run of a tile in raster order, ceil(2^32/seg)
     uint32_t T_h, T_h_magic;    // runs of a tile in one raster plane, ceil(2^32 / T_h)
-    uint32_t line, plane;       // raster line and plane of tokens
-    uint32_t tile_h;            // from a tile to the next along h
+    uint32_t line;              // raster line of tokens: at most 30000 runs of less than 2^16, which stays below 2^31
+    uint64_t plane;             // and plane: 2^32 where one of D = 64 holds 2^29 tokens (64 GB)
+    uint64_t tile_h;            // from a tile to the next along h
     uint64_t tile_t;            // and along t; slices follow each other at multiples of it
 };
+constexpr int kPermuteThreads = 256;
 
-// Fills in what depends on the split of a tile over workgroups; tiles of all slices.
+// n / d with magic = ceil(2^32 / d) for d > 1; exact while n * d < 2^32 (checked on the host).
+__host__ __device__ __forceinline__ uint32_t small_div(uint32_t n, uint32_t d, uint32_t magic)
+{
+    return d == 1 ? n : (uint32_t)(((uint64_t)n * magic) >> 32);
+}
+
+__host__ __device__ __forceinline__ uint32_t fast_div(uint32_t n, const FastDiv &f);
+
+// The tile that a workgroup moves a part of: the chunks where it begins in either order.
+struct PermuteTile {
+    uint64_t raster, tiled;
+    uint32_t part;
+};
+__host__ __device__ __forceinline__ PermuteTile permute_tile(uint32_t id, const PermuteParams &p)
+{
+    const bool left_over = id >= p.in_rounds;
+    const uint32_t turn = left_over ? id : id >> 3;
+    const uint32_t q = fast_div(turn, p.by_row), in_row = turn - q * p.by_row.d;
+    const uint32_t row = left_over ? q : 8 * q + (id & 7);                  // row of tiles along w, of all slices
+    const uint32_t tw = fast_div(in_row, p.by_parts), part = in_row - tw * p.by_parts.d;
+    const uint32_t layer = fast_div(row, p.by_n_h), th = row - layer * p.by_n_h.d;
+    return {layer * p.tile_t + th * p.tile_h + tw * p.seg, ((uint64_t)row * p.n_w + tw) * p.chunks_per_tile, part};
+}
+// Raster chunk, from the tile's first, of chunk idx of the tile.
+__host__ __device__ __forceinline__ uint64_t permute_piece(uint32_t idx, const PermuteParams &p)
+{
+    const uint32_t seg = small_div(idx, p.seg, p.seg_magic);                // which (i_t, i_h) run
+    const uint32_t off = idx - seg * p.seg;
+    const uint32_t it = small_div(seg, p.T_h, p.T_h_magic);
+    const uint32_t ih = seg - it * p.T_h;
+    return it * p.plane + ((uint64_t)ih * p.line + off);
+}
+
+// Split of the tiles of all slices over workgroups, of so many chunks each; false: more of them than are numbered.
+bool permute_split(PermuteParams *p, bool src_f32, bool dst_f32, uint64_t tiles, uint32_t *per_block, bool *streamed);
+
 hipError_t launch_permute(const void *src, void *dst, bool src_f32, bool dst_f32, bool to_tiled,
                           PermuteParams p, uint64_t tiles, hipStream_t stream);
 

@@ -87,13 +87,7 @@ __device__ __forceinline__ void store8(void *base, size_t chunk, const Chunk8bf1
     }
 }
 
-__device__ __forceinline__ uint32_t small_div(uint32_t n, uint32_t d, uint32_t magic)
-{
-    // magic = ceil(2^32 / d) for d > 1; exact while n * d < 2^32 (checked on the host).
-    return d == 1 ? n : __umulhi(n, magic);
-}
-
-constexpr int kPermuteThreads = 256;
+using sta::kPermuteThreads;
 constexpr int kGridShift = 23;                              // a grid holds fewer than 2^32 lanes along x
 
 // TO_TILED: src is raster, dst is tiled.  Otherwise the reverse.
@@ -122,28 +116,16 @@ __global__ __launch_bounds__(kPermuteThreads) void sta_permute_kernel(const void
     asm volatile("" ::"s"(p.blocks), "s"(p.in_rounds), "s"(p.n_w), "s"(p.chunks_per_tile), "s"(p.seg), "s"(p.seg_magic), "s"(p.T_h),
                  "s"(p.T_h_magic), "s"(p.line), "s"(p.plane), "s"(p.tile_h), "s"(p.tile_t));
     const uint32_t id = (blockIdx.y << kGridShift) + blockIdx.x;
-    const bool left_over = id >= p.in_rounds;
-    const uint32_t turn = left_over ? id : id >> 3;
-    const uint32_t q = fast_div(turn, p.by_row), in_row = turn - q * p.by_row.d;
-    const uint32_t row = left_over ? q : 8 * q + (id & 7);                  // row of tiles along w, of all slices
-    const uint32_t tw = fast_div(in_row, p.by_parts), part = in_row - tw * p.by_parts.d;
-    const uint32_t layer = fast_div(row, p.by_n_h), th = row - layer * p.by_n_h.d;
-
-    const size_t tiled_tile = ((size_t)row * p.n_w + tw) * p.chunks_per_tile;
-    const size_t raster_tile = layer * p.tile_t + (size_t)th * p.tile_h + tw * p.seg;         // the tile's first token
-    const uint32_t first = part * (kPermuteThreads * CHUNKS) + threadIdx.x;
+    const sta::PermuteTile tile = sta::permute_tile(id, p);
+    const uint32_t first = tile.part * (kPermuteThreads * CHUNKS) + threadIdx.x;
     Chunk8bf16 b[CHUNKS];
     Chunk8f32 f[CHUNKS];
     size_t dst_idx[CHUNKS];
 #pragma unroll
     for (int u = 0; u < CHUNKS; ++u) {
         const uint32_t idx = first + u * kPermuteThreads;
-        const uint32_t seg = small_div(idx, p.seg, p.seg_magic);            // which (i_t, i_h) run
-        const uint32_t off = idx - seg * p.seg;
-        const uint32_t it = small_div(seg, p.T_h, p.T_h_magic);
-        const uint32_t ih = seg - it * p.T_h;
-        const size_t raster = raster_tile + (size_t)it * p.plane + (ih * p.line + off);
-        const size_t tiled = tiled_tile + idx;
+        const size_t raster = tile.raster + sta::permute_piece(idx, p);
+        const size_t tiled = tile.tiled + idx;
         dst_idx[u] = TO_TILED ? tiled : raster;
         if (idx < p.chunks_per_tile && id < p.blocks) load8<SRC_F32, STREAM>(src, TO_TILED ? raster : tiled, b[u], f[u]);
     }
@@ -174,18 +156,26 @@ constexpr size_t kStreamAbove = (size_t)256 << 20;
 
 namespace sta {
 
+bool permute_split(PermuteParams *p, bool src_f32, bool dst_f32, uint64_t tiles, uint32_t *per_block, bool *streamed)
+{
+    *streamed = tiles * p->chunks_per_tile * (src_f32 ? 32 : 16) > kStreamAbove;
+    *per_block = kPermuteThreads * (src_f32 && !dst_f32 && !*streamed ? 2 : 1);
+    const uint32_t parts = (p->chunks_per_tile + *per_block - 1) / *per_block;
+    if (tiles * parts >= ((uint64_t)1 << 31)) return false;                          // terabytes
+    p->blocks = (uint32_t)(tiles * parts);
+    p->by_parts = fast_div_of(parts);
+    p->by_row = fast_div_of(p->n_w * parts);
+    const uint64_t round = (uint64_t)8 * p->by_row.d;
+    p->in_rounds = (uint32_t)(p->blocks / round * round);
+    return true;
+}
+
 hipError_t launch_permute(const void *src, void *dst, bool src_f32, bool dst_f32, bool to_tiled,
                           PermuteParams p, uint64_t tiles, hipStream_t stream)
 {
-    const bool streamed = tiles * p.chunks_per_tile * (src_f32 ? 32 : 16) > kStreamAbove;
-    const uint32_t per_block = kPermuteThreads * (src_f32 && !dst_f32 && !streamed ? 2 : 1);
-    const uint32_t parts = (p.chunks_per_tile + per_block - 1) / per_block;
-    if (tiles * parts >= ((uint64_t)1 << 31)) return hipErrorInvalidValue;           // terabytes
-    p.blocks = (uint32_t)(tiles * parts);
-    p.by_parts = fast_div_of(parts);
-    p.by_row = fast_div_of(p.n_w * parts);
-    const uint64_t round = (uint64_t)8 * p.by_row.d;
-    p.in_rounds = (uint32_t)(p.blocks / round * round);
+    uint32_t per_block;
+    bool streamed;
+    if (!permute_split(&p, src_f32, dst_f32, tiles, &per_block, &streamed)) return hipErrorInvalidValue;
     if (streamed)
         return to_tiled ? launch<true, true>(src, dst, src_f32, dst_f32, p, stream)
                         : launch<false, true>(src, dst, src_f32, dst_f32, p, stream);
