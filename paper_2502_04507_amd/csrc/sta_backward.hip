@@ -1052,7 +1052,7 @@ hipError_t launch_dq(const BwdArgs &a)
     const BwdPlan plan = make_plan(a, QW * 32, false, false);
     if (a.note) {
         char shape[64];
-        snprintf(shape, sizeof shape, "dq<%d,%d,%d,%d>%s", D, QW, G == 8 ? 4 : G, (int)DMA, G == 8 ? " doubled" : SOLO && G == 1 ? " refilled" : "");
+        snprintf(shape, sizeof shape, "%s<%d,%d,%d,%d>", SOLO && G == 1 ? "dq_one_buffer" : "dq", D, QW, G, (int)DMA);
         return note_launch(a, plan, shape);
     }
     return sta::launch_kernel(sta_bwd_dq_kernel<D, QW, G, DMA, SOLO>, dim3(plan.deal.total), dim3(QW * G * 64), a.stream, a.q, a.k, a.v, a.o, a.d_o, a.lse,
@@ -1097,7 +1097,7 @@ hipError_t launch_dkv(const BwdArgs &a)
     const BwdPlan plan = make_plan(a, NW * 32, row_major, row_major && longest_first);
     if (a.note) {
         char shape[64];
-        snprintf(shape, sizeof shape, "dkv<%d,%d,%d,%d,%d>%s", D, NW, G == 8 ? 4 : G, UPS, (int)DMA, G == 8 ? " doubled" : "");
+        snprintf(shape, sizeof shape, "dkv<%d,%d,%d,%d,%d>", D, NW, G, UPS, (int)DMA);
         return note_launch(a, plan, shape);
     }
     return sta::launch_kernel(sta_bwd_dkv_kernel<D, NW, G, UPS, DMA>, dim3(plan.deal.total), dim3(NW * G * 64), a.stream, a.q, a.k, a.v, a.d_o,

@@ -70,8 +70,8 @@ ALONE = [
 
 def test_one_buffer_where_a_wave_alone_fills_the_chip():
     for name, D, grid, tile, B, H, windows in ALONE:
-        assert launches(B, H, D, grid, tile, windows, gradients=True)[0].startswith("dq<%d,1,1,1> refilled items" % D), name
-        assert "refilled" not in launches(B, H - 1, D, grid, tile, windows, gradients=True)[0], name
+        assert launches(B, H, D, grid, tile, windows, gradients=True)[0].startswith("dq_one_buffer<%d,1,1,1> items" % D), name
+        assert launches(B, H - 1, D, grid, tile, windows, gradients=True)[0].startswith("dq<%d,1,1,1> items" % D), name
 
 
 @pytest.mark.gpu

@@ -7,7 +7,8 @@ import numpy as np
 import pytest
 
 import paper_2502_04507_amd as sta
-from tests import test_gpu_backward_groups, test_gpu_backward_launches, test_gpu_forward_groups, test_gpu_forward_large
+from tests import test_gpu_backward_eight_groups, test_gpu_backward_groups, test_gpu_backward_launches, test_gpu_backward_single_waves
+from tests import test_gpu_forward_groups, test_gpu_forward_large
 from tests import test_gpu_forward_launches
 from tests.launch_shapes import launches
 
@@ -248,11 +249,12 @@ BACKWARD = {
     ("p96-many", 128): "dq<128,3,1,1> dkv_pair<3,2,1>", ("p96-some", 64): "dq<64,3,1,1> dkv<64,1,4,1,1>",
     ("p96-some", 128): "dq<128,3,1,1> dkv_pair<3,2,1>", ("p96-few", 128): "dq<128,3,2,1> dkv<128,1,4,1,1>",
     ("p32-some", 64): "dq<64,1,1,1> dkv<64,1,2,1,1>", ("p32-some", 128): "dq<128,1,1,1> dkv_pair<1,1,1>",
-    ("p32-many", 64): "dq<64,1,1,1> dkv<64,1,1,1,1>", ("p32-many", 128): "dq<128,1,1,1> dkv_pair<1,1,1>",
+    ("p32-many", 64): "dq<64,1,1,1> dkv<64,1,1,1,1>", ("p32-many", 128): "dq_one_buffer<128,1,1,1> dkv_pair<1,1,1>",
 }
 # ... and the shapes that other GPU tests run: test_gpu_forward_groups.py (two units per stage), test_gpu_forward_large.py,
-# test_gpu_backward_groups.py (small launches, three waves in two groups)
-ELSEWHERE = {"group<64,4,1,0,2>", "x32<4>", "x32<12>", "solo<64,2,8,1>", "solo<128,2,8,1>", "dq<64,1,4,1>", "dq<128,1,4,1>", "dq<64,3,2,1>"}
+# test_gpu_backward_groups.py (three waves in two groups), test_gpu_backward_eight_groups.py, test_gpu_backward_single_waves.py
+ELSEWHERE = {"group<64,4,1,0,2>", "x32<4>", "x32<12>", "solo<64,2,8,1>", "solo<128,2,8,1>", "dq<64,3,2,1>", "dq<64,1,4,1>", "dq<128,1,4,1>",
+             "dq<64,1,8,1>", "dq<128,1,8,1>", "dkv<64,1,8,1,1>", "dkv<128,1,8,1,1>", "dq_one_buffer<64,1,1,1>"}
 
 
 def kernels(lines):
@@ -277,6 +279,12 @@ def test_the_gpu_tests_run_the_kernels_that_they_are_for():
     for _, grid, tile, B, H, windows in test_gpu_backward_groups.SHAPES:
         for D in (64, 128):
             seen.update(kernels(launches(B, H, D, grid, tile, windows, gradients=True)))
+    single = test_gpu_backward_single_waves
+    for D, grid, tile, B, H, windows in ([(D, *rest) for _, *rest in test_gpu_backward_eight_groups.EIGHT for D in (64, 128)]
+                                         + [(D, *rest) for _, dims, *rest in single.SINGLE for D in dims]
+                                         + [(D, grid, tile, 1, H, windows) for _, D, grid, tile, H, windows in single.KEYS]
+                                         + [case[1:] for case in single.ALONE]):
+        seen.update(kernels(launches(B, H, D, grid, tile, windows, gradients=True)))
     assert ELSEWHERE <= seen, ELSEWHERE - seen
     assert {"dkv_pair<6,1,1>", "dkv<128,4,1,1,1>", "dkv<128,2,2,1,1>"} == {
         kernels(launches(1, H, 128, grid, (6, 8, 8), windows, gradients=True))[1] for _, grid, H, windows in test_gpu_backward_groups.SIX_PAIRS}
