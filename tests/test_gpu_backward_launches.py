@@ -22,6 +22,7 @@ LAUNCHES = [
     ("p96-many", (64, 128), (2, 12, 16), (2, 6, 8), 4, 100, [(1, 1, 2), (1, 2, 1)]),              # 4800
     ("p96-some", (64, 128), (2, 12, 16), (2, 6, 8), 4, 33, [(1, 2, 2), (1, 1, 1)]),               # 1584
     ("p96-few", (128,), (4, 18, 40), (2, 6, 8), 1, 4, [(1, 3, 3), (1, 1, 1)]),                    # 360; 27 sub-blocks and 3
+    ("p192-three-two", (128,), (3, 16, 40), (3, 8, 8), 1, 12, [(1, 1, 5), (1, 1, 1)]),            # 720; 30 and 6
     ("p32-some", (64, 128), (1, 8, 24), (1, 4, 8), 10, 10, [(1, 2, 3), (1, 1, 1)]),               # 600; 6 sub-blocks and 1
     ("p32-many", (64, 128), (1, 8, 24), (1, 4, 8), 20, 10, [(1, 1, 3)]),                          # 1200
 ]

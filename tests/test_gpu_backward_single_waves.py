@@ -14,6 +14,7 @@ SINGLE = [
     ("p192-1020", (64, 128), (3, 16, 40), (3, 8, 8), 1, 17, [(1, 1, 5)]),                 # 1020; 30
     ("p96-512", (64, 128), (2, 12, 16), (2, 6, 8), 21, 2, [(1, 2, 2), (1, 2, 2)]),        # 504 of at most 512; 12
     ("p96-504", (64, 128), (4, 18, 32), (2, 6, 8), 1, 7, [(1, 3, 3)]),                    # 504; 27
+    ("p96-360", (128,), (4, 18, 40), (2, 6, 8), 1, 4, [(1, 3, 3), (1, 1, 1)]),            # 360; 27 and 3
     ("p160-480", (64, 128), (5, 24, 16), (5, 8, 4), 2, 4, [(1, 1, 3), (1, 1, 3)]),        # 480; 15
     ("p32-1024", (64,), (1, 32, 64), (1, 4, 8), 2, 8, [(1, 5, 7), (1, 1, 1)]),            # 1024; 35 and 1
 ]
