@@ -1043,7 +1043,8 @@ hipError_t note_launch(const BwdArgs &a, const BwdPlan &plan, const char *shape)
         all += l;
         most = l > most ? l : most;
     }
-    return a.note->add("%s items %u, fullest XCD %llu of %llu sub-blocks", shape, plan.deal.total, (unsigned long long)most, (unsigned long long)all);
+    return a.note->add("%s items %u, fullest XCD %llu of %llu sub-blocks, %s", shape, plan.deal.total, (unsigned long long)most, (unsigned long long)all,
+                       plan.row_major ? "rows of all heads in turn" : "head after head");
 }
 
 template <int D, int QW, int G, bool DMA = true, bool SOLO = (QW == 1 && G > 1)>
@@ -1071,7 +1072,8 @@ hipError_t launch_dq(const BwdArgs &a)
 //   12x48x48, 48 heads of 128 -3 %) or the rows of a head should stay together (30x48x80, head dimension 64, 12 to 24 heads
 //   +0.4 to +1.5 %; 128 +1 %).
 // - Not where every workgroup has a CU of its own and no order can even anything out (24x32x32, two heads of 128 +3 to +4 %), as in
-//   every launch of six pairs.
+//   every launch of six pairs and of eight walk groups (sixty drawn launches of those at head dimension 64: either order, 0.99 to 1.02, 1.00 in
+//   the mean).
 bool rows_of_all_heads(const BwdArgs &a, uint32_t cols, uint64_t resident)
 {
     const sta::FwdParams &p = a.p;
@@ -1092,7 +1094,7 @@ bool rows_of_all_heads(const BwdArgs &a, uint32_t cols, uint64_t resident)
 template <int D, int NW, int G, int UPS = 1, bool DMA = true>
 hipError_t launch_dkv(const BwdArgs &a)
 {
-    const uint64_t resident = (uint64_t)sta::compute_units() * (D == 64 ? 12 : 8) / (NW * G);     // workgroups
+    const uint64_t resident = (uint64_t)sta::compute_units() * max_of(1, (D == 64 ? 12 : 8) / (NW * G));     // workgroups: whole ones per CU
     const bool row_major = rows_of_all_heads(a, NW * 32, resident), longest_first = a.p.P % 96 == 0 && a.p.P % 128 != 0;
     const BwdPlan plan = make_plan(a, NW * 32, row_major, row_major && longest_first);
     if (a.note) {
