@@ -465,8 +465,8 @@ void sta_bwd_dq_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restric
 // S and dP start.  UPS sub-blocks per stage, i.e. per barrier.
 // NW = 1 ("solo", for the small launches): the stage belongs to one wave, which needs no barrier, only its own requests to have
 // landed, and refills either operand as soon as it has read it: half the LDS, so that a CU holds eight such waves at head
-// dimension 128 and twelve at 64 (of eight groups the eight of one workgroup; 168 registers and 12 bytes of scratch, at 128 52,
-// outside the loop).  There dP and dS come before the product with P, which frees dO first.
+// dimension 128 and twelve at 64 (168 registers and up to 12 bytes of scratch outside the loop, at 128 256 and up to 56; of eight groups,
+// one workgroup and two waves a SIMD at either, 170 and none at 64: 0.994 of the time under the bound of three waves, which spilled 12).  There dP and dS come before the product with P, which frees dO first.
 // What bounds it: matrix pipe and power on large launches (30x48x80, 24 heads, window 3x3x3, head dimension 128: 22.1 ms, 1330
 // TFLOP/s; 64: 11.5 ms, 1280).  Before, each 32 keys were served by a pair of waves, one for S, P and dV, one for dP, dS and dK,
 // with P handed over through LDS at a barrier of its own.  Entry point, pairs against this kernel, us: 30x48x80, 24 heads of 128
@@ -479,7 +479,7 @@ void sta_bwd_dq_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restric
 // A lane holds key column c16 of its wave's two 16-key blocks and the query rows 4*g4 .. 4*g4+3 of a result.
 // ---------------------------------------------------------------------------------------------------------
 template <int D, int NW, int G, int UPS, bool DMA>
-__global__ __attribute__((amdgpu_flat_work_group_size(NW * G * 64, NW * G * 64), amdgpu_waves_per_eu(D == 64 ? 3 : 2)))
+__global__ __attribute__((amdgpu_flat_work_group_size(NW * G * 64, NW * G * 64), amdgpu_waves_per_eu(D == 64 && G < 8 ? 3 : 2)))
 void sta_bwd_dkv_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restrict__ k, const bf16_raw *__restrict__ v,
                         const bf16_raw *__restrict__ d_o, const float *__restrict__ neg_lse,
                         const float *__restrict__ neg_delta, bf16_raw *__restrict__ d_k, bf16_raw *__restrict__ d_v,
