@@ -2014,10 +2014,10 @@ hipError_t launch_cfg(const FwdArgs &a)
     dim3 grid(a.p.N / C::kQB, (uint32_t)a.B * a.p.heads);
     dim3 block(C::kThreads);
     if (a.note) return a.note->add("general<%d,%d,%d>", D, NW, KB);
-    sta_fwd_kernel<D, NW, NQ, KB, TW><<<grid, block, 0, a.stream>>>(
+    return sta::launch_kernel(
+        sta_fwd_kernel<D, NW, NQ, KB, TW>, grid, block, a.stream,
         static_cast<const bf16_raw *>(a.q), static_cast<const bf16_raw *>(a.k), static_cast<const bf16_raw *>(a.v),
         static_cast<bf16_raw *>(a.o), a.p, a.win);
-    return hipGetLastError();
 }
 
 template <int D, bool TW = false>
@@ -2137,8 +2137,7 @@ hipError_t launch_dump_key_tiles(const FwdParams &p, const WindowTable &win, int
                                  hipStream_t stream)
 {
     const uint32_t total = p.heads * p.n_tiles;
-    sta_dump_key_tiles_kernel<<<dim3((total + 255) / 256), dim3(256), 0, stream>>>(p, win, counts, lists);
-    return hipGetLastError();
+    return launch_kernel(sta_dump_key_tiles_kernel, dim3((total + 255) / 256), dim3(256), stream, p, win, counts, lists);
 }
 
 }  // namespace sta

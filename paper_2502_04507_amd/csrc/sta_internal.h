@@ -10,7 +10,8 @@
 namespace sta {
 
 // A launch without the call that keeps its grid for another to fetch, which <<<>>> makes of it: 2.40 -> 2.19 us a launch, as many as the
-// host can make, whatever the arguments (2.4 KB of them 2.65 -> 2.43).
+// host can make, whatever the arguments (2.4 KB of them 2.65 -> 2.43).  It returns its own error alone: one that an earlier call of the
+// program left stays for whoever made that call.
 template <typename... Params>
 hipError_t launch_kernel(void (*kernel)(Params...), dim3 grid, dim3 block, hipStream_t stream, const std::common_type_t<Params> &...args)
 {
