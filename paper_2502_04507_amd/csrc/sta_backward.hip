@@ -248,8 +248,11 @@ constexpr int max_of(int a, int b) { return a > b ? a : b; }
 // fused multiply-add per element is left), dS^T = 2^(c S^T) o dP^T, dQ^T += K^T dS^T; 16 matrix instructions each at head
 // dimension 128, 8 at 64.
 // SOLO (a single wave in each walk group, or alone beyond a round of them): as in the dK/dV kernel the stage belongs to one wave, which refills V as
-// soon as dP is formed and K after its last product.  One buffer for each, as eight groups at head dimension 128 have to share the
-// 160 KB of a CU (143 KB; with two for each four groups took 135); walks of 50 at four groups are no slower for it.
+// soon as dP is formed and K after its last product.  One buffer for each instead of two: eight groups at head dimension 128 then take the 143 KB of
+// LDS that four take with two, and a CU holds two workgroups of four groups (four at 64) where it holds one (two) with two.  The wave waits longer
+// for a buffer that it has just emptied, so four groups keep two where the launch has no workgroup that does not find its place.  Gradients alone,
+// 220 drawn launches, one buffer's time over that of two: up to 256 waves of columns, walks below 40, 128 1.015, 64 1.011; 64 up to 512 waves
+// 1.012; beyond those 128 0.91, 64 0.96.
 // Without groups (tiles of 32 tokens' multiples) a CU holds eight such waves at head dimension 128 and sixteen at 64, with two buffers four and
 // twelve.
 // The row statistics are formed here, from the dO fragments the wave holds anyway and the same fragments of O, and written
@@ -273,7 +276,7 @@ void sta_bwd_dq_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restric
     constexpr int OPS = 2 * L::Groups;                  // DMA instructions per sub-block
     constexpr int WAVE_OPS = (OPS + QW - 1) / QW;       // at most this many per wave
     constexpr int WAVE_OUT = 16 * L::RowB;
-    constexpr int SMEM = SOLO && G > 1 ? G * GROUP_B + 32 * L::RowB
+    constexpr int SMEM = QW == 1 && G > 1 ? G * GROUP_B + 32 * L::RowB
                                           : max_of(G * GROUP_B, max_of((G / 2) * QW * CB * 2 * 1024, QW * WAVE_OUT));
     __shared__ __attribute__((aligned(1024))) char smem[SMEM];
 
@@ -441,7 +444,7 @@ void sta_bwd_dq_kernel(const bf16_raw *__restrict__ q, const bf16_raw *__restric
             if (u + 1 < share.n_steps) sub_block(std::integral_constant<int, 1>{}, u + 1);
         }
     }
-    if constexpr (SOLO && G > 1) {
+    if constexpr (QW == 1 && G > 1) {
         char *rows = smem + G * GROUP_B;
         merge_waves<D, G, GROUP_B>(smem, rows, group, lane, dQ, c * kLn2);
         store_rows<D, G * 64>(rows, d_q + my_row * D, tid);
@@ -1053,7 +1056,7 @@ hipError_t launch_dq(const BwdArgs &a)
     const BwdPlan plan = make_plan(a, QW * 32, false, false);
     if (a.note) {
         char shape[64];
-        snprintf(shape, sizeof shape, "%s<%d,%d,%d,%d>", SOLO && G == 1 ? "dq_one_buffer" : "dq", D, QW, G, (int)DMA);
+        snprintf(shape, sizeof shape, "%s<%d,%d,%d,%d>", SOLO ? "dq_one_buffer" : "dq", D, QW, G, (int)DMA);
         return note_launch(a, plan, shape);
     }
     return sta::launch_kernel(sta_bwd_dq_kernel<D, QW, G, DMA, SOLO>, dim3(plan.deal.total), dim3(QW * G * 64), a.stream, a.q, a.k, a.v, a.o, a.d_o, a.lse,
@@ -1225,7 +1228,8 @@ hipError_t dispatch_dq(const BwdArgs &a)
     }
     if (P % 128 != 0 && !(sta::dma_aligned(a.k) && sta::dma_aligned(a.v))) return launch_dq<D, 1, 1, false>(a);
     if (eight_groups(waves, units)) return launch_dq<D, 1, 8>(a);
-    if (four_groups_of_one<D>(a, waves, units)) return launch_dq<D, 1, 4>(a);
+    // (four groups: two buffers for each operand where every workgroup is resident with them, see the kernel)
+    if (four_groups_of_one<D>(a, waves, units)) return waves <= (D == 64 ? 2 : 1) * cus ? launch_dq<D, 1, 4, true, false>(a) : launch_dq<D, 1, 4>(a);
     if (P % 96 == 0 && P % 128 != 0) return two ? launch_dq<D, 3, 2>(a) : launch_dq<D, 3, 1>(a);
     // One buffer from the first round that two leave short on: training steps, two buffers, one, waves and units: head dimension 64 (2048, 25) 167,
     // 164, (2560, 45) 274, 254, (3200, 90) 841, 790, (8192, 9) 264, 256; below that the wave alone waits longer for a buffer it

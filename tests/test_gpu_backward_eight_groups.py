@@ -28,7 +28,7 @@ FOUR = [
 def test_eight_groups_for_long_walks_where_every_cu_has_at_most_one_workgroup(D):
     for name, grid, tile, B, H, windows in EIGHT:
         lines = launches(B, H, D, grid, tile, windows, gradients=True)
-        assert [line.split(" items")[0] for line in lines] == ["dq<%d,1,8,1>" % D, "dkv<%d,1,8,1,1>" % D], (name, lines)
+        assert [line.split(" items")[0] for line in lines] == ["dq_one_buffer<%d,1,8,1>" % D, "dkv<%d,1,8,1,1>" % D], (name, lines)
         # every workgroup has a CU of its own, and no order of the rows evens anything out
         assert lines[1].endswith(", head after head"), (name, lines)
     for name, grid, tile, B, H, windows in FOUR:

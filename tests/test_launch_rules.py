@@ -247,7 +247,7 @@ BACKWARD = {
     ("p64-two-waves", 128): "dq<128,2,1,1> dkv<128,2,1,1,1>", ("p192-two-groups", 64): "dq<64,3,1,1> dkv<64,2,2,1,1>",
     ("p192-two-groups", 128): "dq<128,3,1,1> dkv<128,2,2,1,1>", ("p96-many", 64): "dq<64,3,1,1> dkv<64,3,1,1,1>",
     ("p96-many", 128): "dq<128,3,1,1> dkv_pair<3,2,1>", ("p96-some", 64): "dq<64,3,1,1> dkv<64,1,4,1,1>",
-    ("p96-some", 128): "dq<128,3,1,1> dkv_pair<3,2,1>", ("p96-few", 128): "dq<128,1,4,1> dkv<128,1,4,1,1>",
+    ("p96-some", 128): "dq<128,3,1,1> dkv_pair<3,2,1>", ("p96-few", 128): "dq_one_buffer<128,1,4,1> dkv<128,1,4,1,1>",
     ("p192-three-two", 128): "dq<128,3,2,1> dkv<128,2,2,1,1>",
     ("p32-some", 64): "dq<64,1,1,1> dkv<64,1,2,1,1>", ("p32-some", 128): "dq<128,1,1,1> dkv_pair<1,1,1>",
     ("p32-many", 64): "dq<64,1,1,1> dkv<64,1,1,1,1>", ("p32-many", 128): "dq_one_buffer<128,1,1,1> dkv_pair<1,1,1>",
@@ -255,7 +255,7 @@ BACKWARD = {
 # ... and the shapes that other GPU tests run: test_gpu_forward_groups.py (two units per stage), test_gpu_forward_large.py,
 # test_gpu_backward_groups.py (three waves in two groups), test_gpu_backward_eight_groups.py, test_gpu_backward_single_waves.py
 ELSEWHERE = {"group<64,4,1,0,2>", "x32<4>", "x32<12>", "solo<64,2,8,1>", "solo<128,2,8,1>", "dq<64,3,2,1>", "dq<64,1,4,1>", "dq<128,1,4,1>",
-             "dq<64,1,8,1>", "dq<128,1,8,1>", "dkv<64,1,8,1,1>", "dkv<128,1,8,1,1>", "dq_one_buffer<64,1,1,1>"}
+             "dq_one_buffer<64,1,4,1>", "dq_one_buffer<64,1,8,1>", "dq_one_buffer<128,1,8,1>", "dkv<64,1,8,1,1>", "dkv<128,1,8,1,1>", "dq_one_buffer<64,1,1,1>"}
 
 
 def kernels(lines):
