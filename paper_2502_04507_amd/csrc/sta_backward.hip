@@ -254,7 +254,7 @@ constexpr int max_of(int a, int b) { return a > b ? a : b; }
 // 220 drawn launches, one buffer's time over that of two: up to 256 waves of columns, walks below 40, 128 1.015, 64 1.011; 64 up to 512 waves
 // 1.012; beyond those 128 0.91, 64 0.96.
 // Without groups (tiles of 32 tokens' multiples) a CU holds eight such waves at head dimension 128 and sixteen at 64, with two buffers four and
-// twelve.
+// nine: `one_buffer_alone` says which take it.
 // The row statistics are formed here, from the dO fragments the wave holds anyway and the same fragments of O, and written
 // for the dK/dV kernel (a kernel of their own for them read dO once more: 6.8 us of a 345 us training step at 16,384 tokens
 // x 8 heads of dimension 64, 0.23 ms of 53 ms at 115,200 x 24 of 128).
@@ -1198,6 +1198,28 @@ bool four_groups_of_one(const BwdArgs &a, uint64_t waves, uint32_t units)
     return waves <= 2 * cus && units >= (one ? 15 : 64);
 }
 
+// One wave alone (tiles of 32 tokens' multiples): one buffer for each operand where two would make a long walk wait for a place.  A CU holds four
+// waves with two buffers at head dimension 128, eight with one; at 64 nine (64 waves a head of 35 sub-blocks: 2304 110, 2368 122 us, with one
+// 109, 112) and sixteen.  Where all are resident with two, a wave waits longer for the one buffer that it has just emptied (gradients alone, two
+// buffers, one: 128 1.086 of the time just below 1024 waves, 0.857 just beyond; 64 1.005, 0.910), and where walks differ that is so as
+// long as the long ones are, over half the longest: 128, 1260 waves of 105 and 7 sub-blocks 214, 237, 1728 of 63 and 3 150, 164.  Many short walks take
+// the places as well: from 1.25 times the even share on.  Nor, at 64, where one begins its second round and two has just filled
+// two (4097 to 4608 waves: up to 1.027).  1082 drawn launches, time over that of two buffers everywhere: equal walks 0.977 (64) and 0.924 (128),
+// at most 1.002, different ones 0.988 and 0.963, 8 of 353 beyond 1.01 and 1.032 at most; by the number of waves alone, from 2048 and 1025 on, 66 of
+// 353 and 1.123.
+template <int D>
+bool one_buffer_alone(const BwdArgs &a, uint64_t waves, uint32_t units)
+{
+    const uint64_t cus = sta::compute_units(), resident = (D == 64 ? 9 : 4) * cus, per_head = (uint64_t)a.B * (a.p.N / 32);
+    uint64_t all = 0, long_walks = 0;
+    for (uint32_t r = 0; r < a.p.heads; ++r) {
+        all += per_head * walk_of_rank(a, r);
+        if (2 * walk_of_rank(a, r) > units) long_walks += per_head;
+    }
+    if (D == 64 && long_walks > 16 * cus && waves <= 18 * cus) return false;
+    return long_walks > resident || 4 * all > 5 * resident * units;
+}
+
 template <int D>
 hipError_t dispatch_dq(const BwdArgs &a)
 {
@@ -1239,11 +1261,7 @@ hipError_t dispatch_dq(const BwdArgs &a)
     // (four groups: two buffers for each operand where every workgroup is resident with them, see the kernel)
     if (four_groups_of_one<D>(a, waves, units)) return waves <= (D == 64 ? 2 : 1) * cus ? launch_dq<D, 1, 4, true, false>(a) : launch_dq<D, 1, 4>(a);
     if (P % 96 == 0 && P % 128 != 0) return two ? launch_dq<D, 3, 2>(a) : launch_dq<D, 3, 1>(a);
-    // One buffer from the first round that two leave short on: training steps, two buffers, one, waves and units: head dimension 64 (2048, 25) 167,
-    // 164, (2560, 45) 274, 254, (3200, 90) 841, 790, (8192, 9) 264, 256; below that the wave alone waits longer for a buffer it
-    // has just emptied, (1280, 25) 126, 128, (1280, 45) 161, 165; 128 (1280, 45) 265, 239, (1280, 25) 200, 183, (1536, 9) 127, 120, (6400, 90)
-    // 2769, 2670; but (800, 45) 193, 197, (640, 25) 136, 138, (1024, 9) 90.3, 90.6.
-    if (P % 64 != 0) return waves >= (D == 64 ? 8 * cus : 4 * cus + 1) ? launch_dq<D, 1, 1, true, true>(a) : launch_dq<D, 1, 1>(a);
+    if (P % 64 != 0) return one_buffer_alone<D>(a, waves, units) ? launch_dq<D, 1, 1, true, true>(a) : launch_dq<D, 1, 1>(a);
     if (two) return launch_dq<D, 2, 2>(a);
     return P % 128 == 0 ? launch_dq<D, 4, 1>(a) : launch_dq<D, 2, 1>(a);
 }

@@ -65,10 +65,18 @@ def test_single_waves_where_walks_are_long():
         assert launches(1, H, D, grid, tile, windows, gradients=True)[0].startswith(want + " "), (D, grid, H, windows)
 
 
-# dQ, one wave alone, one buffer for each operand: beyond a round of those with two
+# dQ, one wave alone, one buffer for each operand: where the long walks are more than are resident with two, or all walks 1.25 times an even share
 ALONE = [
-    ("p32-2048", 64, (1, 32, 64), (1, 4, 8), 2, 16, [(1, 3, 5), (1, 1, 1)]),             # 2048 waves; 15 sub-blocks and 1
-    ("p160-1120", 128, (5, 16, 28), (5, 8, 4), 4, 4, [(1, 1, 5), (1, 2, 1)]),            # 1120; 25 and 10
+    ("p32-2368", 64, (1, 32, 64), (1, 4, 8), 1, 37, [(1, 3, 5)]),                        # 2368 waves, 2304 resident; 15 sub-blocks
+    ("p32-4672", 64, (1, 32, 64), (1, 4, 8), 1, 73, [(1, 3, 5), (1, 1, 1)]),             # 2368 of 15 and 2304 of 1
+    ("p160-1050", 128, (5, 16, 28), (5, 8, 4), 1, 15, [(1, 1, 5)]),                      # 1050, 1024 resident; 25
+    ("p160-2310", 128, (5, 16, 28), (5, 8, 4), 1, 33, [(1, 1, 5), (1, 2, 1), (1, 2, 1), (1, 2, 1)]),     # 630 of 25 and 1680 of 10
+]
+# ... and with two
+TWO_BUFFERS = [
+    (64, (1, 32, 64), (1, 4, 8), 64 + 1, [(1, 3, 5)]),                                   # 4160: the second round with one, and the end of two with two
+    (128, (7, 72, 20), (7, 8, 4), 4, [(1, 2, 5), (1, 1, 1)]),                            # 1260, half of them of 7 sub-blocks beside 105
+    (128, (1, 36, 64), (1, 4, 8), 24, [(1, 9, 7), (1, 3, 1)]),                           # 1728 of 63 and 3
 ]
 
 
@@ -76,6 +84,8 @@ def test_one_buffer_where_a_wave_alone_fills_the_chip():
     for name, D, grid, tile, B, H, windows in ALONE:
         assert launches(B, H, D, grid, tile, windows, gradients=True)[0].startswith("dq_one_buffer<%d,1,1,1> items" % D), name
         assert launches(B, H - 1, D, grid, tile, windows, gradients=True)[0].startswith("dq<%d,1,1,1> items" % D), name
+    for D, grid, tile, H, windows in TWO_BUFFERS:
+        assert launches(1, H, D, grid, tile, windows, gradients=True)[0].startswith("dq<%d,1,1,1> items" % D), (D, grid, H)
 
 
 @pytest.mark.gpu
