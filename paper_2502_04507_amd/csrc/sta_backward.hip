@@ -1151,7 +1151,7 @@ hipError_t launch_dkv_pairs(const BwdArgs &a)
 // 140, three (384) 150, 157; 4x12x24 in 96-token tiles, one head (36) of 64 39.5, 31.2, of 128 59.6, 47.3; twelve (432) 40.6, 35.4
 // and 61.3, 61.9.
 //
-// Eight groups of one wave in both kernels where no CU gets a second workgroup and the walk has 40 sub-blocks or more: two waves a
+// Eight groups of one wave in both kernels where no CU gets a second workgroup and the walk has 40 sub-blocks or more, 44 at head dimension 128: two waves a
 // SIMD, of which one computes while the other waits, and half the steps.  Entry point (with the permutation), four against eight, dQ
 // alone, dK/dV alone and both; waves and units: head dimension 64 (216, 216) 125.1, -6.6, -13.4, -19.2 %; (108, 108) 79.3, -4.0,
 // -8.6, -12.6; (72, 48) 64.0, -2.7, -6.0, -8.9; (56, 40) 54.3, -0.6, -5.9, -6.3; (240, 45) 59.9, -1.3, -4.8, -6.3; (144, 36) 50.5,
@@ -1159,8 +1159,9 @@ hipError_t launch_dkv_pairs(const BwdArgs &a)
 // (72, 48) 92.6, -2.7, -4.4, -7.0; (56, 40) 75.7, 0.0, -3.3, -3.2; (240, 45) 83.7, -0.4, -2.6, -2.8; (144, 36) 69.0, +1.4, +0.4, +1.9;
 // (256, 18) 63.4, +3.1, -0.9, +2.3.  With a second workgroup on some CUs the sum of eight and the LDS that they hold cost more:
 // 64 (324, 108) 99.3, 0.0, +5.5, +5.5; (432, 54) 78.6, +2.0, +5.5, +7.5; 128 (288, 27) 85.7, 0.0, +8.9, +8.9 (and (384, 50), 64x64
-// images, -5.7 and -4.2 % in dK/dV, which the rule leaves out).
-bool eight_groups(uint64_t waves, uint32_t units) { return waves <= (uint64_t)sta::compute_units() && units >= 40; }
+// images, -5.7 and -4.2 % in dK/dV, which the rule leaves out).  Gradients alone, 300 drawn launches, eight groups' time over that of four (on two
+// buffers): 64, 40 to 79 sub-blocks 0.80 to 0.94, from 80 on 0.79; 128, 40 to 43 1.00, from 0.93 to 1.04, 44 to 63 0.95, at most 1.001, 64 to 79 0.91, from 80 on 0.88.
+bool eight_groups(int D, uint64_t waves, uint32_t units) { return waves <= (uint64_t)sta::compute_units() && units >= (D == 64 ? 40 : 44); }
 
 // Four groups of one wave beyond one workgroup per CU, which at head dimension 64 holds four of them (36 KB and 126 registers) and at 128
 // two (73 KB): they wait for no barrier, halve or quarter long walks, and a CU's share is one or two waves a SIMD whatever the tile.
@@ -1257,7 +1258,7 @@ hipError_t dispatch_dq(const BwdArgs &a)
         }
     }
     if (P % 128 != 0 && !(sta::dma_aligned(a.k) && sta::dma_aligned(a.v))) return launch_dq<D, 1, 1, false>(a);
-    if (eight_groups(waves, units)) return launch_dq<D, 1, 8>(a);
+    if (eight_groups(D, waves, units)) return launch_dq<D, 1, 8>(a);
     // (four groups: two buffers for each operand where every workgroup is resident with them, see the kernel)
     if (four_groups_of_one<D>(a, waves, units)) return waves <= (D == 64 ? 2 : 1) * cus ? launch_dq<D, 1, 4, true, false>(a) : launch_dq<D, 1, 4>(a);
     if (P % 96 == 0 && P % 128 != 0) return two ? launch_dq<D, 3, 2>(a) : launch_dq<D, 3, 1>(a);
@@ -1319,7 +1320,7 @@ hipError_t dispatch_dkv(const BwdArgs &a)
     if (P % 64 == 0 && P % 128 != 0 && units >= 48) solo = (D == 64 ? 8 : 3) * cus;
     if (P % 64 != 0 && P % 96 == 0) solo = (D == 64 ? 18 : 6) * cus;
     if (P % 64 != 0 && P % 96 != 0 && units >= 24) solo = 2 * cus;
-    if (eight_groups(waves, units)) return launch_dkv<D, 1, 8>(a);
+    if (eight_groups(D, waves, units)) return launch_dkv<D, 1, 8>(a);
     if (waves > solo && waves <= 4 * cus) solo = single_waves_by_walk(a, D, waves, units, solo);
     if (waves <= solo) return launch_dkv<D, 1, 4>(a);
     if (P % 64 != 0) {
