@@ -1293,18 +1293,27 @@ hipError_t dispatch_dq(const BwdArgs &a)
 //   450, 402, (768, 35) 158, 147, but (640, 40) 147, 151; up to four from 1.5 times on: 64 (840, 75) of several windows 139, 121, (900, 150)
 //   201, 188; 128 (784, 126) 449, 406; not (64, (800, 100) of equal walks 164, 174; 128 (1008, 42) 180, 189, (840, 45) 194, 197).
 // The other tiles: see solo's own lines.
+// Short walks of key tiles that are nearly even gain nothing at 128 where more than a few share a CU: multiples of 32 alone below 100 sub-blocks
+// and 1.2 times the mean (gradients alone, without and with four groups, (750, 50) 99, 106, (728, 56) 107, 112, (540, 90) 163, 166; of 350 drawn
+// launches beyond 512 waves 22 are such, 1.03 of the time in the mean, the others 0.88), multiples of 128 below 84 and 1.5 times beyond 352
+// waves ((512, 48) 67, 70, (432, 48) 58, 60; of 250 drawn 14 are such, 0.95 to 1.04, the others 0.91).
+// Drawn launches with and without this rule, gradients alone: 64 multiples of 32 alone 0.84 (46, 0.96 at most), of 128 0.89 (79, 0.96).
 uint64_t single_waves_by_walk(const BwdArgs &a, int D, uint64_t waves, uint32_t units, uint64_t solo)
 {
     const uint64_t cus = sta::compute_units();
     const uint32_t P = a.p.P;
     const bool whole = P % 128 == 0, one = P % 64 != 0 && P % 96 != 0;
-    if (one && waves <= 3 * cus) return units >= (D == 64 ? 32 : 48) ? 3 * cus : solo;
+    const bool few = one && waves <= 3 * cus;
+    if (few && D == 64) return units >= 32 ? 3 * cus : solo;
     if (whole && D == 64) return units >= 48 ? 3 * cus : solo;
-    if (!(one ? units >= (D == 64 ? 40 : 60) : whole && waves <= 2 * cus && units >= 48)) return solo;
+    if (!(few ? units >= 48 : one ? units >= (D == 64 ? 40 : 60) : whole && waves <= 2 * cus && units >= 48)) return solo;
+    const uint64_t longest = longest_key_walk(a);
     uint64_t all = 0;
     for (uint32_t r = 0; r < a.p.heads; ++r) all += walk_of_rank(a, r);
-    if (10 * (uint64_t)longest_key_walk(a) * a.p.heads < (one ? 15 : 13) * all) return solo;
-    return (one ? 4 : 2) * cus;
+    auto uneven = [&](int tenths) { return 10 * longest * a.p.heads >= tenths * all; };
+    if (few) return longest >= 100 || uneven(12) ? 3 * cus : solo;
+    if (whole) return uneven(longest < 84 && 8 * waves > 11 * cus ? 15 : 13) ? 2 * cus : solo;
+    return uneven(15) ? 4 * cus : solo;
 }
 
 template <int D>

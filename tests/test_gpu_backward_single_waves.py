@@ -43,6 +43,8 @@ OTHER_KEYS = [
     (128, (8, 48, 48), (4, 8, 8), 1, [(1, 4, 3)], "dkv<128,2,2,1,1>"),                   # 576 of 120
     (128, (5, 64, 8), (5, 8, 4), 8, [(1, 8, 1)], "dkv_pair<1,1,1>"),                     # 640 of 40
     (64, (10, 16, 20), (5, 8, 4), 8, [(2, 2, 5)], "dkv<64,1,2,1,1>"),                    # 800 of 100, all equal
+    (128, (5, 40, 8), (5, 8, 4), 14, [(1, 5, 2)], "dkv_pair<1,1,1>"),                    # 700 of 50, all equal
+    (128, (4, 16, 64), (2, 8, 8), 4, [(1, 4, 3)], "dkv<128,2,2,1,1>"),                   # 512 of 48, up to 64
 ]
 
 
