@@ -1146,7 +1146,7 @@ hipError_t launch_dkv_pairs(const BwdArgs &a)
 // up to the 16 that a CU holds (entry point, waves and units: (1664, 50) 104, 98, (2048, 50) 117, 110, (2000, 90) 199, 184; the other tiles,
 // of four and three waves a group, -1 to +1 %).  Four groups of one wave, without barriers, up to one such workgroup per CU
 // (two on 96-token tiles at head dimension 64), and up to four where walks are long (below); entry point, two groups of two or three waves against these,
-// which then still had two buffers for each operand: 12x24x24 in
+// on two buffers for each operand: 12x24x24 in
 // 384-token tiles, one head (216 waves) of 64 100, 87, of 128 151, 131, two (432) 107, 110; 64x64 image, 5x5, one head (128) of 128 149,
 // 140, three (384) 150, 157; 4x12x24 in 96-token tiles, one head (36) of 64 39.5, 31.2, of 128 59.6, 47.3; twelve (432) 40.6, 35.4
 // and 61.3, 61.9.
@@ -1166,7 +1166,7 @@ bool eight_groups(int D, uint64_t waves, uint32_t units) { return waves <= (uint
 // Four groups of one wave beyond one workgroup per CU, which at head dimension 64 holds four of them (36 KB and 126 registers) and at 128
 // two (73 KB): they wait for no barrier, halve or quarter long walks, and a CU's share is one or two waves a SIMD whatever the tile.
 // Entry point (with the permutation and dK/dV), the shapes by barriers against these, waves and units:
-// - head dimension 64: 384-token tiles (432, 108) 102.5, 98.0, (648, 108) 147, 141, (432, 216) 164, 155, (600, 36) 82.8, 81.9, but (864, 108)
+// - head dimension 64 (up to two workgroups a CU on two buffers since, 0.99): 384-token tiles (432, 108) 102.5, 98.0, (648, 108) 147, 141, (432, 216) 164, 155, (600, 36) 82.8, 81.9, but (864, 108)
 //   152.6, 156.3, (960, 36) 90.8, 94.3; 256 (768, 96) 138, 135; 64 (384, 50) 79.6, 77.9, (512, 128) 119, 116, (640, 128) 156, 152, but (512, 18)
 //   53.7, 56.5, (768, 50) 102.6, 103.2, (1024, 50) 112.8, 117; 320 (450, 90) 104.6, 101.4, (750, 90) 136.7, 136.9; 192 (720, 36) 88.7, 87.5,
 //   (960, 36) 100, 95, (960, 108) 201, 186, but (768, 18) 64.1, 65.0; 96 (576, 54) 95.7, 93.6, (1008, 54) 134, 130, but (576, 9) 53.2, 55.3;
@@ -1180,7 +1180,8 @@ bool eight_groups(int D, uint64_t waves, uint32_t units) { return waves <= (uint
 // and 3 (504) 89.5, 75.7; 384, two of 108 and 216 159, 141, three 201, 186; 32-token, twelve of 49 and 9 (768) 104, 93; 192, eight of 30 and 3
 // (480) 79.6, 68.4; 128, the same 134, 116; 305, 280; (512) 120, 97; 117, 102; 256-token, five of 96 and 24 (480) 162, 157; but 192, sixteen of
 // 60 and 18 (960) 161, 167.  At 128, tiles of 96 tokens' multiples, up to two workgroups a CU, walks of 20 to 31 and shorter ones, both kernels:
-// sixty drawn launches 0.87 to 0.97 of the time of two groups of three waves, 0.91 in the mean.
+// sixty drawn launches 0.87 to 0.97 of the time of two groups of three waves, 0.91 in the mean.  Drawn launches that this rule changes, gradients alone,
+// with it over without, the largest in brackets: 64 0.89 (181, 1.01), 128 0.90 (119, 0.99); tiles of 128 tokens' multiples 0.95 at either.
 template <int D>
 bool four_groups_of_one(const BwdArgs &a, uint64_t waves, uint32_t units)
 {
@@ -1206,8 +1207,8 @@ bool four_groups_of_one(const BwdArgs &a, uint64_t waves, uint32_t units)
 // long as the long ones are, over half the longest: 128, 1260 waves of 105 and 7 sub-blocks 214, 237, 1728 of 63 and 3 150, 164.  Many short walks take
 // the places as well: from 1.25 times the even share on.  Nor, at 64, where one begins its second round and two has just filled
 // two (4097 to 4608 waves: up to 1.027).  1082 drawn launches, time over that of two buffers everywhere: equal walks 0.977 (64) and 0.924 (128),
-// at most 1.002, different ones 0.988 and 0.963, 8 of 353 beyond 1.01 and 1.032 at most; by the number of waves alone, from 2048 and 1025 on, 66 of
-// 353 and 1.123.
+// at most 1.002, different ones 0.988 and 0.963, 8 of 353 beyond 1.01 and 1.032 at most (of 300 later ones three, 1050 waves of 50 to 90 sub-blocks at 128 1.058); by the number of
+// waves alone, from 2048 and 1025 on, 66 of 353 and 1.123.
 template <int D>
 bool one_buffer_alone(const BwdArgs &a, uint64_t waves, uint32_t units)
 {
