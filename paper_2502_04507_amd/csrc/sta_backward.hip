@@ -248,7 +248,7 @@ constexpr int max_of(int a, int b) { return a > b ? a : b; }
 // fused multiply-add per element is left), dS^T = 2^(c S^T) o dP^T, dQ^T += K^T dS^T; 16 matrix instructions each at head
 // dimension 128, 8 at 64.
 // SOLO (a single wave in each walk group, or alone beyond a round of them): as in the dK/dV kernel the stage belongs to one wave, which refills V as
-// soon as dP is formed and K after its last product.  One buffer for each instead of two: eight groups at head dimension 128 then take the 143 KB of
+// soon as dP is formed and K after its last product.  One buffer for each instead of two: eight groups at head dimension 128 then take the 140 KB of
 // LDS that four take with two, and a CU holds two workgroups of four groups (four at 64) where it holds one (two) with two.  The wave waits longer
 // for a buffer that it has just emptied, so four groups keep two where the launch has no workgroup that does not find its place.  Gradients alone,
 // 220 drawn launches, one buffer's time over that of two: up to 256 waves of columns, walks below 40, 128 1.015, 64 1.011; 64 up to 512 waves
@@ -1164,7 +1164,7 @@ hipError_t launch_dkv_pairs(const BwdArgs &a)
 bool eight_groups(int D, uint64_t waves, uint32_t units) { return waves <= (uint64_t)sta::compute_units() && units >= (D == 64 ? 40 : 44); }
 
 // Four groups of one wave beyond one workgroup per CU, which at head dimension 64 holds four of them (36 KB and 126 registers) and at 128
-// two (73 KB): they wait for no barrier, halve or quarter long walks, and a CU's share is one or two waves a SIMD whatever the tile.
+// two (74 KB): they wait for no barrier, halve or quarter long walks, and a CU's share is one or two waves a SIMD whatever the tile.
 // Entry point (with the permutation and dK/dV), the shapes by barriers against these, waves and units:
 // - head dimension 64 (up to two workgroups a CU on two buffers since, 0.99): 384-token tiles (432, 108) 102.5, 98.0, (648, 108) 147, 141, (432, 216) 164, 155, (600, 36) 82.8, 81.9, but (864, 108)
 //   152.6, 156.3, (960, 36) 90.8, 94.3; 256 (768, 96) 138, 135; 64 (384, 50) 79.6, 77.9, (512, 128) 119, 116, (640, 128) 156, 152, but (512, 18)
